@@ -139,6 +139,21 @@ def lib() -> ctypes.CDLL:
     return L
 
 
+_host_mod = None
+
+
+def _host():
+    """The CPython module with the binding's host-side loops (raises if it has not been built)."""
+    global _host_mod
+    if _host_mod is None:
+        try:
+            from . import _lychee_host
+        except ImportError as e:
+            raise RuntimeError(f"_lychee_host is missing: build it first (python -m paper_2603_08453_amd.build): {e}")
+        _host_mod = _lychee_host
+    return _host_mod
+
+
 # ------------------------------------------------------------------ helpers
 
 def _check(rc: int, where: str) -> None:
@@ -364,19 +379,10 @@ def lc_index_import(cfg: LcConfig, blob: bytes, index_buf, stream=None) -> Index
 
 def lc_chunk_tokens(tokens: Sequence[str], min_len: int, max_len: int) -> List[int]:
     """Chunk boundaries of a token stream given as the tokens' texts (host routine)."""
-    raw = [t.encode("utf-8") for t in tokens]
-    n = len(raw)
-    off = (ctypes.c_int64 * (n + 1))()
-    acc = 0
-    for i, r in enumerate(raw):
-        off[i] = acc
-        acc += len(r)
-    off[n] = acc
-    bounds = (ctypes.c_int32 * (n + 1))()
-    m = ctypes.c_int(0)
-    _check(lib().lc_chunk_tokens(b"".join(raw), off, n, int(min_len), int(max_len), bounds, n + 1,
-                                 ctypes.byref(m)), "lc_chunk_tokens")
-    return [int(bounds[i]) for i in range(m.value + 1)]
+    got = _host().chunk_tokens(tokens, int(min_len), int(max_len))
+    if not isinstance(got, list):
+        raise LycheeError(got, "lc_chunk_tokens")
+    return got
 
 
 # ------------------------------------------------------------------ blob (de)serialisation

@@ -6,11 +6,14 @@ import re
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblychee.so")
+HOST_LIB = os.path.join(HERE, "_lychee_host.so")      # CPython module, host code only
+HOST_SOURCE = "lc_pyhost.cpp"
 SOURCES = ["lc_api.hip", "lc_retrieve.hip", "lc_decode.hip", "lc_build.hip", "lc_chunker.hip", "lc_bench.hip"]
 
 
@@ -21,8 +24,22 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
+def build_host(verbose: bool = True) -> str:
+    """Compile the CPython module with the host compiler."""
+    cxx = next((c for c in (os.environ.get("CXX"), shutil.which("g++"), shutil.which("c++")) if c), None)
+    cmd = [cxx] if cxx else [hipcc(), "-x", "c++"]
+    cmd += ["-O3", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-cast-function-type",
+            "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+            os.path.join(CSRC, HOST_SOURCE), "-o", HOST_LIB]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return HOST_LIB
+
+
 def build(verbose: bool = True) -> str:
-    """Compile every HIP source for gfx950 and link the shared library."""
+    """Compile every HIP source for gfx950 and link the shared library; then the CPython module."""
+    build_host(verbose)
     cmd = [hipcc(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
            "-Wno-unused-command-line-argument", "-Wno-unknown-warning-option",

@@ -63,3 +63,25 @@ def test_library_chunker_matches_oracle():
     assert lc.lc_chunk_tokens(["a", "b", ".", "c", "d", "e", ",", "f", "g", "h", "i", "j"], 2, 4) == [0, 3, 7, 11, 12]
     with pytest.raises(lc.LycheeError):
         lc.lc_chunk_tokens(["a"], 3, 2)
+
+
+@pytest.mark.parametrize("n,distinct", [(1, 1), (7, 3), (4096, 37), (4096, 4096)])
+def test_library_chunker_takes_any_token_objects(n, distinct):
+    """The same str objects again and again, more objects than the level memo holds, other sequences and str subclasses."""
+    from paper_2603_08453_amd import binding as lc
+
+    class Text(str):
+        pass
+
+    r = np.random.default_rng(n + distinct)
+    ends = ["", ".", ",", " ", "\n", "\n\n", "}", "--", "---", "。", "，", "é"]
+    vocab = [f"t{i}" + ends[int(r.integers(0, len(ends)))] for i in range(distinct)]
+    toks = [vocab[i] for i in r.integers(0, distinct, size=n)]
+    want = co.chunk_tokens(toks, 4, 24)
+    assert lc.lc_chunk_tokens(toks, 4, 24) == want
+    assert lc.lc_chunk_tokens(tuple(toks), 4, 24) == want
+    assert lc.lc_chunk_tokens([Text(t) for t in toks], 4, 24) == want
+    with pytest.raises(UnicodeEncodeError):
+        lc.lc_chunk_tokens(toks + ["\ud800"], 4, 24)
+    with pytest.raises(AttributeError):
+        lc.lc_chunk_tokens(toks + [3], 4, 24)
