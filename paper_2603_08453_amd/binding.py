@@ -360,12 +360,17 @@ def lc_append(idx: Index, K, V, k_new, v_new, close_chunk: Optional[Sequence[int
     _check(rc, "lc_append")
 
 
+_new_bytes = ctypes.pythonapi.PyBytes_FromStringAndSize
+_new_bytes.argtypes = [ctypes.c_char_p, ctypes.c_ssize_t]
+_new_bytes.restype = ctypes.py_object
+
+
 def lc_index_export(idx: Index, stream=None) -> bytes:
     n = ctypes.c_size_t(0)
     _check(lib().lc_index_export(idx.handle, None, ctypes.byref(n), _stream(stream)), "lc_index_export(size)")
-    buf = ctypes.create_string_buffer(n.value)
-    _check(lib().lc_index_export(idx.handle, buf, ctypes.byref(n), _stream(stream)), "lc_index_export")
-    return buf.raw[: n.value]
+    blob = _new_bytes(None, n.value)                       # written in place before anyone else sees it
+    _check(lib().lc_index_export(idx.handle, blob, ctypes.byref(n), _stream(stream)), "lc_index_export")
+    return blob
 
 
 def lc_index_import(cfg: LcConfig, blob: bytes, index_buf, stream=None) -> Index:

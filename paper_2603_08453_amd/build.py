@@ -14,7 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblychee.so")
 HOST_LIB = os.path.join(HERE, "_lychee_host.so")      # CPython module, host code only
 HOST_SOURCE = "lc_pyhost.cpp"
-SOURCES = ["lc_api.hip", "lc_retrieve.hip", "lc_decode.hip", "lc_build.hip", "lc_chunker.hip", "lc_bench.hip"]
+SOURCES = ["lc_api.hip", "lc_retrieve.hip", "lc_decode.hip", "lc_build.hip", "lc_blob.hip", "lc_chunker.hip", "lc_bench.hip"]
 
 
 def hipcc() -> str:

@@ -6,6 +6,7 @@
 #include <new>
 #include <string>
 
+#include "lc_blob.h"
 #include "lc_internal.h"
 
 namespace {
@@ -678,6 +679,82 @@ static size_t blob_size(const lc_index* idx) {
     return n;
 }
 
+namespace {
+// Pinned windows through which blobs travel, and the sequence table of the call that uses them: one set
+// per device, kept for the life of the process, used by one call at a time (LC_BLOB_SLOTS windows of
+// LC_BLOB_WINDOW words, 4 MiB in all; the table grows to the largest batch seen).
+constexpr int LC_BLOB_SLOTS = 4;
+constexpr unsigned LC_BLOB_WINDOW = 256 * 1024;
+struct BlobStage {
+    std::mutex mutex;
+    uint32_t* window = nullptr;
+    long long* table = nullptr;
+    size_t table_rows = 0;
+    hipEvent_t done[LC_BLOB_SLOTS] = {};
+};
+BlobStage g_blob_stage[LC_STAGE_DEVICES];
+
+// The current device's windows, with a table of `rows` entries (the stage's lock must be held).
+int blob_stage_ready(BlobStage* st, size_t rows) {
+    if (!st->window) {
+        void* p = nullptr;
+        LC_HIP_CHECK(hipHostMalloc(&p, (size_t)LC_BLOB_SLOTS * LC_BLOB_WINDOW * 4, hipHostMallocDefault));
+        st->window = static_cast<uint32_t*>(p);
+    }
+    for (hipEvent_t& e : st->done)
+        if (!e) LC_HIP_CHECK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    if (st->table_rows < rows) {
+        if (st->table) LC_HIP_CHECK(hipHostFree(st->table));
+        st->table = nullptr;
+        st->table_rows = 0;
+        void* p = nullptr;
+        LC_HIP_CHECK(hipHostMalloc(&p, (rows + 1024) * sizeof(long long), hipHostMallocDefault));
+        st->table = static_cast<long long*>(p);
+        st->table_rows = rows + 1024;
+    }
+    return LC_OK;
+}
+
+int blob_device(BlobStage** out) {
+    int dev = 0;
+    LC_HIP_CHECK(hipGetDevice(&dev));
+    if (dev < 0 || dev >= LC_STAGE_DEVICES) return LC_ERR_INVALID_ARG;
+    *out = &g_blob_stage[dev];
+    return LC_OK;
+}
+
+// Header and word map of the index's blob; fills the sequence table.
+void blob_map(const lc_index* idx, LcBlobMap* m, long long* table) {
+    memset(m, 0, sizeof(*m));
+    const int32_t hdr[9] = {kMagic, 1, idx->B, idx->H_kv, idx->d, idx->cfg.levels, idx->cfg.fanout, idx->cfg.geometry,
+                            idx->cfg.center_dtype};
+    memcpy(m->hdr, hdr, sizeof(hdr));
+    for (int l = 1; l < LC_MAX_LEVELS; ++l) m->hdr[8 + l] = idx->cfg.fanouts[l];
+    const int L = idx->cfg.levels, R = lc_blob_row(L);
+    unsigned long long at = 16;
+    for (int b = 0; b < idx->B; ++b) {
+        long long* row = table + (size_t)b * R;
+        row[0] = (long long)at;
+        row[2] = idx->T[b];
+        for (int l = 0; l < L; ++l) row[3 + l] = idx->N[(size_t)b * LC_MAX_LEVELS + l];
+        at += (unsigned long long)(L + 1) + (unsigned long long)idx->M[b] + 1;
+    }
+    m->nodes = at;
+    for (int b = 0; b < idx->B; ++b) {
+        long long* row = table + (size_t)b * R;
+        row[1] = (long long)at;
+        for (int l = 0; l < L; ++l)
+            at += (unsigned long long)idx->H_kv * (unsigned long long)row[3 + l] * (unsigned long long)(idx->d + 4);
+    }
+    m->total = at;
+}
+
+unsigned blob_window_words(const LcBlobMap& m, unsigned long long k) {
+    const unsigned long long left = m.total - k * LC_BLOB_WINDOW;
+    return left < LC_BLOB_WINDOW ? (unsigned)left : LC_BLOB_WINDOW;
+}
+}  // namespace
+
 int lc_index_export(const lc_index* idx, void* blob, size_t* bytes, void* stream) {
     if (!idx || !bytes) return LC_ERR_INVALID_ARG;
     const size_t need = blob_size(idx);
@@ -685,52 +762,61 @@ int lc_index_export(const lc_index* idx, void* blob, size_t* bytes, void* stream
     if (*bytes < need) { *bytes = need; return LC_ERR_WORKSPACE_TOO_SMALL; }
     *bytes = need;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    LC_HIP_CHECK(hipStreamSynchronize(s));
-    char* p = static_cast<char*>(blob);
-    int32_t hdr[16] = {kMagic, 1, idx->B, idx->H_kv, idx->d, idx->cfg.levels, idx->cfg.fanout, idx->cfg.geometry,
-                       idx->cfg.center_dtype};
-    for (int l = 1; l < LC_MAX_LEVELS; ++l) hdr[8 + l] = idx->cfg.fanouts[l];
-    memcpy(p, hdr, sizeof(hdr));
-    p += sizeof(hdr);
-    const int L = idx->cfg.levels;
-    const LcDev& D = idx->dev;
-    for (int b = 0; b < idx->B; ++b) {
-        int32_t rec[2 + LC_MAX_LEVELS];
-        rec[0] = idx->T[b];
-        rec[1] = idx->M[b];
-        for (int l = 1; l < L; ++l) rec[1 + l] = idx->N[(size_t)b * LC_MAX_LEVELS + l];
-        memcpy(p, rec, (size_t)(2 + (L - 1)) * 4);
-        p += (size_t)(2 + (L - 1)) * 4;
-        const size_t nb = ((size_t)idx->M[b] + 1) * 4;
-        LC_HIP_CHECK(hipMemcpy(p, D.bounds + (size_t)b * (D.cap[0] + 1), nb, hipMemcpyDeviceToHost));
-        p += nb;
+    BlobStage* st = nullptr;
+    int rc = blob_device(&st);
+    if (rc) return rc;
+    std::lock_guard<std::mutex> lock(st->mutex);
+    rc = blob_stage_ready(st, (size_t)idx->B * lc_blob_row(idx->cfg.levels));
+    if (rc) return rc;
+    LcBlobMap m;
+    blob_map(idx, &m, st->table);
+    // windows in flight ahead of the one being copied out
+    const unsigned long long n_win = (m.total + LC_BLOB_WINDOW - 1) / LC_BLOB_WINDOW;
+    auto start = [&](unsigned long long k) -> int {
+        const int slot = (int)(k % LC_BLOB_SLOTS);
+        const int r = lc_launch_blob_export(idx->dev, m, st->table, k * LC_BLOB_WINDOW, blob_window_words(m, k),
+                                            st->window + (size_t)slot * LC_BLOB_WINDOW, s);
+        if (r) return r;
+        LC_HIP_CHECK(hipEventRecord(st->done[slot], s));
+        return LC_OK;
+    };
+    for (unsigned long long k = 0; k < n_win && k < LC_BLOB_SLOTS && rc == LC_OK; ++k) rc = start(k);
+    for (unsigned long long k = 0; k < n_win && rc == LC_OK; ++k) {
+        const int slot = (int)(k % LC_BLOB_SLOTS);
+        LC_HIP_CHECK(hipEventSynchronize(st->done[slot]));
+        memcpy(static_cast<char*>(blob) + (size_t)k * LC_BLOB_WINDOW * 4, st->window + (size_t)slot * LC_BLOB_WINDOW,
+               (size_t)blob_window_words(m, k) * 4);
+        if (k + LC_BLOB_SLOTS < n_win) rc = start(k + LC_BLOB_SLOTS);
     }
-    for (int b = 0; b < idx->B; ++b)
-        for (int h = 0; h < idx->H_kv; ++h)
-            for (int l = 0; l < L; ++l) {
-                const size_t nl = idx->N[(size_t)b * LC_MAX_LEVELS + l];
-                const size_t base = ((size_t)b * idx->H_kv + h) * D.cap[l];
-                if (nl == 0) continue;
-                if (l == 0 && D.c0_bf16) {
-                    // the blob always carries float32 centers: widen the stored bfloat16 values
-                    std::vector<uint16_t> half(nl * idx->d);
-                    LC_HIP_CHECK(hipMemcpy(half.data(), reinterpret_cast<const uint16_t*>(D.center[0]) + base * idx->d,
-                                           nl * idx->d * 2, hipMemcpyDeviceToHost));
-                    for (size_t i = 0; i < half.size(); ++i) {
-                        const uint32_t w = (uint32_t)half[i] << 16;
-                        memcpy(p + 4 * i, &w, 4);
-                    }
-                } else {
-                    LC_HIP_CHECK(hipMemcpy(p, D.center[l] + base * idx->d, nl * idx->d * 4, hipMemcpyDeviceToHost));
-                }
-                p += nl * idx->d * 4;
-                LC_HIP_CHECK(hipMemcpy(p, D.radius[l] + base, nl * 4, hipMemcpyDeviceToHost)); p += nl * 4;
-                LC_HIP_CHECK(hipMemcpy(p, D.parent[l] + base, nl * 4, hipMemcpyDeviceToHost)); p += nl * 4;
-                LC_HIP_CHECK(hipMemcpy(p, D.ntok[l] + base, nl * 4, hipMemcpyDeviceToHost)); p += nl * 4;
-                LC_HIP_CHECK(hipMemcpy(p, D.nchunk[l] + base, nl * 4, hipMemcpyDeviceToHost)); p += nl * 4;
-            }
-    return LC_OK;
+    LC_HIP_CHECK(hipStreamSynchronize(s));
+    return rc;
 }
+
+namespace {
+// Node records of a validated blob -> index, window by window; returns when the stream has taken them in.
+int import_nodes(const lc_index* idx, const void* blob, hipStream_t s) {
+    BlobStage* st = nullptr;
+    int rc = blob_device(&st);
+    if (rc) return rc;
+    std::lock_guard<std::mutex> lock(st->mutex);
+    rc = blob_stage_ready(st, (size_t)idx->B * lc_blob_row(idx->cfg.levels));
+    if (rc) return rc;
+    LcBlobMap m;
+    blob_map(idx, &m, st->table);
+    const unsigned long long n_win = (m.total + LC_BLOB_WINDOW - 1) / LC_BLOB_WINDOW;
+    for (unsigned long long k = 0; k < n_win && rc == LC_OK; ++k) {
+        const int slot = (int)(k % LC_BLOB_SLOTS);
+        uint32_t* const w = st->window + (size_t)slot * LC_BLOB_WINDOW;
+        const unsigned n = blob_window_words(m, k);
+        LC_HIP_CHECK(hipEventSynchronize(st->done[slot]));      // (an event never recorded is complete)
+        memcpy(w, static_cast<const char*>(blob) + (size_t)k * LC_BLOB_WINDOW * 4, (size_t)n * 4);
+        rc = lc_launch_blob_import(idx->dev, m, st->table, k * LC_BLOB_WINDOW, n, w, s);
+        if (rc == LC_OK) LC_HIP_CHECK(hipEventRecord(st->done[slot], s));
+    }
+    LC_HIP_CHECK(hipStreamSynchronize(s));
+    return rc;
+}
+}  // namespace
 
 int lc_index_import(lc_index** out, const lc_config* cfg, const void* blob, size_t blob_bytes, void* index_buf,
                     size_t index_bytes, void* stream) {
@@ -808,44 +894,9 @@ int lc_index_import(lc_index** out, const lc_config* cfg, const void* blob, size
                 }
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // staged through the chunk centers' memory, which the copies below overwrite once the stream has drained
+    // staged through the chunk centers' memory, which the kernels below overwrite in stream order
     if (rc == LC_OK) rc = upload_state(h, bounds_concat.data(), h->dev.center[0], s);
-    if (rc == LC_OK && hipStreamSynchronize(s) != hipSuccess) rc = LC_ERR_HIP;
-    if (rc == LC_OK) {
-        const LcDev& D = h->dev;
-        for (int b = 0; b < B && rc == LC_OK; ++b)
-            for (int hh = 0; hh < H && rc == LC_OK; ++hh)
-                for (int l = 0; l < L && rc == LC_OK; ++l) {
-                    const size_t nl = h->N[(size_t)b * LC_MAX_LEVELS + l];
-                    if (nl == 0) continue;
-                    const size_t base = ((size_t)b * H + hh) * D.cap[l];
-                    hipError_t e;
-                    if (l == 0 && D.c0_bf16) {
-                        // values of a bfloat16 index are bfloat16-representable; anything else is rounded to nearest even
-                        std::vector<uint16_t> half(nl * d);
-                        for (size_t i = 0; i < half.size(); ++i) {
-                            uint32_t w;
-                            memcpy(&w, p + 4 * i, 4);
-                            half[i] = (uint16_t)((w + 0x7fffu + ((w >> 16) & 1u)) >> 16);
-                        }
-                        e = hipMemcpy(reinterpret_cast<uint16_t*>(D.center[0]) + base * d, half.data(), nl * d * 2,
-                                      hipMemcpyHostToDevice);
-                    } else {
-                        e = hipMemcpy(D.center[l] + base * d, p, nl * d * 4, hipMemcpyHostToDevice);
-                    }
-                    p += nl * d * 4;
-                    if (e == hipSuccess) e = hipMemcpy(D.radius[l] + base, p, nl * 4, hipMemcpyHostToDevice);
-                    if (e == hipSuccess && l >= 1) e = hipMemcpy(D.rbuild[l] + base, p, nl * 4, hipMemcpyHostToDevice);
-                    p += nl * 4;
-                    if (e == hipSuccess) e = hipMemcpy(D.parent[l] + base, p, nl * 4, hipMemcpyHostToDevice);
-                    p += nl * 4;
-                    if (e == hipSuccess) e = hipMemcpy(D.ntok[l] + base, p, nl * 4, hipMemcpyHostToDevice);
-                    p += nl * 4;
-                    if (e == hipSuccess) e = hipMemcpy(D.nchunk[l] + base, p, nl * 4, hipMemcpyHostToDevice);
-                    p += nl * 4;
-                    if (e != hipSuccess) { lc_set_hip_error(e); rc = LC_ERR_HIP; }
-                }
-    }
+    if (rc == LC_OK) rc = import_nodes(h, blob, s);
     if (rc != LC_OK) {
         delete h;
         return rc;
