@@ -113,15 +113,19 @@ size_t lc_layout_ws(const lc_config* cfg, int B, int H_q, int H, int d, int spli
     W->counts_tmp = c.take<int32_t>(BH);
     W->part_acc = c.take<float>((size_t)B * H_q * splits * d);
     W->part_ml = c.take<float>((size_t)B * H_q * splits * 2);
-    W->dirs = W->cent_a = W->cent_b = nullptr;
-    W->anc = nullptr;
+    W->dirs = W->next_pts = W->cent[0] = W->cent[1] = nullptr;
+    W->dirs16 = W->next_pts16 = W->cent16[0] = W->cent16[1] = nullptr;
     W->kflags = nullptr;
     if (with_build) {
         W->dirs = c.take<float>(BH * cap[0] * d);
-        W->cent_a = c.take<float>(BH * cap1 * d);
-        W->cent_b = c.take<float>(BH * cap1 * d);
-        W->anc = c.take<int>(BH * cap[0]);
-        W->kflags = c.take<int>(BH * LC_KM_FLAGS);
+        W->dirs16 = c.take<uint16_t>(BH * cap[0] * d);
+        W->next_pts = c.take<float>(BH * cap1 * d);
+        W->next_pts16 = c.take<uint16_t>(BH * cap1 * d);
+        for (int i = 0; i < 2; ++i) {
+            W->cent[i] = c.take<float>(BH * cap1 * d);
+            W->cent16[i] = c.take<uint16_t>(BH * cap1 * d);
+        }
+        W->kflags = c.take<int>((cfg->levels > 1 ? cfg->levels - 1 : 1) * BH * LC_KM_FLAGS);
     }
     W->total = align_up(c.off);
     return W->total;

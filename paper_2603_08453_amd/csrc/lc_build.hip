@@ -2,16 +2,17 @@
 //
 // Build, per (sequence, KV head):
 //   lc_pool_kernel    chunk representative = mean-pooled keys; covering radius; unit direction
-//   lc_kmeans_*       spherical k-means on unit directions: strided init, then
+//   lc_kmeans_*       spherical k-means on unit directions: strided start, then
 //                     `iters` x (assign by largest inner product, normalised-sum update)
-//   lc_anc_kernel     chunk -> ancestor at the new level
-//   lc_node_kernel    node center, radius over all descendant chunks' balls, counts, direction
+//   lc_center_*       node center (mean of all descendant chunks), counts, direction
+//   lc_radius_kernel  radii of every level over all descendant chunks' balls, after the last level
 // Append: lc_append_kernel writes the token's k, v; on a chunk close it pools the
 // open tail, finds the level-1 node of nearest direction and updates the path to the top.
 //
 // Every reduction runs in a fixed order, so results are reproducible run to run.
 #include "lc_device.h"
 #include "lc_internal.h"
+#include "lc_select.h"
 
 #define LC_BT 256                 // threads per block
 #define LC_BG (LC_BT / 16)        // 16-lane groups per block
@@ -135,6 +136,13 @@ __device__ __forceinline__ void lc_store8(float* p, const float (&v)[8]) {
     *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
     *reinterpret_cast<float4*>(p + 4) = make_float4(v[4], v[5], v[6], v[7]);
 }
+// the same 8 columns rounded to bfloat16 (16 bytes per lane)
+__device__ __forceinline__ void lc_store8_bf16(uint16_t* p, const float (&v)[8]) {
+    uint32_t h[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) h[i] = lc_f32_to_bf16_bits(v[i]);
+    *reinterpret_cast<uint4*>(p) = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
+}
 __device__ __forceinline__ void lc_load8(const float* p, float (&v)[8]) {
     const float4 a = *reinterpret_cast<const float4*>(p);
     const float4 b = *reinterpret_cast<const float4*>(p + 4);
@@ -174,12 +182,52 @@ __device__ __forceinline__ void lc_c0_load8(const LcDev& ix, size_t n, int sub, 
 // once (longer ones find their other rows in the L2 cache the second time).
 // No workgroup barrier: the groups' partial sums meet through wavefront shuffles.
 #define LC_POOLW_KEEP 8
+// Progress flags of the k-means of every level, [level][sequence, head][LC_KM_FLAGS]: cleared by the first kernel of a build.
+__device__ __forceinline__ int* lc_level_flags(const LcDev& ix, int* flags, int l, int bh) {
+    return flags + ((size_t)l * ix.B * ix.H + bh) * LC_KM_FLAGS;
+}
+// Centroid c of a clustering of N points into k starts at point floor(c * N / k).  The kernels that write a
+// level's points also write the rows of those that start a centroid (c <= k <= N, so a point starts at most
+// one): the cluster that point i of N starts, or -1.
+__device__ __forceinline__ int lc_seed_of(int i, int N, int k) {
+    if ((long long)N * k < (1ll << 31)) {                           // (64-bit divisions are long routines)
+        const unsigned c = ((unsigned)i * (unsigned)k + (unsigned)N - 1u) / (unsigned)N;
+        return c < (unsigned)k && c * (unsigned)N / (unsigned)k == (unsigned)i ? (int)c : -1;
+    }
+    const long long c = ((long long)i * k + N - 1) / N;
+    return c < k && (c * N) / k == i ? (int)c : -1;
+}
+// unit direction of point i (8 columns per lane): float32 and bfloat16 rows, and the centroid it starts
+struct LcPointRows {
+    float* pts;              // [B][H][cap][d]
+    uint16_t* pts16;
+    int cap;
+    float* cent;             // [B][H][cent_cap][d]; null if the level is not clustered
+    uint16_t* cent16;
+    int cent_cap;
+};
+__device__ __forceinline__ void lc_store_point(const LcPointRows& w, int bh, int i, int N, int k, int sub, const float (&u)[8]) {
+    const size_t o = ((size_t)bh * w.cap + i) * LC_D + 8 * sub;
+    lc_store8(w.pts + o, u);
+    lc_store8_bf16(w.pts16 + o, u);
+    const int c = w.cent ? lc_seed_of(i, N, k) : -1;
+    if (c >= 0) {
+        const size_t q = ((size_t)bh * w.cent_cap + c) * LC_D + 8 * sub;
+        lc_store8(w.cent + q, u);
+        lc_store8_bf16(w.cent16 + q, u);
+    }
+}
+__device__ __forceinline__ void lc_clear_flags(const LcDev& ix, int bh, int* flags) {
+    if (blockIdx.x == 0 && threadIdx.x < LC_KM_FLAGS)
+        for (int l = 0; l + 1 < ix.L; ++l) lc_level_flags(ix, flags, l, bh)[threadIdx.x] = 0;
+}
 __device__ __forceinline__ float lc_sum_groups4(float v) { v += __shfl_xor(v, 16); v += __shfl_xor(v, 32); return v; }
 __global__ void __launch_bounds__(LC_BT)
 lc_pool_kernel(LcDev ix, const uint16_t* K, long long ks_seq, long long ks_head, long long ks_tok,
-               int geometry, float* dirs) {
+               int geometry, LcPointRows out, int* flags) {
     const int h = blockIdx.y, b = blockIdx.z;
     const int bh = b * ix.H + h;
+    lc_clear_flags(ix, bh, flags);
     const int lane = threadIdx.x & 63, sub = lane & 15, g4 = lane >> 4;
     const int j = blockIdx.x * (LC_BT / 64) + (threadIdx.x >> 6);
     const int M = ix.state[bh * 4 + 1];
@@ -269,7 +317,7 @@ lc_pool_kernel(LcDev ix, const uint16_t* K, long long ks_seq, long long ks_head,
         lc_c0_store8(ix, n, sub, mu);
         float u[8];
         lc_unit_frag(mu, sub, u);
-        lc_store8(dirs + n * LC_D + 8 * sub, u);
+        lc_store_point(out, bh, j, M, ix.L > 1 ? ix.nlev[b * LC_MAX_LEVELS + 1] : 0, sub, u);
         if (sub == 0) {
             ix.radius[0][n] = radius;
             ix.parent[0][n] = -1;
@@ -281,9 +329,10 @@ lc_pool_kernel(LcDev ix, const uint16_t* K, long long ks_seq, long long ks_head,
 
 // Re-clustering starts from the chunk nodes already in the index: unit directions of their centers.
 __global__ void __launch_bounds__(LC_BT)
-lc_dirs_kernel(LcDev ix, float* dirs) {
+lc_dirs_kernel(LcDev ix, LcPointRows out, int* flags) {
     const int h = blockIdx.y, b = blockIdx.z;
     const int bh = b * ix.H + h;
+    lc_clear_flags(ix, bh, flags);
     const int M = ix.state[bh * 4 + 1];
     const int sub = threadIdx.x & 15;
     const int j = blockIdx.x * LC_BG + (threadIdx.x >> 4);
@@ -292,7 +341,7 @@ lc_dirs_kernel(LcDev ix, float* dirs) {
     float mu[8], u[8];
     lc_c0_load8(ix, n, sub, mu);
     lc_unit_frag(mu, sub, u);
-    lc_store8(dirs + n * LC_D + 8 * sub, u);
+    lc_store_point(out, bh, j, M, ix.L > 1 ? ix.nlev[b * LC_MAX_LEVELS + 1] : 0, sub, u);
     if (sub == 0) ix.parent[0][n] = -1;
 }
 
@@ -304,34 +353,17 @@ __device__ __forceinline__ int lc_level_count(const LcDev& ix, int b, int bh, in
     return l == 0 ? ix.state[bh * 4 + 1] : ix.nlev[b * LC_MAX_LEVELS + l];
 }
 
-// centroid c starts at point floor(c * N / k)
-__global__ void __launch_bounds__(LC_D)
-lc_kmeans_init_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* cent, int cent_cap, int* flags) {
-    const int c = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-    const int bh = b * ix.H + h;
-    if (c == 0 && flags && threadIdx.x < LC_KM_FLAGS) flags[bh * LC_KM_FLAGS + threadIdx.x] = 0;
-    const int N = lc_level_count(ix, b, bh, l);
-    const int k = ix.nlev[b * LC_MAX_LEVELS + l + 1];
-    if (c >= k) return;
-    float v = (threadIdx.x == 0) ? 1.f : 0.f;
-    if (N > 0) {
-        const long long src = ((long long)c * N) / k;
-        v = pts[((size_t)bh * pts_cap + src) * LC_D + threadIdx.x];
-    }
-    cent[((size_t)bh * cent_cap + c) * LC_D + threadIdx.x] = v;
-}
-
 // label(i) = argmax_c <x_i, m_c>, ties to the lower c: the one dense contraction of the build
-// (N x k x 128 per iteration), on the matrix cores in float32 (v_mfma_f32_16x16x4_f32).
-// A wavefront takes 16 points (the A operand, in registers for the whole kernel), the workgroup's
-// four wavefronts share centroid tiles staged in LDS (the B operand).  Both operands walk the 128
-// dimensions in the same permuted order -- step (t, u) pairs dimension 16 t + 4 kk + u of a point
-// with the same dimension of a centroid, kk = lane / 16 being the instruction's K index -- so that
-// each lane fetches its share of a row as eight 16-byte pieces.  The result tile leaves lane (q, j)
-// with the similarities of points 4 q + r (r < 4) to centroid j of the block; every lane keeps the
-// best of its column per point, and the 16 lanes of a row merge (value, then lower id) at the end.
-#define LC_AS_PTS 64              // points per workgroup
-#define LC_AS_TILE 64             // centroids per LDS tile
+// (N x k x 128 per iteration), on the matrix cores.  The similarities that decide are float32
+// (v_mfma_f32_16x16x4_f32); which of them are needed at all is found with bfloat16 ones at a sixteenth of
+// the cost (lc_kmeans_assign_kernel).
+// Float32 blocks: a wavefront takes 16 points (the A operand) and 16 centroids (the B operand).  Both
+// operands walk the 128 dimensions in the same permuted order -- step (t, u) pairs dimension
+// 16 t + 4 kk + u of a point with the same dimension of a centroid, kk = lane / 16 being the
+// instruction's K index -- so that each lane fetches its share of a row as eight 16-byte pieces.  The
+// result tile leaves lane (q, j) with the similarities of points 4 q + r (r < 4) to centroid j of the
+// block; every lane keeps the best of its column per point, and the 16 lanes of a row merge (value, then
+// lower id) at the end.
 #define LC_AS_ROW (LC_D + 4)      // floats per staged centroid row (the pad spreads the 16 rows of a block over the banks)
 typedef float lc_f32x4_b __attribute__((ext_vector_type(4)));
 // One 16 x 16 block of similarities: the wavefront's 16 points (xa, the A operand) against the 16
@@ -384,7 +416,7 @@ __device__ __forceinline__ void lc_assign_block2(const float4 (&xa)[8], const fl
     }
 }
 // merge the 16 columns of a row: larger similarity wins, equal ones go to the lower centroid id
-__device__ __forceinline__ int lc_assign_merge(float bv, int ba) {
+__device__ __forceinline__ void lc_assign_merge(float& bv, int& ba) {
     auto merge = [&](float ov, int oa) {
         if (ov > bv || (ov == bv && oa < ba)) { bv = ov; ba = oa; }
     };
@@ -392,174 +424,804 @@ __device__ __forceinline__ int lc_assign_merge(float bv, int ba) {
     merge(lc_dpp<0x4E>(bv), __builtin_amdgcn_update_dpp(0, ba, 0x4E, 0xF, 0xF, true));
     merge(lc_dpp<0x141>(bv), __builtin_amdgcn_update_dpp(0, ba, 0x141, 0xF, 0xF, true));
     merge(lc_dpp<0x140>(bv), __builtin_amdgcn_update_dpp(0, ba, 0x140, 0xF, 0xF, true));
-    return ba;
 }
-// `flags` (may be null): flags[bh][t] = iteration t moved a point.  An iteration that moves none is a
+// Orders a wavefront's own LDS accesses (no other wavefront is involved).
+__device__ __forceinline__ void lc_wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+// `flags` (may be null): flags[level][bh][t] = iteration t moved a point.  An iteration that moves none is a
 // fixed point -- the update would rebuild the same centroids from the same members and every later
 // iteration would repeat it -- so from then on the kernels of this (sequence, head) return at once:
 // iteration `it` assigns only if it <= 1 or iteration it - 1 moved a point, and leaves its own flag
 // at zero otherwise, which passes the verdict on.
-__global__ void __launch_bounds__(LC_BT)
-lc_kmeans_assign_kernel(LcDev ix, int l, const float* pts, int pts_cap, const float* cent, int cent_cap, int it,
-                        int* flags) {
-    __shared__ __attribute__((aligned(16))) float tile[LC_AS_TILE * LC_AS_ROW];
-    const int h = blockIdx.y, b = blockIdx.z;
-    const int bh = b * ix.H + h;
-    if (flags && it >= 2 && flags[bh * LC_KM_FLAGS + it - 1] == 0) return;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+//
+// Which centroids can be a point's nearest: similarities of the bfloat16-rounded directions
+// (v_mfma_f32_16x16x32_bf16, 16 times the float32 rate) are off by at most LC_AS_EPS, because points and
+// centroids are unit vectors and rounding moves each by at most 2^-9 of its length.  So the nearest
+// centroid is among those whose bfloat16 similarity reaches a float32 similarity the point is known to
+// have minus LC_AS_EPS, or the largest bfloat16 similarity minus twice that.  Nearly always that is one
+// centroid and it is the label; the few points with more candidates get them compared in float32, in
+// the arithmetic of lc_assign_block (16 (point, candidate) pairs to a block, the diagonal of the result);
+// a point with more than LC_AS_CAND candidates is compared with every centroid that way.  The labels are
+// those of the float32 argmax over all centroids, ties included.
+#define LC_AS_TILE 64             // centroids per LDS tile
+#define LC_AS_RES 256             // most centroids kept in LDS
+#define LC_AS_PITCH 272           // bytes per staged bfloat16 row (the pad spreads the 16 rows of a block over the banks)
+#define LC_AS_CAND 16             // candidates a point can hold (with 8, one point in 40 K had more: a tail of several times the kernel)
+#define LC_AS_PAIRS 128           // pairs a wavefront compares at a time (and no fewer than its points)
+#define LC_AS_EPS 0.0040f         // 2^-8 (both operands' rounding, Cauchy-Schwarz) and room for the float32 sums
+typedef __bf16 lc_bf16x8_b __attribute__((ext_vector_type(8)));
+#define LC_INLINE __attribute__((always_inline))       // (lambdas that hold registers by reference)
+
+// LDS of the candidates of a workgroup's points: NW wavefronts, WP points each.
+template <int WP, int NW>
+struct LcAssignSh {
+    int cand_n[NW][WP];
+    int cand[NW][WP][LC_AS_CAND];
+    int pair_c[NW][LC_AS_PAIRS];
+    float pair_v[NW][LC_AS_PAIRS];
+    uint8_t pair_p[NW][LC_AS_PAIRS];
+    uint8_t rest_p[NW * WP];
+    int n_rest;
+};
+__device__ __forceinline__ void lc_assign_take(int* n, int* list, int c) {
+    const int at = atomicAdd(n, 1);
+    if (at < LC_AS_CAND) list[at] = c;
+}
+
+// From the candidates of this workgroup's points (the first is w0, wavefront's first p0) to their labels; all
+// threads call.  P, C: float32 rows of the points and centroids; lab: the labels, old_label this lane's.
+template <int WP, int NW>
+__device__ __forceinline__ void lc_assign_finish(LcAssignSh<WP, NW>& sh, const float* P, const float* C, int N, int k, int w0,
+                                                 int p0, int* lab, int old_label, int* flag) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int j = lane & 15, kk = lane >> 4;
-    const int N = lc_level_count(ix, b, bh, l);
-    const int k = ix.nlev[b * LC_MAX_LEVELS + l + 1];
-    const int i0 = blockIdx.x * LC_AS_PTS + wave * 16;             // this wavefront's first point
-    if ((int)blockIdx.x * LC_AS_PTS >= N) return;
-    // A operand: point i0 + j, dimensions 16 t + 4 kk + (0..3)
-    float4 xa[8];
-    {
-        const float* row = pts + ((size_t)bh * pts_cap + min(i0 + j, N - 1)) * LC_D + 4 * kk;
+    // ---- points with one candidate are done; the others' candidates become pairs, 16 to a block, as many
+    // points at a time as the pair list takes
+    const int my_p = lane < WP ? lane : WP - 1;
+    const int n_c = sh.cand_n[wave][my_p];
+    const bool mine = lane < WP && p0 + lane < N;
+    bool open = mine && n_c >= 2 && n_c <= LC_AS_CAND;
+    int ba = n_c == 1 ? sh.cand[wave][my_p][0] : 0;
+    while (__ballot(open) != 0ull) {
+        const int want = open ? n_c : 0;
+        const int incl = lc_wave_scan_incl(want);
+        const int first = incl - want;
+        const bool now = open && incl <= LC_AS_PAIRS;               // (the first open point always fits)
+        const int n_pairs = (int)lc_wave_max_u((uint32_t)(now ? incl : 0));
+        if (now)
+            for (int e = 0; e < n_c; ++e) {
+                sh.pair_c[wave][first + e] = sh.cand[wave][my_p][e];
+                sh.pair_p[wave][first + e] = (uint8_t)my_p;
+            }
+        lc_wave_sync();
+        for (int q0 = 0; q0 < n_pairs; q0 += 16) {
+            const int q = min(q0 + j, n_pairs - 1);
+            const float* xr = P + (size_t)(p0 + (int)sh.pair_p[wave][q]) * LC_D + 4 * kk;
+            const float* mr = C + (size_t)sh.pair_c[wave][q] * LC_D + 4 * kk;
+            float4 x[8], m[8];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) xa[t] = *reinterpret_cast<const float4*>(row + 16 * t);
+            for (int t = 0; t < 8; ++t) {
+                x[t] = *reinterpret_cast<const float4*>(xr + 16 * t);
+                m[t] = *reinterpret_cast<const float4*>(mr + 16 * t);
+            }
+            lc_f32x4_b d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                d = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t].x, m[t].x, d, 0, 0, 0);
+                d = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t].y, m[t].y, d, 0, 0, 0);
+                d = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t].z, m[t].z, d, 0, 0, 0);
+                d = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t].w, m[t].w, d, 0, 0, 0);
+            }
+            const float diag = (j & 2) ? ((j & 1) ? d[3] : d[2]) : ((j & 1) ? d[1] : d[0]);    // row 4 kk + (j & 3) = column j
+            if (kk == (j >> 2) && q0 + j < n_pairs) sh.pair_v[wave][q0 + j] = diag;
+        }
+        lc_wave_sync();
+        if (now) {
+            float bv = LC_NEG_INF;
+            int bc = 0x7fffffff;
+            for (int e = 0; e < n_c; ++e) {
+                const float v = sh.pair_v[wave][first + e];
+                const int c = sh.pair_c[wave][first + e];
+                if (v > bv || (v == bv && c < bc)) { bv = v; bc = c; }
+            }
+            ba = bc < k ? bc : 0;
+            open = false;
+        }
+        lc_wave_sync();
     }
-    const float* cb = cent + (size_t)bh * cent_cap * LC_D;
-    float best[4];
-    int arg[4];
+    // ---- too many candidates (or none: not-a-number): every centroid in float32, 16 such points of the
+    // workgroup at a time, an equal share of the centroids per wavefront
+    if (mine && (n_c == 0 || n_c > LC_AS_CAND)) sh.rest_p[atomicAdd(&sh.n_rest, 1)] = (uint8_t)(wave * WP + lane);
+    __syncthreads();
+    const int rest = sh.n_rest;
+    for (int q0 = 0; q0 < rest; q0 += 16) {
+        const float* xr = P + (size_t)(w0 + sh.rest_p[min(q0 + j, rest - 1)]) * LC_D + 4 * kk;
+        float4 x[8];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) { best[r] = LC_NEG_INF; arg[r] = 0x7fffffff; }
-    // a tile's rows travel global memory -> registers -> LDS; the next tile's loads are issued
-    // before the current tile's products, so their latency is covered by the matrix work
-    constexpr int PF = LC_AS_TILE * (LC_D / 4) / LC_BT;             // float4 pieces per thread and tile
-    float4 pf[PF];
-    auto fetch = [&](int c0) {
-        const int nc = min(LC_AS_TILE, k - c0);
+        for (int t = 0; t < 8; ++t) x[t] = *reinterpret_cast<const float4*>(xr + 16 * t);
+        float best[4];
+        int arg[4];
 #pragma unroll
-        for (int e = 0; e < PF; ++e) {
-            const int v = tid + e * LC_BT;
-            const int c = v / (LC_D / 4), q = v % (LC_D / 4);
-            pf[e] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (c < nc) pf[e] = *reinterpret_cast<const float4*>(cb + (size_t)(c0 + c) * LC_D + 4 * q);
+        for (int r = 0; r < 4; ++r) { best[r] = LC_NEG_INF; arg[r] = 0x7fffffff; }
+        for (int c = 32 * wave; c < k; c += 32 * NW)
+            lc_assign_block2(x, C + (size_t)min(c + j, k - 1) * LC_D + 4 * kk, C + (size_t)min(c + 16 + j, k - 1) * LC_D + 4 * kk,
+                             c + j, c + 16 + j, k, best, arg);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            lc_assign_merge(best[r], arg[r]);
+            if (j == 0) { sh.pair_v[wave][4 * kk + r] = best[r]; sh.pair_c[wave][4 * kk + r] = arg[r]; }
         }
-    };
-    fetch(0);
-    for (int c0 = 0; c0 < k; c0 += LC_AS_TILE) {
-        const int nc = min(LC_AS_TILE, k - c0);
-        __syncthreads();                                            // the previous tile has been used
-#pragma unroll
-        for (int e = 0; e < PF; ++e) {
-            const int v = tid + e * LC_BT;
-            *reinterpret_cast<float4*>(tile + (v / (LC_D / 4)) * LC_AS_ROW + 4 * (v % (LC_D / 4))) = pf[e];
-        }
-        if (c0 + LC_AS_TILE < k) fetch(c0 + LC_AS_TILE);
         __syncthreads();
-        int cj = 0;
-        for (; cj + 16 < nc; cj += 32)
-            lc_assign_block2(xa, tile + (cj + j) * LC_AS_ROW + 4 * kk, tile + (cj + 16 + j) * LC_AS_ROW + 4 * kk,
-                             c0 + cj + j, c0 + cj + 16 + j, k, best, arg);
-        if (cj < nc) lc_assign_block(xa, tile + (cj + j) * LC_AS_ROW + 4 * kk, c0 + cj + j, k, best, arg);
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int ba = lc_assign_merge(best[r], arg[r]);
-        const int i = i0 + 4 * kk + r;
-        if (j == 0 && i < N) {
-            int* lab = ix.parent[l] + (size_t)bh * ix.cap[l] + i;
-            if (flags && *lab != ba) flags[bh * LC_KM_FLAGS + it] = 1;     // (every writer stores the same value)
-            *lab = ba;
+        for (int e = 0; e < 16 && q0 + e < rest; ++e) {             // the owner takes the best of the shares
+            if (mine && sh.rest_p[q0 + e] == wave * WP + lane) {
+                float bv = LC_NEG_INF;
+                int bc = 0x7fffffff;
+                for (int w = 0; w < NW; ++w)
+                    if (sh.pair_v[w][e] > bv || (sh.pair_v[w][e] == bv && sh.pair_c[w][e] < bc)) {
+                        bv = sh.pair_v[w][e];
+                        bc = sh.pair_c[w][e];
+                    }
+                ba = bc < k ? bc : 0;
+            }
         }
+        __syncthreads();
+    }
+    if (mine) {
+        if (flag && old_label != ba) *flag = 1;                     // (every writer stores the same value)
+        lab[p0 + lane] = ba;
     }
 }
 
-// Ascending list, in LDS, of the i in [base, base + LC_MEM_WIN) below n with lab[i] == c; returns its
-// length in every thread.  Every label is loaded once, coalesced, all loads in flight together;
-// positions come from wavefront ballots and one scan of the 64 (row, wavefront) counts, so the order
-// is fixed.  cnt: 2 * 64 + 1 ints of LDS; mem: LC_MEM_WIN ints.  All LC_BT threads must call.
+// Up to 16 NBLK centroids: all of them in LDS, a wavefront's similarities all in registers.  NW
+// wavefronts of 16 points each share the staged rows.  A chain of four memory round trips (counts, rows,
+// pairs, labels) with little between them; the blocks carry no branches so that their LDS reads and
+// products overlap (with one around each block a block took 500 clocks).
+// Measured, 8 heads of 2275 points x 143 centroids: 16.7 -> 8.8 us an iteration.
+template <int NBLK, int NW>
+__global__ void __launch_bounds__(64 * NW, NW / 2)
+lc_kmeans_assign_res_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16, int pts_cap, const float* cent,
+                            const uint16_t* cent16, int cent_cap, int it, int* flags_all) {
+    constexpr int PIECES = NBLK * 256 / (64 * NW);                  // 16-byte pieces of the rows per thread
+    __shared__ __attribute__((aligned(16))) unsigned char rows[16 * NBLK * LC_AS_PITCH];
+    __shared__ LcAssignSh<16, NW> sh;
+    const int h = blockIdx.y, b = blockIdx.z;
+    const int bh = b * ix.H + h;
+    int* const flags = flags_all ? lc_level_flags(ix, flags_all, l, bh) : nullptr;
+    const int N = lc_level_count(ix, b, bh, l);
+    const int k = ix.nlev[b * LC_MAX_LEVELS + l + 1];
+    if (flags && it >= 2 && flags[it - 1] == 0) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int j = lane & 15, kk = lane >> 4;
+    const int w0 = blockIdx.x * (16 * NW), p0 = w0 + wave * 16;     // first point of the workgroup, of this wavefront
+    if (w0 >= N) return;
+    const uint16_t* const C16 = cent16 + (size_t)bh * cent_cap * LC_D;
+    int* const lab = ix.parent[l] + (size_t)bh * ix.cap[l];
+
+    // every load goes out at once: A operand (point p0 + j, dimensions 32 s + 8 kk + (0..7)), the centroid
+    // rows this thread stages (rows past the last centroid repeat it), the label
+    lc_v4i xa[4], st[PIECES];
+    {
+        const uint16_t* row = pts16 + ((size_t)bh * pts_cap + min(p0 + j, N - 1)) * LC_D + 8 * kk;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) xa[s] = *reinterpret_cast<const lc_v4i*>(row + 32 * s);
+    }
+#pragma unroll
+    for (int e = 0; e < PIECES; ++e)
+        st[e] = *reinterpret_cast<const lc_v4i*>(C16 + (size_t)min(4 * NW * e + (tid >> 4), k - 1) * LC_D + 8 * (tid & 15));
+    const int old_label = lab[min(p0 + lane, N - 1)];
+    if (lane < 16) sh.cand_n[wave][lane] = 0;
+    if (tid == 0) sh.n_rest = 0;
+#pragma unroll
+    for (int e = 0; e < PIECES; ++e)
+        *reinterpret_cast<lc_v4i*>(rows + (4 * NW * e + (tid >> 4)) * LC_AS_PITCH + 16 * (tid & 15)) = st[e];
+    __syncthreads();
+
+    lc_f32x4_b d[NBLK];
+#pragma unroll
+    for (int e = 0; e < NBLK; ++e) {
+        const unsigned char* row = rows + (16 * e + j) * LC_AS_PITCH + 16 * kk;
+        d[e] = lc_f32x4_b{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+            d[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(lc_bf16x8_b, xa[s]),
+                                                           __builtin_bit_cast(lc_bf16x8_b, *reinterpret_cast<const lc_v4i*>(row + 64 * s)),
+                                                           d[e], 0, 0, 0);
+    }
+    float top[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {                                   // largest of every row, less the margin
+        top[r] = d[0][r];
+#pragma unroll
+        for (int e = 1; e < NBLK; ++e) top[r] = fmaxf(top[r], d[e][r]);
+        top[r] = fmaxf(top[r], lc_dpp<0xB1>(top[r]));
+        top[r] = fmaxf(top[r], lc_dpp<0x4E>(top[r]));
+        top[r] = fmaxf(top[r], lc_dpp<0x141>(top[r]));
+        top[r] = fmaxf(top[r], lc_dpp<0x140>(top[r])) - 2.0f * LC_AS_EPS;
+    }
+    // this lane's candidates as a bit mask: bit 4 (e mod 8) + r of word e / 8
+#pragma unroll
+    for (int w = 0; w < (NBLK + 7) / 8; ++w) {
+        unsigned hit = 0u;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (8 * w + e < NBLK) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) hit |= d[8 * w + e < NBLK ? 8 * w + e : 0][r] >= top[r] ? 1u << (4 * e + r) : 0u;
+            }
+        while (hit != 0u) {
+            const int v = __ffs((int)hit) - 1;
+            hit &= hit - 1u;
+            const int c = 16 * (8 * w + (v >> 2)) + j, p = 4 * kk + (v & 3);
+            if (c < k) lc_assign_take(&sh.cand_n[wave][p], sh.cand[wave][p], c);
+        }
+    }
+    lc_wave_sync();
+    lc_assign_finish<16, NW>(sh, pts + (size_t)bh * pts_cap * LC_D, cent + (size_t)bh * cent_cap * LC_D, N, k, w0, p0, lab,
+                             old_label, flags ? flags + it : nullptr);
+}
+
+// More centroids: tiles of LC_AS_TILE of them pass through LDS (the next tile's rows are fetched while the
+// current one is multiplied) under the 16 MA points per wavefront held in registers.  The threshold enters
+// as the matrix instruction's starting accumulator, so a candidate is a result >= 0, and a step of 32
+// centroids costs a maximum over its results and a branch that is rarely taken.  The first iteration
+// needs a sweep for the largest similarity before the one for the candidates; later ones start from the
+// similarity to the point's previous centroid (a float32 dot product).
+// Measured, 8 heads of 10.9 K points x 5461 centroids (122 GFLOP a sweep): first iteration 251 us, the second
+// 149 us; the three iterations of such a clustering took 2.7 ms in float32 and take 0.5 ms.
+template <int MA>
+__global__ void __launch_bounds__(LC_BT)
+lc_kmeans_assign_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16, int pts_cap, const float* cent,
+                        const uint16_t* cent16, int cent_cap, int it, int* flags_all) {
+    constexpr int WP = 16 * MA;                                     // points per wavefront
+    __shared__ __attribute__((aligned(16))) unsigned char tiles[2][LC_AS_TILE * LC_AS_PITCH];
+    __shared__ LcAssignSh<WP, 4> sh;
+    const int h = blockIdx.y, b = blockIdx.z;
+    const int bh = b * ix.H + h;
+    int* const flags = flags_all ? lc_level_flags(ix, flags_all, l, bh) : nullptr;
+    const int N = lc_level_count(ix, b, bh, l);
+    const int k = ix.nlev[b * LC_MAX_LEVELS + l + 1];
+    if (flags && it >= 2 && flags[it - 1] == 0) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int j = lane & 15, kk = lane >> 4;
+    const int w0 = blockIdx.x * (4 * WP), p0 = w0 + wave * WP;      // first point of the workgroup, of this wavefront
+    if (w0 >= N) return;
+    const float* const P = pts + (size_t)bh * pts_cap * LC_D;
+    const float* const C = cent + (size_t)bh * cent_cap * LC_D;
+    const uint16_t* const C16 = cent16 + (size_t)bh * cent_cap * LC_D;
+    int* const lab = ix.parent[l] + (size_t)bh * ix.cap[l];
+    const int old_label = lab[min(p0 + lane, N - 1)];
+
+    // A operand: point p0 + 16 a + j, dimensions 32 s + 8 kk + (0..7)
+    lc_v4i xa[MA][4];
+#pragma unroll
+    for (int a = 0; a < MA; ++a) {
+        const uint16_t* row = pts16 + ((size_t)bh * pts_cap + min(p0 + 16 * a + j, N - 1)) * LC_D + 8 * kk;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) xa[a][s] = *reinterpret_cast<const lc_v4i*>(row + 32 * s);
+    }
+    if (lane < WP) sh.cand_n[wave][lane] = 0;
+    if (tid == 0) sh.n_rest = 0;
+
+    lc_f32x4_b start[MA];                                           // starting accumulators of this lane's rows (4 kk + r)
+    auto load_block = [&](const unsigned char* row, lc_v4i (&m)[4]) LC_INLINE {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) m[s] = *reinterpret_cast<const lc_v4i*>(row + 64 * s);
+    };
+    auto multiply = [&](const lc_v4i (&m)[4], lc_f32x4_b (&d)[MA]) LC_INLINE {
+#pragma unroll
+        for (int a = 0; a < MA; ++a) d[a] = start[a];
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int a = 0; a < MA; ++a)
+                d[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(lc_bf16x8_b, xa[a][s]),
+                                                               __builtin_bit_cast(lc_bf16x8_b, m[s]), d[a], 0, 0, 0);
+    };
+    // n staged rows, a multiple of 32: two blocks per step, the next step's rows read before this one's
+    // products (the last step reads its own again)
+    auto sweep = [&](const unsigned char* rows, int n, auto use) LC_INLINE {
+        const unsigned char* row = rows + j * LC_AS_PITCH + 16 * kk;
+        lc_v4i m0[4], m1[4];
+        load_block(row, m0);
+        for (int c = 0; c < n; c += 32) {
+            lc_f32x4_b d0[MA], d1[MA];
+            load_block(row + (c + 16) * LC_AS_PITCH, m1);
+            multiply(m0, d0);
+            load_block(row + min(c + 32, n - 32) * LC_AS_PITCH, m0);
+            multiply(m1, d1);
+            use(c, d0, d1);
+        }
+    };
+    constexpr int PF = LC_AS_TILE * 16 / LC_BT;                     // 16-byte pieces per thread and tile
+    lc_v4i pf[PF];
+    auto fetch = [&](int c0) LC_INLINE {                                      // (rows past the last centroid repeat it)
+#pragma unroll
+        for (int e = 0; e < PF; ++e)
+            pf[e] = *reinterpret_cast<const lc_v4i*>(C16 + (size_t)min(c0 + 16 * e + (tid >> 4), k - 1) * LC_D + 8 * (tid & 15));
+    };
+    auto over_tiles = [&](auto use) LC_INLINE {                               // two tile buffers: one barrier per tile
+        int at = 0;
+        for (int c0 = 0; c0 < k; c0 += LC_AS_TILE) {
+            unsigned char* const buf = tiles[at];
+#pragma unroll
+            for (int e = 0; e < PF; ++e)
+                *reinterpret_cast<lc_v4i*>(buf + (16 * e + (tid >> 4)) * LC_AS_PITCH + 16 * (tid & 15)) = pf[e];
+            if (c0 + LC_AS_TILE < k) fetch(c0 + LC_AS_TILE);
+            lc_barrier_lds();
+            use(buf, c0, min(LC_AS_TILE, (k - c0 + 31) & ~31));
+            at ^= 1;
+        }
+    };
+    fetch(0);
+    if (it == 0) {
+        float top[MA][4];
+#pragma unroll
+        for (int a = 0; a < MA; ++a) {
+            start[a] = lc_f32x4_b{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int r = 0; r < 4; ++r) top[a][r] = LC_NEG_INF;
+        }
+        over_tiles([&](const unsigned char* buf, int, int n) LC_INLINE {
+            sweep(buf, n, [&](int, const lc_f32x4_b (&d0)[MA], const lc_f32x4_b (&d1)[MA]) LC_INLINE {
+#pragma unroll
+                for (int a = 0; a < MA; ++a)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) top[a][r] = fmaxf(top[a][r], fmaxf(d0[a][r], d1[a][r]));
+            });
+        });
+        fetch(0);
+#pragma unroll
+        for (int a = 0; a < MA; ++a)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {                           // largest of the 16 columns of every row
+                float v = top[a][r];
+                v = fmaxf(v, lc_dpp<0xB1>(v));
+                v = fmaxf(v, lc_dpp<0x4E>(v));
+                v = fmaxf(v, lc_dpp<0x141>(v));
+                v = fmaxf(v, lc_dpp<0x140>(v));
+                start[a][r] = 2.0f * LC_AS_EPS - v;
+            }
+        lc_barrier_lds();                                           // the last tile has been used
+    } else {
+        // similarity to the previous centroid, one 16-lane group per point
+        // (group kk takes points 4 MA kk + e; the accumulators want points 16 a + 4 kk + r)
+#pragma unroll 2
+        for (int e = 0; e < 4 * MA; ++e) {
+            const int i = min(p0 + 4 * MA * kk + e, N - 1);
+            const int c = max(0, min(lab[i], k - 1));
+            float x[8], m[8];
+            lc_load8(P + (size_t)i * LC_D + 8 * j, x);
+            lc_load8(C + (size_t)c * LC_D + 8 * j, m);
+            float s = 0.f;
+#pragma unroll
+            for (int t = 0; t < 8; ++t) s = fmaf(x[t], m[t], s);
+            s = lc_sum16(s);
+            if (j == 0) sh.pair_v[wave][4 * MA * kk + e] = s;
+        }
+        lc_wave_sync();
+#pragma unroll
+        for (int a = 0; a < MA; ++a)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) start[a][r] = (LC_AS_EPS + 2e-5f) - sh.pair_v[wave][16 * a + 4 * kk + r];
+        lc_wave_sync();
+    }
+    over_tiles([&](const unsigned char* buf, int c0, int n) LC_INLINE {
+        sweep(buf, n, [&](int c, const lc_f32x4_b (&d0)[MA], const lc_f32x4_b (&d1)[MA]) LC_INLINE {
+            float any = LC_NEG_INF;
+#pragma unroll
+            for (int a = 0; a < MA; ++a)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) any = fmaxf(any, fmaxf(d0[a][r], d1[a][r]));
+            if (any >= 0.f) {
+                unsigned neg = 0u;                                  // sign bits, the last result in bit 0
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+#pragma unroll
+                    for (int a = 0; a < MA; ++a)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(q ? d1[a][r] : d0[a][r]), 31);
+                unsigned hit = ~neg & (8 * MA >= 32 ? 0xffffffffu : (1u << (8 * MA & 31)) - 1u);
+                while (hit != 0u) {
+                    const int v = 8 * MA - 1 - (__ffs((int)hit) - 1);       // (q * MA + a) * 4 + r
+                    hit &= hit - 1u;
+                    const int q = v / (4 * MA), p = 16 * ((v >> 2) - q * MA) + 4 * kk + (v & 3);
+                    const int id = c0 + c + 16 * q + j;
+                    if (id < k) lc_assign_take(&sh.cand_n[wave][p], sh.cand[wave][p], id);
+                }
+            }
+        });
+    });
+    __syncthreads();
+    lc_assign_finish<WP, 4>(sh, P, C, N, k, w0, p0, lab, old_label, flags ? flags + it : nullptr);
+}
+
+// Ascending list, in LDS, of the i in [base, base + LC_MEM_WIN) below n with label c; returns its length in
+// every thread.  Every label is loaded once, coalesced, all loads in flight together (lc_load_labels, which
+// a caller of several windows issues one window ahead); positions come from wavefront ballots and one scan
+// of the 64 (row, wavefront) counts, so the order is fixed.  cnt: 2 * 64 + 1 ints of LDS; mem: LC_MEM_WIN
+// ints.  All NT threads must call.
 #define LC_MEM_WIN 4096
-__device__ __forceinline__ int lc_collect_members(const int* __restrict__ lab, int n, int base, int c, int* mem, int* cnt) {
-    constexpr int E = LC_MEM_WIN / LC_BT;
-    constexpr int W = LC_BT / 64;
+template <int NT, typename LabF>
+__device__ __forceinline__ void lc_load_labels(LabF lab, int n, int base, int (&lv)[LC_MEM_WIN / NT]) {
+#pragma unroll
+    for (int e = 0; e < LC_MEM_WIN / NT; ++e) {
+        lv[e] = -1;
+        if (base + e * NT < n) {                                    // (uniform: whole rows past the end are skipped)
+            const int i = base + e * NT + (int)threadIdx.x;
+            const int v = lab(min(i, n - 1));
+            lv[e] = i < n ? v : -1;
+        }
+    }
+}
+template <int NT>
+__device__ __forceinline__ int lc_list_members(const int (&lv)[LC_MEM_WIN / NT], int base, int c, int* mem, int* cnt) {
+    constexpr int E = LC_MEM_WIN / NT;
+    constexpr int W = NT / 64;
     static_assert(E * W == 64, "one wavefront scans the (row, wavefront) counts");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    int lv[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        const int i = base + e * LC_BT + tid;
-        lv[e] = i < n ? lab[i] : -1;
+        const unsigned long long m = __ballot(lv[e] == c);
+        if (lane == 0) cnt[e * W + wave] = __popcll(m);
     }
-    unsigned long long m[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        m[e] = __ballot(lv[e] == c);
-        if (lane == 0) cnt[e * W + wave] = __popcll(m[e]);
-    }
-    __syncthreads();
+    lc_barrier_lds();
     if (wave == 0) {
         const int v = cnt[lane];
         const int inc = lc_wave_scan_incl(v);
         cnt[64 + lane] = inc - v;
         if (lane == 63) cnt[128] = inc;
     }
-    __syncthreads();
+    lc_barrier_lds();
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        if (lv[e] == c) {
-            const unsigned long long below = m[e] & ((1ull << lane) - 1ull);
-            mem[cnt[64 + e * W + wave] + __popcll(below)] = base + e * LC_BT + tid;
-        }
+        const unsigned long long m = __ballot(lv[e] == c);
+        if (lv[e] == c) mem[cnt[64 + e * W + wave] + lc_mbcnt(m)] = base + e * NT + tid;
     }
-    __syncthreads();
+    lc_barrier_lds();
     return cnt[128];
 }
+template <int NT, typename LabF>
+__device__ __forceinline__ int lc_collect_members(LabF lab, int n, int base, int c, int* mem, int* cnt) {
+    int lv[LC_MEM_WIN / NT];
+    lc_load_labels<NT>(lab, n, base, lv);
+    return lc_list_members<NT>(lv, base, c, mem, cnt);
+}
 
-// m_c = normalise(sum of members); a cluster without members (or with a zero sum) keeps m_c.
-// One workgroup per cluster: it lists its members (above), then the 16 groups add them up in turn.
-__global__ void __launch_bounds__(LC_BT)
-lc_kmeans_update_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* cent, int cent_cap, int it,
-                        const int* flags) {
-    __shared__ float sh[LC_BG * LC_D];
-    __shared__ int mem[LC_MEM_WIN];
-    __shared__ int cnt[2 * 64 + 1];
-    const int c = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-    const int bh = b * ix.H + h;
-    if (flags && it >= 1 && flags[bh * LC_KM_FLAGS + it] == 0) return;      // no point moved: the centroids stand
-    const int sub = threadIdx.x & 15, grp = threadIdx.x >> 4;
-    const int N = lc_level_count(ix, b, bh, l);
-    const int k = ix.nlev[b * LC_MAX_LEVELS + l + 1];
-    if (c >= k) return;
-    const int* lab = ix.parent[l] + (size_t)bh * ix.cap[l];
-    float sum[8];
+// Member lists of up to LC_UB_MAX consecutive clusters at once, for levels of many small clusters: the
+// workgroup reads the labels once, drops every match into an unordered list, sorts that by cluster and,
+// inside a cluster, into the order in which the sums are taken.
+// That order: a cluster's members, ascending, are dealt to 16 partial sums in turn (starting over every
+// LC_MEM_WIN points), and the partial sums are added up in turn.  A 16-lane group that takes the members
+// as listed, adding up its running sum whenever the partial changes, forms exactly those sums.
+// list[off[c] .. off[c + 1]): members of cluster c0 + c, part[]: the partial sum each belongs to.
+#define LC_UB_MAX 64              // clusters of a workgroup
+#define LC_UB_LIST 2048           // members they may have together; beyond that the clusters are listed one by one
+#define LC_UB_BIG 64              // a cluster of more members is summed by the whole workgroup
+struct LcBuckets {
+    int n[LC_UB_MAX], off[LC_UB_MAX + 1];
+    int total;
+    int raw[2 * LC_UB_LIST];      // matches as found: point; cluster and position among its matches
+    int list[LC_UB_LIST];
+    uint8_t part[LC_UB_LIST];
+};
+// Returns false (in every thread) if the clusters have more members than the list holds.  All LC_BT threads must call.
+template <typename LabF>
+__device__ __forceinline__ bool lc_fill_buckets(LabF lab, int N, int c0, int n_c, LcBuckets& s) {
+    const int tid = threadIdx.x;
+    int* const raw_i = s.raw;
+    int* const raw_cs = s.raw + LC_UB_LIST;
+    if (tid < LC_UB_MAX) s.n[tid] = 0;
+    if (tid == 0) s.total = 0;
+    __syncthreads();
+    constexpr int E = 8;
+    for (int base = 0; base < N; base += E * LC_BT) {
+        int lv[E];
 #pragma unroll
-    for (int t = 0; t < 8; ++t) sum[t] = 0.f;
-    for (int base = 0; base < N; base += LC_MEM_WIN) {
-        const int nm = lc_collect_members(lab, N, base, c, mem, cnt);
-#pragma unroll 4
-        for (int t0 = grp; t0 < nm; t0 += LC_BG) {
-            float x[8];
-            lc_load8(pts + ((size_t)bh * pts_cap + mem[t0]) * LC_D + 8 * sub, x);
+        for (int e = 0; e < E; ++e) lv[e] = lab(min(base + e * LC_BT + tid, N - 1));
 #pragma unroll
-            for (int t = 0; t < 8; ++t) sum[t] += x[t];
+        for (int e = 0; e < E; ++e) {
+            const int i = base + e * LC_BT + tid;
+            const int c = lv[e] - c0;
+            if (i < N && c >= 0 && c < n_c) {
+                const int q = atomicAdd(&s.total, 1);
+                const int at = atomicAdd(&s.n[c], 1);
+                if (q < LC_UB_LIST) { raw_i[q] = i; raw_cs[q] = (c << 16) | at; }
+            }
         }
-        __syncthreads();                                            // the list is rewritten by the next window
+    }
+    __syncthreads();
+    const int total = s.total;
+    if (total > LC_UB_LIST) return false;
+    if (tid < 64) {
+        const int v = tid < LC_UB_MAX ? s.n[tid] : 0;
+        const int inc = lc_wave_scan_incl(v);
+        s.off[tid] = inc - v;
+        if (tid == 63) s.off[LC_UB_MAX] = inc;
+    }
+    __syncthreads();
+    for (int q = tid; q < total; q += LC_BT) s.list[s.off[raw_cs[q] >> 16] + (raw_cs[q] & 0xffff)] = raw_i[q];
+    __syncthreads();
+    // partial sum of every member (its rank among the cluster's members of its window, mod 16), then its place
+    constexpr int PER = LC_UB_LIST / LC_BT;
+    int mi[PER], mg[PER], mc[PER];
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+        const int q = tid + e * LC_BT;
+        mi[e] = -1;
+        if (q < total) {
+            const int c = raw_cs[q] >> 16, i = raw_i[q];
+            const int w0 = i & ~(LC_MEM_WIN - 1);
+            int r = 0;
+            for (int t = s.off[c]; t < s.off[c + 1]; ++t) r += (s.list[t] >= w0 && s.list[t] < i) ? 1 : 0;
+            mi[e] = i;
+            mg[e] = r & 15;
+            mc[e] = c;
+            s.part[s.off[c] + (raw_cs[q] & 0xffff)] = (uint8_t)mg[e];
+        }
+    }
+    __syncthreads();
+    int mp[PER];
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+        if (mi[e] >= 0) {
+            int at = s.off[mc[e]];
+            for (int t = s.off[mc[e]]; t < s.off[mc[e] + 1]; ++t) {
+                const int g = s.part[t];
+                at += (g < mg[e] || (g == mg[e] && s.list[t] < mi[e])) ? 1 : 0;
+            }
+            mp[e] = at;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < PER; ++e)
+        if (mi[e] >= 0) { s.list[mp[e]] = mi[e]; s.part[mp[e]] = (uint8_t)mg[e]; }
+    __syncthreads();
+    return true;
+}
+
+// Sum of the rows of list[t0, t1) as described above, by one 16-lane group (8 columns per lane); with
+// `flush` false only the running sum of one partial is wanted (all members of one partial).
+// row(i, x): columns [8 sub, 8 sub + 8) of member i's row.
+template <typename RowF>
+__device__ __forceinline__ void lc_sum_listed(const LcBuckets& s, int t0, int t1, RowF row, float (&sum)[8]) {
+    constexpr int BATCH = 8;                                        // rows in flight per group
+    float run[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) { sum[u] = 0.f; run[u] = 0.f; }
+    int g = t0 < t1 ? s.part[t0] : 0;
+    for (int t = t0; t < t1; t += BATCH) {
+        float x[BATCH][8];
+#pragma unroll
+        for (int e = 0; e < BATCH; ++e) row(s.list[min(t + e, t1 - 1)], x[e]);
+#pragma unroll
+        for (int e = 0; e < BATCH; ++e) {
+            if (t + e < t1) {
+                const int ge = s.part[t + e];
+                if (ge != g) {
+                    g = ge;
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) { sum[u] += run[u]; run[u] = 0.f; }
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) run[u] += x[e][u];
+            }
+        }
     }
 #pragma unroll
-    for (int t = 0; t < 8; ++t) sh[grp * LC_D + 8 * sub + t] = sum[t];
+    for (int u = 0; u < 8; ++u) sum[u] += run[u];
+}
+
+// The sums of the rows of clusters [c0, c0 + n_c), each handed to done(c, n, sum) in one whole 16-lane group
+// (c: cluster, n: members, sum: 8 columns per lane).  Small clusters one per group, clusters of more than
+// LC_UB_BIG members by the workgroup, 16 groups for the 16 partial sums.  sh: 16 * LC_D floats.
+template <typename LabF, typename RowF, typename DoneF>
+__device__ __forceinline__ void lc_cluster_sums(LabF lab, int N, int c0, int n_c, LcBuckets& s, float* sh, RowF row,
+                                                DoneF done) {
+    const int sub = threadIdx.x & 15, grp = threadIdx.x >> 4;
+    if (N > 0 && !lc_fill_buckets(lab, N, c0, n_c, s)) {
+        // ---- more members than the list holds: cluster by cluster
+        int* const mem = s.raw;
+        int* const cnt = s.list;
+        static_assert(sizeof(s.raw) >= LC_MEM_WIN * sizeof(int), "window of the one-by-one listing");
+        for (int c = 0; c < n_c; ++c) {
+            float sum[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) sum[u] = 0.f;
+            int n = 0;
+            for (int base = 0; base < N; base += LC_MEM_WIN) {
+                const int nm = lc_collect_members<LC_BT>(lab, N, base, c0 + c, mem, cnt);
+#pragma unroll 4
+                for (int t = grp; t < nm; t += LC_BG) {
+                    float x[8];
+                    row(mem[t], x);
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) sum[u] += x[u];
+                }
+                n += nm;
+                __syncthreads();                                    // the list is rewritten by the next window
+            }
+            lc_store8(sh + grp * LC_D + 8 * sub, sum);
+            __syncthreads();
+            if (grp == 0) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    float a = 0.f;
+                    for (int g = 0; g < LC_BG; ++g) a += sh[g * LC_D + 8 * sub + u];
+                    sum[u] = a;
+                }
+                done(c0 + c, n, sum);
+            }
+            __syncthreads();
+        }
+        return;
+    }
+    if (N == 0) {
+        for (int c = grp; c < n_c; c += LC_BG) {
+            float sum[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) sum[u] = 0.f;
+            done(c0 + c, 0, sum);
+        }
+        return;
+    }
+    for (int c = grp; c < n_c; c += LC_BG) {
+        if (s.n[c] > LC_UB_BIG) continue;
+        float sum[8];
+        lc_sum_listed(s, s.off[c], s.off[c + 1], row, sum);
+        done(c0 + c, s.n[c], sum);
+    }
+    for (int c = 0; c < n_c; ++c) {                                 // (uniform)
+        if (s.n[c] <= LC_UB_BIG) continue;
+        int lo = s.off[c], hi = s.off[c + 1];                       // this group's partial: a run of the list
+        {
+            int a = lo, z = hi;
+            while (a < z) { const int m = (a + z) >> 1; if (s.part[m] < grp) a = m + 1; else z = m; }
+            lo = a;
+            z = hi;
+            while (a < z) { const int m = (a + z) >> 1; if (s.part[m] <= grp) a = m + 1; else z = m; }
+            hi = a;
+        }
+        float sum[8];
+        lc_sum_listed(s, lo, hi, row, sum);
+        __syncthreads();
+        lc_store8(sh + grp * LC_D + 8 * sub, sum);
+        __syncthreads();
+        if (grp == 0) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                float a = 0.f;
+                for (int g = 0; g < LC_BG; ++g) a += sh[g * LC_D + 8 * sub + u];
+                sum[u] = a;
+            }
+            done(c0 + c, s.n[c], sum);
+        }
+    }
+}
+
+// Sum of the rows of the members of ONE cluster u by a whole workgroup: the members are listed window by
+// window, 16-lane group g takes them in turn for partial sum g mod 16, and the partial sums are added up
+// in turn (the order of lc_cluster_sums).  With 1024 threads the groups split the columns of a partial four
+// ways, for four times the loads in flight.  visit(mem, nm) sees every window's list.
+// On return sh[128] .. hold nothing of use and threads < 16 have the sum (8 columns each); returns the number
+// of members in every thread.  All NT threads must call.
+template <int NT>
+struct LcSumSh {
+    float part[LC_BG][LC_D];
+    int mem[LC_MEM_WIN];
+    int cnt[2 * 64 + 1];
+};
+template <int NT, typename LabF, typename RowF, typename VisitF>
+__device__ __forceinline__ int lc_member_sum(LabF lab, int N, int u, LcSumSh<NT>& s, RowF row, VisitF visit, float (&sum)[8]) {
+    constexpr int COLS = 8 * 256 / NT;                              // columns per lane
+    constexpr int BATCH = NT == 256 ? 4 : 16;                       // rows in flight per group
+    const int tid = threadIdx.x, sub = tid & 15, part = (tid >> 4) & 15;
+    const int col = (tid >> 8) * (COLS * 16) + COLS * sub;
+    float acc[COLS];
+#pragma unroll
+    for (int t = 0; t < COLS; ++t) acc[t] = 0.f;
+    int n = 0;
+    int lv[LC_MEM_WIN / NT];
+    if (N > 0) lc_load_labels<NT>(lab, N, 0, lv);
+    for (int base = 0; base < N; base += LC_MEM_WIN) {
+        const int nm = lc_list_members<NT>(lv, base, u, s.mem, s.cnt);
+        if (base + LC_MEM_WIN < N) lc_load_labels<NT>(lab, N, base + LC_MEM_WIN, lv);
+        for (int t = part; t < nm; t += BATCH * 16) {
+            float x[BATCH][COLS];
+#pragma unroll
+            for (int e = 0; e < BATCH; ++e) {
+                if (t + 16 * e < nm) row(s.mem[t + 16 * e], col, x[e]);
+                else {
+#pragma unroll
+                    for (int q = 0; q < COLS; ++q) x[e][q] = 0.f;
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < BATCH; ++e)
+                if (t + 16 * e < nm) {
+#pragma unroll
+                    for (int q = 0; q < COLS; ++q) acc[q] += x[e][q];
+                }
+        }
+        visit(s.mem, nm);
+        n += nm;
+        if (base + LC_MEM_WIN < N) lc_barrier_lds();                // the list is rewritten by the next window
+    }
+    if constexpr (COLS == 8) lc_store8(&s.part[part][col], acc);
+    else *reinterpret_cast<float2*>(&s.part[part][col]) = make_float2(acc[0], acc[1]);
     __syncthreads();
-    if (threadIdx.x < 16) {
-        float s[8];
+    if (tid < 16) {
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
             float a = 0.f;
-            for (int g = 0; g < LC_BG; ++g) a += sh[g * LC_D + 8 * sub + t];
-            s[t] = a;
-        }
-        float n2 = 0.f;
-#pragma unroll
-        for (int t = 0; t < 8; ++t) n2 = fmaf(s[t], s[t], n2);
-        n2 = lc_sum16(n2);
-        if (n2 > 0.f) {
-            const float inv = 1.0f / sqrtf(n2);
-#pragma unroll
-            for (int t = 0; t < 8; ++t) s[t] *= inv;
-            lc_store8(cent + ((size_t)bh * cent_cap + c) * LC_D + 8 * sub, s);
+            for (int g = 0; g < LC_BG; ++g) a += s.part[g][8 * sub + t];
+            sum[t] = a;
         }
     }
+    return n;
+}
+
+// m_c = normalise(sum of members); a cluster without members (or with a zero sum) keeps m_c.
+__device__ __forceinline__ void lc_write_centroid(float* cent, uint16_t* cent16, size_t o, float (&s)[8]) {
+    float n2 = 0.f;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) n2 = fmaf(s[t], s[t], n2);
+    n2 = lc_sum16(n2);
+    if (n2 > 0.f) {
+        const float inv = 1.0f / sqrtf(n2);
+#pragma unroll
+        for (int t = 0; t < 8; ++t) s[t] *= inv;
+        lc_store8(cent + o, s);
+        lc_store8_bf16(cent16 + o, s);
+    }
+}
+// One workgroup per cluster: for clusters of more than LC_UPD_FEW points on average (their rows are then
+// the larger part of what a workgroup reads, and 16 groups fetch them at once).
+#define LC_UPD_FEW 8
+__global__ void __launch_bounds__(LC_BT)
+lc_kmeans_update_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* cent, uint16_t* cent16, int cent_cap, int it,
+                        int* flags_all) {
+    __shared__ __attribute__((aligned(16))) LcSumSh<LC_BT> sh;
+    const int c = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+    const int bh = b * ix.H + h;
+    const int* const flags = flags_all ? lc_level_flags(ix, flags_all, l, bh) : nullptr;
+    if (flags && it >= 1 && flags[it] == 0) return;                 // no point moved: the centroids stand
+    const int N = lc_level_count(ix, b, bh, l);
+    if (c >= ix.nlev[b * LC_MAX_LEVELS + l + 1]) return;
+    const int* labels = ix.parent[l] + (size_t)bh * ix.cap[l];
+    const float* P = pts + (size_t)bh * pts_cap * LC_D;
+    float sum[8];
+    lc_member_sum<LC_BT>([&](int i) { return labels[i]; }, N, c, sh,
+                         [&](int i, int col, float (&x)[8]) { lc_load8(P + (size_t)i * LC_D + col, x); },
+                         [](const int*, int) {}, sum);
+    if (threadIdx.x < 16)
+        lc_write_centroid(cent, cent16, ((size_t)bh * cent_cap + c) * LC_D + 8 * threadIdx.x, sum);
+}
+// Several clusters per workgroup: for many small clusters.  One workgroup each would read all the labels k
+// times (5461 clusters of 10.9 K points, 8 heads: 1.9 GB of L2 reads per iteration).
+__global__ void __launch_bounds__(LC_BT)
+lc_kmeans_update_few_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* cent, uint16_t* cent16, int cent_cap,
+                            int it, int per, int* flags_all) {
+    __shared__ LcBuckets bk;
+    __shared__ __attribute__((aligned(16))) float sh[LC_BG * LC_D];
+    const int h = blockIdx.y, b = blockIdx.z;
+    const int bh = b * ix.H + h;
+    const int* const flags = flags_all ? lc_level_flags(ix, flags_all, l, bh) : nullptr;
+    if (flags && it >= 1 && flags[it] == 0) return;                 // no point moved: the centroids stand
+    const int sub = threadIdx.x & 15;
+    const int N = lc_level_count(ix, b, bh, l);
+    const int k = ix.nlev[b * LC_MAX_LEVELS + l + 1];
+    const int c0 = blockIdx.x * per;
+    if (c0 >= k) return;
+    const int* labels = ix.parent[l] + (size_t)bh * ix.cap[l];
+    const float* P = pts + (size_t)bh * pts_cap * LC_D;
+    lc_cluster_sums(
+        [&](int i) { return labels[i]; }, N, c0, min(per, k - c0), bk, sh,
+        [&](int i, float (&x)[8]) { lc_load8(P + (size_t)i * LC_D + 8 * sub, x); },
+        [&](int c, int, float (&s)[8]) { lc_write_centroid(cent, cent16, ((size_t)bh * cent_cap + c) * LC_D + 8 * sub, s); });
 }
 
 // The whole clustering of a small level (up to LC_KS_MAX_N points into up to LC_KS_MAX_K clusters)
@@ -567,12 +1229,13 @@ lc_kmeans_update_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* c
 // iterations are separated by workgroup barriers instead of kernel boundaries.  Same steps as the
 // three kernels above: strided start, assign (ties to the lower id), normalised member sums (members
 // added in ascending order; a cluster without members or with a zero sum keeps its centroid).
+#define LC_KS_THREADS 1024        // a wavefront per 16 points, a 16-lane group per cluster
 #define LC_KS_MAX_N 224
 #define LC_KS_MAX_K 64
 static inline size_t lc_kmeans_small_lds(int N, int k) {
     return (size_t)((N > 0 ? N : 1) + ((k + 15) & ~15)) * LC_AS_ROW * sizeof(float);
 }
-__global__ void __launch_bounds__(LC_BT)
+__global__ void __launch_bounds__(LC_KS_THREADS)
 lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* cent, int cent_cap, int iters,
                        int x_rows) {
     extern __shared__ __attribute__((aligned(16))) float ks_dyn[];   // x_rows point rows, then the centroid rows
@@ -591,14 +1254,14 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* ce
     const float* P = pts + (size_t)bh * pts_cap * LC_D;
     float* X = ks_dyn;
     float* cs = ks_dyn + (size_t)x_rows * LC_AS_ROW;
-    for (int v = tid; v < N * (LC_D / 4); v += LC_BT) {
+    for (int v = tid; v < N * (LC_D / 4); v += LC_KS_THREADS) {
         const int i = v / (LC_D / 4), q = v % (LC_D / 4);
         *reinterpret_cast<float4*>(X + i * LC_AS_ROW + 4 * q) = *reinterpret_cast<const float4*>(P + (size_t)i * LC_D + 4 * q);
     }
-    for (int i = tid; i < N; i += LC_BT) lab[i] = 0;
+    for (int i = tid; i < N; i += LC_KS_THREADS) lab[i] = 0;
     if (tid < 2) changed[tid] = 0;
     __syncthreads();
-    for (int v = tid; v < k16 * LC_D; v += LC_BT) {
+    for (int v = tid; v < k16 * LC_D; v += LC_KS_THREADS) {
         const int c = v / LC_D, t = v % LC_D;
         float m = 0.f;
         if (c < k) m = N > 0 ? X[(int)(((long long)c * N) / k) * LC_AS_ROW + t] : (t == 0 ? 1.f : 0.f);
@@ -606,7 +1269,7 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* ce
     }
     __syncthreads();
     for (int it = 0; it < iters; ++it) {
-        for (int i0 = 16 * wave; i0 < N; i0 += 16 * (LC_BT / 64)) {
+        for (int i0 = 16 * wave; i0 < N; i0 += 16 * (LC_KS_THREADS / 64)) {
             float4 xa[8];
             const float* row = X + min(i0 + j, N - 1) * LC_AS_ROW + 4 * kk;
 #pragma unroll
@@ -622,8 +1285,8 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* ce
             if (cj < k) lc_assign_block(xa, cs + (cj + j) * LC_AS_ROW + 4 * kk, cj + j, k, best, arg);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int ba = lc_assign_merge(best[r], arg[r]);
-                const int i = i0 + 4 * kk + r;
+                lc_assign_merge(best[r], arg[r]);
+                const int ba = arg[r], i = i0 + 4 * kk + r;
                 if (j == 0 && i < N) {
                     if (lab[i] != ba) changed[it & 1] = 1;
                     lab[i] = ba;
@@ -637,7 +1300,7 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* ce
         // remaining iterations are skipped (the first iteration always runs its update).
         if (it > 0 && changed[it & 1] == 0) break;
         // members of every cluster, ascending, as one list ordered by cluster: counts, offsets, ids
-        for (int c = wave; c < k; c += LC_BT / 64) {
+        for (int c = wave; c < k; c += LC_KS_THREADS / 64) {
             int n = 0;
             for (int r = 0; r < rounds; ++r) {
                 const int i = lane + 64 * r;
@@ -653,7 +1316,7 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* ce
             if (lane < k) moff[lane + 1] = v;
         }
         __syncthreads();
-        for (int c = wave; c < k; c += LC_BT / 64) {
+        for (int c = wave; c < k; c += LC_KS_THREADS / 64) {
             int at = moff[c];
             for (int r = 0; r < rounds; ++r) {
                 const int i = lane + 64 * r;
@@ -664,7 +1327,7 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* ce
             }
         }
         __syncthreads();
-        for (int c = grp; c < k; c += LC_BG) {
+        for (int c = grp; c < k; c += LC_KS_THREADS / 16) {
             float sum[8];
 #pragma unroll
             for (int t = 0; t < 8; ++t) sum[t] = 0.f;
@@ -689,140 +1352,199 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* ce
         }
         __syncthreads();
     }
-    for (int i = tid; i < N; i += LC_BT) ix.parent[l][(size_t)bh * ix.cap[l] + i] = lab[i];
-    for (int v = tid; v < k * LC_D; v += LC_BT)
+    for (int i = tid; i < N; i += LC_KS_THREADS) ix.parent[l][(size_t)bh * ix.cap[l] + i] = lab[i];
+    for (int v = tid; v < k * LC_D; v += LC_KS_THREADS)
         cent[(size_t)bh * cent_cap * LC_D + v] = cs[(v / LC_D) * LC_AS_ROW + (v % LC_D)];
 }
 
-// anc[j] <- label of anc[j] at the level just clustered (anc starts as identity)
-__global__ void lc_anc_kernel(LcDev ix, int l, int* anc) {
-    const int h = blockIdx.y, b = blockIdx.z;
-    const int bh = b * ix.H + h;
-    const int M = ix.state[bh * 4 + 1];
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= M) return;
-    int* a = anc + (size_t)bh * ix.cap[0];
-    const int cur = (l == 0) ? j : a[j];
-    a[j] = ix.parent[l][(size_t)bh * ix.cap[l] + cur];
+// Chunk j's ancestor at level l + 1, following the parent pointers from level 0.
+__device__ __forceinline__ int lc_ancestor(const LcDev& ix, int bh, int l, int j) {
+    int a = ix.parent[0][(size_t)bh * ix.cap[0] + j];
+    for (int t = 1; t <= l; ++t) a = a >= 0 ? ix.parent[t][(size_t)bh * ix.cap[t] + a] : -1;
+    return a;
 }
 
-// node u of level l+1: center, radius over all descendant chunks, counts, direction
-#define LC_NODE_BATCH 8
+// What is stored of node u of level l + 1 except its radius: center (mean of the descendant chunks'
+// centers; the centroid for the unit geometry and for a node without chunks), counts, unit direction (the
+// next level's point); the radius starts at -inf.  Called by one 16-lane group.
+struct LcNodeArgs {
+    const float* cent;       // this level's centroids
+    int cent_cap;
+    int geometry;
+    LcPointRows next;        // the next level's points and starting centroids
+};
+__device__ __forceinline__ void lc_write_node(const LcDev& ix, int b, int bh, int l, int u, int n_chunks, int n_tok,
+                                              float (&sum)[8], const LcNodeArgs& w) {
+    const int sub = threadIdx.x & 15;
+    float mu[8];
+    if (n_chunks > 0 && w.geometry == LC_GEOMETRY_TOKEN_BALL) {
+        const float inv = 1.0f / (float)n_chunks;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) mu[t] = sum[t] * inv;
+    } else if (lc_level_count(ix, b, bh, l) > 0) {
+        lc_load8(w.cent + ((size_t)bh * w.cent_cap + u) * LC_D + 8 * sub, mu);
+    } else {                                                        // (a sequence without chunks: no centroid was started)
+#pragma unroll
+        for (int t = 0; t < 8; ++t) mu[t] = (sub == 0 && t == 0) ? 1.f : 0.f;
+    }
+    const size_t n = (size_t)bh * ix.cap[l + 1] + u;
+    lc_store8(ix.center[l + 1] + n * LC_D + 8 * sub, mu);
+    float d[8];
+    lc_unit_frag(mu, sub, d);
+    if (w.next.pts)
+        lc_store_point(w.next, bh, u, ix.nlev[b * LC_MAX_LEVELS + l + 1], ix.nlev[b * LC_MAX_LEVELS + l + 2], sub, d);
+    if (sub == 0) {
+        ix.radius[l + 1][n] = LC_NEG_INF;
+        ix.rbuild[l + 1][n] = LC_NEG_INF;
+        ix.parent[l + 1][n] = -1;
+        ix.ntok[l + 1][n] = n_tok;
+        ix.nchunk[l + 1][n] = n_chunks;
+    }
+}
+
+// Centers of a level of many small nodes (LC_UPD_FEW chunks or fewer on average): a workgroup lists the
+// chunks of `per` nodes and gives each node to a 16-lane group.
 __global__ void __launch_bounds__(LC_BT)
-lc_node_kernel(LcDev ix, int l, const int* anc, const float* cent, int cent_cap, int geometry,
-               float* next_pts, int next_cap) {
-    __shared__ float sh[LC_BG * LC_D + LC_BG];
-    __shared__ int shi[2 * LC_BG];
-    __shared__ int mem[LC_MEM_WIN];
-    __shared__ int mcnt[2 * 64 + 1];
+lc_center_few_kernel(LcDev ix, int l, LcNodeArgs w, int per) {
+    __shared__ LcBuckets bk;
+    __shared__ __attribute__((aligned(16))) float sh[LC_BG * LC_D];
+    const int h = blockIdx.y, b = blockIdx.z;
+    const int bh = b * ix.H + h;
+    const int sub = threadIdx.x & 15;
+    const int k = ix.nlev[b * LC_MAX_LEVELS + l + 1];
+    const int u0 = blockIdx.x * per;
+    if (u0 >= k) return;
+    const int M = ix.state[bh * 4 + 1];
+    const size_t cb = (size_t)bh * ix.cap[0];
+    lc_cluster_sums(
+        [&](int j) { return lc_ancestor(ix, bh, l, j); }, M, u0, min(per, k - u0), bk, sh,
+        [&](int j, float (&x)[8]) { lc_c0_load8(ix, cb + j, sub, x); },
+        [&](int u, int n, float (&sum)[8]) {
+            int tok = 0;
+            if (M > 0 && bk.total <= LC_UB_LIST) {                  // the list is still there
+                for (int t = bk.off[u - u0] + sub; t < bk.off[u - u0] + n; t += 16) tok += ix.ntok[0][cb + bk.list[t]];
+            } else {                                                // nodes listed one by one
+                for (int j = sub; j < M; j += 16) tok += lc_ancestor(ix, bh, l, j) == u ? ix.ntok[0][cb + j] : 0;
+            }
+            lc_write_node(ix, b, bh, l, u, n, lc_sum16_i(tok), sum, w);
+        });
+}
+
+// Centers of a level of larger nodes: a workgroup per node, of 1024 threads where nodes hold more than
+// LC_CENTER_WIDE chunks on average (there a single compute unit's rate of reading rows is the bound).
+#define LC_CENTER_WIDE 128
+template <int NT>
+__global__ void __launch_bounds__(NT)
+lc_center_kernel(LcDev ix, int l, LcNodeArgs w) {
+    __shared__ __attribute__((aligned(16))) LcSumSh<NT> sh;
+    __shared__ int tok_sh[NT / 64];
     const int u = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     const int bh = b * ix.H + h;
-    const int sub = threadIdx.x & 15, grp = threadIdx.x >> 4;
-    const int k = ix.nlev[b * LC_MAX_LEVELS + l + 1];
-    if (u >= k) return;
+    if (u >= ix.nlev[b * LC_MAX_LEVELS + l + 1]) return;
+    const int tid = threadIdx.x;
     const int M = ix.state[bh * 4 + 1];
-    const int* a = anc + (size_t)bh * ix.cap[0];
     const size_t cb = (size_t)bh * ix.cap[0];
-    // the node's chunks are listed window by window (lc_collect_members); the 16 groups take them in turn
+    constexpr int COLS = 8 * 256 / NT;
+    const bool half = ix.c0_bf16 != 0;
+    const uint16_t* const c16 = reinterpret_cast<const uint16_t*>(ix.center[0]);
+    int tok = 0;
     float sum[8];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) sum[t] = 0.f;
-    int cnt = 0, tok = 0;
-    int nm = 0;
-    for (int base = 0; base < M; base += LC_MEM_WIN) {
-        nm = lc_collect_members(a, M, base, u, mem, mcnt);
-        for (int t0 = grp; t0 < nm; t0 += LC_NODE_BATCH * LC_BG) {  // a batch of rows in flight per group
-            float c[LC_NODE_BATCH][8];
-            int nt[LC_NODE_BATCH];
-#pragma unroll
-            for (int q = 0; q < LC_NODE_BATCH; ++q) {
-                const int t1 = t0 + q * LC_BG;
-                const bool in = t1 < nm;
-                nt[q] = -1;
-                if (in) {
-                    const int j = mem[t1];
-                    lc_c0_load8(ix, cb + j, sub, c[q]);
-                    nt[q] = ix.ntok[0][cb + j];
-                }
+    const int n = lc_member_sum<NT>(
+        [&](int j) { return lc_ancestor(ix, bh, l, j); }, M, u, sh,
+        [&](int j, int col, float (&x)[COLS]) {
+            const size_t o = (cb + j) * LC_D + col;
+            if constexpr (COLS == 8) {
+                if (half) lc_unpack8(*reinterpret_cast<const uint4*>(c16 + o), x);
+                else lc_load8(ix.center[0] + o, x);
+            } else if (half) {
+                const uint32_t v = *reinterpret_cast<const uint32_t*>(c16 + o);
+                x[0] = lc_bf16_lo(v);
+                x[1] = lc_bf16_hi(v);
+            } else {
+                const float2 v = *reinterpret_cast<const float2*>(ix.center[0] + o);
+                x[0] = v.x;
+                x[1] = v.y;
             }
-#pragma unroll
-            for (int q = 0; q < LC_NODE_BATCH; ++q) {
-                if (nt[q] >= 0) {
-#pragma unroll
-                    for (int t = 0; t < 8; ++t) sum[t] += c[q][t];
-                    cnt += 1;
-                    tok += nt[q];
-                }
-            }
-        }
-        if (base + LC_MEM_WIN < M) __syncthreads();                 // the list is rewritten by the next window
-    }
-#pragma unroll
-    for (int t = 0; t < 8; ++t) sh[grp * LC_D + 8 * sub + t] = sum[t];
-    if (sub == 0) { shi[grp] = cnt; shi[LC_BG + grp] = tok; }
+        },
+        [&](const int* mem, int nm) { for (int t = tid; t < nm; t += NT) tok += ix.ntok[0][cb + mem[t]]; }, sum);
+    tok = lc_wave_scan_incl(tok);
+    if ((tid & 63) == 63) tok_sh[tid >> 6] = tok;
     __syncthreads();
-    int nch = 0, ntk = 0;
-    for (int g = 0; g < LC_BG; ++g) { nch += shi[g]; ntk += shi[LC_BG + g]; }
-    float mu[8];
-    if (nch > 0 && geometry == LC_GEOMETRY_TOKEN_BALL) {
-        const float inv = 1.0f / (float)nch;
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            float s = 0.f;
-            for (int g = 0; g < LC_BG; ++g) s += sh[g * LC_D + 8 * sub + t];
-            mu[t] = s * inv;
-        }
-    } else {
-        lc_load8(cent + ((size_t)bh * cent_cap + u) * LC_D + 8 * sub, mu);
+    if (tid < 16) {
+        int n_tok = 0;
+        for (int v = 0; v < NT / 64; ++v) n_tok += tok_sh[v];
+        lc_write_node(ix, b, bh, l, u, n, n_tok, sum, w);
     }
-    __syncthreads();
-    float far = LC_NEG_INF;
-    for (int base = 0; base < M; base += LC_MEM_WIN) {
-        if (M > LC_MEM_WIN) nm = lc_collect_members(a, M, base, u, mem, mcnt);    // (a single window still holds its list)
-        for (int t0 = grp; t0 < nm; t0 += LC_NODE_BATCH * LC_BG) {
-            float c[LC_NODE_BATCH][8];
-            float r0[LC_NODE_BATCH];
-#pragma unroll
-            for (int q = 0; q < LC_NODE_BATCH; ++q) {
-                const int t1 = t0 + q * LC_BG;
-                const bool in = t1 < nm;
-#pragma unroll
-                for (int t = 0; t < 8; ++t) c[q][t] = mu[t];
-                r0[q] = LC_NEG_INF;                                 // (a slot past the list reaches nothing)
-                if (in) {
-                    const int j = mem[t1];
-                    lc_c0_load8(ix, cb + j, sub, c[q]);
-                    r0[q] = ix.radius[0][cb + j];
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < LC_NODE_BATCH; ++q) {
-                float d2 = 0.f;
-#pragma unroll
-                for (int t = 0; t < 8; ++t) { const float e = c[q][t] - mu[t]; d2 = fmaf(e, e, d2); }
-                d2 = lc_sum16(d2);
-                far = fmaxf(far, lc_pad_radius(sqrtf(d2)) + r0[q]);
-            }
-        }
-        if (base + LC_MEM_WIN < M) __syncthreads();
+}
+
+// Radii of all levels above the chunks, once every center stands: for each chunk and each of its
+// ancestors the reach |center - ancestor's center| + chunk radius, maximum per node.  One pass over the
+// chunk rows instead of one per level.  Levels of few nodes collect their maxima in LDS first, so that the
+// top node is not one address that every chunk of the head queues for.  Radii are >= 0, so their bits
+// order like integers, and a maximum does not depend on the order.
+#define LC_RD_CHUNKS 64           // chunks of a workgroup
+#define LC_RD_LDS 512             // nodes (levels >= 2 together) whose maxima are collected in LDS
+__global__ void __launch_bounds__(LC_BT)
+lc_radius_kernel(LcDev ix) {
+    __shared__ int best[LC_RD_LDS];
+    const int h = blockIdx.y, b = blockIdx.z;
+    const int bh = b * ix.H + h;
+    const int tid = threadIdx.x, sub = tid & 15, grp = tid >> 4;
+    const int M = ix.state[bh * 4 + 1];
+    if ((int)blockIdx.x * LC_RD_CHUNKS >= M) return;
+    const size_t cb = (size_t)bh * ix.cap[0];
+    int n_up = 0;                                                   // nodes above level 1, in level order
+    for (int l = 2; l < ix.L; ++l) n_up += ix.nlev[b * LC_MAX_LEVELS + l];
+    const bool in_lds = n_up <= LC_RD_LDS;
+    if (in_lds) {
+        for (int i = tid; i < n_up; i += LC_BT) best[i] = -1;
+        __syncthreads();
     }
-    if (sub == 0) sh[grp] = far;
-    __syncthreads();
-    float R = LC_NEG_INF;
-    for (int g = 0; g < LC_BG; ++g) R = fmaxf(R, sh[g]);
-    const size_t n = (size_t)bh * ix.cap[l + 1] + u;
-    if (threadIdx.x < 16) {
-        lc_store8(ix.center[l + 1] + n * LC_D + 8 * sub, mu);
-        float d[8];
-        lc_unit_frag(mu, sub, d);
-        lc_store8(next_pts + ((size_t)bh * next_cap + u) * LC_D + 8 * sub, d);
-        if (sub == 0) {
-            const float R_st = nch > 0 ? lc_pad_radius(R) : LC_NEG_INF;
-            ix.radius[l + 1][n] = R_st;
-            ix.rbuild[l + 1][n] = R_st;          // the baseline that lc_index_drift measures growth against
-            ix.parent[l + 1][n] = -1;
-            ix.ntok[l + 1][n] = ntk;
-            ix.nchunk[l + 1][n] = nch;
+    auto raise = [&](int l, int a, int bits) {
+        atomicMax(reinterpret_cast<int*>(ix.radius[l]) + (size_t)bh * ix.cap[l] + a, bits);
+        atomicMax(reinterpret_cast<int*>(ix.rbuild[l]) + (size_t)bh * ix.cap[l] + a, bits);
+    };
+    constexpr int PER = LC_RD_CHUNKS / LC_BG;
+    float c[PER][8], r0[PER];
+    int anc[PER];
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+        const int j = min((int)blockIdx.x * LC_RD_CHUNKS + e * LC_BG + grp, M - 1);
+        anc[e] = ix.parent[0][cb + j];
+        lc_c0_load8(ix, cb + j, sub, c[e]);
+        r0[e] = ix.radius[0][cb + j];
+    }
+    int up = 0;
+    for (int l = 1; l < ix.L; ++l) {
+        float mu[PER][8];
+        int next[PER];
+#pragma unroll
+        for (int e = 0; e < PER; ++e) {
+            const size_t n = (size_t)bh * ix.cap[l] + max(anc[e], 0);
+            lc_load8(ix.center[l] + n * LC_D + 8 * sub, mu[e]);
+            next[e] = l + 1 < ix.L ? ix.parent[l][n] : -1;
+        }
+#pragma unroll
+        for (int e = 0; e < PER; ++e) {
+            float d2 = 0.f;
+#pragma unroll
+            for (int t = 0; t < 8; ++t) { const float x = c[e][t] - mu[e][t]; d2 = fmaf(x, x, d2); }
+            d2 = lc_sum16(d2);
+            const float reach = lc_pad_radius(lc_pad_radius(sqrtf(d2)) + r0[e]);
+            if (sub == 0 && anc[e] >= 0) {
+                if (l >= 2 && in_lds) atomicMax(&best[up + anc[e]], __float_as_int(reach));
+                else raise(l, anc[e], __float_as_int(reach));
+            }
+            anc[e] = anc[e] >= 0 ? next[e] : -1;
+        }
+        if (l >= 2) up += ix.nlev[b * LC_MAX_LEVELS + l];
+    }
+    if (in_lds) {
+        __syncthreads();
+        int l = 2, o = 0;
+        for (int i = tid; i < n_up; i += LC_BT) {
+            while (i - o >= ix.nlev[b * LC_MAX_LEVELS + l]) { o += ix.nlev[b * LC_MAX_LEVELS + l]; ++l; }
+            if (best[i] >= 0) raise(l, i - o, best[i]);
         }
     }
 }
@@ -834,58 +1556,99 @@ int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const i
     const uint16_t* K = static_cast<const uint16_t*>(Kp);
     const int geometry = idx->cfg.geometry;
     const int B = ix.B, H = ix.H, L = ix.L;
-    int* const kflags = idx->cfg.kmeans_iters < LC_KM_FLAGS ? ws.kflags : nullptr;   // (more iterations: no early exit)
+    const long long BH = (long long)B * H;
+    const int iters = idx->cfg.kmeans_iters;
+    int* const kflags = iters < LC_KM_FLAGS ? ws.kflags : nullptr;   // (more iterations: no early exit)
+    // points and centroids of the level being clustered, and of the next one (whose rows are written while
+    // this one's centroids are still read)
+    LcPointRows cur{ws.dirs, ws.dirs16, ix.cap[0], L > 1 ? ws.cent[0] : nullptr, ws.cent16[0], ix.cap[1]};
     if (max_M > 0 && K != nullptr) {
         hipLaunchKernelGGL(lc_pool_kernel, dim3((max_M + LC_BT / 64 - 1) / (LC_BT / 64), H, B), dim3(LC_BT), 0, stream, ix, K,
-                           (long long)ks[0], (long long)ks[1], (long long)ks[2], geometry, ws.dirs);
+                           (long long)ks[0], (long long)ks[1], (long long)ks[2], geometry, cur, ws.kflags);
         LC_HIP_CHECK(hipGetLastError());
     } else if (max_M > 0) {
-        hipLaunchKernelGGL(lc_dirs_kernel, dim3((max_M + LC_BG - 1) / LC_BG, H, B), dim3(LC_BT), 0, stream, ix, ws.dirs);
+        hipLaunchKernelGGL(lc_dirs_kernel, dim3((max_M + LC_BG - 1) / LC_BG, H, B), dim3(LC_BT), 0, stream, ix, cur, ws.kflags);
         LC_HIP_CHECK(hipGetLastError());
     }
-    // per-level maxima over the batch (host mirror)
-    float* pts = ws.dirs;
-    int pts_cap = ix.cap[0];
-    float* other = ws.cent_b;
-    int other_cap = ix.cap[1];
     for (int l = 0; l + 1 < L; ++l) {
+        LcPointRows next{nullptr, nullptr, 0, nullptr, nullptr, 0};
+        if (l + 2 < L) {
+            const bool even = (l & 1) == 0;                          // level 0's points give way to level 2's
+            next = LcPointRows{even ? ws.next_pts : ws.dirs, even ? ws.next_pts16 : ws.dirs16, even ? ix.cap[1] : ix.cap[0],
+                               ws.cent[even ? 1 : 0], ws.cent16[even ? 1 : 0], ix.cap[1]};
+        }
+        // per-level maxima over the batch (host mirror)
         int maxN = 0, maxK = 0;
         for (int b = 0; b < B; ++b) {
             maxN = idx->N[b * LC_MAX_LEVELS + l] > maxN ? idx->N[b * LC_MAX_LEVELS + l] : maxN;
             maxK = idx->N[b * LC_MAX_LEVELS + l + 1] > maxK ? idx->N[b * LC_MAX_LEVELS + l + 1] : maxK;
         }
-        const int cent_cap = ix.cap[1];
-        const bool small = maxN <= LC_KS_MAX_N && maxK <= LC_KS_MAX_K;      // the whole clustering in one kernel
-        if (small) {
-            const int x_rows = maxN > 0 ? maxN : 1;
-            const size_t lds = lc_kmeans_small_lds(x_rows, maxK);
+        // clusters per workgroup of the kernels that list several: one per 16-lane group, more of them where
+        // that would be over a thousand workgroups that each read all the labels
+        const int per = (maxK + LC_BG - 1) / LC_BG * BH > 1024 ? LC_UB_MAX : LC_BG;
+        const dim3 per_grid((maxK + per - 1) / per, H, B);
+        if (maxN > 0 && maxN <= LC_KS_MAX_N && maxK <= LC_KS_MAX_K) {  // the whole clustering in one kernel
+            const size_t lds = lc_kmeans_small_lds(maxN, maxK);
             LC_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(&lc_kmeans_small_kernel),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-            hipLaunchKernelGGL(lc_kmeans_small_kernel, dim3(H, B), dim3(LC_BT), lds, stream, ix, l, (const float*)pts,
-                               pts_cap, ws.cent_a, cent_cap, idx->cfg.kmeans_iters, x_rows);
-        } else {
-            hipLaunchKernelGGL(lc_kmeans_init_kernel, dim3(maxK, H, B), dim3(LC_D), 0, stream, ix, l,
-                               (const float*)pts, pts_cap, ws.cent_a, cent_cap, kflags);
-        }
-        LC_HIP_CHECK(hipGetLastError());
-        if (maxN > 0) {
-            for (int it = 0; it < (small ? 0 : idx->cfg.kmeans_iters); ++it) {
-                hipLaunchKernelGGL(lc_kmeans_assign_kernel, dim3((maxN + LC_AS_PTS - 1) / LC_AS_PTS, H, B), dim3(LC_BT), 0,
-                                   stream, ix, l, (const float*)pts, pts_cap, (const float*)ws.cent_a, cent_cap, it, kflags);
-                hipLaunchKernelGGL(lc_kmeans_update_kernel, dim3(maxK, H, B), dim3(LC_BT), 0, stream, ix, l,
-                                   (const float*)pts, pts_cap, ws.cent_a, cent_cap, it, (const int*)kflags);
+            hipLaunchKernelGGL(lc_kmeans_small_kernel, dim3(H, B), dim3(LC_KS_THREADS), lds, stream, ix, l,
+                               (const float*)cur.pts, cur.cap, cur.cent, cur.cent_cap, iters, maxN);
+            LC_HIP_CHECK(hipGetLastError());
+        } else if (maxN > 0) {
+            // Many centroids: 64 MA points per workgroup.  The fuller a wavefront's A operand, the fewer LDS reads per
+            // product (LDS bandwidth for two blocks of products with MA = 1); MA is the one with the least work on the
+            // busiest compute unit, the larger one if equal.
+            int ma = 1;
+            long long least = 0;
+            for (int m = 1; m <= 4; ++m) {
+                const long long load = ((maxN + 64 * m - 1) / (64 * m) * BH + 255) / 256 * (m > 2 ? m : 2);
+                if (m == 1 || load <= least) { least = load; ma = m; }
+            }
+            // Few centroids: 64 points per workgroup, or 128 where that leaves more workgroups than two per compute unit.
+            const bool wide = (maxN + 63) / 64 * BH > 512;
+            auto assign = [&](auto kernel, int points, int threads, int it) {
+                hipLaunchKernelGGL(kernel, dim3((maxN + points - 1) / points, H, B), dim3(threads), 0, stream, ix, l,
+                                   (const float*)cur.pts, (const uint16_t*)cur.pts16, cur.cap, (const float*)cur.cent,
+                                   (const uint16_t*)cur.cent16, cur.cent_cap, it, kflags);
+            };
+            auto assign_res = [&](auto kernel4, auto kernel8, int it) {
+                if (wide) assign(kernel8, 128, 512, it);
+                else assign(kernel4, 64, 256, it);
+            };
+            for (int it = 0; it < iters; ++it) {
+                if (maxK <= 32) assign_res(&lc_kmeans_assign_res_kernel<2, 4>, &lc_kmeans_assign_res_kernel<2, 8>, it);
+                else if (maxK <= 64) assign_res(&lc_kmeans_assign_res_kernel<4, 4>, &lc_kmeans_assign_res_kernel<4, 8>, it);
+                else if (maxK <= 96) assign_res(&lc_kmeans_assign_res_kernel<6, 4>, &lc_kmeans_assign_res_kernel<6, 8>, it);
+                else if (maxK <= 128) assign_res(&lc_kmeans_assign_res_kernel<8, 4>, &lc_kmeans_assign_res_kernel<8, 8>, it);
+                else if (maxK <= 160) assign_res(&lc_kmeans_assign_res_kernel<10, 4>, &lc_kmeans_assign_res_kernel<10, 8>, it);
+                else if (maxK <= 192) assign_res(&lc_kmeans_assign_res_kernel<12, 4>, &lc_kmeans_assign_res_kernel<12, 8>, it);
+                else if (maxK <= LC_AS_RES) assign_res(&lc_kmeans_assign_res_kernel<16, 4>, &lc_kmeans_assign_res_kernel<16, 8>, it);
+                else if (ma == 4) assign(&lc_kmeans_assign_kernel<4>, 256, LC_BT, it);
+                else if (ma == 3) assign(&lc_kmeans_assign_kernel<3>, 192, LC_BT, it);
+                else if (ma == 2) assign(&lc_kmeans_assign_kernel<2>, 128, LC_BT, it);
+                else assign(&lc_kmeans_assign_kernel<1>, 64, LC_BT, it);
+                if (maxN <= (long long)maxK * LC_UPD_FEW)
+                    hipLaunchKernelGGL(lc_kmeans_update_few_kernel, per_grid, dim3(LC_BT), 0, stream, ix, l,
+                                       (const float*)cur.pts, cur.cap, cur.cent, cur.cent16, cur.cent_cap, it, per, kflags);
+                else
+                    hipLaunchKernelGGL(lc_kmeans_update_kernel, dim3(maxK, H, B), dim3(LC_BT), 0, stream, ix, l,
+                                       (const float*)cur.pts, cur.cap, cur.cent, cur.cent16, cur.cent_cap, it, kflags);
             }
             LC_HIP_CHECK(hipGetLastError());
-            if (max_M > 0) {
-                hipLaunchKernelGGL(lc_anc_kernel, dim3((max_M + 255) / 256, H, B), dim3(256), 0, stream, ix, l, ws.anc);
-                LC_HIP_CHECK(hipGetLastError());
-            }
         }
-        hipLaunchKernelGGL(lc_node_kernel, dim3(maxK, H, B), dim3(LC_BT), 0, stream, ix, l, (const int*)ws.anc,
-                           (const float*)ws.cent_a, cent_cap, geometry, other, other_cap);
+        const LcNodeArgs w{cur.cent, cur.cent_cap, geometry, next};
+        if (max_M <= (long long)maxK * LC_UPD_FEW)
+            hipLaunchKernelGGL(lc_center_few_kernel, per_grid, dim3(LC_BT), 0, stream, ix, l, w, per);
+        else if (max_M <= (long long)maxK * LC_CENTER_WIDE)
+            hipLaunchKernelGGL(lc_center_kernel<256>, dim3(maxK, H, B), dim3(256), 0, stream, ix, l, w);
+        else
+            hipLaunchKernelGGL(lc_center_kernel<1024>, dim3(maxK, H, B), dim3(1024), 0, stream, ix, l, w);
         LC_HIP_CHECK(hipGetLastError());
-        float* t = pts; pts = other; other = t;
-        const int tc = pts_cap; pts_cap = other_cap; other_cap = tc;
+        cur = next;
+    }
+    if (L > 1 && max_M > 0) {
+        hipLaunchKernelGGL(lc_radius_kernel, dim3((max_M + LC_RD_CHUNKS - 1) / LC_RD_CHUNKS, H, B), dim3(LC_BT), 0, stream, ix);
+        LC_HIP_CHECK(hipGetLastError());
     }
     return LC_OK;
 }

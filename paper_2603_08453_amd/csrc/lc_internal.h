@@ -56,14 +56,16 @@ struct LcWs {
     float* part_acc;     // [B][H][S][G][d]
     float* part_ml;      // [B][H][S][G][2]
     // build
-    float* dirs;         // [B][H][cap0][d] unit directions of the level being clustered
-    float* cent_a;       // [B][H][cap1][d] centroids (ping)
-    float* cent_b;       // [B][H][cap1][d] centroids (pong)
-    int* anc;            // [B][H][cap0] chunk -> ancestor at the level being built
-    int* kflags;         // [B][H][LC_KM_FLAGS] "iteration t of the k-means moved a point" (tiled kernels only)
+    float* dirs;         // [B][H][cap0][d] unit directions of the chunks (and of every second level above)
+    uint16_t* dirs16;    // the same rounded to bfloat16
+    float* next_pts;     // [B][H][cap1][d] unit directions of the other levels
+    uint16_t* next_pts16;
+    float* cent[2];      // [B][H][cap1][d] centroids of the level being clustered, start of the next level's
+    uint16_t* cent16[2];
+    int* kflags;         // [level][B][H][LC_KM_FLAGS] "iteration t of the k-means moved a point" (tiled kernels only)
     size_t total;
 };
-// with_build = false leaves out the build scratch (dirs, centroids, ancestors): what a decode step needs.
+// with_build = false leaves out the build scratch (directions, centroids): what a decode step needs.
 size_t lc_layout_ws(const lc_config* cfg, int B, int H_q, int H, int d, int splits, void* base, LcWs* ws,
                     bool with_build = true);
 int lc_auto_splits(const lc_config* cfg, int B, int H);

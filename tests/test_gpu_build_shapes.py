@@ -1,0 +1,114 @@
+"""Index build against a plain float64 computation, at the sizes where its kernels change or have edges: number of
+points and centroids around the tiles of each assignment kernel, clusters listed together, alone, by the whole
+workgroup and beyond what a list holds, points with more equally near centroids than a candidate list holds."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def build(H, chunks, F, iters, levels=2, seed=0, same=0, centers=0, spread=1.0):
+    """GPU build over `chunks` (chunks per sequence) of 1 to 3 tokens; the first `same` chunks have identical keys."""
+    import torch
+    from paper_2603_08453_amd import binding as lc
+    r = np.random.default_rng(seed)
+    bounds = [np.concatenate([[0], np.cumsum(r.integers(1, 4, size=m))]).astype(np.int32) for m in chunks]
+    T = max(int(b[-1]) for b in bounds)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    K = torch.randn((len(chunks), H, T, 128), generator=g, device="cuda")
+    if spread != 1.0:                                        # clusters of very unequal sizes
+        K[..., 0] += spread * torch.randn((len(chunks), H, T), generator=g, device="cuda").abs() ** 3
+    K = K.to(torch.bfloat16)
+    for b, bd in enumerate(bounds):
+        if same:
+            K[b, :, : bd[min(same, len(bd) - 1)]] = K[b, :, :1].clone()
+    cfg = lc.lc_config_default(levels=levels, fanout=F, kmeans_iters=iters, max_chunks=max(chunks), max_tokens=T,
+                               center_dtype=centers)
+    ib = torch.zeros(lc.lc_index_bytes(cfg, len(chunks), H), dtype=torch.uint8, device="cuda")
+    ws = torch.full((lc.lc_workspace_bytes(cfg, len(chunks), H, H),), 0xA5, dtype=torch.uint8, device="cuda")
+    idx = lc.lc_build_index(cfg, K, [int(b[-1]) for b in bounds], bounds, ib, ws)
+    return lc.unpack_blob(lc.lc_index_export(idx))["seqs"]
+
+
+def unit(x):
+    return x / np.linalg.norm(x, axis=1, keepdims=True)
+
+
+def check_labels(lab, x, cent):
+    """Nearest centroid by inner product; a label may differ only where the two are equal to rounding."""
+    s = x @ cent.T
+    best = s.max(axis=1)
+    got = s[np.arange(len(x)), lab]
+    assert np.all(got >= best - 3e-6)
+    clear = np.partition(s, -2, axis=1)[:, -2] < best - 3e-6 if cent.shape[0] > 1 else np.ones(len(x), bool)
+    assert np.array_equal(lab[clear], s.argmax(axis=1)[clear])
+
+
+def check_tree(head):
+    """Centers, counts and radii of every level from the chunk level and the parents alone."""
+    c0, r0 = head[0]["center"].astype(np.float64), head[0]["radius"].astype(np.float64)
+    anc = np.arange(len(r0))
+    for l in range(1, len(head)):
+        anc = head[l - 1]["parent"][anc]
+        k = len(head[l]["radius"])
+        n = np.bincount(anc, minlength=k)
+        assert np.array_equal(head[l]["nchunk"], n)
+        assert np.array_equal(head[l]["ntok"], np.bincount(anc, weights=head[0]["ntok"], minlength=k).astype(np.int64))
+        mean = np.zeros((k, 128))
+        np.add.at(mean, anc, c0)
+        full = n > 0
+        mean[full] /= n[full, None]
+        assert np.abs(head[l]["center"][full] - mean[full]).max() < 2e-5
+        reach = np.full(k, -np.inf)
+        np.maximum.at(reach, anc, np.linalg.norm(c0 - head[l]["center"][anc].astype(np.float64), axis=1) + r0)
+        assert np.all(np.isneginf(head[l]["radius"][~full]))
+        got = head[l]["radius"][full]
+        assert np.all(got >= reach[full]) and np.all(got <= reach[full] * (1.0 + 3e-5) + 1e-6)
+
+
+# points, centroids: one case for each assignment kernel and its remainders (heads and batch decide the wide ones)
+SHAPES = [(8, [225], 15), (8, [640, 1], 15), (2, [700, 65], 16), (2, [1000], 11), (1, [1024], 8), (3, [1120], 7),
+          (1, [1500], 8), (2, [1281], 5), (8, [4500, 300], 32), (8, [4160], 20), (1, [514], 2), (2, [777, 3], 2),
+          (8, [2200, 2100], 4), (8, [5001, 4097], 8), (8, [10922], 2)]
+
+
+@pytest.mark.parametrize("H,chunks,F", SHAPES)
+def test_first_two_iterations(H, chunks, F):
+    one, two = build(H, chunks, F, 1), build(H, chunks, F, 2)
+    for s1, s2 in zip(one, two):
+        for h in (0, H - 1):
+            x = unit(s1["heads"][h][0]["center"].astype(np.float64))
+            N, k = len(x), len(s1["heads"][h][1]["radius"])
+            lab = s1["heads"][h][0]["parent"]
+            cent = x[(np.arange(k) * N) // k]
+            check_labels(lab, x, cent)
+            total = np.zeros((k, 128))
+            np.add.at(total, lab, x)
+            some = np.bincount(lab, minlength=k) > 0
+            cent = cent.copy()
+            cent[some] = unit(total[some])
+            check_labels(s2["heads"][h][0]["parent"], x, cent)
+            check_tree(s2["heads"][h])
+
+
+@pytest.mark.parametrize("H,chunks,F,levels,centers,spread", [
+    (2, [2275], 16, 4, 0, 1.0), (2, [2275, 0, 17], 16, 4, 1, 1.0), (1, [4097], 3, 3, 0, 1.0), (1, [9000], 2, 4, 0, 1.0),
+    (1, [6000], 16, 3, 1, 3.0), (1, [3000], 4, 2, 0, 6.0), (2, [300], 300, 2, 0, 1.0), (1, [5000], 1, 2, 0, 1.0)])
+def test_nodes_of_every_level(H, chunks, F, levels, centers, spread):
+    for s in build(H, chunks, F, 4, levels=levels, centers=centers, spread=spread):
+        if len(s["bounds"]) > 1:
+            for head in s["heads"]:
+                check_tree(head)
+
+
+@pytest.mark.parametrize("chunks,F,same", [(800, 8, 500), (1200, 2, 300), (3000, 3, 3000), (2400, 12, 40)])
+def test_many_equally_near_centroids(chunks, F, same):
+    """Identical chunks start identical centroids: all of them take the lowest one's number."""
+    s = build(2, [chunks], F, 1, same=same)[0]
+    for head in s["heads"]:
+        x = unit(head[0]["center"].astype(np.float64))
+        k = len(head[1]["radius"])
+        check_labels(head[0]["parent"], x, x[(np.arange(k) * chunks) // k])
+        assert np.all(head[0]["parent"][:same] == 0)
+        check_tree(head)
