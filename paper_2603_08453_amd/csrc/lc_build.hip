@@ -580,7 +580,7 @@ __device__ __forceinline__ void lc_assign_finish(LcAssignSh<WP, NW>& sh, const f
 // products overlap (with one around each block a block took 500 clocks).
 // Measured, 8 heads of 2275 points x 143 centroids: 16.7 -> 8.8 us an iteration.
 template <int NBLK, int NW>
-__global__ void __launch_bounds__(64 * NW, NW / 2)
+__global__ void __launch_bounds__(64 * NW, NBLK == 16 ? 2 : NW / 2)
 lc_kmeans_assign_res_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16, int pts_cap, const float* cent,
                             const uint16_t* cent16, int cent_cap, int it, int* flags_all) {
     constexpr int PIECES = NBLK * 256 / (64 * NW);                  // 16-byte pieces of the rows per thread

@@ -24,7 +24,6 @@
 #define LC_DEC_MIN_TOKENS_PER_SPLIT 64
 #define LC_DEC_MAX_SPLITS 256
 #define LC_DEC_TILE 1024          // tokens of a split whose cache rows are resolved into LDS at a time
-#define LC_DEC_WIN 2048           // slots of the entry window of a tile: a power of two above LC_DEC_TILE + 2
 #define LC_DEC_E 2                // selected ids per thread and pass of the row resolution
 #define LC_LOG2E 1.4426950408889634f
 #define LC_LN2 0.6931471805599453f
@@ -47,7 +46,7 @@ struct LcDecodeArgs {
     float* out;           // [B][H*G][d]
     float* lse;           // [B][H*G] or null
     // fused step only (the kernel selects the chunks itself from their score keys):
-    const uint32_t* keys; // [B][H][cap0] score keys of the chunks (0 = not a candidate)
+    const int* entries;   // [B][H][cap0] chunk entries (LcChunkEntry) of the scoring kernel
     int32_t* ids_out;     // [B][H][cap] selected ids, ascending, or null
     int32_t* counts_out;  // [B][H] or null
     int budget, sink;     // token budget, tokens of the pinned prefix
@@ -72,6 +71,16 @@ __device__ __forceinline__ float lc_row_bcast_n(float v, int src) {      // src 
         default: return lc_row_bcast<7>(v);
     }
 }
+// a in the lower half of the wavefront and b in the upper half, each summed over the two halves
+__device__ __forceinline__ float lc_add_halves(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// a in the even 16-lane rows and b in the odd ones, each summed over a row and its neighbour
+__device__ __forceinline__ float lc_add_rows(float a, float b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
 // exp2 of (x - ref) where x may be -inf (gives 0); ref is finite.
 __device__ __forceinline__ float lc_exp2_rel(float x, float ref) { return exp2f(x - ref); }
 
@@ -79,29 +88,22 @@ __device__ __forceinline__ float lc_exp2_rel(float x, float ref) { return exp2f(
 // repeats the budget selection of its (sequence, head) from the chunk score keys -- the same
 // deterministic routine on the same keys, so all splits agree -- and never reads a chunk list.
 //
-// The fused selection (lc_select_chunks) keeps the chunks in registers and leaves every lane with
-// the first rows, lengths and token offsets of its selected chunks; the wavefronts then write the
-// cache row of every token of the split's tile into LDS, 64 lanes per overlapping chunk.
+// Either way the selected chunks sit in a list, in id order; the wavefronts write the cache row of
+// every token of the split's tile into LDS, 64 lanes per overlapping chunk.
 template <int G, bool FUSED, int EC>
 __global__ void __launch_bounds__(LC_DEC_THREADS)
 lc_decode_kernel(const LcDecodeArgs a) {
-    extern __shared__ int lds_dyn[];             // FUSED: key and length of every chunk, for the overflow path only
+    extern __shared__ int lds_dyn[];             // FUSED: the selection's chunk lists
     using SelStore = typename std::conditional<FUSED, LcLeafSelSh, int>::type;
     using FusedStore = typename std::conditional<FUSED, LcFusedSh<LC_DEC_THREADS>, int>::type;
-    constexpr int WIN = FUSED ? 1 : LC_DEC_WIN;
     __shared__ __attribute__((aligned(16))) SelStore sel_store;
     __shared__ __attribute__((aligned(16))) FusedStore fused_store;
     __shared__ int scan_sh[8];
     __shared__ int rows[LC_DEC_TILE];
-    __shared__ int win_off[WIN];                  // first token position of the entries that overlap the tile
-    __shared__ int win_st[WIN];                   // and their first cache row
-    __shared__ int win_hd[2];                     // indices of the entries holding the tile's first / last token
     __shared__ int last_sh;
     __shared__ float comb_ml[LC_DEC_THREADS / 64][G][2];
     __shared__ __attribute__((aligned(16))) float comb_acc[LC_DEC_THREADS / 64][G][LC_D];
-    __shared__ float mrg_m[LC_DEC_MAX_SPLITS * G];
-    __shared__ float mrg_l[LC_DEC_MAX_SPLITS * G];
-    __shared__ float mrg_hd[2 * G];
+    __shared__ float mrg_s[LC_DEC_THREADS / 32][LC_DEC_MAX_SPLITS];
     __shared__ float4 mrg_red[LC_DEC_THREADS];
 
     // tokens per group and batch of loads; two batches are in flight per group (the next one is
@@ -126,7 +128,7 @@ lc_decode_kernel(const LcDecodeArgs a) {
     // ---- the attended tokens are the selected chunks in ascending id order, then the open tail.
     // Entry i of that list is (first cache row, length).  Both variants end up with: n_runs entries,
     // n_tok tokens, and a way to find the cache row of every token of a tile.
-    int n_runs, n_tok, T;
+    int n_runs = 0, n_tok, T;
     // FUSED = false: thread t of a pass owns entries [E t, E t + E); the first pass stays in registers
     const int32_t* ids = nullptr;
     int n_ids = 0, M = 0;
@@ -173,12 +175,11 @@ lc_decode_kernel(const LcDecodeArgs a) {
             n_tok += tot;
         }
     } else {
-        lc_select_chunks<LC_DEC_THREADS, EC>(ix, b, bh, a.keys, a.budget, a.sink, s == 0 ? a.ids_out : nullptr,
+        lc_select_chunks<LC_DEC_THREADS, EC>(ix, b, bh, a.entries, a.budget, a.sink, s == 0 ? a.ids_out : nullptr,
                                              a.counts_out, a.cap, sel_store, fused_store, lds_dyn, cs);
         T = cs.T;
         M = cs.M;
         n_tok = cs.n_tok;
-        n_runs = cs.n_sel + 1;
     }
     int S_eff = (n_tok + LC_DEC_MIN_TOKENS_PER_SPLIT - 1) / LC_DEC_MIN_TOKENS_PER_SPLIT;
     S_eff = max(1, min(S, S_eff));
@@ -284,73 +285,50 @@ lc_decode_kernel(const LcDecodeArgs a) {
         for (int tile0 = lo; tile0 < hi; tile0 += LC_DEC_TILE) {
             const int tl = min(LC_DEC_TILE, hi - tile0);
             const int row_max = max(T - 1, 0);
+            // 64 lanes per selected chunk that overlaps the tile (its lane's values are read by number)
+            auto fill = [&](int o, int st, int ln) {
+                const int k0 = max(o, tile0), k1 = min(o + ln, tile0 + tl);
+                for (int k = k0 + lane; k < k1; k += 64) rows[k - tile0] = max(0, min(st + (k - o), row_max));
+            };
+            auto fill_round = [&](int off, int st, int ln) {
+                unsigned long long mask = __ballot(ln > 0 && off < tile0 + tl && tile0 < off + ln);
+                while (mask != 0ull) {
+                    const int l = __ffsll((long long)mask) - 1;
+                    mask &= mask - 1ull;
+                    fill(lc_readlane(off, l), lc_readlane(st, l), lc_readlane(ln, l));
+                }
+            };
+            if (tile0 != lo) lc_barrier_lds();                      // the previous tile's rows have been used
             if constexpr (FUSED) {
-                // 64 lanes per selected chunk that overlaps the tile (its owner's values are read by lane)
-                if (tile0 != lo) lc_barrier_lds();                  // the previous tile's rows have been used
-                auto fill = [&](int o, int st, int ln) {
-                    const int k0 = max(o, tile0), k1 = min(o + ln, tile0 + tl);
-                    for (int k = k0 + lane; k < k1; k += 64) rows[k - tile0] = max(0, min(st + (k - o), row_max));
-                };
-#pragma unroll
-                for (int e = 0; e < EC; ++e) {
-                    const int off = cs.base_tok + cs.coff[e];
-                    unsigned long long mask = __ballot(cs.stok[e] > 0 && off < tile0 + tl && tile0 < off + cs.stok[e]);
-                    while (mask != 0ull) {
-                        const int l = __ffsll((long long)mask) - 1;
-                        mask &= mask - 1ull;
-                        fill(lc_readlane(off, l), lc_readlane(cs.cst[e], l), lc_readlane(cs.stok[e], l));
-                    }
+                fill_round(cs.base_tok + cs.off0, cs.st0, cs.ln0);
+                int carry = cs.base_tok + lc_readlane(cs.off0 + cs.ln0, 63);
+                for (int r = 64; r < cs.n_list; r += 64) {
+                    int st, ln;
+                    lc_sel_entry<LC_DEC_THREADS, EC>(cs, fused_store, r + lane, &st, &ln);
+                    const int inc = lc_wave_scan_incl(ln);
+                    fill_round(carry + inc - ln, st, ln);
+                    carry += lc_readlane(inc, 63);
                 }
                 if (wave == 0 && cs.tail_ln > 0 && cs.n_sel_tok < tile0 + tl && tile0 < cs.n_sel_tok + cs.tail_ln)
                     fill(cs.n_sel_tok, cs.tail_st, cs.tail_ln);
-                lc_barrier_lds();
             } else {
-                // The few entries that overlap the tile go into a window at slot (entry index mod window
-                // size) -- overlapping entries are consecutive and fewer than the window is long -- and the
-                // entries that hold the tile's first and last token leave their indices; then one small
-                // binary search per token, in parallel.
-                __syncthreads();
-                {
-                    auto entry = [&](int i, int off, int st, int ln) {
-                        if (ln > 0 && off < tile0 + tl && tile0 < off + ln) {
-                            win_off[i & (LC_DEC_WIN - 1)] = off;
-                            win_st[i & (LC_DEC_WIN - 1)] = st;
-                            if (off <= tile0) win_hd[0] = i;
-                            if (tile0 + tl <= off + ln) win_hd[1] = i;
-                        }
-                    };
-                    auto visit = [&](int base, int off, const int (&st)[E], const int (&ln)[E]) {
+                auto visit = [&](int off, const int (&st)[E], const int (&ln)[E]) {
 #pragma unroll
-                        for (int e = 0; e < E; ++e) {
-                            entry(base + tid * E + e, off, st[e], ln[e]);
-                            off += ln[e];
-                        }
-                    };
-                    visit(0, ex0, st0, ln0);
-                    int carry = tot0;
-                    for (int base = LC_DEC_THREADS * E; base < n_runs; base += LC_DEC_THREADS * E) {
-                        int st[E], ln[E], tot;
-                        const int ex = lc_block_scan<LC_DEC_THREADS>(entries(base, false, st, ln), scan_sh, &tot);
-                        visit(base, carry + ex, st, ln);
-                        carry += tot;
+                    for (int e = 0; e < E; ++e) {
+                        fill_round(off, st[e], ln[e]);
+                        off += ln[e];
                     }
+                };
+                visit(ex0, st0, ln0);
+                int carry = tot0;
+                for (int base = LC_DEC_THREADS * E; base < n_runs; base += LC_DEC_THREADS * E) {
+                    int st[E], ln[E], tot;
+                    const int ex = lc_block_scan<LC_DEC_THREADS>(entries(base, false, st, ln), scan_sh, &tot);
+                    visit(carry + ex, st, ln);
+                    carry += tot;
                 }
-                __syncthreads();
-                {
-                    const int w_first = win_hd[0], w_last = win_hd[1];
-                    for (int i = tid; i < tl; i += LC_DEC_THREADS) {
-                        const int tok = tile0 + i;
-                        int lo_w = w_first, hi_w = w_last + 1;   // off[lo_w] <= tok < off[hi_w]
-                        while (hi_w - lo_w > 1) {
-                            const int mid = (lo_w + hi_w) >> 1;
-                            if (win_off[mid & (LC_DEC_WIN - 1)] <= tok) lo_w = mid; else hi_w = mid;
-                        }
-                        const int sl = lo_w & (LC_DEC_WIN - 1);
-                        rows[i] = max(0, min(win_st[sl] + (tok - win_off[sl]), row_max));
-                    }
-                }
-                __syncthreads();
             }
+            lc_barrier_lds();
             const int per = (tl + LC_DEC_GROUPS - 1) / LC_DEC_GROUPS;
             const int n_it = (per + U - 1) / U;            // the same for every wavefront: the MFMA needs all lanes
             tv = min(tl, grp * per);
@@ -368,33 +346,26 @@ lc_decode_kernel(const LcDecodeArgs a) {
             }
         }
 
-        // ---- combine the 4 groups of a wave (xor 16, 32), then the waves through LDS
-#pragma unroll
-        for (int off = 16; off < 64; off <<= 1) {
-            const float m_o = __shfl_xor(m_run, off);
-            const float l_o = __shfl_xor(l_run, off);
-            const float mx = fmaxf(m_run, m_o);
-            const float ref = (mx == LC_NEG_INF) ? 0.f : mx;
-            const float sa = lc_exp2_rel(m_run, ref);
-            const float sb = lc_exp2_rel(m_o, ref);
-            l_run = l_run * sa + l_o * sb;
-            m_run = mx;
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const float sag = lc_row_bcast_n(sa, g), sbg = lc_row_bcast_n(sb, g);
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const float a_o = __shfl_xor(acc[g][i], off);
-                    acc[g][i] = acc[g][i] * sag + a_o * sbg;
-                }
-            }
-        }
-        if (lane < 16) {
-            if (lane < G) { comb_ml[wave][lane][0] = m_run; comb_ml[wave][lane][1] = l_run; }
+        // ---- combine the 4 groups of a wave: one common reference per head, then the accumulators are added
+        // up and spread over the groups by row swaps (lanes of group q4 keep columns 8 sub + 4 (q4 >> 1) +
+        // 2 (q4 & 1) + {0, 1}), two vector instructions per pair of values; the waves meet in LDS
+        {
+            float mx = fmaxf(m_run, __shfl_xor(m_run, 16));
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            const float sc = lc_exp2_rel(m_run, (mx == LC_NEG_INF) ? 0.f : mx);
+            float l = l_run * sc;
+            l += __shfl_xor(l, 16);
+            l += __shfl_xor(l, 32);
+            if (lane < G) { comb_ml[wave][lane][0] = mx; comb_ml[wave][lane][1] = l; }
 #pragma unroll
             for (int g = 0; g < G; ++g) {
+                const float sg = lc_row_bcast_n(sc, g);
+                float h4[4], h2[2];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) comb_acc[wave][g][8 * lane + i] = acc[g][i];
+                for (int i = 0; i < 4; ++i) h4[i] = lc_add_halves(acc[g][i] * sg, acc[g][i + 4] * sg);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) h2[i] = lc_add_rows(h4[i], h4[i + 2]);
+                *reinterpret_cast<float2*>(&comb_acc[wave][g][8 * sub + 4 * (q4 >> 1) + 2 * (q4 & 1)]) = make_float2(h2[0], h2[1]);
             }
         }
         __syncthreads();
@@ -425,8 +396,9 @@ lc_decode_kernel(const LcDecodeArgs a) {
     // ---- the last split to arrive merges (log-sum-exp merge of the partial results)
     if (!lc_arrive_last(&ix.sync[bh * 4 + 1], S, &last_sh)) return;
 
-    // The accumulator partials do not depend on the scales, so their loads go out first and fly
-    // while the (m, l) pairs are fetched and turned into per-split scales.
+    // The accumulator partials do not depend on the scales, so their loads go out first and fly while the
+    // (m, l) pairs are fetched.  Every 32 lanes take one head (slot v of the output below) and turn its
+    // splits' pairs into scales by themselves: no barrier until the sums meet.
     const __amdgpu_buffer_rsrc_t pacc_r = lc_buffer(a.part_acc + (size_t)bh * S * G * LC_D);
     const float* pml = a.part_ml + (size_t)bh * S * G * 2;
     const int n_part = (n_tok > 0) ? S_eff : 0;
@@ -444,27 +416,33 @@ lc_decode_kernel(const LcDecodeArgs a) {
         }
     };
     if (wy < WAYS && n_part > 0) load_round(wy);
-    // partial (m, l) of every split -> LDS; per head: global max, scale of each split, denominator
-    for (int e = tid; e < n_part * G; e += LC_DEC_THREADS) {
-        mrg_m[e] = lc_load_agent(pml + 2 * e);
-        mrg_l[e] = lc_load_agent(pml + 2 * e + 1);
-    }
-    __syncthreads();
-    for (int gg = wave; gg < G; gg += LC_DEC_THREADS / 64) {
-        float mx = LC_NEG_INF;
-        for (int sp = lane; sp < n_part; sp += 64) mx = fmaxf(mx, mrg_m[sp * G + gg]);
-        mx = lc_max64(mx);
-        float den = 0.f;
-        for (int sp = lane; sp < n_part; sp += 64) {
-            const float ms = mrg_m[sp * G + gg];
-            const float sc = (ms == LC_NEG_INF) ? 0.f : exp2f(ms - mx);
-            mrg_m[sp * G + gg] = sc;                    // from here on: the split's scale
-            den = fmaf(mrg_l[sp * G + gg], sc, den);
+    const int half = tid >> 5, hl = tid & 31;
+    float m_all = LC_NEG_INF, den = 0.f;
+    {
+        float m0 = LC_NEG_INF, l0 = 0.f;                     // the first 32 splits (all of them unless more were asked for)
+        if (hl < n_part) {
+            m0 = lc_load_agent(pml + 2 * (hl * G + g));
+            l0 = lc_load_agent(pml + 2 * (hl * G + g) + 1);
         }
-        den = lc_sum64(den);
-        if (lane == 0) { mrg_hd[2 * gg] = mx; mrg_hd[2 * gg + 1] = den; }
+        m_all = m0;
+        for (int sp = hl + 32; sp < n_part; sp += 32) m_all = fmaxf(m_all, lc_load_agent(pml + 2 * (sp * G + g)));
+        m_all = fmaxf(m_all, lc_dpp<0xB1>(m_all));
+        m_all = fmaxf(m_all, lc_dpp<0x4E>(m_all));
+        m_all = fmaxf(m_all, lc_dpp<0x141>(m_all));
+        m_all = fmaxf(m_all, lc_dpp<0x140>(m_all));
+        m_all = fmaxf(m_all, __shfl_xor(m_all, 16));
+        for (int sp = hl; sp < n_part; sp += 32) {
+            const float ms = sp < 32 ? m0 : lc_load_agent(pml + 2 * (sp * G + g));
+            const float ls = sp < 32 ? l0 : lc_load_agent(pml + 2 * (sp * G + g) + 1);
+            const float sc = (ms == LC_NEG_INF) ? 0.f : exp2f(ms - m_all);
+            mrg_s[half][sp] = sc;
+            den = fmaf(ls, sc, den);
+        }
+        den = lc_sum16(den);
+        den += __shfl_xor(den, 16);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
-    __syncthreads();
     float4 acc4 = make_float4(0.f, 0.f, 0.f, 0.f);
     if (wy < WAYS) {
         for (int sp0 = wy; sp0 < n_part; sp0 += MR * WAYS) {
@@ -472,7 +450,7 @@ lc_decode_kernel(const LcDecodeArgs a) {
 #pragma unroll
             for (int k = 0; k < MR; ++k) {
                 const int sp = sp0 + k * WAYS;
-                const float sc = sp < n_part ? mrg_m[sp * G + g] : 0.f;
+                const float sc = sp < n_part ? mrg_s[half][sp] : 0.f;
                 acc4.x = fmaf(x[k].x, sc, acc4.x);
                 acc4.y = fmaf(x[k].y, sc, acc4.y);
                 acc4.z = fmaf(x[k].z, sc, acc4.z);
@@ -488,12 +466,11 @@ lc_decode_kernel(const LcDecodeArgs a) {
             const float4 o4 = mrg_red[(k - 1) * NV + v];
             acc4.x += o4.x; acc4.y += o4.y; acc4.z += o4.z; acc4.w += o4.w;
         }
-        const float mx = mrg_hd[2 * g], den = mrg_hd[2 * g + 1];
         const float inv = den > 0.f ? 1.0f / den : 0.f;
         const size_t o = ((size_t)b * ix.H * G + (size_t)h * G + g);
         *reinterpret_cast<float4*>(a.out + o * LC_D + 4 * c4) =
             make_float4(acc4.x * inv, acc4.y * inv, acc4.z * inv, acc4.w * inv);
-        if (a.lse && c4 == 0) a.lse[o] = den > 0.f ? (mx + log2f(den)) * LC_LN2 : LC_NEG_INF;
+        if (a.lse && c4 == 0) a.lse[o] = den > 0.f ? (m_all + log2f(den)) * LC_LN2 : LC_NEG_INF;
     }
     if (tid == 0) ix.sync[bh * 4 + 1] = 0;
 }
@@ -521,7 +498,7 @@ static void fill_common(LcDecodeArgs& a, const lc_index* idx, const LcWs& ws, co
     a.part_ml = ws.part_ml;
     a.out = out;
     a.lse = lse;
-    a.keys = nullptr;
+    a.entries = nullptr;
     a.ids_out = nullptr;
     a.counts_out = nullptr;
     a.budget = 0;
@@ -562,8 +539,7 @@ bool lc_decode_fused_fits(int G, int max_M) {
 
 template <int G, int EC>
 static int launch_fused_ge(const LcDecodeArgs& a, int splits, hipStream_t stream) {
-    // key and length of every chunk, touched only when the cutoff bin overflows its short list
-    const size_t lds = (size_t)EC * LC_DEC_THREADS * 8;
+    const size_t lds = (size_t)EC * LC_DEC_THREADS * 12;      // the selection's chunk lists
     if (lds > 16 * 1024)        // static + dynamic may pass the default per-workgroup allowance
         LC_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(&lc_decode_kernel<G, true, EC>),
                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
@@ -585,7 +561,7 @@ int lc_launch_decode_fused(const lc_index* idx, const LcWs& ws, const void* q, c
                            int32_t* counts_out, int cap, int max_M, float* out, float* lse, hipStream_t stream) {
     LcDecodeArgs a;
     fill_common(a, idx, ws, q, K, V, ks, out, lse);
-    a.keys = ws.keys;
+    a.entries = ws.scratch;
     a.ids_out = ids_out;
     a.counts_out = counts_out;
     a.cap = cap;

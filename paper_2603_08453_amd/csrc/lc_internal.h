@@ -49,7 +49,7 @@ struct LcWs {
     // retrieval
     uint32_t* keys;      // [B][H][cap0] order-preserving score keys of the chunks (0 = not a candidate)
     uint8_t* want;       // [B][H][cap0] 1 = this chunk's score is needed
-    int* scratch;        // [B][H][4 * cap0] chunk-level staging when it does not fit in LDS
+    int* scratch;        // [B][H][4 * cap0] chunk-level staging when it does not fit in LDS; chunk entries of the fused step
     int32_t* ids_tmp;    // [B][H][cap0] chunk list of a decode step that has to run as two kernels
     int32_t* counts_tmp; // [B][H]
     // decode
@@ -100,8 +100,8 @@ int lc_launch_retrieve(const lc_index* idx, const LcWs& ws, const void* q, int G
 int lc_launch_decode(const lc_index* idx, const LcWs& ws, const void* q, const void* K, const void* V,
                      const int64_t ks[3], const int32_t* ids, const int32_t* counts, int cap, int G,
                      int splits, float* out, float* lse, hipStream_t stream);
-// Fused step: selection from ws.keys (written by lc_launch_retrieve with score_only) + attention.
-// lc_decode_fused_fits tells whether the staged chunk arrays of max_M chunks fit into LDS.
+// Fused step: selection from the chunk entries in ws.scratch (written by lc_launch_retrieve with score_only)
+// + attention.  lc_decode_fused_fits tells whether a selecting workgroup holds max_M chunks.
 bool lc_decode_fused_fits(int G, int max_M);
 int lc_launch_decode_fused(const lc_index* idx, const LcWs& ws, const void* q, const void* K, const void* V,
                            const int64_t ks[3], int G, int splits, int budget, int32_t* ids_out,

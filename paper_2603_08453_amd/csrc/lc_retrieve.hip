@@ -37,7 +37,8 @@ struct LcRetrieveArgs {
     float* scores;           // [B][H][cap0] or null
     int32_t* ids;            // [B][H][cap]
     int32_t* counts;         // [B][H]
-    int* scratch;            // [B][H][4 * cap0] ints: chunk-level staging when it does not fit in LDS
+    int* scratch;            // [B][H][4 * cap0] ints: chunk-level staging when it does not fit in LDS; the
+                             // chunk entries of lc_score_kernel
     int cap;
     int budget;
     int policy;
@@ -912,20 +913,22 @@ lc_score_kernel(const LcRetrieveArgs a) {
     // the per-chunk arrays through range-checked buffer resources (an index derived from stored
     // values -- a parent pointer -- cannot reach memory outside its array)
     const __amdgpu_buffer_rsrc_t bnd_r = lc_buffer(ix.bounds + (size_t)b * (cap0 + 1), (cap0 + 1) * 4);
-    const __amdgpu_buffer_rsrc_t keys_r = lc_buffer(a.keys + cb, cap0 * 4);
+    const __amdgpu_buffer_rsrc_t ent_r = lc_buffer(a.scratch + 4 * cb, cap0 * 16);
     const __amdgpu_buffer_rsrc_t want_r = lc_buffer(a.want + cb, cap0);
     const __amdgpu_buffer_rsrc_t par_r = lc_buffer(ix.parent[0] + cb, cap0 * 4);
     const __amdgpu_buffer_rsrc_t rad_r = lc_buffer(ix.radius[0] + cb, cap0 * 4);
     const bool have_want = a.walk != 0;
     const int j_lo = blockIdx.x * (R * GROUPS);
-    int jj[R], wv[R];
+    int jj[R], wv[R], st[R], en[R];
     float rv[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int j = min(j_lo + r * GROUPS + grp, cap0 - 1);
         jj[r] = j;
         // (rows past the chunk count hold whatever the buffer held: the result is unused)
-        wv[r] = (lc_buf_load_i32(bnd_r, j) >= a.sink ? 1 : 0) & (have_want ? lc_buf_load_u8(want_r, lc_buf_load_i32(par_r, j)) : 1);
+        st[r] = lc_buf_load_i32(bnd_r, j);
+        en[r] = lc_buf_load_i32(bnd_r, j + 1);
+        wv[r] = (st[r] >= a.sink ? 1 : 0) & (have_want ? lc_buf_load_u8(want_r, lc_buf_load_i32(par_r, j)) : 1);
         rv[r] = lc_buf_load_f32(rad_r, j);
     }
     LcNodeFrag pre[R];
@@ -945,7 +948,14 @@ lc_score_kernel(const LcRetrieveArgs a) {
             if (!have_want) sv = lc_score_chunk_frag<G>(pre[r], c0b, rv[r], qf, qn);
             else sv = lc_score_chunk_frag<G>(lc_load_chunk_node(ix.center[0], c0b, cb + jj[r], sub), c0b, rv[r], qf, qn);
         }
-        if (j < M && sub == 0) lc_buf_store_u32(keys_r, j, lc_score_key(sv));
+        if (j < M && sub == 0) {                                // one 16-byte entry per chunk (LcChunkEntry)
+            lc_v4i w;
+            w.x = (int)lc_score_key(sv);
+            w.y = st[r];
+            w.z = max(0, en[r] - st[r]);
+            w.w = 0;
+            __builtin_amdgcn_raw_buffer_store_b128(w, ent_r, j * 16, 0, 0);
+        }
     }
 }
 
