@@ -154,6 +154,25 @@ def _host():
     return _host_mod
 
 
+_fast_mod = None
+
+
+def _fast():
+    """The CPython module that marshals torch tensors for the per-token calls (raises if it has not been built)."""
+    global _fast_mod
+    if _fast_mod is None:
+        import torch  # noqa: F401  (the module links to its libraries)
+        try:
+            from . import _lychee_torch
+        except ImportError as e:
+            raise RuntimeError(f"_lychee_torch is missing: build it first (python -m paper_2603_08453_amd.build): {e}")
+        L = lib()
+        _lychee_torch.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in
+                             (L.lc_decode_step, L.lc_decode_step_static, L.lc_retrieve, L.lc_sparse_decode, L.lc_append)))
+        _fast_mod = _lychee_torch
+    return _fast_mod
+
+
 # ------------------------------------------------------------------ helpers
 
 def _check(rc: int, where: str) -> None:
@@ -216,6 +235,7 @@ class Index:
 
     def __init__(self, handle: int, cfg: LcConfig, index_buf, B: int, H_kv: int):
         self.handle = ctypes.c_void_p(handle)
+        self.address = handle or 0             # the same as a number, 0 once closed
         self.cfg = cfg
         self.index_buf = index_buf
         self.B = B
@@ -231,6 +251,7 @@ class Index:
         if self.handle:
             lib().lc_index_destroy(self.handle)
             self.handle = None
+            self.address = 0
 
     def __del__(self):
         try:
@@ -267,6 +288,11 @@ def lc_set_prune(idx: Index, prune: int) -> None:
 
 def lc_retrieve(idx: Index, q, budget: int, chunk_ids, counts, ws, scores=None, stream=None) -> None:
     """q bf16 [B][H_q][d]; chunk_ids int32 [B][H_kv][cap]; counts int32 [B][H_kv]."""
+    rc = (_fast_mod or _fast()).retrieve(idx.address, q, budget, chunk_ids, counts, ws, scores, stream)
+    if rc is not NotImplemented:
+        if rc:
+            raise LycheeError(rc, "lc_retrieve")
+        return
     H_q = q.shape[1]
     cap = chunk_ids.shape[2]
     rc = lib().lc_retrieve(idx.handle, _ptr(q), H_q, budget, _ptr(chunk_ids), _ptr(counts), _ptr(scores), cap,
@@ -276,6 +302,11 @@ def lc_retrieve(idx: Index, q, budget: int, chunk_ids, counts, ws, scores=None, 
 
 def lc_sparse_decode(idx: Index, q, K, V, chunk_ids, counts, out, ws, lse=None, stream=None) -> None:
     """out float32 [B][H_q][d]; lse float32 [B][H_q] or None."""
+    rc = (_fast_mod or _fast()).sparse_decode(idx.address, q, K, V, chunk_ids, counts, out, ws, lse, stream)
+    if rc is not NotImplemented:
+        if rc:
+            raise LycheeError(rc, "lc_sparse_decode")
+        return
     H_q = q.shape[1]
     cap = chunk_ids.shape[2]
     assert K.stride() == V.stride()
@@ -322,6 +353,11 @@ def lc_bench_read_sweep(src, sink, stream=None) -> None:
 def lc_decode_step(idx: Index, q, K, V, budget: int, out, ws, lse=None, chunk_ids=None, counts=None,
                    stream=None) -> None:
     """q bf16 [B][H_q][d]; out f32 [B][H_q][d]; optional chunk_ids int32 [B][H_kv][cap] + counts."""
+    rc = (_fast_mod or _fast()).decode_step(idx.address, q, K, V, budget, out, ws, lse, chunk_ids, counts, stream, False)
+    if rc is not NotImplemented:
+        if rc:
+            raise LycheeError(rc, "lc_decode_step")
+        return
     assert K.shape == V.shape and K.stride() == V.stride()
     H_q = int(q.shape[1])
     cap = int(chunk_ids.shape[-1]) if chunk_ids is not None else 0
@@ -333,6 +369,11 @@ def lc_decode_step(idx: Index, q, K, V, budget: int, out, ws, lse=None, chunk_id
 def lc_decode_step_static(idx: Index, q, K, V, budget: int, out, lse=None, chunk_ids=None, counts=None,
                           stream=None) -> None:
     """lc_decode_step on the library's own static scratch array (no workspace argument)."""
+    rc = (_fast_mod or _fast()).decode_step(idx.address, q, K, V, budget, out, None, lse, chunk_ids, counts, stream, True)
+    if rc is not NotImplemented:
+        if rc:
+            raise LycheeError(rc, "lc_decode_step_static")
+        return
     assert K.shape == V.shape and K.stride() == V.stride()
     H_q = int(q.shape[1])
     cap = int(chunk_ids.shape[-1]) if chunk_ids is not None else 0
@@ -351,6 +392,11 @@ def lc_static_workspace_bytes() -> int:
 
 def lc_append(idx: Index, K, V, k_new, v_new, close_chunk: Optional[Sequence[int]], ws, stream=None) -> None:
     """k_new, v_new bf16 [B][H_kv][d]; close_chunk: host flags per sequence (or None)."""
+    rc = (_fast_mod or _fast()).append(idx.address, K, V, k_new, v_new, close_chunk, ws, stream)
+    if rc is not NotImplemented:
+        if rc:
+            raise LycheeError(rc, "lc_append")
+        return
     cc = None
     if close_chunk is not None:
         cc = (ctypes.c_uint8 * len(close_chunk))(*[1 if c else 0 for c in close_chunk])

@@ -12,8 +12,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblychee.so")
-HOST_LIB = os.path.join(HERE, "_lychee_host.so")      # CPython module, host code only
-HOST_SOURCE = "lc_pyhost.cpp"
+# CPython modules, host code only: source -> module, and whether it uses torch's C++ objects
+HOST_MODULES = [("lc_pyhost.cpp", os.path.join(HERE, "_lychee_host.so"), False),
+                ("lc_pytorch.cpp", os.path.join(HERE, "_lychee_torch.so"), True)]
 SOURCES = ["lc_api.hip", "lc_retrieve.hip", "lc_decode.hip", "lc_build.hip", "lc_blob.hip", "lc_chunker.hip", "lc_bench.hip"]
 
 
@@ -24,21 +25,30 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
-def build_host(verbose: bool = True) -> str:
-    """Compile the CPython module with the host compiler."""
+def build_host(verbose: bool = True) -> None:
+    """Compile the CPython modules with the host compiler."""
+    import torch
+    tdir = os.path.dirname(torch.__file__)
     cxx = next((c for c in (os.environ.get("CXX"), shutil.which("g++"), shutil.which("c++")) if c), None)
-    cmd = [cxx] if cxx else [hipcc(), "-x", "c++"]
-    cmd += ["-O3", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-cast-function-type",
-            "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-            os.path.join(CSRC, HOST_SOURCE), "-o", HOST_LIB]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
-    return HOST_LIB
+    for source, out, with_torch in HOST_MODULES:
+        cmd = [cxx] if cxx else [hipcc(), "-x", "c++"]
+        cmd += ["-O3", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-cast-function-type",
+                "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), "-I", CSRC]
+        if with_torch:
+            rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc())))
+            cmd += ["-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+                    "-isystem", os.path.join(tdir, "include"), "-isystem", os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
+                    "-isystem", os.path.join(rocm, "include")]
+        cmd += [os.path.join(CSRC, source), "-o", out]
+        if with_torch:
+            cmd += ["-L", os.path.join(tdir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.run(cmd, check=True)
 
 
 def build(verbose: bool = True) -> str:
-    """Compile every HIP source for gfx950 and link the shared library; then the CPython module."""
+    """Compile every HIP source for gfx950 and link the shared library; then the CPython modules."""
     build_host(verbose)
     cmd = [hipcc(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

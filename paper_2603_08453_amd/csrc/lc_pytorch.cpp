@@ -1,0 +1,227 @@
+// CPython module _lychee_torch: argument marshalling of the per-token entry points for torch tensors.
+//
+// A decode step at a short context is shorter on the GPU than its call was in Python: ctypes
+// conversions, tensor accessors and the current-stream object took about half of the 12.9 us a call spent on the
+// host.  Here the tensors are read through torch's C++ objects.  The module calls the C ABI through the
+// addresses the binding hands over (bind), so it works with whichever build of the library is loaded.
+// A call with arguments that are no tensors returns NotImplemented and the binding marshals it itself.
+#define PY_SSIZE_T_CLEAN
+#include <torch/csrc/autograd/python_variable.h>
+
+#include <c10/hip/HIPStream.h>
+
+#include <exception>
+
+#include "lychee.h"
+
+namespace {
+
+decltype(&lc_decode_step) g_decode_step = nullptr;
+decltype(&lc_decode_step_static) g_decode_step_static = nullptr;
+decltype(&lc_retrieve) g_retrieve = nullptr;
+decltype(&lc_sparse_decode) g_sparse_decode = nullptr;
+decltype(&lc_append) g_append = nullptr;
+
+PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    if (n != 5) {
+        PyErr_SetString(PyExc_TypeError, "bind(decode_step, decode_step_static, retrieve, sparse_decode, append)");
+        return nullptr;
+    }
+    g_decode_step = reinterpret_cast<decltype(g_decode_step)>(PyLong_AsVoidPtr(a[0]));
+    g_decode_step_static = reinterpret_cast<decltype(g_decode_step_static)>(PyLong_AsVoidPtr(a[1]));
+    g_retrieve = reinterpret_cast<decltype(g_retrieve)>(PyLong_AsVoidPtr(a[2]));
+    g_sparse_decode = reinterpret_cast<decltype(g_sparse_decode)>(PyLong_AsVoidPtr(a[3]));
+    g_append = reinterpret_cast<decltype(g_append)>(PyLong_AsVoidPtr(a[4]));
+    if (PyErr_Occurred()) return nullptr;
+    Py_RETURN_NONE;
+}
+
+// Positional arguments of one call.
+class Args {
+  public:
+    Args(PyObject* const* a, Py_ssize_t n) : a_(a), n_(n) {}
+    bool count(Py_ssize_t n) {
+        if (n_ == n) return true;
+        PyErr_Format(PyExc_TypeError, "expected %zd arguments, got %zd", n, n_);
+        return false;
+    }
+    // The tensor at i, or null for None; anything else makes the call not ours.
+    const at::Tensor* tensor(int i) {
+        if (a_[i] == Py_None) return nullptr;
+        if (!THPVariable_Check(a_[i])) { foreign_ = true; return nullptr; }
+        return &THPVariable_Unpack(a_[i]);
+    }
+    void* ptr(int i) {
+        const at::Tensor* t = tensor(i);
+        return t ? t->data_ptr() : nullptr;
+    }
+    long integer(int i) {
+        if (PyLong_CheckExact(a_[i])) return PyLong_AsLong(a_[i]);
+        PyObject* const v = PyNumber_Long(a_[i]);
+        const long r = v ? PyLong_AsLong(v) : -1;
+        Py_XDECREF(v);
+        return r;
+    }
+    lc_index* handle(int i) { return static_cast<lc_index*>(PyLong_AsVoidPtr(a_[i])); }
+    void* stream(int i) {
+        if (a_[i] == Py_None) return c10::hip::getCurrentHIPStream().stream();
+        PyObject* const v = PyObject_GetAttrString(a_[i], "cuda_stream");
+        void* const s = v ? PyLong_AsVoidPtr(v) : nullptr;
+        Py_XDECREF(v);
+        return s;
+    }
+    PyObject* operator[](int i) const { return a_[i]; }
+    bool foreign() const { return foreign_; }
+
+  private:
+    PyObject* const* a_;
+    Py_ssize_t n_;
+    bool foreign_ = false;
+};
+
+bool cache_strides(const at::Tensor& K, const at::Tensor& V, bool shapes, int64_t (&s)[3]) {
+    if ((shapes && !K.sizes().equals(V.sizes())) || !K.strides().equals(V.strides())) {
+        PyErr_SetString(PyExc_AssertionError, "K and V must have the same shape and strides");
+        return false;
+    }
+    if (K.dim() != 4 || K.stride(3) != 1) {
+        PyErr_SetString(PyExc_AssertionError, "cache must be [B][H_kv][tokens][d] with d contiguous");
+        return false;
+    }
+    for (int i = 0; i < 3; ++i) s[i] = K.stride(i);
+    return true;
+}
+size_t bytes(const at::Tensor& t) { return (size_t)t.numel() * t.element_size(); }
+
+// The result of a call, or NotImplemented / the pending Python error.
+template <typename F>
+PyObject* guarded(Args& a, F call) {
+    try {
+        int rc = 0;
+        const bool done = call(&rc);
+        if (PyErr_Occurred()) return nullptr;
+        if (a.foreign() || !done) Py_RETURN_NOTIMPLEMENTED;
+        return PyLong_FromLong(rc);
+    } catch (const std::exception& e) {
+        if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, e.what());
+        return nullptr;
+    }
+}
+
+// decode_step(handle, q, K, V, budget, out, ws or None, lse, chunk_ids, counts, stream, static)
+PyObject* decode_step(PyObject*, PyObject* const* args, Py_ssize_t n) {
+    Args a(args, n);
+    if (!a.count(12)) return nullptr;
+    return guarded(a, [&](int* rc) {
+        const at::Tensor *q = a.tensor(1), *K = a.tensor(2), *V = a.tensor(3), *ws = a.tensor(6), *ids = a.tensor(8);
+        const bool fixed = a[11] == Py_True;
+        if (!q || !K || !V || (!fixed && !ws) || a.foreign()) return false;
+        int64_t s[3];
+        if (!cache_strides(*K, *V, true, s)) return true;
+        const int budget = (int)a.integer(4), cap = ids ? (int)ids->size(-1) : 0;
+        float* const out = static_cast<float*>(a.ptr(5));
+        float* const lse = static_cast<float*>(a.ptr(7));
+        int32_t* const counts = static_cast<int32_t*>(a.ptr(9));
+        if (PyErr_Occurred() || a.foreign()) return false;
+        int32_t* const idp = ids ? static_cast<int32_t*>(ids->data_ptr()) : nullptr;
+        void* const st = a.stream(10);
+        if (PyErr_Occurred()) return false;
+        if (fixed)
+            *rc = g_decode_step_static(a.handle(0), q->data_ptr(), K->data_ptr(), V->data_ptr(), s, (int)q->size(1), budget,
+                                       out, lse, idp, counts, cap, st);
+        else
+            *rc = g_decode_step(a.handle(0), q->data_ptr(), K->data_ptr(), V->data_ptr(), s, (int)q->size(1), budget, out,
+                                lse, idp, counts, cap, ws->data_ptr(), bytes(*ws), st);
+        return true;
+    });
+}
+
+// retrieve(handle, q, budget, chunk_ids, counts, ws, scores, stream)
+PyObject* retrieve(PyObject*, PyObject* const* args, Py_ssize_t n) {
+    Args a(args, n);
+    if (!a.count(8)) return nullptr;
+    return guarded(a, [&](int* rc) {
+        const at::Tensor *q = a.tensor(1), *ids = a.tensor(3), *ws = a.tensor(5);
+        if (!q || !ids || !ws || a.foreign()) return false;
+        const int budget = (int)a.integer(2);
+        int32_t* const counts = static_cast<int32_t*>(a.ptr(4));
+        float* const scores = static_cast<float*>(a.ptr(6));
+        if (PyErr_Occurred() || a.foreign()) return false;
+        void* const st = a.stream(7);
+        if (PyErr_Occurred()) return false;
+        *rc = g_retrieve(a.handle(0), q->data_ptr(), (int)q->size(1), budget, static_cast<int32_t*>(ids->data_ptr()), counts,
+                         scores, (int)ids->size(2), ws->data_ptr(), bytes(*ws), st);
+        return true;
+    });
+}
+
+// sparse_decode(handle, q, K, V, chunk_ids, counts, out, ws, lse, stream)
+PyObject* sparse_decode(PyObject*, PyObject* const* args, Py_ssize_t n) {
+    Args a(args, n);
+    if (!a.count(10)) return nullptr;
+    return guarded(a, [&](int* rc) {
+        const at::Tensor *q = a.tensor(1), *K = a.tensor(2), *V = a.tensor(3), *ids = a.tensor(4), *ws = a.tensor(7);
+        if (!q || !K || !V || !ids || !ws || a.foreign()) return false;
+        int64_t s[3];
+        if (!cache_strides(*K, *V, false, s)) return true;
+        const int32_t* const counts = static_cast<const int32_t*>(a.ptr(5));
+        float* const out = static_cast<float*>(a.ptr(6));
+        float* const lse = static_cast<float*>(a.ptr(8));
+        if (a.foreign()) return false;
+        void* const st = a.stream(9);
+        if (PyErr_Occurred()) return false;
+        *rc = g_sparse_decode(a.handle(0), q->data_ptr(), K->data_ptr(), V->data_ptr(), s,
+                              static_cast<const int32_t*>(ids->data_ptr()), counts, (int)ids->size(2), (int)q->size(1), out,
+                              lse, ws->data_ptr(), bytes(*ws), st);
+        return true;
+    });
+}
+
+// append(handle, K, V, k_new, v_new, close flags or None, ws, stream)
+PyObject* append(PyObject*, PyObject* const* args, Py_ssize_t n) {
+    Args a(args, n);
+    if (!a.count(8)) return nullptr;
+    return guarded(a, [&](int* rc) {
+        const at::Tensor *K = a.tensor(1), *V = a.tensor(2), *k = a.tensor(3), *v = a.tensor(4), *ws = a.tensor(6);
+        if (!K || !V || !k || !v || !ws || a.foreign()) return false;
+        int64_t s[3];
+        if (!cache_strides(*K, *V, false, s)) return true;
+        uint8_t flags[1024] = {};                            // lc_append takes at most 1024 sequences
+        const bool given = a[5] != Py_None;
+        if (given) {
+            PyObject* const seq = PySequence_Fast(a[5], "close_chunk must be a sequence");
+            if (!seq) return false;
+            const Py_ssize_t m = PySequence_Fast_GET_SIZE(seq);
+            bool ok = m <= (Py_ssize_t)sizeof(flags);
+            for (Py_ssize_t i = 0; ok && i < m; ++i) {
+                const int t = PyObject_IsTrue(PySequence_Fast_GET_ITEM(seq, i));
+                if (t < 0) ok = false;
+                else flags[i] = (uint8_t)t;
+            }
+            Py_DECREF(seq);
+            if (!ok) return false;
+        }
+        void* const st = a.stream(7);
+        if (PyErr_Occurred()) return false;
+        *rc = g_append(a.handle(0), K->data_ptr(), V->data_ptr(), s, k->data_ptr(), v->data_ptr(), given ? flags : nullptr,
+                       ws->data_ptr(), bytes(*ws), st);
+        return true;
+    });
+}
+
+template <typename F>
+PyCFunction fast(F f) { return reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(f)); }
+
+PyMethodDef methods[] = {
+    {"bind", fast(bind), METH_FASTCALL, "addresses of the library's entry points"},
+    {"decode_step", fast(decode_step), METH_FASTCALL, ""},
+    {"retrieve", fast(retrieve), METH_FASTCALL, ""},
+    {"sparse_decode", fast(sparse_decode), METH_FASTCALL, ""},
+    {"append", fast(append), METH_FASTCALL, ""},
+    {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_lychee_torch", "Tensor marshalling of the per-token entry points.", -1,
+                      methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__lychee_torch() { return PyModule_Create(&module); }
