@@ -200,6 +200,7 @@ lc_index* new_handle(const lc_config* cfg, int B, int H, int d, void* buf, size_
     lc_layout_index(cfg, B, H, d, buf, &h->dev);
     h->T.assign(B, 0);
     h->M.assign(B, 0);
+    h->tail.assign(B, 0);
     h->N.assign((size_t)B * LC_MAX_LEVELS, 0);
     return h;
 }
@@ -328,9 +329,12 @@ int lc_build_index(lc_index** out, const lc_config* cfg, const void* K, const in
     lc_index* h = new_handle(cfg, B, H_kv, d, index_buf, index_bytes);
     if (!h) return LC_ERR_INVALID_ARG;
     int max_M = 0;
+    off = 0;
     for (int b = 0; b < B; ++b) {
         h->T[b] = seq_lens[b];
         h->M[b] = chunk_counts[b];
+        off += (size_t)chunk_counts[b] + 1;
+        h->tail[b] = seq_lens[b] - chunk_bounds[off - 1];
         if (h->M[b] > max_M) max_M = h->M[b];
     }
     fill_level_counts(h);
@@ -499,6 +503,20 @@ int decode_step_checks(const lc_index* idx, const void* q, const void* K, const 
     return LC_OK;
 }
 
+// Splits that can find work: the attention kernel gives a split at least LC_DEC_MIN_TOKENS_PER_SPLIT tokens, and a
+// (sequence, head) attends to at most its budget and its open tail (all its tokens if some are pinned).
+// Splits beyond that would only repeat the selection and count as arrived.
+int useful_splits(const lc_index* idx, int budget, int splits) {
+    long long most = 1;
+    for (int b = 0; b < idx->B; ++b) {
+        long long n = idx->T[b];
+        if (idx->cfg.sink_tokens == 0 && (long long)budget + idx->tail[b] < n) n = (long long)budget + idx->tail[b];
+        if (n > most) most = n;
+    }
+    const long long need = (most + LC_DEC_MIN_TOKENS_PER_SPLIT - 1) / LC_DEC_MIN_TOKENS_PER_SPLIT;
+    return need < splits ? (int)need : splits;
+}
+
 // The step itself on a laid-out workspace (every check has passed).
 int decode_step_run(const lc_index* idx, const LcWs& w, const RetrievePlan& p, int splits, const void* q,
                     const void* K, const void* V, const int64_t kv_strides[3], int H_q, int budget, float* out,
@@ -506,6 +524,7 @@ int decode_step_run(const lc_index* idx, const LcWs& w, const RetrievePlan& p, i
                     bool second_kernel_only = false) {
     const bool want_ids = chunk_ids != nullptr;
     const int G = H_q / idx->H_kv;
+    splits = useful_splits(idx, budget, splits);
     int rc;
     // Every workgroup of the fused kernel repeats the selection with 256 threads: with a few thousand
     // chunks that is cheaper than the hand-off through a chunk list, with more it is not.
@@ -657,7 +676,9 @@ int lc_append(lc_index* idx, void* K, void* V, const int64_t kv_strides[3], cons
     if (rc != LC_OK) return rc;
     for (int b = 0; b < idx->B; ++b) {
         idx->T[b] += 1;
+        idx->tail[b] += 1;
         if (close_chunk && close_chunk[b]) {
+            idx->tail[b] = 0;
             idx->M[b] += 1;
             idx->N[(size_t)b * LC_MAX_LEVELS + 0] = idx->M[b];
         }
@@ -875,6 +896,7 @@ int lc_index_import(lc_index** out, const lc_config* cfg, const void* blob, size
         if (bd[0] != 0 || bd[M] > T) { rc = LC_ERR_BAD_BLOB; break; }
         for (int j = 0; j < M; ++j)
             if (bd[j + 1] <= bd[j]) { rc = LC_ERR_BAD_BLOB; break; }
+        h->tail[b] = T - bd[M];
     }
     if (rc == LC_OK) {
         // validate the node records before touching the GPU

@@ -21,7 +21,6 @@
 #define LC_DEC_THREADS 256
 #endif
 #define LC_DEC_GROUPS (LC_DEC_THREADS / 16)
-#define LC_DEC_MIN_TOKENS_PER_SPLIT 64
 #define LC_DEC_MAX_SPLITS 256
 #define LC_DEC_TILE 1024          // tokens of a split whose cache rows are resolved into LDS at a time
 #define LC_DEC_E 2                // selected ids per thread and pass of the row resolution
@@ -81,6 +80,13 @@ __device__ __forceinline__ float lc_add_rows(float a, float b) {
     const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
+// maximum over the four 16-lane groups, in every lane
+__device__ __forceinline__ float lc_max_groups(float v) {
+    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(h[0]), __uint_as_float(h[1]));
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
 // exp2 of (x - ref) where x may be -inf (gives 0); ref is finite.
 __device__ __forceinline__ float lc_exp2_rel(float x, float ref) { return exp2f(x - ref); }
 
@@ -103,7 +109,7 @@ lc_decode_kernel(const LcDecodeArgs a) {
     __shared__ int last_sh;
     __shared__ float comb_ml[LC_DEC_THREADS / 64][G][2];
     __shared__ __attribute__((aligned(16))) float comb_acc[LC_DEC_THREADS / 64][G][LC_D];
-    __shared__ float mrg_s[LC_DEC_THREADS / 32][LC_DEC_MAX_SPLITS];
+    __shared__ float mrg_s[LC_DEC_THREADS / 32][LC_DEC_MAX_SPLITS + 128];
     __shared__ float4 mrg_red[LC_DEC_THREADS];
 
     // tokens per group and batch of loads; two batches are in flight per group (the next one is
@@ -350,12 +356,10 @@ lc_decode_kernel(const LcDecodeArgs a) {
         // up and spread over the groups by row swaps (lanes of group q4 keep columns 8 sub + 4 (q4 >> 1) +
         // 2 (q4 & 1) + {0, 1}), two vector instructions per pair of values; the waves meet in LDS
         {
-            float mx = fmaxf(m_run, __shfl_xor(m_run, 16));
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            const float mx = lc_max_groups(m_run);
             const float sc = lc_exp2_rel(m_run, (mx == LC_NEG_INF) ? 0.f : mx);
-            float l = l_run * sc;
-            l += __shfl_xor(l, 16);
-            l += __shfl_xor(l, 32);
+            float l = lc_add_halves(l_run * sc, l_run * sc);
+            l = lc_add_rows(l, l);
             if (lane < G) { comb_ml[wave][lane][0] = mx; comb_ml[wave][lane][1] = l; }
 #pragma unroll
             for (int g = 0; g < G; ++g) {
@@ -430,16 +434,24 @@ lc_decode_kernel(const LcDecodeArgs a) {
         m_all = fmaxf(m_all, lc_dpp<0x4E>(m_all));
         m_all = fmaxf(m_all, lc_dpp<0x141>(m_all));
         m_all = fmaxf(m_all, lc_dpp<0x140>(m_all));
-        m_all = fmaxf(m_all, __shfl_xor(m_all, 16));
-        for (int sp = hl; sp < n_part; sp += 32) {
-            const float ms = sp < 32 ? m0 : lc_load_agent(pml + 2 * (sp * G + g));
-            const float ls = sp < 32 ? l0 : lc_load_agent(pml + 2 * (sp * G + g) + 1);
+        {
+            const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(m_all), __float_as_uint(m_all), false, false);
+            m_all = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+        }
+        // (zero scales up to the end of the last round, whose slots past the last split repeat it)
+        const int n_slots = (n_part + MR * WAYS - 1) / (MR * WAYS) * (MR * WAYS);
+        for (int sp = hl; sp < n_slots; sp += 32) {
+            float ms = m0, ls = l0;
+            if (sp >= 32) {
+                ms = sp < n_part ? lc_load_agent(pml + 2 * (sp * G + g)) : LC_NEG_INF;
+                ls = sp < n_part ? lc_load_agent(pml + 2 * (sp * G + g) + 1) : 0.f;
+            }
             const float sc = (ms == LC_NEG_INF) ? 0.f : exp2f(ms - m_all);
             mrg_s[half][sp] = sc;
             den = fmaf(ls, sc, den);
         }
         den = lc_sum16(den);
-        den += __shfl_xor(den, 16);
+        den = lc_add_rows(den, den);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
     }
@@ -450,7 +462,7 @@ lc_decode_kernel(const LcDecodeArgs a) {
 #pragma unroll
             for (int k = 0; k < MR; ++k) {
                 const int sp = sp0 + k * WAYS;
-                const float sc = sp < n_part ? mrg_s[half][sp] : 0.f;
+                const float sc = mrg_s[half][sp];
                 acc4.x = fmaf(x[k].x, sc, acc4.x);
                 acc4.y = fmaf(x[k].y, sc, acc4.y);
                 acc4.z = fmaf(x[k].z, sc, acc4.z);
@@ -540,9 +552,13 @@ bool lc_decode_fused_fits(int G, int max_M) {
 template <int G, int EC>
 static int launch_fused_ge(const LcDecodeArgs& a, int splits, hipStream_t stream) {
     const size_t lds = (size_t)EC * LC_DEC_THREADS * 12;      // the selection's chunk lists
-    if (lds > 16 * 1024)        // static + dynamic may pass the default per-workgroup allowance
-        LC_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(&lc_decode_kernel<G, true, EC>),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    if (lds > 16 * 1024) {      // static + dynamic may pass the default per-workgroup allowance: raised once per device
+        static LcOnce raised;
+        LC_HIP_CHECK(raised.run([&] {
+            return hipFuncSetAttribute(reinterpret_cast<const void*>(&lc_decode_kernel<G, true, EC>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        }));
+    }
     hipLaunchKernelGGL((lc_decode_kernel<G, true, EC>), dim3(splits, a.ix.H, a.ix.B), dim3(LC_DEC_THREADS), lds, stream, a);
     LC_HIP_CHECK(hipGetLastError());
     return LC_OK;

@@ -5,6 +5,7 @@
 #include <stdint.h>
 #include <stddef.h>
 
+#include <atomic>
 #include <vector>
 
 #include "lychee.h"
@@ -38,6 +39,7 @@ struct lc_index {
     std::vector<int> T;      // host mirror, per sequence
     std::vector<int> M;      // host mirror, per sequence
     std::vector<int> N;      // [B][LC_MAX_LEVELS] nodes per level (N[b][0] mirrors M)
+    std::vector<int> tail;   // host mirror, per sequence: tokens behind the last closed chunk
 };
 
 // Layout of the index buffer: fills dev pointers from base; returns total bytes.
@@ -68,6 +70,7 @@ struct LcWs {
 // with_build = false leaves out the build scratch (directions, centroids): what a decode step needs.
 size_t lc_layout_ws(const lc_config* cfg, int B, int H_q, int H, int d, int splits, void* base, LcWs* ws,
                     bool with_build = true);
+#define LC_DEC_MIN_TOKENS_PER_SPLIT 64      // tokens of a split of the attention kernel, at least
 int lc_auto_splits(const lc_config* cfg, int B, int H);
 
 void lc_set_hip_error(hipError_t e);
@@ -79,6 +82,22 @@ void lc_set_hip_error(hipError_t e);
             return LC_ERR_HIP;                   \
         }                                        \
     } while (0)
+
+// Runs a call that has to succeed once per device (setting a kernel's attribute) and remembers that it did.
+struct LcOnce {
+    std::atomic<unsigned long long> done{0};     // one bit per device; devices beyond 63 run it every time
+    template <typename F>
+    hipError_t run(F f) {
+        int dev = 0;
+        const hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return e;
+        const unsigned long long bit = dev >= 0 && dev < 64 ? 1ull << dev : 0ull;
+        if (bit && (done.load(std::memory_order_acquire) & bit)) return hipSuccess;
+        const hipError_t r = f();
+        if (r == hipSuccess) done.fetch_or(bit, std::memory_order_release);
+        return r;
+    }
+};
 
 // lc_decode_step with a switch for the measurement aid that launches its second kernel alone
 // (C linkage: it is defined among the entry points).
