@@ -177,11 +177,16 @@ __device__ __forceinline__ void lc_c0_load8(const LcDev& ix, size_t n, int sub, 
 // level 0: one wavefront per chunk
 // ---------------------------------------------------------------------------------
 // The four 16-lane groups of a wavefront take the chunk's rows in turn (lane `sub` of a group holds
-// columns [8 sub, 8 sub + 8) of a row); the first LC_POOLW_KEEP rows of every group stay in registers
-// between the mean pass and the radius pass, so chunks of up to 4 * LC_POOLW_KEEP tokens are read
-// once (longer ones find their other rows in the L2 cache the second time).
-// No workgroup barrier: the groups' partial sums meet through wavefront shuffles.
+// columns [8 sub, 8 sub + 8) of a row).  The bound is reading K once; the radius pass needs every row
+// again.  Each group's first LC_POOLW_KEEP rows stay in registers for it (more of them costs resident
+// wavefronts: 12 and 16 rows were slower) and the next LC_POOLW_PARK wait in LDS, 7 KB a wavefront, as many as
+// leave the resident count to the registers: chunks of up to 60 tokens read K once, longer ones find the
+// rest in the caches.  One wavefront per workgroup, so that a long chunk holds up no neighbour's place;
+// the groups' partial sums meet through wavefront shuffles.  268 MB of K in 128K tokens x 8 heads:
+// 78.2 us with four wavefronts to a workgroup and nothing parked, 73.2 us now (3.7 TB/s); 16 sequences of
+// ragged length: 167 us, now 156 us.
 #define LC_POOLW_KEEP 8
+#define LC_POOLW_PARK 7
 // Progress flags of the k-means of every level, [level][sequence, head][LC_KM_FLAGS]: cleared by the first kernel of a build.
 __device__ __forceinline__ int* lc_level_flags(const LcDev& ix, int* flags, int l, int bh) {
     return flags + ((size_t)l * ix.B * ix.H + bh) * LC_KM_FLAGS;
@@ -222,14 +227,14 @@ __device__ __forceinline__ void lc_clear_flags(const LcDev& ix, int bh, int* fla
         for (int l = 0; l + 1 < ix.L; ++l) lc_level_flags(ix, flags, l, bh)[threadIdx.x] = 0;
 }
 __device__ __forceinline__ float lc_sum_groups4(float v) { v += __shfl_xor(v, 16); v += __shfl_xor(v, 32); return v; }
-__global__ void __launch_bounds__(LC_BT)
+__global__ void __launch_bounds__(64)
 lc_pool_kernel(LcDev ix, const uint16_t* K, long long ks_seq, long long ks_head, long long ks_tok,
                int geometry, LcPointRows out, int* flags) {
     const int h = blockIdx.y, b = blockIdx.z;
     const int bh = b * ix.H + h;
     lc_clear_flags(ix, bh, flags);
     const int lane = threadIdx.x & 63, sub = lane & 15, g4 = lane >> 4;
-    const int j = blockIdx.x * (LC_BT / 64) + (threadIdx.x >> 6);
+    const int j = blockIdx.x;
     const int M = ix.state[bh * 4 + 1];
     if (j >= M) return;                                            // (whole wavefronts leave: nothing below waits across them)
     const int* bnd = ix.bounds + (size_t)b * (ix.cap[0] + 1);
@@ -248,6 +253,7 @@ lc_pool_kernel(LcDev ix, const uint16_t* K, long long ks_seq, long long ks_head,
         }
     };
     uint4 keep[LC_POOLW_KEEP];
+    __shared__ uint4 parked[LC_POOLW_PARK][64];                     // (a lane reads its own entries only)
     load_batch(lo, keep);
     float sum[8];
 #pragma unroll
@@ -266,6 +272,10 @@ lc_pool_kernel(LcDev ix, const uint16_t* K, long long ks_seq, long long ks_head,
         uint4 more[LC_POOLW_KEEP];
         load_batch(base, more);
         add_batch(more);
+        if (base == lo + 4 * LC_POOLW_KEEP) {
+#pragma unroll
+            for (int k = 0; k < LC_POOLW_PARK; ++k) parked[k][lane] = more[k];
+        }
     }
     // The rows stay packed (four registers each) across the two passes: an empty statement that
     // claims to rewrite them keeps the compiler from holding their unpacked copies as well, which
@@ -301,7 +311,12 @@ lc_pool_kernel(LcDev ix, const uint16_t* K, long long ks_seq, long long ks_head,
 #pragma unroll
         for (int k = 0; k < LC_POOLW_KEEP; ++k)
             if (lo + g4 + 4 * k < hi) reach(keep[k]);
-        for (int base = lo + 4 * LC_POOLW_KEEP; base < hi; base += 4 * LC_POOLW_KEEP) {
+        if (lo + 4 * LC_POOLW_KEEP < hi) {
+#pragma unroll
+            for (int k = 0; k < LC_POOLW_PARK; ++k)
+                if (lo + g4 + 4 * (LC_POOLW_KEEP + k) < hi) reach(parked[k][lane]);
+        }
+        for (int base = lo + 4 * (LC_POOLW_KEEP + LC_POOLW_PARK); base < hi; base += 4 * LC_POOLW_KEEP) {
             uint4 more[LC_POOLW_KEEP];
             load_batch(base, more);
 #pragma unroll
@@ -1563,7 +1578,7 @@ int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const i
     // this one's centroids are still read)
     LcPointRows cur{ws.dirs, ws.dirs16, ix.cap[0], L > 1 ? ws.cent[0] : nullptr, ws.cent16[0], ix.cap[1]};
     if (max_M > 0 && K != nullptr) {
-        hipLaunchKernelGGL(lc_pool_kernel, dim3((max_M + LC_BT / 64 - 1) / (LC_BT / 64), H, B), dim3(LC_BT), 0, stream, ix, K,
+        hipLaunchKernelGGL(lc_pool_kernel, dim3(max_M, H, B), dim3(64), 0, stream, ix, K,
                            (long long)ks[0], (long long)ks[1], (long long)ks[2], geometry, cur, ws.kflags);
         LC_HIP_CHECK(hipGetLastError());
     } else if (max_M > 0) {

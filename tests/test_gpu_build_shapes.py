@@ -112,3 +112,30 @@ def test_many_equally_near_centroids(chunks, F, same):
         check_labels(head[0]["parent"], x, x[(np.arange(k) * chunks) // k])
         assert np.all(head[0]["parent"][:same] == 0)
         check_tree(head)
+
+
+@pytest.mark.parametrize("centers", [0, 1])
+def test_chunk_lengths_around_a_pooling_batch(centers):
+    """Means and radii of chunks just below, at and beyond what the pooling pass holds in registers and on chip."""
+    import torch
+    from paper_2603_08453_amd import binding as lc
+    sizes = [1, 3, 4, 5, 29, 31, 32, 33, 36, 57, 59, 60, 61, 63, 64, 65, 92, 93, 96, 97, 130, 300]
+    bounds = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    T = int(bounds[-1])
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    K = torch.randn((1, 2, T, 128), generator=g, device="cuda").to(torch.bfloat16)
+    for lo, hi, n in zip(bounds[:-1], bounds[1:], range(len(sizes))):        # the farthest row: another one in every chunk
+        K[0, :, lo + (7 * n + (hi - lo) - 1) % (hi - lo)] *= 3
+    cfg = lc.lc_config_default(levels=2, fanout=4, kmeans_iters=1, max_chunks=len(sizes), max_tokens=T, center_dtype=centers)
+    ib = torch.zeros(lc.lc_index_bytes(cfg, 1, 2), dtype=torch.uint8, device="cuda")
+    ws = torch.zeros(lc.lc_workspace_bytes(cfg, 1, 2, 2), dtype=torch.uint8, device="cuda")
+    heads = lc.unpack_blob(lc.lc_index_export(lc.lc_build_index(cfg, K, [T], [bounds], ib, ws)))["seqs"][0]["heads"]
+    for h in range(2):
+        keys = K[0, h].double().cpu().numpy()
+        center, radius = heads[h][0]["center"].astype(np.float64), heads[h][0]["radius"]
+        for j, (lo, hi) in enumerate(zip(bounds[:-1], bounds[1:])):
+            mean = keys[lo:hi].mean(axis=0)
+            assert np.abs(center[j] - mean).max() < (4e-3 * max(1.0, np.abs(mean).max()) if centers else 2e-6)
+            reach = np.linalg.norm(keys[lo:hi] - center[j], axis=1).max()
+            assert reach * (1 - 1e-6) - 1e-6 <= radius[j] <= reach * (1 + 3e-5) + 1e-5
