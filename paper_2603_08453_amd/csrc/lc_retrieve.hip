@@ -22,8 +22,12 @@
 // and nothing reads global memory element by element inside a dependent loop.
 #include "lc_device.h"
 #include "lc_internal.h"
+#include "lc_select.h"
 #include "lc_walk_layout.h"
 
+#include <type_traits>
+
+#define LC_INLINE __attribute__((always_inline))       // (lambdas that hold registers by reference)
 #define LC_TAU_SLACK 1e-3f
 #define LC_COUNT_SELECT_MAX 1024         // up to this many candidates the O(n^2 / threads) rank is used
 
@@ -52,13 +56,11 @@ struct LcRetrieveArgs {
 };
 
 // Selection among n <= LC_COUNT_SELECT_MAX candidates whose keys / weights sit in 16-byte aligned,
-// zero-padded LDS arrays.
-//   mode 0: keep the longest prefix with weight <= W and count <= C  (exact ties by index)
-//   mode 1: keep the shortest prefix whose weight reaches W (everything if it never does)
+// zero-padded LDS arrays: keeps the shortest prefix whose weight reaches W (everything if it never does).
 // Writes flags[i] for i < n.  With REDUCE it also returns, in every thread, the smallest kept key
-// (0 if nothing kept) and whether the kept weight reached W (mode 1); that costs three barriers.
+// (0 if nothing kept) and whether the kept weight reached W; that costs three barriers.
 template <int NT, bool REDUCE>
-__device__ __forceinline__ void lc_small_select(int n, int mode, long long W, long long C, const uint32_t* keys,
+__device__ __forceinline__ void lc_small_select(int n, long long W, const uint32_t* keys,
                                                 const int* wgts, uint8_t* flags, int* sh, uint32_t* min_kept,
                                                 int* reached) {
     uint32_t mk = 0xffffffffu;
@@ -72,11 +74,8 @@ __device__ __forceinline__ void lc_small_select(int n, int mode, long long W, lo
         int keep = 0;
         if (ki != 0u) {
             const int wi = wgts[i];
-            if (mode == 0) keep = ((long long)wb + wi <= W && (long long)cb + 1 <= C) ? 1 : 0;
-            else {
-                keep = ((long long)wb < W) ? 1 : 0;
-                if (keep && (long long)wb + wi >= W) hit = 1;
-            }
+            keep = ((long long)wb < W) ? 1 : 0;
+            if (keep && (long long)wb + wi >= W) hit = 1;
         }
         if (part == 0 && i < n) flags[i] = (uint8_t)keep;
         if (keep) mk = min(mk, ki);
@@ -247,7 +246,7 @@ lc_upper_kernel(const LcRetrieveArgs a) {
         {
             // EXACT, probe pass: keep the best frontier nodes until their subtree token counts reach the budget
             if (n_l <= LC_COUNT_SELECT_MAX) {
-                lc_small_select<LC_UP_THREADS, false>(n_l, 1, (long long)a.budget, 0x7fffffffLL, ek, ew, kp + o, sel_sh, &mk, &reached);
+                lc_small_select<LC_UP_THREADS, false>(n_l, (long long)a.budget, ek, ew, kp + o, sel_sh, &mk, &reached);
             } else {
                 auto keyf = [&](int i) -> uint32_t { return ek[i]; };
                 auto wf = [&](int i) -> int { return ew[i]; };
@@ -335,7 +334,7 @@ lc_upper_kernel(const LcRetrieveArgs a) {
         uint32_t cut = 0u;
         int reached = 0;
         if (n_probe <= LC_COUNT_SELECT_MAX) {
-            lc_small_select<LC_UP_THREADS, true>(n_probe, 1, (long long)a.budget, 0x7fffffffLL, pkey, plen,
+            lc_small_select<LC_UP_THREADS, true>(n_probe, (long long)a.budget, pkey, plen,
                                                  reinterpret_cast<uint8_t*>(ekA), sel_sh, &cut, &reached);
         } else {
             auto keyf = [&](int i) -> uint32_t { return pkey[i]; };
@@ -367,343 +366,618 @@ lc_upper_kernel(const LcRetrieveArgs a) {
 
 
 // ---------------------------------------------------------------------------------
-// top-k per level (Algorithm 1): the whole retrieval in one workgroup per (sequence, head)
+// top-k per level (Algorithm 1): the whole retrieval in one workgroup per (sequence, KV head)
 // ---------------------------------------------------------------------------------
 // Only the children of the kept nodes are ever scored, so the work follows the beam sizes, not the
 // size of the index: per level, score the candidate list (ascending node order, so that equal
-// scores fall to the lower id), rank it, mark the kept nodes in a bitmap, gather their children.
+// scores fall to the lower id), keep the best, mark them in a bitmap, gather their children.
 // The chunks under the kept level-1 nodes are scored the same way, cut by the token budget (and the
 // chunk-count limit beam[0]) and written out in ascending order behind the pinned chunks.
-// The lists live in LDS while a level's candidates number at most `chunk_cap`; a longer list goes
-// to the workspace (same code through generic pointers, slower).
+//
+// One compute unit works on a (sequence, head), one stage after the other: what bounds it is the chain of
+// memory round trips, and the unit's instruction rate -- an instruction that all sixteen wavefronts execute takes
+// 16 cycles.  So
+//   - everything whose address does not depend on a result is on its way before the first wait: the query,
+//     the top level's first rows, and the parent pointers of all levels straight into LDS (those that fit:
+//     the upper levels first);
+//   - a group of 16 lanes scores four nodes at a time (lc_score4_packed), the best are found by one wavefront from a
+//     histogram of 64 bins (lc_wave_cut), a list is written from the lanes' marks by one scan and one
+//     exchange of counts (gather below);
+//   - all levels run through one loop, so that the later ones find its code in the instruction cache;
+//   - the lists are in LDS, and code that reads them knows that they are (an address that may be either
+//     LDS or memory costs a wait for both); a list longer than `list_slots` goes to the workspace.
+// 10.9 K chunks under 5461 and 249 nodes, 43 and 8 of them kept, 8 heads: 34.7 us with a copy of the code per level,
+// every node scored by itself and ranks by counting, 25.2 us now; 2275 chunks under four levels: 26 and 24.4 us.
 #define LC_BM_THREADS 1024
+#define LC_BM_WAVES (LC_BM_THREADS / 64)
 #define LC_BM_GROUPS (LC_BM_THREADS / 16)
-#define LC_BM_KEPT_WORDS 2048             // kept bitmap: up to 65536 nodes per internal level
-#define LC_BM_MAX_LEVEL_NODES (LC_BM_KEPT_WORDS * 32)
-#define LC_BM_PF 4                       // chunks per thread whose parent and boundary are fetched at kernel start
-#define LC_BM_RANK_MAX 128               // chunk lists up to this length are ranked directly, longer ones by histogram
+#define LC_BM_MAX_LEVEL_NODES 65536       // marks of kept nodes: one byte each in LDS
+#define LC_BM_CUT_MAX 1024               // lists up to this length are cut by one wavefront, longer ones by the workgroup
+#define LC_BM_STATIC_LDS (8 * 1024)      // what the kernel's own arrays take, rounded up
+#define LC_BM_SPAN 8                     // blocks of 4096 items that one pass of the gather looks at
 
+// The kernel's arguments by level, from the top (0) to the chunks (L - 1): what a level needs is together, and the
+// top level's part has a fixed address in the argument block (an entry that is looked up by a number known
+// only at run time waits for its own read of that block).
+struct LcBeamLevel {
+    const float* center;
+    const float* radius;
+    const int* nchunk;
+    const int* parent;
+    int cap, beam;
+    int par_words;           // LDS words its parent pointers take
+};
+struct LcBeamArgs {
+    LcBeamLevel lev[LC_MAX_LEVELS];
+    const uint16_t* q;
+    const int* bounds;
+    const int* state;
+    const int* nlev;
+    float* scores;
+    int32_t* ids;
+    int32_t* counts;
+    int* scratch;
+    int H, L, cap0, cap, budget, sink, c0_bf16;
+    int list_slots;          // LDS entries of each candidate list
+    int kept_words;          // LDS words for the marks of kept nodes
+    int par_slots;           // LDS words for parent pointers
+};
 
-template <int G>
-__global__ void __launch_bounds__(LC_BM_THREADS)
-lc_beam_kernel(const LcRetrieveArgs a) {
-    extern __shared__ int lds_dyn[];
-    __shared__ LcLeafSelSh leaf_sh;
-    __shared__ int sel_sh[LC_SEL_SH];
-    __shared__ uint32_t kept[LC_BM_KEPT_WORDS];
-    constexpr int NB = G <= 6 ? 2 : 1;            // nodes in flight per group (the lists are short; 128 registers per lane)
-
-    const LcDev& ix = a.ix;
-    const int h = blockIdx.x, b = blockIdx.y;
-    const int bh = b * ix.H + h;
-    const int tid = threadIdx.x;
-    const int sub = tid & 15, grp = tid >> 4;
-    const int L = ix.L;
-    const int cap0 = ix.cap[0];
-    const int M = min(ix.state[bh * 4 + 1], cap0);
-    const int* bnd = ix.bounds + (size_t)b * (cap0 + 1);
-
-    // candidate lists: ids of the current level, ids of the next, keys, weights, kept flags
-    const int CL = a.chunk_cap;
-    const LcBeamLayout ly = lc_beam_layout(CL);
-    char* const lds_b = reinterpret_cast<char*>(lds_dyn);
-    int* const l_cid = reinterpret_cast<int*>(lds_b + ly.cid);
-    int* const l_nxt = reinterpret_cast<int*>(lds_b + ly.nxt);
-    uint32_t* const l_key = reinterpret_cast<uint32_t*>(lds_b + ly.key);
-    int* const l_wgt = reinterpret_cast<int*>(lds_b + ly.wgt);
-    uint8_t* const l_flg = reinterpret_cast<uint8_t*>(lds_b + ly.flg);
-    int* const gs = a.scratch + (size_t)bh * 4 * cap0;
-    int* const g_cid = gs;
-    int* const g_nxt = gs + cap0;
-    uint32_t* const g_key = reinterpret_cast<uint32_t*>(gs + 2 * cap0);
-    int* const g_wgt = gs + 3 * cap0;
-    uint8_t* const g_flg = a.want + (size_t)bh * cap0;
-
-    constexpr bool QP = G > 2;                   // (see lc_upper_kernel; this kernel waits for memory, not for the ALU)
-    float qf[QP ? 1 : G][8], qn[G];
-    uint32_t qp[QP ? G : 1][4];
-    if constexpr (QP) lc_load_query_packed<G>(a.q + (size_t)b * ix.H * G * LC_D, h, sub, qp, qn);
-    else lc_load_query_frags<G>(a.q + (size_t)b * ix.H * G * LC_D, h, sub, qf, qn);
-    auto score_node = [&](const LcNodeFrag& f, float R) -> float {
-        if constexpr (QP) return lc_score_frag_packed<G>(f, R, qp, qn);
-        else return lc_score_frag<G>(f, R, qf, qn);
+// Bins of a key range [a, b], 64 of them: even steps of the score (keys of scores of both signs crowd around zero)
+// or of the key.  Higher keys are in the same bin or a higher one.
+struct LcKeyBins {
+    uint32_t a, b;
+    float s_lo, step;
+    int shift;
+    bool by_score;
+    __device__ __forceinline__ void over(uint32_t lo, uint32_t hi, bool score) {
+        a = lo;
+        b = hi;
+        const uint32_t span = b - a;
+        shift = span >= 64u ? 26 - __clz((int)span) : 0;             // (span >> shift) < 64
+        s_lo = lc_key_score(a);
+        step = 64.0f * __builtin_amdgcn_rcpf(lc_key_score(b) - s_lo);
+        by_score = score && step > 0.f && step < 1e30f;             // (not for one key, nor for infinities)
+    }
+    __device__ __forceinline__ int of(uint32_t k) const {            // -1: not in the range, or no candidate
+        const int by_s = min(max((int)((lc_key_score(k) - s_lo) * step), 0), 63);
+        return k >= a && k <= b && k != 0u ? (by_score ? by_s : (int)((k - a) >> shift)) : -1;
+    }
+};
+// The longest prefix (key descending, position ascending) of at most C candidates, and if `weighted` of total weight
+// <= W, of a list in LDS: candidate i is in it iff key[i] > the returned value; keys at the cut have been replaced by
+// the highest value (in) or 0 (not).  64 bins over the range of the keys, a scan from the top for the bin in which
+// the prefix ends, and that bin's candidates ranked against each other; a bin of more than 64 is split again.
+// One wavefront's work: an instruction that all sixteen wavefronts of a workgroup execute costs their compute
+// unit 16 cycles, so what one of them can do alone is not shared out (249 candidates ranked against each other by
+// all wavefronts: 6 us; halving the key range: 3 us; here: 2 us).  `hist`: 192 ints of LDS.
+__device__ __forceinline__ uint32_t lc_wave_cut(int n, uint32_t* key, const int* wgt, bool weighted, int W, int C, int* hist) {
+    const int lane = threadIdx.x & 63;
+    const bool counted = C < 0x7fffffff;
+    auto four = [&](int i0, uint32_t (&k)[4]) LC_INLINE {           // candidates i0 + lane + 64 r; past the end: key 0
+        const int last = n - 1;
+        uint32_t x[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[r] = key[min(i0 + 64 * r + lane, last)];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) k[r] = i0 + 64 * r + lane < n ? x[r] : 0u;
     };
-
-    // What the chunk stage will need much later -- parents and boundaries of this thread's first
-    // LC_BM_PF chunks (thread t looks at the chunks [t E, t E + E), E = ceil(M / threads)) -- is
-    // fetched now: the arrays are cap0 long, so only the count has to arrive first.
-    const int* par0 = ix.parent[0] + (size_t)bh * cap0;
-    const int EM = (M + LC_BM_THREADS - 1) / LC_BM_THREADS;
-    const int j_lo = min(M, tid * EM), j_hi = min(M, j_lo + EM);
-    int pf_p[LC_BM_PF], pf_s[LC_BM_PF];
+    uint32_t lo = 0xffffffffu, hi = 0u;
+    for (int i0 = 0; i0 < n; i0 += 256) {
+        uint32_t k[4];
+        four(i0, k);
 #pragma unroll
-    for (int k = 0; k < LC_BM_PF; ++k) {
-        const int j = min(j_lo + k, cap0 - 1);
-        pf_p[k] = L > 1 ? par0[j] : 0;
-        pf_s[k] = bnd[j];
+        for (int r = 0; r < 4; ++r) { lo = min(lo, k[r] - 1u); hi = max(hi, k[r]); }      // (key 0 wraps to the largest value: ignored)
     }
-
-    // optional score output: everything that is never scored reads -inf
-    float* scores = a.scores ? a.scores + (size_t)bh * cap0 : nullptr;
-    if (scores)
-        for (int j = tid; j < M; j += LC_BM_THREADS) scores[j] = LC_NEG_INF;
-
-    // ---- top level: every node is a candidate
-    int n_c = L > 1 ? ix.nlev[b * LC_MAX_LEVELS + (L - 1)] : 0;
-    bool in_lds = n_c <= CL;
-    int* cid = in_lds ? l_cid : g_cid;
-    for (int i = tid; i < n_c; i += LC_BM_THREADS) cid[i] = i;
-    __syncthreads();
-
-    for (int l = L - 1; l >= 1; --l) {
-        uint32_t* key = in_lds ? l_key : g_key;
-        int* wgt = in_lds ? l_wgt : g_wgt;
-        uint8_t* flg = in_lds ? l_flg : g_flg;
-        // ---- score the candidates of this level
-        for (int i0 = grp; i0 < n_c; i0 += NB * LC_BM_GROUPS) {
-            LcNodeFrag f[NB];
-            float R[NB];
-            int nc[NB];
+    uint32_t a = lc_wave_min_uniform(lo) + 1u, b = lc_wave_max_uniform(hi);               // range that is still open
+    LcKeyBins bins;
+    bins.over(a, b, true);
+    for (;;) {
+        hist[lane] = 0;
+        hist[64 + lane] = 0;
+        for (int i0 = 0; i0 < n; i0 += 256) {
+            uint32_t k[4];
+            four(i0, k);
 #pragma unroll
-            for (int k = 0; k < NB; ++k) {
-                const size_t n = (size_t)bh * ix.cap[l] + cid[min(i0 + k * LC_BM_GROUPS, n_c - 1)];
-                f[k] = lc_load_node(ix.center[l] + n * LC_D, sub);
-                R[k] = ix.radius[l][n];
-                nc[k] = ix.nchunk[l][n];
-            }
-#pragma unroll
-            for (int k = 0; k < NB; ++k) {
-                const int i = i0 + k * LC_BM_GROUPS;
-                float sc = score_node(f[k], R[k]);
-                if (nc[k] <= 0) sc = LC_NEG_INF;
-                if (sub == 0 && i < n_c) { key[i] = lc_score_key(sc); wgt[i] = 0; }
+            for (int r = 0; r < 4; ++r) {
+                // (no branch around the additions: what is no candidate adds to a slot that nobody reads)
+                const int bin = bins.of(k[r]), slot = bin >= 0 ? 63 - bin : 128 + lane;
+                if (weighted) atomicAdd(&hist[slot], wgt[min(i0 + 64 * r + lane, n - 1)]);
+                if (counted) atomicAdd(&hist[bin >= 0 ? slot + 64 : slot], 1);
             }
         }
-        if (in_lds && tid < 4 && n_c + tid < ((n_c + 3) & ~3)) { key[n_c + tid] = 0u; wgt[n_c + tid] = 0; }
-        __syncthreads();
-        // ---- keep the beam[l] best
-        const long long C = a.beam[l] > 0 ? a.beam[l] : 0x7fffffffLL;
-        if (in_lds && n_c <= LC_COUNT_SELECT_MAX) {
-            uint32_t mk;
-            int reached;
-            lc_small_select<LC_BM_THREADS, false>(n_c, 0, 0x7fffffffffffLL, C, key, wgt, flg, sel_sh, &mk, &reached);
-        } else {
-            auto keyf = [&](int i) -> uint32_t { return key[i]; };
-            auto wf = [&](int) -> int { return 0; };
-            const LcSel r = lc_block_select<LC_BM_THREADS>(n_c, 0x7fffffffffffLL, C, keyf, wf, sel_sh);
-            int tie_c = 0;
-            for (int t0 = 0; t0 < n_c; t0 += LC_BM_THREADS) {
-                const int i = t0 + tid;
-                const uint32_t k = (i < n_c) ? key[i] : 0u;
-                const int eq = (!r.all && k != 0u && k == r.kstar) ? 1 : 0;
-                int tot;
-                const int ex = lc_block_scan<LC_BM_THREADS>(eq, sel_sh, &tot);
-                if (i < n_c) flg[i] = (k != 0u && (k > r.kstar || (eq && tie_c + ex + 1 <= r.remC))) ? 1 : 0;
-                tie_c += tot;
-            }
-        }
-        // ---- bitmap of the kept nodes
-        const int n_l = ix.nlev[b * LC_MAX_LEVELS + l];
-        for (int i = tid; i < (n_l + 31) / 32; i += LC_BM_THREADS) kept[i] = 0u;
-        __syncthreads();
-        for (int i = tid; i < n_c; i += LC_BM_THREADS)
-            if (flg[i]) atomicOr(&kept[cid[i] >> 5], 1u << (cid[i] & 31));
-        __syncthreads();
-        if (l == 1) break;
-        // ---- the kept nodes' children, in ascending order: count them, pick where the list goes, write it
-        const int n_b = ix.nlev[b * LC_MAX_LEVELS + (l - 1)];
-        const int* par = ix.parent[l - 1] + (size_t)bh * ix.cap[l - 1];
-        auto is_child = [&](int i) -> int {
-            if (i >= n_b) return 0;
-            const int p = par[i];
-            return (p >= 0 && p < n_l && ((kept[p >> 5] >> (p & 31)) & 1u)) ? 1 : 0;
-        };
-        // (thread t looks at the nodes [t E, t E + E): one count, one scan, one write pass.  The parent
-        // pointers are fetched in batches of eight with no branch around the loads -- a memory round
-        // trip per batch, not per node -- and the verdicts of the first 32 nodes stay in a register mask.)
-        const int E = (n_b + LC_BM_THREADS - 1) / LC_BM_THREADS;
-        const int i_lo = min(n_b, tid * E), i_hi = min(n_b, i_lo + E);
-        const int i_last = max(n_b - 1, 0);
-        unsigned vmask = 0u;
-        const int E_b = E > 4 ? min(E, 32) : 0;                   // short runs: node by node below
-        for (int k0 = 0; k0 < E_b; k0 += 8) {
-            int pv[8];
+        __builtin_amdgcn_wave_barrier();
+        const int hw = hist[lane], hc = hist[64 + lane];            // lane l: bin 63 - l
+        const int sw = weighted ? lc_wave_scan_incl(hw) : 0, sc = counted ? lc_wave_scan_incl(hc) : 0;
+        const unsigned long long over = __ballot(sw > W || sc > C);
+        if (over == 0ull) return a - 1u;                            // everything (that is open) fits
+        const int l = __ffsll((long long)over) - 1;                 // the prefix ends in this lane's bin
+        W -= lc_readlane(sw - hw, l);
+        C -= counted ? lc_readlane(sc - hc, l) : 0;
+        lo = 0xffffffffu;
+        hi = 0u;
+        int in = 0;
+        for (int i0 = 0; i0 < n; i0 += 256) {
+            uint32_t k[4];
+            four(i0, k);
 #pragma unroll
-            for (int k = 0; k < 8; ++k) pv[k] = par[min(i_lo + k0 + k, i_last)];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int pp = pv[k];
-                const bool in = i_lo + k0 + k < i_hi && pp >= 0 && pp < n_l;
-                const uint32_t w = kept[in ? pp >> 5 : 0];
-                vmask |= (in && ((w >> (pp & 31)) & 1u)) ? 1u << (k0 + k) : 0u;
+            for (int r = 0; r < 4; ++r) {
+                const bool here = bins.of(k[r]) == 63 - l;
+                const unsigned long long m = __ballot(here);
+                const int at = in + lc_mbcnt(m);
+                if (here && at < 64) hist[at] = i0 + 64 * r + lane;
+                in += __popcll(m);
+                lo = min(lo, here ? k[r] : 0xffffffffu);
+                hi = max(hi, here ? k[r] : 0u);
             }
         }
-        int n_new = 0, mine = __popc(vmask);
-        for (int i = i_lo + E_b; i < i_hi; ++i) mine += is_child(i);
-        int pos = lc_block_scan<LC_BM_THREADS>(mine, sel_sh, &n_new);
-        const bool nxt_lds = n_new <= CL;
-        int* nxt = nxt_lds ? (cid == l_cid ? l_nxt : l_cid) : (cid == g_cid ? g_nxt : g_cid);
-        if (mine > 0) {
-            while (vmask != 0u) {
-                nxt[pos++] = i_lo + __ffs((int)vmask) - 1;
-                vmask &= vmask - 1u;
+        if (in <= 64) {
+            // few enough to rank: lane c has the c-th of them (in order of position)
+            const int me = hist[min(lane, in - 1)];
+            const uint32_t mine = key[me];
+            const int w = weighted ? wgt[me] : 0;
+            int c_before = 0, w_before = 0;
+            for (int c = 0; c < in; ++c) {
+                const uint32_t k = (uint32_t)lc_readlane((int)mine, c);
+                const bool before = k > mine || (k == mine && c < lane);
+                c_before += before ? 1 : 0;
+                w_before += before ? lc_readlane(w, c) : 0;
             }
-            for (int i = i_lo + E_b; i < i_hi; ++i)
-                if (is_child(i)) nxt[pos++] = i;
+            const bool keep = c_before < C && w_before + w <= W;
+            b = lc_wave_max_uniform(hi);                            // (at least one of them is not kept)
+            if (lane < in) key[me] = keep ? 0xffffffffu : 0u;
+            return b;
         }
-        __syncthreads();
-        cid = nxt;
-        in_lds = nxt_lds;
-        n_c = n_new;
+        a = lc_wave_min_uniform(lo);
+        b = lc_wave_max_uniform(hi);
+        if (a == b) {                                               // equal keys are cut in order
+            for (int i0 = 0; i0 < n; i0 += 64) {
+                const int i = i0 + lane;
+                const bool tie = i < n && key[min(i, n - 1)] == b;
+                const unsigned long long e = __ballot(tie);
+                if (e == 0ull) continue;
+                const int inc = lc_wave_scan_incl(tie && weighted ? wgt[i] : 0);
+                const unsigned long long sel = __ballot(tie && inc <= W && lc_mbcnt(e) < C);
+                if (tie) key[i] = ((sel >> lane) & 1ull) ? 0xffffffffu : 0u;
+                W = sel == e ? W - lc_readlane(inc, 63) : -1;
+                C -= __popcll(sel);
+            }
+            return b;
+        }
+        bins.over(a, b, false);
     }
+}
 
-    // ---- chunks: children of the kept level-1 nodes (every chunk if the index has no level above
-    // them), without the pinned ones; the pinned chunks are the leading ones and are counted here
-    const int W = a.budget > 0 ? a.budget : 0;
-    const int n_1 = L > 1 ? ix.nlev[b * LC_MAX_LEVELS + 1] : 0;
-    auto chunk_state_of = [&](int j, int start, int p) -> int {        // 0 = not a candidate, 1 = candidate, 2 = pinned
-        if (j >= M) return 0;
-        if (start < a.sink) return 2;
-        if (W <= 0) return 0;
-        if (L == 1) return 1;
-        return (p >= 0 && p < n_1 && ((kept[p >> 5] >> (p & 31)) & 1u)) ? 1 : 0;
+// The same by a workgroup, for long lists (in LDS or in the workspace).  `sh`: 256 + 6 NT / 64 ints.  Begins behind a
+// barrier and ends with one.
+template <int NT>
+__device__ __forceinline__ uint32_t lc_block_cut(int n, uint32_t* key, const int* wgt, bool weighted, int W, int C, int* sh) {
+    constexpr int NW = NT / 64;
+    static_assert(NW == 16, "a row of 16 lanes goes over the wavefronts' parts");
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const bool counted = C < 0x7fffffff;
+    int* const slots = sh + 256;
+    uint32_t lo = 0xffffffffu, hi = 0u;
+    int in = 0, turn = 0;
+    for (int i = threadIdx.x; i < n; i += NT) { const uint32_t k = key[i]; lo = min(lo, k - 1u); hi = max(hi, k); }
+    LcKeyBins bins;
+    // lowest and highest key and number over the workgroup; the next histogram is emptied meanwhile
+    auto exchange = [&]() LC_INLINE {
+        lo = lc_wave_min_uniform(lo);
+        hi = lc_wave_max_uniform(hi);
+        in = lc_wave_sum_i(in);
+        int* const s = slots + turn * 3 * NW;
+        if (lane == 0) { s[wave] = (int)lo; s[NW + wave] = (int)hi; s[2 * NW + wave] = in; }
+        if (threadIdx.x < 128) sh[turn * 128 + threadIdx.x] = 0;
+        __syncthreads();
+        lo = lc_wave_min_uniform((uint32_t)s[lane & 15]);
+        hi = lc_wave_max_uniform((uint32_t)s[NW + (lane & 15)]);
+        in = lc_readlane(lc_sum16_i(s[2 * NW + (lane & 15)]), 0);
     };
-    auto chunk_state = [&](int j) -> int { return j < M ? chunk_state_of(j, bnd[j], L > 1 ? par0[j] : 0) : 0; };
-    int n_pin = 0;
-    n_c = 0;
-    {
-        // (the verdicts of a thread's first 32 chunks stay in a register mask: those of the prefetched
-        // chunks, then batches of eight whose parents and boundaries are fetched together with no
-        // branch around the loads; longer runs read memory chunk by chunk)
-        unsigned cand = 0u;
-        int pins = 0;
-#pragma unroll
-        for (int k = 0; k < LC_BM_PF; ++k) {
-            const int st = j_lo + k < j_hi ? chunk_state_of(j_lo + k, pf_s[k], pf_p[k]) : 0;
-            cand |= st == 1 ? 1u << k : 0u;
-            pins += st == 2 ? 1 : 0;
-        }
-        const int j_last = max(M - 1, 0);
-        for (int k0 = LC_BM_PF; k0 < min(EM, 32); k0 += 8) {
-            int pv[8], sv[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int j = min(j_lo + k0 + k, j_last);
-                pv[k] = L > 1 ? par0[j] : 0;
-                sv[k] = bnd[j];
-            }
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int st = (k0 + k < 32 && j_lo + k0 + k < j_hi) ? chunk_state_of(j_lo + k0 + k, sv[k], pv[k]) : 0;
-                cand |= st == 1 ? 1u << (k0 + k) : 0u;
-                pins += st == 2 ? 1 : 0;
+    exchange();
+    uint32_t a = lo + 1u, b = hi;
+    bins.over(a, b, true);
+    for (;;) {
+        int* const hist = sh + turn * 128;
+        for (int i = threadIdx.x; i < n; i += NT) {
+            const int bin = bins.of(key[i]);
+            if (bin >= 0) {
+                if (weighted) atomicAdd(&hist[63 - bin], wgt[i]);
+                if (counted) atomicAdd(&hist[127 - bin], 1);
             }
         }
-        int mine = __popc(cand);
-        for (int j = j_lo + 32; j < j_hi; ++j) {
-            const int st = chunk_state(j);
-            mine += st == 1 ? 1 : 0;
-            pins += st == 2 ? 1 : 0;
+        __syncthreads();
+        const int hw = hist[lane], hc = hist[64 + lane];
+        const int sw = weighted ? lc_wave_scan_incl(hw) : 0, sc = counted ? lc_wave_scan_incl(hc) : 0;
+        const unsigned long long over = __ballot(sw > W || sc > C);
+        if (over == 0ull) {
+            b = a - 1u;
+            break;
         }
-        int pos, e1;
-        lc_block_scan2<LC_BM_THREADS>(mine, pins, sel_sh, &pos, &e1, &n_c, &n_pin);
-        in_lds = n_c <= CL;
-        int* nxt = in_lds ? (cid == l_cid ? l_nxt : l_cid) : (cid == g_cid ? g_nxt : g_cid);
-        if (mine > 0) {
-            while (cand != 0u) {
-                nxt[pos++] = j_lo + __ffs((int)cand) - 1;
-                cand &= cand - 1u;
-            }
-            for (int j = j_lo + 32; j < j_hi; ++j)
-                if (chunk_state(j) == 1) nxt[pos++] = j;
+        const int l = __ffsll((long long)over) - 1;
+        W -= lc_readlane(sw - hw, l);
+        C -= counted ? lc_readlane(sc - hc, l) : 0;
+        lo = 0xffffffffu;
+        hi = 0u;
+        in = 0;
+        for (int i = threadIdx.x; i < n; i += NT) {
+            const uint32_t k = key[i];
+            if (bins.of(k) == 63 - l) { lo = min(lo, k); hi = max(hi, k); ++in; }
         }
-        cid = nxt;
-    }
-    lc_leaf_select_prepare<LC_BM_THREADS>(leaf_sh);
-    __syncthreads();
-    uint32_t* key = in_lds ? l_key : g_key;
-    int* wgt = in_lds ? l_wgt : g_wgt;
-    // ---- score them: key and length per candidate
-    {
-        const size_t cb = (size_t)bh * cap0;
-        const bool c0b = ix.c0_bf16 != 0;
-        uint32_t kmin = 0xffffffffu, kmax = 0u;
-        constexpr int NBC = G <= 2 ? 4 : (G <= 4 ? 3 : NB);     // (little else is live here)
-        for (int i0 = grp; i0 < n_c; i0 += NBC * LC_BM_GROUPS) {
-            LcNodeFrag f[NBC];
-            float R[NBC];
-            int s0[NBC], s1[NBC], jj[NBC];
-#pragma unroll
-            for (int k = 0; k < NBC; ++k) {
-                const int j = cid[min(i0 + k * LC_BM_GROUPS, n_c - 1)];
-                jj[k] = j;
-                f[k] = lc_load_chunk_node(ix.center[0], c0b, cb + j, sub);
-                R[k] = ix.radius[0][cb + j];
-                s0[k] = bnd[j];
-                s1[k] = bnd[j + 1];
-            }
-#pragma unroll
-            for (int k = 0; k < NBC; ++k) {
-                const int i = i0 + k * LC_BM_GROUPS;
-                const float sc = score_node(c0b ? lc_widen_chunk_frag(f[k]) : f[k], R[k]);
-                uint32_t kk = lc_score_key(sc);
-                if (kk == 0xffffffffu) kk = 0xfffffffeu;           // the select routine's mark is reserved
-                if (sub == 0 && i < n_c) {
-                    key[i] = kk;
-                    wgt[i] = max(0, s1[k] - s0[k]);
-                    if (scores) scores[jj[k]] = sc;
+        turn ^= 1;
+        exchange();
+        a = lo;
+        b = hi;
+        if (in == 1) break;
+        if (a == b) {
+            if (wave == 0) {
+                for (int i0 = 0; i0 < n; i0 += 64) {
+                    const int i = i0 + lane;
+                    const bool tie = i < n && key[min(i, n - 1)] == b;
+                    const unsigned long long e = __ballot(tie);
+                    if (e == 0ull) continue;
+                    const int inc = lc_wave_scan_incl(tie && weighted ? wgt[i] : 0);
+                    const unsigned long long sel = __ballot(tie && inc <= W && lc_mbcnt(e) < C);
+                    if (tie) key[i] = ((sel >> lane) & 1ull) ? 0xffffffffu : 0u;
+                    W = sel == e ? W - lc_readlane(inc, 63) : -1;
+                    C -= __popcll(sel);
                 }
-                if (i < n_c && kk != 0u) { kmin = min(kmin, kk); kmax = max(kmax, kk); }
             }
+            break;
         }
-        lc_leaf_select_range(kmin, kmax, leaf_sh);
-    }
-    if (in_lds && tid < 4 && n_c + tid < ((n_c + 3) & ~3)) { key[n_c + tid] = 0u; wgt[n_c + tid] = 0; }
-    __syncthreads();
-    const long long C0 = a.beam[0] > 0 ? a.beam[0] : 0x7fffffffLL;
-    uint8_t* flg = in_lds ? l_flg : g_flg;
-    if (in_lds && n_c <= LC_BM_RANK_MAX) {
-        // a short list: every chunk is ranked against the others directly
-        uint32_t mk;
-        int reached;
-        lc_small_select<LC_BM_THREADS, false>(n_c, 0, (long long)W, C0, key, wgt, flg, sel_sh, &mk, &reached);
-    } else {
-        const uint32_t thr = lc_leaf_select<LC_BM_THREADS>(n_c, key, wgt, (long long)W, C0, leaf_sh);
-        __syncthreads();
-        for (int i = tid; i < n_c; i += LC_BM_THREADS) flg[i] = key[i] > thr ? 1 : 0;
+        bins.over(a, b, false);
     }
     __syncthreads();
-    // ---- the chunk list: pinned chunks (ids 0 .. n_pin - 1), then the selected candidates in ascending order
-    int32_t* ids = a.ids + (size_t)bh * a.cap;
-    for (int j = tid; j < min(n_pin, a.cap); j += LC_BM_THREADS) ids[j] = j;
-    int n_sel = 0;
-    {
-        const int E = (n_c + LC_BM_THREADS - 1) / LC_BM_THREADS;
-        const int i_lo = min(n_c, tid * E), i_hi = min(n_c, i_lo + E);
-        int mine = 0;
-        for (int i = i_lo; i < i_hi; ++i) mine += flg[i] ? 1 : 0;
-        int pos = n_pin + lc_block_scan<LC_BM_THREADS>(mine, sel_sh, &n_sel);
-        for (int i = i_lo; i < i_hi; ++i) {
-            if (flg[i]) {
-                if (pos < a.cap) ids[pos] = cid[i];
-                ++pos;
-            }
-        }
-    }
-    const int pos0 = n_pin + n_sel;
-    if (tid == 0) a.counts[bh] = min(pos0, a.cap);
+    return b;
 }
 
 template <int G>
-static int launch_beam_g(LcRetrieveArgs& a, int max_nodes, hipStream_t stream) {
-    // LDS lists for up to LC_BEAM_LIST_MAX candidates per level (more go to the workspace)
-    const int cl = lc_beam_list_slots(max_nodes);
-    a.chunk_cap = cl;
-    const size_t lds = (size_t)lc_beam_layout(cl).total;
-    if (lds + sizeof(LcLeafSelSh) + LC_SEL_SH * 4 + LC_BM_KEPT_WORDS * 4 + 256 > 48 * 1024)
+__global__ void __launch_bounds__(LC_BM_THREADS)
+lc_beam_kernel(const LcBeamArgs a) {
+    extern __shared__ int lds_dyn[];
+    __shared__ int cnt_sh[LC_BM_SPAN * LC_BM_WAVES];
+    __shared__ int hist_sh[256 + 6 * LC_BM_WAVES];       // (of either cut)
+    __shared__ uint32_t cut_sh;
+    constexpr int STEP = 4 * LC_BM_GROUPS;               // four nodes per group of 16 lanes at a time
+
+    const int h = blockIdx.x, b = blockIdx.y;
+    const int bh = b * a.H + h;
+    int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int sub = tid & 15, grp = tid >> 4;
+    const int L = a.L, bottom = L - 1;                   // levels are counted from the top here: 0 .. L - 1 (the chunks)
+    const int cap0 = a.cap0;
+    const size_t cb = (size_t)bh * cap0;
+    const bool c0b = a.c0_bf16 != 0;
+    const int* const n_lev = a.nlev + b * LC_MAX_LEVELS + (L - 1);      // nodes of level v: n_lev[-v]
+    const int* const bnd = a.bounds + (size_t)b * (cap0 + 1);
+    const int W = a.budget > 0 ? a.budget : 0;
+
+    // candidate lists: ids of the current level, ids of the next, keys, weights; in LDS up to CL entries, in the
+    // workspace beyond
+    const int CL = a.list_slots;
+    const LcBeamLayout ly = lc_beam_layout(CL);
+    int* l_cid = lds_dyn + ly.cid / 4;
+    int* l_nxt = lds_dyn + ly.nxt / 4;
+    uint32_t* const l_key = reinterpret_cast<uint32_t*>(lds_dyn + ly.key / 4);
+    int* const l_wgt = lds_dyn + ly.wgt / 4;
+    // behind them: a mark for each node of a level that is kept, and parent pointers
+    uint8_t* const kept = reinterpret_cast<uint8_t*>(lds_dyn + ly.total / 4);
+    const int KW = a.kept_words;                         // (a multiple of four: what follows is read 16 bytes at a time)
+    uint32_t* const kept_w = reinterpret_cast<uint32_t*>(kept);
+    int* const l_par = lds_dyn + ly.total / 4 + KW;
+    int* const gs = a.scratch + 4 * cb;
+    int* g_cid = gs;
+    int* g_nxt = gs + cap0;
+    uint32_t* const g_key = reinterpret_cast<uint32_t*>(gs + 2 * cap0);
+    int* const g_wgt = gs + 3 * cap0;
+
+    // ---- Candidates base + 4 grp .. + 3 of a list: their centers; radius and two integers, whose difference is a node's
+    // chunk count or a chunk's length, of number (sub & 3) of them (range-checked buffers: an address is one
+    // register, rows past the end read 0).
+    LcNodeFrag f[4];
+    float R;
+    int x0, x1, own;
+    auto load = [&](const LcBeamLevel& v, bool chunks, int valid, const int (&id)[4]) LC_INLINE {
+        const size_t at = (size_t)bh * v.cap;
+        const bool half = chunks && c0b;
+        const char* const base = reinterpret_cast<const char*>(v.center);
+        const __amdgpu_buffer_rsrc_t cen_r = lc_buffer(base + at * (half ? 2 * LC_D : 4 * LC_D), v.cap * (half ? 2 * LC_D : 4 * LC_D));
+        const __amdgpu_buffer_rsrc_t rad_r = lc_buffer(v.radius + at, v.cap * 4);
+        const __amdgpu_buffer_rsrc_t end_r = chunks ? lc_buffer(bnd + 1, cap0 * 4) : lc_buffer(v.nchunk + at, v.cap * 4);
+        const __amdgpu_buffer_rsrc_t beg_r = lc_buffer(bnd, chunks ? cap0 * 4 : 0);
+        if (16 * wave >= valid) return;                  // (whole wavefronts: rows nobody needs would take the cache's time)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (half) {
+                const lc_v2i x = __builtin_amdgcn_raw_buffer_load_b64(cen_r, id[k] * (LC_D * 2) + 8 * sub, 0, 0);
+                const lc_v2i y = __builtin_amdgcn_raw_buffer_load_b64(cen_r, id[k] * (LC_D * 2) + 8 * sub + 128, 0, 0);
+                f[k].a.x = __int_as_float(x.x); f[k].a.y = __int_as_float(x.y);
+                f[k].b.x = __int_as_float(y.x); f[k].b.y = __int_as_float(y.y);
+            } else {
+                f[k].a = lc_buf_load_f32x4(cen_r, id[k] * (LC_D * 4) + 16 * sub);
+                f[k].b = lc_buf_load_f32x4(cen_r, id[k] * (LC_D * 4) + 16 * sub + 256);
+            }
+        }
+        R = lc_buf_load_f32(rad_r, own);
+        x0 = lc_buf_load_i32(beg_r, own);
+        x1 = lc_buf_load_i32(end_r, own);
+    };
+    own = 4 * grp + (sub & 3);
+    {
+        const int id[4] = {4 * grp, 4 * grp + 1, 4 * grp + 2, 4 * grp + 3};
+        load(a.lev[0], L == 1, a.lev[0].cap, id);        // top level: every node is a candidate
+    }
+    // ---- parent pointers, those of level v at l_par + o: the levels from the top down as long as there is room
+    auto parents_of = [&](const LcBeamLevel& v) LC_INLINE {
+        return lc_buffer(v.parent ? v.parent + (size_t)bh * v.cap : nullptr, v.parent ? v.cap * 4 : 0);     // (none: reads return 0)
+    };
+    int next_par = 0;                                    // LDS words taken
+    for (int v = 1; v < L; ++v) {
+        const int words = a.lev[v].par_words;
+        if (next_par + words <= a.par_slots) {
+            const __amdgpu_buffer_rsrc_t r = parents_of(a.lev[v]);
+            for (int w = 64 * wave; w < words; w += LC_BM_THREADS)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(l_par + next_par + w), 4,
+                                                         4 * lane, 4 * w, 0, 0);
+            next_par += words;
+        }
+    }
+    next_par = 0;
+    // (scalar reads that would otherwise wait for their own round trip further down)
+    const int M = min(a.state[bh * 4 + 1], cap0);
+    int n_c = L > 1 ? n_lev[0] : (W > 0 ? M : 0), n_dn = L > 1 ? n_lev[-1] : 0;
+    asm volatile("" :: "s"(M), "s"(n_c), "s"(n_dn));
+    uint32_t qp[G][4];
+    float qn[G];
+    lc_load_query_packed<G>(a.q + (size_t)b * a.H * G * LC_D, h, sub, qp, qn);
+
+    for (int i = tid; i < KW; i += LC_BM_THREADS) kept_w[i] = 0u;
+    // optional score output: everything that is never scored reads -inf
+    float* const scores = a.scores ? a.scores + cb : nullptr;
+    if (scores) {
+        for (int j = tid; j < M; j += LC_BM_THREADS) scores[j] = LC_NEG_INF;
+        __syncthreads();
+    }
+    // pinned chunks (first token below `sink`) are the leading ones: their number, counted by every wavefront
+    int n_pin = 0;
+    if (a.sink > 0)
+        for (;;) {
+            const int j = n_pin + lane;
+            const int c = __popcll(__ballot(j < M && bnd[min(j, cap0)] < a.sink));
+            n_pin += c;
+            if (c < 64) break;
+        }
+
+    // ---- Items i < n that `in(i)` accepts (bits of four of them from i on), in ascending order, through put(i, position):
+    // a wavefront takes 256 consecutive items of every 4096, a lane four of them; a scan of the lanes' counts
+    // and one exchange of the wavefronts' give the places.
+    auto gather = [&](int n, auto in, auto put) LC_INLINE -> int {
+        int total = 0;
+        for (int s0 = 0; s0 < n; s0 += LC_BM_SPAN * 4 * LC_BM_THREADS) {     // (once, nearly always)
+            unsigned mask = 0u;
+            const int blocks = min(LC_BM_SPAN, (n - s0 + 4 * LC_BM_THREADS - 1) / (4 * LC_BM_THREADS));
+            for (int e = 0; e < blocks; ++e) {
+                const int first = s0 + (e * LC_BM_WAVES + wave) * 256;
+                int c = 0;
+                if (first < n) {                                    // (whole wavefronts)
+                    const int i = first + 4 * lane;
+                    const unsigned q = in(i) & ((1u << min(max(n - i, 0), 4)) - 1u);
+                    mask |= q << (4 * e);
+                    c = lc_wave_sum_i(__popc(q));
+                }
+                if (lane == 0) cnt_sh[e * LC_BM_WAVES + wave] = c;
+            }
+            lc_barrier_lds();
+            for (int e = 0; e < blocks; ++e) {
+                const int c = cnt_sh[e * LC_BM_WAVES + (lane & 15)];
+                const int inc = lc_wave_scan_incl((lane < 16) ? c : 0);
+                static_assert(LC_BM_WAVES == 16, "one count per lane of a row");
+                unsigned q = (mask >> (4 * e)) & 15u;
+                if (__ballot(q != 0u) != 0ull) {
+                    const int mine = __popc(q);
+                    int at = total + lc_readlane(inc - c, wave) + lc_wave_scan_incl(mine) - mine;
+                    const int i = s0 + (e * LC_BM_WAVES + wave) * 256 + 4 * lane;
+                    while (q != 0u) {                               // (one or two of four, mostly)
+                        put(i + __ffs((int)q) - 1, at++);
+                        q &= q - 1u;
+                    }
+                }
+                total += lc_readlane(inc, 15);
+            }
+            if (s0 + LC_BM_SPAN * 4 * LC_BM_THREADS < n) lc_barrier_lds();      // the counts are written anew
+        }
+        return total;
+    };
+
+    // ---- All levels run through this one loop, NB x 64 candidates at a time: the code of a level is fetched
+    // once and found in the instruction cache by the levels after it.
+    int v = 0, base = 0, n_sel = 0, n_own = n_c;                      // (uniform: what depends on them stays in scalar registers)
+    bool in_lds = n_c <= CL;
+    if (n_c > STEP || L == 1)                            // (the first STEP are on their way)
+        for (int i = tid; i < n_c; i += LC_BM_THREADS) {
+            if (i < CL) l_cid[i] = i;
+            if (!in_lds) g_cid[i] = i;
+        }
+    int32_t* const ids = a.ids + (size_t)bh * a.cap;
+    int C = a.lev[0].beam, par_words = a.lev[1].par_words, n_next = L > 2 ? n_lev[-2] : 0;
+    for (;;) {
+        const bool last = v == bottom;
+        // (what is derived from the thread's number is worked out anew where it is needed: hoisted out of this
+        // loop, as the compiler would, it fills the registers)
+        asm volatile("" : "+v"(tid));
+        const int lane = tid & 63, sub = tid & 15, grp = tid >> 4;
+        if (base + 16 * wave < n_c) {                               // (whole wavefronts)
+            if (last && c0b) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) f[k] = lc_widen_chunk_frag(f[k]);
+            }
+            const float sc = lc_score4_packed<G>(f, R, sub, qp, qn);
+            const int i = base + 4 * grp + (sub & 3);
+            const int w = max(x1 - x0, 0);
+            uint32_t key = lc_score_key(sc);
+            if (key == 0xffffffffu) key = 0xfffffffeu;             // (the highest value marks chosen equal keys)
+            if (last ? own < n_pin : w == 0) key = 0u;              // pinned chunks and empty nodes are no candidates
+            if ((sub >> 2) == 1 && i < n_c) {
+                if (in_lds) { l_key[i] = key; l_wgt[i] = w; }
+                else { g_key[i] = key; g_wgt[i] = w; }
+                if (last && scores && key != 0u) scores[own] = sc;
+            }
+        }
+        base += STEP;
+        if (base >= n_c) {
+            // ---- the level is scored: keep the beam's best (at the chunks: what the budget holds as well)
+            if (in_lds) lc_barrier_lds();
+            else __syncthreads();
+            C = C > 0 ? C : 0x7fffffff;
+            const int n_up = n_own;
+            if (v + 1 == bottom) n_dn = W > 0 ? M : 0;
+            auto mark = [&](int node) LC_INLINE { kept[node] = 1; };
+            if (n_c <= LC_BM_CUT_MAX) {
+                if (wave == 0) {
+                    const uint32_t b = lc_wave_cut(n_c, l_key, l_wgt, last, W, C, hist_sh);
+                    if (tid == 0) cut_sh = b;
+                }
+                lc_barrier_lds();
+                const uint32_t b = cut_sh;
+                if (!last) {
+                    if (tid < n_c && l_key[tid] > b) mark(v == 0 ? tid : l_cid[tid]);
+                } else if (64 * wave < n_c || wave == 0) {
+                    int at = n_pin;
+                    n_sel = 0;
+                    for (int i0 = 0; i0 < n_c; i0 += 64) {          // (the wavefronts before this one: their number alone)
+                        const bool keep = i0 + lane < n_c && l_key[i0 + lane] > b;
+                        const unsigned long long m = __ballot(keep);
+                        if (i0 == 64 * wave) {
+                            at += n_sel + lc_mbcnt(m);
+                            if (keep && at < a.cap) ids[at] = l_cid[i0 + lane];
+                        }
+                        n_sel += __popcll(m);
+                    }
+                }
+            } else {
+                // a longer list (generic pointers: LDS or workspace)
+                uint32_t* const key = in_lds ? l_key : g_key;
+                const int* const wgt = in_lds ? l_wgt : g_wgt;
+                const int* const cid = in_lds ? l_cid : g_cid;
+                const uint32_t b = lc_block_cut<LC_BM_THREADS>(n_c, key, wgt, last, W, C, hist_sh);
+                if (!last) {
+                    for (int i = tid; i < n_c; i += LC_BM_THREADS)
+                        if (key[i] > b) mark(v == 0 ? i : cid[i]);
+                } else {
+                    n_sel = gather(n_c, [&](int i) LC_INLINE -> unsigned {
+                        unsigned q = 0u;
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) q |= key[min(i + k, n_c - 1)] > b ? 1u << k : 0u;
+                        return q;
+                    }, [&](int i, int at) LC_INLINE { if (n_pin + at < a.cap) ids[n_pin + at] = cid[i]; });
+                }
+            }
+            if (last) break;
+            lc_barrier_lds();
+            // ---- the kept nodes' children are the next level's candidates: a list in LDS as far as it fits, in
+            // the workspace too if there may be more of them
+            ++v;
+            const LcBeamLevel& lev = a.lev[v];
+            const bool both = n_dn > CL;
+            auto kept_of = [&](int p) LC_INLINE -> unsigned { return kept[min((unsigned)p, (unsigned)n_up)]; };     // (no node n_up: 0)
+            auto put = [&](int i, int at) LC_INLINE {
+                if (at < CL) l_nxt[at] = i;
+                if (both) g_nxt[at] = i;
+            };
+            const int o = next_par;
+            const bool here = o + par_words <= a.par_slots;
+            if (here) next_par += par_words;
+            if (here && n_dn <= par_words) {
+                n_c = gather(n_dn, [&](int i) LC_INLINE -> unsigned {
+                    const int4 p = *reinterpret_cast<const int4*>(l_par + o + i);      // (past n: other words of the LDS)
+                    return kept_of(p.x) | kept_of(p.y) << 1 | kept_of(p.z) << 2 | kept_of(p.w) << 3;
+                }, put);
+            } else {
+                const __amdgpu_buffer_rsrc_t r = parents_of(lev);
+                n_c = gather(n_dn, [&](int i) LC_INLINE -> unsigned {
+                    int p[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) p[k] = lc_buf_load_i32(r, i + k);
+                    return kept_of(p[0]) | kept_of(p[1]) << 1 | kept_of(p[2]) << 2 | kept_of(p[3]) << 3;
+                }, put);
+            }
+            int* const tl = l_cid; l_cid = l_nxt; l_nxt = tl;
+            int* const tg = g_cid; g_cid = g_nxt; g_nxt = tg;
+            in_lds = n_c <= CL;
+            if (in_lds) lc_barrier_lds();
+            else __syncthreads();
+            for (int i = tid; i < KW; i += LC_BM_THREADS) kept_w[i] = 0u;
+            base = 0;
+            n_own = n_dn;
+            n_dn = n_next;
+            // (what the end of the next level needs)
+            C = a.lev[v].beam;
+            par_words = a.lev[min(v + 1, LC_MAX_LEVELS - 1)].par_words;
+            n_next = v + 2 < L ? n_lev[-v - 2] : 0;
+        }
+        // (entries past the list's end hold anything: their rows' scores are dropped)
+        int id[4];
+        if (in_lds) {
+            const int4 x = *reinterpret_cast<const int4*>(l_cid + base + 4 * grp);
+            id[0] = x.x; id[1] = x.y; id[2] = x.z; id[3] = x.w;
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) id[k] = g_cid[min(base + 4 * grp + k, n_c - 1)];
+        }
+        own = (sub & 2) ? ((sub & 1) ? id[3] : id[2]) : ((sub & 1) ? id[1] : id[0]);
+        load(a.lev[v], v == bottom, n_c - base, id);
+    }
+    for (int j = tid; j < min(n_pin, a.cap); j += LC_BM_THREADS) ids[j] = j;
+    if (tid == 0) a.counts[bh] = min(n_pin + n_sel, a.cap);
+}
+
+template <int G>
+static int launch_beam_g(const LcRetrieveArgs& r, int max_M, int max_nodes, hipStream_t stream) {
+    const LcDev& ix = r.ix;
+    LcBeamArgs a = {};
+    const int L = ix.L;
+    int want = 0;
+    for (int l = 0; l < L; ++l) {
+        LcBeamLevel& v = a.lev[L - 1 - l];
+        v.center = ix.center[l];
+        v.radius = ix.radius[l];
+        v.nchunk = l > 0 ? ix.nchunk[l] : nullptr;
+        v.parent = l + 1 < L ? ix.parent[l] : nullptr;
+        v.cap = ix.cap[l];
+        v.beam = r.beam[l];
+        v.par_words = l + 1 < L ? ((l == 0 ? max_M : ix.cap[l]) + 255) / 256 * 256 : 0;
+        want += v.par_words;
+    }
+    a.q = r.q;
+    a.bounds = ix.bounds;
+    a.state = ix.state;
+    a.nlev = ix.nlev;
+    a.scores = r.scores;
+    a.ids = r.ids;
+    a.counts = r.counts;
+    a.scratch = r.scratch;
+    a.H = ix.H;
+    a.L = L;
+    a.cap0 = ix.cap[0];
+    a.cap = r.cap;
+    a.budget = r.budget;
+    a.sink = r.sink;
+    a.c0_bf16 = ix.c0_bf16;
+    // LDS: lists for up to LC_BEAM_LIST_MAX candidates per level (more go to the workspace), marks of the kept
+    // nodes, and as many parent pointers as fit beside them
+    a.list_slots = lc_beam_list_slots(max_nodes);
+    const int most = L > 1 ? (ix.cap[1] < LC_BM_MAX_LEVEL_NODES ? ix.cap[1] : LC_BM_MAX_LEVEL_NODES) : 0;
+    a.kept_words = (most + 16) / 16 * 4;                             // (one more than there are nodes)
+    const int lists = lc_beam_layout(a.list_slots).total + 4 * a.kept_words;
+    const int room = (LC_WALK_LDS_LIMIT - LC_BM_STATIC_LDS - lists) / 4;
+    a.par_slots = want < room ? want : (room > 0 ? room : 0);
+    const size_t lds = (size_t)lists + 4 * (size_t)a.par_slots;
+    if (lds + LC_BM_STATIC_LDS > 48 * 1024)
         LC_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(&lc_beam_kernel<G>),
                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL(lc_beam_kernel<G>, dim3(a.ix.H, a.ix.B), dim3(LC_BM_THREADS), lds, stream, a);
+    hipLaunchKernelGGL(lc_beam_kernel<G>, dim3(ix.H, ix.B), dim3(LC_BM_THREADS), lds, stream, a);
     LC_HIP_CHECK(hipGetLastError());
     return LC_OK;
 }
@@ -993,7 +1267,7 @@ static int launch_retrieve_g(LcRetrieveArgs& a, int max_M, hipStream_t stream) {
     const LcDev& ix = a.ix;
     const int mc = ((max_M + 63) / 64) * 64;
     const size_t lds_limit = LC_WALK_LDS_LIMIT;
-    if (a.policy == LC_POLICY_BEAM) return launch_beam_g<G>(a, a.upper_cap > max_M ? a.upper_cap : max_M, stream);
+    if (a.policy == LC_POLICY_BEAM) return launch_beam_g<G>(a, max_M, a.upper_cap > max_M ? a.upper_cap : max_M, stream);
     if (a.walk) {
         // as long a probe list as LDS holds next to the internal-node slots (the host has checked that one fits)
         int uc, pc;

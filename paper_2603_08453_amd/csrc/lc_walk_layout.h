@@ -69,7 +69,7 @@ LC_LAYOUT_FN int lc_upper_max_internal_nodes() {
 
 // ---- top-k per level (lc_beam_kernel).  CL = slots of each candidate list, a multiple of 64.
 struct LcBeamLayout {
-    int cid, nxt, key, wgt, flg;           // candidate ids (two lists), keys, weights, kept flags (1 byte each)
+    int cid, nxt, key, wgt, flg;           // candidate ids (two lists), keys, weights, a spare byte each
     int total;
 };
 #define LC_BEAM_LIST_MAX 4096             // longer candidate lists go to the workspace
