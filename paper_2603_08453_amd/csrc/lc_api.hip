@@ -517,6 +517,15 @@ int useful_splits(const lc_index* idx, int budget, int splits) {
     return need < splits ? (int)need : splits;
 }
 
+// One kernel or two (without a level walk): every workgroup scoring all chunks costs 0.5 us per 64 chunks at group
+// size 4, twice that at 7 or 8, times the workgroups that share a compute unit; the scoring kernel costs about 2 us.
+// Measured from 16 to 256 chunks, 8 to 128 (sequence, head) pairs and group sizes 1, 4 and 7: up to 64 chunks
+// one kernel is always faster (by 0.3 to 2.8 us), up to 128 unless a large group meets several workgroups per unit
+// (16 sequences x 4 heads of group size 7: 1 us slower), at 192 hardly ever.
+bool step_is_single(int max_M, int G, long long workgroups) {
+    return max_M <= 64 || (max_M <= LC_STEP_SINGLE_MAX_CHUNKS && (G <= 4 || workgroups <= 256));
+}
+
 // The step itself on a laid-out workspace (every check has passed).
 int decode_step_run(const lc_index* idx, const LcWs& w, const RetrievePlan& p, int splits, const void* q,
                     const void* K, const void* V, const int64_t kv_strides[3], int H_q, int budget, float* out,
@@ -530,14 +539,15 @@ int decode_step_run(const lc_index* idx, const LcWs& w, const RetrievePlan& p, i
     // chunks that is cheaper than the hand-off through a chunk list, with more it is not.
     if (idx->cfg.policy != LC_POLICY_BEAM && p.max_M <= LC_STEP_FUSED_MAX_CHUNKS && lc_decode_fused_fits(G, p.max_M)) {
         // kernel 1 (and the level walk before it) leaves the chunk score keys in the workspace;
-        // kernel 2 selects from them in every workgroup and attends
-        if (!second_kernel_only) {
+        // kernel 2 selects from them in every workgroup and attends.  With few chunks it does it all.
+        const bool single = !p.walk && step_is_single(p.max_M, G, (long long)idx->B * idx->H_kv * splits);
+        if (!single && !second_kernel_only) {
             rc = lc_launch_retrieve(idx, w, q, G, budget, nullptr, nullptr, nullptr, 1, p.max_M,
                                     p.walk ? p.max_upper : -1, 1, st);
             if (rc) return rc;
         }
         return lc_launch_decode_fused(idx, w, q, K, V, kv_strides, G, splits, budget, chunk_ids, counts,
-                                      want_ids ? cap : 0, p.max_M, out, lse, st);
+                                      want_ids ? cap : 0, p.max_M, single, out, lse, st);
     }
     if (second_kernel_only) return LC_ERR_CAPACITY;
     // too many chunks for the registers of the selecting workgroups: the two kernels of lc_retrieve + lc_sparse_decode, with the

@@ -45,7 +45,7 @@ struct LcDecodeArgs {
     float* out;           // [B][H*G][d]
     float* lse;           // [B][H*G] or null
     // fused step only (the kernel selects the chunks itself from their score keys):
-    const int* entries;   // [B][H][cap0] chunk entries (LcChunkEntry) of the scoring kernel
+    const int* entries;   // [B][H][cap0] chunk entries (LcChunkEntry) of the scoring kernel; null: scored here
     int32_t* ids_out;     // [B][H][cap] selected ids, ascending, or null
     int32_t* counts_out;  // [B][H] or null
     int budget, sink;     // token budget, tokens of the pinned prefix
@@ -94,9 +94,13 @@ __device__ __forceinline__ float lc_exp2_rel(float x, float ref) { return exp2f(
 // repeats the budget selection of its (sequence, head) from the chunk score keys -- the same
 // deterministic routine on the same keys, so all splits agree -- and never reads a chunk list.
 //
+// SCORE = true (with FUSED): it scores the chunks as well, so that the step is one kernel.  That costs every split
+// the scoring of all chunks -- four per group of lanes, 0.5 us and more for every 64 of them -- and saves a launch
+// and a pass through memory (113 chunks, 8 heads: 12.9 -> 11.3 us; where the line lies: step_is_single in the host code).
+//
 // Either way the selected chunks sit in a list, in id order; the wavefronts write the cache row of
 // every token of the split's tile into LDS, 64 lanes per overlapping chunk.
-template <int G, bool FUSED, int EC>
+template <int G, bool FUSED, int EC, bool SCORE>
 __global__ void __launch_bounds__(LC_DEC_THREADS)
 lc_decode_kernel(const LcDecodeArgs a) {
     extern __shared__ int lds_dyn[];             // FUSED: the selection's chunk lists
@@ -104,6 +108,7 @@ lc_decode_kernel(const LcDecodeArgs a) {
     using FusedStore = typename std::conditional<FUSED, LcFusedSh<LC_DEC_THREADS>, int>::type;
     __shared__ __attribute__((aligned(16))) SelStore sel_store;
     __shared__ __attribute__((aligned(16))) FusedStore fused_store;
+    __shared__ lc_v4i entry_sh[SCORE ? LC_STEP_SINGLE_MAX_CHUNKS : 1];
     __shared__ int scan_sh[8];
     __shared__ int rows[LC_DEC_TILE];
     __shared__ int last_sh;
@@ -163,6 +168,65 @@ lc_decode_kernel(const LcDecodeArgs a) {
         return sum;
     };
 
+    // SCORE: entries of the chunks, 64 at a time: group `grp` has chunks 64 p + 4 grp + (0..3) of pass p < 2
+    static_assert(LC_STEP_SINGLE_MAX_CHUNKS <= 128, "two passes");
+    auto score_chunks = [&]() {
+        const int cap0 = ix.cap[0];
+        const size_t cb = (size_t)bh * cap0;
+        const bool c0b = ix.c0_bf16 != 0;
+        const int cen_row = c0b ? LC_D * 2 : LC_D * 4;
+        const __amdgpu_buffer_rsrc_t cen_r = lc_buffer(reinterpret_cast<const char*>(ix.center[0]) + cb * cen_row, cap0 * cen_row);
+        const __amdgpu_buffer_rsrc_t rad_r = lc_buffer(ix.radius[0] + cb, cap0 * 4);
+        const __amdgpu_buffer_rsrc_t bnd_r = lc_buffer(bnd, (cap0 + 1) * 4);
+        struct Pass {
+            LcNodeFrag f[4];
+            float R;
+            int s0, s1;
+        };
+        auto load = [&](Pass& w, int p) {
+            const int j = 64 * p + 4 * grp;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (c0b) {
+                    const lc_v2i x = __builtin_amdgcn_raw_buffer_load_b64(cen_r, (j + k) * cen_row + 8 * sub, 0, 0);
+                    const lc_v2i y = __builtin_amdgcn_raw_buffer_load_b64(cen_r, (j + k) * cen_row + 8 * sub + 128, 0, 0);
+                    w.f[k].a.x = __int_as_float(x.x); w.f[k].a.y = __int_as_float(x.y);
+                    w.f[k].b.x = __int_as_float(y.x); w.f[k].b.y = __int_as_float(y.y);
+                } else {
+                    w.f[k].a = lc_buf_load_f32x4(cen_r, (j + k) * cen_row + 16 * sub);
+                    w.f[k].b = lc_buf_load_f32x4(cen_r, (j + k) * cen_row + 16 * sub + 256);
+                }
+            }
+            const int own = j + (sub & 3);
+            w.R = lc_buf_load_f32(rad_r, own);
+            w.s0 = lc_buf_load_i32(bnd_r, own);
+            w.s1 = lc_buf_load_i32(bnd_r, own + 1);
+        };
+        uint32_t qp[G][4];
+        float qn[G];
+        // (both loads go out before the chunk count is known)
+        Pass first, second;
+        load(first, 0);
+        if (cap0 > 64) load(second, 1);
+        lc_load_query_packed<G>(a.q + (size_t)b * ix.H * G * LC_D, h, sub, qp, qn);
+        auto score = [&](Pass& w, int p) {
+            if (c0b) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) w.f[k] = lc_widen_chunk_frag(w.f[k]);
+            }
+            const float sc = lc_score4_packed<G>(w.f, w.R, sub, qp, qn);
+            lc_v4i e;
+            e.x = a.budget > 0 && w.s0 >= a.sink ? (int)lc_score_key(sc) : 0;
+            e.y = w.s0;
+            e.z = max(0, w.s1 - w.s0);
+            e.w = 0;
+            if ((sub >> 2) == 1) entry_sh[64 * p + 4 * grp + (sub & 3)] = e;
+        };
+        score(first, 0);
+        if (ix.state[bh * 4 + 1] > 64) score(second, 1);
+        lc_barrier_lds();
+    };
+
     if constexpr (!FUSED) {
         ids = a.ids + (size_t)bh * a.cap;
         // independent loads first: the ids a thread will need are fetched before the count is known
@@ -181,7 +245,14 @@ lc_decode_kernel(const LcDecodeArgs a) {
             n_tok += tot;
         }
     } else {
-        lc_select_chunks<LC_DEC_THREADS, EC>(ix, b, bh, a.entries, a.budget, a.sink, s == 0 ? a.ids_out : nullptr,
+        if constexpr (SCORE) score_chunks();
+        const __amdgpu_buffer_rsrc_t ent_r = lc_buffer(a.entries + (size_t)bh * 4 * ix.cap[0], ix.cap[0] * 16);
+        const int first = wave * (EC * 64) + lane;
+        auto entry = [&](int e) -> lc_v4i {
+            if constexpr (SCORE) return entry_sh[min(first + 64 * e, LC_STEP_SINGLE_MAX_CHUNKS - 1)];
+            else return __builtin_amdgcn_raw_buffer_load_b128(ent_r, first * 16, e * 1024, 0);
+        };
+        lc_select_chunks<LC_DEC_THREADS, EC>(ix, b, bh, entry, a.budget, a.sink, s == 0 ? a.ids_out : nullptr,
                                              a.counts_out, a.cap, sel_store, fused_store, lds_dyn, cs);
         T = cs.T;
         M = cs.M;
@@ -489,7 +560,7 @@ lc_decode_kernel(const LcDecodeArgs a) {
 
 template <int G>
 static int launch_decode_g(const LcDecodeArgs& a, int splits, hipStream_t stream) {
-    hipLaunchKernelGGL((lc_decode_kernel<G, false, 1>), dim3(splits, a.ix.H, a.ix.B), dim3(LC_DEC_THREADS), 0, stream, a);
+    hipLaunchKernelGGL((lc_decode_kernel<G, false, 1, false>), dim3(splits, a.ix.H, a.ix.B), dim3(LC_DEC_THREADS), 0, stream, a);
     LC_HIP_CHECK(hipGetLastError());
     return LC_OK;
 }
@@ -549,35 +620,38 @@ bool lc_decode_fused_fits(int G, int max_M) {
     return G >= 1 && G <= LC_MAX_GROUP && max_M <= LC_DEC_THREADS * LC_DEC_EC_MAX;
 }
 
-template <int G, int EC>
+template <int G, int EC, bool SCORE>
 static int launch_fused_ge(const LcDecodeArgs& a, int splits, hipStream_t stream) {
     const size_t lds = (size_t)EC * LC_DEC_THREADS * 12;      // the selection's chunk lists
     if (lds > 16 * 1024) {      // static + dynamic may pass the default per-workgroup allowance: raised once per device
         static LcOnce raised;
         LC_HIP_CHECK(raised.run([&] {
-            return hipFuncSetAttribute(reinterpret_cast<const void*>(&lc_decode_kernel<G, true, EC>),
+            return hipFuncSetAttribute(reinterpret_cast<const void*>(&lc_decode_kernel<G, true, EC, SCORE>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         }));
     }
-    hipLaunchKernelGGL((lc_decode_kernel<G, true, EC>), dim3(splits, a.ix.H, a.ix.B), dim3(LC_DEC_THREADS), lds, stream, a);
+    hipLaunchKernelGGL((lc_decode_kernel<G, true, EC, SCORE>), dim3(splits, a.ix.H, a.ix.B), dim3(LC_DEC_THREADS), lds, stream, a);
     LC_HIP_CHECK(hipGetLastError());
     return LC_OK;
 }
 template <int G>
 static int launch_fused_g(const LcDecodeArgs& a, int splits, hipStream_t stream) {
-    if (a.ew <= 2) return launch_fused_ge<G, 2>(a, splits, stream);
-    if (a.ew <= 4) return launch_fused_ge<G, 4>(a, splits, stream);
-    if (a.ew <= 6) return launch_fused_ge<G, 6>(a, splits, stream);
-    if (a.ew <= 10) return launch_fused_ge<G, 10>(a, splits, stream);
-    return launch_fused_ge<G, LC_DEC_EC_MAX>(a, splits, stream);
+    if (a.entries == nullptr) return launch_fused_ge<G, 1, true>(a, splits, stream);
+    if (a.ew <= 2) return launch_fused_ge<G, 2, false>(a, splits, stream);
+    if (a.ew <= 4) return launch_fused_ge<G, 4, false>(a, splits, stream);
+    if (a.ew <= 6) return launch_fused_ge<G, 6, false>(a, splits, stream);
+    if (a.ew <= 10) return launch_fused_ge<G, 10, false>(a, splits, stream);
+    return launch_fused_ge<G, LC_DEC_EC_MAX, false>(a, splits, stream);
 }
 
 int lc_launch_decode_fused(const lc_index* idx, const LcWs& ws, const void* q, const void* K, const void* V,
                            const int64_t ks[3], int G, int splits, int budget, int32_t* ids_out,
-                           int32_t* counts_out, int cap, int max_M, float* out, float* lse, hipStream_t stream) {
+                           int32_t* counts_out, int cap, int max_M, bool single, float* out, float* lse,
+                           hipStream_t stream) {
     LcDecodeArgs a;
     fill_common(a, idx, ws, q, K, V, ks, out, lse);
-    a.entries = ws.scratch;
+    a.entries = single ? nullptr : ws.scratch;
+    if (single && max_M > LC_STEP_SINGLE_MAX_CHUNKS) return LC_ERR_CAPACITY;
     a.ids_out = ids_out;
     a.counts_out = counts_out;
     a.cap = cap;

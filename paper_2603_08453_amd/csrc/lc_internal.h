@@ -70,6 +70,8 @@ struct LcWs {
 // with_build = false leaves out the build scratch (directions, centroids): what a decode step needs.
 size_t lc_layout_ws(const lc_config* cfg, int B, int H_q, int H, int d, int splits, void* base, LcWs* ws,
                     bool with_build = true);
+// Up to this many chunks per (sequence, head) the workgroups of a decode step may score all of them themselves.
+#define LC_STEP_SINGLE_MAX_CHUNKS 128
 #define LC_DEC_MIN_TOKENS_PER_SPLIT 64      // tokens of a split of the attention kernel, at least
 int lc_auto_splits(const lc_config* cfg, int B, int H);
 
@@ -120,11 +122,11 @@ int lc_launch_decode(const lc_index* idx, const LcWs& ws, const void* q, const v
                      const int64_t ks[3], const int32_t* ids, const int32_t* counts, int cap, int G,
                      int splits, float* out, float* lse, hipStream_t stream);
 // Fused step: selection from the chunk entries in ws.scratch (written by lc_launch_retrieve with score_only)
-// + attention.  lc_decode_fused_fits tells whether a selecting workgroup holds max_M chunks.
+// + attention; `single` (up to LC_STEP_SINGLE_MAX_CHUNKS chunks): the scoring as well.  lc_decode_fused_fits tells whether a selecting workgroup holds max_M chunks.
 bool lc_decode_fused_fits(int G, int max_M);
 int lc_launch_decode_fused(const lc_index* idx, const LcWs& ws, const void* q, const void* K, const void* V,
                            const int64_t ks[3], int G, int splits, int budget, int32_t* ids_out,
-                           int32_t* counts_out, int cap, int max_M, float* out, float* lse, hipStream_t stream);
+                           int32_t* counts_out, int cap, int max_M, bool single, float* out, float* lse, hipStream_t stream);
 // out (device): [B][H][4] floats: sum of radii at build, sum now, largest growth, nodes counted
 int lc_launch_drift(const lc_index* idx, int level, float* out, hipStream_t stream);
 // Puts a staged [state | nlev | chunk boundaries of all sequences] block (device memory) in place

@@ -103,12 +103,12 @@ __device__ __forceinline__ void lc_sel_entry(const LcChunkSel<EC>& o, const LcFu
 //      bin), the general select routine runs on them;
 //   3. token offsets by a wavefront scan of the list, one exchange of the wavefronts' totals.
 // (2275 chunks: 3.3 us from the loads to here with all of it in registers over every chunk, now.)
-// `entries`: [B][H][cap0]; chunks whose first token lies below `sink` are pinned: always selected, not
+// `entry(e)`: entry e of this lane (LcChunkEntry; past the array's end anything); chunks whose first token lies below `sink` are pinned: always selected, not
 // charged to the budget.  With `ids_out` (per (sequence, head) `cap` entries) the selected ids are also
 // written in ascending order and their number to counts_out[bh].  `lds_dyn`: 12 * EC * NT bytes.
 // All NT threads must call; NT / 64 wavefronts; holds up to EC * NT chunks.
-template <int NT, int EC>
-__device__ __forceinline__ void lc_select_chunks(const LcDev& ix, int b, int bh, const int* entries, int budget,
+template <int NT, int EC, typename Entry>
+__device__ __forceinline__ void lc_select_chunks(const LcDev& ix, int b, int bh, Entry entry, int budget,
                                                  int sink, int32_t* ids_out, int32_t* counts_out, int cap,
                                                  LcLeafSelSh& sel_sh, LcFusedSh<NT>& fs, int* lds_dyn,
                                                  LcChunkSel<EC>& o) {
@@ -118,14 +118,12 @@ __device__ __forceinline__ void lc_select_chunks(const LcDev& ix, int b, int bh,
     // bins of the histogram: about one per four chunks, so that the cutoff bin holds a handful
     constexpr int BITS = EC * NT <= 1024 ? 8 : (EC * NT <= 2560 ? 9 : 10);
     constexpr int BINS = 1 << BITS;
-    const int cap0 = ix.cap[0];
-    // ---- every load of the selection goes out at once, before the chunk count is known (reads
-    // past the array's end return 0; what lies past the count is masked below)
-    const __amdgpu_buffer_rsrc_t ent_r = lc_buffer(entries + (size_t)bh * 4 * cap0, cap0 * 16);
+    // ---- every load of the selection goes out at once, before the chunk count is known (what lies past the
+    // count is masked below)
     const int j0 = wave * (EC * 64) + lane;                      // this lane's chunk e is j0 + 64 e
     lc_v4i ent[EC];
 #pragma unroll
-    for (int e = 0; e < EC; ++e) ent[e] = __builtin_amdgcn_raw_buffer_load_b128(ent_r, j0 * 16, e * 1024, 0);
+    for (int e = 0; e < EC; ++e) ent[e] = entry(e);
     o.T = ix.state[bh * 4 + 0];
     const int M_all = ix.state[bh * 4 + 1];
     o.l_st = lds_dyn;
