@@ -388,11 +388,15 @@ lc_upper_kernel(const LcRetrieveArgs a) {
 //     LDS or memory costs a wait for both); a list longer than `list_slots` goes to the workspace.
 // 10.9 K chunks under 5461 and 249 nodes, 43 and 8 of them kept, 8 heads: 34.7 us with a copy of the code per level,
 // every node scored by itself and ranks by counting, 25.2 us now; 2275 chunks under four levels: 26 and 24.4 us.
+// A flat scan of up to this many chunks is the same with one level: no hand-off between workgroups (48 chunks:
+// 8.0 us as lc_leaf_kernel, 6.8 us here); beyond, one compute unit's scoring and cut cost more (240: 9.0 and 10.1 us).
+#define LC_FLAT_MAX_CHUNKS 64
 #define LC_BM_THREADS 1024
 #define LC_BM_WAVES (LC_BM_THREADS / 64)
 #define LC_BM_GROUPS (LC_BM_THREADS / 16)
 #define LC_BM_MAX_LEVEL_NODES 65536       // marks of kept nodes: one byte each in LDS
-#define LC_BM_CUT_MAX 1024               // lists up to this length are cut by one wavefront, longer ones by the workgroup
+#define LC_BM_RANK_MAX 24                // lists up to this length are ranked by one wavefront,
+#define LC_BM_CUT_MAX 1024               // up to this length cut by one wavefront with a histogram, longer ones by the workgroup
 #define LC_BM_STATIC_LDS (8 * 1024)      // what the kernel's own arrays take, rounded up
 #define LC_BM_SPAN 8                     // blocks of 4096 items that one pass of the gather looks at
 
@@ -462,6 +466,24 @@ __device__ __forceinline__ uint32_t lc_wave_cut(int n, uint32_t* key, const int*
 #pragma unroll
         for (int r = 0; r < 4; ++r) k[r] = i0 + 64 * r + lane < n ? x[r] : 0u;
     };
+    // candidates of a list position each, ranked against each other: kept ones get the highest key, the others 0
+    auto rank = [&](int in, int me, uint32_t mine) LC_INLINE {
+        const int w = weighted ? wgt[me] : 0;
+        int c_before = 0, w_before = 0;
+        for (int c = 0; c < in; ++c) {
+            const uint32_t k = (uint32_t)lc_readlane((int)mine, c);
+            const bool before = k > mine || (k == mine && c < lane);
+            c_before += before ? 1 : 0;
+            w_before += before ? lc_readlane(w, c) : 0;
+        }
+        if (lane < in) key[me] = mine != 0u && c_before < C && w_before + w <= W ? 0xffffffffu : 0u;
+    };
+    if (n <= C && !weighted) return 0u;
+    if (n <= LC_BM_RANK_MAX) {                                      // (too few for the histogram to pay)
+        const int me = min(lane, max(n - 1, 0));
+        rank(n, me, key[me]);
+        return 0u;
+    }
     uint32_t lo = 0xffffffffu, hi = 0u;
     for (int i0 = 0; i0 < n; i0 += 256) {
         uint32_t k[4];
@@ -514,18 +536,8 @@ __device__ __forceinline__ uint32_t lc_wave_cut(int n, uint32_t* key, const int*
         if (in <= 64) {
             // few enough to rank: lane c has the c-th of them (in order of position)
             const int me = hist[min(lane, in - 1)];
-            const uint32_t mine = key[me];
-            const int w = weighted ? wgt[me] : 0;
-            int c_before = 0, w_before = 0;
-            for (int c = 0; c < in; ++c) {
-                const uint32_t k = (uint32_t)lc_readlane((int)mine, c);
-                const bool before = k > mine || (k == mine && c < lane);
-                c_before += before ? 1 : 0;
-                w_before += before ? lc_readlane(w, c) : 0;
-            }
-            const bool keep = c_before < C && w_before + w <= W;
             b = lc_wave_max_uniform(hi);                            // (at least one of them is not kept)
-            if (lane < in) key[me] = keep ? 0xffffffffu : 0u;
+            rank(in, me, key[me]);
             return b;
         }
         a = lc_wave_min_uniform(lo);
@@ -1288,6 +1300,12 @@ static int launch_retrieve_g(LcRetrieveArgs& a, int max_M, hipStream_t stream) {
         if (rs == 1) return launch_score<G, 1>(a, max_M, stream);
         if (rs == 2) return launch_score<G, 2>(a, max_M, stream);
         return launch_score<G, 4>(a, max_M, stream);
+    }
+    if (!a.walk && max_M <= LC_FLAT_MAX_CHUNKS) {        // one level, every chunk a candidate
+        LcRetrieveArgs f = a;
+        f.ix.L = 1;
+        f.beam[0] = 0;
+        return launch_beam_g<G>(f, max_M, max_M, stream);
     }
     a.chunk_cap = ((size_t)mc * 8 + sizeof(LcLeafSelSh) + 1024 <= lds_limit) ? mc : 0;
     const size_t lds2 = (size_t)a.chunk_cap * 8;
