@@ -217,25 +217,31 @@ void fill_level_counts(lc_index* h) {
     }
 }
 
-// Host side of the small uploads (counts, chunk boundaries): one pinned buffer per device, kept for
-// the life of the process and grown on demand, so that an upload is one asynchronous copy and no
-// wait for the stream.  The event marks the last copy that read the buffer; it is waited for before
-// the buffer is written again (long done, normally).
+// Host side of the small uploads (counts, chunk boundaries): a few pinned buffers per device, used in turn, kept for
+// the life of the process and grown on demand.  Kernels read them where they are: a copy by the DMA engine
+// costs the stream two hand-overs, 10 to 30 us around a kernel that takes 3.  A buffer's event marks the last
+// kernel that read it; it is waited for before the buffer is written again (long done, normally).
 struct LcStage {
     int32_t* host = nullptr;
     size_t ints = 0;
     hipEvent_t read = nullptr;
 };
-constexpr int LC_STAGE_DEVICES = 64;
-LcStage g_stage[LC_STAGE_DEVICES];
+constexpr int LC_STAGE_DEVICES = 64, LC_STAGE_SLOTS = 4;
+struct LcStages {
+    LcStage slot[LC_STAGE_SLOTS];
+    int next = 0;
+};
+LcStages g_stage[LC_STAGE_DEVICES];
 std::mutex g_stage_mutex;
 
-// Returns the current device's buffer with room for `ints` values (the lock must be held).
+// Returns a buffer of the current device with room for `ints` values (the lock must be held).
 int stage_reserve(size_t ints, LcStage** out) {
     int dev = 0;
     LC_HIP_CHECK(hipGetDevice(&dev));
     if (dev < 0 || dev >= LC_STAGE_DEVICES) return LC_ERR_INVALID_ARG;
-    LcStage& st = g_stage[dev];
+    LcStages& all = g_stage[dev];
+    LcStage& st = all.slot[all.next];
+    all.next = (all.next + 1) % LC_STAGE_SLOTS;
     if (!st.read) LC_HIP_CHECK(hipEventCreateWithFlags(&st.read, hipEventDisableTiming));
     else LC_HIP_CHECK(hipEventSynchronize(st.read));
     if (st.ints < ints) {
@@ -250,32 +256,39 @@ int stage_reserve(size_t ints, LcStage** out) {
     return LC_OK;
 }
 
-// state, nlev, zeroed arrival counters and chunk boundaries -> device: staged as
-// [state | nlev | boundaries of all sequences], copied once into `dev_stage` (workspace memory the
-// build overwrites later) and put in place by one kernel.
-int upload_state(lc_index* h, const int32_t* bounds_concat, void* dev_stage, hipStream_t stream) {
+// state, nlev, zeroed arrival counters and chunk boundaries -> device: staged as [state | nlev | where each sequence's
+// boundaries begin | boundaries of all sequences] and put in place by one kernel.
+int upload_state(lc_index* h, const int32_t* bounds_concat, hipStream_t stream) {
     const int B = h->B, H = h->H_kv;
     const size_t n_state = (size_t)B * H * 4, n_nlev = (size_t)B * LC_MAX_LEVELS;
     size_t n_bounds = 0;
-    for (int b = 0; b < B; ++b) n_bounds += (size_t)h->M[b] + 1;
-    const size_t total = n_state + n_nlev + n_bounds;
+    int max_M = 0;
+    for (int b = 0; b < B; ++b) {
+        n_bounds += (size_t)h->M[b] + 1;
+        max_M = h->M[b] > max_M ? h->M[b] : max_M;
+    }
+    const size_t head = n_state + n_nlev + B, total = head + n_bounds;
     std::lock_guard<std::mutex> lock(g_stage_mutex);
     LcStage* st = nullptr;
-    const int rc = stage_reserve(total, &st);
+    int rc = stage_reserve(total, &st);
     if (rc != LC_OK) return rc;
     int32_t* p = st->host;
     memset(p, 0, n_state * sizeof(int32_t));
+    size_t off = head;
     for (int b = 0; b < B; ++b) {
         for (int hh = 0; hh < H; ++hh) {
             p[((size_t)b * H + hh) * 4 + 0] = h->T[b];
             p[((size_t)b * H + hh) * 4 + 1] = h->M[b];
         }
+        p[n_state + n_nlev + b] = (int32_t)off;
+        off += (size_t)h->M[b] + 1;
     }
     for (size_t i = 0; i < n_nlev; ++i) p[n_state + i] = h->N[i];
-    memcpy(p + n_state + n_nlev, bounds_concat, n_bounds * sizeof(int32_t));
-    LC_HIP_CHECK(hipMemcpyAsync(dev_stage, p, total * sizeof(int32_t), hipMemcpyHostToDevice, stream));
+    memcpy(p + head, bounds_concat, n_bounds * sizeof(int32_t));
+    rc = lc_launch_place_state(h, p, max_M, stream);
+    if (rc != LC_OK) return rc;
     LC_HIP_CHECK(hipEventRecord(st->read, stream));
-    return lc_launch_place_state(h, static_cast<const int32_t*>(dev_stage), stream);
+    return LC_OK;
 }
 
 // nodes per level -> device (lc_recluster)
@@ -283,12 +296,52 @@ int upload_level_counts(lc_index* h, hipStream_t stream) {
     const size_t n_nlev = (size_t)h->B * LC_MAX_LEVELS;
     std::lock_guard<std::mutex> lock(g_stage_mutex);
     LcStage* st = nullptr;
-    const int rc = stage_reserve(n_nlev, &st);
+    int rc = stage_reserve(n_nlev, &st);
     if (rc != LC_OK) return rc;
     for (size_t i = 0; i < n_nlev; ++i) st->host[i] = h->N[i];
-    LC_HIP_CHECK(hipMemcpyAsync(h->dev.nlev, st->host, n_nlev * sizeof(int32_t), hipMemcpyHostToDevice, stream));
+    rc = lc_launch_place_counts(h, st->host, stream);
+    if (rc != LC_OK) return rc;
     LC_HIP_CHECK(hipEventRecord(st->read, stream));
     return LC_OK;
+}
+
+// Pinned memory that a kernel of a waiting call writes its answer into, taken from a short list of spare ones and put
+// back, or released if the list is full.
+struct LcAnswer {
+    float* host = nullptr;
+    size_t floats = 0;
+};
+constexpr size_t LC_ANSWERS_KEPT = 4;
+std::vector<LcAnswer> g_answers;
+std::mutex g_answers_mutex;
+
+int take_answer(size_t floats, LcAnswer* a) {
+    {
+        std::lock_guard<std::mutex> lock(g_answers_mutex);
+        if (!g_answers.empty()) {
+            *a = g_answers.back();
+            g_answers.pop_back();
+        }
+    }
+    if (a->floats >= floats) return LC_OK;
+    if (a->host) {
+        LC_HIP_CHECK(hipHostFree(a->host));
+        *a = LcAnswer();
+    }
+    const size_t want = floats < 1024 ? 1024 : floats;
+    LC_HIP_CHECK(hipHostMalloc(reinterpret_cast<void**>(&a->host), want * sizeof(float), hipHostMallocPortable | hipHostMallocMapped));
+    a->floats = want;
+    return LC_OK;
+}
+void give_back(const LcAnswer& a) {
+    {
+        std::lock_guard<std::mutex> lock(g_answers_mutex);
+        if (g_answers.size() < LC_ANSWERS_KEPT) {
+            g_answers.push_back(a);
+            return;
+        }
+    }
+    (void)hipHostFree(a.host);
 }
 
 }  // namespace
@@ -339,7 +392,7 @@ int lc_build_index(lc_index** out, const lc_config* cfg, const void* K, const in
     }
     fill_level_counts(h);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    rc = upload_state(h, chunk_bounds, w.dirs, s);
+    rc = upload_state(h, chunk_bounds, s);
     if (rc == LC_OK) rc = lc_launch_build(h, w, K, k_strides, max_M, s);
     if (rc != LC_OK) {
         delete h;
@@ -389,11 +442,20 @@ int lc_index_drift(const lc_index* idx, int level, float* drift, void* ws, size_
     const size_t n = (size_t)idx->B * idx->H_kv * 4;
     if (ws_bytes < n * sizeof(float)) return LC_ERR_WORKSPACE_TOO_SMALL;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    int rc = lc_launch_drift(idx, level, static_cast<float*>(ws), s);
+    LcAnswer a;
+    int rc = take_answer(n, &a);
     if (rc) return rc;
-    LC_HIP_CHECK(hipMemcpyAsync(drift, ws, n * sizeof(float), hipMemcpyDeviceToHost, s));
-    LC_HIP_CHECK(hipStreamSynchronize(s));
-    return LC_OK;
+    rc = lc_launch_drift(idx, level, a.host, s);
+    if (rc == LC_OK) {
+        const hipError_t e = hipStreamSynchronize(s);
+        if (e == hipSuccess) memcpy(drift, a.host, n * sizeof(float));
+        else {
+            lc_set_hip_error(e);
+            rc = LC_ERR_HIP;
+        }
+    }
+    give_back(a);
+    return rc;
 }
 
 void lc_walk_limits(int32_t* exact_walk_internal_nodes, int32_t* beam_level_nodes) {
@@ -931,7 +993,7 @@ int lc_index_import(lc_index** out, const lc_config* cfg, const void* blob, size
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     // staged through the chunk centers' memory, which the kernels below overwrite in stream order
-    if (rc == LC_OK) rc = upload_state(h, bounds_concat.data(), h->dev.center[0], s);
+    if (rc == LC_OK) rc = upload_state(h, bounds_concat.data(), s);
     if (rc == LC_OK) rc = import_nodes(h, blob, s);
     if (rc != LC_OK) {
         delete h;

@@ -1706,26 +1706,53 @@ lc_drift_kernel(LcDev ix, int level, float* out) {
     }
 }
 
-// staged = [state: B*H*4 | nlev: B*LC_MAX_LEVELS | boundaries: M_0 + 1, M_1 + 1, ...]; block b < B
-// moves sequence b's boundaries, block B the counts (and clears the arrival counters).
+// staged (pinned host memory) = [state: B*H*4 | nlev: B*LC_MAX_LEVELS | where each sequence's boundaries begin: B |
+// boundaries: M_0 + 1, M_1 + 1, ...]; row b < B of the grid moves sequence b's boundaries, row B the counts (and
+// clears the arrival counters).  What bounds it is the way over the bus: two round trips, four words per thread in
+// flight.
+#define LC_PS_WORDS (4 * LC_BT)
 __global__ void __launch_bounds__(LC_BT)
 lc_place_state_kernel(LcDev ix, const int32_t* staged, int B) {
-    const int b = blockIdx.x, tid = threadIdx.x;
+    const int b = blockIdx.y, tid = threadIdx.x;
     const int n_state = B * ix.H * 4, n_nlev = B * LC_MAX_LEVELS;
     if (b == B) {
-        for (int i = tid; i < n_state; i += LC_BT) { ix.state[i] = staged[i]; ix.sync[i] = 0; }
-        for (int i = tid; i < n_nlev; i += LC_BT) ix.nlev[i] = staged[n_state + i];
+        for (int i0 = blockIdx.x * LC_PS_WORDS; i0 < n_state + n_nlev; i0 += gridDim.x * LC_PS_WORDS) {
+            int v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = staged[min(i0 + k * LC_BT + tid, n_state + n_nlev - 1)];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int i = i0 + k * LC_BT + tid;
+                if (i < n_state) { ix.state[i] = v[k]; ix.sync[i] = 0; }
+                else if (i < n_state + n_nlev) ix.nlev[i - n_state] = v[k];
+            }
+        }
         return;
     }
-    int off = n_state + n_nlev;
-    for (int s = 0; s < b; ++s) off += staged[s * ix.H * 4 + 1] + 1;
-    const int n = staged[b * ix.H * 4 + 1] + 1;
+    const int off = staged[n_state + n_nlev + b], n = staged[b * ix.H * 4 + 1] + 1;
     int* dst = ix.bounds + (size_t)b * (ix.cap[0] + 1);
-    for (int i = tid; i < n; i += LC_BT) dst[i] = staged[off + i];
+    const int i0 = blockIdx.x * LC_PS_WORDS;
+    int v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = staged[off + min(i0 + k * LC_BT + tid, n - 1)];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int i = i0 + k * LC_BT + tid;
+        if (i < n) dst[i] = v[k];
+    }
+}
+__global__ void __launch_bounds__(LC_BT)
+lc_place_counts_kernel(int* dst, const int32_t* staged, int n) {
+    for (int i = blockIdx.x * LC_BT + threadIdx.x; i < n; i += gridDim.x * LC_BT) dst[i] = staged[i];
 }
 
-int lc_launch_place_state(const lc_index* idx, const int32_t* staged, hipStream_t stream) {
-    hipLaunchKernelGGL(lc_place_state_kernel, dim3(idx->B + 1), dim3(LC_BT), 0, stream, idx->dev, staged, idx->B);
+int lc_launch_place_state(const lc_index* idx, const int32_t* staged, int max_M, hipStream_t stream) {
+    hipLaunchKernelGGL(lc_place_state_kernel, dim3(max_M / LC_PS_WORDS + 1, idx->B + 1), dim3(LC_BT), 0, stream, idx->dev, staged, idx->B);
+    LC_HIP_CHECK(hipGetLastError());
+    return LC_OK;
+}
+int lc_launch_place_counts(const lc_index* idx, const int32_t* staged, hipStream_t stream) {
+    hipLaunchKernelGGL(lc_place_counts_kernel, dim3(1), dim3(LC_BT), 0, stream, idx->dev.nlev, staged, idx->B * LC_MAX_LEVELS);
     LC_HIP_CHECK(hipGetLastError());
     return LC_OK;
 }
