@@ -807,11 +807,14 @@ lc_beam_kernel(const LcBeamArgs a) {
     // once and found in the instruction cache by the levels after it.
     int v = 0, base = 0, n_sel = 0, n_own = n_c;                      // (uniform: what depends on them stays in scalar registers)
     bool in_lds = n_c <= CL;
-    if (n_c > STEP || L == 1)                            // (the first STEP are on their way)
+    if (n_c > STEP || L == 1) {                          // (the first STEP are on their way)
         for (int i = tid; i < n_c; i += LC_BM_THREADS) {
             if (i < CL) l_cid[i] = i;
             if (!in_lds) g_cid[i] = i;
         }
+        if (in_lds) lc_barrier_lds();                    // other wavefronts read what this one wrote from the second STEP on
+        else __syncthreads();
+    }
     int32_t* const ids = a.ids + (size_t)bh * a.cap;
     int C = a.lev[0].beam, par_words = a.lev[1].par_words, n_next = L > 2 ? n_lev[-2] : 0;
     for (;;) {

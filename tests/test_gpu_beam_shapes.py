@@ -51,6 +51,14 @@ def test_nodes_of_the_top_level(n):
     check(2, [2 * n], 2, 2, [0, max(1, n // 7)], 60)
 
 
+# Candidates of the top level beyond the first 256 come from a list that all wavefronts write and each reads from
+# another: in LDS, and past 4096 of them in the workspace.  Every node is kept, so one lost entry shows in the ids.
+@pytest.mark.parametrize("n", [300, 2000, 4096, 4097, 9000])
+def test_list_of_the_top_level(n):
+    check(1, [2 * n], 2, 2, [0, 0], 2 * n)
+    check(2, [n], 1, 2, [0, 0], n, G=7, centers=1)
+
+
 @pytest.mark.parametrize("n", [1, 3, 64, 257, 1024, 1025, 4096, 4097, 9000])
 @pytest.mark.parametrize("levels", [1, 2])
 def test_every_chunk_a_candidate(n, levels):
