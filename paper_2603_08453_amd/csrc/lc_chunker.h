@@ -53,6 +53,8 @@ inline int lc_separator_level(const LcTokenText& t) {
 // chunk in ascending order and returns false to stop.  Only the tokens in the search windows are looked at.
 template <typename LevelF, typename CutF>
 inline bool lc_chunk_cuts(int64_t n, int64_t min_len, int64_t max_len, LevelF level, CutF cut) {
+    if (max_len > n) max_len = n;                            // (no chunk is longer than the text: the sums below stay in range)
+    if (min_len > max_len) min_len = max_len;
     int64_t pos = 0;
     while (pos < n) {
         const int64_t hi = (pos + max_len < n ? pos + max_len : n) - 1;

@@ -85,3 +85,18 @@ def test_library_chunker_takes_any_token_objects(n, distinct):
         lc.lc_chunk_tokens(toks + ["\ud800"], 4, 24)
     with pytest.raises(AttributeError):
         lc.lc_chunk_tokens(toks + [3], 4, 24)
+
+
+@pytest.mark.parametrize("n", [0, 1, 5, 160])
+def test_limits_beyond_the_text(n):
+    """A limit that no chunk can reach is no limit, up to the largest integer (a sum with it must not wrap)."""
+    import sys
+    from paper_2603_08453_amd import binding as lc
+    toks = (["a", "b", ".", "c"] * 40)[:n]
+    for big in (max(n, 4) + 1, 2 ** 31 - 1, 2 ** 31, sys.maxsize - 3, sys.maxsize):
+        assert lc.lc_chunk_tokens(toks, 4, big) == co.chunk_tokens(toks, 4, max(n, 4))
+        assert lc.lc_chunk_tokens(toks, big, big) == co.chunk_tokens(toks, max(n, 1), max(n, 1))
+    with pytest.raises(lc.LycheeError):
+        lc.lc_chunk_tokens(toks, sys.maxsize, 4)
+    with pytest.raises(OverflowError):
+        lc.lc_chunk_tokens(toks, 4, sys.maxsize + 1)
