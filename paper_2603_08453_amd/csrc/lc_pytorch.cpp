@@ -55,10 +55,18 @@ class Args {
         const at::Tensor* t = tensor(i);
         return t ? t->data_ptr() : nullptr;
     }
-    long integer(int i) {
-        if (PyLong_CheckExact(a_[i])) return PyLong_AsLong(a_[i]);
-        PyObject* const v = PyNumber_Long(a_[i]);
-        const long r = v ? PyLong_AsLong(v) : -1;
+    // What int(x) gives, in C's int (as ctypes passes it: the low 32 bits).
+    int integer(int i) {
+        PyObject* const v = PyLong_CheckExact(a_[i]) ? Py_NewRef(a_[i]) : PyNumber_Long(a_[i]);
+        const int r = v ? (int)PyLong_AsUnsignedLongMask(v) : -1;
+        Py_XDECREF(v);
+        return r;
+    }
+    // The same of an integer alone; a float or a text makes the call not ours (ctypes refuses it).
+    int whole(int i) {
+        if (!PyIndex_Check(a_[i])) { foreign_ = true; return -1; }
+        PyObject* const v = PyNumber_Index(a_[i]);
+        const int r = v ? (int)PyLong_AsUnsignedLongMask(v) : -1;
         Py_XDECREF(v);
         return r;
     }
@@ -118,7 +126,7 @@ PyObject* decode_step(PyObject*, PyObject* const* args, Py_ssize_t n) {
         if (!q || !K || !V || (!fixed && !ws) || a.foreign()) return false;
         int64_t s[3];
         if (!cache_strides(*K, *V, true, s)) return true;
-        const int budget = (int)a.integer(4), cap = ids ? (int)ids->size(-1) : 0;
+        const int budget = a.integer(4), cap = ids ? (int)ids->size(-1) : 0;
         float* const out = static_cast<float*>(a.ptr(5));
         float* const lse = static_cast<float*>(a.ptr(7));
         int32_t* const counts = static_cast<int32_t*>(a.ptr(9));
@@ -143,7 +151,7 @@ PyObject* retrieve(PyObject*, PyObject* const* args, Py_ssize_t n) {
     return guarded(a, [&](int* rc) {
         const at::Tensor *q = a.tensor(1), *ids = a.tensor(3), *ws = a.tensor(5);
         if (!q || !ids || !ws || a.foreign()) return false;
-        const int budget = (int)a.integer(2);
+        const int budget = a.whole(2);
         int32_t* const counts = static_cast<int32_t*>(a.ptr(4));
         float* const scores = static_cast<float*>(a.ptr(6));
         if (PyErr_Occurred() || a.foreign()) return false;

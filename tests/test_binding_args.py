@@ -1,0 +1,76 @@
+"""How the per-token calls marshal their arguments, without a GPU: the native module is bound to stand-ins for the
+library's entry points that record what they are called with."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_08453_amd import binding as lc
+
+VP, INT, SZ = ctypes.c_void_p, ctypes.c_int, ctypes.c_size_t
+SIGNATURES = {
+    "decode_step": (VP, VP, VP, VP, VP, INT, INT, VP, VP, VP, VP, INT, VP, SZ, VP),
+    "decode_step_static": (VP, VP, VP, VP, VP, INT, INT, VP, VP, VP, VP, INT, VP),
+    "retrieve": (VP, VP, INT, INT, VP, VP, VP, INT, VP, SZ, VP),
+    "sparse_decode": (VP, VP, VP, VP, VP, VP, VP, INT, INT, VP, VP, VP, SZ, VP),
+    "append": (VP, VP, VP, VP, VP, VP, VP, VP, SZ, VP),
+}
+
+
+class Stream:
+    cuda_stream = 0
+
+
+class FakeIndex:
+    handle = None
+    address = 0x1000
+
+
+@pytest.fixture()
+def calls():
+    """name -> arguments of the last call that reached the (stand-in) library."""
+    seen = {}
+    keep = []
+    for name, sig in SIGNATURES.items():
+        def record(*a, name=name):
+            seen[name] = a
+            if name == "append":
+                seen["flags"] = ctypes.string_at(a[6], 4) if a[6] else None
+            return 0
+        keep.append(ctypes.CFUNCTYPE(INT, *sig)(record))
+    lc._fast().bind(*(ctypes.cast(f, VP).value for f in keep))
+    yield seen
+    lc._fast_mod = None                                      # (the next call binds the library again)
+    lc._fast()
+
+
+def tensors(B=1, H=2, G=2, T=8, cap=5):
+    return dict(q=torch.zeros(B, H * G, 128, dtype=torch.bfloat16), K=torch.zeros(B, H, T, 128, dtype=torch.bfloat16),
+                V=torch.zeros(B, H, T, 128, dtype=torch.bfloat16), out=torch.zeros(B, H * G, 128), ws=torch.zeros(256, dtype=torch.uint8),
+                ids=torch.zeros(B, H, cap, dtype=torch.int32), counts=torch.zeros(B, H, dtype=torch.int32))
+
+
+@pytest.mark.parametrize("budget,want", [(1024, 1024), (np.int64(7), 7), (True, 1), (torch.tensor(9), 9), (2 ** 40 + 3, 3),
+                                         (2 ** 80 + 5, 5), (1024.9, None), ("1024", None), (None, None)])
+def test_budget_of_a_retrieval_is_an_integer(calls, budget, want):
+    t = tensors()
+    args = (FakeIndex, t["q"], budget, t["ids"], t["counts"], t["ws"])
+    if want is None:
+        with pytest.raises(ctypes.ArgumentError):
+            lc.lc_retrieve(*args, stream=Stream)
+        assert "retrieve" not in calls
+    else:
+        lc.lc_retrieve(*args, stream=Stream)
+        assert calls["retrieve"][2:4] == (4, want) and calls["retrieve"][7] == 5
+
+
+@pytest.mark.parametrize("budget,want", [(1024, 1024), (np.int64(7), 7), (1024.9, 1024), ("1024", 1024), (2 ** 40 + 3, 3)])
+def test_budget_of_a_step_is_what_int_gives(calls, budget, want):
+    t = tensors()
+    lc.lc_decode_step(FakeIndex, t["q"], t["K"], t["V"], budget, t["out"], t["ws"], stream=Stream)
+    assert calls["decode_step"][5:7] == (4, want)
+    lc.lc_decode_step_static(FakeIndex, t["q"], t["K"], t["V"], budget, t["out"], stream=Stream)
+    assert calls["decode_step_static"][5:7] == (4, want)
+    with pytest.raises(ValueError):
+        lc.lc_decode_step(FakeIndex, t["q"], t["K"], t["V"], "many", t["out"], t["ws"], stream=Stream)
