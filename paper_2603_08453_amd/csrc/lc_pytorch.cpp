@@ -99,6 +99,18 @@ bool cache_strides(const at::Tensor& K, const at::Tensor& V, bool shapes, int64_
     for (int i = 0; i < 3; ++i) s[i] = K.stride(i);
     return true;
 }
+// The interpreter is free for other threads while a call is in the library, as it is under ctypes: a launch can block
+// (a full hardware queue).  Everything the call needs has been read from the Python objects before.
+class Unlocked {
+  public:
+    Unlocked() : state_(PyEval_SaveThread()) {}
+    ~Unlocked() { PyEval_RestoreThread(state_); }
+    Unlocked(const Unlocked&) = delete;
+    Unlocked& operator=(const Unlocked&) = delete;
+
+  private:
+    PyThreadState* state_;
+};
 size_t bytes(const at::Tensor& t) { return (size_t)t.numel() * t.element_size(); }
 
 // The result of a call, or NotImplemented / the pending Python error.
@@ -134,12 +146,15 @@ PyObject* decode_step(PyObject*, PyObject* const* args, Py_ssize_t n) {
         int32_t* const idp = ids ? static_cast<int32_t*>(ids->data_ptr()) : nullptr;
         void* const st = a.stream(10);
         if (PyErr_Occurred()) return false;
-        if (fixed)
-            *rc = g_decode_step_static(a.handle(0), q->data_ptr(), K->data_ptr(), V->data_ptr(), s, (int)q->size(1), budget,
-                                       out, lse, idp, counts, cap, st);
-        else
-            *rc = g_decode_step(a.handle(0), q->data_ptr(), K->data_ptr(), V->data_ptr(), s, (int)q->size(1), budget, out,
-                                lse, idp, counts, cap, ws->data_ptr(), bytes(*ws), st);
+        lc_index* const idx = a.handle(0);
+        if (PyErr_Occurred()) return false;
+        const void *qd = q->data_ptr(), *kd = K->data_ptr(), *vd = V->data_ptr();
+        void* const wd = fixed ? nullptr : ws->data_ptr();
+        const size_t wn = fixed ? 0 : bytes(*ws);
+        const int H_q = (int)q->size(1);
+        const Unlocked unlocked;
+        *rc = fixed ? g_decode_step_static(idx, qd, kd, vd, s, H_q, budget, out, lse, idp, counts, cap, st)
+                    : g_decode_step(idx, qd, kd, vd, s, H_q, budget, out, lse, idp, counts, cap, wd, wn, st);
         return true;
     });
 }
@@ -157,8 +172,15 @@ PyObject* retrieve(PyObject*, PyObject* const* args, Py_ssize_t n) {
         if (PyErr_Occurred() || a.foreign()) return false;
         void* const st = a.stream(7);
         if (PyErr_Occurred()) return false;
-        *rc = g_retrieve(a.handle(0), q->data_ptr(), (int)q->size(1), budget, static_cast<int32_t*>(ids->data_ptr()), counts,
-                         scores, (int)ids->size(2), ws->data_ptr(), bytes(*ws), st);
+        lc_index* const idx = a.handle(0);
+        if (PyErr_Occurred()) return false;
+        const void* const qd = q->data_ptr();
+        int32_t* const idp = static_cast<int32_t*>(ids->data_ptr());
+        const int H_q = (int)q->size(1), cap = (int)ids->size(2);
+        void* const wd = ws->data_ptr();
+        const size_t wn = bytes(*ws);
+        const Unlocked unlocked;
+        *rc = g_retrieve(idx, qd, H_q, budget, idp, counts, scores, cap, wd, wn, st);
         return true;
     });
 }
@@ -178,9 +200,15 @@ PyObject* sparse_decode(PyObject*, PyObject* const* args, Py_ssize_t n) {
         if (a.foreign()) return false;
         void* const st = a.stream(9);
         if (PyErr_Occurred()) return false;
-        *rc = g_sparse_decode(a.handle(0), q->data_ptr(), K->data_ptr(), V->data_ptr(), s,
-                              static_cast<const int32_t*>(ids->data_ptr()), counts, (int)ids->size(2), (int)q->size(1), out,
-                              lse, ws->data_ptr(), bytes(*ws), st);
+        lc_index* const idx = a.handle(0);
+        if (PyErr_Occurred()) return false;
+        const void *qd = q->data_ptr(), *kd = K->data_ptr(), *vd = V->data_ptr();
+        const int32_t* const idp = static_cast<const int32_t*>(ids->data_ptr());
+        const int H_q = (int)q->size(1), cap = (int)ids->size(2);
+        void* const wd = ws->data_ptr();
+        const size_t wn = bytes(*ws);
+        const Unlocked unlocked;
+        *rc = g_sparse_decode(idx, qd, kd, vd, s, idp, counts, cap, H_q, out, lse, wd, wn, st);
         return true;
     });
 }
@@ -211,8 +239,14 @@ PyObject* append(PyObject*, PyObject* const* args, Py_ssize_t n) {
         }
         void* const st = a.stream(7);
         if (PyErr_Occurred()) return false;
-        *rc = g_append(a.handle(0), K->data_ptr(), V->data_ptr(), s, k->data_ptr(), v->data_ptr(), given ? flags : nullptr,
-                       ws->data_ptr(), bytes(*ws), st);
+        lc_index* const idx = a.handle(0);
+        if (PyErr_Occurred()) return false;
+        void *kd = K->data_ptr(), *vd = V->data_ptr();
+        const void *kn = k->data_ptr(), *vn = v->data_ptr();
+        void* const wd = ws->data_ptr();
+        const size_t wn = bytes(*ws);
+        const Unlocked unlocked;
+        *rc = g_append(idx, kd, vd, s, kn, vn, given ? flags : nullptr, wd, wn, st);
         return true;
     });
 }

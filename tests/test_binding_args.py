@@ -74,3 +74,42 @@ def test_budget_of_a_step_is_what_int_gives(calls, budget, want):
     assert calls["decode_step_static"][5:7] == (4, want)
     with pytest.raises(ValueError):
         lc.lc_decode_step(FakeIndex, t["q"], t["K"], t["V"], "many", t["out"], t["ws"], stream=Stream)
+
+
+@pytest.mark.parametrize("call", ["retrieve", "decode_step", "decode_step_static", "sparse_decode", "append"])
+def test_other_threads_run_while_the_library_works(call):
+    """The library's entry points replaced by the C library's usleep, whose argument is the handle: 200 ms in which
+    another thread has to get on."""
+    import threading
+    usleep = ctypes.cast(ctypes.CDLL(None).usleep, VP).value
+    lc._fast().bind(*[usleep] * 5)
+    try:
+        class Sleep:
+            handle = None
+            address = 200_000
+        t, ticks, done = tensors(), [0], threading.Event()
+        row = torch.zeros(1, 2, 128, dtype=torch.bfloat16)
+
+        def tick():
+            while not done.wait(0.001):
+                ticks[0] += 1
+        thread = threading.Thread(target=tick)
+        thread.start()
+        before = ticks[0]
+        if call == "retrieve":
+            lc.lc_retrieve(Sleep, t["q"], 8, t["ids"], t["counts"], t["ws"], stream=Stream)
+        elif call == "decode_step":
+            lc.lc_decode_step(Sleep, t["q"], t["K"], t["V"], 8, t["out"], t["ws"], stream=Stream)
+        elif call == "decode_step_static":
+            lc.lc_decode_step_static(Sleep, t["q"], t["K"], t["V"], 8, t["out"], stream=Stream)
+        elif call == "sparse_decode":
+            lc.lc_sparse_decode(Sleep, t["q"], t["K"], t["V"], t["ids"], t["counts"], t["out"], t["ws"], stream=Stream)
+        else:
+            lc.lc_append(Sleep, t["K"], t["V"], row, row, [1], t["ws"], stream=Stream)
+        got = ticks[0] - before
+        done.set()
+        thread.join()
+        assert got >= 5
+    finally:
+        lc._fast_mod = None
+        lc._fast()
