@@ -100,3 +100,31 @@ def test_limits_beyond_the_text(n):
         lc.lc_chunk_tokens(toks, sys.maxsize, 4)
     with pytest.raises(OverflowError):
         lc.lc_chunk_tokens(toks, 4, sys.maxsize + 1)
+
+
+def test_list_changed_by_the_collector():
+    """The cyclic collector may run when the result list is made, and a finalizer may empty the caller's list then."""
+    import gc
+    from paper_2603_08453_amd import binding as lc
+    chunk = lc._host().chunk_tokens
+    toks = [f"token{i}." for i in range(5000)]
+
+    class Trap:
+        def __del__(self):
+            toks.clear()
+
+    was = gc.get_threshold()
+    gc.collect()
+    gc.disable()
+    try:
+        gc.set_threshold(1)
+        t = Trap()
+        t.me = t
+        del t
+        keep = [[] for _ in range(10)]                       # (enough new objects for a collection to be due)
+        gc.enable()
+        got = chunk(toks, 4, 24)
+    finally:
+        gc.set_threshold(*was)
+        gc.enable()
+    assert len(keep) == 10 and toks == [] and got == [0]
