@@ -225,12 +225,13 @@ PyObject* append(PyObject*, PyObject* const* args, Py_ssize_t n) {
         uint8_t flags[1024] = {};                            // lc_append takes at most 1024 sequences
         const bool given = a[5] != Py_None;
         if (given) {
-            PyObject* const seq = PySequence_Fast(a[5], "close_chunk must be a sequence");
+            // (a tuple of its own: telling whether an element is true can run code that changes the caller's list)
+            PyObject* const seq = PyObject_Size(a[5]) >= 0 ? PySequence_Tuple(a[5]) : nullptr;
             if (!seq) return false;
-            const Py_ssize_t m = PySequence_Fast_GET_SIZE(seq);
+            const Py_ssize_t m = PyTuple_GET_SIZE(seq);
             bool ok = m <= (Py_ssize_t)sizeof(flags);
             for (Py_ssize_t i = 0; ok && i < m; ++i) {
-                const int t = PyObject_IsTrue(PySequence_Fast_GET_ITEM(seq, i));
+                const int t = PyObject_IsTrue(PyTuple_GET_ITEM(seq, i));
                 if (t < 0) ok = false;
                 else flags[i] = (uint8_t)t;
             }

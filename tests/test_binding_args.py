@@ -113,3 +113,30 @@ def test_other_threads_run_while_the_library_works(call):
     finally:
         lc._fast_mod = None
         lc._fast()
+
+
+def test_close_flags(calls):
+    """Any sized iterable of truth values; one that an element's truth value shortens is read as it was."""
+    t = tensors(B=4)
+    row = torch.zeros(4, 2, 128, dtype=torch.bfloat16)
+
+    def flags(close):
+        calls.clear()
+        lc.lc_append(FakeIndex, t["K"], t["V"], row, row, close, t["ws"], stream=Stream)
+        return calls["flags"]
+
+    assert flags(None) is None
+    assert flags([0, 1, 0, 1]) == flags((False, True, None, "x")) == flags(np.array([0, 1, 0, 2])) == b"\0\1\0\1"
+    assert flags([1]) == b"\1\0\0\0"
+    with pytest.raises(TypeError):
+        flags(x for x in (1, 0, 1, 0))
+    with pytest.raises(TypeError):
+        flags(3)
+
+    class Shortens:
+        def __bool__(self):
+            del changing[1:]
+            return True
+
+    changing = [Shortens(), 0, [1], [1]]
+    assert flags(changing) == b"\1\0\1\1"
