@@ -140,3 +140,34 @@ def test_close_flags(calls):
 
     changing = [Shortens(), 0, [1], [1]]
     assert flags(changing) == b"\1\0\1\1"
+
+
+def test_calls_without_the_native_module(monkeypatch):
+    """ctypes marshals the per-token calls then, and says so once; here they reach the library, which refuses the
+    null handle before any GPU work."""
+    import sys
+    import warnings
+    monkeypatch.setattr(lc, "_fast_mod", None)
+    monkeypatch.delattr(sys.modules[lc.__package__], "_lychee_torch", raising=False)
+    monkeypatch.setitem(sys.modules, lc.__package__ + "._lychee_torch", None)
+
+    class Closed:
+        handle = None
+        address = 0
+
+    t = tensors()
+    row = torch.zeros(1, 2, 128, dtype=torch.bfloat16)
+    with pytest.warns(RuntimeWarning, match="ctypes marshals"):
+        with pytest.raises(lc.LycheeError) as e:
+            lc.lc_retrieve(Closed, t["q"], 8, t["ids"], t["counts"], t["ws"], stream=Stream)
+        assert e.value.code == lc.LC_ERR_INVALID_ARG
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")
+        for call in (lambda: lc.lc_decode_step(Closed, t["q"], t["K"], t["V"], 8, t["out"], t["ws"], stream=Stream),
+                     lambda: lc.lc_decode_step_static(Closed, t["q"], t["K"], t["V"], 8, t["out"], stream=Stream),
+                     lambda: lc.lc_sparse_decode(Closed, t["q"], t["K"], t["V"], t["ids"], t["counts"], t["out"], t["ws"],
+                                                 stream=Stream),
+                     lambda: lc.lc_append(Closed, t["K"], t["V"], row, row, [1], t["ws"], stream=Stream)):
+            with pytest.raises(lc.LycheeError) as e:
+                call()
+            assert e.value.code == lc.LC_ERR_INVALID_ARG
