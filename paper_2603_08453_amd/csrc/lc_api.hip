@@ -311,17 +311,15 @@ struct LcAnswer {
     float* host = nullptr;
     size_t floats = 0;
 };
-constexpr size_t LC_ANSWERS_KEPT = 4;
-std::vector<LcAnswer> g_answers;
+constexpr int LC_ANSWERS_KEPT = 4;
+LcAnswer g_answers[LC_ANSWERS_KEPT];
+int g_n_answers = 0;
 std::mutex g_answers_mutex;
 
 int take_answer(size_t floats, LcAnswer* a) {
     {
         std::lock_guard<std::mutex> lock(g_answers_mutex);
-        if (!g_answers.empty()) {
-            *a = g_answers.back();
-            g_answers.pop_back();
-        }
+        if (g_n_answers > 0) *a = g_answers[--g_n_answers];
     }
     if (a->floats >= floats) return LC_OK;
     if (a->host) {
@@ -336,8 +334,8 @@ int take_answer(size_t floats, LcAnswer* a) {
 void give_back(const LcAnswer& a) {
     {
         std::lock_guard<std::mutex> lock(g_answers_mutex);
-        if (g_answers.size() < LC_ANSWERS_KEPT) {
-            g_answers.push_back(a);
+        if (g_n_answers < LC_ANSWERS_KEPT) {
+            g_answers[g_n_answers++] = a;
             return;
         }
     }
@@ -446,14 +444,12 @@ int lc_index_drift(const lc_index* idx, int level, float* drift, void* ws, size_
     int rc = take_answer(n, &a);
     if (rc) return rc;
     rc = lc_launch_drift(idx, level, a.host, s);
-    if (rc == LC_OK) {
-        const hipError_t e = hipStreamSynchronize(s);
-        if (e == hipSuccess) memcpy(drift, a.host, n * sizeof(float));
-        else {
-            lc_set_hip_error(e);
-            rc = LC_ERR_HIP;
-        }
+    const hipError_t e = hipStreamSynchronize(s);
+    if (e != hipSuccess) {                 // the kernel may still write the answer: the memory is left to it
+        lc_set_hip_error(e);
+        return LC_ERR_HIP;
     }
+    if (rc == LC_OK) memcpy(drift, a.host, n * sizeof(float));
     give_back(a);
     return rc;
 }
