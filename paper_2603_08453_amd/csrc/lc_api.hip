@@ -256,6 +256,22 @@ int stage_reserve(size_t ints, LcStage** out) {
     return LC_OK;
 }
 
+// After the launch (of result rc) of a kernel that reads the buffer: marks it.  Where that fails the stream is waited for,
+// and where that fails too the buffer is left to the kernel: never written or freed again, the slot gets a new one.
+int stage_launched(LcStage* st, int rc, hipStream_t stream) {
+    if (rc == LC_OK) {
+        const hipError_t e = hipEventRecord(st->read, stream);
+        if (e == hipSuccess) return LC_OK;
+        lc_set_hip_error(e);
+        rc = LC_ERR_HIP;
+    }
+    if (hipStreamSynchronize(stream) != hipSuccess) {
+        st->host = nullptr;
+        st->ints = 0;
+    }
+    return rc;
+}
+
 // state, nlev, zeroed arrival counters and chunk boundaries -> device: staged as [state | nlev | where each sequence's
 // boundaries begin | boundaries of all sequences] and put in place by one kernel.
 int upload_state(lc_index* h, const int32_t* bounds_concat, hipStream_t stream) {
@@ -285,10 +301,7 @@ int upload_state(lc_index* h, const int32_t* bounds_concat, hipStream_t stream) 
     }
     for (size_t i = 0; i < n_nlev; ++i) p[n_state + i] = h->N[i];
     memcpy(p + head, bounds_concat, n_bounds * sizeof(int32_t));
-    rc = lc_launch_place_state(h, p, max_M, stream);
-    if (rc != LC_OK) return rc;
-    LC_HIP_CHECK(hipEventRecord(st->read, stream));
-    return LC_OK;
+    return stage_launched(st, lc_launch_place_state(h, p, max_M, stream), stream);
 }
 
 // nodes per level -> device (lc_recluster)
@@ -299,10 +312,7 @@ int upload_level_counts(lc_index* h, hipStream_t stream) {
     int rc = stage_reserve(n_nlev, &st);
     if (rc != LC_OK) return rc;
     for (size_t i = 0; i < n_nlev; ++i) st->host[i] = h->N[i];
-    rc = lc_launch_place_counts(h, st->host, stream);
-    if (rc != LC_OK) return rc;
-    LC_HIP_CHECK(hipEventRecord(st->read, stream));
-    return LC_OK;
+    return stage_launched(st, lc_launch_place_counts(h, st->host, stream), stream);
 }
 
 // Pinned memory that a kernel of a waiting call writes its answer into, taken from a short list of spare ones and put

@@ -134,8 +134,8 @@ int main() {
 
     struct Call { const char* name; bool may_fail; std::function<int()> run; };
     const std::vector<Call> calls = {
-        {"build", false, [&] { lc_index* i = nullptr; const int rc = build(&i); lc_index_destroy(i); return rc; }},
-        {"recluster", false, [&] { return lc_recluster(idx, ws, wb, s); }},
+        {"build", true, [&] { lc_index* i = nullptr; const int rc = build(&i); lc_index_destroy(i); return rc; }},
+        {"recluster", true, [&] { return lc_recluster(idx, ws, wb, s); }},
         {"drift", true, [&] { return lc_index_drift(idx, 1, drift.data(), ws, wb, s); }},
         {"export", false, [&] { size_t n = bytes; return lc_index_export(idx, copy.data(), &n, s); }},
         {"import", false, [&] {
