@@ -818,6 +818,25 @@ int blob_stage_ready(BlobStage* st, size_t rows) {
     return LC_OK;
 }
 
+// End of a call (of result rc) that used the windows: waits for its kernels, so that every call finds the windows idle,
+// after an error too.  Where the stream cannot be waited for, windows and table are left to the kernels that may
+// still use them, and the next call makes new ones.
+int blob_stage_done(BlobStage* st, int rc, hipStream_t s) {
+    const hipError_t e = hipStreamSynchronize(s);
+    if (e == hipSuccess) return rc;
+    lc_set_hip_error(e);
+    st->window = nullptr;
+    st->table = nullptr;
+    st->table_rows = 0;
+    return LC_ERR_HIP;
+}
+
+// Waits for the kernel that last used a slot's window in this call.
+int blob_slot_wait(BlobStage* st, int slot) {
+    LC_HIP_CHECK(hipEventSynchronize(st->done[slot]));
+    return LC_OK;
+}
+
 int blob_device(BlobStage** out) {
     int dev = 0;
     LC_HIP_CHECK(hipGetDevice(&dev));
@@ -873,7 +892,7 @@ int lc_index_export(const lc_index* idx, void* blob, size_t* bytes, void* stream
     if (rc) return rc;
     LcBlobMap m;
     blob_map(idx, &m, st->table);
-    // windows in flight ahead of the one being copied out
+    // windows in flight ahead of the one being copied out; a slot's is started again once it has been
     const unsigned long long n_win = (m.total + LC_BLOB_WINDOW - 1) / LC_BLOB_WINDOW;
     auto start = [&](unsigned long long k) -> int {
         const int slot = (int)(k % LC_BLOB_SLOTS);
@@ -886,13 +905,13 @@ int lc_index_export(const lc_index* idx, void* blob, size_t* bytes, void* stream
     for (unsigned long long k = 0; k < n_win && k < LC_BLOB_SLOTS && rc == LC_OK; ++k) rc = start(k);
     for (unsigned long long k = 0; k < n_win && rc == LC_OK; ++k) {
         const int slot = (int)(k % LC_BLOB_SLOTS);
-        LC_HIP_CHECK(hipEventSynchronize(st->done[slot]));
+        rc = blob_slot_wait(st, slot);
+        if (rc) break;
         memcpy(static_cast<char*>(blob) + (size_t)k * LC_BLOB_WINDOW * 4, st->window + (size_t)slot * LC_BLOB_WINDOW,
                (size_t)blob_window_words(m, k) * 4);
         if (k + LC_BLOB_SLOTS < n_win) rc = start(k + LC_BLOB_SLOTS);
     }
-    LC_HIP_CHECK(hipStreamSynchronize(s));
-    return rc;
+    return blob_stage_done(st, rc, s);
 }
 
 namespace {
@@ -907,17 +926,21 @@ int import_nodes(const lc_index* idx, const void* blob, hipStream_t s) {
     LcBlobMap m;
     blob_map(idx, &m, st->table);
     const unsigned long long n_win = (m.total + LC_BLOB_WINDOW - 1) / LC_BLOB_WINDOW;
+    auto mark = [&](int slot) -> int {
+        LC_HIP_CHECK(hipEventRecord(st->done[slot], s));
+        return LC_OK;
+    };
     for (unsigned long long k = 0; k < n_win && rc == LC_OK; ++k) {
         const int slot = (int)(k % LC_BLOB_SLOTS);
         uint32_t* const w = st->window + (size_t)slot * LC_BLOB_WINDOW;
         const unsigned n = blob_window_words(m, k);
-        LC_HIP_CHECK(hipEventSynchronize(st->done[slot]));      // (an event never recorded is complete)
+        if (k >= LC_BLOB_SLOTS) rc = blob_slot_wait(st, slot);
+        if (rc) break;
         memcpy(w, static_cast<const char*>(blob) + (size_t)k * LC_BLOB_WINDOW * 4, (size_t)n * 4);
         rc = lc_launch_blob_import(idx->dev, m, st->table, k * LC_BLOB_WINDOW, n, w, s);
-        if (rc == LC_OK) LC_HIP_CHECK(hipEventRecord(st->done[slot], s));
+        if (rc == LC_OK) rc = mark(slot);
     }
-    LC_HIP_CHECK(hipStreamSynchronize(s));
-    return rc;
+    return blob_stage_done(st, rc, s);
 }
 }  // namespace
 
