@@ -1301,7 +1301,7 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* ce
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 lc_assign_merge(best[r], arg[r]);
-                const int ba = arg[r], i = i0 + 4 * kk + r;
+                const int ba = arg[r] < k ? arg[r] : 0, i = i0 + 4 * kk + r;     // (no similarity that compares: not-a-number)
                 if (j == 0 && i < N) {
                     if (lab[i] != ba) changed[it & 1] = 1;
                     lab[i] = ba;

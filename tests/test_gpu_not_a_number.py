@@ -1,0 +1,80 @@
+"""Keys that are not a number or infinite.  The direction of a vector whose length is not a number is e_0, like the zero
+vector's; an infinite component leaves a direction that compares with nothing, and such a point goes to cluster 0 of its
+level whatever its neighbours are.  Every stored index stays inside its array, and no other chunk is affected beyond
+what its cluster's mean is."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def setup(chunks, F, levels, iters, bad, H=2, centers=0, geometry=0, room=0, seed=0):
+    """GPU index over one sequence of chunks of 1 to 3 tokens, some with a value of `bad` (chunk -> value) among their
+    keys in head 0; head 1 has none."""
+    import torch
+    from paper_2603_08453_amd import binding as lc
+    r = np.random.default_rng(seed)
+    bounds = np.concatenate([[0], np.cumsum(r.integers(1, 4, size=chunks))]).astype(np.int32)
+    T = int(bounds[-1])
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    K = torch.randn((1, H, T + room, 128), generator=g, device="cuda").to(torch.bfloat16)
+    for j, value in bad.items():
+        K[0, 0, bounds[j + 1] - 1, (37 * j) % 128] = value
+    cfg = lc.lc_config_default(levels=levels, fanout=F, kmeans_iters=iters, max_chunks=chunks + room, max_tokens=T + room,
+                               center_dtype=centers, geometry=geometry)
+    ib = torch.zeros(lc.lc_index_bytes(cfg, 1, H), dtype=torch.uint8, device="cuda")
+    ws = torch.full((lc.lc_workspace_bytes(cfg, 1, H, H),), 0xA5, dtype=torch.uint8, device="cuda")
+    return lc, lc.lc_build_index(cfg, K, [T], [bounds], ib, ws), K, ws
+
+
+def head(lc, idx, h=0):
+    return lc.unpack_blob(lc.lc_index_export(idx))["seqs"][0]["heads"][h]
+
+
+def directions(c):
+    n2 = (c * c).sum(axis=1)
+    e0 = np.eye(1, c.shape[1])
+    return np.where((n2 > 0)[:, None], c * (1.0 / np.sqrt(np.where(n2 > 0, n2, 1.0)))[:, None], e0)
+
+
+def check_labels(lab, x, cent):
+    """Nearest centroid among those that compare; cluster 0 where none does."""
+    s = x @ cent.T
+    none = np.isnan(s).all(axis=1)
+    assert np.all(lab[none] == 0)
+    s = np.where(np.isnan(s), -np.inf, s)[~none]
+    lab = lab[~none]
+    assert np.all(s[np.arange(len(s)), lab] >= s.max(axis=1) - 3e-6)
+    clear = np.partition(s, -2, axis=1)[:, -2] < s.max(axis=1) - 3e-6 if s.shape[1] > 1 else np.ones(len(s), bool)
+    assert np.array_equal(lab[clear], s.argmax(axis=1)[clear])
+
+
+def check_clustering(chunks, F, bad, centers=0):
+    """The first two iterations of the chunk level's clustering."""
+    heads = []
+    with np.errstate(invalid="ignore"):
+        for iters in (1, 2):
+            lc, idx, _, _ = setup(chunks, F, 2, iters, bad, centers=centers)
+            heads.append(head(lc, idx))
+        x = directions(heads[0][0]["center"].astype(np.float64))
+        k, lab = len(heads[0][1]["radius"]), heads[0][0]["parent"]
+        assert np.isnan(x).any(axis=1).sum() == sum(np.isinf(v) for v in bad.values())
+        cent = x[(np.arange(k) * chunks) // k].copy()
+        check_labels(lab, x, cent)
+        for c in range(k):
+            s = x[lab == c].sum(axis=0)
+            if s @ s > 0:                                    # (not where it is not a number: the centroid stays)
+                cent[c] = s / np.sqrt(s @ s)
+        check_labels(heads[1][0]["parent"], x, cent)
+
+
+NAN, INF = float("nan"), float("inf")
+# chunks that start a centroid and chunks that start none, neighbours, the first and the last
+SOME = {0: INF, 5: NAN, 6: INF, 33: -INF, 64: -INF, 101: INF, 104: NAN, 199: INF}
+
+
+@pytest.mark.parametrize("chunks,F,bad", [(200, 8, SOME), (200, 4, {7: INF}), (224, 112, SOME), (3, 2, {0: INF, 1: NAN, 2: INF}),
+                                          (3, 1, {0: INF, 1: INF, 2: INF})])
+def test_one_kernel_clustering(chunks, F, bad):
+    check_clustering(chunks, F, bad)
