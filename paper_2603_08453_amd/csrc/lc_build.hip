@@ -140,7 +140,7 @@ __device__ __forceinline__ void lc_store8(float* p, const float (&v)[8]) {
 __device__ __forceinline__ void lc_store8_bf16(uint16_t* p, const float (&v)[8]) {
     uint32_t h[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) h[i] = lc_f32_to_bf16_bits(v[i]);
+    for (int i = 0; i < 8; ++i) h[i] = v[i] == v[i] ? lc_f32_to_bf16_bits(v[i]) : 0x7fc0u;      // (rounding may carry a not-a-number into 0 or infinity)
     *reinterpret_cast<uint4*>(p) = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
 }
 __device__ __forceinline__ void lc_load8(const float* p, float (&v)[8]) {
@@ -546,7 +546,7 @@ __device__ __forceinline__ void lc_assign_finish(LcAssignSh<WP, NW>& sh, const f
         }
         lc_wave_sync();
     }
-    // ---- too many candidates (or none: not-a-number): every centroid in float32, 16 such points of the
+    // ---- too many candidates (or none, or marked as such: not-a-number): every centroid in float32, 16 such points of the
     // workgroup at a time, an equal share of the centroids per wavefront
     if (mine && (n_c == 0 || n_c > LC_AS_CAND)) sh.rest_p[atomicAdd(&sh.n_rest, 1)] = (uint8_t)(wave * WP + lane);
     __syncthreads();
@@ -682,7 +682,10 @@ lc_kmeans_assign_res_kernel(LcDev ix, int l, const float* pts, const uint16_t* p
 // as the matrix instruction's starting accumulator, so a candidate is a result >= 0, and a step of 32
 // centroids costs a maximum over its results and a branch that is rarely taken.  The first iteration
 // needs a sweep for the largest similarity before the one for the candidates; later ones start from the
-// similarity to the point's previous centroid (a float32 dot product).
+// similarity to the point's previous centroid (a float32 dot product).  Hits are read off the results' sign bits, and a
+// result that is not a number may have either: so a point of which no similarity compares is marked beforehand as one
+// with too many candidates (float32 decides: cluster 0), and what a centroid of that kind adds to the other points'
+// candidates falls away in the float32 comparison, where their nearest one always is a candidate too.
 // Measured, 8 heads of 10.9 K points x 5461 centroids (122 GFLOP a sweep): first iteration 251 us, the second
 // 149 us; the three iterations of such a clustering took 2.7 ms in float32 and take 0.5 ms.
 template <int MA>
@@ -797,6 +800,7 @@ lc_kmeans_assign_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
                 v = fmaxf(v, lc_dpp<0x141>(v));
                 v = fmaxf(v, lc_dpp<0x140>(v));
                 start[a][r] = 2.0f * LC_AS_EPS - v;
+                if (j == 0 && !(v > LC_NEG_INF)) sh.cand_n[wave][16 * a + 4 * kk + r] = LC_AS_CAND + 1;
             }
         lc_barrier_lds();                                           // the last tile has been used
     } else {
@@ -814,6 +818,7 @@ lc_kmeans_assign_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
             for (int t = 0; t < 8; ++t) s = fmaf(x[t], m[t], s);
             s = lc_sum16(s);
             if (j == 0) sh.pair_v[wave][4 * MA * kk + e] = s;
+            if (j == 0 && !(s == s)) sh.cand_n[wave][4 * MA * kk + e] = LC_AS_CAND + 1;
         }
         lc_wave_sync();
 #pragma unroll

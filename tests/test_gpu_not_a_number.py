@@ -78,3 +78,24 @@ SOME = {0: INF, 5: NAN, 6: INF, 33: -INF, 64: -INF, 101: INF, 104: NAN, 199: INF
                                           (3, 1, {0: INF, 1: INF, 2: INF})])
 def test_one_kernel_clustering(chunks, F, bad):
     check_clustering(chunks, F, bad)
+
+
+# centroids in registers (up to 256 of them), then in tiles; every kernel of either kind by the number of points
+@pytest.mark.parametrize("chunks,F", [(600, 16), (1100, 8), (1500, 6), (514, 2), (1300, 4), (2200, 4), (5001, 8), (10922, 2)])
+def test_tiled_clustering(chunks, F):
+    bad = {j: v for j, v in SOME.items() if j < chunks}
+    bad.update({chunks // 2 + 3 * i: INF if i % 3 else NAN for i in range(40)})
+    bad[chunks - 1] = -INF
+    check_clustering(chunks, F, bad)
+    check_clustering(chunks, F, {j: -INF for j in range(0, chunks, 2)}, centers=1)
+
+
+def test_tiled_clustering_without_a_point_that_compares():
+    check_clustering(1300, 4, {j: INF for j in range(1300)})
+
+
+@pytest.mark.parametrize("value", [INF, -INF])
+def test_neighbours_candidate_is_no_candidate(value):
+    """The last chunk shares its lanes with one finite chunk alone, the one that starts the last centroid (the only
+    centroid of the last step): the one similarity there that is a hit must not become the infinite chunk's candidate."""
+    check_clustering(514, 2, {513: value})
