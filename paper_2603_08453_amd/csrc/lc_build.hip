@@ -1500,8 +1500,8 @@ lc_center_kernel(LcDev ix, int l, LcNodeArgs w) {
 // Radii of all levels above the chunks, once every center stands: for each chunk and each of its
 // ancestors the reach |center - ancestor's center| + chunk radius, maximum per node.  One pass over the
 // chunk rows instead of one per level.  Levels of few nodes collect their maxima in LDS first, so that the
-// top node is not one address that every chunk of the head queues for.  Radii are >= 0, so their bits
-// order like integers, and a maximum does not depend on the order.
+// top node is not one address that every chunk of the head queues for.  Radii are >= 0 (what is not a number is left
+// out, as fmaxf would), so their bits order like integers, and a maximum does not depend on the order.
 #define LC_RD_CHUNKS 64           // chunks of a workgroup
 #define LC_RD_LDS 512             // nodes (levels >= 2 together) whose maxima are collected in LDS
 __global__ void __launch_bounds__(LC_BT)
@@ -1551,7 +1551,7 @@ lc_radius_kernel(LcDev ix) {
             for (int t = 0; t < 8; ++t) { const float x = c[e][t] - mu[e][t]; d2 = fmaf(x, x, d2); }
             d2 = lc_sum16(d2);
             const float reach = lc_pad_radius(lc_pad_radius(sqrtf(d2)) + r0[e]);
-            if (sub == 0 && anc[e] >= 0) {
+            if (sub == 0 && anc[e] >= 0 && reach >= 0.f) {          // (not a number: reaches nothing)
                 if (l >= 2 && in_lds) atomicMax(&best[up + anc[e]], __float_as_int(reach));
                 else raise(l, anc[e], __float_as_int(reach));
             }

@@ -99,3 +99,31 @@ def test_neighbours_candidate_is_no_candidate(value):
     """The last chunk shares its lanes with one finite chunk alone, the one that starts the last centroid (the only
     centroid of the last step): the one similarity there that is a hit must not become the infinite chunk's candidate."""
     check_clustering(514, 2, {513: value})
+
+
+def check_radii(levels):
+    """Every node's radius covers the chunks below it of which the distance compares; none: no radius."""
+    with np.errstate(invalid="ignore"):
+        c0, r0 = levels[0]["center"].astype(np.float64), levels[0]["radius"].astype(np.float64)
+        anc = np.arange(len(r0))
+        for l in range(1, len(levels)):
+            par = levels[l - 1]["parent"]
+            k = len(levels[l]["radius"])
+            assert np.all((par >= 0) & (par < k))
+            anc = par[anc]
+            assert np.array_equal(levels[l]["nchunk"], np.bincount(anc, minlength=k))
+            assert np.array_equal(levels[l]["ntok"], np.bincount(anc, weights=levels[0]["ntok"], minlength=k).astype(np.int64))
+            reach = np.full(k, -np.inf)
+            np.fmax.at(reach, anc, np.linalg.norm(c0 - levels[l]["center"][anc].astype(np.float64), axis=1) + r0)
+            got, some = levels[l]["radius"].astype(np.float64), ~np.isneginf(reach)
+            assert np.all(np.isneginf(got[~some]))
+            assert np.all(got[some] >= reach[some]) and np.all(got[some] <= reach[some] * (1.0 + 3e-5) + 1e-6)
+
+
+@pytest.mark.parametrize("geometry", [0, 1])
+@pytest.mark.parametrize("chunks,F,levels", [(200, 8, 3), (1300, 4, 4), (2275, 16, 4), (4500, 2, 2)])
+def test_radii(chunks, F, levels, geometry):
+    for value in (NAN, INF):
+        lc, idx, _, _ = setup(chunks, F, levels, 3, {j: value for j in (0, 7, 8, 100, chunks - 1)}, geometry=geometry)
+        for h in (0, 1):
+            check_radii(head(lc, idx, h))
