@@ -1838,6 +1838,7 @@ lc_append_kernel(LcDev ix, uint16_t* K, uint16_t* V, long long ks_seq, long long
             const int ag = best_arg[g];
             if (sg > s || (sg == s && ag < p)) { s = sg; p = ag; }
         }
+        if (p >= n1) p = 0;                                 // (no similarity that compares: an infinite key)
         // path to the top: moving-average centers, monotone radii
         if (tid < 16) {
             int a = p;

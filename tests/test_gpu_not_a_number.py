@@ -127,3 +127,33 @@ def test_radii(chunks, F, levels, geometry):
         lc, idx, _, _ = setup(chunks, F, levels, 3, {j: value for j in (0, 7, 8, 100, chunks - 1)}, geometry=geometry)
         for h in (0, 1):
             check_radii(head(lc, idx, h))
+
+
+@pytest.mark.parametrize("value", [NAN, INF, -INF])
+@pytest.mark.parametrize("chunks,levels", [(3, 2), (40, 3), (600, 3)])
+def test_append(chunks, levels, value):
+    """An appended chunk that compares with no level-1 node goes to the first one; later ones are grafted as ever."""
+    import torch
+    lc, idx, K, ws = setup(chunks, 8, levels, 2, {}, room=4)
+    V = torch.zeros_like(K)
+    before = [head(lc, idx, h) for h in (0, 1)]
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    for i in range(4):
+        k = torch.randn((1, 2, 128), generator=g, device="cuda").to(torch.bfloat16)
+        if i == 0:
+            k[0, 0, 5] = value
+        lc.lc_append(idx, K, V, k, k, [1], ws)
+    with np.errstate(invalid="ignore"):
+        for h in (0, 1):
+            got = head(lc, idx, h)
+            k1 = len(got[1]["radius"])
+            new = got[0]["parent"][chunks:]
+            assert np.all((new >= 0) & (new < k1)) and np.array_equal(got[0]["parent"][:chunks], before[h][0]["parent"])
+            if h == 0 and np.isinf(value):
+                assert new[0] == 0
+            added = np.bincount(new, minlength=k1)
+            assert np.array_equal(got[1]["nchunk"], before[h][1]["nchunk"] + added)
+            calm = added == 0
+            for name in ("center", "radius"):
+                assert np.array_equal(got[1][name][calm], before[h][1][name][calm])
