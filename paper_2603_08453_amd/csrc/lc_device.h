@@ -95,8 +95,8 @@ __device__ __forceinline__ float4 lc_buf_load_f32x4(__amdgpu_buffer_rsrc_t r, in
     const int x = v.x, y = v.y, z = v.z, w = v.w;
     return make_float4(__int_as_float(x), __int_as_float(y), __int_as_float(z), __int_as_float(w));
 }
-// 4-byte and 1-byte reads and 4-byte writes through a range-checked buffer resource: an index outside
-// [0, extent) reads 0 / writes nothing instead of touching memory that is not the array's.
+// 4-byte and 1-byte reads through a range-checked buffer resource: an index outside [0, extent) reads 0 instead
+// of touching memory that is not the array's.
 __device__ __forceinline__ int lc_buf_load_i32(__amdgpu_buffer_rsrc_t r, int index) {
     return __builtin_amdgcn_raw_buffer_load_b32(r, index * 4, 0, 0);
 }
@@ -105,9 +105,6 @@ __device__ __forceinline__ float lc_buf_load_f32(__amdgpu_buffer_rsrc_t r, int i
 }
 __device__ __forceinline__ int lc_buf_load_u8(__amdgpu_buffer_rsrc_t r, int index) {
     return (int)(unsigned char)__builtin_amdgcn_raw_buffer_load_b8(r, index, 0, 0);
-}
-__device__ __forceinline__ void lc_buf_store_u32(__amdgpu_buffer_rsrc_t r, int index, uint32_t v) {
-    __builtin_amdgcn_raw_buffer_store_b32((int)v, r, index * 4, 0, 0);
 }
 // Returns true in every thread of the last workgroup to arrive at `counter` (of `expected`).
 __device__ __forceinline__ bool lc_arrive_last(int* counter, int expected, int* flag_sh) {
@@ -205,11 +202,6 @@ __device__ __forceinline__ float lc_score_frag(const LcNodeFrag& f, float R, con
         best = fmaxf(best, ub);
     }
     return best;
-}
-template <int G>
-__device__ __forceinline__ float lc_score_node(const float* __restrict__ center, float R, int sub,
-                                               const float (&qf)[G][8], const float (&qn)[G]) {
-    return lc_score_frag<G>(lc_load_node(center, sub), R, qf, qn);
 }
 // Eq. 2 for a chunk node from its loaded fragment (see lc_load_chunk_node).
 template <int G>

@@ -230,12 +230,11 @@ lc_upper_kernel(const LcRetrieveArgs a) {
     int* ew = ewA;
     uint32_t* ek_next = ekB;
     int* ew_next = ewB;
-    const bool with_tokens = true;
     {
         const int o = off_sh[L - 1], n_l = off_sh[L] - o;
         for (int i = tid; i < ((n_l + 3) & ~3); i += LC_UP_THREADS) {
             ek[i] = i < n_l ? ukey[o + i] : 0u;
-            ew[i] = (i < n_l && with_tokens) ? untok[o + i] : 0;
+            ew[i] = i < n_l ? untok[o + i] : 0;
         }
         __syncthreads();
     }
@@ -261,7 +260,7 @@ lc_upper_kernel(const LcRetrieveArgs a) {
             for (int n = tid; n < ((n_b + 3) & ~3); n += LC_UP_THREADS) {
                 const bool in = n < n_b && kp[o + upar[ob + n]];
                 ek_next[n] = in ? ukey[ob + n] : 0u;
-                ew_next[n] = (in && with_tokens) ? untok[ob + n] : 0;
+                ew_next[n] = in ? untok[ob + n] : 0;
             }
             __syncthreads();
             uint32_t* tk = ek; ek = ek_next; ek_next = tk;
@@ -1000,7 +999,6 @@ static int launch_beam_g(const LcRetrieveArgs& r, int max_M, int max_nodes, hipS
 // lc_leaf_kernel runs 1024 threads = 64 groups: one chunk per group while scoring; the last workgroup
 // has enough threads to hold a few keys each during the select.
 #define LC_LF_THREADS 1024
-#define LC_LF_THREADS_MAX LC_LF_THREADS
 #define LC_LF_GROUPS (LC_LF_THREADS / 16)
 
 // ---------------------------------------------------------------------------------

@@ -69,7 +69,7 @@ LC_LAYOUT_FN int lc_upper_max_internal_nodes() {
 
 // ---- top-k per level (lc_beam_kernel).  CL = slots of each candidate list, a multiple of 64.
 struct LcBeamLayout {
-    int cid, nxt, key, wgt, flg;           // candidate ids (two lists), keys, weights, a spare byte each
+    int cid, nxt, key, wgt;                // candidate ids (two lists), keys, weights
     int total;
 };
 #define LC_BEAM_LIST_MAX 4096             // longer candidate lists go to the workspace
@@ -80,7 +80,6 @@ LC_LAYOUT_FN LcBeamLayout lc_beam_layout(int CL) {
     y.nxt = o; o += 4 * CL;
     y.key = o; o += 4 * CL;
     y.wgt = o; o += 4 * CL;
-    y.flg = o; o += CL;
     y.total = o;
     return y;
 }

@@ -55,10 +55,10 @@ int main() {
         if (CL % 64 || CL < 64 || CL > LC_BEAM_LIST_MAX) return fail("list slots", n, CL);
         if (n <= LC_BEAM_LIST_MAX && CL < n) return fail("list shorter than the level", n, CL);
         const LcBeamLayout y = lc_beam_layout(CL);
-        const int offs[5] = {y.cid, y.nxt, y.key, y.wgt, y.flg};
-        const int sizes[5] = {4 * CL, 4 * CL, 4 * CL, 4 * CL, CL};
+        const int offs[4] = {y.cid, y.nxt, y.key, y.wgt};
+        const int sizes[4] = {4 * CL, 4 * CL, 4 * CL, 4 * CL};
         int end = 0;
-        for (int i = 0; i < 5; ++i) {
+        for (int i = 0; i < 4; ++i) {
             if (offs[i] < end) return fail("beam arrays overlap", n, i);
             if (i >= 2 && i <= 3 && offs[i] % 16) return fail("beam key/weight arrays misaligned", n, i);
             end = offs[i] + sizes[i];
