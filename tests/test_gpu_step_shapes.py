@@ -1,6 +1,10 @@
-"""The decode step against the two separate calls around the sizes where it changes from one kernel to two."""
+"""The decode step against the two separate calls, and both against the oracle on the stored index, around the sizes where
+the step changes from one kernel to two."""
 import numpy as np
 import pytest
+
+from oracle import lychee_oracle as orc
+from tests import helpers
 
 pytestmark = pytest.mark.gpu
 
@@ -10,6 +14,7 @@ pytestmark = pytest.mark.gpu
 def test_few_chunks(chunks, G, centers):
     import torch
     from paper_2603_08453_amd import binding as lc
+    from tests.gpu_common import attention_errors, levels_to_oracle_index
     H, B = 2, len(chunks)
     r = np.random.default_rng(sum(chunks) + G)
     bounds = [np.concatenate([[0], np.cumsum(r.integers(1, 30, size=m))]).astype(np.int32) for m in chunks]
@@ -38,3 +43,15 @@ def test_few_chunks(chunks, G, centers):
             for h in range(H):
                 assert torch.equal(got[0][b, h, : n[0][b, h]], got[1][b, h, : n[1][b, h]])
         assert torch.allclose(out[0], out[1], rtol=1e-4, atol=2e-5) and torch.allclose(lse[0], lse[1], rtol=1e-5, atol=1e-5)
+        # the oracle on the stored index: selection within the score band, attention over the selected chunks (the
+        # acceptance bars of the other parity tests)
+        seqs = lc.unpack_blob(lc.lc_index_export(idx))["seqs"]
+        for b in range(B):
+            for h in range(H):
+                oi = levels_to_oracle_index(seqs[b]["heads"][h], bounds[b], lens[b], 8, orc.TOKEN_BALL)
+                qh, ids = q[b, h * G:(h + 1) * G].double().cpu().numpy(), got[1][b, h, : n[1][b, h]].cpu().numpy()
+                helpers.accept_ids(ids, orc.node_scores(oi, 0, qh), oi.lens(), budget, pinned=orc.pinned_chunks(oi, sink))
+                ref, ref_lse = orc.sparse_decode(qh, K[b, h].double().cpu().numpy(), V[b, h].double().cpu().numpy(), oi.bounds, oi.T, ids)
+                mx, rel = attention_errors(out[1][b, h * G:(h + 1) * G].cpu().numpy(), ref)
+                assert mx <= 1e-2 and rel <= 2e-3
+                assert np.abs(lse[1][b, h * G:(h + 1) * G].cpu().numpy() - ref_lse).max() <= 1e-3
