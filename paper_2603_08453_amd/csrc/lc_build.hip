@@ -136,11 +136,12 @@ __device__ __forceinline__ void lc_store8(float* p, const float (&v)[8]) {
     *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
     *reinterpret_cast<float4*>(p + 4) = make_float4(v[4], v[5], v[6], v[7]);
 }
-// the same 8 columns rounded to bfloat16 (16 bytes per lane)
+// the same 8 columns of a direction rounded to bfloat16 (16 bytes per lane); its not-a-numbers are the hardware's own
+// (lc_unit_frag), which rounding keeps
 __device__ __forceinline__ void lc_store8_bf16(uint16_t* p, const float (&v)[8]) {
     uint32_t h[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) h[i] = v[i] == v[i] ? lc_f32_to_bf16_bits(v[i]) : 0x7fc0u;      // (rounding may carry a not-a-number into 0 or infinity)
+    for (int i = 0; i < 8; ++i) h[i] = lc_f32_to_bf16_bits(v[i]);
     *reinterpret_cast<uint4*>(p) = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
 }
 __device__ __forceinline__ void lc_load8(const float* p, float (&v)[8]) {
@@ -800,8 +801,14 @@ lc_kmeans_assign_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
                 v = fmaxf(v, lc_dpp<0x141>(v));
                 v = fmaxf(v, lc_dpp<0x140>(v));
                 start[a][r] = 2.0f * LC_AS_EPS - v;
-                if (j == 0 && !(v > LC_NEG_INF)) sh.cand_n[wave][16 * a + 4 * kk + r] = LC_AS_CAND + 1;
+                top[a][r] = v;
             }
+        if (j == 0) {
+#pragma unroll
+            for (int a = 0; a < MA; ++a)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) sh.pair_v[wave][16 * a + 4 * kk + r] = top[a][r];
+        }
         lc_barrier_lds();                                           // the last tile has been used
     } else {
         // similarity to the previous centroid, one 16-lane group per point
@@ -818,15 +825,15 @@ lc_kmeans_assign_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
             for (int t = 0; t < 8; ++t) s = fmaf(x[t], m[t], s);
             s = lc_sum16(s);
             if (j == 0) sh.pair_v[wave][4 * MA * kk + e] = s;
-            if (j == 0 && !(s == s)) sh.cand_n[wave][4 * MA * kk + e] = LC_AS_CAND + 1;
         }
         lc_wave_sync();
 #pragma unroll
         for (int a = 0; a < MA; ++a)
 #pragma unroll
             for (int r = 0; r < 4; ++r) start[a][r] = (LC_AS_EPS + 2e-5f) - sh.pair_v[wave][16 * a + 4 * kk + r];
-        lc_wave_sync();
     }
+    if (lane < WP && !(sh.pair_v[wave][lane] > LC_NEG_INF)) sh.cand_n[wave][lane] = LC_AS_CAND + 1;     // (see above)
+    lc_wave_sync();
     over_tiles([&](const unsigned char* buf, int c0, int n) LC_INLINE {
         sweep(buf, n, [&](int c, const lc_f32x4_b (&d0)[MA], const lc_f32x4_b (&d1)[MA]) LC_INLINE {
             float any = LC_NEG_INF;
