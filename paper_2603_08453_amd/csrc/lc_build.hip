@@ -1631,25 +1631,29 @@ int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const i
                 const long long load = ((maxN + 64 * m - 1) / (64 * m) * BH + 255) / 256 * (m > 2 ? m : 2);
                 if (m == 1 || load <= least) { least = load; ma = m; }
             }
-            // Few centroids: 64 points per workgroup, or 128 where that leaves more workgroups than two per compute unit.
+            // Few centroids: as many blocks as hold them (work for absent centroids costs: 40000 points x 4 heads, us by blocks,
+            // 64 points per workgroup: 2: 20.6, 4: 22.3, 6: 26, 8: 31, 10: 33, 12: 43, 16: 48; 2275 x 8: 8.0, 9.0, 9.6, 9.7, 10.3, 11.1,
+            // 12.6), and 64 points per workgroup.  128 points stage half as many rows, at the price of registers: with more
+            // than two workgroups per compute unit that pays at 12 blocks (33 instead of 43 us; 4200 x 16: 20.9 instead of 24),
+            // hardly at 8 and 10 (29.6 instead of 31.2, 31.3 instead of 33.5; 4200 x 16: 18.4 instead of 17.4) and at no other
+            // number (2, 4, 6, 16: 24.1, 25.9, 27.5, 50 us).
             const bool wide = (maxN + 63) / 64 * BH > 512;
             auto assign = [&](auto kernel, int points, int threads, int it) {
                 hipLaunchKernelGGL(kernel, dim3((maxN + points - 1) / points, H, B), dim3(threads), 0, stream, ix, l,
                                    (const float*)cur.pts, (const uint16_t*)cur.pts16, cur.cap, (const float*)cur.cent,
                                    (const uint16_t*)cur.cent16, cur.cent_cap, it, kflags);
             };
-            auto assign_res = [&](auto kernel4, auto kernel8, int it) {
-                if (wide) assign(kernel8, 128, 512, it);
-                else assign(kernel4, 64, 256, it);
-            };
             for (int it = 0; it < iters; ++it) {
-                if (maxK <= 32) assign_res(&lc_kmeans_assign_res_kernel<2, 4>, &lc_kmeans_assign_res_kernel<2, 8>, it);
-                else if (maxK <= 64) assign_res(&lc_kmeans_assign_res_kernel<4, 4>, &lc_kmeans_assign_res_kernel<4, 8>, it);
-                else if (maxK <= 96) assign_res(&lc_kmeans_assign_res_kernel<6, 4>, &lc_kmeans_assign_res_kernel<6, 8>, it);
-                else if (maxK <= 128) assign_res(&lc_kmeans_assign_res_kernel<8, 4>, &lc_kmeans_assign_res_kernel<8, 8>, it);
-                else if (maxK <= 160) assign_res(&lc_kmeans_assign_res_kernel<10, 4>, &lc_kmeans_assign_res_kernel<10, 8>, it);
-                else if (maxK <= 192) assign_res(&lc_kmeans_assign_res_kernel<12, 4>, &lc_kmeans_assign_res_kernel<12, 8>, it);
-                else if (maxK <= LC_AS_RES) assign_res(&lc_kmeans_assign_res_kernel<16, 4>, &lc_kmeans_assign_res_kernel<16, 8>, it);
+                if (maxK <= 32) assign(&lc_kmeans_assign_res_kernel<2, 4>, 64, 256, it);
+                else if (maxK <= 64) assign(&lc_kmeans_assign_res_kernel<4, 4>, 64, 256, it);
+                else if (maxK <= 96) assign(&lc_kmeans_assign_res_kernel<6, 4>, 64, 256, it);
+                else if (maxK <= 128 && wide) assign(&lc_kmeans_assign_res_kernel<8, 8>, 128, 512, it);
+                else if (maxK <= 128) assign(&lc_kmeans_assign_res_kernel<8, 4>, 64, 256, it);
+                else if (maxK <= 160 && wide) assign(&lc_kmeans_assign_res_kernel<10, 8>, 128, 512, it);
+                else if (maxK <= 160) assign(&lc_kmeans_assign_res_kernel<10, 4>, 64, 256, it);
+                else if (maxK <= 192 && wide) assign(&lc_kmeans_assign_res_kernel<12, 8>, 128, 512, it);
+                else if (maxK <= 192) assign(&lc_kmeans_assign_res_kernel<12, 4>, 64, 256, it);
+                else if (maxK <= LC_AS_RES) assign(&lc_kmeans_assign_res_kernel<16, 4>, 64, 256, it);
                 else if (ma == 4) assign(&lc_kmeans_assign_kernel<4>, 256, LC_BT, it);
                 else if (ma == 3) assign(&lc_kmeans_assign_kernel<3>, 192, LC_BT, it);
                 else if (ma == 2) assign(&lc_kmeans_assign_kernel<2>, 128, LC_BT, it);
