@@ -124,7 +124,11 @@ size_t lc_index_bytes(const lc_config* cfg /* host */, int B, int H_kv, int d);
 
 /* Bytes of workspace sufficient for lc_build_index, lc_retrieve,
  * lc_sparse_decode and lc_append on such an index (pure host function; 0 on
- * invalid arguments).  The workspace holds no state between calls. */
+ * invalid arguments).  The workspace holds no state between calls.  Most of it is
+ * scratch of the index build (unit directions of the points of two levels and the
+ * centroids of two levels, each in float32 and bfloat16): per chunk and head about
+ * 768 bytes and 2.3 KB / fan-out of level 1, i.e. 0.9 KB at fan-out 16 and 1.9 KB at
+ * fan-out 2.  Every call that takes a workspace asks for this size (lc_index_drift: see there). */
 size_t lc_workspace_bytes(const lc_config* cfg /* host */, int B, int H_q, int H_kv, int d);
 
 /*
@@ -182,8 +186,9 @@ int lc_recluster(lc_index* idx, void* ws, size_t ws_bytes, void* stream);
  * start: the Eq. 2 bounds of that level have then loosened by a quarter on average).
  *   level   1 <= level < cfg.levels
  *   drift   host float[B * H_kv * 4]
- *   ws      device workspace of at least B * H_kv * 16 bytes (any lc_workspace_bytes() buffer does)
- * Synchronises the stream (the result is copied to the host).
+ *   ws      device workspace of at least B * H_kv * 16 bytes (any lc_workspace_bytes() buffer does); checked as in
+ *           the other calls, not used: the kernel writes its figures to pinned host memory
+ * Synchronises the stream (the result is returned to the host).
  */
 int lc_index_drift(const lc_index* idx, int level, float* drift /* host */, void* ws, size_t ws_bytes, void* stream);
 
@@ -239,6 +244,8 @@ int lc_sparse_decode(const lc_index* idx, const void* q, const void* K, const vo
  * from the scoring kernel to the attention kernel through the workspace; every
  * workgroup of the attention kernel repeats the selection of its (sequence,
  * head) from them, so no chunk list travels through memory on the critical path.
+ * With up to 64 chunks per sequence (128 unless a large group meets many workgroups)
+ * there is no scoring kernel: every workgroup scores all chunks itself.
  * When a sequence has more than 4096 chunks, the chunks no longer fit the registers of
  * the selecting workgroups and the call runs the kernels of the two separate entry
  * points instead (through a chunk list in the workspace); so it does under the BEAM
@@ -322,9 +329,9 @@ int lc_index_info(const lc_index* idx, int b, int32_t* T, int32_t* M, int32_t* n
  *                      int32 parent[N_l], int32 ntok[N_l], int32 nchunk[N_l]
  * Centers are float32 in the blob whatever center_dtype says (bfloat16 values widened); import
  * requires the blob's L, fan-outs, geometry and center_dtype to equal the configuration's.
- * lc_index_export and lc_index_import synchronise the stream (import copies with blocking
- * copies; it is a test and checkpoint path, not a hot one).  With blob == NULL export only
- * stores the required size in *bytes.
+ * lc_index_export and lc_index_import synchronise the stream: one kernel per MiB of blob moves it
+ * between the index and pinned host windows (4 MiB per device, kept for the life of the process
+ * and used by one call at a time).  With blob == NULL export only stores the required size in *bytes.
  */
 int lc_index_export(const lc_index* idx, void* blob /* host */, size_t* bytes /* host, in/out */, void* stream);
 int lc_index_import(lc_index** out, const lc_config* cfg, const void* blob /* host */, size_t blob_bytes,
@@ -349,6 +356,7 @@ void lc_index_destroy(lc_index* idx);
  *   4  ends in a blank or tab
  *
  *   text     host: the tokens' UTF-8 bytes, concatenated
+ *   max_len  a value beyond n is no limit
  *   offsets  host int64[n+1]: token i is text[offsets[i] .. offsets[i+1])
  *   n        number of tokens (0 allowed)
  *   bounds   host int32[capacity] out: b_0 = 0 < ... < b_M = n

@@ -1,4 +1,5 @@
-"""ctypes binding of liblychee.so: same names as the C ABI, argument marshalling only.
+"""Binding of liblychee.so: same names as the C ABI, argument marshalling only (ctypes; the per-token calls on torch
+tensors and the token chunker through two small CPython modules, _lychee_torch and _lychee_host).
 
 PyTorch provides device memory and streams; every step of the path runs inside
 the library's HIP kernels.  There is no CPU fallback: if the shared library has
@@ -159,7 +160,8 @@ _fast_mod = None
 
 
 class _Unmarshalled:
-    """Stands in for _lychee_torch where it has not been built: ctypes marshals every call (12.9 instead of 7.7 us of host time per decode step)."""
+    """Stands in for _lychee_torch where it has not been built: ctypes marshals every call (12.9 instead of 7.7 us
+    of host time per decode step)."""
 
     @staticmethod
     def _pass(*_args):
@@ -443,7 +445,8 @@ def lc_index_import(cfg: LcConfig, blob: bytes, index_buf, stream=None) -> Index
 
 
 def lc_chunk_tokens(tokens: Sequence[str], min_len: int, max_len: int) -> List[int]:
-    """Chunk boundaries of a token stream given as the tokens' texts (host routine)."""
+    """Chunk boundaries of a token stream given as the tokens' texts (host routine).  A max_len beyond the number of
+    tokens is no limit."""
     got = _host().chunk_tokens(tokens, int(min_len), int(max_len))
     if not isinstance(got, list):
         raise LycheeError(got, "lc_chunk_tokens")

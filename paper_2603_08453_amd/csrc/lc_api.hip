@@ -1021,7 +1021,6 @@ int lc_index_import(lc_index** out, const lc_config* cfg, const void* blob, size
                 }
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // staged through the chunk centers' memory, which the kernels below overwrite in stream order
     if (rc == LC_OK) rc = upload_state(h, bounds_concat.data(), s);
     if (rc == LC_OK) rc = import_nodes(h, blob, s);
     if (rc != LC_OK) {

@@ -18,9 +18,11 @@ inline bool str_text(PyObject* t, LcTokenText* out) {
     return p != nullptr;
 }
 
-// Levels of the tokens of one call, by object: a tokenizer hands out the same str object for a
-// vocabulary entry again and again, and a separator test costs a few mispredicted branches (26 ns
-// against 3 ns for the look-up).  Direct-mapped; a miss computes the level.
+// Levels of the tokens of one call, by object: where the tokens are looked up in a vocabulary the same str object comes
+// again and again, and a separator test costs a few mispredicted branches (26 ns against 3 ns for the look-up).
+// Direct-mapped; a miss computes the level, and a tokenizer that makes a str per token misses nearly always.
+// 32768 tokens: 53 us as 37 objects, 109 us as 32768 objects of the same texts, 249 us from a vocabulary of 50000
+// (its texts are not in the processor's caches either); 2.95 ms with an encode() and an offset per token in Python.
 class LevelMemo {
   public:
     LevelMemo() : slot_() {}
@@ -42,7 +44,6 @@ class LevelMemo {
 // The tokens' bytes are read where the objects hold them: no concatenated copy, no offset array, and
 // apart from a check of every object only the tokens inside the search windows are looked at.  The interpreter stays
 // locked throughout (the bytes belong to the caller's objects).
-// 32K tokens: 2.95 ms with an encode() and an offset per token in Python.
 PyObject* chunk_tokens(PyObject*, PyObject* const* args, Py_ssize_t n_args) {
     if (n_args != 3) {
         PyErr_SetString(PyExc_TypeError, "chunk_tokens(tokens, min_len, max_len)");
