@@ -1793,6 +1793,12 @@ lc_append_kernel(LcDev ix, uint16_t* K, uint16_t* V, long long ks_seq, long long
     const int h = blockIdx.x, b = blockIdx.y;
     const int bh = b * ix.H + h;
     const int tid = threadIdx.x, sub = tid & 15, grp = tid >> 4;
+    // The new rows do not depend on the counts: they are on their way before the counts arrive.  (What bounds a token
+    // that closes no chunk is two round trips to memory, these loads and the stores; with the loads behind the
+    // counts it was three.)
+    uint4 row = make_uint4(0u, 0u, 0u, 0u);
+    if (tid < 32)
+        row = *reinterpret_cast<const uint4*>((tid < 16 ? k_new : v_new) + (size_t)bh * LC_D + 8 * sub);
     const int T = ix.state[bh * 4 + 0];
     const int M = ix.state[bh * 4 + 1];
     // The host checks the capacities against its own counts before it launches; these guards are for
@@ -1800,13 +1806,8 @@ lc_append_kernel(LcDev ix, uint16_t* K, uint16_t* V, long long ks_seq, long long
     if (T >= max_tokens) return;
     uint16_t* Kbh = K + b * ks_seq + h * ks_head;
     uint16_t* Vbh = V + b * ks_seq + h * ks_head;
-    if (tid < 16) {
-        *reinterpret_cast<uint4*>(Kbh + (long long)T * ks_tok + 8 * sub) =
-            *reinterpret_cast<const uint4*>(k_new + (size_t)bh * LC_D + 8 * sub);
-    } else if (tid < 32) {
-        *reinterpret_cast<uint4*>(Vbh + (long long)T * ks_tok + 8 * sub) =
-            *reinterpret_cast<const uint4*>(v_new + (size_t)bh * LC_D + 8 * sub);
-    }
+    if (tid < 32)
+        *reinterpret_cast<uint4*>((tid < 16 ? Kbh : Vbh) + (long long)T * ks_tok + 8 * sub) = row;
     const bool do_close = ((close.w[b >> 5] >> (b & 31)) & 1u) && M < ix.cap[0];
     if (!do_close) {
         if (tid == 0) ix.state[bh * 4 + 0] = T + 1;
