@@ -231,6 +231,7 @@ __device__ __forceinline__ float lc_sum_groups4(float v) { v += __shfl_xor(v, 16
 __global__ void __launch_bounds__(64)
 lc_pool_kernel(LcDev ix, const uint16_t* K, long long ks_seq, long long ks_head, long long ks_tok,
                int geometry, LcPointRows out, int* flags) {
+    lc_fetch_args<sizeof(LcDev) + 40 + sizeof(LcPointRows)>();
     const int h = blockIdx.y, b = blockIdx.z;
     const int bh = b * ix.H + h;
     lc_clear_flags(ix, bh, flags);
@@ -346,6 +347,7 @@ lc_pool_kernel(LcDev ix, const uint16_t* K, long long ks_seq, long long ks_head,
 // Re-clustering starts from the chunk nodes already in the index: unit directions of their centers.
 __global__ void __launch_bounds__(LC_BT)
 lc_dirs_kernel(LcDev ix, LcPointRows out, int* flags) {
+    lc_fetch_args<sizeof(LcDev) + sizeof(LcPointRows)>();
     const int h = blockIdx.y, b = blockIdx.z;
     const int bh = b * ix.H + h;
     lc_clear_flags(ix, bh, flags);
@@ -599,6 +601,7 @@ template <int NBLK, int NW>
 __global__ void __launch_bounds__(64 * NW, NBLK == 16 ? 2 : NW / 2)
 lc_kmeans_assign_res_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16, int pts_cap, const float* cent,
                             const uint16_t* cent16, int cent_cap, int it, int* flags_all) {
+    lc_fetch_args<sizeof(LcDev) + 40>();
     constexpr int PIECES = NBLK * 256 / (64 * NW);                  // 16-byte pieces of the rows per thread
     __shared__ __attribute__((aligned(16))) unsigned char rows[16 * NBLK * LC_AS_PITCH];
     __shared__ LcAssignSh<16, NW> sh;
@@ -693,6 +696,7 @@ template <int MA>
 __global__ void __launch_bounds__(LC_BT)
 lc_kmeans_assign_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16, int pts_cap, const float* cent,
                         const uint16_t* cent16, int cent_cap, int it, int* flags_all) {
+    lc_fetch_args<sizeof(LcDev) + 40>();
     constexpr int WP = 16 * MA;                                     // points per wavefront
     __shared__ __attribute__((aligned(16))) unsigned char tiles[2][LC_AS_TILE * LC_AS_PITCH];
     __shared__ LcAssignSh<WP, 4> sh;
@@ -1211,6 +1215,7 @@ __device__ __forceinline__ void lc_write_centroid(float* cent, uint16_t* cent16,
 __global__ void __launch_bounds__(LC_BT)
 lc_kmeans_update_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* cent, uint16_t* cent16, int cent_cap, int it,
                         int* flags_all) {
+    lc_fetch_args<sizeof(LcDev) + 40>();
     __shared__ __attribute__((aligned(16))) LcSumSh<LC_BT> sh;
     const int c = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     const int bh = b * ix.H + h;
@@ -1232,6 +1237,7 @@ lc_kmeans_update_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* c
 __global__ void __launch_bounds__(LC_BT)
 lc_kmeans_update_few_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* cent, uint16_t* cent16, int cent_cap,
                             int it, int per, int* flags_all) {
+    lc_fetch_args<sizeof(LcDev) + 40>();
     __shared__ LcBuckets bk;
     __shared__ __attribute__((aligned(16))) float sh[LC_BG * LC_D];
     const int h = blockIdx.y, b = blockIdx.z;
@@ -1265,6 +1271,7 @@ static inline size_t lc_kmeans_small_lds(int N, int k) {
 __global__ void __launch_bounds__(LC_KS_THREADS)
 lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* cent, int cent_cap, int iters,
                        int x_rows) {
+    lc_fetch_args<sizeof(LcDev) + 40>();
     extern __shared__ __attribute__((aligned(16))) float ks_dyn[];   // x_rows point rows, then the centroid rows
     __shared__ int lab[LC_KS_MAX_N];
     __shared__ int moff[LC_KS_MAX_K + 1];
@@ -1433,6 +1440,7 @@ __device__ __forceinline__ void lc_write_node(const LcDev& ix, int b, int bh, in
 // chunks of `per` nodes and gives each node to a 16-lane group.
 __global__ void __launch_bounds__(LC_BT)
 lc_center_few_kernel(LcDev ix, int l, LcNodeArgs w, int per) {
+    lc_fetch_args<sizeof(LcDev) + sizeof(LcNodeArgs)>();
     __shared__ LcBuckets bk;
     __shared__ __attribute__((aligned(16))) float sh[LC_BG * LC_D];
     const int h = blockIdx.y, b = blockIdx.z;
@@ -1463,6 +1471,7 @@ lc_center_few_kernel(LcDev ix, int l, LcNodeArgs w, int per) {
 template <int NT>
 __global__ void __launch_bounds__(NT)
 lc_center_kernel(LcDev ix, int l, LcNodeArgs w) {
+    lc_fetch_args<sizeof(LcDev) + sizeof(LcNodeArgs)>();
     __shared__ __attribute__((aligned(16))) LcSumSh<NT> sh;
     __shared__ int tok_sh[NT / 64];
     const int u = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
@@ -1513,6 +1522,7 @@ lc_center_kernel(LcDev ix, int l, LcNodeArgs w) {
 #define LC_RD_LDS 512             // nodes (levels >= 2 together) whose maxima are collected in LDS
 __global__ void __launch_bounds__(LC_BT)
 lc_radius_kernel(LcDev ix) {
+    lc_fetch_args<sizeof(LcDev)>();
     __shared__ int best[LC_RD_LDS];
     const int h = blockIdx.y, b = blockIdx.z;
     const int bh = b * ix.H + h;
@@ -1787,6 +1797,7 @@ struct LcCloseBits { uint32_t w[32]; };       // one bit per sequence (B <= 1024
 __global__ void __launch_bounds__(LC_BT)
 lc_append_kernel(LcDev ix, uint16_t* K, uint16_t* V, long long ks_seq, long long ks_head, long long ks_tok,
                  const uint16_t* k_new, const uint16_t* v_new, LcCloseBits close, int geometry, int max_tokens) {
+    lc_fetch_args<sizeof(LcDev) + 64 + sizeof(LcCloseBits)>();
     __shared__ float sh[LC_BG * LC_D + LC_BG];
     __shared__ float best_sim[LC_BG];
     __shared__ int best_arg[LC_BG];

@@ -103,6 +103,7 @@ __device__ __forceinline__ float lc_exp2_rel(float x, float ref) { return exp2f(
 template <int G, bool FUSED, int EC, bool SCORE>
 __global__ void __launch_bounds__(LC_DEC_THREADS)
 lc_decode_kernel(const LcDecodeArgs a) {
+    lc_fetch_args<sizeof(LcDecodeArgs)>();
     extern __shared__ int lds_dyn[];             // FUSED: the selection's chunk lists
     using SelStore = typename std::conditional<FUSED, LcLeafSelSh, int>::type;
     using FusedStore = typename std::conditional<FUSED, LcFusedSh<LC_DEC_THREADS>, int>::type;

@@ -645,6 +645,7 @@ __device__ __forceinline__ uint32_t lc_block_cut(int n, uint32_t* key, const int
 template <int G>
 __global__ void __launch_bounds__(LC_BM_THREADS)
 lc_beam_kernel(const LcBeamArgs a) {
+    lc_fetch_args<sizeof(LcBeamArgs)>();
     extern __shared__ int lds_dyn[];
     __shared__ int cnt_sh[LC_BM_SPAN * LC_BM_WAVES];
     __shared__ int hist_sh[256 + 6 * LC_BM_WAVES];       // (of either cut)
@@ -1008,6 +1009,7 @@ static int launch_beam_g(const LcRetrieveArgs& r, int max_M, int max_nodes, hipS
 template <int G, int R, bool BF16>
 __global__ void __launch_bounds__(LC_LF_THREADS)
 lc_leaf_kernel(const LcRetrieveArgs a) {
+    lc_fetch_args<sizeof(LcRetrieveArgs)>();
     extern __shared__ int lds_dyn[];
     __shared__ LcLeafSelSh sel_sh;
     __shared__ int last_sh;
@@ -1188,6 +1190,7 @@ lc_leaf_kernel(const LcRetrieveArgs a) {
 template <int G, int R, bool BF16>
 __global__ void __launch_bounds__(LC_SC_THREADS)
 lc_score_kernel(const LcRetrieveArgs a) {
+    lc_fetch_args<sizeof(LcRetrieveArgs)>();
     constexpr int GROUPS = LC_SC_THREADS / 16;
     const LcDev& ix = a.ix;
     const int h = blockIdx.y, b = blockIdx.z;
