@@ -623,7 +623,7 @@ bool lc_decode_fused_fits(int G, int max_M) {
 
 template <int G, int EC, bool SCORE>
 static int launch_fused_ge(const LcDecodeArgs& a, int splits, hipStream_t stream) {
-    const size_t lds = (size_t)EC * LC_DEC_THREADS * 12;      // the selection's chunk lists
+    const size_t lds = lc_select_lds<LC_DEC_THREADS, EC>();   // the selection's chunk lists
     if (lds > 16 * 1024) {      // static + dynamic may pass the default per-workgroup allowance: raised once per device
         static LcOnce raised;
         LC_HIP_CHECK(raised.run([&] {

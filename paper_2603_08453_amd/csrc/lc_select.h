@@ -65,9 +65,8 @@ __device__ __forceinline__ int lc_mbcnt(unsigned long long mask) {
 // [w * 64 EC, w * 64 EC + n_list), 64 of them per round; the first round stays in registers.
 template <int EC>
 struct LcChunkSel {
-    int* l_st;           // LDS: first row; length, or -1 - c for chunk c of the cutoff bin; id
-    int* l_ln;
-    int* l_id;
+    int2* l_row;         // LDS: first row; length, or -1 - c for chunk c of the cutoff bin
+    int* l_id;           // LDS: id (where the ids are wanted)
     int seg, n_list;     // this wavefront's entries (those of the cutoff bin among them, selected or not)
     unsigned long long in_cut;     // chunks of the cutoff bin that are selected, by list position
     int st0, ln0, off0;  // this lane's entry of the first round: row, length (0 = not selected), offset among the wavefront's tokens
@@ -81,8 +80,9 @@ struct LcChunkSel {
 template <int NT, int EC>
 __device__ __forceinline__ void lc_sel_entry(const LcChunkSel<EC>& o, const LcFusedSh<NT>& fs, int r, int* st, int* ln) {
     const int p = o.seg + min(r, max(o.n_list - 1, 0));
-    int l = r < o.n_list ? o.l_ln[p] : 0;
-    *st = o.l_st[p];
+    const int2 x = o.l_row[p];
+    int l = r < o.n_list ? x.y : 0;
+    *st = x.x;
     if (l < 0) {                                                    // (rare: one or two chunks of a wavefront)
         const int c = -1 - l;
         l = ((o.in_cut >> c) & 1ull) ? fs.cand[c / LC_SEL_CAND][c % LC_SEL_CAND].y : 0;
@@ -102,11 +102,14 @@ __device__ __forceinline__ void lc_sel_entry(const LcChunkSel<EC>& o, const LcFu
 //      every wavefront ranks (key descending, id ascending) -- or, if it overflows (a crowded or tied
 //      bin), the general select routine runs on them;
 //   3. token offsets by a wavefront scan of the list, one exchange of the wavefronts' totals.
-// (2275 chunks: 3.3 us from the loads to here with all of it in registers over every chunk, now.)
+// (The compaction is six vector instructions per chunk and lane, without a branch; with branches around its writes
+// and the short list's in the same loop it was fifty, and a step at 2275 chunks per head took 21.5 us instead of 20.2.)
 // `entry(e)`: entry e of this lane (LcChunkEntry; past the array's end anything); chunks whose first token lies below `sink` are pinned: always selected, not
 // charged to the budget.  With `ids_out` (per (sequence, head) `cap` entries) the selected ids are also
-// written in ascending order and their number to counts_out[bh].  `lds_dyn`: 12 * EC * NT bytes.
+// written in ascending order and their number to counts_out[bh].  `lds_dyn`: lc_select_lds<NT, EC>() bytes.
 // All NT threads must call; NT / 64 wavefronts; holds up to EC * NT chunks.
+template <int NT, int EC>
+constexpr size_t lc_select_lds() { return (size_t)(EC * NT) * 12 + 64 * 8; }
 template <int NT, int EC, typename Entry>
 __device__ __forceinline__ void lc_select_chunks(const LcDev& ix, int b, int bh, Entry entry, int budget,
                                                  int sink, int32_t* ids_out, int32_t* counts_out, int cap,
@@ -126,9 +129,8 @@ __device__ __forceinline__ void lc_select_chunks(const LcDev& ix, int b, int bh,
     for (int e = 0; e < EC; ++e) ent[e] = entry(e);
     o.T = ix.state[bh * 4 + 0];
     const int M_all = ix.state[bh * 4 + 1];
-    o.l_st = lds_dyn;
-    o.l_ln = lds_dyn + EC * NT;
-    o.l_id = lds_dyn + 2 * EC * NT;
+    o.l_row = reinterpret_cast<int2*>(lds_dyn);
+    o.l_id = lds_dyn + 2 * (EC * NT + 64);
     o.seg = wave * (EC * 64);
     // meanwhile: empty histogram and list (their first use is behind the barrier of the key range)
     for (int i = tid; i < BINS + 4; i += NT) fs.hw[i] = 0;
@@ -198,23 +200,41 @@ __device__ __forceinline__ void lc_select_chunks(const LcDev& ix, int b, int bh,
         }
     }
     // ---- chunks of that bin and above, and the pinned ones, to this wavefront's list; those in it to the short list
+    if (sink > 0) {                                             // (pinned chunks: as if in a bin above all)
+#pragma unroll
+        for (int e = 0; e < EC; ++e) cbin[e] = j0 + 64 * e < o.M && ent[e].y < sink ? BINS : cbin[e];
+    }
+    const bool want_ids = ids_out != nullptr;                   // (uniform)
+    const int lowest = max(fb, 0), cutoff = fb >= 0 ? fb : -2;
     int n_cut = 0;
     o.n_list = 0;
+    unsigned long long mi[EC], mc[EC];
+    int first[EC];
+    // (no branch: a lane without a chunk for the list writes to a slot of its own behind it)
 #pragma unroll
     for (int e = 0; e < EC; ++e) {
-        const int j = j0 + 64 * e;
-        const bool cut = fb >= 0 && cbin[e] == fb;
-        const bool in = cut || cbin[e] > fb || (j < o.M && ent[e].y < sink);
-        const unsigned long long mi = __ballot(in), mc = __ballot(cut);
-        const int p = o.seg + o.n_list + lc_mbcnt(mi), c = n_cut + lc_mbcnt(mc);
-        if (in) {
-            o.l_st[p] = ent[e].y;
-            o.l_ln[p] = cut ? -1 - (wave * LC_SEL_CAND + c) : ent[e].z;
-            o.l_id[p] = j;
+        mi[e] = __ballot(cbin[e] >= lowest);
+        mc[e] = __ballot(cbin[e] == cutoff);
+        first[e] = o.seg + o.n_list;
+        const int at = first[e] + lc_mbcnt(mi[e]);
+        o.l_row[cbin[e] >= lowest ? at : EC * NT + lane] = make_int2(ent[e].y, ent[e].z);
+        o.n_list += __popcll(mi[e]);
+    }
+    if (want_ids) {
+#pragma unroll
+        for (int e = 0; e < EC; ++e)
+            if (cbin[e] >= lowest) o.l_id[first[e] + lc_mbcnt(mi[e])] = j0 + 64 * e;
+    }
+#pragma unroll
+    for (int e = 0; e < EC; ++e) {
+        if (mc[e] != 0ull) {                                    // (uniform; few of the rows)
+            const int c = n_cut + lc_mbcnt(mc[e]);
+            if (cbin[e] == cutoff) {
+                o.l_row[first[e] + lc_mbcnt(mi[e])].y = -1 - (wave * LC_SEL_CAND + c);
+                if (c < LC_SEL_CAND) fs.cand[wave][c] = make_int4((int)ck[e], ent[e].z, j0 + 64 * e, 0);
+            }
+            n_cut += __popcll(mc[e]);
         }
-        if (cut && c < LC_SEL_CAND) fs.cand[wave][c] = make_int4((int)ck[e], ent[e].z, j, 0);
-        o.n_list += __popcll(mi);
-        n_cut += __popcll(mc);
     }
     if (lane == 0) fs.n_cand[wave] = n_cut;
     lc_barrier_lds();
@@ -229,13 +249,12 @@ __device__ __forceinline__ void lc_select_chunks(const LcDev& ix, int b, int bh,
         const int4 me = fs.cand[cw][ci];
         const bool valid = ci < fs.n_cand[cw];
         int wb = 0;
-#pragma unroll
-        for (int w = 0; w < NW; ++w)
-            for (int t = 0; t < fs.n_cand[w]; ++t) {            // (uniform)
-                const int4 x = fs.cand[w][t];
-                const bool before = (uint32_t)x.x > (uint32_t)me.x || (x.x == me.x && x.z < me.z);
-                wb += before ? x.y : 0;
-            }
+        for (unsigned long long left = __ballot(valid); left != 0ull; left &= left - 1ull) {      // (uniform)
+            const int l = __ffsll((long long)left) - 1;
+            const uint32_t k = (uint32_t)lc_readlane(me.x, l);
+            const bool before = k > (uint32_t)me.x || (k == (uint32_t)me.x && lc_readlane(me.z, l) < me.z);
+            wb += before ? lc_readlane(me.y, l) : 0;
+        }
         o.in_cut = __ballot(valid && wb + me.y <= remW);
     } else {
         // ---- a crowded or tied cutoff bin: the general select routine on its chunks alone, then the lists anew
@@ -265,11 +284,11 @@ __device__ __forceinline__ void lc_select_chunks(const LcDev& ix, int b, int bh,
 #pragma unroll
         for (int e = 0; e < EC; ++e) {
             const int j = j0 + 64 * e;
-            const bool in = keep[e] || cbin[e] > fb || (j < o.M && ent[e].y < sink);
-            const unsigned long long mi = __ballot(in);
-            const int p = o.seg + o.n_list + lc_mbcnt(mi);
-            if (in) { o.l_st[p] = ent[e].y; o.l_ln[p] = ent[e].z; o.l_id[p] = j; }
-            o.n_list += __popcll(mi);
+            const bool in = keep[e] || cbin[e] > fb;
+            const unsigned long long m = __ballot(in);
+            const int p = o.seg + o.n_list + lc_mbcnt(m);
+            if (in) { o.l_row[p] = make_int2(ent[e].y, ent[e].z); if (want_ids) o.l_id[p] = j; }
+            o.n_list += __popcll(m);
         }
         lc_barrier_lds();
     }
