@@ -491,6 +491,15 @@ static int common_decode_checks(const lc_index* idx, const void* q, int H_q, int
 #define LC_STEP_FUSED_MAX_CHUNKS 4096
 
 namespace {
+// Of the splits that the workspace is laid out for (lc_auto_splits, or the caller's number, which stands), those that
+// run at the same time: the attention kernel's registers allow two workgroups per compute unit, and one more of them
+// would be served after all others (48 pairs: 11 splits 40.0 us a step, 10 splits 29.1; 72 pairs: 8 splits 47.1, 7 splits 38.8).
+int resident_splits(const lc_index* idx, int splits) {
+    if (idx->cfg.decode_splits > 0) return splits;
+    const int fit = 2 * LC_COMPUTE_UNITS / (idx->B * idx->H_kv);
+    return fit < 1 ? 1 : (fit < splits ? fit : splits);
+}
+
 // What a retrieval over the current index needs: sizes, the capacity check, walk or flat scan.
 struct RetrievePlan {
     int max_M = 0;
@@ -582,6 +591,7 @@ int useful_splits(const lc_index* idx, int budget, int splits) {
         if (n > most) most = n;
     }
     const long long need = (most + LC_DEC_MIN_TOKENS_PER_SPLIT - 1) / LC_DEC_MIN_TOKENS_PER_SPLIT;
+    splits = resident_splits(idx, splits);
     return need < splits ? (int)need : splits;
 }
 
@@ -734,8 +744,8 @@ int lc_sparse_decode(const lc_index* idx, const void* q, const void* K, const vo
     if ((long long)idx->cfg.max_tokens * kv_strides[2] * 2 >= (1LL << 31)) return LC_ERR_BAD_SHAPE;
     LcWs w;
     lc_layout_ws(&idx->cfg, idx->B, H_q, idx->H_kv, idx->d, splits, ws, &w);
-    return lc_launch_decode(idx, w, q, K, V, kv_strides, chunk_ids, counts, cap, H_q / idx->H_kv, splits, out, lse,
-                            static_cast<hipStream_t>(stream));
+    return lc_launch_decode(idx, w, q, K, V, kv_strides, chunk_ids, counts, cap, H_q / idx->H_kv, resident_splits(idx, splits),
+                            out, lse, static_cast<hipStream_t>(stream));
 }
 
 int lc_append(lc_index* idx, void* K, void* V, const int64_t kv_strides[3], const void* k_new, const void* v_new,

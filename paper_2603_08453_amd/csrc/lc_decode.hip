@@ -7,10 +7,19 @@
 //   tokens, whose K rows form the 16 x 128 A operand of four 16x16x32 bf16 MFMAs;
 //   the B operand is the query block (head n in column n).  The result leaves lane
 //   (group, n) with the logits of the group's own tokens for head n, so each lane
-//   keeps the online softmax (base 2) of one head and the probabilities reach the
-//   other 15 lanes of the group by DPP row broadcasts.
-//   P.V stays on the vector ALU: lane n of a group holds columns [8n, 8n + 8) of a
-//   V row (one 16-byte load), four rows make a full 1 KiB wavefront load.
+//   keeps the online softmax (base 2) of one head.
+//   P.V runs there too, without a value crossing lanes: a lane's four probabilities are
+//   its share of the A operand (row n: head n), and the eight columns [8n, 8n + 8) it
+//   loaded of its group's four V rows are, column by column, its share of eight B operands
+//   (operand c: columns c, c + 8, ...).  V is bfloat16 as stored; a probability goes in
+//   as three bfloat16 terms that add up to its float32 value (lc_split3), so that
+//   products and sums are those of float32.
+//   With P.V on the vector ALU a batch of 16 tokens took a wavefront 150 instructions at
+//   group size 4 and 250 at 7 (with half the lanes' K loads empty there, for want of
+//   registers), now about 100 and 64 cycles of the matrix pipe, and the groups' sums need
+//   no combining.  A step: 18.1 -> 16.9 us (4 x 32K tokens), 20.2 -> 19.2 (128K), 29.9 ->
+//   27.6 (16 ragged sequences, group size 7).  Relative error against float64 over steps
+//   of the sizes in use: 3.88e-7, on the vector ALU 3.91e-7.
 #include <type_traits>
 
 #include "lc_device.h"
@@ -20,6 +29,7 @@
 #ifndef LC_DEC_THREADS
 #define LC_DEC_THREADS 256
 #endif
+#define LC_INLINE __attribute__((always_inline))       // (lambdas that hold registers by reference)
 #define LC_DEC_GROUPS (LC_DEC_THREADS / 16)
 #define LC_DEC_MAX_SPLITS 256
 #define LC_DEC_TILE 1024          // tokens of a split whose cache rows are resolved into LDS at a time
@@ -53,21 +63,27 @@ struct LcDecodeArgs {
     int max_tokens;       // rows of one (sequence, head) slab of K and V
 };
 
-// Value of lane `src` (0..15) of the caller's 16-lane row, in every lane of the row.
-template <int SRC>
-__device__ __forceinline__ float lc_row_bcast(float v) {
-    return lc_dpp<0x150 + SRC>(v);
-}
-__device__ __forceinline__ float lc_row_bcast_n(float v, int src) {      // src folds to a constant once unrolled
-    switch (src) {
-        case 0: return lc_row_bcast<0>(v);
-        case 1: return lc_row_bcast<1>(v);
-        case 2: return lc_row_bcast<2>(v);
-        case 3: return lc_row_bcast<3>(v);
-        case 4: return lc_row_bcast<4>(v);
-        case 5: return lc_row_bcast<5>(v);
-        case 6: return lc_row_bcast<6>(v);
-        default: return lc_row_bcast<7>(v);
+// N probabilities as three bfloat16 terms each, packed in pairs: t[s] holds the terms number s.  The three add up to
+// the float32 value exactly: each takes the upper eight of the bits that are left, and where those are all of them, one unit less, so
+// that something is left (a term of zero would turn an infinite V into a not-a-number).
+template <int N>
+__device__ __forceinline__ void lc_split3(const float (&p)[N], int (&t)[3][N / 2]) {
+    float r[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) r[u] = p[u];
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+        uint32_t w[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            w[u] = __float_as_uint(r[u]);
+            if (s < 2) {
+                w[u] = __builtin_elementwise_sub_sat(w[u], 1u);     // (0 stays 0)
+                r[u] -= __uint_as_float(w[u] & 0xffff0000u);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < N / 2; ++k) t[s][k] = (int)__builtin_amdgcn_perm(w[2 * k + 1], w[2 * k], 0x07060302u);   // the upper halves
     }
 }
 // a in the lower half of the wavefront and b in the upper half, each summed over the two halves
@@ -101,26 +117,37 @@ __device__ __forceinline__ float lc_exp2_rel(float x, float ref) { return exp2f(
 // Either way the selected chunks sit in a list, in id order; the wavefronts write the cache row of
 // every token of the split's tile into LDS, 64 lanes per overlapping chunk.
 template <int G, bool FUSED, int EC, bool SCORE>
-__global__ void __launch_bounds__(LC_DEC_THREADS)
+// (two wavefronts per SIMD asked for: without that the compiler puts the accumulators into the other half of the register
+// file and copies them back and forth)
+__global__ void __launch_bounds__(LC_DEC_THREADS, 2)
 lc_decode_kernel(const LcDecodeArgs a) {
     lc_fetch_args<sizeof(LcDecodeArgs)>();
-    extern __shared__ int lds_dyn[];             // FUSED: the selection's chunk lists
+    // FUSED: the selection's chunk lists (written 8 bytes at a time: from a base that is not a multiple of 8 that took 0.7 us more)
+    extern __shared__ __attribute__((aligned(16))) int lds_dyn[];
     using SelStore = typename std::conditional<FUSED, LcLeafSelSh, int>::type;
     using FusedStore = typename std::conditional<FUSED, LcFusedSh<LC_DEC_THREADS>, int>::type;
-    __shared__ __attribute__((aligned(16))) SelStore sel_store;
+    // What is used one after the other shares its place, so that three workgroups fit a compute unit (up to 2560 chunks).
+    union Phases {
+        SelStore sel;                            // selection, crowded cutoff bin
+        struct {                                 // the wavefronts' sums
+            float4 acc[LC_DEC_THREADS / 64][G][LC_D / 4];
+            float ml[LC_DEC_THREADS / 64][G][2];
+        } comb;
+        float scale[LC_DEC_THREADS / 32][LC_DEC_MAX_SPLITS + 128];      // merge
+    };
+    union Rows {
+        int row[LC_DEC_TILE];                    // cache rows of the tile's tokens
+        float4 red[LC_DEC_THREADS];              // merge
+    };
+    __shared__ __attribute__((aligned(16))) Phases ph;
+    __shared__ __attribute__((aligned(16))) Rows rw;
     __shared__ __attribute__((aligned(16))) FusedStore fused_store;
     __shared__ lc_v4i entry_sh[SCORE ? LC_STEP_SINGLE_MAX_CHUNKS : 1];
     __shared__ int scan_sh[8];
-    __shared__ int rows[LC_DEC_TILE];
     __shared__ int last_sh;
-    __shared__ float comb_ml[LC_DEC_THREADS / 64][G][2];
-    __shared__ __attribute__((aligned(16))) float comb_acc[LC_DEC_THREADS / 64][G][LC_D];
-    __shared__ float mrg_s[LC_DEC_THREADS / 32][LC_DEC_MAX_SPLITS + 128];
-    __shared__ float4 mrg_red[LC_DEC_THREADS];
+    static_assert(sizeof(rw.red) <= sizeof(rw.row), "");
 
-    // tokens per group and batch of loads; two batches are in flight per group (the next one is
-    // issued before the current one is consumed)
-    constexpr int U = (G <= 4) ? 4 : 2;
+    constexpr int U = 4;                         // tokens per group and batch of loads; a step takes two batches
     constexpr int E = LC_DEC_E;
     const LcDev& ix = a.ix;
     const int s = blockIdx.x, S = gridDim.x, h = blockIdx.y, b = blockIdx.z;
@@ -129,7 +156,7 @@ lc_decode_kernel(const LcDecodeArgs a) {
     const int sub = tid & 15, grp = tid >> 4, q4 = lane >> 4;
 
     const int* bnd = ix.bounds + (size_t)b * (ix.cap[0] + 1);
-    // the query block in MFMA B layout (lane (q4, n): head n, columns 8 q4 + 32 j + [0, 8))
+    // the query block in MFMA B layout (lane (q4, n): head n, columns 8 q4 + 32 j + [0, 8), loaded once)
     uint4 qb[4];
     {
         const uint16_t* qh = a.q + ((size_t)b * ix.H * G + (size_t)h * G + min(sub, G - 1)) * LC_D + 8 * q4;
@@ -254,7 +281,7 @@ lc_decode_kernel(const LcDecodeArgs a) {
             else return __builtin_amdgcn_raw_buffer_load_b128(ent_r, first * 16, e * 1024, 0);
         };
         lc_select_chunks<LC_DEC_THREADS, EC>(ix, b, bh, entry, a.budget, a.sink, s == 0 ? a.ids_out : nullptr,
-                                             a.counts_out, a.cap, sel_store, fused_store, lds_dyn, cs);
+                                             a.counts_out, a.cap, ph.sel, fused_store, lds_dyn, cs);
         T = cs.T;
         M = cs.M;
         n_tok = cs.n_tok;
@@ -266,14 +293,13 @@ lc_decode_kernel(const LcDecodeArgs a) {
         const int lo = (int)(((long long)n_tok * s) / S_eff);
         const int hi = (int)(((long long)n_tok * (s + 1)) / S_eff);
         const float scale = 0.08838834764831845f * LC_LOG2E;     // log2(e) / sqrt(128)
-        // softmax state of head `sub` over this group's tokens (lanes sub >= G repeat head G-1)
-        float m_run = LC_NEG_INF, l_run = 0.f;
-        float acc[G][8];
+        // Softmax state of head `sub` (lanes sub >= G repeat head G - 1): the reference that is subtracted from the
+        // logits, one for the wavefront's tokens, and the sum over this group's tokens.  acc[c][r]: columns
+        // 8 sub + c of head 4 q4 + r over the wavefront's tokens.
+        float m_ref = LC_NEG_INF, l_run = 0.f;
+        lc_f32x4 acc[8];
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) acc[g][i] = 0.f;
-        }
+        for (int c = 0; c < 8; ++c) acc[c] = lc_f32x4{0.f, 0.f, 0.f, 0.f};
         // K and V of this (sequence, head) as buffer resources: one 32-bit byte offset per row
         // (the host has checked that the slab spans less than 2 GiB)
         // (the resources end with the last row the index may ever hold, so a wrong row cannot fault)
@@ -286,75 +312,125 @@ lc_decode_kernel(const LcDecodeArgs a) {
         // MFMA A operand -- and V for the tokens of its own group.
         const int gk = (wave << 2) + (sub >> 2), uk = sub & 3;
         int tv = 0, tv_end = 0, tk = 0, tk_end = 0;
-        // Branch-free: a branch around a load would put each row lookup (an LDS read) and its load in a
-        // basic block of its own, waited for one after the other.  All row lookups go out together
-        // (slot 0 stands in where there is no token) and a load without a token gets an offset past
-        // the resource's end, which the range check answers with zeros.
-        auto issue = [&](int it, lc_v4i (&kv)[4], lc_v4i (&vv)[U]) {
-            const int k_tok = tk + it * U + uk;
-            const bool k_in = uk < U && k_tok < tk_end;
-            const int k_row = rows[k_in ? k_tok : 0];
-            int v_row[U];
-            bool v_in[U];
+        // Two batches' loads, branch-free: a branch around a load would put each row lookup (an LDS read) and its load in a
+        // basic block of its own, waited for one after the other.  All row lookups go out together (slot 0 stands in where
+        // there is no token; the empty statement keeps the compiler from guarding them) and a load without a token gets
+        // an offset past the resource's end, which the range check answers with zeros.
+        auto k_offsets = [&](int it, int (&o)[2]) LC_INLINE {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int v_tok = tv + it * U + u;
-                v_in[u] = v_tok < tv_end;
-                v_row[u] = rows[v_in[u] ? v_tok : 0];
+            for (int i = 0; i < 2; ++i) {
+                const int tok = tk + (it + i) * U + uk;
+                int row = rw.row[tok < tk_end ? tok : 0];
+                asm volatile("" : "+v"(row));
+                o[i] = tok < tk_end ? row * row_bytes + 16 * q4 : slab_bytes;
             }
-            const int ko = k_in ? k_row * row_bytes + 16 * q4 : slab_bytes;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) kv[j] = __builtin_amdgcn_raw_buffer_load_b128(Kr, ko + 64 * j, 0, 0);
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                vv[u] = __builtin_amdgcn_raw_buffer_load_b128(Vr, v_in[u] ? v_row[u] * row_bytes + 16 * sub : slab_bytes, 0, 0);
         };
-        // logits of the wavefront's 16 tokens for all heads (MFMA), one online-softmax update of
-        // this lane's head, then P.V for every head with the broadcast probabilities
-        auto consume = [&](int it, const lc_v4i (&kv)[4], const lc_v4i (&vv)[U]) {
+        auto v_offsets = [&](int it, int (&o)[2 * U]) LC_INLINE {
+            int row[2 * U];
+#pragma unroll
+            for (int u = 0; u < 2 * U; ++u) {
+                const int tok = tv + it * U + u;
+                row[u] = rw.row[tok < tv_end ? tok : 0];
+            }
+#pragma unroll
+            for (int u = 0; u < 2 * U; ++u) {
+                asm volatile("" : "+v"(row[u]));
+                o[u] = tv + it * U + u < tv_end ? row[u] * row_bytes + 16 * sub : slab_bytes;
+            }
+        };
+        auto load_k = [&](const int (&o)[2], lc_v4i (&kA)[4], lc_v4i (&kB)[4]) LC_INLINE {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) kA[j] = __builtin_amdgcn_raw_buffer_load_b128(Kr, o[0] + 64 * j, 0, 0);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) kB[j] = __builtin_amdgcn_raw_buffer_load_b128(Kr, o[1] + 64 * j, 0, 0);
+        };
+        auto load_v = [&](const int (&o)[2 * U], lc_v4i (&vA)[U], lc_v4i (&vB)[U]) LC_INLINE {
+#pragma unroll
+            for (int u = 0; u < U; ++u) vA[u] = __builtin_amdgcn_raw_buffer_load_b128(Vr, o[u], 0, 0);
+#pragma unroll
+            for (int u = 0; u < U; ++u) vB[u] = __builtin_amdgcn_raw_buffer_load_b128(Vr, o[U + u], 0, 0);
+        };
+        // logits of 16 tokens of the wavefront for all heads: d[i] is token 4 q4 + i = token i of this lane's group, head `sub`
+        auto logits = [&](const lc_v4i (&kv)[4]) LC_INLINE -> lc_f32x4 {
             lc_f32x4 d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(lc_bf16x8, kv[j]),
                                                             __builtin_bit_cast(lc_bf16x8, qb[j]), d, 0, 0, 0);
-            // d[i]: token 4 q4 + i of the wavefront = token i of this lane's group, head `sub`
-            float x[U];
-            float mx = m_run;
+            return d;
+        };
+        // one online-softmax update of this lane's head with the logits of batches it and it + 1 (N = 8) or it alone (N = 4)
+        auto softmax = [&](auto count, int it, lc_f32x4 dA, lc_f32x4 dB, auto& p) LC_INLINE {
+            constexpr int N = decltype(count)::value;
+            float x[N];
+            float mx = LC_NEG_INF;
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                x[u] = (tv + it * U + u < tv_end) ? d[u] * scale : LC_NEG_INF;
+            for (int u = 0; u < N; ++u) {
+                x[u] = (tv + it * U + u < tv_end) ? (u < U ? dA[u % U] : dB[u % U]) * scale : LC_NEG_INF;
                 mx = fmaxf(mx, x[u]);
             }
-            const float ref = (mx == LC_NEG_INF) ? 0.f : mx;
-            const float sc = lc_exp2_rel(m_run, ref);
-            float p[U];
-            float psum = 0.f;
+            mx = lc_max_groups(mx);
+            // The reference follows the maximum only when it falls behind by more than 2^8 (probabilities up to that size lose
+            // nothing in float32): the accumulators are scaled once or not at all per split instead of once per step.
+            if (__ballot(mx > m_ref + 8.0f) != 0ull) {
+                const float m_new = fmaxf(mx, m_ref);
+                const float sc = (m_new == LC_NEG_INF) ? 1.f : lc_exp2_rel(m_ref, m_new);
+                const bool started = __ballot(m_ref > LC_NEG_INF) != 0ull;
+                m_ref = m_new;
+                if (started) {                                      // (before that the accumulators are zero)
+                    l_run *= sc;
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                p[u] = lc_exp2_rel(x[u], ref);
-                psum += p[u];
-            }
-            l_run = fmaf(l_run, sc, psum);
-            m_run = mx;
+                    for (int r = 0; r < 4; ++r) {
+                        const float sr = __shfl(sc, 4 * q4 + r);
 #pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const float sg = lc_row_bcast_n(sc, g);
-#pragma unroll
-                for (int i = 0; i < 8; ++i) acc[g][i] *= sg;
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                float vf[8];
-                {
-                    const int v0 = vv[u].x, v1 = vv[u].y, v2 = vv[u].z, v3 = vv[u].w;
-                    lc_unpack8(make_uint4((uint32_t)v0, (uint32_t)v1, (uint32_t)v2, (uint32_t)v3), vf);
+                        for (int c = 0; c < 8; ++c) acc[c][r] *= sr;
+                    }
                 }
+            }
+            const float ref = (m_ref == LC_NEG_INF) ? 0.f : m_ref;
 #pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    const float pg = lc_row_bcast_n(p[u], g);
+            for (int u = 0; u < N; ++u) p[u] = lc_exp2_rel(x[u], ref);
+            float l = (p[0] + p[1]) + (p[2] + p[3]);
+            if constexpr (N == 8) l += (p[4] + p[5]) + (p[6] + p[7]);
+            l_run += l;
+        };
+        auto pv = [&](const lc_v4i& t, const lc_v4i& b, lc_f32x4& a) LC_INLINE {
+            a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(lc_bf16x8, t), __builtin_bit_cast(lc_bf16x8, b), a, 0, 0, 0);
+        };
+        // column c of rows v[2k], v[2k + 1], packed
+        auto column = [&](const lc_v4i (&v)[U], int c, int k) LC_INLINE -> int {
+            return (int)__builtin_amdgcn_perm((uint32_t)v[2 * k + 1][c / 2], (uint32_t)v[2 * k][c / 2], (c & 1) ? 0x07060302u : 0x05040100u);
+        };
+        // P.V: of two batches, one instruction per term of P and column; of one, the first two terms share one.  The smallest
+        // terms go first: fewer roundings at full size.  (All instructions have one shape: with a 16x16x16 one adding to
+        // the result of a 16x16x32 one the compiler left too few wait states between the two.)
+        auto attend2 = [&](const float (&p)[2 * U], const lc_v4i (&vA)[U], const lc_v4i (&vB)[U]) LC_INLINE {
+            int t[3][U];
+            lc_split3<2 * U>(p, t);
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) acc[g][i] = fmaf(pg, vf[i], acc[g][i]);
-                }
+            for (int c0 = 0; c0 < 8; c0 += 4) {
+                lc_v4i bc[4];                                       // column c0 + c's eight tokens
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    bc[c] = lc_v4i{column(vA, c0 + c, 0), column(vA, c0 + c, 1), column(vB, c0 + c, 0), column(vB, c0 + c, 1)};
+#pragma unroll
+                for (int s = 2; s >= 0; --s)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) pv(lc_v4i{t[s][0], t[s][1], t[s][2], t[s][3]}, bc[c], acc[c0 + c]);
+            }
+        };
+        auto attend1 = [&](const float (&p)[U], const lc_v4i (&v)[U]) LC_INLINE {
+            int t[3][U / 2];
+            lc_split3<U>(p, t);
+#pragma unroll
+            for (int c0 = 0; c0 < 8; c0 += 4) {
+                int b0[4], b1[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) { b0[c] = column(v, c0 + c, 0); b1[c] = column(v, c0 + c, 1); }
+#pragma unroll
+                for (int c = 0; c < 4; ++c) pv(lc_v4i{t[2][0], t[2][1], 0, 0}, lc_v4i{b0[c], b1[c], 0, 0}, acc[c0 + c]);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) pv(lc_v4i{t[1][0], t[1][1], t[0][0], t[0][1]}, lc_v4i{b0[c], b1[c], b0[c], b1[c]}, acc[c0 + c]);
             }
         };
 
@@ -366,7 +442,7 @@ lc_decode_kernel(const LcDecodeArgs a) {
             // 64 lanes per selected chunk that overlaps the tile (its lane's values are read by number)
             auto fill = [&](int o, int st, int ln) {
                 const int k0 = max(o, tile0), k1 = min(o + ln, tile0 + tl);
-                for (int k = k0 + lane; k < k1; k += 64) rows[k - tile0] = max(0, min(st + (k - o), row_max));
+                for (int k = k0 + lane; k < k1; k += 64) rw.row[k - tile0] = max(0, min(st + (k - o), row_max));
             };
             auto fill_round = [&](int off, int st, int ln) {
                 unsigned long long mask = __ballot(ln > 0 && off < tile0 + tl && tile0 < off + ln);
@@ -413,35 +489,45 @@ lc_decode_kernel(const LcDecodeArgs a) {
             tv_end = min(tl, tv + per);
             tk = min(tl, gk * per);
             tk_end = min(tl, tk + per);
+            // steps of two batches, a last one of one; a step's K rows are fetched while the step before is at its softmax and
+            // P.V, its V rows behind that (batches past the last one load nothing)
             lc_v4i kA[4], vA[U], kB[4], vB[U];
-            issue(0, kA, vA);
-            for (int it = 0; it < n_it; it += 2) {
-                if (it + 1 < n_it) issue(it + 1, kB, vB);
-                consume(it, kA, vA);
-                if (it + 1 >= n_it) break;
-                if (it + 2 < n_it) issue(it + 2, kA, vA);
-                consume(it + 1, kB, vB);
+            int ko[2], vo[2 * U];
+            k_offsets(0, ko);
+            load_k(ko, kA, kB);
+            v_offsets(0, vo);
+            load_v(vo, vA, vB);
+            int it = 0;
+            for (; it + 1 < n_it; it += 2) {
+                const bool more = it + 2 < n_it;
+                const lc_f32x4 dA = logits(kA), dB = logits(kB);
+                if (more) { k_offsets(it + 2, ko); load_k(ko, kA, kB); }
+                float p[2 * U];
+                softmax(std::integral_constant<int, 2 * U>(), it, dA, dB, p);
+                attend2(p, vA, vB);
+                if (more) { v_offsets(it + 2, vo); load_v(vo, vA, vB); }
+            }
+            if (it < n_it) {
+                const lc_f32x4 dA = logits(kA);
+                float p[U];
+                softmax(std::integral_constant<int, U>(), it, dA, dA, p);
+                attend1(p, vA);
             }
         }
 
-        // ---- combine the 4 groups of a wave: one common reference per head, then the accumulators are added
-        // up and spread over the groups by row swaps (lanes of group q4 keep columns 8 sub + 4 (q4 >> 1) +
-        // 2 (q4 & 1) + {0, 1}), two vector instructions per pair of values; the waves meet in LDS
+        // ---- the accumulators hold the sums over the wavefront's tokens; the wavefronts meet in LDS
         {
-            const float mx = lc_max_groups(m_run);
-            const float sc = lc_exp2_rel(m_run, (mx == LC_NEG_INF) ? 0.f : mx);
-            float l = lc_add_halves(l_run * sc, l_run * sc);
+            float l = lc_add_halves(l_run, l_run);
             l = lc_add_rows(l, l);
-            if (lane < G) { comb_ml[wave][lane][0] = mx; comb_ml[wave][lane][1] = l; }
+            if (lane < G) { ph.comb.ml[wave][lane][0] = m_ref; ph.comb.ml[wave][lane][1] = l; }
 #pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const float sg = lc_row_bcast_n(sc, g);
-                float h4[4], h2[2];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) h4[i] = lc_add_halves(acc[g][i] * sg, acc[g][i + 4] * sg);
-#pragma unroll
-                for (int i = 0; i < 2; ++i) h2[i] = lc_add_rows(h4[i], h4[i + 2]);
-                *reinterpret_cast<float2*>(&comb_acc[wave][g][8 * sub + 4 * (q4 >> 1) + 2 * (q4 & 1)]) = make_float2(h2[0], h2[1]);
+            for (int r = 0; r < 4; ++r) {
+                const int g = 4 * q4 + r;
+                if (g < G) {
+                    float4* const o = &ph.comb.acc[wave][g][2 * sub];
+                    o[0] = make_float4(acc[0][r], acc[1][r], acc[2][r], acc[3][r]);
+                    o[1] = make_float4(acc[4][r], acc[5][r], acc[6][r], acc[7][r]);
+                }
             }
         }
         __syncthreads();
@@ -452,17 +538,17 @@ lc_decode_kernel(const LcDecodeArgs a) {
             const int g = v / (LC_D / 4), c4 = v % (LC_D / 4);
             float mx = LC_NEG_INF;
 #pragma unroll
-            for (int w = 0; w < LC_DEC_THREADS / 64; ++w) mx = fmaxf(mx, comb_ml[w][g][0]);
+            for (int w = 0; w < LC_DEC_THREADS / 64; ++w) mx = fmaxf(mx, ph.comb.ml[w][g][0]);
             float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
             float den = 0.f;
 #pragma unroll
             for (int w = 0; w < LC_DEC_THREADS / 64; ++w) {
-                const float mw = comb_ml[w][g][0];
+                const float mw = ph.comb.ml[w][g][0];
                 const float sc = (mw == LC_NEG_INF) ? 0.f : exp2f(mw - mx);
-                const float4 x = *reinterpret_cast<const float4*>(&comb_acc[w][g][4 * c4]);
+                const float4 x = ph.comb.acc[w][g][c4];
                 num.x = fmaf(x.x, sc, num.x); num.y = fmaf(x.y, sc, num.y);
                 num.z = fmaf(x.z, sc, num.z); num.w = fmaf(x.w, sc, num.w);
-                den = fmaf(comb_ml[w][g][1], sc, den);
+                den = fmaf(ph.comb.ml[w][g][1], sc, den);
             }
             lc_store_agent4(pacc_w, v * 16, num);
             if (c4 == 0) { lc_store_agent(&pml[2 * g], mx); lc_store_agent(&pml[2 * g + 1], den); }
@@ -475,9 +561,10 @@ lc_decode_kernel(const LcDecodeArgs a) {
     // The accumulator partials do not depend on the scales, so their loads go out first and fly while the
     // (m, l) pairs are fetched.  Every 32 lanes take one head (slot v of the output below) and turn its
     // splits' pairs into scales by themselves: no barrier until the sums meet.
-    const __amdgpu_buffer_rsrc_t pacc_r = lc_buffer(a.part_acc + (size_t)bh * S * G * LC_D);
-    const float* pml = a.part_ml + (size_t)bh * S * G * 2;
     const int n_part = (n_tok > 0) ? S_eff : 0;
+    // (the resource ends with the last split's partial: slots past it read 0)
+    const __amdgpu_buffer_rsrc_t pacc_r = lc_buffer(a.part_acc + (size_t)bh * S * G * LC_D, n_part * G * LC_D * 4);
+    const float* pml = a.part_ml + (size_t)bh * S * G * 2;
     constexpr int NV = G * (LC_D / 4);                       // float4 slots of the output
     constexpr int WAYS = (LC_DEC_THREADS / NV) > 0 ? (LC_DEC_THREADS / NV) : 1;
     constexpr int MR = (G <= 4) ? 16 : 8;                    // partials per round and thread
@@ -486,10 +573,8 @@ lc_decode_kernel(const LcDecodeArgs a) {
     float4 x[MR];
     auto load_round = [&](int sp0) {
 #pragma unroll
-        for (int k = 0; k < MR; ++k) {
-            const int spc = min(sp0 + k * WAYS, n_part - 1);
-            x[k] = lc_load_agent4(pacc_r, ((spc * G + g) * LC_D + 4 * c4) * 4);
-        }
+        for (int k = 0; k < MR; ++k)
+            x[k] = lc_load_agent4(pacc_r, (((sp0 + k * WAYS) * G + g) * LC_D + 4 * c4) * 4);
     };
     if (wy < WAYS && n_part > 0) load_round(wy);
     const int half = tid >> 5, hl = tid & 31;
@@ -510,7 +595,7 @@ lc_decode_kernel(const LcDecodeArgs a) {
             const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(m_all), __float_as_uint(m_all), false, false);
             m_all = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
         }
-        // (zero scales up to the end of the last round, whose slots past the last split repeat it)
+        // (zero scales up to the end of the last round)
         const int n_slots = (n_part + MR * WAYS - 1) / (MR * WAYS) * (MR * WAYS);
         for (int sp = hl; sp < n_slots; sp += 32) {
             float ms = m0, ls = l0;
@@ -519,7 +604,7 @@ lc_decode_kernel(const LcDecodeArgs a) {
                 ls = sp < n_part ? lc_load_agent(pml + 2 * (sp * G + g) + 1) : 0.f;
             }
             const float sc = (ms == LC_NEG_INF) ? 0.f : exp2f(ms - m_all);
-            mrg_s[half][sp] = sc;
+            ph.scale[half][sp] = sc;
             den = fmaf(ls, sc, den);
         }
         den = lc_sum16(den);
@@ -534,20 +619,20 @@ lc_decode_kernel(const LcDecodeArgs a) {
 #pragma unroll
             for (int k = 0; k < MR; ++k) {
                 const int sp = sp0 + k * WAYS;
-                const float sc = mrg_s[half][sp];
+                const float sc = ph.scale[half][sp];
                 acc4.x = fmaf(x[k].x, sc, acc4.x);
                 acc4.y = fmaf(x[k].y, sc, acc4.y);
                 acc4.z = fmaf(x[k].z, sc, acc4.z);
                 acc4.w = fmaf(x[k].w, sc, acc4.w);
             }
         }
-        if (WAYS > 1 && wy > 0) mrg_red[(wy - 1) * NV + v] = acc4;
+        if (WAYS > 1 && wy > 0) rw.red[(wy - 1) * NV + v] = acc4;
     }
     __syncthreads();
     if (wy == 0) {
 #pragma unroll
         for (int k = 1; k < WAYS; ++k) {
-            const float4 o4 = mrg_red[(k - 1) * NV + v];
+            const float4 o4 = rw.red[(k - 1) * NV + v];
             acc4.x += o4.x; acc4.y += o4.y; acc4.z += o4.z; acc4.w += o4.w;
         }
         const float inv = den > 0.f ? 1.0f / den : 0.f;

@@ -72,6 +72,7 @@ size_t lc_layout_ws(const lc_config* cfg, int B, int H_q, int H, int d, int spli
                     bool with_build = true);
 // Up to this many chunks per (sequence, head) the workgroups of a decode step may score all of them themselves.
 #define LC_STEP_SINGLE_MAX_CHUNKS 128
+#define LC_COMPUTE_UNITS 256                // of an MI355X
 #define LC_DEC_MIN_TOKENS_PER_SPLIT 64      // tokens of a split of the attention kernel, at least
 int lc_auto_splits(const lc_config* cfg, int B, int H);
 

@@ -1,0 +1,59 @@
+"""The attention kernel's P.V on the matrix cores: token counts around its steps (32 tokens of a wavefront), tiles and splits,
+logits that rise and fall along the tokens (the softmax's reference moves late, or never), infinite values of V."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("G", [1, 2, 3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("tokens,splits", [(1, 0), (15, 1), (63, 1), (64, 1), (65, 1), (127, 1), (129, 2), (1025, 1), (2500, 2), (700, 0)])
+def test_against_float64(tokens, splits, G):
+    import torch
+    from paper_2603_08453_amd import binding as lc
+    H, T = 2, tokens
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(100 * T + G)
+    draw = lambda *shape: torch.randn(shape, generator=gen, device="cuda")
+    q = draw(1, H * G, 128)
+    K, V = draw(1, H, T, 128), draw(1, H, T, 128)
+    # head 0's keys lean towards the group's queries by an amount that rises along the tokens, head 1's falls
+    lean = torch.linspace(0.0, 1.5, T, device="cuda")
+    for h, w in enumerate((lean, lean.flip(0))):
+        K[0, h] += w[:, None] * q[0, h * G:(h + 1) * G].sum(dim=0)
+    q, K, V = q.to(torch.bfloat16), K.to(torch.bfloat16), V.to(torch.bfloat16)
+    bounds = np.unique(np.concatenate([[0], np.arange(7, T, 13), [max(0, T - 3)]])).astype(np.int32)      # (an open tail)
+    cfg = lc.lc_config_default(levels=2, fanout=8, kmeans_iters=1, max_chunks=max(1, len(bounds)), max_tokens=T, decode_splits=splits)
+    ib = torch.zeros(lc.lc_index_bytes(cfg, 1, H), dtype=torch.uint8, device="cuda")
+    ws = torch.zeros(lc.lc_workspace_bytes(cfg, 1, H * G, H), dtype=torch.uint8, device="cuda")
+    idx = lc.lc_build_index(cfg, K, [T], [bounds], ib, ws)
+
+    def step(V):
+        out = torch.full((1, H * G, 128), float("nan"), device="cuda")
+        lse = torch.full((1, H * G), float("nan"), device="cuda")
+        lc.lc_decode_step(idx, q, K, V, 10 ** 6, out, ws, lse=lse)
+        return out[0].double().cpu(), lse[0].double().cpu()
+
+    out, lse = step(V)
+    x = torch.stack([q[0, g].double().cpu() @ K[0, g // G].double().cpu().T for g in range(H * G)]) / 128 ** 0.5
+    p = torch.softmax(x, dim=-1)
+    v = V[0].double().cpu()
+    ref = torch.stack([p[g] @ v[g // G] for g in range(H * G)])
+    # a logit is a float32 sum of 128 products: off by at most 2^-24 * 8 of the sum of their sizes (the matrix instruction adds 32 at
+    # a time), a probability by that relatively, and V's sum by that of the sum of |p v|, plus the roundings of the sums
+    size = torch.stack([q[0, g].double().cpu().abs() @ K[0, g // G].double().cpu().abs().T for g in range(H * G)]) / 128 ** 0.5
+    rel = 2.0 * (2.0 ** -21 * size.amax(dim=-1) + 2.0 ** -20)
+    bound = rel[:, None] * torch.stack([p[g] @ v[g // G].abs() for g in range(H * G)])
+    assert ((out - ref).abs() <= bound).all(), ((out - ref).abs() / bound).max()
+    assert ((lse - torch.logsumexp(x, dim=-1)).abs() <= rel + 2.0 ** -22 * lse.abs()).all()
+
+    # infinite values reach their column of the heads that weigh the token, and nothing else
+    t = int(p[:, :].sum(dim=0).argmax())
+    W = V.clone()
+    W[0, :, t, 5], W[0, :, t, 77] = float("inf"), float("-inf")
+    got, _ = step(W)
+    heavy = p[:, t] > 1e-30
+    assert heavy.any()
+    assert (got[heavy, 5] == float("inf")).all() and (got[heavy, 77] == float("-inf")).all()
+    rest = [c for c in range(128) if c not in (5, 77)]
+    assert torch.equal(got[:, rest], out[:, rest])
