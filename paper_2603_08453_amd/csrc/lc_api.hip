@@ -583,7 +583,7 @@ int decode_step_checks(const lc_index* idx, const void* q, const void* K, const 
 // Splits that can find work: the attention kernel gives a split at least LC_DEC_MIN_TOKENS_PER_SPLIT tokens, and a
 // (sequence, head) attends to at most its budget and its open tail (all its tokens if some are pinned).
 // Splits beyond that would only repeat the selection and count as arrived.
-int useful_splits(const lc_index* idx, int budget, int splits) {
+int useful_splits(const lc_index* idx, int G, int budget, int splits) {
     long long most = 1;
     for (int b = 0; b < idx->B; ++b) {
         long long n = idx->T[b];
@@ -592,7 +592,15 @@ int useful_splits(const lc_index* idx, int budget, int splits) {
     }
     const long long need = (most + LC_DEC_MIN_TOKENS_PER_SPLIT - 1) / LC_DEC_MIN_TOKENS_PER_SPLIT;
     splits = resident_splits(idx, splits);
-    return need < splits ? (int)need : splits;
+    if (need < splits) splits = (int)need;
+    // One workgroup per compute unit instead of two where that leaves few units idle and no split more than a few steps
+    // of tokens: the selection runs once per unit and the merge has half the partials, at the price of loads in flight.
+    // Steps of 10 to 128 pairs, us with two and with one: group size 4, 93 tokens a split 12.8 and 11.5, 78: 23.0 and 21.9, but 264: 14.4
+    // and 15.7; group size 7 (a larger merge), 118: 12.4 and 11.0, 274: 19.3 and 18.3, 338: 16.8 and 16.1.
+    const int pairs = idx->B * idx->H_kv, one = LC_COMPUTE_UNITS / pairs;
+    const long long few = G > 4 ? 352 : 192;
+    if (idx->cfg.decode_splits == 0 && splits > one && 8 * one * pairs >= 7 * LC_COMPUTE_UNITS && most <= few * one) splits = one;
+    return splits;
 }
 
 // One kernel or two (without a level walk): every workgroup scoring all chunks costs 0.5 us per 64 chunks at group
@@ -611,7 +619,7 @@ int decode_step_run(const lc_index* idx, const LcWs& w, const RetrievePlan& p, i
                     bool second_kernel_only = false) {
     const bool want_ids = chunk_ids != nullptr;
     const int G = H_q / idx->H_kv;
-    splits = useful_splits(idx, budget, splits);
+    splits = useful_splits(idx, G, budget, splits);
     int rc;
     // Every workgroup of the fused kernel repeats the selection with 256 threads: with a few thousand
     // chunks that is cheaper than the hand-off through a chunk list, with more it is not.
