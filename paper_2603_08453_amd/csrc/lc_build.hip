@@ -14,6 +14,8 @@
 #include "lc_internal.h"
 #include "lc_select.h"
 
+#include <type_traits>
+
 #define LC_BT 256                 // threads per block
 #define LC_BG (LC_BT / 16)        // 16-lane groups per block
 #define LC_RADIUS_PAD 4e-6f       // stored radii are inflated by this relative amount so that
@@ -143,6 +145,11 @@ __device__ __forceinline__ void lc_store8_bf16(uint16_t* p, const float (&v)[8])
 #pragma unroll
     for (int i = 0; i < 8; ++i) h[i] = lc_f32_to_bf16_bits(v[i]);
     *reinterpret_cast<uint4*>(p) = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
+}
+template <typename Acc>
+__device__ __forceinline__ void lc_store_acc8(Acc* p, const Acc (&v)[8]) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) p[t] = v[t];
 }
 __device__ __forceinline__ void lc_load8(const float* p, float (&v)[8]) {
     const float4 a = *reinterpret_cast<const float4*>(p);
@@ -1014,20 +1021,33 @@ __device__ __forceinline__ bool lc_fill_buckets(LabF lab, int N, int c0, int n_c
     return true;
 }
 
+// One row more in a sum: plain float32 rows, or rows of weight w (0: left out, whatever the row holds) in float64.
+template <int N>
+__device__ __forceinline__ void lc_add_row(float (&acc)[N], const float (&x)[N], int) {
+#pragma unroll
+    for (int t = 0; t < N; ++t) acc[t] += x[t];
+}
+template <int N>
+__device__ __forceinline__ void lc_add_row(double (&acc)[N], const float (&x)[N], int w) {
+#pragma unroll
+    for (int t = 0; t < N; ++t) acc[t] = fma((double)(w > 0 ? x[t] : 0.f), (double)w, acc[t]);
+}
+
 // Sum of the rows of list[t0, t1) as described above, by one 16-lane group (8 columns per lane); with
 // `flush` false only the running sum of one partial is wanted (all members of one partial).
-// row(i, x): columns [8 sub, 8 sub + 8) of member i's row.
-template <typename RowF>
-__device__ __forceinline__ void lc_sum_listed(const LcBuckets& s, int t0, int t1, RowF row, float (&sum)[8]) {
+// row(i, x): columns [8 sub, 8 sub + 8) of member i's row; returns its weight.
+template <typename Acc, typename RowF>
+__device__ __forceinline__ void lc_sum_listed(const LcBuckets& s, int t0, int t1, RowF row, Acc (&sum)[8]) {
     constexpr int BATCH = 8;                                        // rows in flight per group
-    float run[8];
+    Acc run[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) { sum[u] = 0.f; run[u] = 0.f; }
+    for (int u = 0; u < 8; ++u) { sum[u] = 0; run[u] = 0; }
     int g = t0 < t1 ? s.part[t0] : 0;
     for (int t = t0; t < t1; t += BATCH) {
         float x[BATCH][8];
+        int w[BATCH];
 #pragma unroll
-        for (int e = 0; e < BATCH; ++e) row(s.list[min(t + e, t1 - 1)], x[e]);
+        for (int e = 0; e < BATCH; ++e) w[e] = row(s.list[min(t + e, t1 - 1)], x[e]);
 #pragma unroll
         for (int e = 0; e < BATCH; ++e) {
             if (t + e < t1) {
@@ -1035,10 +1055,9 @@ __device__ __forceinline__ void lc_sum_listed(const LcBuckets& s, int t0, int t1
                 if (ge != g) {
                     g = ge;
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) { sum[u] += run[u]; run[u] = 0.f; }
+                    for (int u = 0; u < 8; ++u) { sum[u] += run[u]; run[u] = 0; }
                 }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) run[u] += x[e][u];
+                lc_add_row(run, x[e], w[e]);
             }
         }
     }
@@ -1048,9 +1067,10 @@ __device__ __forceinline__ void lc_sum_listed(const LcBuckets& s, int t0, int t1
 
 // The sums of the rows of clusters [c0, c0 + n_c), each handed to done(c, n, sum) in one whole 16-lane group
 // (c: cluster, n: members, sum: 8 columns per lane).  Small clusters one per group, clusters of more than
-// LC_UB_BIG members by the workgroup, 16 groups for the 16 partial sums.  sh: 16 * LC_D floats.
-template <typename LabF, typename RowF, typename DoneF>
-__device__ __forceinline__ void lc_cluster_sums(LabF lab, int N, int c0, int n_c, LcBuckets& s, float* sh, RowF row,
+// LC_UB_BIG members by the workgroup, 16 groups for the 16 partial sums.  sh: 16 * LC_D values.
+// Acc: the type the rows are summed in.
+template <typename Acc, typename LabF, typename RowF, typename DoneF>
+__device__ __forceinline__ void lc_cluster_sums(LabF lab, int N, int c0, int n_c, LcBuckets& s, Acc* sh, RowF row,
                                                 DoneF done) {
     const int sub = threadIdx.x & 15, grp = threadIdx.x >> 4;
     if (N > 0 && !lc_fill_buckets(lab, N, c0, n_c, s)) {
@@ -1059,28 +1079,27 @@ __device__ __forceinline__ void lc_cluster_sums(LabF lab, int N, int c0, int n_c
         int* const cnt = s.list;
         static_assert(sizeof(s.raw) >= LC_MEM_WIN * sizeof(int), "window of the one-by-one listing");
         for (int c = 0; c < n_c; ++c) {
-            float sum[8];
+            Acc sum[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) sum[u] = 0.f;
+            for (int u = 0; u < 8; ++u) sum[u] = 0;
             int n = 0;
             for (int base = 0; base < N; base += LC_MEM_WIN) {
                 const int nm = lc_collect_members<LC_BT>(lab, N, base, c0 + c, mem, cnt);
 #pragma unroll 4
                 for (int t = grp; t < nm; t += LC_BG) {
                     float x[8];
-                    row(mem[t], x);
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) sum[u] += x[u];
+                    const int w = row(mem[t], x);
+                    lc_add_row(sum, x, w);
                 }
                 n += nm;
                 __syncthreads();                                    // the list is rewritten by the next window
             }
-            lc_store8(sh + grp * LC_D + 8 * sub, sum);
+            lc_store_acc8(sh + grp * LC_D + 8 * sub, sum);
             __syncthreads();
             if (grp == 0) {
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
-                    float a = 0.f;
+                    Acc a = 0;
                     for (int g = 0; g < LC_BG; ++g) a += sh[g * LC_D + 8 * sub + u];
                     sum[u] = a;
                 }
@@ -1092,16 +1111,16 @@ __device__ __forceinline__ void lc_cluster_sums(LabF lab, int N, int c0, int n_c
     }
     if (N == 0) {
         for (int c = grp; c < n_c; c += LC_BG) {
-            float sum[8];
+            Acc sum[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) sum[u] = 0.f;
+            for (int u = 0; u < 8; ++u) sum[u] = 0;
             done(c0 + c, 0, sum);
         }
         return;
     }
     for (int c = grp; c < n_c; c += LC_BG) {
         if (s.n[c] > LC_UB_BIG) continue;
-        float sum[8];
+        Acc sum[8];
         lc_sum_listed(s, s.off[c], s.off[c + 1], row, sum);
         done(c0 + c, s.n[c], sum);
     }
@@ -1116,15 +1135,15 @@ __device__ __forceinline__ void lc_cluster_sums(LabF lab, int N, int c0, int n_c
             while (a < z) { const int m = (a + z) >> 1; if (s.part[m] <= grp) a = m + 1; else z = m; }
             hi = a;
         }
-        float sum[8];
+        Acc sum[8];
         lc_sum_listed(s, lo, hi, row, sum);
         __syncthreads();
-        lc_store8(sh + grp * LC_D + 8 * sub, sum);
+        lc_store_acc8(sh + grp * LC_D + 8 * sub, sum);
         __syncthreads();
         if (grp == 0) {
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                float a = 0.f;
+                Acc a = 0;
                 for (int g = 0; g < LC_BG; ++g) a += sh[g * LC_D + 8 * sub + u];
                 sum[u] = a;
             }
@@ -1139,21 +1158,21 @@ __device__ __forceinline__ void lc_cluster_sums(LabF lab, int N, int c0, int n_c
 // ways, for four times the loads in flight.  visit(mem, nm) sees every window's list.
 // On return sh[128] .. hold nothing of use and threads < 16 have the sum (8 columns each); returns the number
 // of members in every thread.  All NT threads must call.
-template <int NT>
+template <int NT, typename Acc>
 struct LcSumSh {
-    float part[LC_BG][LC_D];
+    Acc part[LC_BG][LC_D];
     int mem[LC_MEM_WIN];
     int cnt[2 * 64 + 1];
 };
-template <int NT, typename LabF, typename RowF, typename VisitF>
-__device__ __forceinline__ int lc_member_sum(LabF lab, int N, int u, LcSumSh<NT>& s, RowF row, VisitF visit, float (&sum)[8]) {
+template <int NT, typename Acc, typename LabF, typename RowF, typename VisitF>
+__device__ __forceinline__ int lc_member_sum(LabF lab, int N, int u, LcSumSh<NT, Acc>& s, RowF row, VisitF visit, Acc (&sum)[8]) {
     constexpr int COLS = 8 * 256 / NT;                              // columns per lane
     constexpr int BATCH = NT == 256 ? 4 : 16;                       // rows in flight per group
     const int tid = threadIdx.x, sub = tid & 15, part = (tid >> 4) & 15;
     const int col = (tid >> 8) * (COLS * 16) + COLS * sub;
-    float acc[COLS];
+    Acc acc[COLS];
 #pragma unroll
-    for (int t = 0; t < COLS; ++t) acc[t] = 0.f;
+    for (int t = 0; t < COLS; ++t) acc[t] = 0;
     int n = 0;
     int lv[LC_MEM_WIN / NT];
     if (N > 0) lc_load_labels<NT>(lab, N, 0, lv);
@@ -1162,9 +1181,11 @@ __device__ __forceinline__ int lc_member_sum(LabF lab, int N, int u, LcSumSh<NT>
         if (base + LC_MEM_WIN < N) lc_load_labels<NT>(lab, N, base + LC_MEM_WIN, lv);
         for (int t = part; t < nm; t += BATCH * 16) {
             float x[BATCH][COLS];
+            int w[BATCH];
 #pragma unroll
             for (int e = 0; e < BATCH; ++e) {
-                if (t + 16 * e < nm) row(s.mem[t + 16 * e], col, x[e]);
+                w[e] = 0;
+                if (t + 16 * e < nm) w[e] = row(s.mem[t + 16 * e], col, x[e]);
                 else {
 #pragma unroll
                     for (int q = 0; q < COLS; ++q) x[e][q] = 0.f;
@@ -1172,22 +1193,19 @@ __device__ __forceinline__ int lc_member_sum(LabF lab, int N, int u, LcSumSh<NT>
             }
 #pragma unroll
             for (int e = 0; e < BATCH; ++e)
-                if (t + 16 * e < nm) {
-#pragma unroll
-                    for (int q = 0; q < COLS; ++q) acc[q] += x[e][q];
-                }
+                if (t + 16 * e < nm) lc_add_row(acc, x[e], w[e]);
         }
         visit(s.mem, nm);
         n += nm;
         if (base + LC_MEM_WIN < N) lc_barrier_lds();                // the list is rewritten by the next window
     }
-    if constexpr (COLS == 8) lc_store8(&s.part[part][col], acc);
-    else *reinterpret_cast<float2*>(&s.part[part][col]) = make_float2(acc[0], acc[1]);
+#pragma unroll
+    for (int q = 0; q < COLS; ++q) s.part[part][col + q] = acc[q];
     __syncthreads();
     if (tid < 16) {
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
-            float a = 0.f;
+            Acc a = 0;
             for (int g = 0; g < LC_BG; ++g) a += s.part[g][8 * sub + t];
             sum[t] = a;
         }
@@ -1216,7 +1234,7 @@ __global__ void __launch_bounds__(LC_BT)
 lc_kmeans_update_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* cent, uint16_t* cent16, int cent_cap, int it,
                         int* flags_all) {
     lc_fetch_args<sizeof(LcDev) + 40>();
-    __shared__ __attribute__((aligned(16))) LcSumSh<LC_BT> sh;
+    __shared__ __attribute__((aligned(16))) LcSumSh<LC_BT, float> sh;
     const int c = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     const int bh = b * ix.H + h;
     const int* const flags = flags_all ? lc_level_flags(ix, flags_all, l, bh) : nullptr;
@@ -1226,9 +1244,9 @@ lc_kmeans_update_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* c
     const int* labels = ix.parent[l] + (size_t)bh * ix.cap[l];
     const float* P = pts + (size_t)bh * pts_cap * LC_D;
     float sum[8];
-    lc_member_sum<LC_BT>([&](int i) { return labels[i]; }, N, c, sh,
-                         [&](int i, int col, float (&x)[8]) { lc_load8(P + (size_t)i * LC_D + col, x); },
-                         [](const int*, int) {}, sum);
+    lc_member_sum<LC_BT, float>([&](int i) { return labels[i]; }, N, c, sh,
+                                [&](int i, int col, float (&x)[8]) { lc_load8(P + (size_t)i * LC_D + col, x); return 1; },
+                                [](const int*, int) {}, sum);
     if (threadIdx.x < 16)
         lc_write_centroid(cent, cent16, ((size_t)bh * cent_cap + c) * LC_D + 8 * threadIdx.x, sum);
 }
@@ -1251,9 +1269,9 @@ lc_kmeans_update_few_kernel(LcDev ix, int l, const float* pts, int pts_cap, floa
     if (c0 >= k) return;
     const int* labels = ix.parent[l] + (size_t)bh * ix.cap[l];
     const float* P = pts + (size_t)bh * pts_cap * LC_D;
-    lc_cluster_sums(
+    lc_cluster_sums<float>(
         [&](int i) { return labels[i]; }, N, c0, min(per, k - c0), bk, sh,
-        [&](int i, float (&x)[8]) { lc_load8(P + (size_t)i * LC_D + 8 * sub, x); },
+        [&](int i, float (&x)[8]) { lc_load8(P + (size_t)i * LC_D + 8 * sub, x); return 1; },
         [&](int c, int, float (&s)[8]) { lc_write_centroid(cent, cent16, ((size_t)bh * cent_cap + c) * LC_D + 8 * sub, s); });
 }
 
@@ -1391,13 +1409,6 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* ce
         cent[(size_t)bh * cent_cap * LC_D + v] = cs[(v / LC_D) * LC_AS_ROW + (v % LC_D)];
 }
 
-// Chunk j's ancestor at level l + 1, following the parent pointers from level 0.
-__device__ __forceinline__ int lc_ancestor(const LcDev& ix, int bh, int l, int j) {
-    int a = ix.parent[0][(size_t)bh * ix.cap[0] + j];
-    for (int t = 1; t <= l; ++t) a = a >= 0 ? ix.parent[t][(size_t)bh * ix.cap[t] + a] : -1;
-    return a;
-}
-
 // What is stored of node u of level l + 1 except its radius: center (mean of the descendant chunks'
 // centers; the centroid for the unit geometry and for a node without chunks), counts, unit direction (the
 // next level's point); the radius starts at -inf.  Called by one 16-lane group.
@@ -1407,14 +1418,15 @@ struct LcNodeArgs {
     int geometry;
     LcPointRows next;        // the next level's points and starting centroids
 };
+template <typename Acc>
 __device__ __forceinline__ void lc_write_node(const LcDev& ix, int b, int bh, int l, int u, int n_chunks, int n_tok,
-                                              float (&sum)[8], const LcNodeArgs& w) {
+                                              const Acc (&sum)[8], const LcNodeArgs& w) {
     const int sub = threadIdx.x & 15;
     float mu[8];
     if (n_chunks > 0 && w.geometry == LC_GEOMETRY_TOKEN_BALL) {
-        const float inv = 1.0f / (float)n_chunks;
+        const Acc inv = (Acc)1 / (Acc)n_chunks;
 #pragma unroll
-        for (int t = 0; t < 8; ++t) mu[t] = sum[t] * inv;
+        for (int t = 0; t < 8; ++t) mu[t] = (float)(sum[t] * inv);
     } else if (lc_level_count(ix, b, bh, l) > 0) {
         lc_load8(w.cent + ((size_t)bh * w.cent_cap + u) * LC_D + 8 * sub, mu);
     } else {                                                        // (a sequence without chunks: no centroid was started)
@@ -1436,80 +1448,114 @@ __device__ __forceinline__ void lc_write_node(const LcDev& ix, int b, int bh, in
     }
 }
 
-// Centers of a level of many small nodes (LC_UPD_FEW chunks or fewer on average): a workgroup lists the
-// chunks of `per` nodes and gives each node to a 16-lane group.
+// What a node of level l + 1 is made of: the chunks under it, or above the first level its child nodes, each weighted by
+// the chunks it holds: a child's center is their mean, so the weighted sum is the sum over all descendant chunks.  It is taken in
+// float64, so that its error is no larger than that of the float32 sum of the chunks (relative to the center, level 2 and
+// 3 of 2275 chunks: 8.8e-8 and 2.2e-7 as the chunks' sum, 7.0e-8 and 1.3e-7 now).  Children instead of chunks: 143 nodes into 9
+// and 9 into 1, 8 heads, 27 and 10 us, now 6.8 and 5.5; 5461 nodes into 249: 62 us, now 34.
+template <bool NODES>
+struct LcMembers {
+    const float* center;             // rows of the members: float32, or bfloat16 at the chunk level if `half`
+    const int* label;
+    const int* ntok;
+    const int* nchunk;               // NODES
+    bool half;
+    int n;
+    __device__ __forceinline__ LcMembers(const LcDev& ix, int b, int bh, int l) {
+        const size_t at = (size_t)bh * ix.cap[NODES ? l : 0];
+        half = !NODES && ix.c0_bf16 != 0;
+        center = half ? reinterpret_cast<const float*>(reinterpret_cast<const uint16_t*>(ix.center[0]) + at * LC_D)
+                      : ix.center[NODES ? l : 0] + at * LC_D;
+        label = ix.parent[NODES ? l : 0] + at;
+        ntok = ix.ntok[NODES ? l : 0] + at;
+        nchunk = NODES ? ix.nchunk[l] + at : nullptr;
+        n = NODES ? ix.nlev[b * LC_MAX_LEVELS + l] : ix.state[bh * 4 + 1];
+    }
+    // columns [col, col + COLS) of member j's row; returns its weight
+    template <int COLS>
+    __device__ __forceinline__ int row(int j, int col, float (&x)[COLS]) const {
+        const size_t o = (size_t)j * LC_D + col;
+        const uint16_t* const c16 = reinterpret_cast<const uint16_t*>(center);
+        if constexpr (COLS == 8) {
+            if (half) lc_unpack8(*reinterpret_cast<const uint4*>(c16 + o), x);
+            else lc_load8(center + o, x);
+        } else if (half) {
+            const uint32_t v = *reinterpret_cast<const uint32_t*>(c16 + o);
+            x[0] = lc_bf16_lo(v);
+            x[1] = lc_bf16_hi(v);
+        } else {
+            const float2 v = *reinterpret_cast<const float2*>(center + o);
+            x[0] = v.x;
+            x[1] = v.y;
+        }
+        return chunks(j);
+    }
+    __device__ __forceinline__ int chunks(int j) const { return NODES ? nchunk[j] : 1; }
+};
+
+// Centers of a level of many small nodes (LC_UPD_FEW members or fewer on average): a workgroup lists the
+// members of `per` nodes and gives each node to a 16-lane group.
+template <bool NODES>
 __global__ void __launch_bounds__(LC_BT)
 lc_center_few_kernel(LcDev ix, int l, LcNodeArgs w, int per) {
     lc_fetch_args<sizeof(LcDev) + sizeof(LcNodeArgs)>();
+    using Acc = typename std::conditional<NODES, double, float>::type;
     __shared__ LcBuckets bk;
-    __shared__ __attribute__((aligned(16))) float sh[LC_BG * LC_D];
+    __shared__ __attribute__((aligned(16))) Acc sh[LC_BG * LC_D];
     const int h = blockIdx.y, b = blockIdx.z;
     const int bh = b * ix.H + h;
     const int sub = threadIdx.x & 15;
     const int k = ix.nlev[b * LC_MAX_LEVELS + l + 1];
     const int u0 = blockIdx.x * per;
     if (u0 >= k) return;
-    const int M = ix.state[bh * 4 + 1];
-    const size_t cb = (size_t)bh * ix.cap[0];
-    lc_cluster_sums(
-        [&](int j) { return lc_ancestor(ix, bh, l, j); }, M, u0, min(per, k - u0), bk, sh,
-        [&](int j, float (&x)[8]) { lc_c0_load8(ix, cb + j, sub, x); },
-        [&](int u, int n, float (&sum)[8]) {
-            int tok = 0;
-            if (M > 0 && bk.total <= LC_UB_LIST) {                  // the list is still there
-                for (int t = bk.off[u - u0] + sub; t < bk.off[u - u0] + n; t += 16) tok += ix.ntok[0][cb + bk.list[t]];
+    const LcMembers<NODES> m(ix, b, bh, l);
+    lc_cluster_sums<Acc>(
+        [&](int j) { return m.label[j]; }, m.n, u0, min(per, k - u0), bk, sh,
+        [&](int j, float (&x)[8]) { return m.row(j, 8 * sub, x); },
+        [&](int u, int n, Acc (&sum)[8]) {
+            int tok = 0, chunks = 0;
+            auto count = [&](int j) { tok += m.ntok[j]; chunks += m.chunks(j); };
+            if (m.n > 0 && bk.total <= LC_UB_LIST) {                // the list is still there
+                for (int t = bk.off[u - u0] + sub; t < bk.off[u - u0] + n; t += 16) count(bk.list[t]);
             } else {                                                // nodes listed one by one
-                for (int j = sub; j < M; j += 16) tok += lc_ancestor(ix, bh, l, j) == u ? ix.ntok[0][cb + j] : 0;
+                for (int j = sub; j < m.n; j += 16)
+                    if (m.label[j] == u) count(j);
             }
-            lc_write_node(ix, b, bh, l, u, n, lc_sum16_i(tok), sum, w);
+            lc_write_node(ix, b, bh, l, u, lc_sum16_i(chunks), lc_sum16_i(tok), sum, w);
         });
 }
 
 // Centers of a level of larger nodes: a workgroup per node, of 1024 threads where nodes hold more than
-// LC_CENTER_WIDE chunks on average (there a single compute unit's rate of reading rows is the bound).
+// LC_CENTER_WIDE members on average (there a single compute unit's rate of reading rows is the bound).
 #define LC_CENTER_WIDE 128
-template <int NT>
+template <int NT, bool NODES>
 __global__ void __launch_bounds__(NT)
 lc_center_kernel(LcDev ix, int l, LcNodeArgs w) {
     lc_fetch_args<sizeof(LcDev) + sizeof(LcNodeArgs)>();
-    __shared__ __attribute__((aligned(16))) LcSumSh<NT> sh;
-    __shared__ int tok_sh[NT / 64];
+    using Acc = typename std::conditional<NODES, double, float>::type;
+    __shared__ __attribute__((aligned(16))) LcSumSh<NT, Acc> sh;
+    __shared__ int tok_sh[NT / 64], chunk_sh[NT / 64];
     const int u = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     const int bh = b * ix.H + h;
     if (u >= ix.nlev[b * LC_MAX_LEVELS + l + 1]) return;
     const int tid = threadIdx.x;
-    const int M = ix.state[bh * 4 + 1];
-    const size_t cb = (size_t)bh * ix.cap[0];
     constexpr int COLS = 8 * 256 / NT;
-    const bool half = ix.c0_bf16 != 0;
-    const uint16_t* const c16 = reinterpret_cast<const uint16_t*>(ix.center[0]);
-    int tok = 0;
-    float sum[8];
-    const int n = lc_member_sum<NT>(
-        [&](int j) { return lc_ancestor(ix, bh, l, j); }, M, u, sh,
-        [&](int j, int col, float (&x)[COLS]) {
-            const size_t o = (cb + j) * LC_D + col;
-            if constexpr (COLS == 8) {
-                if (half) lc_unpack8(*reinterpret_cast<const uint4*>(c16 + o), x);
-                else lc_load8(ix.center[0] + o, x);
-            } else if (half) {
-                const uint32_t v = *reinterpret_cast<const uint32_t*>(c16 + o);
-                x[0] = lc_bf16_lo(v);
-                x[1] = lc_bf16_hi(v);
-            } else {
-                const float2 v = *reinterpret_cast<const float2*>(ix.center[0] + o);
-                x[0] = v.x;
-                x[1] = v.y;
-            }
-        },
-        [&](const int* mem, int nm) { for (int t = tid; t < nm; t += NT) tok += ix.ntok[0][cb + mem[t]]; }, sum);
+    const LcMembers<NODES> m(ix, b, bh, l);
+    int tok = 0, chunks = 0;
+    Acc sum[8];
+    lc_member_sum<NT, Acc>(
+        [&](int j) { return m.label[j]; }, m.n, u, sh, [&](int j, int col, float (&x)[COLS]) { return m.row(j, col, x); },
+        [&](const int* mem, int nm) {
+            for (int t = tid; t < nm; t += NT) { tok += m.ntok[mem[t]]; chunks += m.chunks(mem[t]); }
+        }, sum);
     tok = lc_wave_scan_incl(tok);
-    if ((tid & 63) == 63) tok_sh[tid >> 6] = tok;
+    chunks = lc_wave_scan_incl(chunks);
+    if ((tid & 63) == 63) { tok_sh[tid >> 6] = tok; chunk_sh[tid >> 6] = chunks; }
     __syncthreads();
     if (tid < 16) {
-        int n_tok = 0;
-        for (int v = 0; v < NT / 64; ++v) n_tok += tok_sh[v];
-        lc_write_node(ix, b, bh, l, u, n, n_tok, sum, w);
+        int n_tok = 0, n_chunks = 0;
+        for (int v = 0; v < NT / 64; ++v) { n_tok += tok_sh[v]; n_chunks += chunk_sh[v]; }
+        lc_write_node(ix, b, bh, l, u, n_chunks, n_tok, sum, w);
     }
 }
 
@@ -1678,12 +1724,17 @@ int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const i
             LC_HIP_CHECK(hipGetLastError());
         }
         const LcNodeArgs w{cur.cent, cur.cent_cap, geometry, next};
-        if (max_M <= (long long)maxK * LC_UPD_FEW)
-            hipLaunchKernelGGL(lc_center_few_kernel, per_grid, dim3(LC_BT), 0, stream, ix, l, w, per);
-        else if (max_M <= (long long)maxK * LC_CENTER_WIDE)
-            hipLaunchKernelGGL(lc_center_kernel<256>, dim3(maxK, H, B), dim3(256), 0, stream, ix, l, w);
-        else
-            hipLaunchKernelGGL(lc_center_kernel<1024>, dim3(maxK, H, B), dim3(1024), 0, stream, ix, l, w);
+        auto center = [&](auto nodes) {
+            constexpr bool NODES = decltype(nodes)::value;
+            if (maxN <= (long long)maxK * LC_UPD_FEW)
+                hipLaunchKernelGGL(lc_center_few_kernel<NODES>, per_grid, dim3(LC_BT), 0, stream, ix, l, w, per);
+            else if (maxN <= (long long)maxK * LC_CENTER_WIDE)
+                hipLaunchKernelGGL((lc_center_kernel<256, NODES>), dim3(maxK, H, B), dim3(256), 0, stream, ix, l, w);
+            else
+                hipLaunchKernelGGL((lc_center_kernel<1024, NODES>), dim3(maxK, H, B), dim3(1024), 0, stream, ix, l, w);
+        };
+        if (l == 0) center(std::false_type());
+        else center(std::true_type());
         LC_HIP_CHECK(hipGetLastError());
         cur = next;
     }
