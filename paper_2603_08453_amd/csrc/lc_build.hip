@@ -496,9 +496,10 @@ __device__ __forceinline__ void lc_assign_take(int* n, int* list, int c) {
 }
 
 // From the candidates of this workgroup's points (the first is w0, wavefront's first p0) to their labels; all
-// threads call.  P, C: float32 rows of the points and centroids; lab: the labels, old_label this lane's.
+// threads call.  P, C: float32 rows of the points and centroids; lab: the labels, old_label this lane's.  Returns the label of
+// this lane's point, -1 without one; every wavefront is past its last use of the centroid rows then.
 template <int WP, int NW>
-__device__ __forceinline__ void lc_assign_finish(LcAssignSh<WP, NW>& sh, const float* P, const float* C, int N, int k, int w0,
+__device__ __forceinline__ int lc_assign_finish(LcAssignSh<WP, NW>& sh, const float* P, const float* C, int N, int k, int w0,
                                                  int p0, int* lab, int old_label, int* flag) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int j = lane & 15, kk = lane >> 4;
@@ -597,7 +598,17 @@ __device__ __forceinline__ void lc_assign_finish(LcAssignSh<WP, NW>& sh, const f
         if (flag && old_label != ba) *flag = 1;                     // (every writer stores the same value)
         lab[p0 + lane] = ba;
     }
+    return mine ? ba : -1;
 }
+
+// Which points belong to a cluster, as bits: word [block][cluster] of a (sequence, head) has bit i set if point 64 * block + i
+// carries that label.  The assignment of up to LC_AS_RES centroids leaves them, so that the update of a cluster reads a word per 64
+// points instead of every label, and knows from the words of the iteration before whether it has anything to do.
+struct LcMemberBits {
+    unsigned long long* w[2];        // by parity of the iteration; null: not kept
+    long long stride[2];             // words of a (sequence, head)
+    int pitch;                       // words of a block
+};
 
 // Up to 16 NBLK centroids: all of them in LDS, a wavefront's similarities all in registers.  NW
 // wavefronts of 16 points each share the staged rows.  A chain of four memory round trips (counts, rows,
@@ -607,7 +618,7 @@ __device__ __forceinline__ void lc_assign_finish(LcAssignSh<WP, NW>& sh, const f
 template <int NBLK, int NW>
 __global__ void __launch_bounds__(64 * NW, NBLK == 16 ? 2 : NW / 2)
 lc_kmeans_assign_res_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16, int pts_cap, const float* cent,
-                            const uint16_t* cent16, int cent_cap, int it, int* flags_all) {
+                            const uint16_t* cent16, int cent_cap, int it, int* flags_all, LcMemberBits bits) {
     lc_fetch_args<sizeof(LcDev) + 40>();
     constexpr int PIECES = NBLK * 256 / (64 * NW);                  // 16-byte pieces of the rows per thread
     __shared__ __attribute__((aligned(16))) unsigned char rows[16 * NBLK * LC_AS_PITCH];
@@ -684,8 +695,24 @@ lc_kmeans_assign_res_kernel(LcDev ix, int l, const float* pts, const uint16_t* p
         }
     }
     lc_wave_sync();
-    lc_assign_finish<16, NW>(sh, pts + (size_t)bh * pts_cap * LC_D, cent + (size_t)bh * cent_cap * LC_D, N, k, w0, p0, lab,
-                             old_label, flags ? flags + it : nullptr);
+    const int label = lc_assign_finish<16, NW>(sh, pts + (size_t)bh * pts_cap * LC_D, cent + (size_t)bh * cent_cap * LC_D, N, k,
+                                               w0, p0, lab, old_label, flags ? flags + it : nullptr);
+    // the members' bits of this workgroup's blocks of 64 points, collected where the centroid rows were
+    unsigned long long* const mb = bits.w[it & 1];
+    if (mb == nullptr) return;
+    constexpr int BLOCKS = NW / 4;
+    unsigned* const half = reinterpret_cast<unsigned*>(rows);
+    static_assert(BLOCKS * 16 * NBLK * 8 <= (int)sizeof(rows), "bits in the place of the rows");
+    for (int i = tid; i < BLOCKS * k * 2; i += 64 * NW) half[i] = 0u;
+    lc_barrier_lds();
+    const int at = 16 * wave + lane;                                // this lane's point, from the workgroup's first
+    if (label >= 0) atomicOr(&half[2 * ((at >> 6) * k + label) + ((at >> 5) & 1)], 1u << (at & 31));
+    lc_barrier_lds();
+    unsigned long long* const o = mb + bh * bits.stride[it & 1] + (size_t)(w0 >> 6) * bits.pitch;
+    for (int i = tid; i < BLOCKS * k; i += 64 * NW) {
+        const int blk = BLOCKS == 1 ? 0 : i / k, c = i - blk * k;
+        if (w0 + 64 * blk < N) o[(size_t)blk * bits.pitch + c] = reinterpret_cast<const unsigned long long*>(rows)[i];
+    }
 }
 
 // More centroids: tiles of LC_AS_TILE of them pass through LDS (the next tile's rows are fetched while the
@@ -1164,6 +1191,25 @@ struct LcSumSh {
     int mem[LC_MEM_WIN];
     int cnt[2 * 64 + 1];
 };
+// The partial sums `acc` (number `part`, columns from `col` on) added up in turn, a column per thread; threads < 16 get eight columns each.
+template <int NT, typename Acc, int COLS>
+__device__ __forceinline__ void lc_sum_partials(LcSumSh<NT, Acc>& s, int col, int part, const Acc (&acc)[COLS], Acc (&sum)[8]) {
+    const int tid = threadIdx.x;
+#pragma unroll
+    for (int q = 0; q < COLS; ++q) s.part[part][col + q] = acc[q];
+    __syncthreads();
+    if (tid < LC_D) {
+        Acc a = 0;
+#pragma unroll
+        for (int g = 0; g < LC_BG; ++g) a += s.part[g][tid];
+        s.part[0][tid] = a;                                         // (this thread's column alone)
+    }
+    __syncthreads();
+    if (tid < 16) {
+#pragma unroll
+        for (int t = 0; t < 8; ++t) sum[t] = s.part[0][8 * tid + t];
+    }
+}
 template <int NT, typename Acc, typename LabF, typename RowF, typename VisitF>
 __device__ __forceinline__ int lc_member_sum(LabF lab, int N, int u, LcSumSh<NT, Acc>& s, RowF row, VisitF visit, Acc (&sum)[8]) {
     constexpr int COLS = 8 * 256 / NT;                              // columns per lane
@@ -1199,17 +1245,7 @@ __device__ __forceinline__ int lc_member_sum(LabF lab, int N, int u, LcSumSh<NT,
         n += nm;
         if (base + LC_MEM_WIN < N) lc_barrier_lds();                // the list is rewritten by the next window
     }
-#pragma unroll
-    for (int q = 0; q < COLS; ++q) s.part[part][col + q] = acc[q];
-    __syncthreads();
-    if (tid < 16) {
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            Acc a = 0;
-            for (int g = 0; g < LC_BG; ++g) a += s.part[g][8 * sub + t];
-            sum[t] = a;
-        }
-    }
+    lc_sum_partials(s, col, part, acc, sum);
     return n;
 }
 
@@ -1247,6 +1283,63 @@ lc_kmeans_update_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* c
     lc_member_sum<LC_BT, float>([&](int i) { return labels[i]; }, N, c, sh,
                                 [&](int i, int col, float (&x)[8]) { lc_load8(P + (size_t)i * LC_D + col, x); return 1; },
                                 [](const int*, int) {}, sum);
+    if (threadIdx.x < 16)
+        lc_write_centroid(cent, cent16, ((size_t)bh * cent_cap + c) * LC_D + 8 * threadIdx.x, sum);
+}
+// The same from the members' bits (LcMemberBits): a window's list is a scan over 64 words, and a cluster whose words are those of
+// the iteration before keeps its centroid (the sum would be the same one).  Same members in the same order: same bits as above.
+// What bounds it is three round trips, counts, words and rows.  8 heads, 2275 points in 143 clusters: 7.7 us from the labels, now
+// 4.5; 5461 points in 249: 23.3 and 9.2.
+__global__ void __launch_bounds__(LC_BT)
+lc_kmeans_update_bits_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* cent, uint16_t* cent16, int cent_cap, int it,
+                             int* flags_all, LcMemberBits bits) {
+    lc_fetch_args<sizeof(LcDev) + 40 + sizeof(LcMemberBits)>();
+    __shared__ __attribute__((aligned(16))) LcSumSh<LC_BT, float> sh;
+    const int c = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+    const int bh = b * ix.H + h;
+    const int* const flags = flags_all ? lc_level_flags(ix, flags_all, l, bh) : nullptr;
+    const int N = lc_level_count(ix, b, bh, l), k = ix.nlev[b * LC_MAX_LEVELS + l + 1];
+    if (flags && it >= 1 && flags[it] == 0) return;                 // no point moved: the centroids stand
+    if (c >= k) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, sub = threadIdx.x & 15, part = threadIdx.x >> 4;
+    const int blocks = (N + 63) >> 6;
+    const unsigned long long* const now = bits.w[it & 1] + bh * bits.stride[it & 1] + c;
+    const unsigned long long* const old = bits.w[~it & 1] + bh * bits.stride[~it & 1] + c;
+    auto word = [&](const unsigned long long* w, int blk) { return blk < blocks ? w[(size_t)blk * bits.pitch] : 0ull; };
+    unsigned long long m = word(now, lane);                         // (every wavefront reads them: none waits for another's verdict)
+    if (it >= 1) {
+        bool moved = m != word(old, lane);
+        for (int w0 = 64; w0 < blocks; w0 += 64) moved = moved || word(now, w0 + lane) != word(old, w0 + lane);
+        if (__ballot(moved) == 0ull) return;
+    }
+    const float* P = pts + (size_t)bh * pts_cap * LC_D;
+    constexpr int BATCH = 4;
+    float acc[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) acc[t] = 0.f;
+    for (int w0 = 0; w0 < blocks; w0 += 64) {                       // windows of 64 blocks: LC_MEM_WIN points
+        static_assert(LC_MEM_WIN == 64 * 64, "a word per lane");
+        const int n = __popcll(m), inc = lc_wave_scan_incl(n);
+        const int nm = lc_readlane(inc, 63);
+        if (wave == 0)
+            for (int at = inc - n; m != 0ull; m &= m - 1ull) sh.mem[at++] = 64 * (w0 + lane) + __ffsll((long long)m) - 1;
+        if (w0 + 64 < blocks) m = word(now, w0 + 64 + lane);
+        lc_barrier_lds();
+        for (int t = part; t < nm; t += BATCH * LC_BG) {
+            float x[BATCH][8];
+#pragma unroll
+            for (int e = 0; e < BATCH; ++e) {
+                const int at = min(t + e * LC_BG, nm - 1);
+                lc_load8(P + (size_t)sh.mem[at] * LC_D + 8 * sub, x[e]);
+            }
+#pragma unroll
+            for (int e = 0; e < BATCH; ++e)
+                if (t + e * LC_BG < nm) lc_add_row(acc, x[e], 1);
+        }
+        if (w0 + 64 < blocks) lc_barrier_lds();                     // the list is rewritten by the next window
+    }
+    float sum[8];
+    lc_sum_partials(sh, 8 * sub, part, acc, sum);
     if (threadIdx.x < 16)
         lc_write_centroid(cent, cent16, ((size_t)bh * cent_cap + c) * LC_D + 8 * threadIdx.x, sum);
 }
@@ -1694,22 +1787,35 @@ int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const i
             // hardly at 8 and 10 (29.6 instead of 31.2, 31.3 instead of 33.5; 4200 x 16: 18.4 instead of 17.4) and at no other
             // number (2, 4, 6, 16: 24.1, 25.9, 27.5, 50 us).
             const bool wide = (maxN + 63) / 64 * BH > 512;
-            auto assign = [&](auto kernel, int points, int threads, int it) {
+            auto assign = [&](auto kernel, int points, int threads, int it, auto... more) {
                 hipLaunchKernelGGL(kernel, dim3((maxN + points - 1) / points, H, B), dim3(threads), 0, stream, ix, l,
                                    (const float*)cur.pts, (const uint16_t*)cur.pts16, cur.cap, (const float*)cur.cent,
-                                   (const uint16_t*)cur.cent16, cur.cent_cap, it, kflags);
+                                   (const uint16_t*)cur.cent16, cur.cent_cap, it, kflags, more...);
             };
+            // Members' bits, for clusters that are updated one by one from up to LC_AS_RES centroids: they take the place of the next
+            // level's points and centroids, which nothing has written yet, where both hold them (up to 4096 points always).
+            LcMemberBits bits{{nullptr, nullptr}, {0, 0}, maxK};
+            {
+                const bool even = (l & 1) == 0;
+                const long long need = ((long long)maxN + 63) / 64 * maxK * 8;
+                const long long room[2] = {(long long)(even ? ix.cap[1] : ix.cap[0]) * LC_D * 4, (long long)ix.cap[1] * LC_D * 4};
+                if (maxK <= LC_AS_RES && maxN > (long long)maxK * LC_UPD_FEW && need <= room[0] && need <= room[1])
+                    for (int i = 0; i < 2; ++i) {
+                        bits.w[i] = reinterpret_cast<unsigned long long*>(i == 1 ? ws.cent[even ? 1 : 0] : (even ? ws.next_pts : ws.dirs));
+                        bits.stride[i] = room[i] / 8;
+                    }
+            }
             for (int it = 0; it < iters; ++it) {
-                if (maxK <= 32) assign(&lc_kmeans_assign_res_kernel<2, 4>, 64, 256, it);
-                else if (maxK <= 64) assign(&lc_kmeans_assign_res_kernel<4, 4>, 64, 256, it);
-                else if (maxK <= 96) assign(&lc_kmeans_assign_res_kernel<6, 4>, 64, 256, it);
-                else if (maxK <= 128 && wide) assign(&lc_kmeans_assign_res_kernel<8, 8>, 128, 512, it);
-                else if (maxK <= 128) assign(&lc_kmeans_assign_res_kernel<8, 4>, 64, 256, it);
-                else if (maxK <= 160 && wide) assign(&lc_kmeans_assign_res_kernel<10, 8>, 128, 512, it);
-                else if (maxK <= 160) assign(&lc_kmeans_assign_res_kernel<10, 4>, 64, 256, it);
-                else if (maxK <= 192 && wide) assign(&lc_kmeans_assign_res_kernel<12, 8>, 128, 512, it);
-                else if (maxK <= 192) assign(&lc_kmeans_assign_res_kernel<12, 4>, 64, 256, it);
-                else if (maxK <= LC_AS_RES) assign(&lc_kmeans_assign_res_kernel<16, 4>, 64, 256, it);
+                if (maxK <= 32) assign(&lc_kmeans_assign_res_kernel<2, 4>, 64, 256, it, bits);
+                else if (maxK <= 64) assign(&lc_kmeans_assign_res_kernel<4, 4>, 64, 256, it, bits);
+                else if (maxK <= 96) assign(&lc_kmeans_assign_res_kernel<6, 4>, 64, 256, it, bits);
+                else if (maxK <= 128 && wide) assign(&lc_kmeans_assign_res_kernel<8, 8>, 128, 512, it, bits);
+                else if (maxK <= 128) assign(&lc_kmeans_assign_res_kernel<8, 4>, 64, 256, it, bits);
+                else if (maxK <= 160 && wide) assign(&lc_kmeans_assign_res_kernel<10, 8>, 128, 512, it, bits);
+                else if (maxK <= 160) assign(&lc_kmeans_assign_res_kernel<10, 4>, 64, 256, it, bits);
+                else if (maxK <= 192 && wide) assign(&lc_kmeans_assign_res_kernel<12, 8>, 128, 512, it, bits);
+                else if (maxK <= 192) assign(&lc_kmeans_assign_res_kernel<12, 4>, 64, 256, it, bits);
+                else if (maxK <= LC_AS_RES) assign(&lc_kmeans_assign_res_kernel<16, 4>, 64, 256, it, bits);
                 else if (ma == 4) assign(&lc_kmeans_assign_kernel<4>, 256, LC_BT, it);
                 else if (ma == 3) assign(&lc_kmeans_assign_kernel<3>, 192, LC_BT, it);
                 else if (ma == 2) assign(&lc_kmeans_assign_kernel<2>, 128, LC_BT, it);
@@ -1717,6 +1823,9 @@ int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const i
                 if (maxN <= (long long)maxK * LC_UPD_FEW)
                     hipLaunchKernelGGL(lc_kmeans_update_few_kernel, per_grid, dim3(LC_BT), 0, stream, ix, l,
                                        (const float*)cur.pts, cur.cap, cur.cent, cur.cent16, cur.cent_cap, it, per, kflags);
+                else if (bits.w[0])
+                    hipLaunchKernelGGL(lc_kmeans_update_bits_kernel, dim3(maxK, H, B), dim3(LC_BT), 0, stream, ix, l,
+                                       (const float*)cur.pts, cur.cap, cur.cent, cur.cent16, cur.cent_cap, it, kflags, bits);
                 else
                     hipLaunchKernelGGL(lc_kmeans_update_kernel, dim3(maxK, H, B), dim3(LC_BT), 0, stream, ix, l,
                                        (const float*)cur.pts, cur.cap, cur.cent, cur.cent16, cur.cent_cap, it, kflags);

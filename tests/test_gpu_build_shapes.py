@@ -7,7 +7,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-def build(H, chunks, F, iters, levels=2, seed=0, same=0, centers=0, spread=1.0):
+def build(H, chunks, F, iters, levels=2, seed=0, same=0, centers=0, spread=1.0, **config):
     """GPU build over `chunks` (chunks per sequence) of 1 to 3 tokens; the first `same` chunks have identical keys."""
     import torch
     from paper_2603_08453_amd import binding as lc
@@ -24,7 +24,7 @@ def build(H, chunks, F, iters, levels=2, seed=0, same=0, centers=0, spread=1.0):
         if same:
             K[b, :, : bd[min(same, len(bd) - 1)]] = K[b, :, :1].clone()
     cfg = lc.lc_config_default(levels=levels, fanout=F, kmeans_iters=iters, max_chunks=max(chunks), max_tokens=T,
-                               center_dtype=centers)
+                               center_dtype=centers, **config)
     ib = torch.zeros(lc.lc_index_bytes(cfg, len(chunks), H), dtype=torch.uint8, device="cuda")
     ws = torch.full((lc.lc_workspace_bytes(cfg, len(chunks), H, H),), 0xA5, dtype=torch.uint8, device="cuda")
     idx = lc.lc_build_index(cfg, K, [int(b[-1]) for b in bounds], bounds, ib, ws)
@@ -90,6 +90,32 @@ def test_first_two_iterations(H, chunks, F):
             cent[some] = unit(total[some])
             check_labels(s2["heads"][h][0]["parent"], x, cent)
             check_tree(s2["heads"][h])
+
+
+@pytest.mark.parametrize("iters", [2, 4, 8])
+@pytest.mark.parametrize("H,chunks,F,level,config", [
+    (1, [225], 15, 0, {}), (2, [640, 256, 64], 10, 0, {}), (2, [1281, 1279], 9, 0, {}), (8, [2275], 16, 0, {}), (1, [4096], 17, 0, {}),
+    (8, [2100, 1000], 17, 0, {}), (2, [10000, 300], 2, 1, {"levels": 3, "fanouts": [0, 2, 25]}),
+    (1, [8320], 2, 1, {"levels": 3, "fanouts": [0, 2, 17]})])
+def test_an_iteration_follows_from_the_one_before(H, chunks, F, level, config, iters):
+    """Clusters that are updated one by one from their members' bits, those without a change left alone: up to one window of 4096
+    points and beyond, blocks of 64 points with a remainder, batches of unequal sequences."""
+    before, after = build(H, chunks, F, iters, **config), build(H, chunks, F, iters + 1, **config)
+    for s1, s2 in zip(before, after):
+        for h in (0, H - 1):
+            here1, here2 = s1["heads"][h], s2["heads"][h]
+            if level and not np.array_equal(here1[0]["parent"], here2[0]["parent"]):
+                continue                                    # (the level below is not at rest yet: other points)
+            x = unit(here1[level]["center"].astype(np.float64))
+            k = len(here1[level + 1]["radius"])
+            lab = here1[level]["parent"]
+            n = np.bincount(lab, minlength=k)
+            if len(x) <= k or not n.all():
+                continue
+            total = np.zeros((k, 128))
+            np.add.at(total, lab, x)
+            check_labels(here2[level]["parent"], x, unit(total))
+            check_tree(here2)
 
 
 @pytest.mark.parametrize("H,chunks,F,levels,centers,spread", [
