@@ -1291,6 +1291,7 @@ __device__ __forceinline__ void lc_write_centroid(float* cent, uint16_t* cent16,
 // One workgroup per cluster: for clusters of more than LC_UPD_FEW points on average (their rows are then
 // the larger part of what a workgroup reads, and 16 groups fetch them at once).
 #define LC_UPD_FEW 8
+#define LC_UPD_FEW_MANY 20        // (with thousands of clusters)
 __global__ void __launch_bounds__(LC_BT)
 lc_kmeans_update_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* cent, uint16_t* cent16, int cent_cap, int it,
                         int* flags_all) {
@@ -1784,6 +1785,10 @@ int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const i
             maxN = idx->N[b * LC_MAX_LEVELS + l] > maxN ? idx->N[b * LC_MAX_LEVELS + l] : maxN;
             maxK = idx->N[b * LC_MAX_LEVELS + l + 1] > maxK ? idx->N[b * LC_MAX_LEVELS + l + 1] : maxK;
         }
+        // Several clusters per workgroup where they are small, or where one each would be thousands of workgroups that all read every
+        // label (8 heads, 10.6 K points in 660 clusters, update and centers: 66 and 71 us one by one, 25 and 29 here; but 332 clusters of
+        // 32: 39 and 42, 43 and 49; 249 of 22: centers 27 and 29).
+        const bool few = maxN <= (long long)maxK * LC_UPD_FEW || (maxN <= (long long)maxK * LC_UPD_FEW_MANY && maxK * BH > 2048);
         // clusters per workgroup of the kernels that list several: one per 16-lane group, more of them where
         // that would be over a thousand workgroups that each read all the labels
         const int per = (maxK + LC_BG - 1) / LC_BG * BH > 1024 ? LC_UB_MAX : LC_BG;
@@ -1845,7 +1850,7 @@ int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const i
                 else if (ma == 3) assign(&lc_kmeans_assign_kernel<3>, 192, LC_BT, it);
                 else if (ma == 2) assign(&lc_kmeans_assign_kernel<2>, 128, LC_BT, it);
                 else assign(&lc_kmeans_assign_kernel<1>, 64, LC_BT, it);
-                if (maxN <= (long long)maxK * LC_UPD_FEW)
+                if (few && bits.w[0] == nullptr)
                     hipLaunchKernelGGL(lc_kmeans_update_few_kernel, per_grid, dim3(LC_BT), 0, stream, ix, l,
                                        (const float*)cur.pts, cur.cap, cur.cent, cur.cent16, cur.cent_cap, it, per, kflags);
                 else if (bits.w[0])
@@ -1860,7 +1865,7 @@ int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const i
         const LcNodeArgs w{cur.cent, cur.cent_cap, geometry, next};
         auto center = [&](auto nodes) {
             constexpr bool NODES = decltype(nodes)::value;
-            if (maxN <= (long long)maxK * LC_UPD_FEW)
+            if (few)
                 hipLaunchKernelGGL(lc_center_few_kernel<NODES>, per_grid, dim3(LC_BT), 0, stream, ix, l, w, per);
             else if (maxN <= (long long)maxK * LC_CENTER_WIDE)
                 hipLaunchKernelGGL((lc_center_kernel<256, NODES>), dim3(maxK, H, B), dim3(256), 0, stream, ix, l, w);
