@@ -440,15 +440,21 @@ __device__ __forceinline__ void lc_assign_block2(const float4 (&xa)[8], const fl
             if (d1[r] > best[r]) { best[r] = d1[r]; arg[r] = c1; }
     }
 }
-// merge the 16 columns of a row: larger similarity wins, equal ones go to the lower centroid id
+// merge the 16 columns of a row: larger similarity wins, equal ones go to the lower centroid id (the maximum first, then the lowest of
+// the ids that have it: ten instructions, where carrying both through every step took forty)
 __device__ __forceinline__ void lc_assign_merge(float& bv, int& ba) {
-    auto merge = [&](float ov, int oa) {
-        if (ov > bv || (ov == bv && oa < ba)) { bv = ov; ba = oa; }
-    };
-    merge(lc_dpp<0xB1>(bv), __builtin_amdgcn_update_dpp(0, ba, 0xB1, 0xF, 0xF, true));
-    merge(lc_dpp<0x4E>(bv), __builtin_amdgcn_update_dpp(0, ba, 0x4E, 0xF, 0xF, true));
-    merge(lc_dpp<0x141>(bv), __builtin_amdgcn_update_dpp(0, ba, 0x141, 0xF, 0xF, true));
-    merge(lc_dpp<0x140>(bv), __builtin_amdgcn_update_dpp(0, ba, 0x140, 0xF, 0xF, true));
+    float v = bv;
+    v = fmaxf(v, lc_dpp<0xB1>(v));
+    v = fmaxf(v, lc_dpp<0x4E>(v));
+    v = fmaxf(v, lc_dpp<0x141>(v));
+    v = fmaxf(v, lc_dpp<0x140>(v));
+    int id = bv == v ? ba : 0x7fffffff;
+    id = min(id, __builtin_amdgcn_update_dpp(0, id, 0xB1, 0xF, 0xF, true));
+    id = min(id, __builtin_amdgcn_update_dpp(0, id, 0x4E, 0xF, 0xF, true));
+    id = min(id, __builtin_amdgcn_update_dpp(0, id, 0x141, 0xF, 0xF, true));
+    id = min(id, __builtin_amdgcn_update_dpp(0, id, 0x140, 0xF, 0xF, true));
+    bv = v;
+    ba = id;
 }
 // Orders a wavefront's own LDS accesses (no other wavefront is involved).
 __device__ __forceinline__ void lc_wave_sync() {
@@ -1395,13 +1401,17 @@ lc_kmeans_update_few_kernel(LcDev ix, int l, const float* pts, int pts_cap, floa
 }
 
 // The whole clustering of a small level (up to LC_KS_MAX_N points into up to LC_KS_MAX_K clusters)
-// in one kernel, one workgroup per (sequence, head): centroids and labels live in LDS, the
-// iterations are separated by workgroup barriers instead of kernel boundaries.  Same steps as the
+// in one kernel, one workgroup per (sequence, head): points, centroids and labels live in LDS (a wavefront's 16 points in its
+// registers as well), the iterations are separated by workgroup barriers instead of kernel boundaries.  Same steps as the
 // three kernels above: strided start, assign (ties to the lower id), normalised member sums (members
 // added in ascending order; a cluster without members or with a zero sum keeps its centroid).
+// What bounds an iteration is a chain: 32 dependent matrix instructions, four barriers, and the longest cluster's members one after
+// the other, eight rows in flight.  143 points into 9 clusters, 8 heads: 33 us, now 27.6; 9 into 1: 7.5 and 6.5 (before: points read from LDS each
+// time, offsets by one wavefront between two barriers of their own, a group per cluster whatever their number).
 #define LC_KS_THREADS 1024        // a wavefront per 16 points, a 16-lane group per cluster
 #define LC_KS_MAX_N 224
 #define LC_KS_MAX_K 64
+static_assert(LC_KS_MAX_N <= 16 * (LC_KS_THREADS / 64) && LC_KS_MAX_K <= LC_KS_THREADS / 16, "one tile per wavefront, one cluster per group");
 static inline size_t lc_kmeans_small_lds(int N, int k) {
     return (size_t)((N > 0 ? N : 1) + ((k + 15) & ~15)) * LC_AS_ROW * sizeof(float);
 }
@@ -1411,8 +1421,9 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* ce
     lc_fetch_args<sizeof(LcDev) + 40>();
     extern __shared__ __attribute__((aligned(16))) float ks_dyn[];   // x_rows point rows, then the centroid rows
     __shared__ int lab[LC_KS_MAX_N];
-    __shared__ int moff[LC_KS_MAX_K + 1];
-    __shared__ unsigned short mem[LC_KS_MAX_N];
+    __shared__ int count[LC_KS_MAX_K];
+    __shared__ __attribute__((aligned(16))) unsigned short mem[LC_KS_MAX_N + 8 * LC_KS_MAX_K];     // a cluster's list begins at a multiple of 8
+    __shared__ __attribute__((aligned(16))) float sums[LC_KS_THREADS / 64][LC_D];
     __shared__ int changed[2];                    // labels changed in this iteration (one flag per parity of `it`)
     const int h = blockIdx.x, b = blockIdx.y;
     const int bh = b * ix.H + h;
@@ -1438,13 +1449,16 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* ce
         if (c < k) m = N > 0 ? X[(int)(((long long)c * N) / k) * LC_AS_ROW + t] : (t == 0 ? 1.f : 0.f);
         cs[c * LC_AS_ROW + t] = m;
     }
+    const int i0 = 16 * wave;                                       // this wavefront's points
+    float4 xa[8];
+    if (i0 < N) {
+        const float* row = X + min(i0 + j, N - 1) * LC_AS_ROW + 4 * kk;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) xa[t] = *reinterpret_cast<const float4*>(row + 16 * t);
+    }
     __syncthreads();
     for (int it = 0; it < iters; ++it) {
-        for (int i0 = 16 * wave; i0 < N; i0 += 16 * (LC_KS_THREADS / 64)) {
-            float4 xa[8];
-            const float* row = X + min(i0 + j, N - 1) * LC_AS_ROW + 4 * kk;
-#pragma unroll
-            for (int t = 0; t < 8; ++t) xa[t] = *reinterpret_cast<const float4*>(row + 16 * t);
+        if (i0 < N) {
             float best[4];
             int arg[4];
 #pragma unroll
@@ -1470,55 +1484,79 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* ce
         // centroids from the same members and every later iteration would repeat it, so the
         // remaining iterations are skipped (the first iteration always runs its update).
         if (it > 0 && changed[it & 1] == 0) break;
-        // members of every cluster, ascending, as one list ordered by cluster: counts, offsets, ids
+        // members of every cluster, ascending, as one list ordered by cluster: counts, then every wavefront works out the places
         for (int c = wave; c < k; c += LC_KS_THREADS / 64) {
             int n = 0;
             for (int r = 0; r < rounds; ++r) {
                 const int i = lane + 64 * r;
                 n += __popcll(__ballot(i < N && lab[i] == c));
             }
-            if (lane == 0) moff[c + 1] = n;
-        }
-        if (tid == 0) moff[0] = 0;
-        __syncthreads();
-        if (wave == 0) {
-            int v = lane < k ? moff[lane + 1] : 0;
-            v = lc_wave_scan_incl(v);
-            if (lane < k) moff[lane + 1] = v;
+            if (lane == 0) count[c] = n;
         }
         __syncthreads();
+        const int n_c = lane < k ? count[lane] : 0, room = (n_c + 7) & ~7;
+        const int first = lc_wave_scan_incl(room) - room;           // lane c: where cluster c's list begins
         for (int c = wave; c < k; c += LC_KS_THREADS / 64) {
-            int at = moff[c];
+            int at = lc_readlane(first, c);
             for (int r = 0; r < rounds; ++r) {
                 const int i = lane + 64 * r;
                 const bool in = i < N && lab[i] == c;
                 const unsigned long long m = __ballot(in);
-                if (in) mem[at + __popcll(m & ((1ull << lane) - 1ull))] = (unsigned short)i;
+                if (in) mem[at + lc_mbcnt(m)] = (unsigned short)i;
                 at += __popcll(m);
             }
         }
         __syncthreads();
-        for (int c = grp; c < k; c += LC_KS_THREADS / 16) {
+        {
+            // up to 16 clusters: a wavefront each, two columns per lane; beyond that a 16-lane group each, eight columns per lane
+            const bool wide = k <= LC_KS_THREADS / 64;
+            const int c = wide ? wave : grp;                        // (clusters past the last have no members)
+            const int n = __shfl(n_c, min(c, 63)), at = __shfl(first, min(c, 63));
             float sum[8];
+            auto add_rows = [&](auto cols, int col) LC_INLINE {
+                constexpr int C = decltype(cols)::value;
 #pragma unroll
-            for (int t = 0; t < 8; ++t) sum[t] = 0.f;
-            const int j1 = moff[c + 1];
-#pragma unroll 4
-            for (int jm = moff[c]; jm < j1; ++jm) {
-                float x[8];
-                lc_load8(X + (int)mem[jm] * LC_AS_ROW + 8 * sub, x);
+                for (int t = 0; t < 8; ++t) sum[t] = 0.f;
+                for (int q = 0; q < n; q += 8) {
+                    const uint4 id = *reinterpret_cast<const uint4*>(mem + at + q);
+                    const uint32_t w[4] = {id.x, id.y, id.z, id.w};
+                    float x[8][C];
 #pragma unroll
-                for (int t = 0; t < 8; ++t) sum[t] += x[t];
+                    for (int e = 0; e < 8; ++e) {                   // (past the end: the batch's first row again)
+                        const int i = q + e < n ? (int)((w[e / 2] >> (16 * (e & 1))) & 0xffffu) : (int)(w[0] & 0xffffu);
+                        if constexpr (C == 8) {
+                            lc_load8(X + i * LC_AS_ROW + col, x[e]);
+                        } else {
+                            const float2 v = *reinterpret_cast<const float2*>(X + i * LC_AS_ROW + col);
+                            x[e][0] = v.x;
+                            x[e][1] = v.y;
+                        }
+                    }
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        if (q + e < n) {
+#pragma unroll
+                            for (int t = 0; t < C; ++t) sum[t] += x[e][t];
+                        }
+                }
+            };
+            if (wide) {
+                add_rows(std::integral_constant<int, 2>(), 2 * lane);
+                *reinterpret_cast<float2*>(sums[wave] + 2 * lane) = make_float2(sum[0], sum[1]);
+                lc_wave_sync();
+                lc_load8(sums[wave] + 8 * sub, sum);                // (every group the same)
+            } else {
+                add_rows(std::integral_constant<int, 8>(), 8 * sub);
             }
             float n2 = 0.f;
 #pragma unroll
             for (int t = 0; t < 8; ++t) n2 = fmaf(sum[t], sum[t], n2);
             n2 = lc_sum16(n2);
-            if (n2 > 0.f) {
+            if (n > 0 && n2 > 0.f) {
                 const float inv = 1.0f / sqrtf(n2);
 #pragma unroll
                 for (int t = 0; t < 8; ++t) sum[t] *= inv;
-                lc_store8(cs + c * LC_AS_ROW + 8 * sub, sum);
+                if (!wide || lane < 16) lc_store8(cs + c * LC_AS_ROW + 8 * sub, sum);
             }
         }
         __syncthreads();

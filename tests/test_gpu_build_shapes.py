@@ -95,12 +95,13 @@ def test_first_two_iterations(H, chunks, F):
 
 @pytest.mark.parametrize("iters", [2, 4, 8])
 @pytest.mark.parametrize("H,chunks,F,level,config", [
-    (1, [225], 15, 0, {}), (2, [640, 256, 64], 10, 0, {}), (2, [1281, 1279], 9, 0, {}), (8, [2275], 16, 0, {}), (1, [4096], 17, 0, {}),
+    (2, [143, 16, 9], 16, 0, {}), (2, [224, 65, 8], 14, 0, {}), (2, [224, 33, 7], 4, 0, {}), (1, [200], 12, 0, {}), (1, [225], 15, 0, {}), (2, [640, 256, 64], 10, 0, {}), (2, [1281, 1279], 9, 0, {}), (8, [2275], 16, 0, {}), (1, [4096], 17, 0, {}),
     (8, [2100, 1000], 17, 0, {}), (2, [10000, 300], 2, 1, {"levels": 3, "fanouts": [0, 2, 25]}),
     (1, [8320], 2, 1, {"levels": 3, "fanouts": [0, 2, 17]})])
 def test_an_iteration_follows_from_the_one_before(H, chunks, F, level, config, iters):
-    """Clusters that are updated one by one from their members' bits, those without a change left alone: up to one window of 4096
-    points and beyond, blocks of 64 points with a remainder, batches of unequal sequences."""
+    """Small clusterings in one kernel, up to 16 clusters and beyond; and clusters that are updated one by one from their members'
+    bits, those without a change left alone: up to one window of 4096 points and beyond, blocks of 64 points with a
+    remainder, batches of unequal sequences."""
     before, after = build(H, chunks, F, iters, **config), build(H, chunks, F, iters + 1, **config)
     for s1, s2 in zip(before, after):
         for h in (0, H - 1):
