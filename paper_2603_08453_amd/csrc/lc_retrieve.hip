@@ -11,12 +11,16 @@
 // retrieval -- per level score the candidates, keep the beam[l] best, gather their children; at
 // the chunk level cut by the token budget and write the ids.
 //
-// lc_leaf_kernel (lc_retrieve, and the decode step beyond what its selecting workgroups hold):
-// many workgroups per (sequence, KV head) score the wanted chunks; the last workgroup to finish
-// for a (sequence, head) pulls the keys into LDS, runs the weighted histogram select (weights =
-// chunk lengths) and emits the ids in ascending order.
+// lc_score_kernel: one 16-byte entry (key, first token, length) per chunk, many workgroups per (sequence, KV head).  First kernel of
+// a decode step, whose attention workgroups select from the entries, and of lc_retrieve, whose
+// second kernel does:
 //
-// lc_score_kernel (first kernel of a decode step): the scoring half of lc_leaf_kernel alone.
+// lc_select_kernel: one workgroup per (sequence, KV head) selects from the entries and writes the ids (lc_retrieve, and the
+// decode step beyond what its selecting workgroups hold).
+//
+// lc_leaf_kernel (the same beyond what lc_select_kernel's registers hold): many workgroups per
+// (sequence, KV head) score the wanted chunks; the last workgroup to finish for a (sequence, head) pulls the keys into LDS, runs the weighted histogram select (weights =
+// chunk lengths) and emits the ids in ascending order.
 //
 // The kernels are latency-bound at batch 1, so global loads are issued in batches
 // and nothing reads global memory element by element inside a dependent loop.
@@ -1180,12 +1184,16 @@ lc_leaf_kernel(const LcRetrieveArgs a) {
 // launcher
 // ---------------------------------------------------------------------------------
 // ---------------------------------------------------------------------------------
-// lc_score_kernel: chunk scoring only (the decode step's second kernel selects by itself)
+// lc_score_kernel: chunk scoring only (the second kernel selects by itself)
 // ---------------------------------------------------------------------------------
 // The same scoring as lc_leaf_kernel without the selection behind it, so without its LDS and its
 // 1024-thread workgroups: NT threads = NT/16 groups, R chunks per group.
 #define LC_SC_THREADS 256
 #define LC_SCORE_MAX_WGS 1024          // measured flat between 512 and 2048 workgroups
+// Two chunks per group longer where the centers are float32: four of them are twice the registers of bfloat16 ones, one wavefront
+// less per SIMD (lc_retrieve on 8 heads of 10.9 K chunks at 2731 workgroups 17.1 us, at 1366 18.3; on 64 pairs of 910 at 1856 workgroups
+// 14.4 and 14.9, with bfloat16 centers 13.9 and 13.1; of 3276 at 6592 34.5 and 32.8).
+#define LC_SCORE_MAX_WGS_F32 4096
 // BF16: how the chunk-level centers are stored (a compile-time copy of the index's flag).
 template <int G, int R, bool BF16>
 __global__ void __launch_bounds__(LC_SC_THREADS)
@@ -1239,6 +1247,7 @@ lc_score_kernel(const LcRetrieveArgs a) {
             else sv = lc_score_chunk_frag<G>(lc_load_chunk_node(ix.center[0], c0b, cb + jj[r], sub), c0b, rv[r], qf, qn);
         }
         if (j < M && sub == 0) {                                // one 16-byte entry per chunk (LcChunkEntry)
+            if (a.scores) a.scores[cb + j] = sv;
             lc_v4i w;
             w.x = (int)lc_score_key(sv);
             w.y = st[r];
@@ -1249,6 +1258,212 @@ lc_score_kernel(const LcRetrieveArgs a) {
     }
 }
 
+
+// ---------------------------------------------------------------------------------
+// lc_select_kernel: the chunk list from the entries, one workgroup per (sequence, head)
+// ---------------------------------------------------------------------------------
+// The selection of lc_select_chunks for a caller that wants the ids: wavefront w owns chunks [64 EC w, 64 EC (w + 1)), lane l of it
+// (EC w + e) 64 + l, everything stays in registers -- a bit per chunk says whether it is selected -- and the ids go out by
+// one exchange of the wavefronts' counts.  What bounds it is one compute unit's instruction rate, some 20 instructions per chunk and lane,
+// and one cold round trip.  As a kernel of its own behind lc_score_kernel it costs a launch, and saves the arrival of all scoring
+// workgroups at one counter, keys staged in LDS and two passes over them: lc_retrieve on 8 heads of 10.9 K chunks 21.2 us as one
+// kernel (lc_leaf_kernel), 17.4 as two; of 2299 11.5 and 9.3; of 500 9.2 and 7.4.
+#define LC_SL_THREADS 1024
+#define LC_SL_CAND 64             // chunks of the cutoff bin that are ranked directly
+#define LC_SL_EC_MAX 12
+struct LcSelectArgs {
+    const int* entries;      // [B][H][cap0] LcChunkEntry
+    const int* state;
+    int32_t* ids;
+    int32_t* counts;
+    int cap0, cap, budget, sink;
+};
+template <int EC>
+__global__ void __launch_bounds__(LC_SL_THREADS)
+lc_select_kernel(const LcSelectArgs a) {
+    constexpr int NT = LC_SL_THREADS, NW = NT / 64;
+    constexpr int BITS = EC == 1 ? 8 : (EC == 2 ? 9 : 10);
+    constexpr int BINS = 1 << BITS;
+    extern __shared__ __attribute__((aligned(16))) int lds_dyn[];   // crowded cutoff bin: keys and lengths
+    __shared__ __attribute__((aligned(16))) int hist[BINS];
+    __shared__ int4 cand[LC_SL_CAND];
+    __shared__ uint32_t range[2 * NW];
+    __shared__ int number[NW], n_cand;
+    __shared__ LcLeafSelSh sel_sh;
+    const int bh = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const __amdgpu_buffer_rsrc_t ent_r = lc_buffer(a.entries + (size_t)bh * 4 * a.cap0, a.cap0 * 16);
+    const int j0 = wave * (EC * 64) + lane;                         // this lane's chunk e is j0 + 64 e
+    uint32_t ck[EC];
+    int len[EC], bin[EC];
+    {
+        lc_v4i ent[EC];
+#pragma unroll
+        for (int e = 0; e < EC; ++e) ent[e] = __builtin_amdgcn_raw_buffer_load_b128(ent_r, j0 * 16, e * 1024, 0);
+        for (int i = tid; i < BINS; i += NT) hist[i] = 0;
+        if (tid == 0) n_cand = 0;
+        const int M = a.state[bh * 4 + 1];
+#pragma unroll
+        for (int e = 0; e < EC; ++e) {
+            const bool in = j0 + 64 * e < M;
+            ck[e] = in ? (uint32_t)ent[e].x : 0u;
+            len[e] = ent[e].z;
+            bin[e] = in && ent[e].y < a.sink ? BINS : -1;           // pinned chunks: as if in a bin above all
+        }
+    }
+    const int W = a.budget > 0 ? a.budget : 0;
+    uint32_t kmin1 = 0xffffffffu, kmax = 0u;                        // (lowest candidate key) - 1, highest
+#pragma unroll
+    for (int e = 0; e < EC; ++e) { kmin1 = min(kmin1, ck[e] - 1u); kmax = max(kmax, ck[e]); }       // (key 0 wraps: ignored)
+    kmin1 = lc_wave_min_uniform(kmin1);
+    kmax = lc_wave_max_uniform(kmax);
+    if (lane == 0) { range[wave] = kmin1; range[NW + wave] = kmax; }
+    lc_barrier_lds();
+    static_assert(NW == 16, "a row of 16 lanes goes over the wavefronts' parts");
+    const uint32_t kmin = lc_wave_min_uniform(range[lane & 15]) + 1u;
+    kmax = lc_wave_max_uniform(range[NW + (lane & 15)]);
+    // ---- Histogram of chunk lengths over the upper half of the keys' range: the budget nearly always ends there, few chunks are in it (LDS
+    // atomics of all of them, most in the same few bins, are the longest step otherwise), and its bins are finer.  Over all of the
+    // range if the upper half fits the budget whole.
+    int fb = -1, remW = W;                                          // cutoff bin (-1: every candidate fits), budget left for it
+    uint32_t lo = kmax - (kmax - kmin) / 2u;
+    for (;;) {
+        const uint32_t span = kmax - lo;
+        const int bits = (kmax != 0u && span) ? 32 - __clz(span) : 0;
+        const int shift = bits > BITS ? bits - BITS : 0;            // (span >> shift) < BINS
+#pragma unroll
+        for (int e = 0; e < EC; ++e) {
+            const bool in = ck[e] >= lo && ck[e] != 0u;
+            const int b = (int)((ck[e] - lo) >> shift);
+            bin[e] = in ? b : (bin[e] == BINS ? BINS : -1);
+            if (in) atomicAdd(&hist[b], len[e]);
+        }
+        lc_barrier_lds();
+        // every wavefront scans all bins from the top: lane l holds bins BINS - 1 - PER l - i, i < PER
+        constexpr int PER = BINS / 64;
+        int pw[PER];
+        const int4* hw4 = reinterpret_cast<const int4*>(hist + BINS - PER * (lane + 1));
+#pragma unroll
+        for (int v = 0; v < PER / 4; ++v) {
+            const int4 x = hw4[PER / 4 - 1 - v];
+            pw[4 * v + 0] = x.w; pw[4 * v + 1] = x.z; pw[4 * v + 2] = x.y; pw[4 * v + 3] = x.x;
+        }
+#pragma unroll
+        for (int i = 1; i < PER; ++i) pw[i] += pw[i - 1];
+        const int cw = lc_wave_scan_incl(pw[PER - 1]) - pw[PER - 1];
+        int fit = 0, fitw = 0;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const bool ok = cw + pw[i] <= W;
+            fit += ok ? 1 : 0;
+            fitw = ok ? pw[i] : fitw;
+        }
+        const unsigned long long bal = __ballot(fit < PER);         // the prefix ends in the first bin that no longer fits
+        if (bal != 0ull) {
+            const int fl = __ffsll((long long)bal) - 1;
+            fb = BINS - 1 - (PER * fl + lc_readlane(fit, fl));
+            remW = W - (lc_readlane(cw, fl) + lc_readlane(fitw, fl));
+            break;
+        }
+        if (lo <= kmin) break;                                      // (kmin is 0 if there is no candidate)
+        lo = kmin;
+        lc_barrier_lds();                                           // the bins have been read
+        for (int i = tid; i < BINS; i += NT) hist[i] = 0;
+        lc_barrier_lds();
+    }
+    // ---- chunks above that bin are selected, those in it go to a list
+    unsigned sel = 0u;                                              // bit e: this lane's chunk e is selected
+    const int cutoff = fb >= 0 ? fb : -2;
+#pragma unroll
+    for (int e = 0; e < EC; ++e) {
+        sel |= bin[e] > fb ? 1u << e : 0u;
+        if (__ballot(bin[e] == cutoff) != 0ull) {                   // (uniform; few of the rows)
+            if (bin[e] == cutoff) {
+                const int at = atomicAdd(&n_cand, 1);
+                if (at < LC_SL_CAND) cand[at] = make_int4((int)ck[e], len[e], j0 + 64 * e, 0);
+            }
+        }
+    }
+    lc_barrier_lds();
+    const int nc = n_cand;
+    if (nc <= LC_SL_CAND) {
+        // ---- lane c ranks chunk c of it: length of the chunks before it (key descending, id ascending)
+        const int4 me = cand[min(lane, max(nc - 1, 0))];
+        int wb = 0;
+        for (int c = 0; c < nc; ++c) {                              // (uniform)
+            const uint32_t k = (uint32_t)lc_readlane(me.x, c);
+            const bool before = k > (uint32_t)me.x || (k == (uint32_t)me.x && lc_readlane(me.z, c) < me.z);
+            wb += before ? lc_readlane(me.y, c) : 0;
+        }
+        for (unsigned long long won = __ballot(lane < nc && wb + me.y <= remW); won != 0ull; won &= won - 1ull) {
+            const int id = lc_readlane(me.z, __ffsll((long long)won) - 1), e = (id >> 6) - wave * EC;
+            if (e >= 0 && e < EC) sel |= lane == (id & 63) ? 1u << e : 0u;       // (uniform but for the lane)
+        }
+    } else {
+        // ---- a crowded or tied cutoff bin: the general select routine on its chunks alone
+        uint32_t* const skey = reinterpret_cast<uint32_t*>(lds_dyn);
+        int* const slen = lds_dyn + EC * NT;
+        lc_leaf_select_prepare<NT>(sel_sh);
+        lc_barrier_lds();
+        uint32_t bmin = 0xffffffffu, bmax = 0u;
+#pragma unroll
+        for (int e = 0; e < EC; ++e) {
+            const uint32_t k = bin[e] == cutoff ? (ck[e] == 0xffffffffu ? 0xfffffffeu : ck[e]) : 0u;      // the mark is reserved
+            skey[j0 + 64 * e] = k;
+            slen[j0 + 64 * e] = len[e];
+            if (k != 0u) { bmin = min(bmin, k); bmax = max(bmax, k); }
+        }
+        lc_leaf_select_range(bmin, bmax, sel_sh);
+        lc_barrier_lds();
+        const uint32_t thr = lc_leaf_select<NT>(EC * NT, skey, slen, (long long)remW, 0x7fffffffLL, sel_sh);
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < EC; ++e) sel |= bin[e] == cutoff && skey[j0 + 64 * e] > thr ? 1u << e : 0u;
+    }
+    // ---- the ids, ascending
+    unsigned long long row[EC];
+    int total = 0;
+#pragma unroll
+    for (int e = 0; e < EC; ++e) {
+        row[e] = __ballot((sel >> e) & 1u);
+        total += __popcll(row[e]);
+    }
+    if (lane == 0) number[wave] = total;
+    lc_barrier_lds();
+    const int n = lane < NW ? number[lane] : 0, before = lc_wave_scan_incl(n) - n;
+    int at = lc_readlane(before, wave);
+    int32_t* const ids = a.ids + (size_t)bh * a.cap;
+#pragma unroll
+    for (int e = 0; e < EC; ++e) {
+        const int p = at + lc_mbcnt(row[e]);
+        if (((sel >> e) & 1u) && p < a.cap) ids[p] = j0 + 64 * e;
+        at += __popcll(row[e]);
+    }
+    if (tid == 0) a.counts[bh] = min(lc_readlane(before + n, NW - 1), a.cap);
+}
+template <int EC>
+static int launch_select_e(const LcSelectArgs& a, int pairs, hipStream_t stream) {
+    constexpr size_t lds = (size_t)EC * LC_SL_THREADS * 8;
+    if (lds > 16 * 1024) {                                          // static + dynamic beyond the default allowance: raised once per device
+        static LcOnce raised;
+        LC_HIP_CHECK(raised.run([&] {
+            return hipFuncSetAttribute(reinterpret_cast<const void*>(&lc_select_kernel<EC>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        }));
+    }
+    hipLaunchKernelGGL(lc_select_kernel<EC>, dim3(pairs), dim3(LC_SL_THREADS), lds, stream, a);
+    LC_HIP_CHECK(hipGetLastError());
+    return LC_OK;
+}
+static int launch_select(const LcRetrieveArgs& r, int max_M, hipStream_t stream) {
+    const LcSelectArgs a{r.scratch, r.ix.state, r.ids, r.counts, r.ix.cap[0], r.cap, r.budget, r.sink};
+    const int pairs = r.ix.B * r.ix.H, rows = (max_M + LC_SL_THREADS - 1) / LC_SL_THREADS;
+    if (rows <= 1) return launch_select_e<1>(a, pairs, stream);
+    if (rows <= 2) return launch_select_e<2>(a, pairs, stream);
+    if (rows <= 4) return launch_select_e<4>(a, pairs, stream);
+    if (rows <= 8) return launch_select_e<8>(a, pairs, stream);
+    return launch_select_e<LC_SL_EC_MAX>(a, pairs, stream);
+}
 
 template <int G, int R>
 static int launch_score(const LcRetrieveArgs& a, int max_M, hipStream_t stream) {
@@ -1297,13 +1512,21 @@ static int launch_retrieve_g(LcRetrieveArgs& a, int max_M, hipStream_t stream) {
         hipLaunchKernelGGL(lc_upper_kernel<G>, dim3(ix.H, ix.B), dim3(LC_UP_THREADS), lds, stream, a);
         LC_HIP_CHECK(hipGetLastError());
     }
-    if (a.score_only) {
+    // lc_retrieve: two kernels as far as the selecting one holds a (sequence, head)'s chunks in registers (measured there); only with seven
+    // or eight queries per KV head and some hundred thousand chunks in all was one kernel up to 3 % faster (64 pairs of 1820: 19.5 and 20.1 us;
+    // of 910 16.3 and 14.4, of 3276 40.9 and 32.8).
+    const bool two = !a.score_only && max_M > LC_FLAT_MAX_CHUNKS && max_M <= LC_SL_THREADS * LC_SL_EC_MAX;
+    if (a.score_only || two) {
         // chunks per group: enough work per workgroup without leaving compute units idle
         int rs = 1;
-        while (rs < 4 && (long long)((max_M + 16 * rs - 1) / (16 * rs)) * ix.H * ix.B > LC_SCORE_MAX_WGS) rs *= 2;
-        if (rs == 1) return launch_score<G, 1>(a, max_M, stream);
-        if (rs == 2) return launch_score<G, 2>(a, max_M, stream);
-        return launch_score<G, 4>(a, max_M, stream);
+        while (rs < 4) {
+            const long long wgs = (long long)((max_M + 16 * rs - 1) / (16 * rs)) * ix.H * ix.B;
+            if (wgs <= (rs == 2 && !ix.c0_bf16 ? LC_SCORE_MAX_WGS_F32 : LC_SCORE_MAX_WGS)) break;
+            rs *= 2;
+        }
+        const int rc = rs == 1 ? launch_score<G, 1>(a, max_M, stream)
+                               : (rs == 2 ? launch_score<G, 2>(a, max_M, stream) : launch_score<G, 4>(a, max_M, stream));
+        return rc != LC_OK || !two ? rc : launch_select(a, max_M, stream);
     }
     if (!a.walk && max_M <= LC_FLAT_MAX_CHUNKS) {        // one level, every chunk a candidate
         LcRetrieveArgs f = a;

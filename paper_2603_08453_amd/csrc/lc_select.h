@@ -1,9 +1,5 @@
 // Budget selection of one (sequence, head) from the chunk entries the scoring kernel left, by one workgroup.
-// Used by every workgroup of the select+attend kernel of a decode step.  (One 1024-thread workgroup per
-// (sequence, head) running it as a kernel of its own behind the scoring kernel was measured too: no faster
-// than the last scoring workgroup selecting from staged keys -- 12.5 against 11.4 us at 2.3 K chunks per
-// head, 26 against 22 us at 11 K: a single compute unit's instruction rate bounds both -- so lc_retrieve
-// keeps the one-kernel form.)
+// Used by every workgroup of the select+attend kernel of a decode step.  (lc_select_kernel does the same for the two separate calls.)
 #pragma once
 
 #include "lc_device.h"

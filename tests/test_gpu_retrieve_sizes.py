@@ -1,0 +1,56 @@
+"""lc_retrieve where its selection changes shape: chunk counts around the rows of its selecting kernel and its largest, budgets that
+end in the upper half of the keys' range, below it, nowhere, and inside large groups of equal scores."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def by_the_rule(scores, lens, starts, budget, sink):
+    """Pinned chunks, and the longest prefix of the others (score descending, id ascending) that fits the budget."""
+    pinned = starts < sink
+    rest = np.flatnonzero(~pinned)
+    order = rest[np.lexsort((rest, -scores[rest]))]
+    fits = np.cumsum(lens[order]) <= max(budget, 0)
+    return np.sort(np.concatenate([np.flatnonzero(pinned), order[: int(fits.sum())]]))
+
+
+@pytest.mark.parametrize("distinct", [0, 37])                   # 37: the chunks repeat 37 contents, so scores are equal by the hundreds
+@pytest.mark.parametrize("chunks", [65, 129, 1023, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193, 12287, 12288, 12289])
+def test_selection_follows_the_scores(chunks, distinct):
+    import torch
+    from paper_2603_08453_amd import binding as lc
+    B, H, G = 2, 2, 4
+    r = np.random.default_rng(chunks + distinct)
+    counts = [chunks, max(1, chunks // 3)]
+    kinds = r.integers(0, 37, size=chunks)
+    size = r.integers(1, 6, size=37)[kinds] if distinct else r.integers(1, 6, size=chunks)
+    bounds = [np.concatenate([[0], np.cumsum(size[:m])]).astype(np.int32) for m in counts]
+    lens = [int(b[-1]) + 2 for b in bounds]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(chunks)
+    K = torch.randn((B, H, max(lens), 128), generator=gen, device="cuda").to(torch.bfloat16)
+    if distinct:
+        content = torch.randn((37, 5, 128), generator=gen, device="cuda").to(torch.bfloat16)
+        kind = np.repeat(kinds, size)
+        at = np.concatenate([np.arange(n) for n in size])
+        K[:, :, : len(kind)] = content[torch.from_numpy(kind).cuda(), torch.from_numpy(at).cuda()]
+    q = torch.randn((B, H * G, 128), generator=gen, device="cuda").to(torch.bfloat16)
+    q[:, :G] *= 1.0 if chunks % 2 else 0.0                      # (no query: every score of head 0 is zero)
+    total = int(bounds[0][-1])
+    for sink, budget in ((0, 0), (3, 7), (0, total // 50 + 1), (total // 3, total // 9), (0, (9 * total) // 10), (0, total), (9, 10 ** 9)):
+        cfg = lc.lc_config_default(levels=2, fanout=32, kmeans_iters=1, max_chunks=chunks, max_tokens=max(lens), sink_tokens=sink, prune=0)
+        ib = torch.zeros(lc.lc_index_bytes(cfg, B, H), dtype=torch.uint8, device="cuda")
+        ws = torch.zeros(lc.lc_workspace_bytes(cfg, B, H * G, H), dtype=torch.uint8, device="cuda")
+        idx = lc.lc_build_index(cfg, K, lens, bounds, ib, ws)
+        cap = max(1, min(chunks, budget + sink))
+        ids = torch.full((B, H, cap), -7, dtype=torch.int32, device="cuda")
+        n = torch.full((B, H), -1, dtype=torch.int32, device="cuda")
+        scores = torch.full((B, H, chunks), float("nan"), device="cuda")
+        lc.lc_retrieve(idx, q, budget, ids, n, ws, scores=scores)
+        for b in range(B):
+            m = counts[b]
+            for h in range(H):
+                want = by_the_rule(scores[b, h, :m].cpu().numpy(), np.diff(bounds[b]), bounds[b][:-1], budget, sink)
+                assert int(n[b, h]) == len(want), (sink, budget, b, h)
+                assert np.array_equal(ids[b, h, : len(want)].cpu().numpy(), want), (sink, budget, b, h)
