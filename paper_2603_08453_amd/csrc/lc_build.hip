@@ -481,6 +481,7 @@ __device__ __forceinline__ void lc_wave_sync() {
 #define LC_AS_PITCH 272           // bytes per staged bfloat16 row (the pad spreads the 16 rows of a block over the banks)
 #define LC_AS_CAND 16             // candidates a point can hold (with 8, one point in 40 K had more: a tail of several times the kernel)
 #define LC_AS_REFRESH 256         // first iteration: centroids between two looks at what is known of the points (a power of two)
+#define LC_AS_SAMPLE 1024         // first iteration: centroids up to which the first sweep takes all of them (see lc_kmeans_assign_kernel)
 #define LC_AS_PAIRS 128           // pairs a wavefront compares at a time (and no fewer than its points)
 #define LC_AS_EPS 0.0040f         // 2^-8 (both operands' rounding, Cauchy-Schwarz) and room for the float32 sums
 typedef __bf16 lc_bf16x8_b __attribute__((ext_vector_type(8)));
@@ -726,13 +727,16 @@ lc_kmeans_assign_res_kernel(LcDev ix, int l, const float* pts, const uint16_t* p
 // current one is multiplied) under the 16 MA points per wavefront held in registers.  The threshold enters
 // as the matrix instruction's starting accumulator, so a candidate is a result >= 0, and a step of 32
 // centroids costs a maximum over its results and a branch that is rarely taken.  Later iterations start from the
-// similarity to the point's previous centroid (a float32 dot product).  The first one has no such centroid: a sweep over a quarter of them
-// -- 16 of every 64, so that every neighbourhood is in it -- gives a similarity that about three others exceed, and each candidate
-// found raises it, with effect from the next LC_AS_REFRESH centroids on.  Hits are read off the results' sign bits, and a
-// result that is not a number may have either: so a point of which no similarity compares is marked beforehand as one
+// similarity to the point's previous centroid (a float32 dot product).  The first one has no such centroid.  Up to LC_AS_SAMPLE
+// centroids, a sweep over all of them finds the largest similarity; of more, a sweep over a quarter -- 16 of every 64, so that
+// every neighbourhood is in it -- gives one that about three others exceed, and each candidate found raises it, with effect from the next
+// LC_AS_REFRESH centroids on.  (The more candidates cost a fixed time per point, the shorter sweep saves one by the centroid.  Clusterings
+// of 8 heads with the quarter and with all: 5.8 K points x 361 centroids 480 and 452 us, 10.9 K x 682 741 and 707,
+// x 1365 492 and 488 -- of 2 heads 322 and 325 --, x 2730 513 and 514 -- 299 and 308 --, x 5461 516 and 574.)  Hits are read off
+// the results' sign bits, and a result that is not a number may have either: so a point of which no similarity compares is marked beforehand as one
 // with too many candidates (float32 decides: cluster 0), and what a centroid of that kind adds to the other points'
 // candidates falls away in the float32 comparison, where their nearest one always is a candidate too.
-// Measured, 8 heads of 10.9 K points x 5461 centroids (122 GFLOP a sweep): first iteration 251 us, the second
+// Measured, 8 heads of 10.9 K points x 5461 centroids (122 GFLOP a sweep): first iteration 218 us, the second
 // 149 us; the three iterations of such a clustering took 2.7 ms in float32 and take 0.5 ms.
 template <int MA>
 __global__ void __launch_bounds__(LC_BT, 2)
@@ -804,15 +808,15 @@ lc_kmeans_assign_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
     constexpr int PF = LC_AS_TILE * 16 / LC_BT;                     // 16-byte pieces per thread and tile
     lc_v4i pf[PF];
     // (rows past the last centroid repeat it; of a sample, 16-row block j is block j mod 4 of the centroids' tile number j)
-    auto fetch = [&](auto sample, int c0) LC_INLINE {
+    auto fetch = [&](bool sample, int c0) LC_INLINE {
 #pragma unroll
         for (int e = 0; e < PF; ++e) {
             const int blk = (c0 >> 4) + e;
-            const int row = decltype(sample)::value ? LC_AS_TILE * blk + 16 * (blk & 3) : 16 * blk;
+            const int row = sample ? LC_AS_TILE * blk + 16 * (blk & 3) : 16 * blk;
             pf[e] = *reinterpret_cast<const lc_v4i*>(C16 + (size_t)min(row + (tid >> 4), k - 1) * LC_D + 8 * (tid & 15));
         }
     };
-    auto over_tiles = [&](auto sample, int rows, auto use) LC_INLINE {       // two tile buffers: one barrier per tile
+    auto over_tiles = [&](bool sample, int rows, auto use) LC_INLINE {       // two tile buffers: one barrier per tile
         int at = 0;
         for (int c0 = 0; c0 < rows; c0 += LC_AS_TILE) {
             unsigned char* const buf = tiles[at];
@@ -835,24 +839,26 @@ lc_kmeans_assign_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
                                   2.0f * LC_AS_EPS + 2.0f - __int_as_float(v.z), 2.0f * LC_AS_EPS + 2.0f - __int_as_float(v.w)};
         }
     };
-    const std::true_type sampled;
-    const std::false_type all;
-    if (it == 0) fetch(sampled, 0);
-    else fetch(all, 0);
+    const bool sample = it == 0 && k > LC_AS_SAMPLE;
+    fetch(sample, 0);
     // similarity to the previous centroid -- before the first iteration to the one that this point or a neighbour of it starts --,
     // one 16-lane group per point (group kk takes points 4 MA kk + e; the accumulators want points 16 a + 4 kk + r)
+    if (it == 0 && !sample) {
+        if (lane < WP) sh.pair_v[wave][lane] = LC_NEG_INF;
+    } else {
 #pragma unroll 2
-    for (int e = 0; e < 4 * MA; ++e) {
-        const int i = min(p0 + 4 * MA * kk + e, N - 1);
-        const int c = it == 0 ? min((int)(((long long)i * k + N - 1) / N), k - 1) : max(0, min(lab[i], k - 1));
-        float x[8], m[8];
-        lc_load8(P + (size_t)i * LC_D + 8 * j, x);
-        lc_load8(C + (size_t)c * LC_D + 8 * j, m);
-        float s = 0.f;
+        for (int e = 0; e < 4 * MA; ++e) {
+            const int i = min(p0 + 4 * MA * kk + e, N - 1);
+            const int c = it == 0 ? min((int)(((long long)i * k + N - 1) / N), k - 1) : max(0, min(lab[i], k - 1));
+            float x[8], m[8];
+            lc_load8(P + (size_t)i * LC_D + 8 * j, x);
+            lc_load8(C + (size_t)c * LC_D + 8 * j, m);
+            float s = 0.f;
 #pragma unroll
-        for (int t = 0; t < 8; ++t) s = fmaf(x[t], m[t], s);
-        s = lc_sum16(s);
-        if (j == 0) sh.pair_v[wave][4 * MA * kk + e] = it == 0 ? s - 2e-5f + 2.0f : s;      // (as `known`; less its own rounding)
+            for (int t = 0; t < 8; ++t) s = fmaf(x[t], m[t], s);
+            s = lc_sum16(s);
+            if (j == 0) sh.pair_v[wave][4 * MA * kk + e] = it == 0 ? s - 2e-5f + 2.0f : s;      // (as `known`; less its own rounding)
+        }
     }
     lc_wave_sync();
     if (it == 0) {
@@ -863,7 +869,7 @@ lc_kmeans_assign_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
 #pragma unroll
             for (int r = 0; r < 4; ++r) top[a][r] = LC_NEG_INF;
         }
-        over_tiles(sampled, (k + LC_AS_TILE - 1) / LC_AS_TILE * 16, [&](const unsigned char* buf, int, int n) LC_INLINE {
+        over_tiles(sample, sample ? (k + LC_AS_TILE - 1) / LC_AS_TILE * 16 : k, [&](const unsigned char* buf, int, int n) LC_INLINE {
             sweep(buf, n, [&](int, const lc_f32x4_b (&d0)[MA], const lc_f32x4_b (&d1)[MA]) LC_INLINE {
 #pragma unroll
                 for (int a = 0; a < MA; ++a)
@@ -871,7 +877,7 @@ lc_kmeans_assign_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
                     for (int r = 0; r < 4; ++r) top[a][r] = fmaxf(top[a][r], fmaxf(d0[a][r], d1[a][r]));
             });
         });
-        fetch(all, 0);
+        fetch(false, 0);
 #pragma unroll
         for (int a = 0; a < MA; ++a)
 #pragma unroll
@@ -893,7 +899,7 @@ lc_kmeans_assign_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
     }
     if (lane < WP && !(sh.pair_v[wave][lane] > LC_NEG_INF)) sh.cand_n[wave][lane] = LC_AS_CAND + 1;     // (see above)
     lc_wave_sync();
-    over_tiles(all, k, [&](const unsigned char* buf, int c0, int n) LC_INLINE {
+    over_tiles(false, k, [&](const unsigned char* buf, int c0, int n) LC_INLINE {
         if (it == 0 && c0 != 0 && (c0 & (LC_AS_REFRESH - 1)) == 0) threshold();
         sweep(buf, n, [&](int c, const lc_f32x4_b (&d0)[MA], const lc_f32x4_b (&d1)[MA]) LC_INLINE {
             float any = LC_NEG_INF;
