@@ -16,6 +16,8 @@
 
 #include <type_traits>
 
+#define LC_INLINE __attribute__((always_inline))       // (lambdas that hold registers by reference)
+
 #define LC_BT 256                 // threads per block
 #define LC_BG (LC_BT / 16)        // 16-lane groups per block
 #define LC_RADIUS_PAD 4e-6f       // stored radii are inflated by this relative amount so that
@@ -185,16 +187,17 @@ __device__ __forceinline__ void lc_c0_load8(const LcDev& ix, size_t n, int sub, 
 // level 0: one wavefront per chunk
 // ---------------------------------------------------------------------------------
 // The four 16-lane groups of a wavefront take the chunk's rows in turn (lane `sub` of a group holds
-// columns [8 sub, 8 sub + 8) of a row).  The bound is reading K once; the radius pass needs every row
-// again.  Each group's first LC_POOLW_KEEP rows stay in registers for it (more of them costs resident
-// wavefronts: 12 and 16 rows were slower) and the next LC_POOLW_PARK wait in LDS, 7 KB a wavefront, as many as
-// leave the resident count to the registers: chunks of up to 60 tokens read K once, longer ones find the
-// rest in the caches.  One wavefront per workgroup, so that a long chunk holds up no neighbour's place;
-// the groups' partial sums meet through wavefront shuffles.  268 MB of K in 128K tokens x 8 heads:
-// 78.2 us with four wavefronts to a workgroup and nothing parked, 73.2 us now (3.7 TB/s); 16 sequences of
-// ragged length: 167 us, now 156 us.
+// columns [8 sub, 8 sub + 8) of a row), LC_POOLW_KEEP rows per group to a batch.  The bound is reading K once; the radius pass needs every
+// row again.  The first two batches are loaded together and stay in registers for it, the third waits in LDS (8 KB a wavefront, as
+// many as leave the resident count to the registers): chunks of up to 96 tokens read K once, longer ones find the rest in the
+// caches.  Instructions were the other half of the time -- 1261 per chunk of 57 rows --: the sums are the matrix cores' work, range-checked
+// loads zero the rows past the chunk, eight rows' distances are reduced over the lanes together.  One wavefront per workgroup, so
+// that a long chunk holds up no neighbour's place.  268 MB of K in 128K tokens x 8 heads, 57 to a chunk: 72 us with sums by
+// addition, one batch in registers and seven rows per group in LDS; 69 us with two and none; 62 us now (292 MB with what is
+// written: 4.7 TB/s).  16 sequences of ragged length: 157 us, now 143 (734 MB: 5.1 TB/s).  Chunks of 8 to 16 tokens: 130 and 118 us.
 #define LC_POOLW_KEEP 8
-#define LC_POOLW_PARK 7
+typedef __bf16 lc_bf16x8_p __attribute__((ext_vector_type(8)));
+typedef float lc_f32x4_p __attribute__((ext_vector_type(4)));
 // Progress flags of the k-means of every level, [level][sequence, head][LC_KM_FLAGS]: cleared by the first kernel of a build.
 __device__ __forceinline__ int* lc_level_flags(const LcDev& ix, int* flags, int l, int bh) {
     return flags + ((size_t)l * ix.B * ix.H + bh) * LC_KM_FLAGS;
@@ -235,6 +238,28 @@ __device__ __forceinline__ void lc_clear_flags(const LcDev& ix, int bh, int* fla
         for (int l = 0; l + 1 < ix.L; ++l) lc_level_flags(ix, flags, l, bh)[threadIdx.x] = 0;
 }
 __device__ __forceinline__ float lc_sum_groups4(float v) { v += __shfl_xor(v, 16); v += __shfl_xor(v, 32); return v; }
+// A batch of rows, row base + 4 k + (lane / 16) of it in buf[k]; rows past the chunk read as zeros, all loads in flight together.  NEAR:
+// a batch lies within a range-checked buffer (rows of 256 bytes or more that do not overlap, 31 bits of offset), whose
+// checks replace the zeroing and whose addresses are one addition each.
+template <bool NEAR>
+__device__ __forceinline__ void lc_pool_batch(const uint16_t* Kbh, long long ks_tok, int base, int hi, lc_v4i (&buf)[LC_POOLW_KEEP]) {
+    const int lane = threadIdx.x & 63, sub = lane & 15, g4 = lane >> 4;
+    if constexpr (NEAR) {
+        const int row = (int)ks_tok * 2, rows = min(hi - base, 4 * LC_POOLW_KEEP);
+        const __amdgpu_buffer_rsrc_t r = lc_buffer(Kbh + (long long)base * ks_tok, rows > 0 ? (rows - 1) * row + 2 * LC_D : 0);
+        const int at = g4 * row + 16 * sub;
+#pragma unroll
+        for (int k = 0; k < LC_POOLW_KEEP; ++k) buf[k] = __builtin_amdgcn_raw_buffer_load_b128(r, at + 4 * k * row, 0, 0);
+    } else {
+#pragma unroll
+        for (int k = 0; k < LC_POOLW_KEEP; ++k) {
+            const int r = base + g4 + 4 * k;
+            const lc_v4i v = *reinterpret_cast<const lc_v4i*>(Kbh + (long long)max(min(r, hi - 1), 0) * ks_tok + 8 * sub);
+            buf[k] = r < hi ? v : lc_v4i{0, 0, 0, 0};
+        }
+    }
+}
+template <bool NEAR>
 __global__ void __launch_bounds__(64)
 lc_pool_kernel(LcDev ix, const uint16_t* K, long long ks_seq, long long ks_head, long long ks_tok,
                int geometry, LcPointRows out, int* flags) {
@@ -250,52 +275,67 @@ lc_pool_kernel(LcDev ix, const uint16_t* K, long long ks_seq, long long ks_head,
     const int lo = bnd[j], hi = bnd[j + 1];
     const uint16_t* Kbh = K + b * ks_seq + h * ks_head;
     const bool round_bf16 = ix.c0_bf16 != 0;
-    // a batch = LC_POOLW_KEEP rows per group, all loads in flight together (rows past the chunk read as zeros)
-    auto load_batch = [&](int base, uint4 (&buf)[LC_POOLW_KEEP]) {
+    constexpr int ROWS = 4 * LC_POOLW_KEEP;
+    __shared__ lc_v4i parked[LC_POOLW_KEEP][64];                    // (a lane reads its own entries only)
+    lc_v4i keep[LC_POOLW_KEEP], second[LC_POOLW_KEEP];
+    lc_pool_batch<NEAR>(Kbh, ks_tok, lo, hi, keep);
+    const bool two = hi - lo > ROWS;                                // (uniform)
+    if (two) lc_pool_batch<NEAR>(Kbh, ks_tok, lo + ROWS, hi, second);
+    // ---- sums over the rows, on the matrix cores: a lane's registers as they are loaded are column `sub` of a B operand whose 32
+    // rows are (row of K of this group of lanes, column 8 sub + t); the A operand picks t = i mod 8.  Row 4 g4 + r of the result
+    // is the sum of column 8 sub + (4 g4 + r) mod 8: products by one and zero are exact, sums are float32.
+    const int t = sub & 7, one = (t & 1) ? 0x3f800000 : 0x00003f80;
+    const lc_v4i pick = lc_v4i{t >> 1 == 0 ? one : 0, t >> 1 == 1 ? one : 0, t >> 1 == 2 ? one : 0, t >> 1 == 3 ? one : 0};
+    lc_f32x4_p acc[4];
 #pragma unroll
-        for (int k = 0; k < LC_POOLW_KEEP; ++k) {
-            // (no branch around the load -- the compiler would wait for one load before issuing the
-            // next; a row past the chunk re-reads the chunk's last row and is zeroed afterwards)
-            const int r = base + g4 + 4 * k;
-            const uint4 v = *reinterpret_cast<const uint4*>(Kbh + (long long)max(min(r, hi - 1), lo) * ks_tok + 8 * sub);
-            buf[k] = r < hi ? v : make_uint4(0u, 0u, 0u, 0u);
-        }
-    };
-    uint4 keep[LC_POOLW_KEEP];
-    __shared__ uint4 parked[LC_POOLW_PARK][64];                     // (a lane reads its own entries only)
-    load_batch(lo, keep);
-    float sum[8];
+    for (int e = 0; e < 4; ++e) acc[e] = lc_f32x4_p{0.f, 0.f, 0.f, 0.f};
+    auto add_batch = [&](const lc_v4i (&buf)[LC_POOLW_KEEP]) LC_INLINE {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) sum[i] = 0.f;
-    auto add_batch = [&](const uint4 (&buf)[LC_POOLW_KEEP]) {
-#pragma unroll
-        for (int k = 0; k < LC_POOLW_KEEP; ++k) {                   // (zero rows add nothing)
-            float f[8];
-            lc_unpack8(buf[k], f);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) sum[i] += f[i];
-        }
+        for (int k = 0; k < LC_POOLW_KEEP; ++k)                     // (zero rows add nothing)
+            acc[k & 3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(lc_bf16x8_p, pick),
+                                                                 __builtin_bit_cast(lc_bf16x8_p, buf[k]), acc[k & 3], 0, 0, 0);
     };
     add_batch(keep);
-    for (int base = lo + 4 * LC_POOLW_KEEP; base < hi; base += 4 * LC_POOLW_KEEP) {
-        uint4 more[LC_POOLW_KEEP];
-        load_batch(base, more);
-        add_batch(more);
-        if (base == lo + 4 * LC_POOLW_KEEP) {
+    if (two) {
+        add_batch(second);
+        for (int base = lo + 2 * ROWS; base < hi; base += ROWS) {
+            lc_v4i more[LC_POOLW_KEEP];
+            lc_pool_batch<NEAR>(Kbh, ks_tok, base, hi, more);
+            add_batch(more);
+            if (base == lo + 2 * ROWS) {
 #pragma unroll
-            for (int k = 0; k < LC_POOLW_PARK; ++k) parked[k][lane] = more[k];
+                for (int k = 0; k < LC_POOLW_KEEP; ++k) parked[k][lane] = more[k];
+            }
         }
     }
-    // The rows stay packed (four registers each) across the two passes: an empty statement that
-    // claims to rewrite them keeps the compiler from holding their unpacked copies as well, which
-    // would double the registers per row and halve the resident wavefronts.
-#pragma unroll
-    for (int k = 0; k < LC_POOLW_KEEP; ++k)
-        asm volatile("" : "+v"(keep[k].x), "+v"(keep[k].y), "+v"(keep[k].z), "+v"(keep[k].w));
     float mu[8];
     const float inv_n = 1.0f / (float)(hi - lo);
+    {
+        float z = 0.f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) mu[i] = lc_sum_groups4(sum[i]) * inv_n;
+        for (int r = 0; r < 4; ++r) {
+            const float s = (acc[0][r] + acc[1][r]) + (acc[2][r] + acc[3][r]), o = __shfl_xor(s, 16);
+            mu[r] = (g4 & 1) ? o : s;
+            mu[4 + r] = (g4 & 1) ? s : o;
+            z += s - s;
+        }
+        if (__ballot(!(z == 0.f)) != 0ull) {
+            // infinities and what is no number (times zero, they have reached their neighbours' sums): column by column
+            float sum[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) sum[i] = 0.f;
+            for (int r = lo + g4; r < hi; r += 4) {
+                float f[8];
+                lc_unpack8(*reinterpret_cast<const uint4*>(Kbh + (long long)r * ks_tok + 8 * sub), f);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) sum[i] += f[i];
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) mu[i] = lc_sum_groups4(sum[i]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) mu[i] *= inv_n;
     float radius = 0.f;
     if (geometry == LC_GEOMETRY_PAPER_UNIT) {
         float un[8];
@@ -308,30 +348,49 @@ lc_pool_kernel(LcDev ix, const uint16_t* K, long long ks_seq, long long ks_head,
             for (int i = 0; i < 8; ++i) mu[i] = lc_round_bf16(mu[i]);
         }
         float far2 = 0.f;
-        auto reach = [&](const uint4& v) {
-            float f[8];
-            lc_unpack8(v, f);
-            float d2 = 0.f;
+        // Squared distances of a batch's rows.  Eight rows' parts are reduced over the 16 lanes together: at each of three steps a
+        // lane passes on the half of them that its partner goes on with, and ends with one row's, number 4 (sub bit 1) + 2 (bit 2) + (bit 3).
+        const bool b3 = (sub & 8) != 0, b2 = (sub & 4) != 0, b1 = (sub & 2) != 0;
+        const int mine = g4 + 4 * ((b1 ? 4 : 0) + (b2 ? 2 : 0) + (b3 ? 1 : 0));
+        auto reach = [&](const lc_v4i (&buf)[LC_POOLW_KEEP], int n) LC_INLINE {
+            float d[LC_POOLW_KEEP];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) { const float t = f[i] - mu[i]; d2 = fmaf(t, t, d2); }
-            d2 = lc_sum16(d2);
-            far2 = fmaxf(far2, d2);
+            for (int k = 0; k < LC_POOLW_KEEP; ++k) {
+                d[k] = 0.f;
+                if (4 * k < n) {                                    // (uniform)
+                    float f[8];
+                    lc_unpack8(__builtin_bit_cast(uint4, buf[k]), f);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) { const float x = f[i] - mu[i]; d[k] = fmaf(x, x, d[k]); }
+                }
+            }
+            static_assert(LC_POOLW_KEEP == 8, "three halvings");
+#pragma unroll
+            for (int k = 0; k < 4; ++k) { const float give = b3 ? d[2 * k] : d[2 * k + 1]; d[k] = (b3 ? d[2 * k + 1] : d[2 * k]) + lc_dpp<0x140>(give); }
+#pragma unroll
+            for (int k = 0; k < 2; ++k) { const float give = b2 ? d[2 * k] : d[2 * k + 1]; d[k] = (b2 ? d[2 * k + 1] : d[2 * k]) + lc_dpp<0x141>(give); }
+            const float give = b1 ? d[0] : d[1];
+            float v = (b1 ? d[1] : d[0]) + lc_dpp<0x4E>(give);
+            v += lc_dpp<0xB1>(v);
+            far2 = mine < n ? fmaxf(far2, v) : far2;
         };
+        reach(keep, hi - lo);
+        if (two) {
+            reach(second, hi - lo - ROWS);
+            for (int base = lo + 2 * ROWS; base < hi; base += ROWS) {
+                lc_v4i more[LC_POOLW_KEEP];
+                if (base == lo + 2 * ROWS) {
 #pragma unroll
-        for (int k = 0; k < LC_POOLW_KEEP; ++k)
-            if (lo + g4 + 4 * k < hi) reach(keep[k]);
-        if (lo + 4 * LC_POOLW_KEEP < hi) {
-#pragma unroll
-            for (int k = 0; k < LC_POOLW_PARK; ++k)
-                if (lo + g4 + 4 * (LC_POOLW_KEEP + k) < hi) reach(parked[k][lane]);
+                    for (int k = 0; k < LC_POOLW_KEEP; ++k) more[k] = parked[k][lane];
+                } else {
+                    lc_pool_batch<NEAR>(Kbh, ks_tok, base, hi, more);
+                }
+                reach(more, hi - base);
+            }
         }
-        for (int base = lo + 4 * (LC_POOLW_KEEP + LC_POOLW_PARK); base < hi; base += 4 * LC_POOLW_KEEP) {
-            uint4 more[LC_POOLW_KEEP];
-            load_batch(base, more);
-#pragma unroll
-            for (int k = 0; k < LC_POOLW_KEEP; ++k)
-                if (base + g4 + 4 * k < hi) reach(more[k]);
-        }
+        far2 = fmaxf(far2, lc_dpp<0x4E>(far2));
+        far2 = fmaxf(far2, lc_dpp<0x141>(far2));
+        far2 = fmaxf(far2, lc_dpp<0x140>(far2));
         far2 = fmaxf(far2, __shfl_xor(far2, 16));
         far2 = fmaxf(far2, __shfl_xor(far2, 32));
         radius = lc_pad_radius(sqrtf(far2));
@@ -485,7 +544,6 @@ __device__ __forceinline__ void lc_wave_sync() {
 #define LC_AS_PAIRS 128           // pairs a wavefront compares at a time (and no fewer than its points)
 #define LC_AS_EPS 0.0040f         // 2^-8 (both operands' rounding, Cauchy-Schwarz) and room for the float32 sums
 typedef __bf16 lc_bf16x8_b __attribute__((ext_vector_type(8)));
-#define LC_INLINE __attribute__((always_inline))       // (lambdas that hold registers by reference)
 
 // LDS of the candidates of a workgroup's points: NW wavefronts, WP points each.
 template <int WP, int NW>
@@ -1809,7 +1867,8 @@ int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const i
     // this one's centroids are still read)
     LcPointRows cur{ws.dirs, ws.dirs16, ix.cap[0], L > 1 ? ws.cent[0] : nullptr, ws.cent16[0], ix.cap[1]};
     if (max_M > 0 && K != nullptr) {
-        hipLaunchKernelGGL(lc_pool_kernel, dim3(max_M, H, B), dim3(64), 0, stream, ix, K,
+        const bool near = ks[2] >= LC_D && ks[2] * 2 * (4 * LC_POOLW_KEEP) < (1ll << 31);     // (see lc_pool_batch)
+        hipLaunchKernelGGL(near ? lc_pool_kernel<true> : lc_pool_kernel<false>, dim3(max_M, H, B), dim3(64), 0, stream, ix, K,
                            (long long)ks[0], (long long)ks[1], (long long)ks[2], geometry, cur, ws.kflags);
         LC_HIP_CHECK(hipGetLastError());
     } else if (max_M > 0) {
