@@ -550,11 +550,14 @@ template <int WP, int NW>
 struct LcAssignSh {
     int cand_n[NW][WP];
     int cand[NW][WP][LC_AS_CAND];
-    int pair_c[NW][LC_AS_PAIRS];
-    float pair_v[NW][LC_AS_PAIRS];
-    uint8_t pair_p[NW][LC_AS_PAIRS];
     uint8_t rest_p[NW * WP];
     int n_rest;
+};
+template <int NW>
+struct LcAssignPairs {
+    float pair_v[NW][LC_AS_PAIRS];
+    int pair_c[NW][LC_AS_PAIRS];
+    uint8_t pair_p[NW][LC_AS_PAIRS];
 };
 __device__ __forceinline__ void lc_assign_take(int* n, int* list, int c) {
     const int at = atomicAdd(n, 1);
@@ -565,7 +568,7 @@ __device__ __forceinline__ void lc_assign_take(int* n, int* list, int c) {
 // threads call.  P, C: float32 rows of the points and centroids; lab: the labels, old_label this lane's.  Returns the label of
 // this lane's point, -1 without one; every wavefront is past its last use of the centroid rows then.
 template <int WP, int NW>
-__device__ __forceinline__ int lc_assign_finish(LcAssignSh<WP, NW>& sh, const float* P, const float* C, int N, int k, int w0,
+__device__ __forceinline__ int lc_assign_finish(LcAssignSh<WP, NW>& sh, LcAssignPairs<NW>& pairs, const float* P, const float* C, int N, int k, int w0,
                                                  int p0, int* lab, int old_label, int* flag) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int j = lane & 15, kk = lane >> 4;
@@ -584,14 +587,14 @@ __device__ __forceinline__ int lc_assign_finish(LcAssignSh<WP, NW>& sh, const fl
         const int n_pairs = (int)lc_wave_max_u((uint32_t)(now ? incl : 0));
         if (now)
             for (int e = 0; e < n_c; ++e) {
-                sh.pair_c[wave][first + e] = sh.cand[wave][my_p][e];
-                sh.pair_p[wave][first + e] = (uint8_t)my_p;
+                pairs.pair_c[wave][first + e] = sh.cand[wave][my_p][e];
+                pairs.pair_p[wave][first + e] = (uint8_t)my_p;
             }
         lc_wave_sync();
         for (int q0 = 0; q0 < n_pairs; q0 += 16) {
             const int q = min(q0 + j, n_pairs - 1);
-            const float* xr = P + (size_t)(p0 + (int)sh.pair_p[wave][q]) * LC_D + 4 * kk;
-            const float* mr = C + (size_t)sh.pair_c[wave][q] * LC_D + 4 * kk;
+            const float* xr = P + (size_t)(p0 + (int)pairs.pair_p[wave][q]) * LC_D + 4 * kk;
+            const float* mr = C + (size_t)pairs.pair_c[wave][q] * LC_D + 4 * kk;
             float4 x[8], m[8];
 #pragma unroll
             for (int t = 0; t < 8; ++t) {
@@ -607,15 +610,15 @@ __device__ __forceinline__ int lc_assign_finish(LcAssignSh<WP, NW>& sh, const fl
                 d = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t].w, m[t].w, d, 0, 0, 0);
             }
             const float diag = (j & 2) ? ((j & 1) ? d[3] : d[2]) : ((j & 1) ? d[1] : d[0]);    // row 4 kk + (j & 3) = column j
-            if (kk == (j >> 2) && q0 + j < n_pairs) sh.pair_v[wave][q0 + j] = diag;
+            if (kk == (j >> 2) && q0 + j < n_pairs) pairs.pair_v[wave][q0 + j] = diag;
         }
         lc_wave_sync();
         if (now) {
             float bv = LC_NEG_INF;
             int bc = 0x7fffffff;
             for (int e = 0; e < n_c; ++e) {
-                const float v = sh.pair_v[wave][first + e];
-                const int c = sh.pair_c[wave][first + e];
+                const float v = pairs.pair_v[wave][first + e];
+                const int c = pairs.pair_c[wave][first + e];
                 if (v > bv || (v == bv && c < bc)) { bv = v; bc = c; }
             }
             ba = bc < k ? bc : 0;
@@ -643,7 +646,7 @@ __device__ __forceinline__ int lc_assign_finish(LcAssignSh<WP, NW>& sh, const fl
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             lc_assign_merge(best[r], arg[r]);
-            if (j == 0) { sh.pair_v[wave][4 * kk + r] = best[r]; sh.pair_c[wave][4 * kk + r] = arg[r]; }
+            if (j == 0) { pairs.pair_v[wave][4 * kk + r] = best[r]; pairs.pair_c[wave][4 * kk + r] = arg[r]; }
         }
         __syncthreads();
         for (int e = 0; e < 16 && q0 + e < rest; ++e) {             // the owner takes the best of the shares
@@ -651,9 +654,9 @@ __device__ __forceinline__ int lc_assign_finish(LcAssignSh<WP, NW>& sh, const fl
                 float bv = LC_NEG_INF;
                 int bc = 0x7fffffff;
                 for (int w = 0; w < NW; ++w)
-                    if (sh.pair_v[w][e] > bv || (sh.pair_v[w][e] == bv && sh.pair_c[w][e] < bc)) {
-                        bv = sh.pair_v[w][e];
-                        bc = sh.pair_c[w][e];
+                    if (pairs.pair_v[w][e] > bv || (pairs.pair_v[w][e] == bv && pairs.pair_c[w][e] < bc)) {
+                        bv = pairs.pair_v[w][e];
+                        bc = pairs.pair_c[w][e];
                     }
                 ba = bc < k ? bc : 0;
             }
@@ -688,7 +691,14 @@ lc_kmeans_assign_res_kernel(LcDev ix, int l, const float* pts, const uint16_t* p
     lc_fetch_args<sizeof(LcDev) + 40>();
     constexpr int PIECES = NBLK * 256 / (64 * NW);                  // 16-byte pieces of the rows per thread
     __shared__ __attribute__((aligned(16))) unsigned char rows[16 * NBLK * LC_AS_PITCH];
+    // (16 blocks under eight wavefronts: the pairs come where the rows were, behind the bits, so that two workgroups fit a compute unit)
+    constexpr bool SHARE = NBLK == 16 && NW == 8;
+    constexpr int BITS_END = NW / 4 * 16 * NBLK * 8;
+    using Pairs = LcAssignPairs<NW>;
     __shared__ LcAssignSh<16, NW> sh;
+    __shared__ __attribute__((aligned(16))) unsigned char own_pairs[SHARE ? 16 : sizeof(Pairs)];
+    static_assert(!SHARE || BITS_END + sizeof(Pairs) <= sizeof(rows), "");
+    Pairs& pairs = *reinterpret_cast<Pairs*>(SHARE ? rows + BITS_END : own_pairs);
     const int h = blockIdx.y, b = blockIdx.z;
     const int bh = b * ix.H + h;
     int* const flags = flags_all ? lc_level_flags(ix, flags_all, l, bh) : nullptr;
@@ -760,8 +770,9 @@ lc_kmeans_assign_res_kernel(LcDev ix, int l, const float* pts, const uint16_t* p
             if (c < k) lc_assign_take(&sh.cand_n[wave][p], sh.cand[wave][p], c);
         }
     }
-    lc_wave_sync();
-    const int label = lc_assign_finish<16, NW>(sh, pts + (size_t)bh * pts_cap * LC_D, cent + (size_t)bh * cent_cap * LC_D, N, k,
+    if (SHARE) __syncthreads();                                     // the rows have been read
+    else lc_wave_sync();
+    const int label = lc_assign_finish<16, NW>(sh, pairs, pts + (size_t)bh * pts_cap * LC_D, cent + (size_t)bh * cent_cap * LC_D, N, k,
                                                w0, p0, lab, old_label, flags ? flags + it : nullptr);
     // the members' bits of this workgroup's blocks of 64 points, collected where the centroid rows were
     unsigned long long* const mb = bits.w[it & 1];
@@ -804,8 +815,8 @@ lc_kmeans_assign_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
     constexpr int WP = 16 * MA;                                     // points per wavefront
     __shared__ __attribute__((aligned(16))) unsigned char tiles[2][LC_AS_TILE * LC_AS_PITCH];
     using Sh = LcAssignSh<WP, 4>;
-    __shared__ __attribute__((aligned(16))) Sh sh;       // (pair_v is read 16 bytes at a time)
-    static_assert(offsetof(Sh, pair_v) % 16 == 0, "");
+    __shared__ Sh sh;
+    __shared__ __attribute__((aligned(16))) LcAssignPairs<4> pairs;      // (pair_v is read 16 bytes at a time)
     const int h = blockIdx.y, b = blockIdx.z;
     const int bh = b * ix.H + h;
     int* const flags = flags_all ? lc_level_flags(ix, flags_all, l, bh) : nullptr;
@@ -888,7 +899,7 @@ lc_kmeans_assign_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
         }
     };
     // The largest similarity a point is known to have, as an integer that orders like it (similarities lie above -2).
-    int* const known = reinterpret_cast<int*>(sh.pair_v[wave]);
+    int* const known = reinterpret_cast<int*>(pairs.pair_v[wave]);
     auto threshold = [&]() LC_INLINE {
 #pragma unroll
         for (int a = 0; a < MA; ++a) {
@@ -902,7 +913,7 @@ lc_kmeans_assign_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
     // similarity to the previous centroid -- before the first iteration to the one that this point or a neighbour of it starts --,
     // one 16-lane group per point (group kk takes points 4 MA kk + e; the accumulators want points 16 a + 4 kk + r)
     if (it == 0 && !sample) {
-        if (lane < WP) sh.pair_v[wave][lane] = LC_NEG_INF;
+        if (lane < WP) pairs.pair_v[wave][lane] = LC_NEG_INF;
     } else {
 #pragma unroll 2
         for (int e = 0; e < 4 * MA; ++e) {
@@ -915,7 +926,7 @@ lc_kmeans_assign_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
 #pragma unroll
             for (int t = 0; t < 8; ++t) s = fmaf(x[t], m[t], s);
             s = lc_sum16(s);
-            if (j == 0) sh.pair_v[wave][4 * MA * kk + e] = it == 0 ? s - 2e-5f + 2.0f : s;      // (as `known`; less its own rounding)
+            if (j == 0) pairs.pair_v[wave][4 * MA * kk + e] = it == 0 ? s - 2e-5f + 2.0f : s;      // (as `known`; less its own rounding)
         }
     }
     lc_wave_sync();
@@ -953,9 +964,9 @@ lc_kmeans_assign_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
 #pragma unroll
         for (int a = 0; a < MA; ++a)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) start[a][r] = (LC_AS_EPS + 2e-5f) - sh.pair_v[wave][16 * a + 4 * kk + r];
+            for (int r = 0; r < 4; ++r) start[a][r] = (LC_AS_EPS + 2e-5f) - pairs.pair_v[wave][16 * a + 4 * kk + r];
     }
-    if (lane < WP && !(sh.pair_v[wave][lane] > LC_NEG_INF)) sh.cand_n[wave][lane] = LC_AS_CAND + 1;     // (see above)
+    if (lane < WP && !(pairs.pair_v[wave][lane] > LC_NEG_INF)) sh.cand_n[wave][lane] = LC_AS_CAND + 1;     // (see above)
     lc_wave_sync();
     over_tiles(false, k, [&](const unsigned char* buf, int c0, int n) LC_INLINE {
         if (it == 0 && c0 != 0 && (c0 & (LC_AS_REFRESH - 1)) == 0) threshold();
@@ -995,7 +1006,7 @@ lc_kmeans_assign_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
         });
     });
     __syncthreads();
-    lc_assign_finish<WP, 4>(sh, P, C, N, k, w0, p0, lab, old_label, flags ? flags + it : nullptr);
+    lc_assign_finish<WP, 4>(sh, pairs, P, C, N, k, w0, p0, lab, old_label, flags ? flags + it : nullptr);
 }
 
 // Ascending list, in LDS, of the i in [base, base + LC_MEM_WIN) below n with label c; returns its length in
@@ -1917,8 +1928,9 @@ int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const i
             // 64 points per workgroup: 2: 20.6, 4: 22.3, 6: 26, 8: 31, 10: 33, 12: 43, 16: 48; 2275 x 8: 8.0, 9.0, 9.6, 9.7, 10.3, 11.1,
             // 12.6), and 64 points per workgroup.  128 points stage half as many rows, at the price of registers: with more
             // than two workgroups per compute unit that pays at 12 blocks (33 instead of 43 us; 4200 x 16: 20.9 instead of 24),
-            // hardly at 8 and 10 (29.6 instead of 31.2, 31.3 instead of 33.5; 4200 x 16: 18.4 instead of 17.4) and at no other
-            // number (2, 4, 6, 16: 24.1, 25.9, 27.5, 50 us).
+            // hardly at 8 and 10 (29.6 instead of 31.2, 31.3 instead of 33.5; 4200 x 16: 18.4 instead of 17.4) and not at 2, 4
+            // or 6 (24.1, 25.9, 27.5 us).  At 16 blocks it does since two of them fit a compute unit: 5461 x 8 points under 249 centroids
+            // 14.8 instead of 17.4 us, whole clusterings of 10.9 K x 8 points 722 instead of 760, of 4166 x 64 under 208 1081 instead of 1219.
             const bool wide = (maxN + 63) / 64 * BH > 512;
             auto assign = [&](auto kernel, int points, int threads, int it, auto... more) {
                 hipLaunchKernelGGL(kernel, dim3((maxN + points - 1) / points, H, B), dim3(threads), 0, stream, ix, l,
@@ -1948,6 +1960,7 @@ int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const i
                 else if (maxK <= 160) assign(&lc_kmeans_assign_res_kernel<10, 4>, 64, 256, it, bits);
                 else if (maxK <= 192 && wide) assign(&lc_kmeans_assign_res_kernel<12, 8>, 128, 512, it, bits);
                 else if (maxK <= 192) assign(&lc_kmeans_assign_res_kernel<12, 4>, 64, 256, it, bits);
+                else if (maxK <= LC_AS_RES && wide) assign(&lc_kmeans_assign_res_kernel<16, 8>, 128, 512, it, bits);
                 else if (maxK <= LC_AS_RES) assign(&lc_kmeans_assign_res_kernel<16, 4>, 64, 256, it, bits);
                 else if (ma == 4) assign(&lc_kmeans_assign_kernel<4>, 256, LC_BT, it);
                 else if (ma == 3) assign(&lc_kmeans_assign_kernel<3>, 192, LC_BT, it);
