@@ -1,5 +1,5 @@
 """lc_retrieve where its selection changes shape: chunk counts around the rows of its selecting kernel and its largest, budgets that
-end in the upper half of the keys' range, below it, nowhere, and inside large groups of equal scores."""
+end in the upper half of the scores' range, below it, nowhere, and inside large groups of equal scores."""
 import numpy as np
 import pytest
 
@@ -15,9 +15,10 @@ def by_the_rule(scores, lens, starts, budget, sink):
     return np.sort(np.concatenate([np.flatnonzero(pinned), order[: int(fits.sum())]]))
 
 
+@pytest.mark.parametrize("geometry", [0, 1])                    # 1: scores of both signs
 @pytest.mark.parametrize("distinct", [0, 37])                   # 37: the chunks repeat 37 contents, so scores are equal by the hundreds
 @pytest.mark.parametrize("chunks", [65, 129, 1023, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193, 12287, 12288, 12289])
-def test_selection_follows_the_scores(chunks, distinct):
+def test_selection_follows_the_scores(chunks, distinct, geometry):
     import torch
     from paper_2603_08453_amd import binding as lc
     B, H, G = 2, 2, 4
@@ -39,7 +40,8 @@ def test_selection_follows_the_scores(chunks, distinct):
     q[:, :G] *= 1.0 if chunks % 2 else 0.0                      # (no query: every score of head 0 is zero)
     total = int(bounds[0][-1])
     for sink, budget in ((0, 0), (3, 7), (0, total // 50 + 1), (total // 3, total // 9), (0, (9 * total) // 10), (0, total), (9, 10 ** 9)):
-        cfg = lc.lc_config_default(levels=2, fanout=32, kmeans_iters=1, max_chunks=chunks, max_tokens=max(lens), sink_tokens=sink, prune=0)
+        cfg = lc.lc_config_default(levels=2, fanout=32, kmeans_iters=1, max_chunks=chunks, max_tokens=max(lens), sink_tokens=sink, prune=0,
+                                   geometry=geometry)
         ib = torch.zeros(lc.lc_index_bytes(cfg, B, H), dtype=torch.uint8, device="cuda")
         ws = torch.zeros(lc.lc_workspace_bytes(cfg, B, H * G, H), dtype=torch.uint8, device="cuda")
         idx = lc.lc_build_index(cfg, K, lens, bounds, ib, ws)
