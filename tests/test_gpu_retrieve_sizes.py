@@ -56,3 +56,34 @@ def test_selection_follows_the_scores(chunks, distinct, geometry):
                 want = by_the_rule(scores[b, h, :m].cpu().numpy(), np.diff(bounds[b]), bounds[b][:-1], budget, sink)
                 assert int(n[b, h]) == len(want), (sink, budget, b, h)
                 assert np.array_equal(ids[b, h, : len(want)].cpu().numpy(), want), (sink, budget, b, h)
+
+
+@pytest.mark.parametrize("infinite", [False, True])
+@pytest.mark.parametrize("geometry", [0, 1])
+@pytest.mark.parametrize("chunks", [64, 65, 130, 241, 600, 1030, 2050, 4096])
+def test_a_step_selects_the_same(chunks, geometry, infinite):
+    import torch
+    from paper_2603_08453_amd import binding as lc
+    H, G = 2, 4
+    size = np.random.default_rng(chunks).integers(1, 6, size=chunks)
+    bounds = np.concatenate([[0], np.cumsum(size)]).astype(np.int32)
+    T = int(bounds[-1]) + 2
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(chunks)
+    K, V = (torch.randn((1, H, T, 128), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
+    q = torch.randn((1, H * G, 128), generator=gen, device="cuda").to(torch.bfloat16)
+    if infinite:
+        K[0, 0, T // 2, 3], K[0, 1, T // 3, 5] = float("inf"), 3e38
+    cfg = lc.lc_config_default(levels=2, fanout=32, kmeans_iters=1, max_chunks=chunks, max_tokens=T, prune=0, geometry=geometry)
+    ib = torch.zeros(lc.lc_index_bytes(cfg, 1, H), dtype=torch.uint8, device="cuda")
+    ws = torch.zeros(lc.lc_workspace_bytes(cfg, 1, H * G, H), dtype=torch.uint8, device="cuda")
+    idx = lc.lc_build_index(cfg, K, [T], [bounds], ib, ws)
+    for budget in (3, T // 40 + 1, T // 9, (9 * T) // 10, 10 ** 9):
+        ids = [torch.full((1, H, chunks), -7, dtype=torch.int32, device="cuda") for _ in range(2)]
+        n = [torch.full((1, H), -1, dtype=torch.int32, device="cuda") for _ in range(2)]
+        out = torch.empty((1, H * G, 128), device="cuda")
+        lc.lc_retrieve(idx, q, budget, ids[0], n[0], ws)
+        lc.lc_decode_step(idx, q, K, V, budget, out, ws, chunk_ids=ids[1], counts=n[1])
+        assert torch.equal(n[0], n[1]), budget
+        for h in range(H):
+            assert torch.equal(ids[0][0, h, : n[0][0, h]], ids[1][0, h, : n[1][0, h]]), (budget, h)
