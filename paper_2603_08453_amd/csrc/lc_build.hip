@@ -4,7 +4,7 @@
 //   lc_pool_kernel    chunk representative = mean-pooled keys; covering radius; unit direction
 //   lc_kmeans_*       spherical k-means on unit directions: strided start, then
 //                     `iters` x (assign by largest inner product, normalised-sum update)
-//   lc_center_*       node center (mean of all descendant chunks), counts, direction
+//   lc_center_*       node center (mean of all descendant chunks), counts, direction (small levels: in lc_kmeans_small_kernel)
 //   lc_radius_kernel  radii of every level over all descendant chunks' balls, after the last level
 // Append: lc_append_kernel writes the token's k, v; on a chunk close it pools the
 // open tail, finds the level-1 node of nearest direction and updates the path to the top.
@@ -1475,6 +1475,91 @@ lc_kmeans_update_few_kernel(LcDev ix, int l, const float* pts, int pts_cap, floa
         [&](int c, int, float (&s)[8]) { lc_write_centroid(cent, cent16, ((size_t)bh * cent_cap + c) * LC_D + 8 * sub, s); });
 }
 
+// What is stored of node u of level l + 1 except its radius: center (mean of the descendant chunks'
+// centers; the centroid for the unit geometry and for a node without chunks), counts, unit direction (the
+// next level's point); the radius starts at -inf.  Called by one 16-lane group.
+struct LcNodeArgs {
+    const float* cent;       // this level's centroids
+    int cent_cap;
+    int geometry;
+    LcPointRows next;        // the next level's points and starting centroids
+    __device__ __forceinline__ const float* centroid(int bh, int u) const { return cent + ((size_t)bh * cent_cap + u) * LC_D; }
+};
+template <typename Acc>
+__device__ __forceinline__ void lc_write_node(const LcDev& ix, int b, int bh, int l, int u, int n_chunks, int n_tok,
+                                              const Acc (&sum)[8], const LcNodeArgs& w, const float* centroid) {
+    const int sub = threadIdx.x & 15;
+    float mu[8];
+    if (n_chunks > 0 && w.geometry == LC_GEOMETRY_TOKEN_BALL) {
+        const Acc inv = (Acc)1 / (Acc)n_chunks;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) mu[t] = (float)(sum[t] * inv);
+    } else if (lc_level_count(ix, b, bh, l) > 0) {
+        lc_load8(centroid + 8 * sub, mu);
+    } else {                                                        // (a sequence without chunks: no centroid was started)
+#pragma unroll
+        for (int t = 0; t < 8; ++t) mu[t] = (sub == 0 && t == 0) ? 1.f : 0.f;
+    }
+    const size_t n = (size_t)bh * ix.cap[l + 1] + u;
+    lc_store8(ix.center[l + 1] + n * LC_D + 8 * sub, mu);
+    float d[8];
+    lc_unit_frag(mu, sub, d);
+    if (w.next.pts)
+        lc_store_point(w.next, bh, u, ix.nlev[b * LC_MAX_LEVELS + l + 1], ix.nlev[b * LC_MAX_LEVELS + l + 2], sub, d);
+    if (sub == 0) {
+        ix.radius[l + 1][n] = LC_NEG_INF;
+        ix.rbuild[l + 1][n] = LC_NEG_INF;
+        ix.parent[l + 1][n] = -1;
+        ix.ntok[l + 1][n] = n_tok;
+        ix.nchunk[l + 1][n] = n_chunks;
+    }
+}
+
+// What a node of level l + 1 is made of: the chunks under it, or above the first level its child nodes, each weighted by
+// the chunks it holds: a child's center is their mean, so the weighted sum is the sum over all descendant chunks.  It is taken in
+// float64, so that its error is no larger than that of the float32 sum of the chunks (relative to the center, level 2 and
+// 3 of 2275 chunks: 8.8e-8 and 2.2e-7 as the chunks' sum, 7.0e-8 and 1.3e-7 now).  Children instead of chunks: 143 nodes into 9
+// and 9 into 1, 8 heads, 27 and 10 us, then 6.8 and 5.5; 5461 nodes into 249: 62 us, now 34.
+template <bool NODES>
+struct LcMembers {
+    const float* center;             // rows of the members: float32, or bfloat16 at the chunk level if `half`
+    const int* label;
+    const int* ntok;
+    const int* nchunk;               // NODES
+    bool half;
+    int n;
+    __device__ __forceinline__ LcMembers(const LcDev& ix, int b, int bh, int l) {
+        const size_t at = (size_t)bh * ix.cap[NODES ? l : 0];
+        half = !NODES && ix.c0_bf16 != 0;
+        center = half ? reinterpret_cast<const float*>(reinterpret_cast<const uint16_t*>(ix.center[0]) + at * LC_D)
+                      : ix.center[NODES ? l : 0] + at * LC_D;
+        label = ix.parent[NODES ? l : 0] + at;
+        ntok = ix.ntok[NODES ? l : 0] + at;
+        nchunk = NODES ? ix.nchunk[l] + at : nullptr;
+        n = NODES ? ix.nlev[b * LC_MAX_LEVELS + l] : ix.state[bh * 4 + 1];
+    }
+    // columns [col, col + COLS) of member j's row; returns its weight
+    template <int COLS>
+    __device__ __forceinline__ int row(int j, int col, float (&x)[COLS]) const {
+        const size_t o = (size_t)j * LC_D + col;
+        const uint16_t* const c16 = reinterpret_cast<const uint16_t*>(center);
+        if constexpr (COLS == 8) {
+            if (half) lc_unpack8(*reinterpret_cast<const uint4*>(c16 + o), x);
+            else lc_load8(center + o, x);
+        } else if (half) {
+            const uint32_t v = *reinterpret_cast<const uint32_t*>(c16 + o);
+            x[0] = lc_bf16_lo(v);
+            x[1] = lc_bf16_hi(v);
+        } else {
+            const float2 v = *reinterpret_cast<const float2*>(center + o);
+            x[0] = v.x;
+            x[1] = v.y;
+        }
+        return chunks(j);
+    }
+    __device__ __forceinline__ int chunks(int j) const { return NODES ? nchunk[j] : 1; }
+};
+
 // The whole clustering of a small level (up to LC_KS_MAX_N points into up to LC_KS_MAX_K clusters)
 // in one kernel, one workgroup per (sequence, head): points, centroids and labels live in LDS (a wavefront's 16 points in its
 // registers as well), the iterations are separated by workgroup barriers instead of kernel boundaries.  Same steps as the
@@ -1483,6 +1568,9 @@ lc_kmeans_update_few_kernel(LcDev ix, int l, const float* pts, int pts_cap, floa
 // What bounds an iteration is a chain: 32 dependent matrix instructions, four barriers, and the longest cluster's members one after
 // the other, eight rows in flight.  143 points into 9 clusters, 8 heads: 33 us, now 27.6; 9 into 1: 7.5 and 6.5 (before: points read from LDS each
 // time, offsets by one wavefront between two barriers of their own, a group per cluster whatever their number).
+// The nodes themselves follow in the same kernel: the members' lists are in LDS, and a launch and its first round trips are worth more than
+// the compute units that a workgroup per node would have.  143 nodes into 9 and 9 into 1: 27.6 and 6.5 us and
+// 5.7 for each's nodes in a kernel of their own, 31.8 and 8.9 together (and two launches less); prefill of 128K tokens 288 us, now 285.
 #define LC_KS_THREADS 1024        // a wavefront per 16 points, a 16-lane group per cluster
 #define LC_KS_MAX_N 224
 #define LC_KS_MAX_K 64
@@ -1490,10 +1578,10 @@ static_assert(LC_KS_MAX_N <= 16 * (LC_KS_THREADS / 64) && LC_KS_MAX_K <= LC_KS_T
 static inline size_t lc_kmeans_small_lds(int N, int k) {
     return (size_t)((N > 0 ? N : 1) + ((k + 15) & ~15)) * LC_AS_ROW * sizeof(float);
 }
+template <bool NODES>
 __global__ void __launch_bounds__(LC_KS_THREADS)
-lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* cent, int cent_cap, int iters,
-                       int x_rows) {
-    lc_fetch_args<sizeof(LcDev) + 40>();
+lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, LcNodeArgs w, int iters, int x_rows) {
+    lc_fetch_args<sizeof(LcDev) + 32 + sizeof(LcNodeArgs)>();
     extern __shared__ __attribute__((aligned(16))) float ks_dyn[];   // x_rows point rows, then the centroid rows
     __shared__ int lab[LC_KS_MAX_N];
     __shared__ int count[LC_KS_MAX_K];
@@ -1515,7 +1603,7 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* ce
         const int i = v / (LC_D / 4), q = v % (LC_D / 4);
         *reinterpret_cast<float4*>(X + i * LC_AS_ROW + 4 * q) = *reinterpret_cast<const float4*>(P + (size_t)i * LC_D + 4 * q);
     }
-    for (int i = tid; i < N; i += LC_KS_THREADS) lab[i] = 0;
+    for (int i = tid; i < N; i += LC_KS_THREADS) { lab[i] = 0; mem[i] = (unsigned short)i; }
     if (tid < 2) changed[tid] = 0;
     __syncthreads();
     for (int v = tid; v < k16 * LC_D; v += LC_KS_THREADS) {
@@ -1532,6 +1620,7 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* ce
         for (int t = 0; t < 8; ++t) xa[t] = *reinterpret_cast<const float4*>(row + 16 * t);
     }
     __syncthreads();
+    int n_c = lane == 0 ? N : 0, first = 0;                         // lane c: members of cluster c, where its list begins
     for (int it = 0; it < iters; ++it) {
         if (i0 < N) {
             float best[4];
@@ -1569,8 +1658,9 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* ce
             if (lane == 0) count[c] = n;
         }
         __syncthreads();
-        const int n_c = lane < k ? count[lane] : 0, room = (n_c + 7) & ~7;
-        const int first = lc_wave_scan_incl(room) - room;           // lane c: where cluster c's list begins
+        n_c = lane < k ? count[lane] : 0;
+        const int room = (n_c + 7) & ~7;
+        first = lc_wave_scan_incl(room) - room;
         for (int c = wave; c < k; c += LC_KS_THREADS / 64) {
             int at = lc_readlane(first, c);
             for (int r = 0; r < rounds; ++r) {
@@ -1637,93 +1727,46 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, float* ce
         __syncthreads();
     }
     for (int i = tid; i < N; i += LC_KS_THREADS) ix.parent[l][(size_t)bh * ix.cap[l] + i] = lab[i];
-    for (int v = tid; v < k * LC_D; v += LC_KS_THREADS)
-        cent[(size_t)bh * cent_cap * LC_D + v] = cs[(v / LC_D) * LC_AS_ROW + (v % LC_D)];
-}
-
-// What is stored of node u of level l + 1 except its radius: center (mean of the descendant chunks'
-// centers; the centroid for the unit geometry and for a node without chunks), counts, unit direction (the
-// next level's point); the radius starts at -inf.  Called by one 16-lane group.
-struct LcNodeArgs {
-    const float* cent;       // this level's centroids
-    int cent_cap;
-    int geometry;
-    LcPointRows next;        // the next level's points and starting centroids
-};
-template <typename Acc>
-__device__ __forceinline__ void lc_write_node(const LcDev& ix, int b, int bh, int l, int u, int n_chunks, int n_tok,
-                                              const Acc (&sum)[8], const LcNodeArgs& w) {
-    const int sub = threadIdx.x & 15;
-    float mu[8];
-    if (n_chunks > 0 && w.geometry == LC_GEOMETRY_TOKEN_BALL) {
-        const Acc inv = (Acc)1 / (Acc)n_chunks;
+    // ---- the nodes: the lists are those of the labels as they stand.  A wavefront per node, its groups taking the members in turn, or
+    // beyond 16 nodes a group each; four rows per group in flight.
+    const bool wide = k <= LC_KS_THREADS / 64;
+    const int c = wide ? wave : grp;
+    const int n = __shfl(n_c, min(c, 63)), at = __shfl(first, min(c, 63));     // (while every lane is there)
+    if (c >= k) return;
+    const LcMembers<NODES> m(ix, b, bh, l);
+    const int step = wide ? 4 : 1;
+    double sum[8];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) mu[t] = (float)(sum[t] * inv);
-    } else if (lc_level_count(ix, b, bh, l) > 0) {
-        lc_load8(w.cent + ((size_t)bh * w.cent_cap + u) * LC_D + 8 * sub, mu);
-    } else {                                                        // (a sequence without chunks: no centroid was started)
+    for (int t = 0; t < 8; ++t) sum[t] = 0.0;
+    for (int q = wide ? kk : 0; q < n; q += 4 * step) {
+        float x[4][8];
+        int weight[4];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) mu[t] = (sub == 0 && t == 0) ? 1.f : 0.f;
+        for (int e = 0; e < 4; ++e) weight[e] = m.row((int)mem[at + min(q + step * e, n - 1)], 8 * sub, x[e]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (q + step * e < n) lc_add_row(sum, x[e], weight[e]);
     }
-    const size_t n = (size_t)bh * ix.cap[l + 1] + u;
-    lc_store8(ix.center[l + 1] + n * LC_D + 8 * sub, mu);
-    float d[8];
-    lc_unit_frag(mu, sub, d);
-    if (w.next.pts)
-        lc_store_point(w.next, bh, u, ix.nlev[b * LC_MAX_LEVELS + l + 1], ix.nlev[b * LC_MAX_LEVELS + l + 2], sub, d);
-    if (sub == 0) {
-        ix.radius[l + 1][n] = LC_NEG_INF;
-        ix.rbuild[l + 1][n] = LC_NEG_INF;
-        ix.parent[l + 1][n] = -1;
-        ix.ntok[l + 1][n] = n_tok;
-        ix.nchunk[l + 1][n] = n_chunks;
+    int tok = 0, chunks = 0;
+    for (int q = wide ? lane : sub; q < n; q += 16 * step) {
+        const int i = mem[at + q];
+        tok += m.ntok[i];
+        chunks += m.chunks(i);
     }
+    tok = lc_sum16_i(tok);
+    chunks = lc_sum16_i(chunks);
+    if (wide) {
+        tok += __shfl_xor(tok, 16);
+        chunks += __shfl_xor(chunks, 16);
+        tok += __shfl_xor(tok, 32);
+        chunks += __shfl_xor(chunks, 32);
+#pragma unroll
+        for (int t = 0; t < 8; ++t) sum[t] += __shfl_xor(sum[t], 16);
+#pragma unroll
+        for (int t = 0; t < 8; ++t) sum[t] += __shfl_xor(sum[t], 32);
+    }
+    if (!wide || lane < 16) lc_write_node(ix, b, bh, l, c, chunks, tok, sum, w, cs + c * LC_AS_ROW);
 }
-
-// What a node of level l + 1 is made of: the chunks under it, or above the first level its child nodes, each weighted by
-// the chunks it holds: a child's center is their mean, so the weighted sum is the sum over all descendant chunks.  It is taken in
-// float64, so that its error is no larger than that of the float32 sum of the chunks (relative to the center, level 2 and
-// 3 of 2275 chunks: 8.8e-8 and 2.2e-7 as the chunks' sum, 7.0e-8 and 1.3e-7 now).  Children instead of chunks: 143 nodes into 9
-// and 9 into 1, 8 heads, 27 and 10 us, now 6.8 and 5.5; 5461 nodes into 249: 62 us, now 34.
-template <bool NODES>
-struct LcMembers {
-    const float* center;             // rows of the members: float32, or bfloat16 at the chunk level if `half`
-    const int* label;
-    const int* ntok;
-    const int* nchunk;               // NODES
-    bool half;
-    int n;
-    __device__ __forceinline__ LcMembers(const LcDev& ix, int b, int bh, int l) {
-        const size_t at = (size_t)bh * ix.cap[NODES ? l : 0];
-        half = !NODES && ix.c0_bf16 != 0;
-        center = half ? reinterpret_cast<const float*>(reinterpret_cast<const uint16_t*>(ix.center[0]) + at * LC_D)
-                      : ix.center[NODES ? l : 0] + at * LC_D;
-        label = ix.parent[NODES ? l : 0] + at;
-        ntok = ix.ntok[NODES ? l : 0] + at;
-        nchunk = NODES ? ix.nchunk[l] + at : nullptr;
-        n = NODES ? ix.nlev[b * LC_MAX_LEVELS + l] : ix.state[bh * 4 + 1];
-    }
-    // columns [col, col + COLS) of member j's row; returns its weight
-    template <int COLS>
-    __device__ __forceinline__ int row(int j, int col, float (&x)[COLS]) const {
-        const size_t o = (size_t)j * LC_D + col;
-        const uint16_t* const c16 = reinterpret_cast<const uint16_t*>(center);
-        if constexpr (COLS == 8) {
-            if (half) lc_unpack8(*reinterpret_cast<const uint4*>(c16 + o), x);
-            else lc_load8(center + o, x);
-        } else if (half) {
-            const uint32_t v = *reinterpret_cast<const uint32_t*>(c16 + o);
-            x[0] = lc_bf16_lo(v);
-            x[1] = lc_bf16_hi(v);
-        } else {
-            const float2 v = *reinterpret_cast<const float2*>(center + o);
-            x[0] = v.x;
-            x[1] = v.y;
-        }
-        return chunks(j);
-    }
-    __device__ __forceinline__ int chunks(int j) const { return NODES ? nchunk[j] : 1; }
-};
 
 // Centers of a level of many small nodes (LC_UPD_FEW members or fewer on average): a workgroup lists the
 // members of `per` nodes and gives each node to a 16-lane group.
@@ -1753,7 +1796,7 @@ lc_center_few_kernel(LcDev ix, int l, LcNodeArgs w, int per) {
                 for (int j = sub; j < m.n; j += 16)
                     if (m.label[j] == u) count(j);
             }
-            lc_write_node(ix, b, bh, l, u, lc_sum16_i(chunks), lc_sum16_i(tok), sum, w);
+            lc_write_node(ix, b, bh, l, u, lc_sum16_i(chunks), lc_sum16_i(tok), sum, w, w.centroid(bh, u));
         });
 }
 
@@ -1787,7 +1830,7 @@ lc_center_kernel(LcDev ix, int l, LcNodeArgs w) {
     if (tid < 16) {
         int n_tok = 0, n_chunks = 0;
         for (int v = 0; v < NT / 64; ++v) { n_tok += tok_sh[v]; n_chunks += chunk_sh[v]; }
-        lc_write_node(ix, b, bh, l, u, n_chunks, n_tok, sum, w);
+        lc_write_node(ix, b, bh, l, u, n_chunks, n_tok, sum, w, w.centroid(bh, u));
     }
 }
 
@@ -1907,14 +1950,17 @@ int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const i
         // that would be over a thousand workgroups that each read all the labels
         const int per = (maxK + LC_BG - 1) / LC_BG * BH > 1024 ? LC_UB_MAX : LC_BG;
         const dim3 per_grid((maxK + per - 1) / per, H, B);
-        if (maxN > 0 && maxN <= LC_KS_MAX_N && maxK <= LC_KS_MAX_K) {  // the whole clustering in one kernel
+        const LcNodeArgs w{cur.cent, cur.cent_cap, geometry, next};
+        if (maxN > 0 && maxN <= LC_KS_MAX_N && maxK <= LC_KS_MAX_K) {  // the whole level in one kernel
             const size_t lds = lc_kmeans_small_lds(maxN, maxK);
-            LC_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(&lc_kmeans_small_kernel),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-            hipLaunchKernelGGL(lc_kmeans_small_kernel, dim3(H, B), dim3(LC_KS_THREADS), lds, stream, ix, l,
-                               (const float*)cur.pts, cur.cap, cur.cent, cur.cent_cap, iters, maxN);
+            const auto kernel = l == 0 ? &lc_kmeans_small_kernel<false> : &lc_kmeans_small_kernel<true>;
+            LC_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+            hipLaunchKernelGGL(kernel, dim3(H, B), dim3(LC_KS_THREADS), lds, stream, ix, l, (const float*)cur.pts, cur.cap, w, iters, maxN);
             LC_HIP_CHECK(hipGetLastError());
-        } else if (maxN > 0) {
+            cur = next;
+            continue;
+        }
+        if (maxN > 0) {
             // Many centroids: 64 MA points per workgroup.  The fuller a wavefront's A operand, the fewer LDS reads per
             // product (LDS bandwidth for two blocks of products with MA = 1); MA is the one with the least work on the
             // busiest compute unit, the larger one if equal.
@@ -1978,7 +2024,6 @@ int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const i
             }
             LC_HIP_CHECK(hipGetLastError());
         }
-        const LcNodeArgs w{cur.cent, cur.cent_cap, geometry, next};
         auto center = [&](auto nodes) {
             constexpr bool NODES = decltype(nodes)::value;
             if (few)

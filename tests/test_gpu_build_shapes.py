@@ -94,6 +94,21 @@ def test_first_two_iterations(H, chunks, F):
             check_tree(s2["heads"][h])
 
 
+@pytest.mark.parametrize("centers", [0, 1])
+@pytest.mark.parametrize("chunks,F", [([200, 1], 4), ([224], 14), ([16], 16), ([150, 30], 9)])
+def test_small_levels_without_iterations(chunks, F, centers):
+    """Every chunk in node 0, whose center is their mean; the other nodes keep their starting centroid."""
+    for s, n in zip(build(2, chunks, F, 0, centers=centers), chunks):
+        for lev in s["heads"]:
+            x = lev[0]["center"].astype(np.float64)
+            k = len(lev[1]["radius"])
+            assert not lev[0]["parent"].any() and lev[1]["nchunk"].tolist() == [n] + [0] * (k - 1)
+            assert lev[1]["ntok"][0] == lev[0]["ntok"].sum()
+            want = np.concatenate([x.mean(axis=0)[None], unit(x)[(np.arange(1, k) * n) // k]])
+            # a sum in float64 rounded once; a direction from a float32 norm of 128 squares
+            assert np.abs(lev[1]["center"] - want).max() <= 2.0 ** -20 * np.abs(want).max()
+
+
 @pytest.mark.parametrize("iters", [2, 4, 8])
 @pytest.mark.parametrize("H,chunks,F,level,config", [
     (2, [143, 16, 9], 16, 0, {}), (2, [224, 65, 8], 14, 0, {}), (2, [224, 33, 7], 4, 0, {}), (1, [200], 12, 0, {}), (1, [225], 15, 0, {}), (2, [640, 256, 64], 10, 0, {}), (2, [1281, 1279], 9, 0, {}), (8, [2275], 16, 0, {}), (1, [4096], 17, 0, {}),
