@@ -1836,23 +1836,33 @@ lc_center_kernel(LcDev ix, int l, LcNodeArgs w) {
 
 // Radii of all levels above the chunks, once every center stands: for each chunk and each of its
 // ancestors the reach |center - ancestor's center| + chunk radius, maximum per node.  One pass over the
-// chunk rows instead of one per level.  Levels of few nodes collect their maxima in LDS first, so that the
-// top node is not one address that every chunk of the head queues for.  Radii are >= 0 (what is not a number is left
-// out, as fmaxf would), so their bits order like integers, and a maximum does not depend on the order.
-#define LC_RD_CHUNKS 64           // chunks of a workgroup
-#define LC_RD_LDS 512             // nodes (levels >= 2 together) whose maxima are collected in LDS
+// chunk rows instead of one per level.  Levels of few nodes collect their maxima in LDS first -- all levels if together they have
+// no more than LC_RD_LDS nodes, else those above level 1 --, so that a node is not one address that every chunk under it queues
+// for: the atomics are the larger part of the time where they go to memory, two per chunk and level (radius and its copy for the drift).
+// Radii are >= 0 (what is not a number is left out, as fmaxf would), so their bits order like integers, and a maximum does not
+// depend on the order.
+// PER chunks per 16-lane group: 4 while that gives each compute unit no more than one workgroup, 8 beyond (more rows in flight).  us with level 1 in
+// memory and 4 per group; in LDS with 4; with 8: 820 chunks x 8 heads under 52 nodes 7.5, 5.8, 7.7; 2299 x 8 under 143 13.0, 11.6, 11.2; 64 pairs
+// of up to 1820 under 57 18.4, 10.8, 11.0; 10.9 K x 8 under 5461 (level 1 in memory all the same) 29, 30, 23.3.
+#define LC_RD_LDS 512             // nodes whose maxima are collected in LDS
+template <int PER>
 __global__ void __launch_bounds__(LC_BT)
 lc_radius_kernel(LcDev ix) {
+    constexpr int CHUNKS = PER * LC_BG;                             // of a workgroup
     lc_fetch_args<sizeof(LcDev)>();
     __shared__ int best[LC_RD_LDS];
     const int h = blockIdx.y, b = blockIdx.z;
     const int bh = b * ix.H + h;
     const int tid = threadIdx.x, sub = tid & 15, grp = tid >> 4;
     const int M = ix.state[bh * 4 + 1];
-    if ((int)blockIdx.x * LC_RD_CHUNKS >= M) return;
+    if ((int)blockIdx.x * CHUNKS >= M) return;
     const size_t cb = (size_t)bh * ix.cap[0];
-    int n_up = 0;                                                   // nodes above level 1, in level order
-    for (int l = 2; l < ix.L; ++l) n_up += ix.nlev[b * LC_MAX_LEVELS + l];
+    int n_up = 0, lowest = 1;                                       // nodes of level `lowest` and above, in level order
+    for (int l = 1; l < ix.L; ++l) n_up += ix.nlev[b * LC_MAX_LEVELS + l];
+    if (n_up > LC_RD_LDS) {
+        n_up -= ix.nlev[b * LC_MAX_LEVELS + 1];
+        lowest = 2;
+    }
     const bool in_lds = n_up <= LC_RD_LDS;
     if (in_lds) {
         for (int i = tid; i < n_up; i += LC_BT) best[i] = -1;
@@ -1862,12 +1872,11 @@ lc_radius_kernel(LcDev ix) {
         atomicMax(reinterpret_cast<int*>(ix.radius[l]) + (size_t)bh * ix.cap[l] + a, bits);
         atomicMax(reinterpret_cast<int*>(ix.rbuild[l]) + (size_t)bh * ix.cap[l] + a, bits);
     };
-    constexpr int PER = LC_RD_CHUNKS / LC_BG;
     float c[PER][8], r0[PER];
     int anc[PER];
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
-        const int j = min((int)blockIdx.x * LC_RD_CHUNKS + e * LC_BG + grp, M - 1);
+        const int j = min((int)blockIdx.x * CHUNKS + e * LC_BG + grp, M - 1);
         anc[e] = ix.parent[0][cb + j];
         lc_c0_load8(ix, cb + j, sub, c[e]);
         r0[e] = ix.radius[0][cb + j];
@@ -1890,16 +1899,16 @@ lc_radius_kernel(LcDev ix) {
             d2 = lc_sum16(d2);
             const float reach = lc_pad_radius(lc_pad_radius(sqrtf(d2)) + r0[e]);
             if (sub == 0 && anc[e] >= 0 && reach >= 0.f) {          // (not a number: reaches nothing)
-                if (l >= 2 && in_lds) atomicMax(&best[up + anc[e]], __float_as_int(reach));
+                if (l >= lowest && in_lds) atomicMax(&best[up + anc[e]], __float_as_int(reach));
                 else raise(l, anc[e], __float_as_int(reach));
             }
             anc[e] = anc[e] >= 0 ? next[e] : -1;
         }
-        if (l >= 2) up += ix.nlev[b * LC_MAX_LEVELS + l];
+        if (l >= lowest) up += ix.nlev[b * LC_MAX_LEVELS + l];
     }
     if (in_lds) {
         __syncthreads();
-        int l = 2, o = 0;
+        int l = lowest, o = 0;
         for (int i = tid; i < n_up; i += LC_BT) {
             while (i - o >= ix.nlev[b * LC_MAX_LEVELS + l]) { o += ix.nlev[b * LC_MAX_LEVELS + l]; ++l; }
             if (best[i] >= 0) raise(l, i - o, best[i]);
@@ -2039,7 +2048,9 @@ int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const i
         cur = next;
     }
     if (L > 1 && max_M > 0) {
-        hipLaunchKernelGGL(lc_radius_kernel, dim3((max_M + LC_RD_CHUNKS - 1) / LC_RD_CHUNKS, H, B), dim3(LC_BT), 0, stream, ix);
+        const int per = (max_M + 4 * LC_BG - 1) / (4 * LC_BG) * BH <= LC_COMPUTE_UNITS ? 4 : 8;
+        hipLaunchKernelGGL(per == 4 ? lc_radius_kernel<4> : lc_radius_kernel<8>, dim3((max_M + per * LC_BG - 1) / (per * LC_BG), H, B),
+                           dim3(LC_BT), 0, stream, ix);
         LC_HIP_CHECK(hipGetLastError());
     }
     return LC_OK;

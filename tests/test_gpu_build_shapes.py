@@ -72,7 +72,7 @@ SHAPES = [(8, [225], 15), (8, [640, 1], 15), (2, [700, 65], 16), (2, [1000], 11)
           (1, [1500], 8), (2, [1281], 5), (8, [4500, 300], 32), (8, [4160], 20), (1, [514], 2), (2, [777, 3], 2),
           (8, [2200, 2100], 4), (8, [5001, 4097], 8), (8, [10922], 2), (8, [4160], 33), (8, [4160], 22), (8, [5300], 20),
           (8, [5300, 700], 17), (4, [2050, 2048], 2),
-          (8, [4160, 100], 17), (8, [4224], 16)]
+          (8, [4160, 100], 17), (8, [4224], 16), (2, [2048], 4), (2, [2052], 4)]
 
 
 @pytest.mark.parametrize("H,chunks,F", SHAPES)
