@@ -391,8 +391,8 @@ lc_upper_kernel(const LcRetrieveArgs a) {
 //     LDS or memory costs a wait for both); a list longer than `list_slots` goes to the workspace.
 // 10.9 K chunks under 5461 and 249 nodes, 43 and 8 of them kept, 8 heads: 34.7 us with a copy of the code per level,
 // every node scored by itself and ranks by counting, 25.2 us now; 2275 chunks under four levels: 26 and 24.4 us.
-// A flat scan of up to this many chunks is the same with one level: no hand-off between workgroups (48 chunks:
-// 8.0 us as lc_leaf_kernel, 6.8 us here); beyond, one compute unit's scoring and cut cost more (240: 9.0 and 10.1 us).
+// A flat scan of up to this many chunks is the same with one level: one kernel (8 heads of 48 chunks: 7.6 us as scoring and
+// selection, 6.7 here; of 63 7.3 and 6.7); beyond, one compute unit's scoring and cut cost more (240: 6.7 and 10.1 us).
 #define LC_FLAT_MAX_CHUNKS 64
 #define LC_BM_THREADS 1024
 #define LC_BM_WAVES (LC_BM_THREADS / 64)
