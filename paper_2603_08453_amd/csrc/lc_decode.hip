@@ -19,7 +19,9 @@
 //   registers), now about 100 and 64 cycles of the matrix pipe, and the groups' sums need
 //   no combining.  A step: 18.1 -> 16.9 us (4 x 32K tokens), 20.2 -> 19.2 (128K), 29.9 ->
 //   27.6 (16 ragged sequences, group size 7).  Relative error against float64 over steps
-//   of the sizes in use: 3.88e-7, on the vector ALU 3.91e-7.
+//   of the sizes in use: 3.88e-7, on the vector ALU 3.91e-7 (both with logits rounded before
+//   the reference was subtracted; random steps of 300 to 20000 tokens at group size 4: 2.40e-7
+//   then, 2.35e-7 with one rounding, the log-sum-exp 4.0e-7 and 2.6e-7).
 #include <type_traits>
 
 #include "lc_device.h"
@@ -33,6 +35,7 @@
 #define LC_DEC_GROUPS (LC_DEC_THREADS / 16)
 #define LC_DEC_MAX_SPLITS 256
 #define LC_DEC_TILE 1024          // tokens of a split whose cache rows are resolved into LDS at a time
+#define LC_DEC_LAG 8              // powers of two that a logit may lie above the softmax's reference
 #define LC_DEC_E 2                // selected ids per thread and pass of the row resolution
 #define LC_LOG2E 1.4426950408889634f
 #define LC_LN2 0.6931471805599453f
@@ -103,8 +106,13 @@ __device__ __forceinline__ float lc_max_groups(float v) {
     const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
-// exp2 of (x - ref) where x may be -inf (gives 0); ref is finite.
-__device__ __forceinline__ float lc_exp2_rel(float x, float ref) { return exp2f(x - ref); }
+// 2^(x - LC_DEC_LAG) of a logit that lies x above its reference, -inf included: at most 1 where x is at most LC_DEC_LAG, so that P.V
+// overflows no sooner than the values' own sum.  (The exponent is lowered behind the exponential and not in x, which would lose its lowest
+// bits, by the factor that keeps small results out of the instruction's reach of zero: no instruction more than without.)
+__device__ __forceinline__ float lc_probability(float x) {
+    const bool small = x < -64.f;
+    return __builtin_amdgcn_exp2f(x + (small ? 64.f : 0.f)) * (small ? __builtin_ldexpf(1.f, -64 - LC_DEC_LAG) : __builtin_ldexpf(1.f, -LC_DEC_LAG));
+}
 
 // FUSED = false: the chunk list comes from a.ids / a.counts.  FUSED = true: every workgroup first
 // repeats the budget selection of its (sequence, head) from the chunk score keys -- the same
@@ -362,19 +370,19 @@ lc_decode_kernel(const LcDecodeArgs a) {
         // one online-softmax update of this lane's head with the logits of batches it and it + 1 (N = 8) or it alone (N = 4)
         auto softmax = [&](auto count, int it, lc_f32x4 dA, lc_f32x4 dB, auto& p) LC_INLINE {
             constexpr int N = decltype(count)::value;
-            float x[N];
+            float x[N];                                             // logits, not yet scaled
             float mx = LC_NEG_INF;
 #pragma unroll
             for (int u = 0; u < N; ++u) {
-                x[u] = (tv + it * U + u < tv_end) ? (u < U ? dA[u % U] : dB[u % U]) * scale : LC_NEG_INF;
+                x[u] = (tv + it * U + u < tv_end) ? (u < U ? dA[u % U] : dB[u % U]) : LC_NEG_INF;
                 mx = fmaxf(mx, x[u]);
             }
-            mx = lc_max_groups(mx);
-            // The reference follows the maximum only when it falls behind by more than 2^8 (probabilities up to that size lose
-            // nothing in float32): the accumulators are scaled once or not at all per split instead of once per step.
-            if (__ballot(mx > m_ref + 8.0f) != 0ull) {
-                const float m_new = fmaxf(mx, m_ref);
-                const float sc = (m_new == LC_NEG_INF) ? 1.f : lc_exp2_rel(m_ref, m_new);
+            mx = lc_max_groups(mx) * scale;
+            // The reference follows the maximum only when it falls behind by more than LC_DEC_LAG: the accumulators are scaled once or
+            // not at all per split instead of once per step.  It is a whole number, so that scaling rounds nothing.
+            if (__ballot(mx > m_ref + (float)LC_DEC_LAG) != 0ull) {
+                const float m_new = mx > m_ref + (float)LC_DEC_LAG ? ceilf(mx) : m_ref;
+                const float sc = (m_new == LC_NEG_INF) ? 1.f : exp2f(m_ref - m_new);
                 const bool started = __ballot(m_ref > LC_NEG_INF) != 0ull;
                 m_ref = m_new;
                 if (started) {                                      // (before that the accumulators are zero)
@@ -389,7 +397,7 @@ lc_decode_kernel(const LcDecodeArgs a) {
             }
             const float ref = (m_ref == LC_NEG_INF) ? 0.f : m_ref;
 #pragma unroll
-            for (int u = 0; u < N; ++u) p[u] = lc_exp2_rel(x[u], ref);
+            for (int u = 0; u < N; ++u) p[u] = lc_probability(fmaf(x[u], scale, -ref));
             float l = (p[0] + p[1]) + (p[2] + p[3]);
             if constexpr (N == 8) l += (p[4] + p[5]) + (p[6] + p[7]);
             l_run += l;
@@ -639,7 +647,11 @@ lc_decode_kernel(const LcDecodeArgs a) {
         const size_t o = ((size_t)b * ix.H * G + (size_t)h * G + g);
         *reinterpret_cast<float4*>(a.out + o * LC_D + 4 * c4) =
             make_float4(acc4.x * inv, acc4.y * inv, acc4.z * inv, acc4.w * inv);
-        if (a.lse && c4 == 0) a.lse[o] = den > 0.f ? (m_all + log2f(den)) * LC_LN2 : LC_NEG_INF;
+        if (a.lse && c4 == 0) {
+            int e;                                              // (whole powers of two aside, the logarithm is of a number near 1)
+            const float part = frexpf(den, &e);
+            a.lse[o] = den > 0.f ? fmaf(m_all + (float)(e + LC_DEC_LAG), LC_LN2, logf(part)) : LC_NEG_INF;
+        }
     }
     if (tid == 0) ix.sync[bh * 4 + 1] = 0;
 }

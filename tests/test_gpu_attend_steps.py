@@ -57,3 +57,62 @@ def test_against_float64(tokens, splits, G):
     assert (got[heavy, 5] == float("inf")).all() and (got[heavy, 77] == float("-inf")).all()
     rest = [c for c in range(128) if c not in (5, 77)]
     assert torch.equal(got[:, rest], out[:, rest])
+
+
+def _attend(q, K, V, splits):
+    """Output and log-sum-exp of a step that attends to every token of one sequence, float64 on the CPU."""
+    import torch
+    from paper_2603_08453_amd import binding as lc
+    H, T = K.shape[1], K.shape[2]
+    bounds = np.unique(np.concatenate([[0], np.arange(7, T, 13), [max(0, T - 3)]])).astype(np.int32)      # (an open tail)
+    cfg = lc.lc_config_default(levels=2, fanout=8, kmeans_iters=1, max_chunks=max(1, len(bounds)), max_tokens=T, decode_splits=splits)
+    ib = torch.zeros(lc.lc_index_bytes(cfg, 1, H), dtype=torch.uint8, device="cuda")
+    ws = torch.zeros(lc.lc_workspace_bytes(cfg, 1, q.shape[1], H), dtype=torch.uint8, device="cuda")
+    idx = lc.lc_build_index(cfg, K, [T], [bounds], ib, ws)
+    out = torch.full((1, q.shape[1], 128), float("nan"), device="cuda")
+    lse = torch.full((1, q.shape[1]), float("nan"), device="cuda")
+    lc.lc_decode_step(idx, q, K, V, 10 ** 6, out, ws, lse=lse)
+    return out[0].double().cpu(), lse[0].double().cpu()
+
+
+def _aimed(logits, G):
+    """One-hot queries and keys of one KV head: `logits` (base 2) for head 0, 15/16 of it and so on for the next; the logits as they come out."""
+    import torch
+    q, K = torch.zeros((1, G, 128)), torch.zeros((1, 1, len(logits), 128))
+    q[0, :, 0] = 1 - torch.arange(G) / 16
+    K[0, 0, :, 0] = torch.as_tensor(logits, dtype=torch.float32) * float(np.log(2.0) * 128 ** 0.5)
+    K = K.to(torch.bfloat16)
+    x = q[0, :, :1].double() * K[0, 0, :, 0].double() / 128 ** 0.5
+    return q.to(torch.bfloat16).cuda(), K.cuda(), x
+
+
+@pytest.mark.parametrize("G", [1, 4, 7])
+@pytest.mark.parametrize("tokens,splits", [(40, 1), (129, 1), (200, 1), (1025, 1), (2500, 2), (700, 0)])
+def test_large_and_small_values(tokens, splits, G):
+    """Every 64th token weighs some 2^7.5 times the others, late in its lane group's slice: the softmax's reference, set at the first tokens,
+    does not move.  A column's largest value sits there alone, up to the largest of bfloat16: the result lies below it."""
+    import torch
+    T = tokens
+    heavy = np.unique(np.concatenate([np.arange(63, T, 64), [T - 1]]))
+    logits = np.zeros(T)
+    logits[heavy] = 7.5
+    q, K, x = _aimed(logits, G)
+    p = torch.softmax(x, dim=-1)
+    gen = torch.Generator()
+    gen.manual_seed(T + G)
+    noise = torch.randn((T, 128), generator=gen).clamp(-4, 4)
+    noise[heavy] = 0.0
+    for scale in (2.0 ** 127, -1.9921875 * 2.0 ** 127, 2.0 ** -110):
+        V = noise * (2.0 ** -14 * scale)                            # (a column's other values together stay below the one)
+        for c in range(128):
+            V[heavy[c % len(heavy)], c] = scale
+        V = V.to(torch.bfloat16).cuda()[None, None].contiguous()
+        out, lse = _attend(q, K, V, splits)
+        v = V[0, 0].double().cpu()
+        # as above; and of values this small a sum is cut off at the last bit of float32's range, at most once per product and
+        # term of its probability, divided by a sum of probabilities that are 2^-9 and more where they are largest
+        rel = 2.0 * (2.0 ** -21 * x.abs().amax(dim=-1) + 2.0 ** -20)
+        bound = rel[:, None] * (p @ v.abs()) + 3 * T * 2.0 ** -149 * 2.0 ** 9
+        assert torch.isfinite(out).all()
+        assert ((out - p @ v).abs() <= bound).all(), ((out - p @ v).abs() / bound).max()
+        assert ((lse - torch.logsumexp(x, dim=-1)).abs() <= rel + 2.0 ** -22 * lse.abs()).all()
