@@ -36,6 +36,7 @@
 #define LC_DEC_MAX_SPLITS 256
 #define LC_DEC_TILE 1024          // tokens of a split whose cache rows are resolved into LDS at a time
 #define LC_DEC_LAG 8              // powers of two that a logit may lie above the softmax's reference
+#define LC_DEC_FAINT -102.f       // logits that lie further below the reference have probabilities that lc_split3 does not hold (below 2^-110)
 #define LC_DEC_E 2                // selected ids per thread and pass of the row resolution
 #define LC_LOG2E 1.4426950408889634f
 #define LC_LN2 0.6931471805599453f
@@ -68,7 +69,9 @@ struct LcDecodeArgs {
 
 // N probabilities as three bfloat16 terms each, packed in pairs: t[s] holds the terms number s.  The three add up to
 // the float32 value exactly: each takes the upper eight of the bits that are left, and where those are all of them, one unit less, so
-// that something is left (a term of zero would turn an infinite V into a not-a-number).
+// that something is left (a term of zero would turn an infinite V into a not-a-number).  Below 2^-110 the lowest bits have no
+// place in bfloat16's range: where such a probability meets a value of 2^64 or more, infinities among them, the split is done
+// again on the vector ALU (attend_plain) by the workgroup that merges; smaller values are off by less than 2^-69.
 template <int N>
 __device__ __forceinline__ void lc_split3(const float (&p)[N], int (&t)[3][N / 2]) {
     float r[N];
@@ -113,6 +116,10 @@ __device__ __forceinline__ float lc_probability(float x) {
     const bool small = x < -64.f;
     return __builtin_amdgcn_exp2f(x + (small ? 64.f : 0.f)) * (small ? __builtin_ldexpf(1.f, -64 - LC_DEC_LAG) : __builtin_ldexpf(1.f, -LC_DEC_LAG));
 }
+
+// What a sum is scaled by when its reference moves from `from` up to `to`: a power of two, at least the smallest number there is, so
+// that an infinite sum stays one.
+__device__ __forceinline__ float lc_rescale(float from, float to) { return fmaxf(exp2f(from - to), __builtin_ldexpf(1.f, -149)); }
 
 // FUSED = false: the chunk list comes from a.ids / a.counts.  FUSED = true: every workgroup first
 // repeats the budget selection of its (sequence, head) from the chunk score keys -- the same
@@ -297,153 +304,201 @@ lc_decode_kernel(const LcDecodeArgs a) {
     int S_eff = (n_tok + LC_DEC_MIN_TOKENS_PER_SPLIT - 1) / LC_DEC_MIN_TOKENS_PER_SPLIT;
     S_eff = max(1, min(S, S_eff));
 
-    if (s < S_eff) {
-        const int lo = (int)(((long long)n_tok * s) / S_eff);
-        const int hi = (int)(((long long)n_tok * (s + 1)) / S_eff);
-        const float scale = 0.08838834764831845f * LC_LOG2E;     // log2(e) / sqrt(128)
-        // Softmax state of head `sub` (lanes sub >= G repeat head G - 1): the reference that is subtracted from the
-        // logits, one for the wavefront's tokens, and the sum over this group's tokens.  acc[c][r]: columns
-        // 8 sub + c of head 4 q4 + r over the wavefront's tokens.
-        float m_ref = LC_NEG_INF, l_run = 0.f;
-        lc_f32x4 acc[8];
+    const float scale = 0.08838834764831845f * LC_LOG2E;     // log2(e) / sqrt(128)
+    // Softmax state of head `sub` (lanes sub >= G repeat head G - 1): the reference that is subtracted from the
+    // logits, one for the wavefront's tokens, and the sum over this group's tokens.  acc[c][r]: columns
+    // 8 sub + c of head 4 q4 + r over the wavefront's tokens.
+    float m_ref = LC_NEG_INF, l_run = 0.f;
+    lc_f32x4 acc[8];
 #pragma unroll
-        for (int c = 0; c < 8; ++c) acc[c] = lc_f32x4{0.f, 0.f, 0.f, 0.f};
-        // K and V of this (sequence, head) as buffer resources: one 32-bit byte offset per row
-        // (the host has checked that the slab spans less than 2 GiB)
-        // (the resources end with the last row the index may ever hold, so a wrong row cannot fault)
-        const int row_bytes = (int)a.ks_tok * 2;
-        const int slab_bytes = (a.max_tokens - 1) * row_bytes + LC_D * 2;
-        const __amdgpu_buffer_rsrc_t Kr = lc_buffer(a.K + (size_t)b * a.ks_seq + (size_t)h * a.ks_head, slab_bytes);
-        const __amdgpu_buffer_rsrc_t Vr = lc_buffer(a.V + (size_t)b * a.ks_seq + (size_t)h * a.ks_head, slab_bytes);
+    for (int c = 0; c < 8; ++c) acc[c] = lc_f32x4{0.f, 0.f, 0.f, 0.f};
+    // K and V of this (sequence, head) as buffer resources: one 32-bit byte offset per row
+    // (the host has checked that the slab spans less than 2 GiB)
+    // (the resources end with the last row the index may ever hold, so a wrong row cannot fault)
+    const int row_bytes = (int)a.ks_tok * 2;
+    const int slab_bytes = (a.max_tokens - 1) * row_bytes + LC_D * 2;
+    const __amdgpu_buffer_rsrc_t Kr = lc_buffer(a.K + (size_t)b * a.ks_seq + (size_t)h * a.ks_head, slab_bytes);
+    const __amdgpu_buffer_rsrc_t Vr = lc_buffer(a.V + (size_t)b * a.ks_seq + (size_t)h * a.ks_head, slab_bytes);
 
-        // A lane loads K for token (sub & 3) of group (sub >> 2) of its wavefront -- row `sub` of the
-        // MFMA A operand -- and V for the tokens of its own group.
-        const int gk = (wave << 2) + (sub >> 2), uk = sub & 3;
-        int tv = 0, tv_end = 0, tk = 0, tk_end = 0;
-        // Two batches' loads, branch-free: a branch around a load would put each row lookup (an LDS read) and its load in a
-        // basic block of its own, waited for one after the other.  All row lookups go out together (slot 0 stands in where
-        // there is no token; the empty statement keeps the compiler from guarding them) and a load without a token gets
-        // an offset past the resource's end, which the range check answers with zeros.
-        auto k_offsets = [&](int it, int (&o)[2]) LC_INLINE {
+    // A lane loads K for token (sub & 3) of group (sub >> 2) of its wavefront -- row `sub` of the
+    // MFMA A operand -- and V for the tokens of its own group.
+    const int gk = (wave << 2) + (sub >> 2), uk = sub & 3;
+    int tv = 0, tv_end = 0, tk = 0, tk_end = 0;
+    // Two batches' loads, branch-free: a branch around a load would put each row lookup (an LDS read) and its load in a
+    // basic block of its own, waited for one after the other.  All row lookups go out together (slot 0 stands in where
+    // there is no token; the empty statement keeps the compiler from guarding them) and a load without a token gets
+    // an offset past the resource's end, which the range check answers with zeros.
+    auto k_offsets = [&](int it, int (&o)[2]) LC_INLINE {
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int tok = tk + (it + i) * U + uk;
-                int row = rw.row[tok < tk_end ? tok : 0];
-                asm volatile("" : "+v"(row));
-                o[i] = tok < tk_end ? row * row_bytes + 16 * q4 : slab_bytes;
-            }
-        };
-        auto v_offsets = [&](int it, int (&o)[2 * U]) LC_INLINE {
-            int row[2 * U];
+        for (int i = 0; i < 2; ++i) {
+            const int tok = tk + (it + i) * U + uk;
+            int row = rw.row[tok < tk_end ? tok : 0];
+            asm volatile("" : "+v"(row));
+            o[i] = tok < tk_end ? row * row_bytes + 16 * q4 : slab_bytes;
+        }
+    };
+    auto v_offsets = [&](int it, int (&o)[2 * U]) LC_INLINE {
+        int row[2 * U];
 #pragma unroll
-            for (int u = 0; u < 2 * U; ++u) {
-                const int tok = tv + it * U + u;
-                row[u] = rw.row[tok < tv_end ? tok : 0];
-            }
+        for (int u = 0; u < 2 * U; ++u) {
+            const int tok = tv + it * U + u;
+            row[u] = rw.row[tok < tv_end ? tok : 0];
+        }
 #pragma unroll
-            for (int u = 0; u < 2 * U; ++u) {
-                asm volatile("" : "+v"(row[u]));
-                o[u] = tv + it * U + u < tv_end ? row[u] * row_bytes + 16 * sub : slab_bytes;
-            }
-        };
-        auto load_k = [&](const int (&o)[2], lc_v4i (&kA)[4], lc_v4i (&kB)[4]) LC_INLINE {
+        for (int u = 0; u < 2 * U; ++u) {
+            asm volatile("" : "+v"(row[u]));
+            o[u] = tv + it * U + u < tv_end ? row[u] * row_bytes + 16 * sub : slab_bytes;
+        }
+    };
+    auto load_k = [&](const int (&o)[2], lc_v4i (&kA)[4], lc_v4i (&kB)[4]) LC_INLINE {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) kA[j] = __builtin_amdgcn_raw_buffer_load_b128(Kr, o[0] + 64 * j, 0, 0);
+        for (int j = 0; j < 4; ++j) kA[j] = __builtin_amdgcn_raw_buffer_load_b128(Kr, o[0] + 64 * j, 0, 0);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) kB[j] = __builtin_amdgcn_raw_buffer_load_b128(Kr, o[1] + 64 * j, 0, 0);
-        };
-        auto load_v = [&](const int (&o)[2 * U], lc_v4i (&vA)[U], lc_v4i (&vB)[U]) LC_INLINE {
+        for (int j = 0; j < 4; ++j) kB[j] = __builtin_amdgcn_raw_buffer_load_b128(Kr, o[1] + 64 * j, 0, 0);
+    };
+    auto load_v = [&](const int (&o)[2 * U], lc_v4i (&vA)[U], lc_v4i (&vB)[U]) LC_INLINE {
 #pragma unroll
-            for (int u = 0; u < U; ++u) vA[u] = __builtin_amdgcn_raw_buffer_load_b128(Vr, o[u], 0, 0);
+        for (int u = 0; u < U; ++u) vA[u] = __builtin_amdgcn_raw_buffer_load_b128(Vr, o[u], 0, 0);
 #pragma unroll
-            for (int u = 0; u < U; ++u) vB[u] = __builtin_amdgcn_raw_buffer_load_b128(Vr, o[U + u], 0, 0);
-        };
-        // logits of 16 tokens of the wavefront for all heads: d[i] is token 4 q4 + i = token i of this lane's group, head `sub`
-        auto logits = [&](const lc_v4i (&kv)[4]) LC_INLINE -> lc_f32x4 {
-            lc_f32x4 d = {0.f, 0.f, 0.f, 0.f};
+        for (int u = 0; u < U; ++u) vB[u] = __builtin_amdgcn_raw_buffer_load_b128(Vr, o[U + u], 0, 0);
+    };
+    // logits of 16 tokens of the wavefront for all heads: d[i] is token 4 q4 + i = token i of this lane's group, head `sub`
+    auto logits = [&](const lc_v4i (&kv)[4]) LC_INLINE -> lc_f32x4 {
+        lc_f32x4 d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(lc_bf16x8, kv[j]),
-                                                            __builtin_bit_cast(lc_bf16x8, qb[j]), d, 0, 0, 0);
-            return d;
-        };
-        // one online-softmax update of this lane's head with the logits of batches it and it + 1 (N = 8) or it alone (N = 4)
-        auto softmax = [&](auto count, int it, lc_f32x4 dA, lc_f32x4 dB, auto& p) LC_INLINE {
-            constexpr int N = decltype(count)::value;
-            float x[N];                                             // logits, not yet scaled
-            float mx = LC_NEG_INF;
+        for (int j = 0; j < 4; ++j)
+            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(lc_bf16x8, kv[j]),
+                                                        __builtin_bit_cast(lc_bf16x8, qb[j]), d, 0, 0, 0);
+        return d;
+    };
+    // one online-softmax update of this lane's head with the logits of batches it and it + 1 (N = 8) or it alone (N = 4);
+    // whether any of the probabilities is too small for attend1 and attend2 (uniform)
+    auto softmax = [&](auto count, int it, lc_f32x4 dA, lc_f32x4 dB, auto& p) LC_INLINE -> bool {
+        constexpr int N = decltype(count)::value;
+        float x[N];                                             // logits, not yet scaled
+        float mx = LC_NEG_INF;
 #pragma unroll
-            for (int u = 0; u < N; ++u) {
-                x[u] = (tv + it * U + u < tv_end) ? (u < U ? dA[u % U] : dB[u % U]) : LC_NEG_INF;
-                mx = fmaxf(mx, x[u]);
-            }
-            mx = lc_max_groups(mx) * scale;
-            // The reference follows the maximum only when it falls behind by more than LC_DEC_LAG: the accumulators are scaled once or
-            // not at all per split instead of once per step.  It is a whole number, so that scaling rounds nothing.
-            if (__ballot(mx > m_ref + (float)LC_DEC_LAG) != 0ull) {
-                const float m_new = mx > m_ref + (float)LC_DEC_LAG ? ceilf(mx) : m_ref;
-                const float sc = (m_new == LC_NEG_INF) ? 1.f : exp2f(m_ref - m_new);
-                const bool started = __ballot(m_ref > LC_NEG_INF) != 0ull;
-                m_ref = m_new;
-                if (started) {                                      // (before that the accumulators are zero)
-                    l_run *= sc;
+        for (int u = 0; u < N; ++u) {
+            x[u] = (tv + it * U + u < tv_end) ? (u < U ? dA[u % U] : dB[u % U]) : LC_NEG_INF;
+            mx = fmaxf(mx, x[u]);
+        }
+        mx = lc_max_groups(mx) * scale;
+        // The reference follows the maximum only when it falls behind by more than LC_DEC_LAG: the accumulators are scaled once or
+        // not at all per split instead of once per step.  It is a whole number, so that scaling rounds nothing.
+        if (__ballot(mx > m_ref + (float)LC_DEC_LAG) != 0ull) {
+            const float m_new = mx > m_ref + (float)LC_DEC_LAG ? ceilf(mx) : m_ref;
+            const float sc = (m_new == LC_NEG_INF) ? 1.f : lc_rescale(m_ref, m_new);
+            const bool started = __ballot(m_ref > LC_NEG_INF) != 0ull;
+            m_ref = m_new;
+            if (started) {                                      // (before that the accumulators are zero)
+                l_run *= sc;
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const float sr = __shfl(sc, 4 * q4 + r);
+                for (int r = 0; r < 4; ++r) {
+                    const float sr = __shfl(sc, 4 * q4 + r);
 #pragma unroll
-                        for (int c = 0; c < 8; ++c) acc[c][r] *= sr;
-                    }
+                    for (int c = 0; c < 8; ++c) acc[c][r] *= sr;
                 }
             }
-            const float ref = (m_ref == LC_NEG_INF) ? 0.f : m_ref;
+        }
+        const float ref = (m_ref == LC_NEG_INF) ? 0.f : m_ref;
 #pragma unroll
-            for (int u = 0; u < N; ++u) p[u] = lc_probability(fmaf(x[u], scale, -ref));
-            float l = (p[0] + p[1]) + (p[2] + p[3]);
-            if constexpr (N == 8) l += (p[4] + p[5]) + (p[6] + p[7]);
-            l_run += l;
-        };
-        auto pv = [&](const lc_v4i& t, const lc_v4i& b, lc_f32x4& a) LC_INLINE {
-            a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(lc_bf16x8, t), __builtin_bit_cast(lc_bf16x8, b), a, 0, 0, 0);
-        };
-        // column c of rows v[2k], v[2k + 1], packed
-        auto column = [&](const lc_v4i (&v)[U], int c, int k) LC_INLINE -> int {
-            return (int)__builtin_amdgcn_perm((uint32_t)v[2 * k + 1][c / 2], (uint32_t)v[2 * k][c / 2], (c & 1) ? 0x07060302u : 0x05040100u);
-        };
-        // P.V: of two batches, one instruction per term of P and column; of one, the first two terms share one.  The smallest
-        // terms go first: fewer roundings at full size.  (All instructions have one shape: with a 16x16x16 one adding to
-        // the result of a 16x16x32 one the compiler left too few wait states between the two.)
-        auto attend2 = [&](const float (&p)[2 * U], const lc_v4i (&vA)[U], const lc_v4i (&vB)[U]) LC_INLINE {
-            int t[3][U];
-            lc_split3<2 * U>(p, t);
+        for (int u = 0; u < N; ++u) p[u] = lc_probability(fmaf(x[u], scale, -ref));
+        float l = (p[0] + p[1]) + (p[2] + p[3]);
+        if constexpr (N == 8) l += (p[4] + p[5]) + (p[6] + p[7]);
+        l_run += l;
+        float mn = fminf(fminf(dA[0], dA[1]), fminf(dA[2], dA[3]));            // (0 where there is no token)
+        if constexpr (N == 8) mn = fminf(mn, fminf(fminf(dB[0], dB[1]), fminf(dB[2], dB[3])));
+        return __ballot(fmaf(mn, scale, -ref) < LC_DEC_FAINT) != 0ull;
+    };
+    auto pv = [&](const lc_v4i& t, const lc_v4i& b, lc_f32x4& a) LC_INLINE {
+        a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(lc_bf16x8, t), __builtin_bit_cast(lc_bf16x8, b), a, 0, 0, 0);
+    };
+    // column c of rows v[2k], v[2k + 1], packed
+    auto column = [&](const lc_v4i (&v)[U], int c, int k) LC_INLINE -> int {
+        return (int)__builtin_amdgcn_perm((uint32_t)v[2 * k + 1][c / 2], (uint32_t)v[2 * k][c / 2], (c & 1) ? 0x07060302u : 0x05040100u);
+    };
+    // P.V: of two batches, one instruction per term of P and column; of one, the first two terms share one.  The smallest
+    // terms go first: fewer roundings at full size.  (All instructions have one shape: with a 16x16x16 one adding to
+    // the result of a 16x16x32 one the compiler left too few wait states between the two.)
+    auto attend2 = [&](const float (&p)[2 * U], const lc_v4i (&vA)[U], const lc_v4i (&vB)[U]) LC_INLINE {
+        int t[3][U];
+        lc_split3<2 * U>(p, t);
 #pragma unroll
-            for (int c0 = 0; c0 < 8; c0 += 4) {
-                lc_v4i bc[4];                                       // column c0 + c's eight tokens
+        for (int c0 = 0; c0 < 8; c0 += 4) {
+            lc_v4i bc[4];                                       // column c0 + c's eight tokens
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    bc[c] = lc_v4i{column(vA, c0 + c, 0), column(vA, c0 + c, 1), column(vB, c0 + c, 0), column(vB, c0 + c, 1)};
+            for (int c = 0; c < 4; ++c)
+                bc[c] = lc_v4i{column(vA, c0 + c, 0), column(vA, c0 + c, 1), column(vB, c0 + c, 0), column(vB, c0 + c, 1)};
 #pragma unroll
-                for (int s = 2; s >= 0; --s)
+            for (int s = 2; s >= 0; --s)
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) pv(lc_v4i{t[s][0], t[s][1], t[s][2], t[s][3]}, bc[c], acc[c0 + c]);
-            }
-        };
-        auto attend1 = [&](const float (&p)[U], const lc_v4i (&v)[U]) LC_INLINE {
-            int t[3][U / 2];
-            lc_split3<U>(p, t);
+                for (int c = 0; c < 4; ++c) pv(lc_v4i{t[s][0], t[s][1], t[s][2], t[s][3]}, bc[c], acc[c0 + c]);
+        }
+    };
+    auto attend1 = [&](const float (&p)[U], const lc_v4i (&v)[U]) LC_INLINE {
+        int t[3][U / 2];
+        lc_split3<U>(p, t);
 #pragma unroll
-            for (int c0 = 0; c0 < 8; c0 += 4) {
-                int b0[4], b1[4];
+        for (int c0 = 0; c0 < 8; c0 += 4) {
+            int b0[4], b1[4];
 #pragma unroll
-                for (int c = 0; c < 4; ++c) { b0[c] = column(v, c0 + c, 0); b1[c] = column(v, c0 + c, 1); }
+            for (int c = 0; c < 4; ++c) { b0[c] = column(v, c0 + c, 0); b1[c] = column(v, c0 + c, 1); }
 #pragma unroll
-                for (int c = 0; c < 4; ++c) pv(lc_v4i{t[2][0], t[2][1], 0, 0}, lc_v4i{b0[c], b1[c], 0, 0}, acc[c0 + c]);
+            for (int c = 0; c < 4; ++c) pv(lc_v4i{t[2][0], t[2][1], 0, 0}, lc_v4i{b0[c], b1[c], 0, 0}, acc[c0 + c]);
 #pragma unroll
-                for (int c = 0; c < 4; ++c) pv(lc_v4i{t[1][0], t[1][1], t[0][0], t[0][1]}, lc_v4i{b0[c], b1[c], b0[c], b1[c]}, acc[c0 + c]);
-            }
-        };
+            for (int c = 0; c < 4; ++c) pv(lc_v4i{t[1][0], t[1][1], t[0][0], t[0][1]}, lc_v4i{b0[c], b1[c], b0[c], b1[c]}, acc[c0 + c]);
+        }
+    };
 
-        // The split's tokens are handled in tiles; for each tile the workgroup first writes the cache
-        // row of every token into LDS, then every group streams a contiguous slice of the tile.
+    // Whether any of a step's values is 2^64 or more, infinite or not a number (uniform).
+    auto large = [&](const lc_v4i (&vA)[U], const lc_v4i (&vB)[U]) LC_INLINE -> bool {
+        typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+        u16x2 m = {0, 0};
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, vA[u][w] & 0x7fff7fff));
+                m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, vB[u][w] & 0x7fff7fff));
+            }
+        return __ballot(m.x >= 0x5f80 || m.y >= 0x5f80) != 0ull;
+    };
+    // P.V of two batches in float32 on the vector ALU: this lane's columns of its group's tokens, a head at a time, then summed over the
+    // groups.  A probability is at least the smallest number there is: an infinite value reaches its column however little its
+    // token weighs.
+    auto attend_plain = [&](const float (&p)[2 * U], int it, const lc_v4i (&vA)[U], const lc_v4i (&vB)[U]) LC_INLINE {
+#pragma unroll 1
+        for (int g = 0; g < G; ++g) {
+            float y[8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) y[c] = 0.f;
+#pragma unroll
+            for (int u = 0; u < 2 * U; ++u) {
+                float pu = __shfl(p[u], 16 * q4 + g);
+                if (tv + it * U + u < tv_end) pu = fmaxf(pu, __builtin_ldexpf(1.f, -149));
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    const uint32_t w = (uint32_t)(u < U ? vA[u % U][c / 2] : vB[u % U][c / 2]);
+                    y[c] = fmaf(pu, (c & 1) ? lc_bf16_hi(w) : lc_bf16_lo(w), y[c]);
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                y[c] = lc_add_halves(y[c], y[c]);
+                y[c] = lc_add_rows(y[c], y[c]);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[c][r] += 4 * q4 + r == g ? y[c] : 0.f;
+            }
+        }
+    };
+
+    // The split's tokens are handled in tiles; for each tile the workgroup first writes the cache
+    // row of every token into LDS, then every group streams a contiguous slice of the tile.
+    auto over_tiles = [&](int split, auto stream) LC_INLINE {
+        // tokens [n_tok split / S_eff, n_tok (split + 1) / S_eff), in 32 bits: with n_tok = each S_eff + more, more < S_eff <= 256
+        const uint32_t each = (uint32_t)n_tok / (uint32_t)S_eff, more = (uint32_t)n_tok % (uint32_t)S_eff;
+        const int lo = (int)(each * (uint32_t)split + more * (uint32_t)split / (uint32_t)S_eff);
+        const int hi = (int)(each * (uint32_t)(split + 1) + more * (uint32_t)(split + 1) / (uint32_t)S_eff);
         for (int tile0 = lo; tile0 < hi; tile0 += LC_DEC_TILE) {
             const int tl = min(LC_DEC_TILE, hi - tile0);
             const int row_max = max(T - 1, 0);
@@ -497,6 +552,54 @@ lc_decode_kernel(const LcDecodeArgs a) {
             tv_end = min(tl, tv + per);
             tk = min(tl, gk * per);
             tk_end = min(tl, tk + per);
+            stream(n_it);
+        }
+    };
+    // ---- the accumulators hold the sums over the wavefront's tokens; the wavefronts meet in LDS
+    // (`again`: the splits' merge is to do this split again, which it sees by a reference that is not a number: no other reference is one,
+    // and with the mark in a word that is read anyway a step costs what it did; a vote of its own in LDS took 0.2 us)
+    auto meet = [&](bool again) LC_INLINE {
+        float l = lc_add_halves(l_run, l_run);
+        l = lc_add_rows(l, l);
+        if (lane < G) { ph.comb.ml[wave][lane][0] = again ? __builtin_nanf("") : m_ref; ph.comb.ml[wave][lane][1] = l; }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int g = 4 * q4 + r;
+            if (g < G) {
+                float4* const o = &ph.comb.acc[wave][g][2 * sub];
+                o[0] = make_float4(acc[0][r], acc[1][r], acc[2][r], acc[3][r]);
+                o[1] = make_float4(acc[4][r], acc[5][r], acc[6][r], acc[7][r]);
+            }
+        }
+    };
+    // one float4 slot of the split's partial per thread, stored at agent scope
+    auto store_partial = [&](int split) LC_INLINE {
+        float* pml = a.part_ml + ((size_t)bh * S + split) * G * 2;
+        const __amdgpu_buffer_rsrc_t pacc_w = lc_buffer(a.part_acc + ((size_t)bh * S + split) * G * LC_D);
+        for (int v = tid; v < G * (LC_D / 4); v += LC_DEC_THREADS) {
+            const int g = v / (LC_D / 4), c4 = v % (LC_D / 4);
+            float mx = LC_NEG_INF;
+#pragma unroll
+            for (int w = 0; w < LC_DEC_THREADS / 64; ++w) mx = __builtin_elementwise_maximum(mx, ph.comb.ml[w][g][0]);      // (hands on what is not a number)
+            float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
+            float den = 0.f;
+#pragma unroll
+            for (int w = 0; w < LC_DEC_THREADS / 64; ++w) {
+                const float mw = ph.comb.ml[w][g][0];
+                const float sc = (mw == LC_NEG_INF) ? 0.f : lc_rescale(mw, mx);
+                const float4 x = ph.comb.acc[w][g][c4];
+                num.x = fmaf(x.x, sc, num.x); num.y = fmaf(x.y, sc, num.y);
+                num.z = fmaf(x.z, sc, num.z); num.w = fmaf(x.w, sc, num.w);
+                den = fmaf(ph.comb.ml[w][g][1], sc, den);
+            }
+            lc_store_agent4(pacc_w, v * 16, num);
+            if (c4 == 0) { lc_store_agent(&pml[2 * g], mx); lc_store_agent(&pml[2 * g + 1], den); }
+        }
+    };
+
+    if (s < S_eff) {
+        bool again = false;                                             // (the same for the wavefront)
+        over_tiles(s, [&](int n_it) LC_INLINE {
             // steps of two batches, a last one of one; a step's K rows are fetched while the step before is at its softmax and
             // P.V, its V rows behind that (batches past the last one load nothing)
             lc_v4i kA[4], vA[U], kB[4], vB[U];
@@ -511,56 +614,22 @@ lc_decode_kernel(const LcDecodeArgs a) {
                 const lc_f32x4 dA = logits(kA), dB = logits(kB);
                 if (more) { k_offsets(it + 2, ko); load_k(ko, kA, kB); }
                 float p[2 * U];
-                softmax(std::integral_constant<int, 2 * U>(), it, dA, dB, p);
+                const bool faint = softmax(std::integral_constant<int, 2 * U>(), it, dA, dB, p);
+                if (__builtin_expect(faint, 0)) again = again || large(vA, vB);
                 attend2(p, vA, vB);
                 if (more) { v_offsets(it + 2, vo); load_v(vo, vA, vB); }
             }
             if (it < n_it) {
                 const lc_f32x4 dA = logits(kA);
                 float p[U];
-                softmax(std::integral_constant<int, U>(), it, dA, dA, p);
+                const bool faint = softmax(std::integral_constant<int, U>(), it, dA, dA, p);
+                if (__builtin_expect(faint, 0)) again = again || large(vA, vA);
                 attend1(p, vA);
             }
-        }
-
-        // ---- the accumulators hold the sums over the wavefront's tokens; the wavefronts meet in LDS
-        {
-            float l = lc_add_halves(l_run, l_run);
-            l = lc_add_rows(l, l);
-            if (lane < G) { ph.comb.ml[wave][lane][0] = m_ref; ph.comb.ml[wave][lane][1] = l; }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int g = 4 * q4 + r;
-                if (g < G) {
-                    float4* const o = &ph.comb.acc[wave][g][2 * sub];
-                    o[0] = make_float4(acc[0][r], acc[1][r], acc[2][r], acc[3][r]);
-                    o[1] = make_float4(acc[4][r], acc[5][r], acc[6][r], acc[7][r]);
-                }
-            }
-        }
+        });
+        meet(again);
         __syncthreads();
-        // one float4 slot of the split's partial per thread, stored at agent scope
-        float* pml = a.part_ml + ((size_t)bh * S + s) * G * 2;
-        const __amdgpu_buffer_rsrc_t pacc_w = lc_buffer(a.part_acc + ((size_t)bh * S + s) * G * LC_D);
-        for (int v = tid; v < G * (LC_D / 4); v += LC_DEC_THREADS) {
-            const int g = v / (LC_D / 4), c4 = v % (LC_D / 4);
-            float mx = LC_NEG_INF;
-#pragma unroll
-            for (int w = 0; w < LC_DEC_THREADS / 64; ++w) mx = fmaxf(mx, ph.comb.ml[w][g][0]);
-            float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
-            float den = 0.f;
-#pragma unroll
-            for (int w = 0; w < LC_DEC_THREADS / 64; ++w) {
-                const float mw = ph.comb.ml[w][g][0];
-                const float sc = (mw == LC_NEG_INF) ? 0.f : exp2f(mw - mx);
-                const float4 x = ph.comb.acc[w][g][c4];
-                num.x = fmaf(x.x, sc, num.x); num.y = fmaf(x.y, sc, num.y);
-                num.z = fmaf(x.z, sc, num.z); num.w = fmaf(x.w, sc, num.w);
-                den = fmaf(ph.comb.ml[w][g][1], sc, den);
-            }
-            lc_store_agent4(pacc_w, v * 16, num);
-            if (c4 == 0) { lc_store_agent(&pml[2 * g], mx); lc_store_agent(&pml[2 * g + 1], den); }
-        }
+        store_partial(s);
     }
 
     // ---- the last split to arrive merges (log-sum-exp merge of the partial results)
@@ -584,17 +653,57 @@ lc_decode_kernel(const LcDecodeArgs a) {
         for (int k = 0; k < MR; ++k)
             x[k] = lc_load_agent4(pacc_r, (((sp0 + k * WAYS) * G + g) * LC_D + 4 * c4) * 4);
     };
-    if (wy < WAYS && n_part > 0) load_round(wy);
     const int half = tid >> 5, hl = tid & 31;
     float m_all = LC_NEG_INF, den = 0.f;
-    {
-        float m0 = LC_NEG_INF, l0 = 0.f;                     // the first 32 splits (all of them unless more were asked for)
+    float m0 = LC_NEG_INF, l0 = 0.f;                         // the first 32 splits (all of them unless more were asked for)
+    auto fetch = [&]() LC_INLINE -> bool {                   // whether a split is to be done again (the same for the workgroup)
+        if (wy < WAYS && n_part > 0) load_round(wy);
         if (hl < n_part) {
             m0 = lc_load_agent(pml + 2 * (hl * G + g));
             l0 = lc_load_agent(pml + 2 * (hl * G + g) + 1);
         }
         m_all = m0;
-        for (int sp = hl + 32; sp < n_part; sp += 32) m_all = fmaxf(m_all, lc_load_agent(pml + 2 * (sp * G + g)));
+        bool again = m0 != m0;
+        for (int sp = hl + 32; sp < n_part; sp += 32) {
+            const float m = lc_load_agent(pml + 2 * (sp * G + g));
+            again = again || m != m;
+            m_all = fmaxf(m_all, m);
+        }
+        return __ballot(again) != 0ull;
+    };
+    if (__builtin_expect(fetch(), 0)) {
+        // Splits with tokens too light for lc_split3 and large values: done here once more, one after the other, without it.
+        for (int sp = 0; sp < n_part; ++sp) {
+            const float mark = lc_load_agent(pml + 2 * sp * G);
+            if (__ballot(mark != mark) == 0ull) continue;
+            m_ref = LC_NEG_INF;
+            l_run = 0.f;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) acc[c] = lc_f32x4{0.f, 0.f, 0.f, 0.f};
+            __syncthreads();                                 // (everyone has the mark, and is done with the rows and sums before)
+            over_tiles(sp, [&](int n_it) LC_INLINE {
+#pragma unroll 1
+                for (int it = 0; it < n_it; it += 2) {
+                    lc_v4i kA[4], vA[U], kB[4], vB[U];
+                    int ko[2], vo[2 * U];
+                    k_offsets(it, ko);
+                    load_k(ko, kA, kB);
+                    v_offsets(it, vo);
+                    load_v(vo, vA, vB);
+                    float p[2 * U];
+                    softmax(std::integral_constant<int, 2 * U>(), it, logits(kA), logits(kB), p);
+                    attend_plain(p, it, vA, vB);
+                }
+            });
+            meet(false);
+            __syncthreads();
+            store_partial(sp);
+            __builtin_amdgcn_s_waitcnt(0);
+        }
+        __syncthreads();
+        fetch();
+    }
+    {
         m_all = fmaxf(m_all, lc_dpp<0xB1>(m_all));
         m_all = fmaxf(m_all, lc_dpp<0x4E>(m_all));
         m_all = fmaxf(m_all, lc_dpp<0x141>(m_all));
@@ -611,7 +720,7 @@ lc_decode_kernel(const LcDecodeArgs a) {
                 ms = sp < n_part ? lc_load_agent(pml + 2 * (sp * G + g)) : LC_NEG_INF;
                 ls = sp < n_part ? lc_load_agent(pml + 2 * (sp * G + g) + 1) : 0.f;
             }
-            const float sc = (ms == LC_NEG_INF) ? 0.f : exp2f(ms - m_all);
+            const float sc = (ms == LC_NEG_INF) ? 0.f : lc_rescale(ms, m_all);
             ph.scale[half][sp] = sc;
             den = fmaf(ls, sc, den);
         }

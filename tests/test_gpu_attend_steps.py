@@ -1,5 +1,6 @@
 """The attention kernel's P.V on the matrix cores: token counts around its steps (32 tokens of a wavefront), tiles and splits,
-logits that rise and fall along the tokens (the softmax's reference moves late, or never), infinite values of V."""
+logits that rise and fall along the tokens (the softmax's reference moves late, or never), infinite, large and small values of V,
+and tokens whose weight bfloat16 does not hold in three terms."""
 import numpy as np
 import pytest
 
@@ -115,4 +116,39 @@ def test_large_and_small_values(tokens, splits, G):
         bound = rel[:, None] * (p @ v.abs()) + 3 * T * 2.0 ** -149 * 2.0 ** 9
         assert torch.isfinite(out).all()
         assert ((out - p @ v).abs() <= bound).all(), ((out - p @ v).abs() / bound).max()
+        assert ((lse - torch.logsumexp(x, dim=-1)).abs() <= rel + 2.0 ** -22 * lse.abs()).all()
+
+
+@pytest.mark.parametrize("G", [1, 7, 8])
+@pytest.mark.parametrize("below", [104, 112, 125, 145, 700])
+@pytest.mark.parametrize("tokens,splits,light,heavy", [(3, 1, 2, 0), (40, 1, 0, 39), (200, 1, 13, 199), (200, 1, 199, 0), (1100, 1, 3, 1090), (2500, 2, 10, 2400), (700, 0, 650, 5)])
+def test_values_of_light_tokens(tokens, splits, light, heavy, below, G):
+    """One token weighs 2^-below of the heaviest.  An infinite value of it reaches its column whatever the weight, as it does in float64;
+    a finite one is counted to float32's precision as far as the weight has a place in float32's range."""
+    import torch
+    T = tokens
+    gen = torch.Generator()
+    gen.manual_seed(T + below + G)
+    logits = np.full(T, -3.0)
+    logits[heavy], logits[light] = 0.0, -below
+    q, K, x = _aimed(logits, G)
+    p = torch.softmax(x, dim=-1)
+    assert (p[:, light] > 0).all()
+    V = torch.randn((T, 128), generator=gen)
+    V[:, 9], V[:, 40] = 0.0, 0.0
+    V[light, 9], V[light, 40] = 1.7 * 2.0 ** 127, -1.3 * 2.0 ** 100
+    V = V.to(torch.bfloat16)
+    W = V.clone()
+    W[light, 5], W[light, 77] = float("inf"), float("-inf")
+    rel = 2.0 * (2.0 ** -21 * x.abs().amax(dim=-1) + 2.0 ** -20)
+    for values in (V, W):
+        out, lse = _attend(q, K, values[None, None].cuda(), splits)
+        v = values.double()
+        ref = p @ v
+        # as above; the light token's probability is off by the last bit of float32's range (at most one scaling on its way loses as
+        # much again, twice), against sums of 2^-9 and more
+        bound = rel[:, None] * (p @ v.abs()) + 3 * T * 2.0 ** -149 * 2.0 ** 9 + 4 * 2.0 ** -149 * 2.0 ** 9 * v[light].abs()
+        finite = torch.isfinite(v).all(dim=0)
+        assert ((out - ref).abs() <= bound)[:, finite].all(), ((out - ref).abs() / bound)[:, finite].max()
+        assert torch.equal(out[:, ~finite], ref[:, ~finite])       # infinities of the sign that float64 gives
         assert ((lse - torch.logsumexp(x, dim=-1)).abs() <= rel + 2.0 ** -22 * lse.abs()).all()
