@@ -1268,8 +1268,13 @@ lc_score_kernel(const LcRetrieveArgs a) {
 // and one cold round trip.  As a kernel of its own behind lc_score_kernel it costs a launch, and saves the arrival of all scoring
 // workgroups at one counter, keys staged in LDS and two passes over them: lc_retrieve on 8 heads of 10.9 K chunks 21.2 us as one
 // kernel (lc_leaf_kernel), 17.4 as two; of 2299 11.5 and 9.3; of 500 9.2 and 7.4.
+// Where the budget ends among the bulk of the chunks, the cutoff bin holds tens or hundreds of them.  The wavefronts share their ranking and take
+// up to LC_SL_CAND of them: with 64, ranked by every wavefront (four of them on each SIMD) and all beyond left to the general routine, half of
+// the tokens as the budget cost 12.1 us at 8 heads of 1000 chunks, now 8.0; at 11 K 30.9, now 19.7; at 64 x 500 11.7, now 9.5 (one kernel: 8.8); and a
+// twelfth at 11 K 19.1, now 17.5.
 #define LC_SL_THREADS 1024
-#define LC_SL_CAND 64             // chunks of the cutoff bin that are ranked directly
+#define LC_SL_CAND 256            // chunks of the cutoff bin that are ranked directly
+#define LC_SL_FEW 4               // by every wavefront for itself
 #define LC_SL_EC_MAX 12
 struct LcSelectArgs {
     const int* entries;      // [B][H][cap0] LcChunkEntry
@@ -1287,6 +1292,7 @@ lc_select_kernel(const LcSelectArgs a) {
     extern __shared__ __attribute__((aligned(16))) int lds_dyn[];   // crowded cutoff bin: keys and lengths
     __shared__ __attribute__((aligned(16))) int hist[BINS];
     __shared__ int4 cand[LC_SL_CAND];
+    __shared__ int ahead[LC_SL_CAND];                               // length of the chunks of the list that come before this one
     __shared__ uint32_t range[2 * NW];
     __shared__ int number[NW], n_cand;
     __shared__ LcLeafSelSh sel_sh;
@@ -1297,12 +1303,15 @@ lc_select_kernel(const LcSelectArgs a) {
     const int j0 = wave * (EC * 64) + lane;                         // this lane's chunk e is j0 + 64 e
     uint32_t ck[EC];
     int len[EC], bin[EC];
+    int T;
     {
         lc_v4i ent[EC];
 #pragma unroll
         for (int e = 0; e < EC; ++e) ent[e] = __builtin_amdgcn_raw_buffer_load_b128(ent_r, j0 * 16, e * 1024, 0);
         for (int i = tid; i < BINS; i += NT) hist[i] = 0;
+        if (tid < LC_SL_CAND) ahead[tid] = 0;
         if (tid == 0) n_cand = 0;
+        T = a.state[bh * 4 + 0];
         const int M = a.state[bh * 4 + 1];
 #pragma unroll
         for (int e = 0; e < EC; ++e) {
@@ -1325,13 +1334,15 @@ lc_select_kernel(const LcSelectArgs a) {
     kmax = lc_wave_max_uniform(range[NW + (lane & 15)]);
     // ---- Histogram of chunk lengths over the upper half of the scores' range: the budget nearly always ends there, few chunks are in it (LDS
     // atomics of all of them, most in the same few bins, are the longest step otherwise), and its bins are finer.  Over all of the
-    // range if the upper half fits the budget whole.  Bins are even steps of the key, which cost less, or of the score where the keys'
+    // range if the upper half fits the budget whole, and at once if the budget is a third of the tokens or more (then the upper half rarely
+    // goes beyond it: whole range first against half first, 0.90 to 0.97 of the time at two thirds, a half and a third of the tokens, 1.00 to
+    // 1.03 at a quarter and less, over 8 to 256 pairs of 200 to 11 K chunks).  Bins are even steps of the key, which cost less, or of the score where the keys'
     // range is over 32 binary orders (keys of scores of both signs crowd around zero: of 1.6 K such chunks the top 40 were in three
     // bins, and the crowded bin's way took 13.5 us, now 5.1).
     int fb = -1, remW = W;                                          // cutoff bin (-1: every candidate fits), budget left for it
     const float s_hi = lc_key_score(kmax), s_all = s_hi - lc_key_score(kmin);
     const bool by_score = kmax - kmin > (32u << 23) && s_all > 1e-30f && s_all < 1e30f;      // (not for infinities)
-    for (bool half = true;; half = false) {
+    for (bool half = W < T / 3;; half = false) {
         if (by_score) {
             const float s_lo = half ? s_hi - 0.5f * s_all : lc_key_score(kmin);
             const float per_bin = (float)BINS * __builtin_amdgcn_rcpf(half ? 0.5f * s_all : s_all);
@@ -1403,17 +1414,36 @@ lc_select_kernel(const LcSelectArgs a) {
     lc_barrier_lds();
     const int nc = n_cand;
     if (nc <= LC_SL_CAND) {
-        // ---- lane c ranks chunk c of it: length of the chunks before it (key descending, id ascending)
-        const int4 me = cand[min(lane, max(nc - 1, 0))];
-        int wb = 0;
-        for (int c = 0; c < nc; ++c) {                              // (uniform)
-            const uint32_t k = (uint32_t)lc_readlane(me.x, c);
-            const bool before = k > (uint32_t)me.x || (k == (uint32_t)me.x && lc_readlane(me.z, c) < me.z);
-            wb += before ? lc_readlane(me.y, c) : 0;
-        }
-        for (unsigned long long won = __ballot(lane < nc && wb + me.y <= remW); won != 0ull; won &= won - 1ull) {
-            const int id = lc_readlane(me.z, __ffsll((long long)won) - 1), e = (id >> 6) - wave * EC;
-            if (e >= 0 && e < EC) sel |= lane == (id & 63) ? 1u << e : 0u;       // (uniform but for the lane)
+        // ---- the list in order (key descending, id ascending): lane c adds up the lengths before chunk c, then a wavefront takes its own of
+        // those that fit.  A few are ranked by every wavefront; of more, a wavefront adds up every 16th and the sums meet in LDS (a barrier, 0.2 us).
+        auto precedes = [](const int4& o, const int4& me) LC_INLINE { return (uint32_t)o.x > (uint32_t)me.x || (o.x == me.x && o.z < me.z); };
+        auto take = [&](int c0, const int4& me, int before) LC_INLINE {
+            const int e_me = (me.z >> 6) - wave * EC;
+            for (unsigned long long won = __ballot(c0 + lane < nc && e_me >= 0 && e_me < EC && before + me.y <= remW); won != 0ull; won &= won - 1ull) {
+                const int id = lc_readlane(me.z, __ffsll((long long)won) - 1);
+                sel |= lane == (id & 63) ? 1u << ((id >> 6) - wave * EC) : 0u;       // (uniform but for the lane)
+            }
+        };
+        if (nc <= LC_SL_FEW) {
+            const int4 me = cand[min(lane, max(nc - 1, 0))];
+            int sum = 0;
+            for (int c = 0; c < nc; ++c) {                          // (uniform)
+                const int4 o = make_int4(lc_readlane(me.x, c), lc_readlane(me.y, c), lc_readlane(me.z, c), 0);
+                sum += precedes(o, me) ? o.y : 0;
+            }
+            take(0, me, sum);
+        } else {
+            for (int c0 = 0; c0 < nc; c0 += 64) {
+                const int4 me = cand[min(c0 + lane, nc - 1)];
+                int sum = 0;
+                for (int c = wave; c < nc; c += NW) sum += precedes(cand[c], me) ? cand[c].y : 0;
+                if (sum != 0 && c0 + lane < nc) atomicAdd(&ahead[c0 + lane], sum);
+            }
+            lc_barrier_lds();
+            for (int c0 = 0; c0 < nc; c0 += 64) {
+                const int c = min(c0 + lane, nc - 1);
+                take(c0, cand[c], ahead[c]);
+            }
         }
     } else {
         // ---- a crowded or tied cutoff bin: the general select routine on its chunks alone

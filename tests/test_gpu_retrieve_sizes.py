@@ -87,3 +87,39 @@ def test_a_step_selects_the_same(chunks, geometry, infinite):
         assert torch.equal(n[0], n[1]), budget
         for h in range(H):
             assert torch.equal(ids[0][0, h, : n[0][0, h]], ids[1][0, h, : n[1][0, h]]), (budget, h)
+
+
+@pytest.mark.parametrize("others", [70, 1500, 9000])
+@pytest.mark.parametrize("tied", [1, 15, 17, 64, 65, 255, 256, 257, 700])
+def test_a_budget_that_ends_among_equal_scores(tied, others):
+    """`tied` chunks of one score and different lengths between `others` of higher and lower ones: as many of them as the list of the
+    cutoff bin holds, and one more and less.  (All tokens of a chunk are one row, so its score does not depend on its length.)"""
+    import torch
+    from paper_2603_08453_amd import binding as lc
+    G, M = 4, tied + others
+    r = np.random.default_rng(tied + others)
+    size = r.integers(1, 6, size=M)
+    bounds = np.concatenate([[0], np.cumsum(size)]).astype(np.int32)
+    T = int(bounds[-1])
+    level = r.permutation(np.concatenate([np.zeros(tied), r.normal(size=others)]))
+    rows = np.zeros((M, 128), dtype=np.float32)
+    rows[:, 0], rows[:, 1] = 8 + level, 0.25
+    K = torch.from_numpy(np.repeat(rows, size, axis=0)).cuda().to(torch.bfloat16)[None, None].contiguous()
+    q = torch.zeros((1, G, 128), device="cuda")
+    q[0, :, 0] = torch.arange(G, 0, -1, device="cuda")
+    q = q.to(torch.bfloat16)
+    cfg = lc.lc_config_default(levels=2, fanout=32, kmeans_iters=1, max_chunks=M, max_tokens=T, prune=0)
+    ib = torch.zeros(lc.lc_index_bytes(cfg, 1, 1), dtype=torch.uint8, device="cuda")
+    ws = torch.zeros(lc.lc_workspace_bytes(cfg, 1, G, 1), dtype=torch.uint8, device="cuda")
+    idx = lc.lc_build_index(cfg, K, [T], [bounds], ib, ws)
+    higher, here = int(size[level > 0].sum()), int(size[level == 0].sum())
+    for budget in (1, higher // 2, higher, higher + 1, higher + here // 3, higher + here - 1, higher + here, higher + here + 5, T // 3, T // 3 + 1, T - 1, T):
+        ids = torch.full((1, 1, M), -7, dtype=torch.int32, device="cuda")
+        n = torch.full((1, 1), -1, dtype=torch.int32, device="cuda")
+        scores = torch.full((1, 1, M), float("nan"), device="cuda")
+        lc.lc_retrieve(idx, q, budget, ids, n, ws, scores=scores)
+        got = scores[0, 0].cpu().numpy()
+        assert len(np.unique(got[level == 0])) == 1
+        want = by_the_rule(got, size, bounds[:-1], budget, 0)
+        assert int(n[0, 0]) == len(want), budget
+        assert np.array_equal(ids[0, 0, : len(want)].cpu().numpy(), want), budget
