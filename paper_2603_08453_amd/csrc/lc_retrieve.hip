@@ -18,7 +18,7 @@
 // lc_select_kernel: one workgroup per (sequence, KV head) selects from the entries and writes the ids (lc_retrieve, and the
 // decode step beyond what its selecting workgroups hold).
 //
-// lc_leaf_kernel (the same beyond what lc_select_kernel's registers hold): many workgroups per
+// lc_leaf_kernel (the same beyond what lc_select_kernel's registers hold, and in one band below: launch_retrieve_g): many workgroups per
 // (sequence, KV head) score the wanted chunks; the last workgroup to finish for a (sequence, head) pulls the keys into LDS, runs the weighted histogram select (weights =
 // chunk lengths) and emits the ids in ascending order.
 //
@@ -1557,10 +1557,17 @@ static int launch_retrieve_g(LcRetrieveArgs& a, int max_M, hipStream_t stream) {
         hipLaunchKernelGGL(lc_upper_kernel<G>, dim3(ix.H, ix.B), dim3(LC_UP_THREADS), lds, stream, a);
         LC_HIP_CHECK(hipGetLastError());
     }
-    // lc_retrieve: two kernels as far as the selecting one holds a (sequence, head)'s chunks in registers (measured there); only with seven
-    // or eight queries per KV head and some hundred thousand chunks in all was one kernel up to 3 % faster (64 pairs of 1820: 19.5 and 20.1 us;
-    // of 910 16.3 and 14.4, of 3276 40.9 and 32.8).
-    const bool two = !a.score_only && max_M > LC_FLAT_MAX_CHUNKS && max_M <= LC_SL_THREADS * LC_SL_EC_MAX;
+    // lc_retrieve: two kernels as far as the selecting one holds a (sequence, head)'s chunks in registers (measured there).  Not with seven
+    // or eight queries per KV head on float32 centers where the one kernel's workgroups, of up to 512 chunks, are on the device at once and nearly
+    // fill it: scoring is arithmetic then, and a group of lanes has eight chunks for a query it unpacks once.  us with one and two kernels at
+    // group size 7, a quarter of the tokens: 256 (sequence, head) pairs of 250 chunks 15.2 and 14.0, of 300 14.4 and 15.8, of 450 17.6 and 19.7; 208 of 440
+    // 16.5 and 17.0; 192 of 450 16.4 and 16.9, of 510 17.1 and 17.5; 176 of 510 17.1 and 16.8; 128 of 850 18.9 and 19.0, of 900 19.1 and 19.7, of 1020 20.2 and
+    // 20.8; 64 of 1500 18.8 and 17.5, of 1750 19.3 and 19.5, of 1850 19.8 and 20.2, of 2400 (in turns) 30.4 and 24.1.  bfloat16 centers: 2 to 30 % slower as one.
+    const int pairs = ix.H * ix.B;
+    const bool full = pairs >= 64 && (long long)((max_M + 511) / 512) * pairs <= LC_COMPUTE_UNITS &&
+                      ((long long)pairs * max_M >= 116000 || (pairs >= 200 && max_M > 256));
+    const bool one = G >= 7 && !ix.c0_bf16 && !a.walk && full;
+    const bool two = !a.score_only && !one && max_M > LC_FLAT_MAX_CHUNKS && max_M <= LC_SL_THREADS * LC_SL_EC_MAX;
     if (a.score_only || two) {
         // chunks per group: enough work per workgroup without leaving compute units idle
         int rs = 1;

@@ -123,3 +123,34 @@ def test_a_budget_that_ends_among_equal_scores(tied, others):
         want = by_the_rule(got, size, bounds[:-1], budget, 0)
         assert int(n[0, 0]) == len(want), budget
         assert np.array_equal(ids[0, 0, : len(want)].cpu().numpy(), want), budget
+
+
+@pytest.mark.parametrize("G", [7, 8])
+@pytest.mark.parametrize("B,chunks", [(8, 1812), (8, 1813), (8, 2048), (8, 2049), (25, 256), (25, 257), (32, 512), (32, 513)])
+def test_many_pairs_at_the_largest_group_sizes(B, chunks, G):
+    """Both sides of the band in which one kernel scores and selects for many (sequence, head) pairs."""
+    import torch
+    from paper_2603_08453_amd import binding as lc
+    H = 8
+    r = np.random.default_rng(chunks + G)
+    counts = [chunks if b % 3 != 1 else max(1, chunks // 2 - b) for b in range(B)]
+    bounds = [np.concatenate([[0], np.cumsum(r.integers(1, 4, size=m))]).astype(np.int32) for m in counts]
+    lens = [int(b[-1]) + 1 for b in bounds]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(chunks)
+    K = torch.randn((B, H, max(lens), 128), generator=gen, device="cuda").to(torch.bfloat16)
+    q = torch.randn((B, H * G, 128), generator=gen, device="cuda").to(torch.bfloat16)
+    cfg = lc.lc_config_default(levels=2, fanout=32, kmeans_iters=1, max_chunks=chunks, max_tokens=max(lens), prune=0)
+    ib = torch.zeros(lc.lc_index_bytes(cfg, B, H), dtype=torch.uint8, device="cuda")
+    ws = torch.zeros(lc.lc_workspace_bytes(cfg, B, H * G, H), dtype=torch.uint8, device="cuda")
+    idx = lc.lc_build_index(cfg, K, lens, bounds, ib, ws)
+    for budget in (chunks // 8, chunks, 10 ** 9):
+        ids = torch.full((B, H, chunks), -7, dtype=torch.int32, device="cuda")
+        n = torch.full((B, H), -1, dtype=torch.int32, device="cuda")
+        scores = torch.full((B, H, chunks), float("nan"), device="cuda")
+        lc.lc_retrieve(idx, q, budget, ids, n, ws, scores=scores)
+        ids, n, scores = ids.cpu().numpy(), n.cpu().numpy(), scores.cpu().numpy()
+        for b in range(B):
+            for h in range(H):
+                want = by_the_rule(scores[b, h, : counts[b]], np.diff(bounds[b]), bounds[b][:-1], budget, 0)
+                assert n[b, h] == len(want) and np.array_equal(ids[b, h, : len(want)], want), (budget, b, h)
