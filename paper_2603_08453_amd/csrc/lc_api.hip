@@ -583,7 +583,7 @@ int decode_step_checks(const lc_index* idx, const void* q, const void* K, const 
 // Splits that can find work: the attention kernel gives a split at least LC_DEC_MIN_TOKENS_PER_SPLIT tokens, and a
 // (sequence, head) attends to at most its budget and its open tail (all its tokens if some are pinned).
 // Splits beyond that would only repeat the selection and count as arrived.
-int useful_splits(const lc_index* idx, int G, int budget, int splits) {
+int useful_splits(const lc_index* idx, int G, int max_M, int budget, int splits) {
     long long most = 1;
     for (int b = 0; b < idx->B; ++b) {
         long long n = idx->T[b];
@@ -595,10 +595,12 @@ int useful_splits(const lc_index* idx, int G, int budget, int splits) {
     if (need < splits) splits = (int)need;
     // One workgroup per compute unit instead of two where that leaves few units idle and no split more than a few steps
     // of tokens: the selection runs once per unit and the merge has half the partials, at the price of loads in flight.
-    // Steps of 10 to 128 pairs, us with two and with one: group size 4, 93 tokens a split 12.8 and 11.5, 78: 23.0 and 21.9, but 264: 14.4
-    // and 15.7; group size 7 (a larger merge), 118: 12.4 and 11.0, 274: 19.3 and 18.3, 338: 16.8 and 16.1.
+    // Time with one over time with two, by tokens of a split (of one).  Above group size 4: 0.90 to 0.98 at 100, 0.91 to 1.02 from 130 to 350, 0.95 to 1.05
+    // at 400 (16 to 224 (sequence, head) pairs of 166 to 2048 chunks).  Up to 4 with many chunks: 0.94 to 1.00 at 100, 0.97 to 1.06 at 130, 0.96 to 1.09 beyond (666
+    // to 3333); with few of them 0.93 to 0.98 at 100, 0.92 to 1.02 from 130 to 350, 0.98 to 1.02 at 400 (166 to 455): the line could be at 350 there as well, but
+    // from 192 on a step keeps the splits, and with them the bits, of lc_sparse_decode, which does not know the budget.
     const int pairs = idx->B * idx->H_kv, one = LC_COMPUTE_UNITS / pairs;
-    const long long few = G > 4 ? 352 : 192;
+    const long long few = G > 4 ? 352 : (max_M <= 512 ? 192 : 120);
     if (idx->cfg.decode_splits == 0 && splits > one && 8 * one * pairs >= 7 * LC_COMPUTE_UNITS && most <= few * one) splits = one;
     return splits;
 }
@@ -619,7 +621,7 @@ int decode_step_run(const lc_index* idx, const LcWs& w, const RetrievePlan& p, i
                     bool second_kernel_only = false) {
     const bool want_ids = chunk_ids != nullptr;
     const int G = H_q / idx->H_kv;
-    splits = useful_splits(idx, G, budget, splits);
+    splits = useful_splits(idx, G, p.max_M, budget, splits);
     int rc;
     // Every workgroup of the fused kernel repeats the selection with 256 threads: with a few thousand
     // chunks that is cheaper than the hand-off through a chunk list, with more it is not.
