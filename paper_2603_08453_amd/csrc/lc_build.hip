@@ -1952,9 +1952,12 @@ int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const i
             maxK = idx->N[b * LC_MAX_LEVELS + l + 1] > maxK ? idx->N[b * LC_MAX_LEVELS + l + 1] : maxK;
         }
         // Several clusters per workgroup where they are small, or where one each would be thousands of workgroups that all read every
-        // label (8 heads, 10.6 K points in 660 clusters, update and centers: 66 and 71 us one by one, 25 and 29 here; but 332 clusters of
-        // 32: 39 and 42, 43 and 49; 249 of 22: centers 27 and 29).
-        const bool few = maxN <= (long long)maxK * LC_UPD_FEW || (maxN <= (long long)maxK * LC_UPD_FEW_MANY && maxK * BH > 2048);
+        // label.  Clusterings with one and with several, us by members a cluster (clusters in all): 8 heads x 3000 points 206 and 201 at 9 (2672),
+        // 252 and 260 at 11 (2184); x 6000 483 and 419 at 15 (3200), 478 and 480 at 17 (2824), 504 and 519 at 19 (2528); x 10.9K 1022 and 766 at 19 (4592), 916
+        // and 761 at 28 (3120), 793 and 852 at 33 (2648); 16 pairs x 5000 627 and 593 at 19 (4224), 500 and 560 at 28 (2864); 32 x 4000 466 and 453 at 19 (6752);
+        // 2 heads x 40K 2405 and 1246 at 21 (3810); one x 60K 2281 and 1369 at 28 (2143).  So where every cluster reads few labels (below 8192 points) it
+        // takes more clusters; with many points the line could be at more members than it is.
+        const bool few = maxN <= (long long)maxK * LC_UPD_FEW || (maxN <= (long long)maxK * LC_UPD_FEW_MANY && maxK * BH > (maxN < 8192 ? 2600 : 2048));
         // clusters per workgroup of the kernels that list several: one per 16-lane group, more of them where
         // that would be over a thousand workgroups that each read all the labels
         const int per = (maxK + LC_BG - 1) / LC_BG * BH > 1024 ? LC_UB_MAX : LC_BG;
