@@ -117,9 +117,15 @@ __device__ __forceinline__ float lc_probability(float x) {
     return __builtin_amdgcn_exp2f(x + (small ? 64.f : 0.f)) * (small ? __builtin_ldexpf(1.f, -64 - LC_DEC_LAG) : __builtin_ldexpf(1.f, -LC_DEC_LAG));
 }
 
-// What a sum is scaled by when its reference moves from `from` up to `to`: a power of two, at least the smallest number there is, so
-// that an infinite sum stays one.
-__device__ __forceinline__ float lc_rescale(float from, float to) { return fmaxf(exp2f(from - to), __builtin_ldexpf(1.f, -149)); }
+// Sums whose references lie `by` powers of two apart are added by fma with 2^by.  Where that is below float32's range, an infinite sum has
+// become something that is no number; only then the sums are added once more, each with its infinities (multiplied by 2^-149
+// twice: once would leave 2^-22 of the largest finite ones).
+__device__ __forceinline__ bool lc_no_number(const float4& x) { return __ballot(!((x.x + x.y) + (x.z + x.w) == (x.x + x.y) + (x.z + x.w))) != 0ull; }
+__device__ __forceinline__ void lc_add_scaled(float4& sum, const float4& x, float by) {
+    const float f = by == 0.f ? __builtin_ldexpf(1.f, -149) : 1.f, g = by == 0.f ? f : by;
+    sum.x = fmaf(x.x * f, g, sum.x); sum.y = fmaf(x.y * f, g, sum.y);
+    sum.z = fmaf(x.z * f, g, sum.z); sum.w = fmaf(x.w * f, g, sum.w);
+}
 
 // FUSED = false: the chunk list comes from a.ids / a.counts.  FUSED = true: every workgroup first
 // repeats the budget selection of its (sequence, head) from the chunk score keys -- the same
@@ -372,9 +378,12 @@ lc_decode_kernel(const LcDecodeArgs a) {
         return d;
     };
     // one online-softmax update of this lane's head with the logits of batches it and it + 1 (N = 8) or it alone (N = 4);
-    // whether any of the probabilities is too small for attend1 and attend2 (uniform)
-    auto softmax = [&](auto count, int it, lc_f32x4 dA, lc_f32x4 dB, auto& p) LC_INLINE -> bool {
+    // whether any of the probabilities is too small for attend1 and attend2 (uniform).  `plain`: for attend_plain, which takes probabilities
+    // over the whole of float32's range: the reference does not lag, nothing is lowered, -0 for a logit of -inf.
+    auto softmax = [&](auto count, auto plain, int it, lc_f32x4 dA, lc_f32x4 dB, auto& p) LC_INLINE -> bool {
         constexpr int N = decltype(count)::value;
+        constexpr bool PLAIN = decltype(plain)::value;
+        constexpr float LAG = PLAIN ? 0.f : (float)LC_DEC_LAG;
         float x[N];                                             // logits, not yet scaled
         float mx = LC_NEG_INF;
 #pragma unroll
@@ -384,25 +393,29 @@ lc_decode_kernel(const LcDecodeArgs a) {
         }
         mx = lc_max_groups(mx) * scale;
         // The reference follows the maximum only when it falls behind by more than LC_DEC_LAG: the accumulators are scaled once or
-        // not at all per split instead of once per step.  It is a whole number, so that scaling rounds nothing.
-        if (__ballot(mx > m_ref + (float)LC_DEC_LAG) != 0ull) {
-            const float m_new = mx > m_ref + (float)LC_DEC_LAG ? ceilf(mx) : m_ref;
-            const float sc = (m_new == LC_NEG_INF) ? 1.f : lc_rescale(m_ref, m_new);
+        // not at all per split instead of once per step.  It is a whole number, so that scaling rounds nothing (and leaves an infinite sum one).
+        if (__ballot(mx > m_ref + LAG) != 0ull) {
+            const float m_new = mx > m_ref + LAG ? ceilf(mx) : m_ref;
+            const int by = (int)fmaxf(m_ref - m_new, -1024.f);    // (of sums that are not zero: their reference is not -inf)
             const bool started = __ballot(m_ref > LC_NEG_INF) != 0ull;
             m_ref = m_new;
             if (started) {                                      // (before that the accumulators are zero)
-                l_run *= sc;
+                l_run = __builtin_ldexpf(l_run, by);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const float sr = __shfl(sc, 4 * q4 + r);
+                    const int by_r = __shfl(by, 4 * q4 + r);
 #pragma unroll
-                    for (int c = 0; c < 8; ++c) acc[c][r] *= sr;
+                    for (int c = 0; c < 8; ++c) acc[c][r] = __builtin_ldexpf(acc[c][r], by_r);
                 }
             }
         }
         const float ref = (m_ref == LC_NEG_INF) ? 0.f : m_ref;
 #pragma unroll
-        for (int u = 0; u < N; ++u) p[u] = lc_probability(fmaf(x[u], scale, -ref));
+        for (int u = 0; u < N; ++u) {
+            const float y = fmaf(x[u], scale, -ref);
+            if constexpr (PLAIN) p[u] = x[u] == LC_NEG_INF ? -0.f : exp2f(y);
+            else p[u] = lc_probability(y);
+        }
         float l = (p[0] + p[1]) + (p[2] + p[3]);
         if constexpr (N == 8) l += (p[4] + p[5]) + (p[6] + p[7]);
         l_run += l;
@@ -464,9 +477,8 @@ lc_decode_kernel(const LcDecodeArgs a) {
         return __ballot(m.x >= 0x5f80 || m.y >= 0x5f80) != 0ull;
     };
     // P.V of two batches in float32 on the vector ALU: this lane's columns of its group's tokens, a head at a time, then summed over the
-    // groups.  A probability is at least the smallest number there is: an infinite value reaches its column however little its
-    // token weighs.
-    auto attend_plain = [&](const float (&p)[2 * U], int it, const lc_v4i (&vA)[U], const lc_v4i (&vB)[U]) LC_INLINE {
+    // groups.  An infinite value reaches its column however little its token weighs (unless its logit is -inf).
+    auto attend_plain = [&](const float (&p)[2 * U], const lc_v4i (&vA)[U], const lc_v4i (&vB)[U]) LC_INLINE {
 #pragma unroll 1
         for (int g = 0; g < G; ++g) {
             float y[8];
@@ -474,12 +486,12 @@ lc_decode_kernel(const LcDecodeArgs a) {
             for (int c = 0; c < 8; ++c) y[c] = 0.f;
 #pragma unroll
             for (int u = 0; u < 2 * U; ++u) {
-                float pu = __shfl(p[u], 16 * q4 + g);
-                if (tv + it * U + u < tv_end) pu = fmaxf(pu, __builtin_ldexpf(1.f, -149));
+                float pu = __shfl(p[u], 16 * q4 + g), f = 1.f;
+                if (__float_as_uint(pu) == 0u) pu = f = __builtin_ldexpf(1.f, -149);      // below float32's range: 0 but for infinite values
 #pragma unroll
                 for (int c = 0; c < 8; ++c) {
                     const uint32_t w = (uint32_t)(u < U ? vA[u % U][c / 2] : vB[u % U][c / 2]);
-                    y[c] = fmaf(pu, (c & 1) ? lc_bf16_hi(w) : lc_bf16_lo(w), y[c]);
+                    y[c] = fmaf(pu, ((c & 1) ? lc_bf16_hi(w) : lc_bf16_lo(w)) * f, y[c]);
                 }
             }
 #pragma unroll
@@ -583,14 +595,19 @@ lc_decode_kernel(const LcDecodeArgs a) {
             for (int w = 0; w < LC_DEC_THREADS / 64; ++w) mx = __builtin_elementwise_maximum(mx, ph.comb.ml[w][g][0]);      // (hands on what is not a number)
             float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
             float den = 0.f;
+            const float ref = mx == LC_NEG_INF ? 0.f : mx;
 #pragma unroll
             for (int w = 0; w < LC_DEC_THREADS / 64; ++w) {
-                const float mw = ph.comb.ml[w][g][0];
-                const float sc = (mw == LC_NEG_INF) ? 0.f : lc_rescale(mw, mx);
+                const float sc = exp2f(ph.comb.ml[w][g][0] - ref);
                 const float4 x = ph.comb.acc[w][g][c4];
                 num.x = fmaf(x.x, sc, num.x); num.y = fmaf(x.y, sc, num.y);
                 num.z = fmaf(x.z, sc, num.z); num.w = fmaf(x.w, sc, num.w);
                 den = fmaf(ph.comb.ml[w][g][1], sc, den);
+            }
+            if (__builtin_expect(lc_no_number(num), 0)) {
+                num = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 1
+                for (int w = 0; w < LC_DEC_THREADS / 64; ++w) lc_add_scaled(num, ph.comb.acc[w][g][c4], exp2f(ph.comb.ml[w][g][0] - ref));
             }
             lc_store_agent4(pacc_w, v * 16, num);
             if (c4 == 0) { lc_store_agent(&pml[2 * g], mx); lc_store_agent(&pml[2 * g + 1], den); }
@@ -614,7 +631,7 @@ lc_decode_kernel(const LcDecodeArgs a) {
                 const lc_f32x4 dA = logits(kA), dB = logits(kB);
                 if (more) { k_offsets(it + 2, ko); load_k(ko, kA, kB); }
                 float p[2 * U];
-                const bool faint = softmax(std::integral_constant<int, 2 * U>(), it, dA, dB, p);
+                const bool faint = softmax(std::integral_constant<int, 2 * U>(), std::false_type(), it, dA, dB, p);
                 if (__builtin_expect(faint, 0)) again = again || large(vA, vB);
                 attend2(p, vA, vB);
                 if (more) { v_offsets(it + 2, vo); load_v(vo, vA, vB); }
@@ -622,7 +639,7 @@ lc_decode_kernel(const LcDecodeArgs a) {
             if (it < n_it) {
                 const lc_f32x4 dA = logits(kA);
                 float p[U];
-                const bool faint = softmax(std::integral_constant<int, U>(), it, dA, dA, p);
+                const bool faint = softmax(std::integral_constant<int, U>(), std::false_type(), it, dA, dA, p);
                 if (__builtin_expect(faint, 0)) again = again || large(vA, vA);
                 attend1(p, vA);
             }
@@ -691,10 +708,14 @@ lc_decode_kernel(const LcDecodeArgs a) {
                     v_offsets(it, vo);
                     load_v(vo, vA, vB);
                     float p[2 * U];
-                    softmax(std::integral_constant<int, 2 * U>(), it, logits(kA), logits(kB), p);
-                    attend_plain(p, it, vA, vB);
+                    softmax(std::integral_constant<int, 2 * U>(), std::true_type(), it, logits(kA), logits(kB), p);
+                    attend_plain(p, vA, vB);
                 }
             });
+            // (what lc_probability does to the others' probabilities)
+            l_run *= __builtin_ldexpf(1.f, -LC_DEC_LAG);
+#pragma unroll
+            for (int c = 0; c < 8; ++c) acc[c] *= __builtin_ldexpf(1.f, -LC_DEC_LAG);
             meet(false);
             __syncthreads();
             store_partial(sp);
@@ -712,7 +733,8 @@ lc_decode_kernel(const LcDecodeArgs a) {
             const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(m_all), __float_as_uint(m_all), false, false);
             m_all = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
         }
-        // (zero scales up to the end of the last round)
+        // (up to the end of the last round, where sums are zero)
+        const float ref = m_all == LC_NEG_INF ? 0.f : m_all;
         const int n_slots = (n_part + MR * WAYS - 1) / (MR * WAYS) * (MR * WAYS);
         for (int sp = hl; sp < n_slots; sp += 32) {
             float ms = m0, ls = l0;
@@ -720,7 +742,7 @@ lc_decode_kernel(const LcDecodeArgs a) {
                 ms = sp < n_part ? lc_load_agent(pml + 2 * (sp * G + g)) : LC_NEG_INF;
                 ls = sp < n_part ? lc_load_agent(pml + 2 * (sp * G + g) + 1) : 0.f;
             }
-            const float sc = (ms == LC_NEG_INF) ? 0.f : lc_rescale(ms, m_all);
+            const float sc = exp2f(ms - ref);
             ph.scale[half][sp] = sc;
             den = fmaf(ls, sc, den);
         }
@@ -742,6 +764,12 @@ lc_decode_kernel(const LcDecodeArgs a) {
                 acc4.z = fmaf(x[k].z, sc, acc4.z);
                 acc4.w = fmaf(x[k].w, sc, acc4.w);
             }
+        }
+        if (__builtin_expect(lc_no_number(acc4), 0)) {
+            acc4 = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 1
+            for (int sp = wy; sp < n_part; sp += WAYS)
+                lc_add_scaled(acc4, lc_load_agent4(pacc_r, ((sp * G + g) * LC_D + 4 * c4) * 4), ph.scale[half][sp]);
         }
         if (WAYS > 1 && wy > 0) rw.red[(wy - 1) * NV + v] = acc4;
     }

@@ -145,9 +145,9 @@ def test_values_of_light_tokens(tokens, splits, light, heavy, below, G):
         out, lse = _attend(q, K, values[None, None].cuda(), splits)
         v = values.double()
         ref = p @ v
-        # as above; the light token's probability is off by the last bit of float32's range (at most one scaling on its way loses as
-        # much again, twice), against sums of 2^-9 and more
-        bound = rel[:, None] * (p @ v.abs()) + 3 * T * 2.0 ** -149 * 2.0 ** 9 + 4 * 2.0 ** -149 * 2.0 ** 9 * v[light].abs()
+        # as above; the light token's probability is off by the last bit of float32's range at most (and at most one scaling on its
+        # way loses as much again, twice), where the heaviest's is 1
+        bound = rel[:, None] * (p @ v.abs()) + 3 * T * 2.0 ** -149 * 2.0 ** 9 + 4 * 2.0 ** -149 * v[light].abs()
         finite = torch.isfinite(v).all(dim=0)
         assert ((out - ref).abs() <= bound)[:, finite].all(), ((out - ref).abs() / bound)[:, finite].max()
         assert torch.equal(out[:, ~finite], ref[:, ~finite])       # infinities of the sign that float64 gives
