@@ -119,6 +119,7 @@ def test_an_iteration_follows_from_the_one_before(H, chunks, F, level, config, i
     bits, those without a change left alone: up to one window of 4096 points and beyond, blocks of 64 points with a
     remainder, batches of unequal sequences."""
     before, after = build(H, chunks, F, iters, **config), build(H, chunks, F, iters + 1, **config)
+    checked = 0
     for s1, s2 in zip(before, after):
         for h in (0, H - 1):
             here1, here2 = s1["heads"][h], s2["heads"][h]
@@ -134,6 +135,8 @@ def test_an_iteration_follows_from_the_one_before(H, chunks, F, level, config, i
             np.add.at(total, lab, x)
             check_labels(here2[level]["parent"], x, unit(total))
             check_tree(here2)
+            checked += s1 is before[0]
+    assert checked > 0                                      # (the first sequence, the one of the size that is asked for)
 
 
 @pytest.mark.parametrize("H,chunks,F,levels,centers,spread", [
