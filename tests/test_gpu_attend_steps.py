@@ -61,7 +61,7 @@ def test_against_float64(tokens, splits, G):
 
 
 def _attend(q, K, V, splits):
-    """Output and log-sum-exp of a step that attends to every token of one sequence, float64 on the CPU."""
+    """Output and log-sum-exp of a step that attends to every token of one sequence and of the two calls in its place, float64 on the CPU."""
     import torch
     from paper_2603_08453_amd import binding as lc
     H, T = K.shape[1], K.shape[2]
@@ -73,7 +73,12 @@ def _attend(q, K, V, splits):
     out = torch.full((1, q.shape[1], 128), float("nan"), device="cuda")
     lse = torch.full((1, q.shape[1]), float("nan"), device="cuda")
     lc.lc_decode_step(idx, q, K, V, 10 ** 6, out, ws, lse=lse)
-    return out[0].double().cpu(), lse[0].double().cpu()
+    step = (out[0].double().cpu(), lse[0].double().cpu())
+    ids = torch.full((1, H, len(bounds)), -7, dtype=torch.int32, device="cuda")
+    n = torch.full((1, H), -1, dtype=torch.int32, device="cuda")
+    lc.lc_retrieve(idx, q, 10 ** 6, ids, n, ws)
+    lc.lc_sparse_decode(idx, q, K, V, ids, n, out.fill_(float("nan")), ws, lse=lse.fill_(float("nan")))
+    return step, (out[0].double().cpu(), lse[0].double().cpu())
 
 
 def _aimed(logits, G):
@@ -108,15 +113,15 @@ def test_large_and_small_values(tokens, splits, G):
         for c in range(128):
             V[heavy[c % len(heavy)], c] = scale
         V = V.to(torch.bfloat16).cuda()[None, None].contiguous()
-        out, lse = _attend(q, K, V, splits)
         v = V[0, 0].double().cpu()
         # as above; and of values this small a sum is cut off at the last bit of float32's range, at most once per product and
         # term of its probability, divided by a sum of probabilities that are 2^-9 and more where they are largest
         rel = 2.0 * (2.0 ** -21 * x.abs().amax(dim=-1) + 2.0 ** -20)
         bound = rel[:, None] * (p @ v.abs()) + 3 * T * 2.0 ** -149 * 2.0 ** 9
-        assert torch.isfinite(out).all()
-        assert ((out - p @ v).abs() <= bound).all(), ((out - p @ v).abs() / bound).max()
-        assert ((lse - torch.logsumexp(x, dim=-1)).abs() <= rel + 2.0 ** -22 * lse.abs()).all()
+        for out, lse in _attend(q, K, V, splits):
+            assert torch.isfinite(out).all()
+            assert ((out - p @ v).abs() <= bound).all(), ((out - p @ v).abs() / bound).max()
+            assert ((lse - torch.logsumexp(x, dim=-1)).abs() <= rel + 2.0 ** -22 * lse.abs()).all()
 
 
 @pytest.mark.parametrize("G", [1, 7, 8])
@@ -142,13 +147,13 @@ def test_values_of_light_tokens(tokens, splits, light, heavy, below, G):
     W[light, 5], W[light, 77] = float("inf"), float("-inf")
     rel = 2.0 * (2.0 ** -21 * x.abs().amax(dim=-1) + 2.0 ** -20)
     for values in (V, W):
-        out, lse = _attend(q, K, values[None, None].cuda(), splits)
         v = values.double()
         ref = p @ v
         # as above; the light token's probability is off by the last bit of float32's range at most (and at most one scaling on its
         # way loses as much again, twice), where the heaviest's is 1
         bound = rel[:, None] * (p @ v.abs()) + 3 * T * 2.0 ** -149 * 2.0 ** 9 + 4 * 2.0 ** -149 * v[light].abs()
         finite = torch.isfinite(v).all(dim=0)
-        assert ((out - ref).abs() <= bound)[:, finite].all(), ((out - ref).abs() / bound)[:, finite].max()
-        assert torch.equal(out[:, ~finite], ref[:, ~finite])       # infinities of the sign that float64 gives
-        assert ((lse - torch.logsumexp(x, dim=-1)).abs() <= rel + 2.0 ** -22 * lse.abs()).all()
+        for out, lse in _attend(q, K, values[None, None].cuda(), splits):
+            assert ((out - ref).abs() <= bound)[:, finite].all(), ((out - ref).abs() / bound)[:, finite].max()
+            assert torch.equal(out[:, ~finite], ref[:, ~finite])       # infinities of the sign that float64 gives
+            assert ((lse - torch.logsumexp(x, dim=-1)).abs() <= rel + 2.0 ** -22 * lse.abs()).all()
