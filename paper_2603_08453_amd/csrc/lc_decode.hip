@@ -36,7 +36,7 @@
 #define LC_DEC_MAX_SPLITS 256
 #define LC_DEC_TILE 1024          // tokens of a split whose cache rows are resolved into LDS at a time
 #define LC_DEC_LAG 8              // powers of two that a logit may lie above the softmax's reference
-#define LC_DEC_FAINT -102.f       // logits that lie further below the reference have probabilities that lc_split3 does not hold (below 2^-110)
+#define LC_DEC_FAINT -101.f       // logits that lie further below the reference have probabilities that lc_split3 does not hold (below 2^-109)
 #define LC_DEC_E 2                // selected ids per thread and pass of the row resolution
 #define LC_LOG2E 1.4426950408889634f
 #define LC_LN2 0.6931471805599453f
@@ -69,8 +69,8 @@ struct LcDecodeArgs {
 
 // N probabilities as three bfloat16 terms each, packed in pairs: t[s] holds the terms number s.  The three add up to
 // the float32 value exactly: each takes the upper eight of the bits that are left, and where those are all of them, one unit less, so
-// that something is left (a term of zero would turn an infinite V into a not-a-number).  Below 2^-110 the lowest bits have no
-// place in bfloat16's range: where such a probability meets a value of 2^64 or more, infinities among them, the split is done
+// that something is left (a term of zero would turn an infinite V into a not-a-number).  Below 2^-109 one in 65536
+// has a term of zero, below 2^-110 the lowest bits have no place in bfloat16's range: where such a probability meets a value of 2^64 or more, infinities among them, the split is done
 // again on the vector ALU (attend_plain) by the workgroup that merges; smaller values are off by less than 2^-69.
 template <int N>
 __device__ __forceinline__ void lc_split3(const float (&p)[N], int (&t)[3][N / 2]) {

@@ -157,3 +157,33 @@ def test_values_of_light_tokens(tokens, splits, light, heavy, below, G):
             assert ((out - ref).abs() <= bound)[:, finite].all(), ((out - ref).abs() / bound)[:, finite].max()
             assert torch.equal(out[:, ~finite], ref[:, ~finite])       # infinities of the sign that float64 gives
             assert ((lse - torch.logsumexp(x, dim=-1)).abs() <= rel + 2.0 ** -22 * lse.abs()).all()
+
+
+@pytest.mark.parametrize("top", [99, 100, 101, 102])
+def test_infinite_values_where_three_terms_end(top):
+    """Seven of eight tokens weigh 2^-top to 2^-(top + 1) of the eighth, in 200 K different ways: of so many, some have low bits that leave
+    nothing for the second term where the bits run out.  All of them are infinite in one column, which is infinite then."""
+    import torch
+    T, G = 32768, 8
+    gen = torch.Generator()
+    gen.manual_seed(top)
+    unit = float(np.log(2.0) * 128 ** 0.5)                          # of a logit to base 2
+    q, K = torch.zeros((1, G, 128)), torch.zeros((1, 1, T, 128))
+    q[0, :, :4] = 1.0
+    q[0, :, 3] += torch.arange(G) / 16
+    K[0, 0, :, 0] = torch.tensor(-(top + 0.5) * unit).to(torch.bfloat16)
+    K[0, 0, :, 1] = -(top + 0.5) * unit - K[0, 0, 0, 0]
+    K[0, 0, :, 2] = (torch.rand(T, generator=gen) - 0.5) * 0.9 * unit
+    K[0, 0, :, 3] = (torch.rand(T, generator=gen) - 0.5) * 0.04 * unit
+    K[0, 0, ::8] = 0.0
+    K = K.to(torch.bfloat16)
+    V = torch.randn((T, 128), generator=gen)
+    V[:, 5] = float("inf")
+    V[::8, 5] = 0.0
+    q = q.to(torch.bfloat16)
+    x = q[0, :, :4].double() @ K[0, 0, :, :4].double().T / unit
+    light = x[:, torch.arange(T) % 8 != 0]
+    assert (light < -top).all() and (light > -top - 1).all()
+    for out, lse in _attend(q.cuda(), K.cuda(), V.to(torch.bfloat16)[None, None].cuda(), 4):
+        assert (out[:, 5] == float("inf")).all()
+        assert torch.isfinite(out[:, 6:]).all() and torch.isfinite(lse).all()
