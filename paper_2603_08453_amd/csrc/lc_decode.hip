@@ -147,7 +147,8 @@ lc_decode_kernel(const LcDecodeArgs a) {
     extern __shared__ __attribute__((aligned(16))) int lds_dyn[];
     using SelStore = typename std::conditional<FUSED, LcLeafSelSh, int>::type;
     using FusedStore = typename std::conditional<FUSED, LcFusedSh<LC_DEC_THREADS>, int>::type;
-    // What is used one after the other shares its place, so that three workgroups fit a compute unit (up to 2560 chunks).
+    // What is used one after the other shares its place, so that the two workgroups per compute unit that the registers allow fit its LDS with
+    // the longest chunk lists as well (group size 8: 26 KB and 49 KB of lists; side by side the parts would be 42 KB and more).
     union Phases {
         SelStore sel;                            // selection, crowded cutoff bin
         struct {                                 // the wavefronts' sums
