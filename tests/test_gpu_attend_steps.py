@@ -126,7 +126,7 @@ def test_large_and_small_values(tokens, splits, G):
 
 @pytest.mark.parametrize("G", [1, 7, 8])
 @pytest.mark.parametrize("below", [104, 112, 125, 145, 700])
-@pytest.mark.parametrize("tokens,splits,light,heavy", [(3, 1, 2, 0), (40, 1, 0, 39), (200, 1, 13, 199), (200, 1, 199, 0), (1100, 1, 3, 1090), (2500, 2, 10, 2400), (700, 0, 650, 5)])
+@pytest.mark.parametrize("tokens,splits,light,heavy", [(3, 1, 2, 0), (40, 1, 0, 39), (200, 1, 13, 199), (200, 1, 199, 0), (1100, 1, 3, 1090), (2500, 2, 10, 2400), (4500, 64, 4400, 10), (700, 0, 650, 5)])
 def test_values_of_light_tokens(tokens, splits, light, heavy, below, G):
     """One token weighs 2^-below of the heaviest.  An infinite value of it reaches its column whatever the weight, as it does in float64;
     a finite one is counted to float32's precision as far as the weight has a place in float32's range."""
