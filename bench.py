@@ -2,7 +2,7 @@
 
 A step = one decode step of one attention layer over the whole batch: Eq. 2 scoring of the
 chunks (with pruning when the index is large), budget selection, split-K attention over the
-selected chunks and the merge -- by default through lc_decode_step (two kernels, the second one
+selected chunks and the merge -- by default through lc_decode_step (one kernel, or two of which the second
 selects and attends), with --separate through lc_retrieve followed by lc_sparse_decode.
 Inputs are seeded synthetic tensors, resident in HBM before the timed region.
 To keep the numbers honest about HBM, consecutive steps walk over several
@@ -148,7 +148,8 @@ def bench_stream(args, w):
     lens = np.diff(blob["bounds"].astype(np.int64))
     ih, ch = ids.cpu().numpy(), counts.cpu().numpy()
     tok = sum(int(lens[ih[0, h, : ch[0, h]]].sum()) + (T_e - int(blob["bounds"][-1])) for h in range(w.H_kv))
-    dom_bytes = tok * 4 * w.d + w.H_q * w.d * 6 + M_e * w.H_kv * 12
+    one_kernel = lc.lc_bench_step_is_one_kernel(rp["idx"], w.H_q, w.budget)
+    dom_bytes = tok * 4 * w.d + w.H_q * w.d * 6 + M_e * w.H_kv * ((4 * w.d + 8) if one_kernel else 12)
     side = torch.cuda.Stream()
     g = torch.cuda.CUDAGraph()
     with torch.cuda.stream(side):
@@ -399,14 +400,14 @@ def main():
         torch.cuda.synchronize()
         retrieve_us = float(np.mean([e0.elapsed_time(e1) for e0, e1 in ev])) * 1e3
 
-    # The second kernel of lc_decode_step (selection + attention) by itself: back-to-back launches from
-    # a graph through the measurement aid lc_bench_select_attend -- every replica's workspace still
+    # The last kernel of lc_decode_step by itself: back-to-back launches from a graph through the measurement aid
+    # lc_bench_select_attend -- where it is the second of two (selection + attention), every replica's workspace still
     # holds the score keys of the query it is paired with here (replica r with query r mod nq).
     def step_fused_paired(i):
         rp = reps[i % R]
         lc.lc_decode_step(rp["idx"], Qs[(i % R) % nq], rp["K"], rp["V"], w.budget, out, rp["ws"])
 
-    def second_kernel_paired(i):
+    def last_kernel_paired(i):
         rp = reps[i % R]
         lc.lc_bench_select_attend(rp["idx"], Qs[(i % R) % nq], rp["K"], rp["V"], w.budget, out, rp["ws"])
 
@@ -416,12 +417,13 @@ def main():
             step_fused_paired(i)
         torch.cuda.synchronize()
         try:
-            second_kernel_paired(0)
-            fused_us, _ = graph_us_per_launch(second_kernel_paired, args.steps)
+            last_kernel_paired(0)
+            fused_us, _ = graph_us_per_launch(last_kernel_paired, args.steps)
         except lc.LycheeError as e:          # the step does not run as score + select/attend here (too many chunks, or top-k per level)
             if e.code != lc.LC_ERR_CAPACITY:
                 raise
-    two_kernel_step = fused_us is not None
+    fused_step = fused_us is not None
+    one_kernel_step = fused_step and lc.lc_bench_step_is_one_kernel(reps[0]["idx"], w.H_q, w.budget)
     if fused_us is None:
         fused_us = attend_us
 
@@ -585,11 +587,11 @@ def main():
                "single_thread": {"value": round(one_s * w.B * 1e6, 1), "unit": "us/step", "cores": 1}}
 
     # dominant kernel: the attention kernel (of lc_decode_step: it also repeats the selection, whose
-    # algorithmic input is one key and one boundary pair per chunk and head)
-    if args.separate or not two_kernel_step:
+    # algorithmic input is one key and one boundary pair per chunk and head, and scores the chunks where the step is one kernel)
+    if args.separate or not fused_step:
         dom_name, dom_us, dom_bytes = f"lc_decode_kernel<{G}, false", attend_us, attend_bytes
     else:
-        select_bytes = sum(len(bn) - 1 for bn in bounds_np) * w.H_kv * 12
+        select_bytes = sum(len(bn) - 1 for bn in bounds_np) * w.H_kv * (chunk_node_bytes if one_kernel_step else 12)
         dom_name, dom_us, dom_bytes = f"lc_decode_kernel<{G}, true", fused_us, attend_bytes + select_bytes
     # HBM traffic of that kernel: hardware counters cannot be read from inside this process, so the figure
     # is the one of the committed rocprofv3 --pmc summary of this workload (null if there is none)
@@ -603,7 +605,7 @@ def main():
                 dom_name = cells[1]
                 break
     if not dom_name.endswith(">"):
-        dom_name += ", 1, false>" if (args.separate or not two_kernel_step) else ", ...>"
+        dom_name += ", 1, false>" if (args.separate or not fused_step) else ", ...>"
     res = {
         "metric": "us per decode step per layer (retrieve+attend), 128K ctx" if w.name.startswith("C3") else
                   "us per decode step per layer (retrieve+attend)",

@@ -13,8 +13,9 @@
 extern "C" {
 #endif
 
-/* Launches only the second kernel of lc_decode_step (selection + attention) for callers who want
- * to time it alone.  It takes the chunk score keys that the previous lc_decode_step with the SAME
+/* Launches only the last kernel of lc_decode_step for callers who want to time it alone: the second of two (selection +
+ * attention), or the one that does it all where lc_bench_step_is_one_kernel says so (scoring too; what
+ * follows does not concern it then).  It takes the chunk score keys that the previous lc_decode_step with the SAME
  * query, index, budget and workspace left in the workspace: calling it in any other situation
  * gives undefined results (never a fault: every access is range-checked as in lc_decode_step).
  * Arguments, checks and error codes as lc_decode_step without the chunk list outputs;
@@ -22,6 +23,10 @@ extern "C" {
 int lc_bench_select_attend(const lc_index* idx, const void* q, const void* K, const void* V,
                            const int64_t kv_strides[3], int H_q, int budget,
                            float* out, float* lse, void* ws, size_t ws_bytes, void* stream);
+
+/* 1 if lc_decode_step runs as one kernel on this index as it stands, 0 if as several (or for a null index or a
+ * number of query heads that it refuses). */
+int lc_bench_step_is_one_kernel(const lc_index* idx, int H_q, int budget);
 
 /* Reads `bytes` bytes (a multiple of 16, from a 16-byte aligned device pointer) once with plain
  * streaming loads, so that a benchmark can quote the read bandwidth this GPU reaches.  `sink`

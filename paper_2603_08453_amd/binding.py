@@ -122,6 +122,8 @@ def lib() -> ctypes.CDLL:
     L.lc_bench_select_attend.argtypes = [vp, vp, vp, vp, i64p, ctypes.c_int, ctypes.c_int, vp, vp,
                                          vp, ctypes.c_size_t, vp]
     L.lc_bench_select_attend.restype = ctypes.c_int
+    L.lc_bench_step_is_one_kernel.argtypes = [vp, ctypes.c_int, ctypes.c_int]
+    L.lc_bench_step_is_one_kernel.restype = ctypes.c_int
     L.lc_bench_read_sweep.argtypes = [vp, ctypes.c_size_t, vp, ctypes.c_size_t, vp]
     L.lc_bench_read_sweep.restype = ctypes.c_int
     L.lc_append.argtypes = [vp, vp, vp, i64p, vp, vp, u8p, vp, ctypes.c_size_t, vp]
@@ -352,12 +354,17 @@ def lc_recluster(idx: Index, ws, stream=None) -> None:
 
 
 def lc_bench_select_attend(idx: Index, q, K, V, budget: int, out, ws, lse=None, stream=None) -> None:
-    """Measurement aid: the select+attend kernel of lc_decode_step alone, on the score keys that the
-    previous lc_decode_step with the same query, index, budget and workspace left in `ws`."""
+    """Measurement aid: the last kernel of lc_decode_step alone; of two, the one that selects and attends, on the score keys
+    that the previous lc_decode_step with the same query, index, budget and workspace left in `ws`."""
     assert K.shape == V.shape and K.stride() == V.stride()
     _check(lib().lc_bench_select_attend(idx.handle, _ptr(q), _ptr(K), _ptr(V), _strides3(K), int(q.shape[1]),
                                         int(budget), _ptr(out), _ptr(lse), _ptr(ws),
                                         ws.numel() * ws.element_size(), _stream(stream)), "lc_bench_select_attend")
+
+
+def lc_bench_step_is_one_kernel(idx: Index, q_heads: int, budget: int) -> bool:
+    """Whether lc_decode_step runs as one kernel on this index as it stands."""
+    return bool(lib().lc_bench_step_is_one_kernel(idx.handle, int(q_heads), int(budget)))
 
 
 def lc_bench_read_sweep(src, sink, stream=None) -> None:

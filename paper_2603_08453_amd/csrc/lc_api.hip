@@ -84,6 +84,7 @@ size_t lc_layout_index(const lc_config* cfg, int B, int H, int d, void* base, Lc
         D->nchunk[l] = c.take<int>(n);
         D->rbuild[l] = l >= 1 ? c.take<float>(n) : nullptr;
     }
+    D->posted = c.take<unsigned long long>(BH * D->cap[0]);
     return align_up(c.off);
 }
 
@@ -605,39 +606,49 @@ int useful_splits(const lc_index* idx, int G, int max_M, int budget, int splits)
     return splits;
 }
 
-// One kernel or two (without a level walk): every workgroup scoring all chunks costs 0.5 us per 64 chunks at group
-// size 4, twice that at 7 or 8, times the workgroups that share a compute unit; the scoring kernel costs about 2 us.
-// Measured from 16 to 256 chunks, 8 to 128 (sequence, head) pairs and group sizes 1, 4 and 7: up to 64 chunks
-// one kernel is always faster (by 0.3 to 2.8 us), up to 128 unless a large group meets several workgroups per unit
-// (16 sequences x 4 heads of group size 7: 1 us slower), at 192 hardly ever.
-bool step_is_single(int max_M, int G, long long workgroups) {
-    return max_M <= 64 || (max_M <= LC_STEP_SINGLE_MAX_CHUNKS && (G <= 4 || workgroups <= 256));
+// Scoring shared out over the workgroups of a (sequence, head) or a kernel of its own in front (more than lc_step_is_single takes).  Sharing saves a
+// launch, the entries' way through memory and the wait for the slowest of all (sequence, head) pairs; it costs a wait for the keys (two looks of 0.6 us),
+// which every workgroup reads, and where there are fewer workgroups than compute units the kernel in front scores on all of them.
+// Time of a step shared over that of two kernels, 2 to 128 pairs, group sizes 1 to 7, both kinds of centers: 0.87 to 0.98 at up to 64 chunks a
+// workgroup (1.00 to 1.02 at 1820 chunks with 64 workgroups); at 72 to 120 with the device full 0.88 to 0.95 (16 ragged sequences, group size 7: 27.6 and
+// 23.9 us) up to 1000 chunks, 0.99 at 2275 and 0.98 to 1.04 at 3640, with the device not full 1.01 to 1.10.
+bool step_shares_scoring(int max_M, int splits, long long workgroups) {
+    if (8 * workgroups >= 7 * LC_COMPUTE_UNITS) return max_M <= LC_STEP_SHARE_MAX_CHUNKS && max_M <= LC_STEP_SHARE_CHUNKS * splits;
+    return max_M <= 1536 && max_M <= 64 * splits;
+}
+
+enum { STEP_BY_LIST, STEP_TWO_KERNELS, STEP_ONE_KERNEL };
+// How a step over `splits` workgroups per (sequence, head) runs.
+int step_form(const lc_index* idx, const RetrievePlan& p, int G, int splits) {
+    // Every workgroup of the fused kernel repeats the selection with 256 threads: with a few thousand
+    // chunks that is cheaper than the hand-off through a chunk list, with more it is not.
+    if (idx->cfg.policy == LC_POLICY_BEAM || p.max_M > LC_STEP_FUSED_MAX_CHUNKS || !lc_decode_fused_fits(G, p.max_M)) return STEP_BY_LIST;
+    const long long workgroups = (long long)idx->B * idx->H_kv * splits;
+    return !p.walk && (lc_step_is_single(p.max_M, G, workgroups) || step_shares_scoring(p.max_M, splits, workgroups)) ? STEP_ONE_KERNEL : STEP_TWO_KERNELS;
 }
 
 // The step itself on a laid-out workspace (every check has passed).
 int decode_step_run(const lc_index* idx, const LcWs& w, const RetrievePlan& p, int splits, const void* q,
                     const void* K, const void* V, const int64_t kv_strides[3], int H_q, int budget, float* out,
                     float* lse, int32_t* chunk_ids, int32_t* counts, int cap, hipStream_t st,
-                    bool second_kernel_only = false) {
+                    bool last_kernel_only = false) {
     const bool want_ids = chunk_ids != nullptr;
     const int G = H_q / idx->H_kv;
     splits = useful_splits(idx, G, p.max_M, budget, splits);
     int rc;
-    // Every workgroup of the fused kernel repeats the selection with 256 threads: with a few thousand
-    // chunks that is cheaper than the hand-off through a chunk list, with more it is not.
-    if (idx->cfg.policy != LC_POLICY_BEAM && p.max_M <= LC_STEP_FUSED_MAX_CHUNKS && lc_decode_fused_fits(G, p.max_M)) {
+    const int form = step_form(idx, p, G, splits);
+    if (form != STEP_BY_LIST) {
         // kernel 1 (and the level walk before it) leaves the chunk score keys in the workspace;
-        // kernel 2 selects from them in every workgroup and attends.  With few chunks it does it all.
-        const bool single = !p.walk && step_is_single(p.max_M, G, (long long)idx->B * idx->H_kv * splits);
-        if (!single && !second_kernel_only) {
+        // kernel 2 selects from them in every workgroup and attends; or one kernel does it all.
+        if (form == STEP_TWO_KERNELS && !last_kernel_only) {
             rc = lc_launch_retrieve(idx, w, q, G, budget, nullptr, nullptr, nullptr, 1, p.max_M,
                                     p.walk ? p.max_upper : -1, 1, st);
             if (rc) return rc;
         }
         return lc_launch_decode_fused(idx, w, q, K, V, kv_strides, G, splits, budget, chunk_ids, counts,
-                                      want_ids ? cap : 0, p.max_M, single, out, lse, st);
+                                      want_ids ? cap : 0, p.max_M, form == STEP_ONE_KERNEL, out, lse, st);
     }
-    if (second_kernel_only) return LC_ERR_CAPACITY;
+    if (last_kernel_only) return LC_ERR_CAPACITY;
     // too many chunks for the registers of the selecting workgroups: the two kernels of lc_retrieve + lc_sparse_decode, with the
     // chunk list in the caller's buffer or, without one, in the workspace
     int32_t* ids = want_ids ? chunk_ids : w.ids_tmp;
@@ -662,7 +673,7 @@ int lc_decode_step(const lc_index* idx, const void* q, const void* K, const void
 
 int lc_decode_step_impl(const lc_index* idx, const void* q, const void* K, const void* V, const int64_t kv_strides[3],
                         int H_q, int budget, float* out, float* lse, int32_t* chunk_ids, int32_t* counts, int cap,
-                        void* ws, size_t ws_bytes, void* stream, bool second_kernel_only) {
+                        void* ws, size_t ws_bytes, void* stream, bool last_kernel_only) {
     int rc = decode_step_checks(idx, q, K, V, kv_strides, H_q, budget, out, chunk_ids, counts, cap);
     if (rc) return rc;
     if (!ws || (reinterpret_cast<uintptr_t>(ws) & 255u)) return LC_ERR_INVALID_ARG;
@@ -675,7 +686,14 @@ int lc_decode_step_impl(const lc_index* idx, const void* q, const void* K, const
     LcWs w;
     lc_layout_ws(&idx->cfg, idx->B, H_q, idx->H_kv, idx->d, splits, ws, &w);
     return decode_step_run(idx, w, p, splits, q, K, V, kv_strides, H_q, budget, out, lse, chunk_ids, counts, cap,
-                           static_cast<hipStream_t>(stream), second_kernel_only);
+                           static_cast<hipStream_t>(stream), last_kernel_only);
+}
+
+int lc_decode_step_is_one_kernel(const lc_index* idx, int H_q, int budget) {
+    RetrievePlan p;
+    if (!idx || H_q < idx->H_kv || H_q % idx->H_kv != 0 || budget < 0 || plan_retrieve(idx, budget, 1, false, &p) != LC_OK) return 0;
+    const int G = H_q / idx->H_kv;
+    return step_form(idx, p, G, useful_splits(idx, G, p.max_M, budget, lc_auto_splits(&idx->cfg, idx->B, idx->H_kv))) == STEP_ONE_KERNEL ? 1 : 0;
 }
 
 // ---------------------------------------------------------------------------------

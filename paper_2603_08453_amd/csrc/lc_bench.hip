@@ -54,5 +54,9 @@ extern "C" int lc_bench_select_attend(const lc_index* idx, const void* q, const 
                                       const int64_t kv_strides[3], int H_q, int budget, float* out, float* lse,
                                       void* ws, size_t ws_bytes, void* stream) {
     return lc_decode_step_impl(idx, q, K, V, kv_strides, H_q, budget, out, lse, nullptr, nullptr, 0, ws, ws_bytes,
-                               stream, /*second_kernel_only=*/true);
+                               stream, /*last_kernel_only=*/true);
+}
+
+extern "C" int lc_bench_step_is_one_kernel(const lc_index* idx, int H_q, int budget) {
+    return lc_decode_step_is_one_kernel(idx, H_q, budget);
 }

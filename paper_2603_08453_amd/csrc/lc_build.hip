@@ -2099,13 +2099,15 @@ lc_drift_kernel(LcDev ix, int level, float* out) {
 
 // staged (pinned host memory) = [state: B*H*4 | nlev: B*LC_MAX_LEVELS | where each sequence's boundaries begin: B |
 // boundaries: M_0 + 1, M_1 + 1, ...]; row b < B of the grid moves sequence b's boundaries, row B the counts (and
-// clears the arrival counters).  What bounds it is the way over the bus: two round trips, four words per thread in
+// clears the arrival counters), and all of them clear the posted keys.  What bounds it is the way over the bus: two round trips, four words per thread in
 // flight.
 #define LC_PS_WORDS (4 * LC_BT)
 __global__ void __launch_bounds__(LC_BT)
 lc_place_state_kernel(LcDev ix, const int32_t* staged, int B) {
     const int b = blockIdx.y, tid = threadIdx.x;
     const int n_state = B * ix.H * 4, n_nlev = B * LC_MAX_LEVELS;
+    const size_t n_posted = (size_t)B * ix.H * ix.cap[0];
+    for (size_t i = ((size_t)b * gridDim.x + blockIdx.x) * LC_BT + tid; i < n_posted; i += (size_t)gridDim.y * gridDim.x * LC_BT) ix.posted[i] = 0ull;
     if (b == B) {
         for (int i0 = blockIdx.x * LC_PS_WORDS; i0 < n_state + n_nlev; i0 += gridDim.x * LC_PS_WORDS) {
             int v[4];
@@ -2114,7 +2116,7 @@ lc_place_state_kernel(LcDev ix, const int32_t* staged, int B) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const int i = i0 + k * LC_BT + tid;
-                if (i < n_state) { ix.state[i] = v[k]; ix.sync[i] = 0; }
+                if (i < n_state) { ix.state[i] = v[k]; ix.sync[i] = (i & 3) == 3 ? 1 : 0; }
                 else if (i < n_state + n_nlev) ix.nlev[i - n_state] = v[k];
             }
         }

@@ -37,6 +37,7 @@
 #define LC_DEC_TILE 1024          // tokens of a split whose cache rows are resolved into LDS at a time
 #define LC_DEC_LAG 8              // powers of two that a logit may lie above the softmax's reference
 #define LC_DEC_FAINT -101.f       // logits that lie further below the reference have probabilities that lc_split3 does not hold (below 2^-109)
+#define LC_DEC_LOOKS 128          // times a wavefront looks for keys before it scores them itself (1 us each at least)
 #define LC_DEC_E 2                // selected ids per thread and pass of the row resolution
 #define LC_LOG2E 1.4426950408889634f
 #define LC_LN2 0.6931471805599453f
@@ -65,6 +66,7 @@ struct LcDecodeArgs {
     int budget, sink;     // token budget, tokens of the pinned prefix
     int ew;               // fused step: rows of 64 chunks per wavefront that hold the longest sequence (host side: picks EC)
     int max_tokens;       // rows of one (sequence, head) slab of K and V
+    int share;            // chunks that a workgroup scores (LC_SCORED_SHARED), a multiple of four
 };
 
 // N probabilities as three bfloat16 terms each, packed in pairs: t[s] holds the terms number s.  The three add up to
@@ -131,13 +133,19 @@ __device__ __forceinline__ void lc_add_scaled(float4& sum, const float4& x, floa
 // repeats the budget selection of its (sequence, head) from the chunk score keys -- the same
 // deterministic routine on the same keys, so all splits agree -- and never reads a chunk list.
 //
-// SCORE = true (with FUSED): it scores the chunks as well, so that the step is one kernel.  That costs every split
+// SCORE = LC_SCORED_HERE (with FUSED): it scores the chunks as well, so that the step is one kernel.  That costs every split
 // the scoring of all chunks -- four per group of lanes, 0.5 us and more for every 64 of them -- and saves a launch
-// and a pass through memory (113 chunks, 8 heads: 12.9 -> 11.3 us; where the line lies: step_is_single in the host code).
+// and a pass through memory (113 chunks, 8 heads: 12.9 -> 11.3 us; where the line lies: lc_step_is_single).
+//
+// SCORE = LC_SCORED_SHARED (with FUSED): each of the workgroups of a (sequence, head) scores a share of the chunks and posts their keys in the
+// index, all read all of them.  A key is posted together with the number of the step (`sync`), in one 8-byte access at agent scope, so a reader sees from the
+// word itself whether it is this step's: no counter, no wait for stores.  No workgroup depends on another one to get ahead: a wavefront that has
+// looked LC_DEC_LOOKS times for keys that are not there (a workgroup that has no place yet, behind another stream's kernel) scores
+// its chunks itself and posts what the others would have posted.
 //
 // Either way the selected chunks sit in a list, in id order; the wavefronts write the cache row of
 // every token of the split's tile into LDS, 64 lanes per overlapping chunk.
-template <int G, bool FUSED, int EC, bool SCORE>
+template <int G, bool FUSED, int EC, int SCORE>
 // (two wavefronts per SIMD asked for: without that the compiler puts the accumulators into the other half of the register
 // file and copies them back and forth)
 __global__ void __launch_bounds__(LC_DEC_THREADS, 2)
@@ -164,7 +172,7 @@ lc_decode_kernel(const LcDecodeArgs a) {
     __shared__ __attribute__((aligned(16))) Phases ph;
     __shared__ __attribute__((aligned(16))) Rows rw;
     __shared__ __attribute__((aligned(16))) FusedStore fused_store;
-    __shared__ lc_v4i entry_sh[SCORE ? LC_STEP_SINGLE_MAX_CHUNKS : 1];
+    __shared__ lc_v4i entry_sh[SCORE == LC_SCORED_HERE ? LC_STEP_SINGLE_MAX_CHUNKS : 1];
     __shared__ int scan_sh[8];
     __shared__ int last_sh;
     static_assert(sizeof(rw.red) <= sizeof(rw.row), "");
@@ -218,63 +226,139 @@ lc_decode_kernel(const LcDecodeArgs a) {
         return sum;
     };
 
-    // SCORE: entries of the chunks, 64 at a time: group `grp` has chunks 64 p + 4 grp + (0..3) of pass p < 2
-    static_assert(LC_STEP_SINGLE_MAX_CHUNKS <= 128, "two passes");
-    auto score_chunks = [&]() {
-        const int cap0 = ix.cap[0];
-        const size_t cb = (size_t)bh * cap0;
+    // Scoring of chunks in this kernel, N to a group of lanes at a time (1, 2 or 4).
+    struct Pass {
+        LcNodeFrag f[4];
+        float R;
+        int s0, s1;
+    };
+    uint32_t qp[SCORE != LC_SCORED_BEFORE ? G : 1][4];
+    float qn[SCORE != LC_SCORED_BEFORE ? G : 1];
+    // chunks j .. j + N - 1 (of this lane's group): their centers; radius and boundaries of number (sub & (N - 1)) of them.  From `end` on
+    // nothing is fetched (the offsets are past the arrays' ends).
+    auto load = [&](auto count, Pass& w, int j, int end) LC_INLINE {
+        constexpr int N = decltype(count)::value;
+        const int rows = min(ix.cap[0], LC_STEP_SHARE_MAX_CHUNKS);
+        j = j < end ? j : rows;
+        const size_t cb = (size_t)bh * ix.cap[0];
         const bool c0b = ix.c0_bf16 != 0;
         const int cen_row = c0b ? LC_D * 2 : LC_D * 4;
-        const __amdgpu_buffer_rsrc_t cen_r = lc_buffer(reinterpret_cast<const char*>(ix.center[0]) + cb * cen_row, cap0 * cen_row);
-        const __amdgpu_buffer_rsrc_t rad_r = lc_buffer(ix.radius[0] + cb, cap0 * 4);
-        const __amdgpu_buffer_rsrc_t bnd_r = lc_buffer(bnd, (cap0 + 1) * 4);
-        struct Pass {
-            LcNodeFrag f[4];
-            float R;
-            int s0, s1;
-        };
-        auto load = [&](Pass& w, int p) {
-            const int j = 64 * p + 4 * grp;
+        const __amdgpu_buffer_rsrc_t cen_r = lc_buffer(reinterpret_cast<const char*>(ix.center[0]) + cb * cen_row, rows * cen_row);
+        const __amdgpu_buffer_rsrc_t rad_r = lc_buffer(ix.radius[0] + cb, rows * 4);
+        const __amdgpu_buffer_rsrc_t bnd_r = lc_buffer(bnd, (rows + 1) * 4);
+        if (c0b) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if (c0b) {
-                    const lc_v2i x = __builtin_amdgcn_raw_buffer_load_b64(cen_r, (j + k) * cen_row + 8 * sub, 0, 0);
-                    const lc_v2i y = __builtin_amdgcn_raw_buffer_load_b64(cen_r, (j + k) * cen_row + 8 * sub + 128, 0, 0);
-                    w.f[k].a.x = __int_as_float(x.x); w.f[k].a.y = __int_as_float(x.y);
-                    w.f[k].b.x = __int_as_float(y.x); w.f[k].b.y = __int_as_float(y.y);
-                } else {
-                    w.f[k].a = lc_buf_load_f32x4(cen_r, (j + k) * cen_row + 16 * sub);
-                    w.f[k].b = lc_buf_load_f32x4(cen_r, (j + k) * cen_row + 16 * sub + 256);
-                }
+            for (int k = 0; k < N; ++k) {
+                const lc_v2i x = __builtin_amdgcn_raw_buffer_load_b64(cen_r, (j + k) * cen_row + 8 * sub, 0, 0);
+                const lc_v2i y = __builtin_amdgcn_raw_buffer_load_b64(cen_r, (j + k) * cen_row + 8 * sub + 128, 0, 0);
+                w.f[k].a = make_float4(__int_as_float(x.x), __int_as_float(x.y), 0.f, 0.f);
+                w.f[k].b = make_float4(__int_as_float(y.x), __int_as_float(y.y), 0.f, 0.f);
             }
-            const int own = j + (sub & 3);
-            w.R = lc_buf_load_f32(rad_r, own);
-            w.s0 = lc_buf_load_i32(bnd_r, own);
-            w.s1 = lc_buf_load_i32(bnd_r, own + 1);
-        };
-        uint32_t qp[G][4];
-        float qn[G];
+        } else {
+#pragma unroll
+            for (int k = 0; k < N; ++k) {
+                w.f[k].a = lc_buf_load_f32x4(cen_r, (j + k) * cen_row + 16 * sub);
+                w.f[k].b = lc_buf_load_f32x4(cen_r, (j + k) * cen_row + 16 * sub + 256);
+            }
+        }
+        const int own = j + (sub & (N - 1));
+        w.R = lc_buf_load_f32(rad_r, own);
+        w.s0 = lc_buf_load_i32(bnd_r, own);
+        w.s1 = lc_buf_load_i32(bnd_r, own + 1);
+    };
+    // key of chunk j + (sub & (N - 1)), in the lanes with (sub & 4) set
+    auto score = [&](auto count, Pass& w) LC_INLINE -> uint32_t {
+        constexpr int N = decltype(count)::value;
+        if (ix.c0_bf16) {
+#pragma unroll
+            for (int k = 0; k < N; ++k) w.f[k] = lc_widen_chunk_frag(w.f[k]);
+        }
+        const float sc = lc_score_packed<SCORE != LC_SCORED_BEFORE ? G : 1, N>(w.f, w.R, sub, qp, qn);
+        return a.budget > 0 && w.s0 >= a.sink ? lc_score_key(sc) : 0u;
+    };
+    using One = std::integral_constant<int, 1>;
+    using Two = std::integral_constant<int, 2>;
+    using Four = std::integral_constant<int, 4>;
+    // LC_SCORED_HERE: entries of the chunks, 64 at a time: group `grp` has chunks 64 p + 4 grp + (0..3) of pass p < 2
+    static_assert(LC_STEP_SINGLE_MAX_CHUNKS <= 128 && LC_STEP_SHARE_CHUNKS <= 128, "two passes");
+    auto score_chunks = [&]() LC_INLINE {
         // (both loads go out before the chunk count is known)
         Pass first, second;
-        load(first, 0);
-        if (cap0 > 64) load(second, 1);
-        lc_load_query_packed<G>(a.q + (size_t)b * ix.H * G * LC_D, h, sub, qp, qn);
-        auto score = [&](Pass& w, int p) {
-            if (c0b) {
-#pragma unroll
-                for (int k = 0; k < 4; ++k) w.f[k] = lc_widen_chunk_frag(w.f[k]);
-            }
-            const float sc = lc_score4_packed<G>(w.f, w.R, sub, qp, qn);
+        load(Four(), first, 4 * grp, LC_STEP_SINGLE_MAX_CHUNKS);
+        if (ix.cap[0] > 64) load(Four(), second, 64 + 4 * grp, LC_STEP_SINGLE_MAX_CHUNKS);
+        lc_load_query_packed<SCORE != LC_SCORED_BEFORE ? G : 1>(a.q + (size_t)b * ix.H * G * LC_D, h, sub, qp, qn);
+        auto enter = [&](Pass& w, int p) LC_INLINE {
             lc_v4i e;
-            e.x = a.budget > 0 && w.s0 >= a.sink ? (int)lc_score_key(sc) : 0;
+            e.x = (int)score(Four(), w);
             e.y = w.s0;
             e.z = max(0, w.s1 - w.s0);
             e.w = 0;
             if ((sub >> 2) == 1) entry_sh[64 * p + 4 * grp + (sub & 3)] = e;
         };
-        score(first, 0);
-        if (ix.state[bh * 4 + 1] > 64) score(second, 1);
+        enter(first, 0);
+        if (ix.state[bh * 4 + 1] > 64) enter(second, 1);
         lc_barrier_lds();
+    };
+    // LC_SCORED_SHARED: this workgroup's share of the chunks is scored and posted, then this lane's chunks j0 + 64 e are read
+    auto share_scores = [&](int j0, uint32_t (&key)[EC], int (&begin)[EC], int (&end)[EC]) LC_INLINE {
+        const int rows = min(ix.cap[0], LC_STEP_SHARE_MAX_CHUNKS);
+        const __amdgpu_buffer_rsrc_t bnd_r = lc_buffer(bnd, (rows + 1) * 4);
+        const __amdgpu_buffer_rsrc_t posted_r = lc_buffer(ix.posted + (size_t)bh * ix.cap[0], rows * 8);
+        const int lo = s * a.share, hi = min(lo + a.share, rows);
+        const int M = ix.state[bh * 4 + 1], number = ix.sync[bh * 4 + 3];
+        __builtin_amdgcn_sched_barrier(0);                          // (on their way before the first wait)
+        Pass first, second;
+        // (64 chunks first, or 32; a few more a chunk to a group)
+        const bool small = a.share <= 32, few_more = a.share <= 80;
+        if (small) load(Two(), first, lo + 2 * grp, hi);
+        else load(Four(), first, lo + 4 * grp, hi);
+        if (a.share > 64) {
+            if (few_more) load(One(), second, lo + 64 + grp, hi);
+            else load(Four(), second, lo + 64 + 4 * grp, hi);
+        }
+        lc_load_query_packed<SCORE != LC_SCORED_BEFORE ? G : 1>(a.q + (size_t)b * ix.H * G * LC_D, h, sub, qp, qn);
+        // (a chunk of its own per lane that stores; past the buffer's end nothing is stored)
+        auto post = [&](auto count, Pass& w, int j, int end) LC_INLINE {
+            constexpr int N = decltype(count)::value;
+            const lc_v2i x = {(int)score(count, w), number};
+            const int own = j + (sub & 3);
+            if ((sub >> 2) == 1 && (sub & 3) < N && own < end) __builtin_amdgcn_raw_buffer_store_b64(x, posted_r, own * 8, 0, 16);
+        };
+        const int mine = min(hi, M);                                // (whole wavefronts without a chunk have nothing to do)
+        if (small) {
+            if (lo + 8 * wave < mine) post(Two(), first, lo + 2 * grp, hi);
+        } else {
+            if (lo + 16 * wave < mine) post(Four(), first, lo + 4 * grp, hi);
+            if (few_more) {
+                if (lo + 64 + 4 * wave < mine) post(One(), second, lo + 64 + grp, hi);
+            } else {
+                if (lo + 64 + 16 * wave < mine) post(Four(), second, lo + 64 + 4 * grp, hi);
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < EC; ++e) {
+            begin[e] = __builtin_amdgcn_raw_buffer_load_b32(bnd_r, j0 * 4, e * 256, 0);
+            end[e] = __builtin_amdgcn_raw_buffer_load_b32(bnd_r, j0 * 4 + 4, e * 256, 0);
+        }
+        for (int looks = 1;; ++looks) {
+            lc_v2i x[EC];
+#pragma unroll
+            for (int e = 0; e < EC; ++e) x[e] = __builtin_amdgcn_raw_buffer_load_b64(posted_r, j0 * 8, e * 512, 16);
+            bool there = true;
+#pragma unroll
+            for (int e = 0; e < EC; ++e) {
+                key[e] = (uint32_t)x[e].x;
+                there = there && (x[e].y == number || j0 + 64 * e >= M);
+            }
+            if (__ballot(there) == ~0ull) break;
+            if (__builtin_expect(looks % LC_DEC_LOOKS == 0, 0)) {
+                for (int j = wave * (EC * 64); j < min((wave + 1) * (EC * 64), M); j += 4) {
+                    load(One(), first, j + q4, M);
+                    post(One(), first, j + q4, M);
+                }
+                __builtin_amdgcn_s_waitcnt(0);                      // (at the next look they are all there)
+            }
+        }
     };
 
     if constexpr (!FUSED) {
@@ -295,11 +379,15 @@ lc_decode_kernel(const LcDecodeArgs a) {
             n_tok += tot;
         }
     } else {
-        if constexpr (SCORE) score_chunks();
         const __amdgpu_buffer_rsrc_t ent_r = lc_buffer(a.entries + (size_t)bh * 4 * ix.cap[0], ix.cap[0] * 16);
         const int first = wave * (EC * 64) + lane;
+        uint32_t key[EC];
+        int begin[EC], end[EC];
+        if constexpr (SCORE == LC_SCORED_HERE) score_chunks();
+        if constexpr (SCORE == LC_SCORED_SHARED) share_scores(first, key, begin, end);
         auto entry = [&](int e) -> lc_v4i {
-            if constexpr (SCORE) return entry_sh[min(first + 64 * e, LC_STEP_SINGLE_MAX_CHUNKS - 1)];
+            if constexpr (SCORE == LC_SCORED_HERE) return entry_sh[min(first + 64 * e, LC_STEP_SINGLE_MAX_CHUNKS - 1)];
+            else if constexpr (SCORE == LC_SCORED_SHARED) return lc_v4i{(int)key[e], begin[e], max(0, end[e] - begin[e]), 0};
             else return __builtin_amdgcn_raw_buffer_load_b128(ent_r, first * 16, e * 1024, 0);
         };
         lc_select_chunks<LC_DEC_THREADS, EC>(ix, b, bh, entry, a.budget, a.sink, s == 0 ? a.ids_out : nullptr,
@@ -675,7 +763,7 @@ lc_decode_kernel(const LcDecodeArgs a) {
     float m_all = LC_NEG_INF, den = 0.f;
     float m0 = LC_NEG_INF, l0 = 0.f;                         // the first 32 splits (all of them unless more were asked for)
     auto fetch = [&]() LC_INLINE -> bool {                   // whether a split is to be done again (the same for the workgroup)
-        if (wy < WAYS && n_part > 0) load_round(wy);
+        load_round(wy);                                      // (by all threads: values kept from a load before would be in the way of doing splits again)
         if (hl < n_part) {
             m0 = lc_load_agent(pml + 2 * (hl * G + g));
             l0 = lc_load_agent(pml + 2 * (hl * G + g) + 1);
@@ -792,11 +880,15 @@ lc_decode_kernel(const LcDecodeArgs a) {
         }
     }
     if (tid == 0) ix.sync[bh * 4 + 1] = 0;
+    if (SCORE == LC_SCORED_SHARED && tid == 0) {                 // (every workgroup has read the number: it arrives behind that)
+        const int number = ix.sync[bh * 4 + 3];
+        ix.sync[bh * 4 + 3] = number == -1 ? 1 : number + 1;
+    }
 }
 
 template <int G>
 static int launch_decode_g(const LcDecodeArgs& a, int splits, hipStream_t stream) {
-    hipLaunchKernelGGL((lc_decode_kernel<G, false, 1, false>), dim3(splits, a.ix.H, a.ix.B), dim3(LC_DEC_THREADS), 0, stream, a);
+    hipLaunchKernelGGL((lc_decode_kernel<G, false, 1, LC_SCORED_BEFORE>), dim3(splits, a.ix.H, a.ix.B), dim3(LC_DEC_THREADS), 0, stream, a);
     LC_HIP_CHECK(hipGetLastError());
     return LC_OK;
 }
@@ -823,6 +915,7 @@ static void fill_common(LcDecodeArgs& a, const lc_index* idx, const LcWs& ws, co
     a.budget = 0;
     a.sink = 0;
     a.ew = 0;
+    a.share = 0;
     a.max_tokens = idx->cfg.max_tokens;
 }
 
@@ -856,7 +949,7 @@ bool lc_decode_fused_fits(int G, int max_M) {
     return G >= 1 && G <= LC_MAX_GROUP && max_M <= LC_DEC_THREADS * LC_DEC_EC_MAX;
 }
 
-template <int G, int EC, bool SCORE>
+template <int G, int EC, int SCORE>
 static int launch_fused_ge(const LcDecodeArgs& a, int splits, hipStream_t stream) {
     const size_t lds = lc_select_lds<LC_DEC_THREADS, EC>();   // the selection's chunk lists
     if (lds > 16 * 1024) {      // static + dynamic may pass the default per-workgroup allowance: raised once per device
@@ -871,13 +964,20 @@ static int launch_fused_ge(const LcDecodeArgs& a, int splits, hipStream_t stream
     return LC_OK;
 }
 template <int G>
-static int launch_fused_g(const LcDecodeArgs& a, int splits, hipStream_t stream) {
-    if (a.entries == nullptr) return launch_fused_ge<G, 1, true>(a, splits, stream);
-    if (a.ew <= 2) return launch_fused_ge<G, 2, false>(a, splits, stream);
-    if (a.ew <= 4) return launch_fused_ge<G, 4, false>(a, splits, stream);
-    if (a.ew <= 6) return launch_fused_ge<G, 6, false>(a, splits, stream);
-    if (a.ew <= 10) return launch_fused_ge<G, 10, false>(a, splits, stream);
-    return launch_fused_ge<G, LC_DEC_EC_MAX, false>(a, splits, stream);
+static int launch_fused_g(const LcDecodeArgs& a, int scoring, int splits, hipStream_t stream) {
+    if (scoring == LC_SCORED_HERE) return launch_fused_ge<G, 1, LC_SCORED_HERE>(a, splits, stream);
+    if (scoring == LC_SCORED_SHARED) {
+        static_assert(LC_STEP_SHARE_MAX_CHUNKS <= 10 * LC_DEC_THREADS, "");
+        if (a.ew <= 2) return launch_fused_ge<G, 2, LC_SCORED_SHARED>(a, splits, stream);
+        if (a.ew <= 4) return launch_fused_ge<G, 4, LC_SCORED_SHARED>(a, splits, stream);
+        if (a.ew <= 6) return launch_fused_ge<G, 6, LC_SCORED_SHARED>(a, splits, stream);
+        return launch_fused_ge<G, 10, LC_SCORED_SHARED>(a, splits, stream);
+    }
+    if (a.ew <= 2) return launch_fused_ge<G, 2, LC_SCORED_BEFORE>(a, splits, stream);
+    if (a.ew <= 4) return launch_fused_ge<G, 4, LC_SCORED_BEFORE>(a, splits, stream);
+    if (a.ew <= 6) return launch_fused_ge<G, 6, LC_SCORED_BEFORE>(a, splits, stream);
+    if (a.ew <= 10) return launch_fused_ge<G, 10, LC_SCORED_BEFORE>(a, splits, stream);
+    return launch_fused_ge<G, LC_DEC_EC_MAX, LC_SCORED_BEFORE>(a, splits, stream);
 }
 
 int lc_launch_decode_fused(const lc_index* idx, const LcWs& ws, const void* q, const void* K, const void* V,
@@ -886,8 +986,12 @@ int lc_launch_decode_fused(const lc_index* idx, const LcWs& ws, const void* q, c
                            hipStream_t stream) {
     LcDecodeArgs a;
     fill_common(a, idx, ws, q, K, V, ks, out, lse);
-    a.entries = single ? nullptr : ws.scratch;
-    if (single && max_M > LC_STEP_SINGLE_MAX_CHUNKS) return LC_ERR_CAPACITY;
+    a.entries = ws.scratch;
+    const int scoring = !single ? LC_SCORED_BEFORE
+                                : (lc_step_is_single(max_M, G, (long long)idx->B * idx->H_kv * splits) ? LC_SCORED_HERE : LC_SCORED_SHARED);
+    if (scoring == LC_SCORED_HERE && max_M > LC_STEP_SINGLE_MAX_CHUNKS) return LC_ERR_CAPACITY;
+    a.share = ((max_M + splits - 1) / splits + 3) / 4 * 4;
+    if (scoring == LC_SCORED_SHARED && (a.share > LC_STEP_SHARE_CHUNKS || max_M > LC_STEP_SHARE_MAX_CHUNKS)) return LC_ERR_CAPACITY;
     a.ids_out = ids_out;
     a.counts_out = counts_out;
     a.cap = cap;
@@ -896,14 +1000,14 @@ int lc_launch_decode_fused(const lc_index* idx, const LcWs& ws, const void* q, c
     a.ew = ((max_M > 0 ? max_M : 1) + LC_DEC_THREADS - 1) / LC_DEC_THREADS;
     if (a.ew > LC_DEC_EC_MAX) return LC_ERR_CAPACITY;
     switch (G) {
-        case 1: return launch_fused_g<1>(a, splits, stream);
-        case 2: return launch_fused_g<2>(a, splits, stream);
-        case 3: return launch_fused_g<3>(a, splits, stream);
-        case 4: return launch_fused_g<4>(a, splits, stream);
-        case 5: return launch_fused_g<5>(a, splits, stream);
-        case 6: return launch_fused_g<6>(a, splits, stream);
-        case 7: return launch_fused_g<7>(a, splits, stream);
-        case 8: return launch_fused_g<8>(a, splits, stream);
+        case 1: return launch_fused_g<1>(a, scoring, splits, stream);
+        case 2: return launch_fused_g<2>(a, scoring, splits, stream);
+        case 3: return launch_fused_g<3>(a, scoring, splits, stream);
+        case 4: return launch_fused_g<4>(a, scoring, splits, stream);
+        case 5: return launch_fused_g<5>(a, scoring, splits, stream);
+        case 6: return launch_fused_g<6>(a, scoring, splits, stream);
+        case 7: return launch_fused_g<7>(a, scoring, splits, stream);
+        case 8: return launch_fused_g<8>(a, scoring, splits, stream);
     }
     return LC_ERR_BAD_SHAPE;
 }

@@ -255,23 +255,24 @@ __device__ __forceinline__ float lc_score_frag_packed(const LcNodeFrag& f, float
     }
     return best;
 }
-// Four nodes at a time by a group of 16 lanes, each lane with its columns of all four: the score of node (sub & 3),
-// with radius R of that node, in the lanes with (sub & 4) set.  A head's query words are widened once for the
-// four nodes, and a sum over the lanes halves the values it carries in its first two steps instead of
-// leaving every node's sum in every lane: 54 instructions per head and four nodes instead of 92.  The
+// N = 1, 2 or 4 nodes at a time by a group of 16 lanes, each lane with its columns of all of them: the score of node (sub & (N - 1)),
+// with radius R of that node, in the lanes with (sub & 4) set.  A head's query words are widened once for all
+// nodes, and a sum over the lanes halves the values it carries in its first two steps instead of
+// leaving every node's sum in every lane: 54 instructions per head and four nodes instead of 92 (two: 31, one: 23).  The
 // additions are those of lc_sum16 in its order (lanes in pairs, quads, the two quads of each half, the halves): same bits.
-template <int G>
-__device__ __forceinline__ float lc_score4_packed(const LcNodeFrag (&f)[4], float R, int sub, const uint32_t (&qp)[G][4],
-                                                  const float (&qn)[G]) {
+template <int G, int N>
+__device__ __forceinline__ float lc_score_packed(const LcNodeFrag (&f)[4], float R, int sub, const uint32_t (&qp)[G][4],
+                                                 const float (&qn)[G]) {
+    static_assert(N == 1 || N == 2 || N == 4, "");
     float best = LC_NEG_INF;
     const bool odd = (sub & 1) != 0, upper = (sub & 2) != 0;
 #pragma unroll
     for (int g = 0; g < G; ++g) {
         uint32_t w0 = qp[g][0], w1 = qp[g][1], w2 = qp[g][2], w3 = qp[g][3];
         asm volatile("" : "+v"(w0), "+v"(w1), "+v"(w2), "+v"(w3));      // (widened here, see lc_score_frag_packed)
-        float p[4];
+        float p[N];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < N; ++k) {
             p[k] = f[k].a.x * lc_bf16_lo(w0);
             p[k] = fmaf(f[k].a.y, lc_bf16_hi(w0), p[k]);
             p[k] = fmaf(f[k].a.z, lc_bf16_lo(w1), p[k]);
@@ -282,16 +283,22 @@ __device__ __forceinline__ float lc_score4_packed(const LcNodeFrag (&f)[4], floa
             p[k] = fmaf(f[k].b.w, lc_bf16_hi(w3), p[k]);
             p[k] += lc_dpp<0xB1>(p[k]);                             // lane ^ 1
         }
-        float u = odd ? p[1] : p[0], v = odd ? p[3] : p[2];
-        u += lc_dpp<0x4E>(u);                                       // lane ^ 2
-        v += lc_dpp<0x4E>(v);
-        float t = upper ? v : u;                                    // node (sub & 3), summed over the quad
+        float t = N == 1 ? p[0] : (odd ? p[N > 1 ? 1 : 0] : p[0]);
+        t += lc_dpp<0x4E>(t);                                       // lane ^ 2
+        if constexpr (N == 4) {
+            float v = odd ? p[3] : p[2];
+            v += lc_dpp<0x4E>(v);
+            t = upper ? v : t;                                      // node (sub & 3), summed over the quad
+        }
         t += lc_dpp<0x124>(t);                                      // row_ror:4: the quad below
         t += lc_dpp<0x128>(t);                                      // row_ror:8
         best = fmaxf(best, fmaf(qn[g], R, t) * 0.08838834764831845f);
     }
     return best;
 }
+// The query group of KV head h as packed words (lane `sub` of a 16-lane group: the fragments above) and the norms.  All groups of a wavefront
+// hold the same words, so each works out the norm of another head: a chain of sixteen products and sums and a square
+// root per four heads instead of one per head, in the same order.
 template <int G>
 __device__ __forceinline__ void lc_load_query_packed(const uint16_t* __restrict__ q, int h, int sub,
                                                      uint32_t (&qp)[G][4], float (&qn)[G]) {
@@ -301,13 +308,24 @@ __device__ __forceinline__ void lc_load_query_packed(const uint16_t* __restrict_
         const uint2 a = *reinterpret_cast<const uint2*>(row + 4 * sub);
         const uint2 b = *reinterpret_cast<const uint2*>(row + 64 + 4 * sub);
         qp[g][0] = a.x; qp[g][1] = a.y; qp[g][2] = b.x; qp[g][3] = b.y;
+    }
+    const int group = (threadIdx.x >> 4) & 3;
+#pragma unroll
+    for (int g0 = 0; g0 < G; g0 += 4) {
         float s = 0.f;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            s = fmaf(lc_bf16_lo(qp[g][i]), lc_bf16_lo(qp[g][i]), s);
-            s = fmaf(lc_bf16_hi(qp[g][i]), lc_bf16_hi(qp[g][i]), s);
+            uint32_t w = qp[g0][i];
+#pragma unroll
+            for (int g = 1; g < 4; ++g)
+                if (g0 + g < G) w = group == g ? qp[g0 + g < G ? g0 + g : g0][i] : w;
+            s = fmaf(lc_bf16_lo(w), lc_bf16_lo(w), s);
+            s = fmaf(lc_bf16_hi(w), lc_bf16_hi(w), s);
         }
-        qn[g] = sqrtf(lc_sum16(s));
+        const float norm = sqrtf(lc_sum16(s));
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            if (g0 + g < G) qn[g0 + g < G ? g0 + g : g0] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(norm), 16 * g));
     }
 }
 

@@ -20,7 +20,9 @@ struct LcDev {
     int* state;      // [B][H][4]: {T, M, 0, 0}: tokens written, closed chunks (one copy per head)
     int* nlev;       // [B][LC_MAX_LEVELS]: nodes per level (entry 0 unused: level 0 has M nodes)
     int* bounds;     // [B][cap[0] + 1]: chunk boundaries (shared by the heads of a sequence)
-    int* sync;       // [B][H][4]: arrival counters of the fused kernels; zero between calls
+    int* sync;       // [B][H][4]: arrival counters of the fused kernels (0, 1), zero between calls; 3: number of the next decode step whose
+                     // workgroups share the scoring (never 0)
+    unsigned long long* posted;   // [B][H][cap[0]]: score keys that those workgroups post for each other: key, number of the step << 32
     float* center[LC_MAX_LEVELS];
     float* radius[LC_MAX_LEVELS];
     int* parent[LC_MAX_LEVELS];
@@ -102,12 +104,13 @@ struct LcOnce {
     }
 };
 
-// lc_decode_step with a switch for the measurement aid that launches its second kernel alone
-// (C linkage: it is defined among the entry points).
+// lc_decode_step with a switch for the measurement aid that launches its last kernel alone
+// (C linkage: defined among the entry points), and whether that one kernel is all of it.
 extern "C" int lc_decode_step_impl(const lc_index* idx, const void* q, const void* K, const void* V,
                                    const int64_t kv_strides[3], int H_q, int budget, float* out, float* lse,
                                    int32_t* chunk_ids, int32_t* counts, int cap, void* ws, size_t ws_bytes,
-                                   void* stream, bool second_kernel_only);
+                                   void* stream, bool last_kernel_only);
+extern "C" int lc_decode_step_is_one_kernel(const lc_index* idx, int H_q, int budget);
 
 // Limits of the two level walks (pure host functions).
 int lc_walk_max_internal_nodes();   // exact walk: internal nodes of one (sequence, head), all levels together
@@ -122,8 +125,22 @@ int lc_launch_retrieve(const lc_index* idx, const LcWs& ws, const void* q, int G
 int lc_launch_decode(const lc_index* idx, const LcWs& ws, const void* q, const void* K, const void* V,
                      const int64_t ks[3], const int32_t* ids, const int32_t* counts, int cap, int G,
                      int splits, float* out, float* lse, hipStream_t stream);
-// Fused step: selection from the chunk entries in ws.scratch (written by lc_launch_retrieve with score_only)
-// + attention; `single` (up to LC_STEP_SINGLE_MAX_CHUNKS chunks): the scoring as well.  lc_decode_fused_fits tells whether a selecting workgroup holds max_M chunks.
+// `single`: the scoring too.
+// Who scores the chunks of a fused step: a kernel before it (chunk entries in ws.scratch, lc_launch_retrieve with score_only), every
+// workgroup all of them (up to LC_STEP_SINGLE_MAX_CHUNKS), or the workgroups of a (sequence, head) a share each (up to LC_STEP_SHARE_CHUNKS of
+// LC_STEP_SHARE_MAX_CHUNKS in all).
+enum { LC_SCORED_BEFORE = 0, LC_SCORED_HERE = 1, LC_SCORED_SHARED = 2 };
+#define LC_STEP_SHARE_CHUNKS 128
+#define LC_STEP_SHARE_MAX_CHUNKS 2560
+// One kernel or two (without a level walk): every workgroup scoring all chunks costs 0.5 us per 64 chunks at group
+// size 4, twice that at 7 or 8, times the workgroups that share a compute unit; the scoring kernel costs about 2 us.
+// Measured from 16 to 256 chunks, 8 to 128 (sequence, head) pairs and group sizes 1, 4 and 7: up to 64 chunks
+// one kernel is always faster (by 0.3 to 2.8 us), up to 128 unless a large group meets several workgroups per unit
+// (16 sequences x 4 heads of group size 7: 1 us slower), at 192 hardly ever.
+inline bool lc_step_is_single(int max_M, int G, long long workgroups) {
+    return max_M <= 64 || (max_M <= LC_STEP_SINGLE_MAX_CHUNKS && (G <= 4 || workgroups <= 256));
+}
+// Fused step: selection + attention, with the scoring or after it.  lc_decode_fused_fits tells whether a selecting workgroup holds max_M chunks.
 bool lc_decode_fused_fits(int G, int max_M);
 int lc_launch_decode_fused(const lc_index* idx, const LcWs& ws, const void* q, const void* K, const void* V,
                            const int64_t ks[3], int G, int splits, int budget, int32_t* ids_out,

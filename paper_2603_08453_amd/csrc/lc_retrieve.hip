@@ -383,7 +383,7 @@ lc_upper_kernel(const LcRetrieveArgs a) {
 //   - everything whose address does not depend on a result is on its way before the first wait: the query,
 //     the top level's first rows, and the parent pointers of all levels straight into LDS (those that fit:
 //     the upper levels first);
-//   - a group of 16 lanes scores four nodes at a time (lc_score4_packed), the best are found by one wavefront from a
+//   - a group of 16 lanes scores four nodes at a time (lc_score_packed), the best are found by one wavefront from a
 //     histogram of 64 bins (lc_wave_cut), a list is written from the lanes' marks by one scan and one
 //     exchange of counts (gather below);
 //   - all levels run through one loop, so that the later ones find its code in the instruction cache;
@@ -832,7 +832,7 @@ lc_beam_kernel(const LcBeamArgs a) {
 #pragma unroll
                 for (int k = 0; k < 4; ++k) f[k] = lc_widen_chunk_frag(f[k]);
             }
-            const float sc = lc_score4_packed<G>(f, R, sub, qp, qn);
+            const float sc = lc_score_packed<G, 4>(f, R, sub, qp, qn);
             const int i = base + 4 * grp + (sub & 3);
             const int w = max(x1 - x0, 0);
             uint32_t key = lc_score_key(sc);

@@ -6,6 +6,7 @@
 #include "lc_internal.h"
 
 #define LC_SEL_CAND 16            // chunks of the cutoff bin per wavefront that are ranked directly
+#define LC_SEL_FEW 8              // of them in one step, a lane per pair
 #define LC_SEL_BINS_MAX 1024      // most bins of the selection histogram
 
 // Workgroup barrier that orders LDS accesses only: global loads issued before it stay in flight
@@ -31,7 +32,7 @@ struct LcChunkEntry {
 // overflows its short list, has its own block)
 template <int NT>
 struct LcFusedSh {
-    int hw[LC_SEL_BINS_MAX + 4];     // chunk lengths per bin; the slot after the last bin takes what is no candidate
+    int hw[LC_SEL_BINS_MAX + 64];    // chunk lengths per bin; the slots after the last bin take, lane by lane, what is in none
     int4 cand[NT / 64][LC_SEL_CAND]; // chunks of the cutoff bin, by wavefront: key, length, id
     int n_cand[NT / 64];
     uint32_t kmin[NT / 64], kmax[NT / 64];
@@ -64,7 +65,8 @@ struct LcChunkSel {
     int2* l_row;         // LDS: first row; length, or -1 - c for chunk c of the cutoff bin
     int* l_id;           // LDS: id (where the ids are wanted)
     int seg, n_list;     // this wavefront's entries (those of the cutoff bin among them, selected or not)
-    unsigned long long in_cut;     // chunks of the cutoff bin that are selected, by list position
+    unsigned long long in_cut;     // chunks of the cutoff bin that are selected: this wavefront's chunk c at bit (cut_first + c) << cut_shift
+    int cut_first, cut_shift;
     int st0, ln0, off0;  // this lane's entry of the first round: row, length (0 = not selected), offset among the wavefront's tokens
     int base_tok;        // selected tokens of the wavefronts before this one
     int n_sel_tok;       // selected tokens of the (sequence, head), without the open tail
@@ -81,7 +83,7 @@ __device__ __forceinline__ void lc_sel_entry(const LcChunkSel<EC>& o, const LcFu
     *st = x.x;
     if (l < 0) {                                                    // (rare: one or two chunks of a wavefront)
         const int c = -1 - l;
-        l = ((o.in_cut >> c) & 1ull) ? fs.cand[c / LC_SEL_CAND][c % LC_SEL_CAND].y : 0;
+        l = ((o.in_cut >> ((o.cut_first + c) << o.cut_shift)) & 1ull) ? fs.cand[threadIdx.x >> 6][c].y : 0;
     }
     *ln = l;
 }
@@ -129,7 +131,7 @@ __device__ __forceinline__ void lc_select_chunks(const LcDev& ix, int b, int bh,
     o.l_id = lds_dyn + 2 * (EC * NT + 64);
     o.seg = wave * (EC * 64);
     // meanwhile: empty histogram and list (their first use is behind the barrier of the key range)
-    for (int i = tid; i < BINS + 4; i += NT) fs.hw[i] = 0;
+    for (int i = tid; i < BINS; i += NT) fs.hw[i] = 0;
     o.M = min(M_all, EC * NT);
     o.tail_st = bnd[M_all];
     const int W = budget > 0 ? budget : 0;
@@ -142,6 +144,7 @@ __device__ __forceinline__ void lc_select_chunks(const LcDev& ix, int b, int bh,
         ck[e] = j0 + 64 * e < o.M ? k_e : 0u;
         kmin1 = min(kmin1, ck[e] - 1u);                         // key 0 wraps to the largest value: ignored
         kmax = max(kmax, ck[e]);
+        if (EC > 10 && (e & 3) == 3) __builtin_amdgcn_sched_barrier(0);       // (the conditions of sixteen at a time do not fit the scalar registers)
     }
     {
         const uint32_t wmin = lc_wave_min_uniform(kmin1), wmax = lc_wave_max_uniform(kmax);
@@ -153,42 +156,46 @@ __device__ __forceinline__ void lc_select_chunks(const LcDev& ix, int b, int bh,
 #pragma unroll
     for (int w = 1; w < NW; ++w) { kmin1 = min(kmin1, fs.kmin[w]); kmax = max(kmax, fs.kmax[w]); }
     const uint32_t kmin = kmin1 + 1u;
-    const uint32_t span = kmax - kmin;
-    const int bits = (kmax != 0u && span) ? 32 - __clz(span) : 0;
-    const int shift = bits > BITS ? bits - BITS : 0;            // (span >> shift) < BINS
-    // bin of every chunk: -1 = no candidate (those add their length to a slot nobody reads).  Even steps of the key, or of the score
+    // ---- Histogram of chunk lengths over the upper half of the scores' range (as lc_select_kernel has it, and by its rule): the budget nearly always
+    // ends there, and LDS atomics of all chunks, most of them in the same few bins, are most of the step's time otherwise.  Over all of the range if the
+    // upper half fits the budget whole, and at once if the budget is a third of the tokens or more.  Bins are even steps of the key, or of the score
     // where the keys' range is over 32 binary orders: keys of scores of both signs crowd around zero, with the chunks that
     // matter in two or three bins (unit-norm centers, 4 x 32K tokens in chunks of 16 to 128: 17.6 us a step, now 14.2; one sequence of 49K in
     // chunks of 8 to 16: 23.5 and 16.6).
-    int cbin[EC];
-    bool by_key = true;                                         // (uniform)
-    if (__builtin_expect(span > (32u << 23), 0)) {
-        const float s_lo = lc_key_score(kmin), s_all = lc_key_score(kmax) - s_lo;
-        by_key = !(kmax != 0u && s_all > 1e-30f && s_all < 1e30f);      // (no candidates, infinities)
-        if (!by_key) {
-            const float per_bin = (float)BINS * __builtin_amdgcn_rcpf(s_all);
+    constexpr int PER = BINS / 64;
+    int cbin[EC];                                               // -1: no candidate, or below the range
+    int fb = -1, remW = W;                                      // cutoff bin (-1: every candidate fits), budget left for it
+    const bool signs = kmax - kmin > (32u << 23);
+    for (bool half = W < o.T / 3;; half = false) {
+        uint32_t lo = half ? kmax - (kmax - kmin) / 2u : kmin;
+        bool by_key = true;                                     // (uniform)
+        if (__builtin_expect(signs, 0)) {
+            const float s_hi = lc_key_score(kmax), s_all = s_hi - lc_key_score(kmin);
+            by_key = !(s_all > 1e-30f && s_all < 1e30f);        // (infinities)
+            if (!by_key) {
+                const float s_lo = half ? s_hi - 0.5f * s_all : lc_key_score(kmin);
+                const float per_bin = (float)BINS * __builtin_amdgcn_rcpf(half ? 0.5f * s_all : s_all);
 #pragma unroll
-            for (int e = 0; e < EC; ++e) {
-                const int bin = min((int)((lc_key_score(ck[e]) - s_lo) * per_bin), BINS - 1);
-                cbin[e] = ck[e] != 0u ? bin : -1;
-                atomicAdd(&fs.hw[(int)min((uint32_t)cbin[e], (uint32_t)BINS)], ent[e].z);
+                for (int e = 0; e < EC; ++e) {
+                    const float s = lc_key_score(ck[e]) - s_lo;
+                    cbin[e] = ck[e] != 0u && s >= 0.f ? min((int)(s * per_bin), BINS - 1) : -1;
+                    atomicAdd(&fs.hw[cbin[e] >= 0 ? cbin[e] : BINS + lane], ent[e].z);
+                }
             }
         }
-    }
-    if (__builtin_expect(by_key, 1)) {
+        if (__builtin_expect(by_key, 1)) {
+            lo = max(lo, 1u);                                   // (key 0 is no candidate)
+            const uint32_t span = kmax - lo;
+            const int bits = (kmax != 0u && span) ? 32 - __clz(span) : 0;
+            const int shift = bits > BITS ? bits - BITS : 0;    // (span >> shift) < BINS
 #pragma unroll
-        for (int e = 0; e < EC; ++e) {
-            const int bin = (int)((ck[e] - kmin) >> shift);
-            cbin[e] = ck[e] != 0u ? bin : -1;
-            const int slot = (int)min((uint32_t)cbin[e], (uint32_t)BINS);
-            atomicAdd(&fs.hw[slot], ent[e].z);
+            for (int e = 0; e < EC; ++e) {
+                cbin[e] = ck[e] >= lo ? (int)((ck[e] - lo) >> shift) : -1;
+                atomicAdd(&fs.hw[ck[e] >= lo ? cbin[e] : BINS + lane], ent[e].z);
+            }
         }
-    }
-    lc_barrier_lds();
-    // ---- every wavefront scans all bins from the top: lane l holds bins BINS - 1 - PER l - i, i < PER
-    constexpr int PER = BINS / 64;
-    int fb = -1, remW = W;                                      // cutoff bin (-1: every candidate fits), budget left for it
-    {
+        lc_barrier_lds();
+        // every wavefront scans all bins from the top: lane l holds bins BINS - 1 - PER l - i, i < PER
         int pw[PER];                                            // inclusive prefix sums within the lane, bins descending
         const int4* hw4 = reinterpret_cast<const int4*>(fs.hw + BINS - PER * (lane + 1));
 #pragma unroll
@@ -212,7 +219,12 @@ __device__ __forceinline__ void lc_select_chunks(const LcDev& ix, int b, int bh,
             const int fl = __ffsll((long long)bal) - 1;         // lowest lane = highest bins
             fb = BINS - 1 - (PER * fl + lc_readlane(fit, fl));
             remW = W - (lc_readlane(cw, fl) + lc_readlane(fitw, fl));
+            break;
         }
+        if (!half) break;
+        lc_barrier_lds();                                       // the bins have been read
+        for (int i = tid; i < BINS; i += NT) fs.hw[i] = 0;
+        lc_barrier_lds();
     }
     // ---- chunks of that bin and above, and the pinned ones, to this wavefront's list; those in it to the short list
     if (sink > 0) {                                             // (pinned chunks: as if in a bin above all)
@@ -224,53 +236,81 @@ __device__ __forceinline__ void lc_select_chunks(const LcDev& ix, int b, int bh,
     int n_cut = 0;
     o.n_list = 0;
     unsigned long long mi[EC], mc[EC];
-    int first[EC];
     // (no branch: a lane without a chunk for the list writes to a slot of its own behind it)
 #pragma unroll
     for (int e = 0; e < EC; ++e) {
         mi[e] = __ballot(cbin[e] >= lowest);
         mc[e] = __ballot(cbin[e] == cutoff);
-        first[e] = o.seg + o.n_list;
-        const int at = first[e] + lc_mbcnt(mi[e]);
+        const int at = o.seg + o.n_list + lc_mbcnt(mi[e]);
         o.l_row[cbin[e] >= lowest ? at : EC * NT + lane] = make_int2(ent[e].y, ent[e].z);
         o.n_list += __popcll(mi[e]);
     }
     if (want_ids) {
+        int first = o.seg;
 #pragma unroll
-        for (int e = 0; e < EC; ++e)
-            if (cbin[e] >= lowest) o.l_id[first[e] + lc_mbcnt(mi[e])] = j0 + 64 * e;
+        for (int e = 0; e < EC; ++e) {
+            if (cbin[e] >= lowest) o.l_id[first + lc_mbcnt(mi[e])] = j0 + 64 * e;
+            first += __popcll(mi[e]);
+        }
     }
+    int first = o.seg;
 #pragma unroll
     for (int e = 0; e < EC; ++e) {
         if (mc[e] != 0ull) {                                    // (uniform; few of the rows)
             const int c = n_cut + lc_mbcnt(mc[e]);
             if (cbin[e] == cutoff) {
-                o.l_row[first[e] + lc_mbcnt(mi[e])].y = -1 - (wave * LC_SEL_CAND + c);
+                o.l_row[first + lc_mbcnt(mi[e])].y = -1 - c;
                 if (c < LC_SEL_CAND) fs.cand[wave][c] = make_int4((int)ck[e], ent[e].z, j0 + 64 * e, 0);
             }
             n_cut += __popcll(mc[e]);
         }
+        first += __popcll(mi[e]);
     }
     if (lane == 0) fs.n_cand[wave] = n_cut;
     lc_barrier_lds();
     bool crowded = false;
+    int nc = 0, after[NW];                                      // chunks of the short list: all, up to each wavefront's last
+    o.cut_first = 0;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) crowded = crowded || fs.n_cand[w] > LC_SEL_CAND;
+    for (int w = 0; w < NW; ++w) {
+        const int n = lc_readlane(fs.n_cand[w], 0);
+        crowded = crowded || n > LC_SEL_CAND;
+        if (w == wave) o.cut_first = nc;
+        nc += n;
+        after[w] = nc;
+    }
     o.in_cut = 0ull;
+    o.cut_shift = 0;
     if (!crowded) {
-        // ---- lane c ranks chunk c of the short list: length of the chunks before it
-        const int cw = lane / LC_SEL_CAND, ci = lane % LC_SEL_CAND;
-        static_assert(NW * LC_SEL_CAND == 64, "one lane per slot of the short list");
-        const int4 me = fs.cand[cw][ci];
-        const bool valid = ci < fs.n_cand[cw];
-        int wb = 0;
-        for (unsigned long long left = __ballot(valid); left != 0ull; left &= left - 1ull) {      // (uniform)
-            const int l = __ffsll((long long)left) - 1;
-            const uint32_t k = (uint32_t)lc_readlane(me.x, l);
-            const bool before = k > (uint32_t)me.x || (k == (uint32_t)me.x && lc_readlane(me.z, l) < me.z);
-            wb += before ? lc_readlane(me.y, l) : 0;
+        // ---- the short list ranked by (key descending, id ascending): a chunk is selected if it fits with those before it.
+        // A few, as nearly always, by a lane for each pair of them; more by a lane for each.  (One after the other through scalar registers, every
+        // chunk of the list cost 0.06 us: 0.6 us at the median, 1.1 in one step of twenty, now 0.25.)
+        auto listed = [&](int i) -> int4 {
+            int w = 0, c = i;
+#pragma unroll
+            for (int x = 0; x + 1 < NW; ++x)
+                if (i >= after[x]) { w = x + 1; c = i - after[x]; }
+            return fs.cand[w][min(c, LC_SEL_CAND - 1)];
+        };
+        auto precedes = [](const int4& x, const int4& y) { return (uint32_t)x.x > (uint32_t)y.x || (x.x == y.x && x.z < y.z); };
+        if (nc <= LC_SEL_FEW) {
+            const int i = lane / LC_SEL_FEW, j = lane % LC_SEL_FEW;
+            const int4 me = listed(i), other = listed(j);
+            int before = j < nc && precedes(other, me) ? other.y : 0;
+            before += __builtin_amdgcn_update_dpp(0, before, 0xB1, 0xF, 0xF, true);      // over eight lanes
+            before += __builtin_amdgcn_update_dpp(0, before, 0x4E, 0xF, 0xF, true);
+            before += __builtin_amdgcn_update_dpp(0, before, 0x141, 0xF, 0xF, true);
+            o.in_cut = __ballot(i < nc && before + me.y <= remW);
+            o.cut_shift = 3;
+        } else {
+            const int4 me = listed(lane);
+            int before = 0;
+            for (int c = 0; c < nc; ++c) {                      // (uniform)
+                const int4 other = make_int4(lc_readlane(me.x, c), lc_readlane(me.y, c), lc_readlane(me.z, c), 0);
+                before += precedes(other, me) ? other.y : 0;
+            }
+            o.in_cut = __ballot(lane < nc && before + me.y <= remW);
         }
-        o.in_cut = __ballot(valid && wb + me.y <= remW);
     } else {
         // ---- a crowded or tied cutoff bin: the general select routine on its chunks alone, then the lists anew
         uint32_t* skey = reinterpret_cast<uint32_t*>(lds_dyn);

@@ -1,0 +1,115 @@
+"""The decode step whose workgroups share the scoring, against the two separate calls: shares around the numbers of chunks that a pass
+takes, chunk counts around the kernel's instances and its largest, several steps in a row, a buffer that held another index, and
+chunks that nobody has posted."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+class _Index:
+    def __init__(self, chunks, H, G, centers, budget, sink=0, seed=0, spare=0):
+        import torch
+        from paper_2603_08453_amd import binding as lc
+        self.lc, self.torch, self.budget, self.H, self.G, self.B = lc, torch, budget, H, G, len(chunks)
+        r = np.random.default_rng(seed + sum(chunks))
+        self.bounds = [np.concatenate([[0], np.cumsum(r.integers(1, 6, size=m))]).astype(np.int32) for m in chunks]
+        self.lens = [int(b[-1]) for b in self.bounds]
+        self.gen = torch.Generator(device="cuda")
+        self.gen.manual_seed(seed)
+        rows, self.cap = max(self.lens) + spare, max(chunks) + spare
+        self.K, self.V = self.draw(self.B, H, rows, 128), self.draw(self.B, H, rows, 128)
+        self.cfg = lc.lc_config_default(levels=2, fanout=16, kmeans_iters=1, max_chunks=self.cap, max_tokens=rows, center_dtype=centers,
+                                        sink_tokens=sink)
+        self.ib = torch.full((lc.lc_index_bytes(self.cfg, self.B, H),), 0xA5, dtype=torch.uint8, device="cuda")
+        self.ws = torch.full((lc.lc_workspace_bytes(self.cfg, self.B, H * G, H),), 0xA5, dtype=torch.uint8, device="cuda")
+        self.build()
+
+    def draw(self, *shape):
+        return self.torch.randn(shape, generator=self.gen, device="cuda").to(self.torch.bfloat16)
+
+    def build(self):
+        self.idx = self.lc.lc_build_index(self.cfg, self.K, self.lens, self.bounds, self.ib, self.ws)
+
+    def query(self):
+        return self.draw(self.B, self.H * self.G, 128)
+
+    def step(self, q, out=None, lse=None):
+        out = self.torch.full((self.B, self.H * self.G, 128), float("nan"), device="cuda") if out is None else out
+        lse = self.torch.full((self.B, self.H * self.G), float("nan"), device="cuda") if lse is None else lse
+        ids = self.torch.full((self.B, self.H, self.cap), -7, dtype=self.torch.int32, device="cuda")
+        n = self.torch.full((self.B, self.H), -1, dtype=self.torch.int32, device="cuda")
+        self.lc.lc_decode_step(self.idx, q, self.K, self.V, self.budget, out, self.ws, lse=lse, chunk_ids=ids, counts=n)
+        return ids, n, out, lse
+
+    def check(self, q):
+        torch, lc = self.torch, self.lc
+        ids, n, out, lse = self.step(q)
+        want, m = torch.full_like(ids, -7), torch.full_like(n, -1)
+        ref, ref_lse = torch.full_like(out, float("nan")), torch.full_like(lse, float("nan"))
+        lc.lc_retrieve(self.idx, q, self.budget, want, m, self.ws)
+        lc.lc_sparse_decode(self.idx, q, self.K, self.V, want, m, ref, self.ws, lse=ref_lse)
+        assert torch.equal(n, m)
+        for b in range(self.B):
+            for h in range(self.H):
+                assert torch.equal(ids[b, h, : n[b, h]], want[b, h, : m[b, h]])
+        # (the same chunks; another number of splits adds up in another order)
+        assert torch.allclose(out, ref, rtol=1e-4, atol=2e-5) and torch.allclose(lse, ref_lse, rtol=1e-5, atol=1e-5)
+
+
+# one to 32 splits by the budget; 32 (sequence, head) pairs fill the device, two do not
+@pytest.mark.parametrize("G,centers", [(1, 0), (4, 0), (4, 1), (7, 0), (8, 1)])
+@pytest.mark.parametrize("chunks,H,budget", [([129], 2, 300), ([255, 1], 2, 512), ([257], 2, 512), ([511, 130], 2, 513), ([513], 1, 2048),
+                                             ([1024, 1025], 1, 2048), ([1535], 1, 4000), ([1536, 400], 2, 4000), ([1537], 2, 4000),
+                                             ([513, 7, 400, 512], 8, 512), ([577, 640, 641, 1], 8, 512), ([1023, 1024, 0, 65], 8, 512),
+                                             ([1025] * 4, 8, 512), ([2559], 8, 4096), ([2560, 2300], 8, 2048), ([2561], 8, 4096)])
+def test_shares(chunks, H, budget, G, centers):
+    x = _Index(chunks, H, G, centers, budget)
+    for _ in range(3):
+        x.check(x.query())
+
+
+def test_pinned_chunks_and_no_budget():
+    for sink, budget in ((40, 500), (9, 0), (0, 10 ** 6)):
+        x = _Index([600, 140], 2, 4, 0, budget, sink=sink)
+        x.check(x.query())
+
+
+def test_a_buffer_that_held_another_index():
+    """The keys that the steps on one index have posted are no keys of the index built in the same buffer later."""
+    x = _Index([700], 4, 4, 0, 512)
+    for _ in range(2):
+        for _ in range(3):
+            x.check(x.query())
+        x.K.copy_(x.draw(*x.K.shape))
+        x.build()
+    blob = x.lc.lc_index_export(x.idx)
+    x.idx = x.lc.lc_index_import(x.cfg, blob, x.ib)
+    x.check(x.query())
+
+
+def test_chunks_that_nobody_posted():
+    """A captured step on an index that has grown beyond what its workgroups share out: whoever waits for the other chunks' keys scores them."""
+    import torch
+    x = _Index([130], 2, 4, 0, 256, spare=64)
+    q, out, lse = x.query(), torch.empty((1, 8, 128), device="cuda"), torch.empty((1, 8), device="cuda")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        x.lc.lc_decode_step(x.idx, q, x.K, x.V, x.budget, out, x.ws, lse=lse)
+        side.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            x.lc.lc_decode_step(x.idx, q, x.K, x.V, x.budget, out, x.ws, lse=lse)
+    torch.cuda.current_stream().wait_stream(side)
+    for turn in range(3):
+        if turn:                                             # four splits of 36 chunks: 144 of them are shared out
+            for _ in range(32):
+                x.lc.lc_append(x.idx, x.K, x.V, x.draw(1, 2, 128), x.draw(1, 2, 128), [1], x.ws)
+        q.copy_(x.query())
+        out.fill_(float("nan"))
+        graph.replay()
+        got, got_lse = out.clone(), lse.clone()
+        _, _, ref, ref_lse = x.step(q)
+        assert torch.equal(got, ref) and torch.equal(got_lse, ref_lse)
+        x.check(q)
