@@ -380,8 +380,8 @@ lc_upper_kernel(const LcRetrieveArgs a) {
 // One compute unit works on a (sequence, head), one stage after the other: what bounds it is the chain of
 // memory round trips, and the unit's instruction rate -- an instruction that all sixteen wavefronts execute takes
 // 16 cycles.  So
-//   - everything whose address does not depend on a result is on its way before the first wait: the query,
-//     the top level's first rows, and the parent pointers of all levels straight into LDS (those that fit:
+//   - everything whose address does not depend on a result is on its way before the first wait, the query and
+//     the top level's first rows, and behind them the parent pointers of all levels straight into LDS (those that fit:
 //     the upper levels first);
 //   - a group of 16 lanes scores four nodes at a time (lc_score_packed), the best are found by one wavefront from a
 //     histogram of 64 bins (lc_wave_cut), a list is written from the lanes' marks by one scan and one
@@ -390,7 +390,9 @@ lc_upper_kernel(const LcRetrieveArgs a) {
 //   - the lists are in LDS, and code that reads them knows that they are (an address that may be either
 //     LDS or memory costs a wait for both); a list longer than `list_slots` goes to the workspace.
 // 10.9 K chunks under 5461 and 249 nodes, 43 and 8 of them kept, 8 heads: 34.7 us with a copy of the code per level,
-// every node scored by itself and ranks by counting, 25.2 us now; 2275 chunks under four levels: 26 and 24.4 us.
+// every node scored by itself and ranks by counting, 25.2 us now; 2275 chunks under four levels: 26 and 24.4 us.  A step over the first, with
+// three passes over LDS per cut (2.0 us of 183 candidates) and the parent pointers ahead of the rows 31.8 us, now 29.2 (a cut 1.3 us;
+// of 500 chunks by their lengths 3.1 and 1.7); with 512 threads 34.1, with 256 43.6.
 // A flat scan of up to this many chunks is the same with one level: one kernel (8 heads of 48 chunks: 7.6 us as scoring and
 // selection, 6.7 here; of 63 7.3 and 6.7); beyond, one compute unit's scoring and cut cost more (240: 6.7 and 10.1 us).
 #define LC_FLAT_MAX_CHUNKS 64
@@ -451,6 +453,96 @@ struct LcKeyBins {
         return k >= a && k <= b && k != 0u ? (by_score ? by_s : (int)((k - a) >> shift)) : -1;
     }
 };
+// The first round of lc_wave_cut where a lane holds all its R candidates (positions lane + 64 r, n <= 64 R) in registers: one pass over the LDS instead of
+// three, no loops.  False (and nothing changed) where bins over the score make no sense or the bin of the cut has more than 64
+// candidates.
+template <int R>
+__device__ __forceinline__ bool lc_wave_cut_held(int n, uint32_t* key, const int* wgt, bool weighted, int W, int C, int* hist, uint32_t* cut) {
+    const int lane = threadIdx.x & 63;
+    const bool counted = C < 0x7fffffff;
+    uint32_t k[R];
+    int w[R], bin[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int i = min(64 * r + lane, n - 1);
+        k[r] = key[i];
+        w[r] = wgt[i];
+    }
+    hist[lane] = 0;
+    hist[64 + lane] = 0;
+    uint32_t lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        k[r] = 64 * r + lane < n ? k[r] : 0u;
+        lo = min(lo, k[r] - 1u);                                    // (key 0 wraps to the largest value: ignored)
+        hi = max(hi, k[r]);
+    }
+    lo = lc_wave_min_uniform(lo) + 1u;
+    hi = lc_wave_max_uniform(hi);
+    const float s_lo = lc_key_score(lo), step = 64.0f * __builtin_amdgcn_rcpf(lc_key_score(hi) - s_lo);
+    if (!(hi != 0u && step > 0.f && step < 1e30f)) return false;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        // (no branch around the additions: what is no candidate adds to a slot that nobody reads)
+        const int slot = 63 - min((int)((lc_key_score(k[r]) - s_lo) * step), 63);
+        bin[r] = k[r] != 0u ? slot : -1;
+        if (weighted) atomicAdd(&hist[k[r] != 0u ? slot : 128 + lane], w[r]);
+        if (counted) atomicAdd(&hist[k[r] != 0u ? 64 + slot : 128 + lane], 1);
+    }
+    __builtin_amdgcn_wave_barrier();
+    const int hw = hist[lane], hc = hist[64 + lane];                // lane l: the l-th bin from the top
+    const int sw = weighted ? lc_wave_scan_incl(hw) : 0, sc = counted ? lc_wave_scan_incl(hc) : 0;
+    const unsigned long long over = __ballot(sw > W || sc > C);
+    if (over == 0ull) {
+        *cut = lo - 1u;                                             // everything fits
+        return true;
+    }
+    const int l = __ffsll((long long)over) - 1;                     // the prefix ends in this bin
+    W -= lc_readlane(sw - hw, l);
+    C -= counted ? lc_readlane(sc - hc, l) : 0;
+    int in = 0;
+    uint32_t top = 0u;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const unsigned long long m = __ballot(bin[r] == l);
+        if (m != 0ull) {                                            // (uniform)
+            const int at = in + lc_mbcnt(m);
+            if (bin[r] == l && at < 64) { hist[at] = 64 * r + lane; hist[64 + at] = (int)k[r]; hist[128 + at] = w[r]; }
+            top = max(top, bin[r] == l ? k[r] : 0u);
+            in += __popcll(m);
+        }
+    }
+    if (in > 64) return false;
+    __builtin_amdgcn_wave_barrier();
+    *cut = lc_wave_max_uniform(top);                                // (at least one of the bin is not kept)
+    // those of the bin ranked against each other: up to eight by a lane for each pair, more by a lane for each
+    const int i = in <= 8 ? lane >> 3 : lane, at = min(i, in - 1);
+    const int me = hist[at], mw = weighted ? hist[128 + at] : 0;
+    const uint32_t mk = (uint32_t)hist[64 + at];
+    int c_before = 0, w_before = 0;
+    if (in <= 8) {
+        const int o = min(lane & 7, in - 1);
+        const uint32_t ok = (uint32_t)hist[64 + o];
+        const bool before = (lane & 7) < in && (ok > mk || (ok == mk && o < at));
+        c_before = before ? 1 : 0;
+        w_before = before && weighted ? hist[128 + o] : 0;
+        c_before += __builtin_amdgcn_update_dpp(0, c_before, 0xB1, 0xF, 0xF, true);
+        w_before += __builtin_amdgcn_update_dpp(0, w_before, 0xB1, 0xF, 0xF, true);
+        c_before += __builtin_amdgcn_update_dpp(0, c_before, 0x4E, 0xF, 0xF, true);
+        w_before += __builtin_amdgcn_update_dpp(0, w_before, 0x4E, 0xF, 0xF, true);
+        c_before += __builtin_amdgcn_update_dpp(0, c_before, 0x141, 0xF, 0xF, true);
+        w_before += __builtin_amdgcn_update_dpp(0, w_before, 0x141, 0xF, 0xF, true);
+    } else {
+        for (int c = 0; c < in; ++c) {
+            const uint32_t ok = (uint32_t)lc_readlane((int)mk, c);
+            const bool before = ok > mk || (ok == mk && c < lane);
+            c_before += before ? 1 : 0;
+            w_before += before ? lc_readlane(mw, c) : 0;
+        }
+    }
+    if (i < in) key[me] = c_before < C && w_before + mw <= W ? 0xffffffffu : 0u;      // (of a pair's eight lanes all write the same)
+    return true;
+}
 // The longest prefix (key descending, position ascending) of at most C candidates, and if `weighted` of total weight
 // <= W, of a list in LDS: candidate i is in it iff key[i] > the returned value; keys at the cut have been replaced by
 // the highest value (in) or 0 (not).  64 bins over the range of the keys, a scan from the top for the bin in which
@@ -487,6 +579,9 @@ __device__ __forceinline__ uint32_t lc_wave_cut(int n, uint32_t* key, const int*
         rank(n, me, key[me]);
         return 0u;
     }
+    uint32_t cut;
+    if (n <= 256 ? lc_wave_cut_held<4>(n, key, wgt, weighted, W, C, hist, &cut)
+                 : n <= 512 && lc_wave_cut_held<8>(n, key, wgt, weighted, W, C, hist, &cut)) return cut;
     uint32_t lo = 0xffffffffu, hi = 0u;
     for (int i0 = 0; i0 < n; i0 += 256) {
         uint32_t k[4];
@@ -696,6 +791,7 @@ lc_beam_kernel(const LcBeamArgs a) {
     float R;
     int x0, x1, own;
     auto load = [&](const LcBeamLevel& v, bool chunks, int valid, const int (&id)[4]) LC_INLINE {
+        if (16 * wave >= valid) return;                  // (whole wavefronts: rows nobody needs would take the cache's time)
         const size_t at = (size_t)bh * v.cap;
         const bool half = chunks && c0b;
         const char* const base = reinterpret_cast<const char*>(v.center);
@@ -703,7 +799,6 @@ lc_beam_kernel(const LcBeamArgs a) {
         const __amdgpu_buffer_rsrc_t rad_r = lc_buffer(v.radius + at, v.cap * 4);
         const __amdgpu_buffer_rsrc_t end_r = chunks ? lc_buffer(bnd + 1, cap0 * 4) : lc_buffer(v.nchunk + at, v.cap * 4);
         const __amdgpu_buffer_rsrc_t beg_r = lc_buffer(bnd, chunks ? cap0 * 4 : 0);
-        if (16 * wave >= valid) return;                  // (whole wavefronts: rows nobody needs would take the cache's time)
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             if (half) {
@@ -729,18 +824,23 @@ lc_beam_kernel(const LcBeamArgs a) {
     auto parents_of = [&](const LcBeamLevel& v) LC_INLINE {
         return lc_buffer(v.parent ? v.parent + (size_t)bh * v.cap : nullptr, v.parent ? v.cap * 4 : 0);     // (none: reads return 0)
     };
-    int next_par = 0;                                    // LDS words taken
-    for (int v = 1; v < L; ++v) {
-        const int words = a.lev[v].par_words;
-        if (next_par + words <= a.par_slots) {
-            const __amdgpu_buffer_rsrc_t r = parents_of(a.lev[v]);
-            for (int w = 64 * wave; w < words; w += LC_BM_THREADS)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(l_par + next_par + w), 4,
-                                                         4 * lane, 4 * w, 0, 0);
-            next_par += words;
+    // (They go out behind the top level's rows have come, in wavefronts that do not cut: together with the rows, on one compute unit's way to
+    // memory, they kept the last wavefront's rows waiting 1.2 us.)
+    auto fetch_parents = [&]() LC_INLINE {
+        constexpr int FIRST = LC_BM_WAVES / 4;
+        if (wave < FIRST) return;
+        int at = 0;                                      // LDS words taken
+        for (int v = 1; v < L; ++v) {
+            const int words = a.lev[v].par_words;
+            if (at + words <= a.par_slots) {
+                const __amdgpu_buffer_rsrc_t r = parents_of(a.lev[v]);
+                for (int w = 256 * (wave - FIRST); w < words; w += 256 * (LC_BM_WAVES - FIRST))
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(l_par + at + w), 16, 16 * lane, 4 * w, 0, 0);
+                at += words;
+            }
         }
-    }
-    next_par = 0;
+    };
+    int next_par = 0;                                    // LDS words of the levels before
     // (scalar reads that would otherwise wait for their own round trip further down)
     const int M = min(a.state[bh * 4 + 1], cap0);
     int n_c = L > 1 ? n_lev[0] : (W > 0 ? M : 0), n_dn = L > 1 ? n_lev[-1] : 0;
@@ -844,6 +944,7 @@ lc_beam_kernel(const LcBeamArgs a) {
                 if (last && scores && key != 0u) scores[own] = sc;
             }
         }
+        if (v == 0 && base == 0) fetch_parents();
         base += STEP;
         if (base >= n_c) {
             // ---- the level is scored: keep the beam's best (at the chunks: what the budget holds as well)
@@ -894,6 +995,7 @@ lc_beam_kernel(const LcBeamArgs a) {
                 }
             }
             if (last) break;
+            if (v == 0) __builtin_amdgcn_s_waitcnt(0);              // (this wavefront's share of the parent pointers)
             lc_barrier_lds();
             // ---- the kept nodes' children are the next level's candidates: a list in LDS as far as it fits, in
             // the workspace too if there may be more of them

@@ -84,3 +84,13 @@ def test_group_sizes(G):
 def test_equal_scores_at_the_cut(chunks, same, limit, budget):
     check(1, [chunks], 2, 8, [limit, 0], budget, same=same)
     check(1, [chunks], 3, 3, [limit, 25, 20], budget, same=same)
+
+
+# Lists that the cutting wavefront holds in registers (25 to 256 and to 512 candidates), cut by the budget, by number and by both, with as
+# many equal scores as its pairs take, more, and more than its bin takes.
+@pytest.mark.parametrize("n", [24, 25, 64, 65, 255, 256, 257, 511, 512, 513])
+@pytest.mark.parametrize("same", [0, 8, 9, 70])
+def test_candidates_held_by_one_wavefront(n, same):
+    for limit, budget in ((0, n // 2), (n // 3 + 1, 10 ** 9), (n // 4 + 1, n), (0, 0)):
+        check(1, [n], 1, 2, [limit, 0], budget, same=same, seed=n)
+    check(1, [2 * n], 2, 2, [0, n // 5 + 1], 60, same=2 * same, seed=n)
