@@ -298,35 +298,48 @@ __device__ __forceinline__ float lc_score_packed(const LcNodeFrag (&f)[4], float
 }
 // The query group of KV head h as packed words (lane `sub` of a 16-lane group: the fragments above) and the norms.  All groups of a wavefront
 // hold the same words, so each works out the norm of another head: a chain of sixteen products and sums and a square
-// root per four heads instead of one per head, in the same order.
-template <int G>
+// root per four heads instead of one per head, in the same order.  `loads` is called between the words' loads and their first use: loads come
+// back in order, so the norms are worked out while those of `loads` are on their way.  (The words are local until the end: a choice between
+// elements of a caller's array is one between addresses to the compiler, which then keeps the array in memory.)
+template <int G, typename Loads>
 __device__ __forceinline__ void lc_load_query_packed(const uint16_t* __restrict__ q, int h, int sub,
-                                                     uint32_t (&qp)[G][4], float (&qn)[G]) {
+                                                     uint32_t (&qp)[G][4], float (&qn)[G], Loads loads) {
+    uint32_t w[G][4];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
         const uint16_t* row = q + (size_t)(h * G + g) * LC_D;
         const uint2 a = *reinterpret_cast<const uint2*>(row + 4 * sub);
         const uint2 b = *reinterpret_cast<const uint2*>(row + 64 + 4 * sub);
-        qp[g][0] = a.x; qp[g][1] = a.y; qp[g][2] = b.x; qp[g][3] = b.y;
+        w[g][0] = a.x; w[g][1] = a.y; w[g][2] = b.x; w[g][3] = b.y;
     }
+    loads();
     const int group = (threadIdx.x >> 4) & 3;
 #pragma unroll
     for (int g0 = 0; g0 < G; g0 += 4) {
         float s = 0.f;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            uint32_t w = qp[g0][i];
+            uint32_t x = w[g0][i];
 #pragma unroll
             for (int g = 1; g < 4; ++g)
-                if (g0 + g < G) w = group == g ? qp[g0 + g < G ? g0 + g : g0][i] : w;
-            s = fmaf(lc_bf16_lo(w), lc_bf16_lo(w), s);
-            s = fmaf(lc_bf16_hi(w), lc_bf16_hi(w), s);
+                if (g0 + g < G) x = group == g ? w[g0 + g < G ? g0 + g : g0][i] : x;
+            s = fmaf(lc_bf16_lo(x), lc_bf16_lo(x), s);
+            s = fmaf(lc_bf16_hi(x), lc_bf16_hi(x), s);
         }
         const float norm = sqrtf(lc_sum16(s));
 #pragma unroll
         for (int g = 0; g < 4; ++g)
             if (g0 + g < G) qn[g0 + g < G ? g0 + g : g0] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(norm), 16 * g));
     }
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) qp[g][i] = w[g][i];
+}
+template <int G>
+__device__ __forceinline__ void lc_load_query_packed(const uint16_t* __restrict__ q, int h, int sub,
+                                                     uint32_t (&qp)[G][4], float (&qn)[G]) {
+    lc_load_query_packed<G>(q, h, sub, qp, qn, []() {});
 }
 
 // Load the query group of KV head h into registers (fragments as above) and

@@ -1296,20 +1296,26 @@ lc_leaf_kernel(const LcRetrieveArgs a) {
 // less per SIMD (lc_retrieve on 8 heads of 10.9 K chunks at 2731 workgroups 17.1 us, at 1366 18.3; on 64 pairs of 910 at 1856 workgroups
 // 14.4 and 14.9, with bfloat16 centers 13.9 and 13.1; of 3276 at 6592 34.5 and 32.8).
 #define LC_SCORE_MAX_WGS_F32 4096
+// A group's R chunks are scored together, each head's query words widened once for them and the sums over lanes shared (lc_score_packed); they were
+// scored one after the other, with the query's norms worked out by every group when the centers had come.  What bounds it is the centers' way from
+// memory where they are float32, and arithmetic at group size 7.  us of lc_retrieve and lc_sparse_decode, before and now: 8 heads of 1820 chunks at group
+// size 4 17.0 and 16.7, 16 pairs of 1820 at size 1 and of 7 queries 19.4 and 19.1, 22.5 and 21.8, 8 heads of 10.9 K float32 25.4 and 25.4, bfloat16 25.3 and 24.9;
+// a step over 2 x 4 x 4.2 K at group size 7 21.3 and 20.8.  With the query's loads behind the centers' it was slower than before (25.8 for 25.5).
 // BF16: how the chunk-level centers are stored (a compile-time copy of the index's flag).
 template <int G, int R, bool BF16>
 __global__ void __launch_bounds__(LC_SC_THREADS)
 lc_score_kernel(const LcRetrieveArgs a) {
     lc_fetch_args<sizeof(LcRetrieveArgs)>();
-    constexpr int GROUPS = LC_SC_THREADS / 16;
+    constexpr int PER = R * (LC_SC_THREADS / 16);
+    constexpr int ROW = BF16 ? LC_D * 2 : LC_D * 4;
     const LcDev& ix = a.ix;
     const int h = blockIdx.y, b = blockIdx.z;
     const int bh = b * ix.H + h;
     const int tid = threadIdx.x;
     const int sub = tid & 15, grp = tid >> 4;
     const size_t cb = (size_t)bh * ix.cap[0];
-    constexpr bool c0b = BF16;
     const int cap0 = ix.cap[0];
+    const int j_lo = blockIdx.x * PER;
     // the per-chunk arrays through range-checked buffer resources (an index derived from stored
     // values -- a parent pointer -- cannot reach memory outside its array)
     const __amdgpu_buffer_rsrc_t bnd_r = lc_buffer(ix.bounds + (size_t)b * (cap0 + 1), (cap0 + 1) * 4);
@@ -1317,46 +1323,58 @@ lc_score_kernel(const LcRetrieveArgs a) {
     const __amdgpu_buffer_rsrc_t want_r = lc_buffer(a.want + cb, cap0);
     const __amdgpu_buffer_rsrc_t par_r = lc_buffer(ix.parent[0] + cb, cap0 * 4);
     const __amdgpu_buffer_rsrc_t rad_r = lc_buffer(ix.radius[0] + cb, cap0 * 4);
+    const int rows = max(0, min(cap0 - j_lo, PER));                 // (of this workgroup)
+    const __amdgpu_buffer_rsrc_t cen_r = lc_buffer(reinterpret_cast<const char*>(ix.center[0]) + (cb + min(j_lo, cap0)) * ROW, rows * ROW);
     const bool have_want = a.walk != 0;
-    const int j_lo = blockIdx.x * (R * GROUPS);
-    int jj[R], wv[R], st[R], en[R];
-    float rv[R];
+    // group `grp` has chunks j_lo + R grp + (0 .. R - 1), lane `sub` of it boundaries and radius of number sub mod R
+    // (rows past the chunk count hold whatever the buffer held, past the array's end zero: the result is unused)
+    const int own = j_lo + R * grp + (sub & (R - 1));
+    int st = 0, en = 0;
+    float rv = 0.f;
+    unsigned wanted = (1u << R) - 1u;
+    LcNodeFrag f[4];
+    uint32_t qp[G][4];
+    float qn[G];
+    lc_load_query_packed<G>(a.q + (size_t)b * ix.H * G * LC_D, h, sub, qp, qn, [&]() LC_INLINE {
+        __builtin_amdgcn_sched_barrier(0);
+        st = lc_buf_load_i32(bnd_r, own);
+        en = lc_buf_load_i32(bnd_r, own + 1);
+        rv = lc_buf_load_f32(rad_r, own);
+        if (have_want) {
+            const bool w = lc_buf_load_u8(want_r, lc_buf_load_i32(par_r, own)) != 0;
+            wanted = (unsigned)(__ballot(w) >> (tid & 48)) & 0xffffu;
+        }
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int j = min(j_lo + r * GROUPS + grp, cap0 - 1);
-        jj[r] = j;
-        // (rows past the chunk count hold whatever the buffer held: the result is unused)
-        st[r] = lc_buf_load_i32(bnd_r, j);
-        en[r] = lc_buf_load_i32(bnd_r, j + 1);
-        wv[r] = (st[r] >= a.sink ? 1 : 0) & (have_want ? lc_buf_load_u8(want_r, lc_buf_load_i32(par_r, j)) : 1);
-        rv[r] = lc_buf_load_f32(rad_r, j);
-    }
-    LcNodeFrag pre[R];
-    if (!have_want) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) pre[r] = lc_load_chunk_node(ix.center[0], c0b, cb + jj[r], sub);
-    }
-    float qf[G][8], qn[G];
-    lc_load_query_frags<G>(a.q + (size_t)b * ix.H * G * LC_D, h, sub, qf, qn);
+        for (int k = 0; k < R; ++k) {
+            const int at = ((wanted >> k) & 1u) ? R * grp + k : rows;   // (nothing is fetched from `rows` on)
+            if (BF16) {
+                const lc_v2i x = __builtin_amdgcn_raw_buffer_load_b64(cen_r, at * ROW + 8 * sub, 0, 0);
+                const lc_v2i y = __builtin_amdgcn_raw_buffer_load_b64(cen_r, at * ROW + 8 * sub + 128, 0, 0);
+                f[k].a = make_float4(__int_as_float(x.x), __int_as_float(x.y), 0.f, 0.f);
+                f[k].b = make_float4(__int_as_float(y.x), __int_as_float(y.y), 0.f, 0.f);
+            } else {
+                f[k].a = lc_buf_load_f32x4(cen_r, at * ROW + 16 * sub);
+                f[k].b = lc_buf_load_f32x4(cen_r, at * ROW + 16 * sub + 256);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    });
     const int M = ix.state[bh * 4 + 1];
     if (j_lo >= M) return;
+    if (BF16) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int j = j_lo + r * GROUPS + grp;
-        float sv = LC_NEG_INF;
-        if (a.budget > 0 && j < M && wv[r]) {
-            if (!have_want) sv = lc_score_chunk_frag<G>(pre[r], c0b, rv[r], qf, qn);
-            else sv = lc_score_chunk_frag<G>(lc_load_chunk_node(ix.center[0], c0b, cb + jj[r], sub), c0b, rv[r], qf, qn);
-        }
-        if (j < M && sub == 0) {                                // one 16-byte entry per chunk (LcChunkEntry)
-            if (a.scores) a.scores[cb + j] = sv;
-            lc_v4i w;
-            w.x = (int)lc_score_key(sv);
-            w.y = st[r];
-            w.z = max(0, en[r] - st[r]);
-            w.w = 0;
-            __builtin_amdgcn_raw_buffer_store_b128(w, ent_r, j * 16, 0, 0);
-        }
+        for (int k = 0; k < R; ++k) f[k] = lc_widen_chunk_frag(f[k]);
+    }
+    const float sc = lc_score_packed<G, R>(f, rv, sub, qp, qn);
+    if ((sub >> 2) == 1 && (sub & 3) < R && own < M) {              // one 16-byte entry per chunk (LcChunkEntry)
+        const float sv = a.budget > 0 && st >= a.sink && ((wanted >> (sub & 3)) & 1u) ? sc : LC_NEG_INF;
+        if (a.scores) a.scores[cb + own] = sv;
+        lc_v4i w;
+        w.x = (int)lc_score_key(sv);
+        w.y = st;
+        w.z = max(0, en - st);
+        w.w = 0;
+        __builtin_amdgcn_raw_buffer_store_b128(w, ent_r, own * 16, 0, 0);
     }
 }
 
@@ -1665,6 +1683,8 @@ static int launch_retrieve_g(LcRetrieveArgs& a, int max_M, hipStream_t stream) {
     // group size 7, a quarter of the tokens: 256 (sequence, head) pairs of 250 chunks 15.2 and 14.0, of 300 14.4 and 15.8, of 450 17.6 and 19.7; 208 of 440
     // 16.5 and 17.0; 192 of 450 16.4 and 16.9, of 510 17.1 and 17.5; 176 of 510 17.1 and 16.8; 128 of 850 18.9 and 19.0, of 900 19.1 and 19.7, of 1020 20.2 and
     // 20.8; 64 of 1500 18.8 and 17.5, of 1750 19.3 and 19.5, of 1850 19.8 and 20.2, of 2400 (in turns) 30.4 and 24.1.  bfloat16 centers: 2 to 30 % slower as one.
+    // (The scoring kernel has become 0.3 to 0.7 us faster there since: 256 pairs of 300 and 450 chunks still 1.8 us slower as two, 208 of 440 0.5, fewer pairs
+    // between 0.4 us slower and 0.7 faster, either way within 1 % of a retrieval with its attention.)
     const int pairs = ix.H * ix.B;
     const bool full = pairs >= 64 && (long long)((max_M + 511) / 512) * pairs <= LC_COMPUTE_UNITS &&
                       ((long long)pairs * max_M >= 116000 || (pairs >= 200 && max_M > 256));

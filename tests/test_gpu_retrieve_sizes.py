@@ -154,3 +154,53 @@ def test_many_pairs_at_the_largest_group_sizes(B, chunks, G):
             for h in range(H):
                 want = by_the_rule(scores[b, h, : counts[b]], np.diff(bounds[b]), bounds[b][:-1], budget, 0)
                 assert n[b, h] == len(want) and np.array_equal(ids[b, h, : len(want)], want), (budget, b, h)
+
+
+@pytest.mark.parametrize("center_dtype", [0, 1])
+@pytest.mark.parametrize("G", [1, 3, 7])
+@pytest.mark.parametrize("B,H,chunks", [(1, 2, 65), (1, 2, 127), (8, 8, 300), (8, 8, 321), (16, 8, 1030)])
+def test_scores_of_one_two_and_four_chunks_at_a_time(B, H, chunks, G, center_dtype):
+    """The scoring kernel takes more chunks at a time the more there are in all: scores against 64 bits, and the level walk's (only
+    some chunks wanted) the same bits where it scores at all, with the same chunks selected."""
+    import torch
+    from paper_2603_08453_amd import binding as lc
+    r = np.random.default_rng(chunks + G)
+    counts = [chunks if b % 3 != 1 else chunks // 2 + 1 for b in range(B)]
+    bounds = [np.concatenate([[0], np.cumsum(r.integers(1, 4, size=m))]).astype(np.int32) for m in counts]
+    lens = [int(b[-1]) + 1 for b in bounds]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(chunks)
+    K = torch.randn((B, H, max(lens), 128), generator=gen, device="cuda").to(torch.bfloat16)
+    q = torch.randn((B, H * G, 128), generator=gen, device="cuda").to(torch.bfloat16)
+    budget, got = chunks // 4, {}
+    for prune in (lc.LC_PRUNE_NEVER, lc.LC_PRUNE_ALWAYS):
+        cfg = lc.lc_config_default(levels=2, fanout=32, kmeans_iters=1, max_chunks=chunks, max_tokens=max(lens), prune=prune,
+                                   center_dtype=center_dtype, sink_tokens=5)
+        ib = torch.zeros(lc.lc_index_bytes(cfg, B, H), dtype=torch.uint8, device="cuda")
+        ws = torch.zeros(lc.lc_workspace_bytes(cfg, B, H * G, H), dtype=torch.uint8, device="cuda")
+        idx = lc.lc_build_index(cfg, K, lens, bounds, ib, ws)
+        ids = torch.full((B, H, chunks), -7, dtype=torch.int32, device="cuda")
+        n = torch.full((B, H), -1, dtype=torch.int32, device="cuda")
+        scores = torch.full((B, H, chunks), float("nan"), device="cuda")
+        lc.lc_retrieve(idx, q, budget, ids, n, ws, scores=scores)
+        got[prune] = scores.cpu().numpy(), ids.cpu().numpy(), n.cpu().numpy()
+        if prune == lc.LC_PRUNE_NEVER:
+            blob = lc.unpack_blob(lc.lc_index_export(idx))
+    flat, walk = got[lc.LC_PRUNE_NEVER], got[lc.LC_PRUNE_ALWAYS]
+    qd = q.double().cpu().numpy().reshape(B, H, G, 128)
+    for b in range(B):
+        m, pinned = counts[b], bounds[b][:-1] < 5
+        for h in range(H):
+            s = flat[0][b, h, :m]
+            assert np.all(np.isneginf(s[pinned]))
+            level = blob["seqs"][b]["heads"][h][0]
+            mu, rad = level["center"].astype(np.float64), level["radius"].astype(np.float64)
+            norm = np.linalg.norm(qd[b, h], axis=1)
+            want = ((mu @ qd[b, h].T + rad[:, None] * norm) / np.sqrt(128)).max(axis=1)
+            # 128 products and as many roundings of sums that are at most |q| (|mu| + r)
+            bound = 132 * 2.0 ** -24 * norm.max() * (np.linalg.norm(mu, axis=1) + rad) / np.sqrt(128)
+            assert np.all(np.abs(s - want)[~pinned] <= bound[~pinned]), (b, h)
+            w = walk[0][b, h, :m]
+            assert np.array_equal(w[~np.isneginf(w)], s[~np.isneginf(w)]), (b, h)
+            k = flat[2][b, h]
+            assert k == walk[2][b, h] and np.array_equal(flat[1][b, h, :k], walk[1][b, h, :k]), (b, h)
