@@ -605,7 +605,7 @@ def main():
                 dom_name = cells[1]
                 break
     if not dom_name.endswith(">"):
-        dom_name += ", 1, false>" if (args.separate or not fused_step) else ", ...>"
+        dom_name += ", 1, 0>" if (args.separate or not fused_step) else ", ...>"
     res = {
         "metric": "us per decode step per layer (retrieve+attend), 128K ctx" if w.name.startswith("C3") else
                   "us per decode step per layer (retrieve+attend)",
