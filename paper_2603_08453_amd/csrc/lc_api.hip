@@ -84,7 +84,7 @@ size_t lc_layout_index(const lc_config* cfg, int B, int H, int d, void* base, Lc
         D->nchunk[l] = c.take<int>(n);
         D->rbuild[l] = l >= 1 ? c.take<float>(n) : nullptr;
     }
-    D->posted = c.take<unsigned long long>(BH * D->cap[0]);
+    D->posted = c.take<unsigned long long>(BH * lc_posted_slots(D->cap[0]));
     return align_up(c.off);
 }
 

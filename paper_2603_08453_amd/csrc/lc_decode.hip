@@ -238,7 +238,7 @@ lc_decode_kernel(const LcDecodeArgs a) {
     // nothing is fetched (the offsets are past the arrays' ends).
     auto load = [&](auto count, Pass& w, int j, int end) LC_INLINE {
         constexpr int N = decltype(count)::value;
-        const int rows = min(ix.cap[0], LC_STEP_SHARE_MAX_CHUNKS);
+        const int rows = lc_posted_slots(ix.cap[0]);
         j = j < end ? j : rows;
         const size_t cb = (size_t)bh * ix.cap[0];
         const bool c0b = ix.c0_bf16 != 0;
@@ -301,9 +301,9 @@ lc_decode_kernel(const LcDecodeArgs a) {
     };
     // LC_SCORED_SHARED: this workgroup's share of the chunks is scored and posted, then this lane's chunks j0 + 64 e are read
     auto share_scores = [&](int j0, uint32_t (&key)[EC], int (&begin)[EC], int (&end)[EC]) LC_INLINE {
-        const int rows = min(ix.cap[0], LC_STEP_SHARE_MAX_CHUNKS);
+        const int rows = lc_posted_slots(ix.cap[0]);
         const __amdgpu_buffer_rsrc_t bnd_r = lc_buffer(bnd, (rows + 1) * 4);
-        const __amdgpu_buffer_rsrc_t posted_r = lc_buffer(ix.posted + (size_t)bh * ix.cap[0], rows * 8);
+        const __amdgpu_buffer_rsrc_t posted_r = lc_buffer(ix.posted + (size_t)bh * rows, rows * 8);
         const int lo = s * a.share, hi = min(lo + a.share, rows);
         const int M = ix.state[bh * 4 + 1], number = ix.sync[bh * 4 + 3];
         __builtin_amdgcn_sched_barrier(0);                          // (on their way before the first wait)

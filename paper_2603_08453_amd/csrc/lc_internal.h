@@ -10,6 +10,10 @@
 
 #include "lychee.h"
 
+// Most chunks per (sequence, head) that the workgroups of a decode step share out, and with that the keys they post.
+#define LC_STEP_SHARE_MAX_CHUNKS 2560
+constexpr int lc_posted_slots(int cap0) { return cap0 < LC_STEP_SHARE_MAX_CHUNKS ? cap0 : LC_STEP_SHARE_MAX_CHUNKS; }
+
 // Device-side view of an index, passed to kernels by value.
 // Per-level arrays are indexed [(b * H + h) * cap[l] + n]; centers carry d floats per node, except that
 // center[0] points at rows of d bfloat16 values when c0_bf16 is set (read it through lc_c0_*).
@@ -22,7 +26,7 @@ struct LcDev {
     int* bounds;     // [B][cap[0] + 1]: chunk boundaries (shared by the heads of a sequence)
     int* sync;       // [B][H][4]: arrival counters of the fused kernels (0, 1), zero between calls; 3: number of the next decode step whose
                      // workgroups share the scoring (never 0)
-    unsigned long long* posted;   // [B][H][cap[0]]: score keys that those workgroups post for each other: key, number of the step << 32
+    unsigned long long* posted;   // [B][H][lc_posted_slots(cap[0])]: score keys that those workgroups post for each other: key, number of the step << 32
     float* center[LC_MAX_LEVELS];
     float* radius[LC_MAX_LEVELS];
     int* parent[LC_MAX_LEVELS];
@@ -131,7 +135,6 @@ int lc_launch_decode(const lc_index* idx, const LcWs& ws, const void* q, const v
 // LC_STEP_SHARE_MAX_CHUNKS in all).
 enum { LC_SCORED_BEFORE = 0, LC_SCORED_HERE = 1, LC_SCORED_SHARED = 2 };
 #define LC_STEP_SHARE_CHUNKS 128
-#define LC_STEP_SHARE_MAX_CHUNKS 2560
 // One kernel or two (without a level walk): every workgroup scoring all chunks costs 0.5 us per 64 chunks at group
 // size 4, twice that at 7 or 8, times the workgroups that share a compute unit; the scoring kernel costs about 2 us.
 // Measured from 16 to 256 chunks, 8 to 128 (sequence, head) pairs and group sizes 1, 4 and 7: up to 64 chunks

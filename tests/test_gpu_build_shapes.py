@@ -186,3 +186,31 @@ def test_chunk_lengths_around_a_pooling_batch(centers):
             assert np.abs(center[j] - mean).max() < (4e-3 * max(1.0, np.abs(mean).max()) if centers else 2e-6)
             reach = np.linalg.norm(keys[lo:hi] - center[j], axis=1).max()
             assert reach * (1 - 1e-6) - 1e-6 <= radius[j] <= reach * (1 + 3e-5) + 1e-5
+
+
+def test_capacity_that_is_not_in_use_costs_a_build_nothing():
+    """100 chunks in an index for 100 and in one for 131072: what a build clears does not grow with the capacity (as it did, three times the
+    build's time)."""
+    import torch
+    from paper_2603_08453_amd import binding as lc
+    H, chunks = 8, 100
+    bounds = [np.arange(chunks + 1, dtype=np.int32) * 12]
+    us = {}
+    for most in (chunks, 131072):
+        cfg = lc.lc_config_default(levels=2, fanout=16, kmeans_iters=1, max_chunks=most, max_tokens=max(most, 1200))
+        K = torch.zeros((1, H, cfg.max_tokens, 128), dtype=torch.bfloat16, device="cuda")
+        K[:, :, :1200] = torch.randn((1, H, 1200, 128), device="cuda").to(torch.bfloat16)
+        ib = torch.zeros(lc.lc_index_bytes(cfg, 1, H), dtype=torch.uint8, device="cuda")
+        ws = torch.zeros(lc.lc_workspace_bytes(cfg, 1, H, H), dtype=torch.uint8, device="cuda")
+        took = []
+        for _ in range(20):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda.synchronize()
+            a.record()
+            for _ in range(5):
+                lc.lc_build_index(cfg, K, [1200], bounds, ib, ws)
+            b.record()
+            torch.cuda.synchronize()
+            took.append(a.elapsed_time(b) * 200)
+        us[most] = min(took)
+    assert us[131072] < 1.6 * us[chunks], us

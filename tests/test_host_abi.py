@@ -68,6 +68,16 @@ def test_size_queries(L):
     assert lc.lc_index_bytes(lc.lc_config_default(levels=7, max_chunks=10, max_tokens=10), 1, 1) == 0
 
 
+@pytest.mark.parametrize("center_dtype,row", [(lc.LC_CENTER_F32, 512), (lc.LC_CENTER_BF16, 256)])
+def test_spare_capacity_holds_no_score_keys(L, center_dtype, row):
+    """A decode step posts the keys of at most 2560 chunks per head: capacity beyond that is the chunk's center, radius, parent and two
+    counts per head and its boundary, nothing else."""
+    B, H = 2, 8
+    size = lambda n: lc.lc_index_bytes(lc.lc_config_default(levels=1, max_chunks=n, max_tokens=1 << 17, center_dtype=center_dtype), B, H)
+    assert size(131072) - size(65536) == 65536 * B * (H * (row + 16) + 4)
+    assert size(2048) - size(1024) == 1024 * B * (H * (row + 16 + 8) + 4)
+
+
 def test_strerror(L):
     for code in (0, -1, -2, -3, -4, -5, -6):
         assert lc.lc_strerror(code) not in ("", "unknown error")
