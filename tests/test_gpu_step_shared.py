@@ -113,3 +113,52 @@ def test_chunks_that_nobody_posted():
         _, _, ref, ref_lse = x.step(q)
         assert torch.equal(got, ref) and torch.equal(got_lse, ref_lse)
         x.check(q)
+
+
+def test_an_index_that_has_grown_takes_a_captured_step_no_longer():
+    """The chunks behind all shares are scored before anyone looks for them: a replay on a grown index gives what a step launched anew gives, in
+    about its time (left to those that look for them in vain it took three to four times as long)."""
+    import torch
+    x = _Index([130], 2, 4, 0, 256, spare=320)
+
+    def capture():
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            x.lc.lc_decode_step(x.idx, q, x.K, x.V, x.budget, out, x.ws, lse=lse)
+            side.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=side):
+                for _ in range(10):
+                    x.lc.lc_decode_step(x.idx, q, x.K, x.V, x.budget, out, x.ws, lse=lse)
+        torch.cuda.current_stream().wait_stream(side)
+        return graph
+
+    def us(graph):
+        took = []
+        for _ in range(10):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda.synchronize()
+            a.record()
+            graph.replay()
+            b.record()
+            torch.cuda.synchronize()
+            took.append(a.elapsed_time(b) * 100)
+        return min(took)
+
+    q, out, lse = x.query(), torch.empty((1, 8, 128), device="cuda"), torch.empty((1, 8), device="cuda")
+    assert x.lc.lc_bench_step_is_one_kernel(x.idx, 8, x.budget)
+    graph, grown = capture(), 0
+    # four splits of 36 chunks, an instance that holds 512: one chunk behind them, a workgroup's 64, all of them and more than all of them
+    for more in (15, 64 + 14, 256 + 14, 300):
+        while grown < more:
+            x.lc.lc_append(x.idx, x.K, x.V, x.draw(1, 2, 128), x.draw(1, 2, 128), [1], x.ws)
+            grown += 1
+        q.copy_(x.query())
+        out.fill_(float("nan"))
+        old = us(graph)
+        got, got_lse = out.clone(), lse.clone()
+        _, _, ref, ref_lse = x.step(q)
+        assert torch.equal(got, ref) and torch.equal(got_lse, ref_lse)
+        x.check(q)
+        assert old < 1.8 * us(capture()) + 2, more
