@@ -612,7 +612,11 @@ int useful_splits(const lc_index* idx, int G, int max_M, int budget, int splits)
 // Time of a step shared over that of two kernels, 2 to 128 pairs, group sizes 1 to 7, both kinds of centers: 0.87 to 0.98 at up to 64 chunks a
 // workgroup (1.00 to 1.02 at 1820 chunks with 64 workgroups); at 72 to 120 with the device full 0.88 to 0.95 (16 ragged sequences, group size 7: 27.6 and
 // 23.9 us) up to 1000 chunks, 0.99 at 2275 and 0.98 to 1.04 at 3640, with the device not full 1.01 to 1.10.
+// Of more workgroups than run at the same time (two per compute unit; only where the caller's decode_splits asks for them) those with a place wait for
+// keys of those without one: 0.98 to 1.56 over 70 shapes, 1.1 at the median (32 pairs of 256 chunks in 64 splits: 42.1 us as two kernels, 56.7 shared).  With one
+// split per (sequence, head) there is nobody to wait for.
 bool step_shares_scoring(int max_M, int splits, long long workgroups) {
+    if (splits > 1 && workgroups > 2 * LC_COMPUTE_UNITS) return false;
     if (8 * workgroups >= 7 * LC_COMPUTE_UNITS) return max_M <= LC_STEP_SHARE_MAX_CHUNKS && max_M <= LC_STEP_SHARE_CHUNKS * splits;
     return max_M <= 1536 && max_M <= 64 * splits;
 }

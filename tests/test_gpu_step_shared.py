@@ -8,19 +8,19 @@ pytestmark = pytest.mark.gpu
 
 
 class _Index:
-    def __init__(self, chunks, H, G, centers, budget, sink=0, seed=0, spare=0):
+    def __init__(self, chunks, H, G, centers, budget, sink=0, seed=0, spare=0, splits=0, longest=5):
         import torch
         from paper_2603_08453_amd import binding as lc
         self.lc, self.torch, self.budget, self.H, self.G, self.B = lc, torch, budget, H, G, len(chunks)
         r = np.random.default_rng(seed + sum(chunks))
-        self.bounds = [np.concatenate([[0], np.cumsum(r.integers(1, 6, size=m))]).astype(np.int32) for m in chunks]
+        self.bounds = [np.concatenate([[0], np.cumsum(r.integers(1, longest + 1, size=m))]).astype(np.int32) for m in chunks]
         self.lens = [int(b[-1]) for b in self.bounds]
         self.gen = torch.Generator(device="cuda")
         self.gen.manual_seed(seed)
         rows, self.cap = max(self.lens) + spare, max(chunks) + spare
         self.K, self.V = self.draw(self.B, H, rows, 128), self.draw(self.B, H, rows, 128)
         self.cfg = lc.lc_config_default(levels=2, fanout=16, kmeans_iters=1, max_chunks=self.cap, max_tokens=rows, center_dtype=centers,
-                                        sink_tokens=sink)
+                                        sink_tokens=sink, decode_splits=splits)
         self.ib = torch.full((lc.lc_index_bytes(self.cfg, self.B, H),), 0xA5, dtype=torch.uint8, device="cuda")
         self.ws = torch.full((lc.lc_workspace_bytes(self.cfg, self.B, H * G, H),), 0xA5, dtype=torch.uint8, device="cuda")
         self.build()
@@ -67,6 +67,21 @@ def test_shares(chunks, H, budget, G, centers):
     x = _Index(chunks, H, G, centers, budget)
     for _ in range(3):
         x.check(x.query())
+
+
+# The caller's own number of splits, as far as there are tokens for them: shares of four chunks and up, and more workgroups than run at the
+# same time, where those that run would wait for the others (two kernels).
+@pytest.mark.parametrize("G,centers", [(1, 0), (4, 1), (7, 0)])
+@pytest.mark.parametrize("chunks,H,longest,splits,one", [([200], 2, 160, 256, True), ([200], 2, 60, 64, True), ([200, 190], 2, 160, 256, False),
+                                                         ([513], 2, 5, 64, True), ([700], 8, 5, 256, True), ([700, 650], 8, 5, 256, False),
+                                                         ([2500], 4, 5, 256, True), ([2500], 8, 5, 256, False), ([900, 100, 2], 3, 5, 3, False)])
+def test_splits_of_the_callers(chunks, H, longest, splits, one, G, centers):
+    x = _Index(chunks, H, G, centers, 10 ** 6, splits=splits, longest=longest)
+    assert x.lc.lc_bench_step_is_one_kernel(x.idx, H * G, x.budget) == one
+    for budget in (10 ** 6, x.lens[0] // 2, 300):
+        x.budget = budget
+        for _ in range(2):
+            x.check(x.query())
 
 
 def test_pinned_chunks_and_no_budget():
