@@ -354,6 +354,9 @@ lc_decode_kernel(const LcDecodeArgs a) {
         // 6 gives half of it and 44 a quarter to half.
         __builtin_amdgcn_s_sleep(20);
         for (int looks = 1;; ++looks) {
+            // (a load through a resource is an ordinary one to the compiler: every look is to be one of its own.  Marked volatile, each of the EC loads
+            // would be waited for before the next)
+            __atomic_signal_fence(__ATOMIC_ACQ_REL);
             lc_v2i x[EC];
 #pragma unroll
             for (int e = 0; e < EC; ++e) x[e] = __builtin_amdgcn_raw_buffer_load_b64(posted_r, j0 * 8, e * 512, 16);
