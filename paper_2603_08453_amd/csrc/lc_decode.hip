@@ -305,7 +305,7 @@ lc_decode_kernel(const LcDecodeArgs a) {
         const __amdgpu_buffer_rsrc_t bnd_r = lc_buffer(bnd, (rows + 1) * 4);
         const __amdgpu_buffer_rsrc_t posted_r = lc_buffer(ix.posted + (size_t)bh * rows, rows * 8);
         const int lo = s * a.share, hi = min(lo + a.share, rows);
-        const int M = ix.state[bh * 4 + 1], number = ix.sync[bh * 4 + 3];
+        const int M = min(ix.state[bh * 4 + 1], rows), number = ix.sync[bh * 4 + 3];
         __builtin_amdgcn_sched_barrier(0);                          // (on their way before the first wait)
         Pass first, second;
         // (64 chunks first, or 32; a few more a chunk to a group)
@@ -335,14 +335,6 @@ lc_decode_kernel(const LcDecodeArgs a) {
                 if (lo + 64 + 16 * wave < mine) post(Four(), second, lo + 64 + 4 * grp, hi);
             }
         }
-        // (an index that has grown since this launch was captured: the chunks behind all shares, 64 for each workgroup in turn; left to the
-        // wavefronts that look for them, a replay took 38 to 55 us where a step captured anew takes 12)
-        if (__builtin_expect(S * a.share < M, 0)) {
-            for (int j = S * a.share + 64 * s + 16 * wave; j < M; j += 64 * S) {
-                load(Four(), first, j + 4 * q4, M);
-                post(Four(), first, j + 4 * q4, M);
-            }
-        }
 #pragma unroll
         for (int e = 0; e < EC; ++e) {
             begin[e] = __builtin_amdgcn_raw_buffer_load_b32(bnd_r, j0 * 4, e * 256, 0);
@@ -353,7 +345,20 @@ lc_decode_kernel(const LcDecodeArgs a) {
         // 4 sequences of 32K 16.5 -> 15.8 us, 32 layers of 128K 153.1 -> 146.7, 16 ragged sequences 23.9 -> 23.5; 18 to 26 are the same within 0.5 %,
         // 6 gives half of it and 44 a quarter to half.
         __builtin_amdgcn_s_sleep(20);
-        for (int looks = 1;; ++looks) {
+        // Before the first look the chunks behind all shares, if there are any (an index that has grown since this launch was captured), 64 for each workgroup
+        // in turn; left to the wavefronts that look for them, a replay took 38 to 55 us where a step captured anew takes 12.  After LC_DEC_LOOKS of them all
+        // chunks of this wavefront, then one look more: the loop ends whatever is in memory.  (One copy of the scoring for both: with two a step took 1 to 2 %
+        // longer.)
+        const int behind = S * a.share;
+        for (int looks = 0;; ++looks) {
+            if (__builtin_expect(looks == 0 ? behind < M : looks == LC_DEC_LOOKS, 0)) {
+                const int step = looks == 0 ? 64 * S : 16, end = looks == 0 ? M : min((wave + 1) * (EC * 64), M);
+                for (int j = looks == 0 ? behind + 64 * s + 16 * wave : wave * (EC * 64); j < end; j += step) {
+                    load(Four(), first, j + 4 * q4, end);
+                    post(Four(), first, j + 4 * q4, end);
+                }
+                __builtin_amdgcn_s_waitcnt(0);                      // (at the next look they are there)
+            }
             // (a load through a resource is an ordinary one to the compiler: every look is to be one of its own.  Marked volatile, each of the EC loads
             // would be waited for before the next)
             __atomic_signal_fence(__ATOMIC_ACQ_REL);
@@ -366,14 +371,7 @@ lc_decode_kernel(const LcDecodeArgs a) {
                 key[e] = (uint32_t)x[e].x;
                 there = there && (x[e].y == number || j0 + 64 * e >= M);
             }
-            if (__ballot(there) == ~0ull) break;
-            if (__builtin_expect(looks % LC_DEC_LOOKS == 0, 0)) {
-                for (int j = wave * (EC * 64); j < min((wave + 1) * (EC * 64), M); j += 4) {
-                    load(One(), first, j + q4, M);
-                    post(One(), first, j + q4, M);
-                }
-                __builtin_amdgcn_s_waitcnt(0);                      // (at the next look they are all there)
-            }
+            if (__ballot(there) == ~0ull || looks == LC_DEC_LOOKS) break;
         }
     };
 

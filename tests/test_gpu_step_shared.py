@@ -177,3 +177,27 @@ def test_an_index_that_has_grown_takes_a_captured_step_no_longer():
         assert torch.equal(got, ref) and torch.equal(got_lse, ref_lse)
         x.check(q)
         assert old < 1.8 * us(capture()) + 2, more
+
+
+def test_steps_beside_other_streams_kernels():
+    """Workgroups of a step that have no place yet, because two other streams keep the device busy: those that have one wait for their keys for a while
+    and then score for themselves.  The same bits as on a quiet device."""
+    import torch
+    xs = [_Index([2300], 8, 4, 0, 2048, seed=1), _Index([500, 620, 41], 8, 7, 1, 1024, seed=2)]
+    qs = [x.query() for x in xs]
+    assert all(x.lc.lc_bench_step_is_one_kernel(x.idx, x.H * x.G, x.budget) for x in xs)
+    alone = [x.step(q)[2:] for x, q in zip(xs, qs)]
+    noise = torch.randn((4096, 4096), device="cuda")
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    outs = [[(torch.empty_like(o), torch.empty_like(l)) for _ in range(30)] for o, l in alone]
+    torch.cuda.synchronize()
+    for i in range(30):
+        with torch.cuda.stream(streams[2]):
+            if i % 3 == 0:
+                torch.mm(noise, noise)
+        for x, q, out, stream in zip(xs, qs, outs, streams):
+            x.lc.lc_decode_step(x.idx, q, x.K, x.V, x.budget, out[i][0], x.ws, lse=out[i][1], stream=stream)
+    torch.cuda.synchronize()
+    for (o, l), got in zip(alone, outs):
+        assert all(torch.equal(a, o) and torch.equal(b, l) for a, b in got)
