@@ -285,6 +285,7 @@ __device__ __forceinline__ void lc_select_chunks(const LcDev& ix, int b, int bh,
         // ---- the short list ranked by (key descending, id ascending): a chunk is selected if it fits with those before it.
         // A few, as nearly always, by a lane for each pair of them; more by a lane for each.  (One after the other through scalar registers, every
         // chunk of the list cost 0.06 us: 0.6 us at the median, 1.1 in one step of twenty, now 0.25.)
+        static_assert(NW * LC_SEL_CAND <= 64, "one lane per slot of the short list, one bit of the result for each");
         auto listed = [&](int i) -> int4 {
             int w = 0, c = i;
 #pragma unroll
