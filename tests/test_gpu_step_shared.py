@@ -1,6 +1,7 @@
 """The decode step whose workgroups share the scoring, against the two separate calls: shares around the numbers of chunks that a pass
-takes, chunk counts around the kernel's instances and its largest, several steps in a row, a buffer that held another index, and
-chunks that nobody has posted."""
+takes, chunk counts around the kernel's instances and its largest, several steps in a row, the caller's own number of splits, a buffer that held another
+index, chunks that no workgroup's share holds, and other streams' kernels beside it.  That the scoring is shared is asserted, as the
+two-kernel form gives the same."""
 import numpy as np
 import pytest
 
@@ -34,6 +35,16 @@ class _Index:
     def query(self):
         return self.draw(self.B, self.H * self.G, 128)
 
+    def shares(self):
+        """Whether the step is one kernel (beyond 128 chunks: one whose workgroups share the scoring)."""
+        return self.lc.lc_bench_step_is_one_kernel(self.idx, self.H * self.G, self.budget)
+
+    def posted(self):
+        """The keys that the steps have posted, with the step's number above them: the last part of the index buffer."""
+        words = self.B * self.H * min(self.cap, 2560)
+        assert words * 8 % 256 == 0
+        return self.ib[-words * 8:].view(self.torch.int64)
+
     def step(self, q, out=None, lse=None):
         out = self.torch.full((self.B, self.H * self.G, 128), float("nan"), device="cuda") if out is None else out
         lse = self.torch.full((self.B, self.H * self.G), float("nan"), device="cuda") if lse is None else lse
@@ -57,14 +68,17 @@ class _Index:
         assert torch.allclose(out, ref, rtol=1e-4, atol=2e-5) and torch.allclose(lse, ref_lse, rtol=1e-5, atol=1e-5)
 
 
-# one to 32 splits by the budget; 32 (sequence, head) pairs fill the device, two do not
+# One to 32 splits by the budget; 32 (sequence, head) pairs fill the device, two do not.  `to`: the largest group size at which the workgroups share the
+# scoring (0: never).  The shares: 32 chunks and less, up to 64, 80 and 128; the instances: up to 512, 1024, 1536 and 2560 chunks.
 @pytest.mark.parametrize("G,centers", [(1, 0), (4, 0), (4, 1), (7, 0), (8, 1)])
-@pytest.mark.parametrize("chunks,H,budget", [([129], 2, 300), ([255, 1], 2, 512), ([257], 2, 512), ([511, 130], 2, 513), ([513], 1, 2048),
-                                             ([1024, 1025], 1, 2048), ([1535], 1, 4000), ([1536, 400], 2, 4000), ([1537], 2, 4000),
-                                             ([513, 7, 400, 512], 8, 512), ([577, 640, 641, 1], 8, 512), ([1023, 1024, 0, 65], 8, 512),
-                                             ([1025] * 4, 8, 512), ([2559], 8, 4096), ([2560, 2300], 8, 2048), ([2561], 8, 4096)])
-def test_shares(chunks, H, budget, G, centers):
+@pytest.mark.parametrize("chunks,H,budget,to", [
+    ([129], 2, 300, 8), ([255, 1], 2, 512, 8), ([257], 2, 512, 8), ([511, 130], 2, 513, 8), ([513], 1, 2048, 8), ([1024, 1025], 1, 2048, 8),
+    ([1535], 1, 4000, 8), ([1536, 400], 2, 4000, 8), ([1537], 2, 4000, 0), ([1537], 8, 4096, 8), ([513, 7, 400, 512], 8, 512, 8),
+    ([577, 640, 641, 1], 8, 512, 8), ([1023, 1024, 0, 65], 8, 512, 8), ([1024] * 4, 8, 600, 8), ([1025] * 4, 8, 512, 0), ([2559], 8, 4096, 8),
+    ([2560], 8, 4096, 8), ([2560, 2300], 8, 2048, 4), ([2561], 8, 4096, 0)])
+def test_shares(chunks, H, budget, to, G, centers):
     x = _Index(chunks, H, G, centers, budget)
+    assert x.shares() == (G <= to)
     for _ in range(3):
         x.check(x.query())
 
@@ -77,7 +91,7 @@ def test_shares(chunks, H, budget, G, centers):
                                                          ([2500], 4, 5, 256, True), ([2500], 8, 5, 256, False), ([900, 100, 2], 3, 5, 3, False)])
 def test_splits_of_the_callers(chunks, H, longest, splits, one, G, centers):
     x = _Index(chunks, H, G, centers, 10 ** 6, splits=splits, longest=longest)
-    assert x.lc.lc_bench_step_is_one_kernel(x.idx, H * G, x.budget) == one
+    assert x.shares() == one
     for budget in (10 ** 6, x.lens[0] // 2, 300):
         x.budget = budget
         for _ in range(2):
@@ -87,27 +101,44 @@ def test_splits_of_the_callers(chunks, H, longest, splits, one, G, centers):
 def test_pinned_chunks_and_no_budget():
     for sink, budget in ((40, 500), (9, 0), (0, 10 ** 6)):
         x = _Index([600, 140], 2, 4, 0, budget, sink=sink)
+        assert x.shares()
         x.check(x.query())
 
 
 def test_a_buffer_that_held_another_index():
-    """The keys that the steps on one index have posted are no keys of the index built in the same buffer later."""
-    x = _Index([700], 4, 4, 0, 512)
-    for _ in range(2):
-        for _ in range(3):
-            x.check(x.query())
+    """The keys that the steps on one index have posted are no keys of the index that comes into the same buffer later, by a build or an import: its first step has
+    the number that they carry.  (Whether a stale key would be read is a matter of time, so the words themselves are looked at.)"""
+    x = _Index([704], 4, 4, 0, 720)
+    keys, blob = x.K.clone(), x.lc.lc_index_export(x.idx)
+    for _ in range(3):
+        assert x.shares() and not x.posted().any()
+        x.check(x.query())
+        assert bool((x.posted() >> 32 == 1).all())
         x.K.copy_(x.draw(*x.K.shape))
         x.build()
-    blob = x.lc.lc_index_export(x.idx)
+    x.check(x.query())
+    x.K.copy_(keys)
     x.idx = x.lc.lc_index_import(x.cfg, blob, x.ib)
+    assert not x.posted().any()
     x.check(x.query())
 
 
+@pytest.mark.parametrize("spare", [0, 2456, 9980])
+def test_keys_of_chunks_to_come_are_cleared(spare):
+    """As many as a step may post, however few chunks there are."""
+    x = _Index([100, 36], 8, 4, 0, 512, spare=spare)
+    assert not x.posted().any()
+    x.ib.fill_(0xA5)
+    x.build()
+    assert not x.posted().any()
+
+
 def test_chunks_that_nobody_posted():
-    """A captured step on an index that has grown beyond what its workgroups share out: whoever waits for the other chunks' keys scores them."""
+    """A captured step on an index that has grown beyond what its workgroups share out."""
     import torch
     x = _Index([130], 2, 4, 0, 256, spare=64)
     q, out, lse = x.query(), torch.empty((1, 8, 128), device="cuda"), torch.empty((1, 8), device="cuda")
+    assert x.shares()
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
     with torch.cuda.stream(side):
@@ -162,7 +193,7 @@ def test_an_index_that_has_grown_takes_a_captured_step_no_longer():
         return min(took)
 
     q, out, lse = x.query(), torch.empty((1, 8, 128), device="cuda"), torch.empty((1, 8), device="cuda")
-    assert x.lc.lc_bench_step_is_one_kernel(x.idx, 8, x.budget)
+    assert x.shares()
     graph, grown = capture(), 0
     # four splits of 36 chunks, an instance that holds 512: one chunk behind them, a workgroup's 64, all of them and more than all of them
     for more in (15, 64 + 14, 256 + 14, 300):
@@ -185,7 +216,7 @@ def test_steps_beside_other_streams_kernels():
     import torch
     xs = [_Index([2300], 8, 4, 0, 2048, seed=1), _Index([500, 620, 41], 8, 7, 1, 1024, seed=2)]
     qs = [x.query() for x in xs]
-    assert all(x.lc.lc_bench_step_is_one_kernel(x.idx, x.H * x.G, x.budget) for x in xs)
+    assert all(x.shares() for x in xs)
     alone = [x.step(q)[2:] for x, q in zip(xs, qs)]
     noise = torch.randn((4096, 4096), device="cuda")
     torch.cuda.synchronize()
