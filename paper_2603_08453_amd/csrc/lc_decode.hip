@@ -37,7 +37,7 @@
 #define LC_DEC_TILE 1024          // tokens of a split whose cache rows are resolved into LDS at a time
 #define LC_DEC_LAG 8              // powers of two that a logit may lie above the softmax's reference
 #define LC_DEC_FAINT -101.f       // logits that lie further below the reference have probabilities that lc_split3 does not hold (below 2^-109)
-#define LC_DEC_LOOKS 128          // times a wavefront looks for keys before it scores them itself (1 us each at least)
+#define LC_DEC_LOOKS 128          // times a wavefront looks for keys before it scores them itself (27 to 43 us for all of them on a quiet device, 0.6 us each while others score)
 #define LC_DEC_E 2                // selected ids per thread and pass of the row resolution
 #define LC_LOG2E 1.4426950408889634f
 #define LC_LN2 0.6931471805599453f
@@ -60,7 +60,7 @@ struct LcDecodeArgs {
     float* out;           // [B][H*G][d]
     float* lse;           // [B][H*G] or null
     // fused step only (the kernel selects the chunks itself from their score keys):
-    const int* entries;   // [B][H][cap0] chunk entries (LcChunkEntry) of the scoring kernel; null: scored here
+    const int* entries;   // [B][H][cap0] chunk entries (LcChunkEntry) of the scoring kernel (unused where this kernel scores)
     int32_t* ids_out;     // [B][H][cap] selected ids, ascending, or null
     int32_t* counts_out;  // [B][H] or null
     int budget, sink;     // token budget, tokens of the pinned prefix
@@ -141,7 +141,7 @@ __device__ __forceinline__ void lc_add_scaled(float4& sum, const float4& x, floa
 // index, all read all of them.  A key is posted together with the number of the step (`sync`), in one 8-byte access at agent scope, so a reader sees from the
 // word itself whether it is this step's: no counter, no wait for stores.  No workgroup depends on another one to get ahead: a wavefront that has
 // looked LC_DEC_LOOKS times for keys that are not there (a workgroup that has no place yet, behind another stream's kernel) scores
-// its chunks itself and posts what the others would have posted.
+// its chunks itself, posts what the others would have posted, and looks once more.
 //
 // Either way the selected chunks sit in a list, in id order; the wavefronts write the cache row of
 // every token of the split's tile into LDS, 64 lanes per overlapping chunk.
@@ -342,20 +342,20 @@ lc_decode_kernel(const LcDecodeArgs a) {
         }
         // The keys of the others are on their way for as long as a store takes to reach the memory side (about 0.6 us): a look before
         // that fails, holds the next one back by 0.6 us and takes bandwidth from those that still score.  20 * 64 cycles of waiting, against none:
-        // 4 sequences of 32K 16.5 -> 15.8 us, 32 layers of 128K 153.1 -> 146.7, 16 ragged sequences 23.9 -> 23.5; 18 to 26 are the same within 0.5 %,
+        // 4 sequences of 32K 16.5 -> 15.8 us, eight layers of 128K 153.1 -> 146.7, 16 ragged sequences 23.9 -> 23.5; 18 to 26 are the same within 0.5 %,
         // 6 gives half of it and 44 a quarter to half.
         __builtin_amdgcn_s_sleep(20);
-        // Before the first look the chunks behind all shares, if there are any (an index that has grown since this launch was captured), 64 for each workgroup
+        // Before the first look the chunks behind all shares, if there are any (an index that has grown since this launch was captured), 16 for each workgroup
         // in turn; left to the wavefronts that look for them, a replay took 38 to 55 us where a step captured anew takes 12.  After LC_DEC_LOOKS of them all
-        // chunks of this wavefront, then one look more: the loop ends whatever is in memory.  (One copy of the scoring for both: with two a step took 1 to 2 %
-        // longer.)
+        // chunks of this wavefront, then one look more: the loop ends whatever is in memory.  (One copy of the scoring for both, a chunk to a group: what is
+        // fetched of a kernel's code is in every step's time.  Eight layers of 128K with two copies 150.1 us, four chunks to a group 147.9, so 147.3, without any 146.8.)
         const int behind = S * a.share;
         for (int looks = 0;; ++looks) {
             if (__builtin_expect(looks == 0 ? behind < M : looks == LC_DEC_LOOKS, 0)) {
-                const int step = looks == 0 ? 64 * S : 16, end = looks == 0 ? M : min((wave + 1) * (EC * 64), M);
-                for (int j = looks == 0 ? behind + 64 * s + 16 * wave : wave * (EC * 64); j < end; j += step) {
-                    load(Four(), first, j + 4 * q4, end);
-                    post(Four(), first, j + 4 * q4, end);
+                const int step = looks == 0 ? 16 * S : 4, end = looks == 0 ? M : min((wave + 1) * (EC * 64), M);
+                for (int j = looks == 0 ? behind + 16 * s + 4 * wave : wave * (EC * 64); j < end; j += step) {
+                    load(One(), first, j + q4, end);
+                    post(One(), first, j + q4, end);
                 }
                 __builtin_amdgcn_s_waitcnt(0);                      // (at the next look they are there)
             }
@@ -896,7 +896,7 @@ lc_decode_kernel(const LcDecodeArgs a) {
     if (tid == 0) ix.sync[bh * 4 + 1] = 0;
     if (SCORE == LC_SCORED_SHARED && tid == 0) {                 // (every workgroup has read the number: it arrives behind that)
         const int number = ix.sync[bh * 4 + 3];
-        ix.sync[bh * 4 + 3] = number == -1 ? 1 : number + 1;
+        ix.sync[bh * 4 + 3] = number == -1 ? 1 : (int)((uint32_t)number + 1u);
     }
 }
 

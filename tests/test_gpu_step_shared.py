@@ -195,8 +195,8 @@ def test_an_index_that_has_grown_takes_a_captured_step_no_longer():
     q, out, lse = x.query(), torch.empty((1, 8, 128), device="cuda"), torch.empty((1, 8), device="cuda")
     assert x.shares()
     graph, grown = capture(), 0
-    # four splits of 36 chunks, an instance that holds 512: one chunk behind them, a workgroup's 64, all of them and more than all of them
-    for more in (15, 64 + 14, 256 + 14, 300):
+    # four splits of 36 chunks, an instance that holds 512: one chunk behind them, one workgroup's 16, a turn of all four, several turns
+    for more in (15, 16 + 14, 64 + 14, 65 + 14, 300):
         while grown < more:
             x.lc.lc_append(x.idx, x.K, x.V, x.draw(1, 2, 128), x.draw(1, 2, 128), [1], x.ws)
             grown += 1
