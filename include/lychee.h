@@ -240,16 +240,25 @@ int lc_sparse_decode(const lc_index* idx, const void* q, const void* K, const vo
  * lc_decode_step -- lc_retrieve followed by lc_sparse_decode in one call (Algorithm 1
  * steps 1-3; Eq. 2 scoring, budgeted selection, Eq. 1 over the active set), for
  * callers that do not need the chunk list between the two.  Same selection (bit
- * for bit) and same attention result as the two calls.  The chunk score keys go
- * from the scoring kernel to the attention kernel through the workspace; every
- * workgroup of the attention kernel repeats the selection of its (sequence,
- * head) from them, so no chunk list travels through memory on the critical path.
- * With up to 64 chunks per sequence (128 unless a large group meets many workgroups)
- * there is no scoring kernel: every workgroup scores all chunks itself.
+ * for bit) and same attention result as the two calls.  Every workgroup of the
+ * attention kernel makes the selection of its (sequence, head) by itself, from the
+ * score keys of all chunks, so no chunk list travels through memory on the critical
+ * path.  Where the keys come from goes by the numbers of chunks and workgroups:
+ *   - up to 64 chunks per sequence (128 unless a large group meets many workgroups)
+ *     every workgroup scores all chunks itself;
+ *   - up to 2560 chunks the workgroups of a (sequence, head) score a share each and post
+ *     the keys for each other, if they all run at the same time and the shares are small.
+ *     The keys are posted in the INDEX BUFFER, which such a step writes to although the
+ *     index stays as it is.  A workgroup waits for the others' keys for some 30 to 80 us at
+ *     most (they come within 2 unless another stream's kernel keeps a workgroup from
+ *     starting); then it scores those chunks itself;
+ *   - otherwise a scoring kernel runs first and leaves the keys in the workspace.
  * When a sequence has more than 4096 chunks, the chunks no longer fit the registers of
  * the selecting workgroups and the call runs the kernels of the two separate entry
  * points instead (through a chunk list in the workspace); so it does under the BEAM
  * policy, whose selection needs the kept set of every level.  The results are the same.
+ * A captured step is laid out for the numbers of chunks at the time of its capture: capture it
+ * anew when chunks have been closed since (tokens that closed none may have been appended).
  *
  *   chunk_ids, counts  optional outputs as in lc_retrieve (both or neither); cap
  *                      is checked only when they are given

@@ -19,7 +19,7 @@ extern "C" {
  * query, index, budget and workspace left in the workspace: calling it in any other situation
  * gives undefined results (never a fault: every access is range-checked as in lc_decode_step).
  * Arguments, checks and error codes as lc_decode_step without the chunk list outputs;
- * LC_ERR_CAPACITY if the index is too large for lc_decode_step to run as two kernels. */
+ * LC_ERR_CAPACITY where lc_decode_step runs through a chunk list (too many chunks, or top-k per level). */
 int lc_bench_select_attend(const lc_index* idx, const void* q, const void* K, const void* V,
                            const int64_t kv_strides[3], int H_q, int budget,
                            float* out, float* lse, void* ws, size_t ws_bytes, void* stream);

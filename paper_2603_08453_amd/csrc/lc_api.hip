@@ -606,8 +606,8 @@ int useful_splits(const lc_index* idx, int G, int max_M, int budget, int splits)
     return splits;
 }
 
-// Scoring shared out over the workgroups of a (sequence, head) or a kernel of its own in front (more than lc_step_is_single takes).  Sharing saves a
-// launch, the entries' way through memory and the wait for the slowest of all (sequence, head) pairs; it costs a wait for the keys (two looks of 0.6 us),
+// Scoring shared out over the workgroups of a (sequence, head), or a kernel of its own in front (more chunks than lc_step_is_single takes).  Sharing saves a
+// launch, the entries' way through memory and the wait for the slowest of all (sequence, head) pairs; it costs a wait for the keys (a store's way and a look, 0.6 us each),
 // which every workgroup reads, and where there are fewer workgroups than compute units the kernel in front scores on all of them.
 // Time of a step shared over that of two kernels, 2 to 128 pairs, group sizes 1 to 7, both kinds of centers: 0.87 to 0.98 at up to 64 chunks a
 // workgroup (1.00 to 1.02 at 1820 chunks with 64 workgroups); at 72 to 120 with the device full 0.88 to 0.95 (16 ragged sequences, group size 7: 27.6 and

@@ -129,7 +129,6 @@ int lc_launch_retrieve(const lc_index* idx, const LcWs& ws, const void* q, int G
 int lc_launch_decode(const lc_index* idx, const LcWs& ws, const void* q, const void* K, const void* V,
                      const int64_t ks[3], const int32_t* ids, const int32_t* counts, int cap, int G,
                      int splits, float* out, float* lse, hipStream_t stream);
-// `single`: the scoring too.
 // Who scores the chunks of a fused step: a kernel before it (chunk entries in ws.scratch, lc_launch_retrieve with score_only), every
 // workgroup all of them (up to LC_STEP_SINGLE_MAX_CHUNKS), or the workgroups of a (sequence, head) a share each (up to LC_STEP_SHARE_CHUNKS of
 // LC_STEP_SHARE_MAX_CHUNKS in all).
@@ -143,7 +142,7 @@ enum { LC_SCORED_BEFORE = 0, LC_SCORED_HERE = 1, LC_SCORED_SHARED = 2 };
 inline bool lc_step_is_single(int max_M, int G, long long workgroups) {
     return max_M <= 64 || (max_M <= LC_STEP_SINGLE_MAX_CHUNKS && (G <= 4 || workgroups <= 256));
 }
-// Fused step: selection + attention, with the scoring or after it.  lc_decode_fused_fits tells whether a selecting workgroup holds max_M chunks.
+// Fused step: selection + attention; `single`: the scoring too.  lc_decode_fused_fits tells whether a selecting workgroup holds max_M chunks.
 bool lc_decode_fused_fits(int G, int max_M);
 int lc_launch_decode_fused(const lc_index* idx, const LcWs& ws, const void* q, const void* K, const void* V,
                            const int64_t ks[3], int G, int splits, int budget, int32_t* ids_out,

@@ -380,9 +380,9 @@ lc_upper_kernel(const LcRetrieveArgs a) {
 // One compute unit works on a (sequence, head), one stage after the other: what bounds it is the chain of
 // memory round trips, and the unit's instruction rate -- an instruction that all sixteen wavefronts execute takes
 // 16 cycles.  So
-//   - everything whose address does not depend on a result is on its way before the first wait, the query and
-//     the top level's first rows, and behind them the parent pointers of all levels straight into LDS (those that fit:
-//     the upper levels first);
+//   - the query and the top level's first rows, whose addresses depend on no result, are on their way before the first
+//     wait; when they have come, the parent pointers of all levels go straight into LDS (those that fit: the
+//     upper levels first);
 //   - a group of 16 lanes scores four nodes at a time (lc_score_packed), the best are found by one wavefront from a
 //     histogram of 64 bins (lc_wave_cut), a list is written from the lanes' marks by one scan and one
 //     exchange of counts (gather below);
