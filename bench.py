@@ -640,7 +640,7 @@ def main():
             "bf16_chunk_centers_us": None if half_us is None else round(half_us, 2),
             "entry_points": "lc_retrieve + lc_sparse_decode" if args.separate else "lc_decode_step",
             "separate_calls_us": None if separate_s is None else round(separate_s * 1e6, 2),
-            ("step_kernel_us_event" if one_kernel_step else "select_attend_kernel_us_event"): round(fused_us, 2),
+            ("step_kernel_us_event" if one_kernel_step else "select_attend_kernel_us_event"): round(fused_us, 2) if fused_step else None,
             "retrieve_us_event": round(retrieve_us, 2),
             "attend_us_event": round(attend_us, 2),
             "attend_kernel_alone_frac_of_hbm_peak": round(attend_bytes / (attend_us * 1e-6) / 1e9 / HBM_PEAK_GBS, 4),
