@@ -128,7 +128,9 @@ size_t lc_index_bytes(const lc_config* cfg /* host */, int B, int H_kv, int d);
  * scratch of the index build (unit directions of the points of two levels and the
  * centroids of two levels, each in float32 and bfloat16): per chunk and head about
  * 768 bytes and 2.3 KB / fan-out of level 1, i.e. 0.9 KB at fan-out 16 and 1.9 KB at
- * fan-out 2.  Every call that takes a workspace asks for this size (lc_index_drift: see there). */
+ * fan-out 2.  Up to 128 (sequence, head)s and 16 k-means iterations there is room for what the workgroups of
+ * a clustering post for each other behind that: per (sequence, head) and iteration 512 bytes for each of up to 256 clusters and
+ * 2 bytes for each of up to 8192 points, i.e. 0.4 KB more per chunk and head at fan-out 16 and 10 iterations.  Every call that takes a workspace asks for this size (lc_index_drift: see there). */
 size_t lc_workspace_bytes(const lc_config* cfg /* host */, int B, int H_q, int H_kv, int d);
 
 /*

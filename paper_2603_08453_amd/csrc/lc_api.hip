@@ -117,6 +117,8 @@ size_t lc_layout_ws(const lc_config* cfg, int B, int H_q, int H, int d, int spli
     W->dirs = W->next_pts = W->cent[0] = W->cent[1] = nullptr;
     W->dirs16 = W->next_pts16 = W->cent16[0] = W->cent16[1] = nullptr;
     W->kflags = nullptr;
+    W->rounds = nullptr;
+    W->rounds_bytes = 0;
     if (with_build) {
         W->dirs = c.take<float>(BH * cap[0] * d);
         W->dirs16 = c.take<uint16_t>(BH * cap[0] * d);
@@ -130,6 +132,22 @@ size_t lc_layout_ws(const lc_config* cfg, int B, int H_q, int H, int d, int spli
     }
     W->total = align_up(c.off);
     return W->total;
+}
+
+size_t lc_rounds_bytes(const lc_config* cfg, int B, int H) {
+    const long long BH = (long long)B * H;
+    if (cfg->levels < 2 || BH > LC_RK_MAX_PAIRS || cfg->kmeans_iters < 1 || cfg->kmeans_iters > LC_RK_MAX_ITERS) return 0;
+    int cap[LC_MAX_LEVELS];
+    level_caps(cfg, cap);
+    const size_t n = cap[0] < LC_RK_MAX_POINTS ? cap[0] : LC_RK_MAX_POINTS, k = cap[1] < LC_RK_MAX_CLUSTERS ? cap[1] : LC_RK_MAX_CLUSTERS;
+    return align_up((size_t)BH * ((cfg->kmeans_iters + 1) * k * LC_HEAD_DIM * sizeof(float) + cfg->kmeans_iters * ((n + 15) / 16 * 32)));
+}
+
+// The workspace of a build, with what is behind it.
+static void lay_out_build_ws(const lc_config* cfg, int B, int H, int d, void* ws, size_t ws_bytes, LcWs* w) {
+    const size_t total = lc_layout_ws(cfg, B, H, H, d, 1, ws, w), more = lc_rounds_bytes(cfg, B, H);
+    w->rounds = reinterpret_cast<float*>(static_cast<char*>(ws) + total);
+    w->rounds_bytes = ws_bytes - total < more ? ws_bytes - total : more;
 }
 
 extern "C" {
@@ -167,7 +185,7 @@ size_t lc_index_bytes(const lc_config* cfg, int B, int H_kv, int d) {
 size_t lc_workspace_bytes(const lc_config* cfg, int B, int H_q, int H_kv, int d) {
     if (!config_ok(cfg) || B < 1 || H_kv < 1 || H_q < H_kv || H_q % H_kv != 0 || d != LC_HEAD_DIM) return 0;
     if (H_q / H_kv > LC_MAX_GROUP) return 0;
-    return lc_layout_ws(cfg, B, H_q, H_kv, d, lc_auto_splits(cfg, B, H_kv), nullptr, nullptr);
+    return lc_layout_ws(cfg, B, H_q, H_kv, d, lc_auto_splits(cfg, B, H_kv), nullptr, nullptr) + lc_rounds_bytes(cfg, B, H_kv);
 }
 
 }  // extern "C"
@@ -386,7 +404,7 @@ int lc_build_index(lc_index** out, const lc_config* cfg, const void* K, const in
     // the build does not depend on the number of query heads: size with G = 1
     LcWs w;
     if (ws_bytes < lc_layout_ws(cfg, B, H_kv, H_kv, d, 1, nullptr, nullptr)) return LC_ERR_WORKSPACE_TOO_SMALL;
-    lc_layout_ws(cfg, B, H_kv, H_kv, d, 1, ws, &w);
+    lay_out_build_ws(cfg, B, H_kv, d, ws, ws_bytes, &w);
 
     lc_index* h = new_handle(cfg, B, H_kv, d, index_buf, index_bytes);
     if (!h) return LC_ERR_INVALID_ARG;
@@ -416,7 +434,7 @@ int lc_recluster(lc_index* idx, void* ws, size_t ws_bytes, void* stream) {
     LcWs w;
     if (ws_bytes < lc_layout_ws(&idx->cfg, idx->B, idx->H_kv, idx->H_kv, idx->d, 1, nullptr, nullptr))
         return LC_ERR_WORKSPACE_TOO_SMALL;
-    lc_layout_ws(&idx->cfg, idx->B, idx->H_kv, idx->H_kv, idx->d, 1, ws, &w);
+    lay_out_build_ws(&idx->cfg, idx->B, idx->H_kv, idx->d, ws, ws_bytes, &w);
     hipStream_t s = static_cast<hipStream_t>(stream);
     fill_level_counts(idx);                       // nodes per level follow the current chunk counts
     const int rc = upload_level_counts(idx, s);

@@ -4,6 +4,7 @@
 //   lc_pool_kernel    chunk representative = mean-pooled keys; covering radius; unit direction
 //   lc_kmeans_*       spherical k-means on unit directions: strided start, then
 //                     `iters` x (assign by largest inner product, normalised-sum update)
+//   lc_kmeans_rounds_kernel  all iterations of a level, and its nodes, in one kernel of several workgroups per (sequence, head)
 //   lc_center_*       node center (mean of all descendant chunks), counts, direction (small levels: in lc_kmeans_small_kernel)
 //   lc_radius_kernel  radii of every level over all descendant chunks' balls, after the last level
 // Append: lc_append_kernel writes the token's k, v; on a chunk close it pools the
@@ -237,6 +238,20 @@ __device__ __forceinline__ void lc_clear_flags(const LcDev& ix, int bh, int* fla
     if (blockIdx.x == 0 && threadIdx.x < LC_KM_FLAGS)
         for (int l = 0; l + 1 < ix.L; ++l) lc_level_flags(ix, flags, l, bh)[threadIdx.x] = 0;
 }
+// What the workgroups of lc_kmeans_rounds_kernel post for each other: in a first kernel's hands only the part that it marks as not posted yet.
+struct LcUnposted {
+    lc_v4i* at;              // 16-byte pieces
+    int n;
+};
+#define LC_UNPOSTED (-1)     // the bits of no label and of no number that an update makes (its not-a-numbers are the hardware's own)
+template <int NT>
+__device__ __forceinline__ void lc_clear_posts(const LcUnposted& u) {
+    const int blocks = gridDim.x * gridDim.y * gridDim.z;
+    const int per = (u.n + blocks - 1) / blocks;                    // a run of pieces for each workgroup
+    const int first = (int)(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z)) * per;
+    const int end = min(first + per, u.n);
+    for (int i = first + (int)threadIdx.x; i < end; i += NT) u.at[i] = lc_v4i{LC_UNPOSTED, LC_UNPOSTED, LC_UNPOSTED, LC_UNPOSTED};
+}
 __device__ __forceinline__ float lc_sum_groups4(float v) { v += __shfl_xor(v, 16); v += __shfl_xor(v, 32); return v; }
 // A batch of rows, row base + 4 k + (lane / 16) of it in buf[k]; rows past the chunk read as zeros, all loads in flight together.  NEAR:
 // a batch lies within a range-checked buffer (rows of 256 bytes or more that do not overlap, 31 bits of offset), whose
@@ -262,11 +277,12 @@ __device__ __forceinline__ void lc_pool_batch(const uint16_t* Kbh, long long ks_
 template <bool NEAR>
 __global__ void __launch_bounds__(64)
 lc_pool_kernel(LcDev ix, const uint16_t* K, long long ks_seq, long long ks_head, long long ks_tok,
-               int geometry, LcPointRows out, int* flags) {
+               int geometry, LcPointRows out, int* flags, LcUnposted unposted) {
     lc_fetch_args<sizeof(LcDev) + 40 + sizeof(LcPointRows)>();
     const int h = blockIdx.y, b = blockIdx.z;
     const int bh = b * ix.H + h;
     lc_clear_flags(ix, bh, flags);
+    lc_clear_posts<64>(unposted);
     const int lane = threadIdx.x & 63, sub = lane & 15, g4 = lane >> 4;
     const int j = blockIdx.x;
     const int M = ix.state[bh * 4 + 1];
@@ -412,11 +428,12 @@ lc_pool_kernel(LcDev ix, const uint16_t* K, long long ks_seq, long long ks_head,
 
 // Re-clustering starts from the chunk nodes already in the index: unit directions of their centers.
 __global__ void __launch_bounds__(LC_BT)
-lc_dirs_kernel(LcDev ix, LcPointRows out, int* flags) {
+lc_dirs_kernel(LcDev ix, LcPointRows out, int* flags, LcUnposted unposted) {
     lc_fetch_args<sizeof(LcDev) + sizeof(LcPointRows)>();
     const int h = blockIdx.y, b = blockIdx.z;
     const int bh = b * ix.H + h;
     lc_clear_flags(ix, bh, flags);
+    lc_clear_posts<LC_BT>(unposted);
     const int M = ix.state[bh * 4 + 1];
     const int sub = threadIdx.x & 15;
     const int j = blockIdx.x * LC_BG + (threadIdx.x >> 4);
@@ -1477,7 +1494,7 @@ lc_kmeans_update_few_kernel(LcDev ix, int l, const float* pts, int pts_cap, floa
 
 // What is stored of node u of level l + 1 except its radius: center (mean of the descendant chunks'
 // centers; the centroid for the unit geometry and for a node without chunks), counts, unit direction (the
-// next level's point); the radius starts at -inf.  Called by one 16-lane group.
+// next level's point); the radius starts at -inf.  Called by one 16-lane group; centroid(mu): this lane's columns of the centroid.
 struct LcNodeArgs {
     const float* cent;       // this level's centroids
     int cent_cap;
@@ -1485,9 +1502,9 @@ struct LcNodeArgs {
     LcPointRows next;        // the next level's points and starting centroids
     __device__ __forceinline__ const float* centroid(int bh, int u) const { return cent + ((size_t)bh * cent_cap + u) * LC_D; }
 };
-template <typename Acc>
+template <typename Acc, typename CentroidF>
 __device__ __forceinline__ void lc_write_node(const LcDev& ix, int b, int bh, int l, int u, int n_chunks, int n_tok,
-                                              const Acc (&sum)[8], const LcNodeArgs& w, const float* centroid) {
+                                              const Acc (&sum)[8], const LcNodeArgs& w, CentroidF centroid) {
     const int sub = threadIdx.x & 15;
     float mu[8];
     if (n_chunks > 0 && w.geometry == LC_GEOMETRY_TOKEN_BALL) {
@@ -1495,7 +1512,7 @@ __device__ __forceinline__ void lc_write_node(const LcDev& ix, int b, int bh, in
 #pragma unroll
         for (int t = 0; t < 8; ++t) mu[t] = (float)(sum[t] * inv);
     } else if (lc_level_count(ix, b, bh, l) > 0) {
-        lc_load8(centroid + 8 * sub, mu);
+        centroid(mu);
     } else {                                                        // (a sequence without chunks: no centroid was started)
 #pragma unroll
         for (int t = 0; t < 8; ++t) mu[t] = (sub == 0 && t == 0) ? 1.f : 0.f;
@@ -1765,7 +1782,539 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, LcNodeArg
 #pragma unroll
         for (int t = 0; t < 8; ++t) sum[t] += __shfl_xor(sum[t], 32);
     }
-    if (!wide || lane < 16) lc_write_node(ix, b, bh, l, c, chunks, tok, sum, w, cs + c * LC_AS_ROW);
+    if (!wide || lane < 16) lc_write_node(ix, b, bh, l, c, chunks, tok, sum, w, [&](float (&mu)[8]) { lc_load8(cs + c * LC_AS_ROW + 8 * sub, mu); });
+}
+
+// ---------------------------------------------------------------------------------
+// A whole clustering into up to LC_AS_RES clusters, and its nodes, in one kernel of several workgroups per (sequence, head)
+// ---------------------------------------------------------------------------------
+// An iteration is two steps, labels and centroids, each of which needs all of the other's results.  As launches of
+// lc_kmeans_assign_res_kernel and lc_kmeans_update_*_kernel each step costs its launch, three dependent round trips and the
+// wait for the slowest of all (sequence, head)s.  Here the workgroups of a (sequence, head) stay, one to a compute unit, and post for each
+// other: labels, then the centroids of the clusters that a label came to or left; all read all labels and those centroids.
+// Every iteration posts into memory of its own that an earlier kernel has filled with LC_UNPOSTED, so each 32-bit word shows by
+// itself whether it has been posted: there is no counter, no order between stores and nothing that a late workgroup could overwrite.
+// Nobody depends on another workgroup: a wavefront that has looked for a word LC_RK_LOOKS times works out what is missing itself --
+// everything follows from the points and the words before -- and posts it (same bits), so every wait ends whatever else occupies the device.
+// Labels, centroids and nodes are the bits of the kernels it stands for: members are added in the same order.
+// What bounds an iteration of about 10 us is single wavefronts' instructions: 3 us a cluster (its members listed, their rows' round trip, the sum and
+// its direction), 2 us 16 points against 160 centroids, and twice a store's way and a look.  512 threads: with 1024 the registers of a sum do not fit.  The
+// heads come first in the grid, so that a head's workgroups, eight apart, share an XCD's L2 for the points' rows.
+// Measured, us a build with two kernels an iteration and now: 8 heads of 2275 points, 143 clusters and two small levels 234 and 203; 64 pairs of up
+// to 1820 in 57 334 and 307; 8 of 820 in 52 121 and 88; 8 of 10.9 K in 5461, then of those in 249 850 and 792.
+#define LC_RK_THREADS 512
+#define LC_RK_WAVES (LC_RK_THREADS / 64)
+#define LC_RK_MAX_N LC_RK_MAX_POINTS
+#define LC_RK_LIST 768                       // members that a wavefront lists before it adds their rows
+#define LC_RK_LOOKS 128                      // times a wavefront looks before it works out what is missing
+#define LC_RK_LOOKS_AGAIN 4                  // and once it has
+#define LC_RK_LOOKS_MOST 1024                // more than a wavefront has words to wait for: the wait ends whatever is in memory
+#define LC_RK_WAIT_ROWS 20                   // 64 clocks each: a wavefront without clusters of its own waits before it looks for centroids,
+#define LC_RK_WAIT_LABELS 20                 // one without points before it looks for labels
+struct LcRounds {
+    float* rows;             // [iters + 1][B][H][k][d] centroids: those that iteration i starts with in plane i, as far as they are new there
+    int* labels;             // [iters][B][H][words] two labels a word
+    int k, words;            // most clusters; words of a (sequence, head), 8 for 16 points
+    int row_bytes, label_bytes;
+    LcUnposted unposted;     // planes 1 and up, and the labels
+};
+struct LcRkWave {
+    union {
+        struct {
+            unsigned long long best[16];             // of a point: similarity (as an integer that orders like it), ~centroid
+            int pair[LC_AS_PAIRS];                   // centroid << 4 | point
+        };
+        unsigned short list[LC_RK_LIST + 8];     // (a place for what is not listed)
+    };
+};
+// similarities of 16 points and 16 centroids, 32 columns a lane (see lc_assign_block)
+__device__ __forceinline__ lc_f32x4_b lc_assign_products(const float4 (&x)[8], const float4 (&m)[8]) {
+    lc_f32x4_b d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        d = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t].x, m[t].x, d, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t].y, m[t].y, d, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t].z, m[t].z, d, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t].w, m[t].w, d, 0, 0, 0);
+    }
+    return d;
+}
+// Labels of 16 points, `n` of them real, by one wavefront; the label of point `lane` in lanes < 16.  Candidates are found as in
+// lc_kmeans_assign_res_kernel: a point with one has its label, the others' candidates are compared in float32, 16 (point,
+// candidate) pairs to a block of products of all 16 points with 16 candidates; beyond LC_AS_PAIRS of them with all centroids.
+// rows: the centroids in bfloat16 (LDS, the last one repeated); centroid(c, q): piece q of four columns of centroid c's float32 row;
+// meanwhile(): called once the bfloat16 similarities have been looked through.
+struct LcTile {
+    lc_v4i half[4];          // A operand in bfloat16
+    float4 full[8];          // and in float32
+};
+template <int NBLK, typename CentroidF, typename MeanwhileF>
+__device__ __forceinline__ int lc_rounds_label(LcRkWave& sh, const unsigned char* rows, const LcTile& p, int n, int k, CentroidF centroid,
+                                               MeanwhileF meanwhile) {
+    const int lane = threadIdx.x & 63, j = lane & 15, kk = lane >> 4;
+    // one or two blocks at a time, the next one's rows read before their products (each with its own reads in front of it took 350 clocks)
+    lc_f32x4_b d[NBLK];
+    constexpr int AT = NBLK <= 4 ? 2 : 1;                           // (registers)
+    lc_v4i m[2][AT][4];
+    auto read = [&](int e) LC_INLINE {
+#pragma unroll
+        for (int q = 0; q < AT; ++q)
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                m[(e / AT) & 1][q][s] = *reinterpret_cast<const lc_v4i*>(rows + (16 * (e + q) + j) * LC_AS_PITCH + 16 * kk + 64 * s);
+    };
+    read(0);
+#pragma unroll
+    for (int e = 0; e < NBLK; e += AT) {
+        if (e + AT < NBLK) read(e + AT);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < AT; ++q) d[e + q] = lc_f32x4_b{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int q = 0; q < AT; ++q)
+                d[e + q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(lc_bf16x8_b, p.half[s]),
+                                                                   __builtin_bit_cast(lc_bf16x8_b, m[(e / AT) & 1][q][s]), d[e + q], 0, 0, 0);
+    }
+    if (lane < 16) sh.best[lane] = 0ull;
+    constexpr int WORDS = (NBLK + 7) / 8;
+    unsigned hit[WORDS][4];                                         // [w][r]: candidates 16 (8 w + e) + j of point 4 kk + r in bit 7 - e
+    int only[4];                                                    // candidates of point 4 kk + r << 16, and the sum of their numbers
+    float top[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        top[r] = d[0][r];
+#pragma unroll
+        for (int e = 1; e < NBLK; ++e) top[r] = fmaxf(top[r], d[e][r]);
+    }
+    // largest of every row (the four rows' steps together: none waits for the one before), less the margin
+#pragma unroll
+    for (int r = 0; r < 4; ++r) top[r] = fmaxf(top[r], lc_dpp<0xB1>(top[r]));
+#pragma unroll
+    for (int r = 0; r < 4; ++r) top[r] = fmaxf(top[r], lc_dpp<0x4E>(top[r]));
+#pragma unroll
+    for (int r = 0; r < 4; ++r) top[r] = fmaxf(top[r], lc_dpp<0x141>(top[r]));
+#pragma unroll
+    for (int r = 0; r < 4; ++r) top[r] = fmaxf(top[r], lc_dpp<0x140>(top[r])) - 2.0f * LC_AS_EPS;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        only[r] = 0;
+#pragma unroll
+        for (int w = 0; w < WORDS; ++w) {
+            unsigned below = 0u;                                    // sign bits, the last block's in bit 0
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (8 * w + e < NBLK) below = __builtin_amdgcn_alignbit(below, __float_as_uint(d[8 * w + e < NBLK ? 8 * w + e : 0][r] - top[r]), 31);
+                else below = below << 1 | 1u;
+            const int real = min(max((k - 128 * w - j + 15) >> 4, 0), 8);       // blocks with a centroid in this column
+            const unsigned h = ~below & (0xff00u >> real) & 0xffu;
+            hit[w][r] = h;
+            const int own = (__popc(h) << 16) + 16 * (8 * w + 8 - __ffs((int)h)) + j;
+            only[r] += h != 0u ? own : 0;                           // (one of several: the number is not used then)
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) only[r] += __builtin_amdgcn_update_dpp(0, only[r], 0xB1, 0xF, 0xF, true);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) only[r] += __builtin_amdgcn_update_dpp(0, only[r], 0x4E, 0xF, 0xF, true);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) only[r] += __builtin_amdgcn_update_dpp(0, only[r], 0x141, 0xF, 0xF, true);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        only[r] += __builtin_amdgcn_update_dpp(0, only[r], 0x140, 0xF, 0xF, true);
+        only[r] = 4 * kk + r < n ? only[r] : 1 << 16;
+    }
+    meanwhile();
+    lc_wave_sync();
+    int n_pairs = 0;
+    bool all = false;                                               // no similarity that compares
+    const bool two = max(max(only[0], only[1]), max(only[2], only[3])) >= 2 << 16, none = min(min(only[0], only[1]), min(only[2], only[3])) < 1 << 16;
+    if (__ballot(two || none) != 0ull) {
+        all = __ballot(none) != 0ull;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int w = 0; w < WORDS; ++w) {
+                unsigned h = only[r] >= 2 << 16 ? hit[w][r] : 0u;
+                for (unsigned long long m; (m = __ballot(h != 0u)) != 0ull;) {
+                    const int at = n_pairs + lc_mbcnt(m), e = 8 - __ffs((int)h);
+                    if (h != 0u && at < LC_AS_PAIRS) sh.pair[at] = (16 * (8 * w + e) + j) << 4 | (4 * kk + r);
+                    h &= h - 1u;
+                    n_pairs += __popcll(m);
+                }
+            }
+        all = all || n_pairs > LC_AS_PAIRS;
+        lc_wave_sync();
+    }
+    const auto take = [&](float v, int c, int i) LC_INLINE {        // (not a number: compares with nothing)
+        const unsigned u = __float_as_uint(v + 0.0f), key = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+        if (v == v) atomicMax(&sh.best[i], (unsigned long long)key << 32 | (unsigned)~c);
+    };
+    for (int q0 = 0; q0 < (all ? 0 : n_pairs); q0 += 16) {
+        const int pair = sh.pair[min(q0 + j, n_pairs - 1)], c = pair >> 4, i = pair & 15;
+        float4 m[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) m[t] = centroid(c, 4 * t + kk);
+        const lc_f32x4_b s = lc_assign_products(p.full, m);         // row i, column j
+        const float v = (i & 2) ? ((i & 1) ? s[3] : s[2]) : ((i & 1) ? s[1] : s[0]);
+        if (kk == (i >> 2)) take(v, c, i);
+    }
+    if (all) {
+        for (int c0 = 0; c0 < k; c0 += 16) {
+            const int c = min(c0 + j, k - 1);
+            float4 m[8];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) m[t] = centroid(c, 4 * t + kk);
+            const lc_f32x4_b s = lc_assign_products(p.full, m);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) take(s[r], c, 4 * kk + r);
+        }
+    }
+    lc_wave_sync();
+    const int r = lane & 3, from = (lane & 12) << 2;                // point `lane`: row r of lanes 16 (lane / 4) + (0..15)
+    const int o0 = __shfl(only[0], from), o1 = __shfl(only[1], from), o2 = __shfl(only[2], from), o3 = __shfl(only[3], from);
+    const int o = (r & 2) ? ((r & 1) ? o3 : o2) : ((r & 1) ? o1 : o0);
+    const unsigned long long b = sh.best[lane & 15];
+    lc_wave_sync();
+    if (!all && o >> 16 == 1) return o & 0xffff;
+    const int c = b != 0ull ? (int)~(unsigned)b : 0;
+    return c < k ? c : 0;
+}
+// Exchanges between the rows of 16 lanes: afterwards `a` holds the even rows' a and b, `b` the odd rows' (rows 0, 1 and 2, 3), and the
+// same for the wavefront's halves.
+__device__ __forceinline__ void lc_swap16(float& a, float& b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void lc_swap32(float& a, float& b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void lc_swap16(double& a, double& b) {
+    const unsigned long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    a = __longlong_as_double((long long)((unsigned long long)hi[0] << 32 | lo[0]));
+    b = __longlong_as_double((long long)((unsigned long long)hi[1] << 32 | lo[1]));
+}
+__device__ __forceinline__ void lc_swap32(double& a, double& b) {
+    const unsigned long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    a = __longlong_as_double((long long)((unsigned long long)hi[0] << 32 | lo[0]));
+    b = __longlong_as_double((long long)((unsigned long long)hi[1] << 32 | lo[1]));
+}
+// Sum of the rows of a cluster's members, by one wavefront, in the order of lc_cluster_sums: the members, ascending, are dealt to 16
+// partial sums in turn (starting over every LC_MEM_WIN points), and the partial sums are added up in turn.  Group g of 16 lanes keeps the
+// partials 4 e + g.  members(b): this lane's word of the 64 blocks of 64 points from block b on, a bit per member; row(i, x): columns
+// [8 sub, 8 sub + 8) of point i's row, returns its weight, zeros for i < 0; visit(i) once per member.  Every group gets the sums.
+template <typename Acc, typename MembersF, typename RowF, typename VisitF>
+__device__ __forceinline__ void lc_rounds_sum(int N, unsigned short* list, MembersF members, RowF row, VisitF visit, Acc (&sum)[8]) {
+    constexpr int U = sizeof(Acc) == 4 ? 2 : 1;                     // rows of a partial in flight
+    static_assert(LC_MEM_WIN == 64 * 64 && LC_RK_LIST % 16 == 0, "a word per lane; a partial is a place in the list modulo 16");
+    const int lane = threadIdx.x & 63, g4 = lane >> 4;
+    Acc acc[4][8];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int t = 0; t < 8; ++t) acc[e][t] = 0;
+    for (int base = 0; base < N; base += LC_MEM_WIN) {
+        const unsigned long long word = members(base >> 6);
+        const int n = __popcll(word), inc = lc_wave_scan_incl(n), total = lc_readlane(inc, 63);
+        for (int r0 = 0; r0 < total; r0 += LC_RK_LIST) {
+            lc_wave_sync();                                         // (the list's place had another use)
+            unsigned lo = (unsigned)word, hi = (unsigned)(word >> 32);
+            for (int a = inc - n - r0, z = a + __popc(lo); (lo | hi) != 0u; lo &= lo - 1u, hi &= hi - 1u, ++a, ++z) {
+                list[lo != 0u && (unsigned)a < LC_RK_LIST ? a : LC_RK_LIST] = (unsigned short)(base + 64 * lane + __ffs((int)lo) - 1);
+                list[hi != 0u && (unsigned)z < LC_RK_LIST ? z : LC_RK_LIST] = (unsigned short)(base + 64 * lane + __ffs((int)hi) + 31);
+            }
+            const int m = min(total - r0, LC_RK_LIST);
+            lc_wave_sync();
+            for (int t0 = 0; t0 < m; t0 += 16 * U) {
+                float x[4 * U][8];
+                int w[4 * U];
+#pragma unroll
+                for (int e = 0; e < 4 * U; ++e) {
+                    const int t = t0 + 4 * e + g4;
+                    const int i = list[min(t, m - 1)];
+                    w[e] = row(t < m ? i : -1, x[e]);
+                }
+#pragma unroll
+                for (int e = 0; e < 4 * U; ++e) lc_add_row(acc[e & 3], x[e], w[e]);
+            }
+            for (int t = lane; t < m; t += 64) visit((int)list[t]);
+        }
+    }
+    // two columns a lane of all 16 partials, added up in turn, then eight columns again
+    Acc s2[2] = {0, 0};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) lc_swap32(acc[e][t], acc[e][t + 4]);     // [t]: groups 0, 1; [t + 4]: groups 2, 3; columns t + 4 (g4 / 2)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            lc_swap16(acc[e][t], acc[e][t + 2]);                             // groups 0 and 1; columns t + 2 g4
+            lc_swap16(acc[e][t + 4], acc[e][t + 6]);                         // groups 2 and 3
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            s2[t] += acc[e][t];
+            s2[t] += acc[e][t + 2];
+            s2[t] += acc[e][t + 4];
+            s2[t] += acc[e][t + 6];
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t) { sum[t] = s2[t]; sum[t + 2] = s2[t]; lc_swap16(sum[t], sum[t + 2]); }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) { sum[t + 4] = sum[t]; lc_swap32(sum[t], sum[t + 4]); }
+}
+template <int NBLK, bool NODES>
+__global__ void __launch_bounds__(LC_RK_THREADS)
+lc_kmeans_rounds_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16, int pts_cap, LcNodeArgs w, int iters, LcRounds rd) {
+    lc_fetch_args<sizeof(LcDev) + 32 + sizeof(LcNodeArgs) + sizeof(LcRounds)>();
+    __shared__ __attribute__((aligned(16))) unsigned char rows[16 * NBLK * LC_AS_PITCH];
+    constexpr bool FULL = NBLK <= 10;             // the float32 rows find room as well, piece q of row c at q ^ (c mod 32)
+    __shared__ lc_v4i full[FULL ? 16 * NBLK * 32 : 1];
+    __shared__ lc_v4i lab[LC_RK_MAX_N / 8];
+    __shared__ __attribute__((aligned(16))) LcRkWave own_sh[LC_RK_WAVES];
+    __shared__ int fresh[LC_AS_RES];              // iteration that starts with a new centroid of this cluster
+    __shared__ int plane[LC_AS_RES];              // plane of the centroid that is in `rows`
+    __shared__ int moved;                         // last iteration that moved a point
+    constexpr int BITS = NBLK <= 10 && NBLK > 4 ? 512 : 2048;
+    __shared__ unsigned long long bits[BITS];     // [mine][blocks] members of this workgroup's clusters, a bit per point
+    __shared__ signed char mine_of[LC_AS_RES];    // which of this workgroup's clusters this is, or -1
+    const int h = blockIdx.x, b = blockIdx.y;
+    const int bh = b * ix.H + h, BH = ix.B * ix.H;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int j = lane & 15, kk = lane >> 4, sub = j;
+    const int first = blockIdx.z + gridDim.z * wave, step = gridDim.z * LC_RK_WAVES;     // this wavefront's tiles of 16 points, and its clusters
+    const int N = min(min(lc_level_count(ix, b, bh, l), LC_RK_MAX_N), 2 * rd.words);
+    const int k = min(min(ix.nlev[b * LC_MAX_LEVELS + l + 1], 16 * NBLK), rd.k);
+    const int tiles = (N + 15) >> 4, pieces = 2 * tiles, blocks = (N + 63) >> 6;
+    const int n_mine = ((int)blockIdx.z < k ? k - 1 - (int)blockIdx.z : -1) / (int)gridDim.z + 1;
+    const bool keep_bits = n_mine <= 127 && n_mine * blocks <= BITS;
+    LcRkWave& sh = own_sh[wave];
+    const float* const P = pts + (size_t)bh * pts_cap * LC_D;
+    const __amdgpu_buffer_rsrc_t points_r = lc_buffer(P, N * LC_D * 4);
+    const __amdgpu_buffer_rsrc_t rows_r = lc_buffer(rd.rows, rd.row_bytes), labels_r = lc_buffer(rd.labels, rd.label_bytes);
+    auto row_at = [&](int p, int c) LC_INLINE { return ((p * BH + bh) * rd.k + c) * (LC_D * 4); };
+    auto label_at = [&](int it, int word) LC_INLINE { return ((it * BH + bh) * rd.words + word) * 4; };
+    auto load_half = [&](lc_v4i (&half)[4], int t) LC_INLINE {
+        const uint16_t* const row = pts16 + ((size_t)bh * pts_cap + min(16 * t + j, N - 1)) * LC_D + 8 * kk;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) half[s] = *reinterpret_cast<const lc_v4i*>(row + 32 * s);
+    };
+    // this lane's word of the blocks from b0 on (see lc_rounds_sum): kept as labels change for my own clusters, from the labels for others
+    auto members = [&](int own, int c, int b0) LC_INLINE {
+        if (own >= 0) return b0 + lane < blocks ? bits[own * blocks + min(b0 + lane, blocks - 1)] : 0ull;
+        unsigned long long word = 0ull;
+        for (int i = 0; i < min(blocks - b0, 64); ++i) {
+            const unsigned long long m = __ballot(reinterpret_cast<const unsigned short*>(lab)[64 * (b0 + i) + lane] == c);
+            word = lane == i ? m : word;
+        }
+        return word;
+    };
+    auto centroid = [&](int c, int q) LC_INLINE {
+        if constexpr (FULL) return __builtin_bit_cast(float4, full[32 * c + (q ^ (c & 31))]);
+        else return lc_load_agent4(rows_r, row_at(plane[c], c) + 16 * q);
+    };
+    constexpr int PIECES = LC_RK_MAX_N / 8 / LC_RK_THREADS;         // pieces of labels of a thread
+#pragma unroll
+    for (int e = 0; e < PIECES; ++e) lab[tid + e * LC_RK_THREADS] = lc_v4i{-1, -1, -1, -1};
+    if (tid < LC_AS_RES) { fresh[tid] = 0; plane[tid] = 0; }
+    if (tid == 0) moved = -1;
+    if (keep_bits)
+        for (int i = tid; i < n_mine * blocks; i += LC_RK_THREADS) bits[i] = 0ull;
+    if (tid < LC_AS_RES) mine_of[tid] = (signed char)(keep_bits && tid < k && tid % (int)gridDim.z == (int)blockIdx.z ? tid / (int)gridDim.z : -1);
+    lc_barrier_lds();
+    int patience = LC_RK_LOOKS;
+    for (int it = 0; N > 0; ++it) {
+        // ---- the centroids of my clusters that the last iteration changed; then everybody's, into LDS
+        constexpr int R = 8 * NBLK / LC_RK_WAVES;                   // rows of a lane: half a wavefront to a row
+        unsigned open = 0u;
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const int c = 2 * (wave + LC_RK_WAVES * i) + (lane >> 5);
+            open |= it < iters && c < k && fresh[min(c, LC_AS_RES - 1)] == it ? 1u << i : 0u;
+        }
+        int looks = 0;
+        lc_v4i next[4];                                             // the next tile's rows in bfloat16
+        if (it > 0 && first >= k) __builtin_amdgcn_s_sleep(LC_RK_WAIT_ROWS);
+        for (int own = it == 0 ? k : first, at = wave;;) {
+            int c, mine = -1;
+            if (own < k) {
+                c = own;
+                mine = keep_bits ? at : -1;
+                own += step;
+                at += LC_RK_WAVES;
+                if (__builtin_amdgcn_readfirstlane(fresh[c]) != it) continue;
+            } else {
+                if (looks == 0) load_half(next, min(first, tiles - 1));
+                lc_v4i v[R];
+                asm volatile("" ::: "memory");                      // every look is a load of its own
+#pragma unroll
+                for (int i = 0; i < R; ++i) {
+                    const int row = 2 * (wave + LC_RK_WAVES * i) + (lane >> 5);
+                    v[i] = __builtin_amdgcn_raw_buffer_load_b128(rows_r, (open >> i) & 1u ? row_at(it, row) + 16 * (lane & 31) : 0x7ffffff0, 0, 16);
+                }
+#pragma unroll
+                for (int i = 0; i < R; ++i) {
+                    const int row = 2 * (wave + LC_RK_WAVES * i) + (lane >> 5);
+                    const bool there = it == 0 || (v[i].x != LC_UNPOSTED && v[i].y != LC_UNPOSTED && v[i].z != LC_UNPOSTED && v[i].w != LC_UNPOSTED);
+                    if (((open >> i) & 1u) && there) {
+                        const int x = v[i].x, y = v[i].y, z = v[i].z, u = v[i].w;
+                        *reinterpret_cast<uint2*>(rows + row * LC_AS_PITCH + 8 * (lane & 31)) =
+                            make_uint2(lc_f32_to_bf16_bits(__int_as_float(x)) | (lc_f32_to_bf16_bits(__int_as_float(y)) << 16),
+                                       lc_f32_to_bf16_bits(__int_as_float(z)) | (lc_f32_to_bf16_bits(__int_as_float(u)) << 16));
+                        if (row == k - 1)                           // (absent centroids repeat the last)
+                            for (int a = k; a < 16 * NBLK; ++a)
+                                *reinterpret_cast<uint2*>(rows + a * LC_AS_PITCH + 8 * (lane & 31)) = *reinterpret_cast<const uint2*>(rows + row * LC_AS_PITCH + 8 * (lane & 31));
+                        if constexpr (FULL) full[32 * row + ((lane & 31) ^ (row & 31))] = v[i];
+                        open &= ~(1u << i);
+                        if ((lane & 31) == 0) plane[row] = it;
+                    }
+                }
+                if (__ballot(open != 0u) == 0ull || looks == LC_RK_LOOKS_MOST) break;
+                if (++looks <= patience) { __builtin_amdgcn_s_sleep(1); continue; }
+                patience = LC_RK_LOOKS_AGAIN;
+                const int who = __ffsll((long long)__ballot(open != 0u)) - 1;
+                c = 2 * (wave + LC_RK_WAVES * (__ffs(lc_readlane((int)open, who)) - 1)) + (who >> 5);
+            }
+            float sum[8];
+            lc_rounds_sum<float>(N, sh.list, [&](int b0) LC_INLINE { return members(mine, c, b0); },
+                                 [&](int i, float (&x)[8]) LC_INLINE {        // (no member: past the end, which reads as zeros)
+                                     const int o = i >= 0 ? i * (LC_D * 4) + 32 * sub : 0x7fffffe0;
+                                     const float4 a = lc_buf_load_f32x4(points_r, o), z = lc_buf_load_f32x4(points_r, o + 16);
+                                     x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
+                                     x[4] = z.x; x[5] = z.y; x[6] = z.z; x[7] = z.w;
+                                     return 1;
+                                 }, [](int) {}, sum);
+            float n2 = 0.f;
+#pragma unroll
+            for (int t = 0; t < 8; ++t) n2 = fmaf(sum[t], sum[t], n2);
+            n2 = lc_sum16(n2);
+            const float inv = 1.0f / sqrtf(n2);
+#pragma unroll
+            for (int t = 0; t < 8; ++t) sum[t] *= inv;
+            float4 half = kk == 0 ? make_float4(sum[0], sum[1], sum[2], sum[3]) : make_float4(sum[4], sum[5], sum[6], sum[7]);
+            const int o = 32 * sub + 16 * (kk & 1);
+            if (!(n2 > 0.f)) half = lc_load_agent4(rows_r, row_at(plane[c], c) + o);      // no members, or none in sum: the centroid stands
+            auto posted = [](float f) LC_INLINE { return __float_as_int(f) == LC_UNPOSTED ? __int_as_float(0x7fc00000) : f; };
+            half = make_float4(posted(half.x), posted(half.y), posted(half.z), posted(half.w));
+            if (kk < 2) lc_store_agent4(rows_r, row_at(it, c) + o, half);
+            if (own >= k) __builtin_amdgcn_s_waitcnt(0);            // (my own posts are there when I look)
+        }
+        if (it == iters) break;
+        lc_barrier_lds();
+        // ---- the labels of my points, then everybody's
+        lc_v4i v[PIECES];
+        bool wait[PIECES];
+#pragma unroll
+        for (int e = 0; e < PIECES; ++e) { v[e] = lc_v4i{0, 0, 0, 0}; wait[e] = tid + e * LC_RK_THREADS < pieces; }
+        looks = 0;
+        if (first >= tiles) __builtin_amdgcn_s_sleep(LC_RK_WAIT_LABELS);
+        for (int own = first;;) {
+            int t;
+            if (own < tiles) {
+                t = own;
+                own += step;
+            } else {
+                asm volatile("" ::: "memory");
+#pragma unroll
+                for (int e = 0; e < PIECES; ++e)
+                    if (wait[e]) v[e] = __builtin_amdgcn_raw_buffer_load_b128(labels_r, label_at(it, 4 * (tid + e * LC_RK_THREADS)), 0, 16);
+                bool any = false;
+                int missing = 0;
+#pragma unroll
+                for (int e = PIECES - 1; e >= 0; --e) {
+                    wait[e] = wait[e] && (v[e].x == LC_UNPOSTED || v[e].y == LC_UNPOSTED || v[e].z == LC_UNPOSTED || v[e].w == LC_UNPOSTED);
+                    any = any || wait[e];
+                    missing = wait[e] ? tid + e * LC_RK_THREADS : missing;
+                }
+                if (__ballot(any) == 0ull || looks == LC_RK_LOOKS_MOST) break;
+                if (++looks <= patience) { __builtin_amdgcn_s_sleep(1); continue; }
+                patience = LC_RK_LOOKS_AGAIN;
+                t = lc_readlane(missing, __ffsll((long long)__ballot(any)) - 1) >> 1;
+            }
+            const bool help = looks > 0;
+            if (help) load_half(next, t);
+            LcTile tile;                                            // (its float32 rows come while the bfloat16 ones are multiplied)
+            const float* const row = P + (size_t)min(16 * t + j, N - 1) * LC_D + 4 * kk;
+#pragma unroll
+            for (int s = 0; s < 8; ++s) tile.full[s] = *reinterpret_cast<const float4*>(row + 16 * s);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) tile.half[s] = next[s];
+            const int label = lc_rounds_label<NBLK>(sh, rows, tile, min(N - 16 * t, 16), k, centroid,
+                                                    [&]() LC_INLINE { load_half(next, min(own, tiles - 1)); });
+            const int mine = 16 * t + j < N ? label : 0xfffe;       // (no label behind the last point)
+            const int two = __shfl(mine, 2 * (lane & 7)) | (__shfl(mine, 2 * (lane & 7) + 1) << 16);
+            if (lane < 8) __builtin_amdgcn_raw_buffer_store_b32(two, labels_r, label_at(it, 8 * t + lane), 0, 16);
+
+            if (help) __builtin_amdgcn_s_waitcnt(0);
+        }
+        bool any = false;
+#pragma unroll
+        for (int e = 0; e < PIECES; ++e) {
+            const int piece = tid + e * LC_RK_THREADS;
+            if (piece >= pieces) continue;
+            const lc_v4i old = lab[piece];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (v[e][q] != old[q]) {
+                    any = true;
+#pragma unroll
+                    for (int s = 0; s < 32; s += 16) {
+                        const int a = ((unsigned)v[e][q] >> s) & 0xffff, z = ((unsigned)old[q] >> s) & 0xffff;
+                        if (a == z) continue;
+                        const int at = 8 * piece + 2 * q + s / 16;
+                        if (a < LC_AS_RES) {
+                            fresh[a] = it + 1;
+                            if (mine_of[a] >= 0) atomicOr(reinterpret_cast<unsigned*>(bits + mine_of[a] * blocks) + (at >> 5), 1u << (at & 31));
+                        }
+                        if (z < LC_AS_RES) {
+                            fresh[z] = it + 1;
+                            if (mine_of[z] >= 0) atomicAnd(reinterpret_cast<unsigned*>(bits + mine_of[z] * blocks) + (at >> 5), ~(1u << (at & 31)));
+                        }
+                    }
+                }
+            lab[piece] = v[e];
+        }
+        if (any) moved = it;
+        lc_barrier_lds();
+        // An iteration that moves no point is a fixed point: every later one would repeat it.
+        if (__builtin_amdgcn_readfirstlane(moved) != it) break;
+    }
+    // ---- the labels of my points for good, and my nodes
+    for (int t = first; t < tiles; t += step)
+        if (lane < 16 && 16 * t + lane < N)
+            ix.parent[l][(size_t)bh * ix.cap[l] + 16 * t + lane] = reinterpret_cast<const unsigned short*>(lab)[16 * t + lane];
+    using Acc = typename std::conditional<NODES, double, float>::type;
+    const LcMembers<NODES> m(ix, b, bh, l);
+    for (int c = first, own = wave; c < k; c += step, own += LC_RK_WAVES) {
+        Acc sum[8];
+        int tok = 0, chunks = 0;
+        lc_rounds_sum<Acc>(N, sh.list, [&](int b0) LC_INLINE { return members(keep_bits ? own : -1, c, b0); },
+                           [&](int i, float (&x)[8]) LC_INLINE {
+                               const int n = m.row(max(i, 0), 8 * sub, x);
+#pragma unroll
+                               for (int t = 0; t < 8; ++t) x[t] = i >= 0 ? x[t] : 0.f;
+                               return i >= 0 ? n : 0;
+                           },
+                           [&](int i) LC_INLINE { tok += m.ntok[i]; chunks += m.chunks(i); }, sum);
+        tok = lc_wave_sum_i(tok);
+        chunks = lc_wave_sum_i(chunks);
+        const int at = row_at(fresh[c], c) + 32 * sub;
+        if (lane < 16)
+            lc_write_node(ix, b, bh, l, c, chunks, tok, sum, w, [&](float (&mu)[8]) LC_INLINE {
+                const float4 a = lc_load_agent4(rows_r, at), z = lc_load_agent4(rows_r, at + 16);
+                mu[0] = a.x; mu[1] = a.y; mu[2] = a.z; mu[3] = a.w;
+                mu[4] = z.x; mu[5] = z.y; mu[6] = z.z; mu[7] = z.w;
+            });
+    }
 }
 
 // Centers of a level of many small nodes (LC_UPD_FEW members or fewer on average): a workgroup lists the
@@ -1796,7 +2345,7 @@ lc_center_few_kernel(LcDev ix, int l, LcNodeArgs w, int per) {
                 for (int j = sub; j < m.n; j += 16)
                     if (m.label[j] == u) count(j);
             }
-            lc_write_node(ix, b, bh, l, u, lc_sum16_i(chunks), lc_sum16_i(tok), sum, w, w.centroid(bh, u));
+            lc_write_node(ix, b, bh, l, u, lc_sum16_i(chunks), lc_sum16_i(tok), sum, w, [&](float (&mu)[8]) { lc_load8(w.centroid(bh, u) + 8 * sub, mu); });
         });
 }
 
@@ -1830,7 +2379,7 @@ lc_center_kernel(LcDev ix, int l, LcNodeArgs w) {
     if (tid < 16) {
         int n_tok = 0, n_chunks = 0;
         for (int v = 0; v < NT / 64; ++v) { n_tok += tok_sh[v]; n_chunks += chunk_sh[v]; }
-        lc_write_node(ix, b, bh, l, u, n_chunks, n_tok, sum, w, w.centroid(bh, u));
+        lc_write_node(ix, b, bh, l, u, n_chunks, n_tok, sum, w, [&](float (&mu)[8]) { lc_load8(w.centroid(bh, u) + 8 * tid, mu); });
     }
 }
 
@@ -1916,6 +2465,46 @@ lc_radius_kernel(LcDev ix) {
     }
 }
 
+namespace {
+
+// most nodes that a sequence of the batch has at level l (host mirror)
+int most_nodes(const lc_index* idx, int l) {
+    int n = 0;
+    for (int b = 0; b < idx->B; ++b) n = idx->N[b * LC_MAX_LEVELS + l] > n ? idx->N[b * LC_MAX_LEVELS + l] : n;
+    return n;
+}
+bool small_level(int n, int k) { return n <= LC_KS_MAX_N && k <= LC_KS_MAX_K; }
+
+// Workgroups of lc_kmeans_rounds_kernel for a (sequence, head): all of them run at the same time, one to a compute unit.  Beyond 64 they
+// gain nothing (2 heads x 8000 points under 250 nodes, whole builds, us by workgroups a head: 16 360, 32 259, 64 224, 128 216; x 2000 under 250:
+// 67.5, 64.6, 64.1, 64.4).
+int rounds_share(long long BH) { return (int)(BH * 64 <= LC_COMPUTE_UNITS ? 64 : LC_COMPUTE_UNITS / BH); }
+
+// Whether a level of n points and k clusters is clustered by lc_kmeans_rounds_kernel, and what that posts, in the workspace's place for it.
+// Measured as whole builds of two levels over 1 to 128 pairs, 240 to 8000 points and 4 to 128 members a cluster, the time with it in parts of that
+// with two kernels an iteration (which have no members' bits for over 4096 points): 8 pairs 0.40 to 0.95, 0.60 to 0.98 from 4000 points on; 24
+// 0.48 to 0.99; 48 0.56 to 0.98; 72 0.58 to 0.99; 128 0.63 to 0.98.  Not so, and left to the two kernels: few pairs with more than 100
+// members a cluster, one wavefront's work (1.01 to 1.05); pairs that leave a fifth of the compute units without a workgroup and have more than 256 points
+// to each (96 pairs of 1000 to 4000 points 0.92 to 1.18; of 500 0.75 to 1.02); more than 100 clusters to a workgroup (128 pairs of 1000 in 250: 1.04).
+bool lay_out_rounds(const LcWs& ws, long long BH, int n, int k, int iters, LcRounds* r) {
+    if (iters < 1 || iters > LC_RK_MAX_ITERS || n > LC_RK_MAX_N || BH > LC_RK_MAX_PAIRS) return false;
+    const int share = rounds_share(BH);
+    if (n <= 4096 && ((BH < 24 && n > 100 * k) || (BH > 4 && BH * share * 5 < LC_COMPUTE_UNITS * 4 && n > 256 * share) || k > 100 * share)) return false;
+    r->k = k;
+    r->words = (n + 15) / 16 * 8;
+    const long long plane = BH * k * LC_D * 4, row_bytes = (iters + 1) * plane, label_bytes = iters * BH * r->words * 4;
+    if (row_bytes + label_bytes > (long long)ws.rounds_bytes || row_bytes >= (1ll << 31) - 16) return false;
+    r->rows = ws.rounds;
+    r->labels = reinterpret_cast<int*>(reinterpret_cast<char*>(ws.rounds) + row_bytes);
+    r->row_bytes = (int)row_bytes;
+    r->label_bytes = (int)label_bytes;
+    r->unposted.at = reinterpret_cast<lc_v4i*>(reinterpret_cast<char*>(ws.rounds) + plane);
+    r->unposted.n = (int)((row_bytes + label_bytes - plane) / 16);
+    return true;
+}
+
+}  // namespace
+
 // K == nullptr: keep the chunk nodes (level 0) as they are and rebuild only the levels above them.
 int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const int64_t ks[3],
                     int max_M, hipStream_t stream) {
@@ -1929,13 +2518,24 @@ int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const i
     // points and centroids of the level being clustered, and of the next one (whose rows are written while
     // this one's centroids are still read)
     LcPointRows cur{ws.dirs, ws.dirs16, ix.cap[0], L > 1 ? ws.cent[0] : nullptr, ws.cent16[0], ix.cap[1]};
+    // The level that lc_kmeans_rounds_kernel clusters, if there is one: the first that is neither small nor of too many clusters or points.
+    int rounds_level = -1;
+    LcRounds rounds{nullptr, nullptr, 0, 0, 0, 0, {nullptr, 0}};
+    for (int l = 0; l + 1 < L && rounds_level < 0; ++l) {
+        const int n = most_nodes(idx, l), k = most_nodes(idx, l + 1);
+        if (n > 0 && k <= LC_AS_RES && !small_level(n, k)) {
+            if (lay_out_rounds(ws, BH, n, k, iters, &rounds)) rounds_level = l;
+            break;
+        }
+    }
+    if (rounds_level == 0) { cur.cent = rounds.rows; cur.cent_cap = rounds.k; }
     if (max_M > 0 && K != nullptr) {
         const bool near = ks[2] >= LC_D && ks[2] * 2 * (4 * LC_POOLW_KEEP) < (1ll << 31);     // (see lc_pool_batch)
         hipLaunchKernelGGL(near ? lc_pool_kernel<true> : lc_pool_kernel<false>, dim3(max_M, H, B), dim3(64), 0, stream, ix, K,
-                           (long long)ks[0], (long long)ks[1], (long long)ks[2], geometry, cur, ws.kflags);
+                           (long long)ks[0], (long long)ks[1], (long long)ks[2], geometry, cur, ws.kflags, rounds.unposted);
         LC_HIP_CHECK(hipGetLastError());
     } else if (max_M > 0) {
-        hipLaunchKernelGGL(lc_dirs_kernel, dim3((max_M + LC_BG - 1) / LC_BG, H, B), dim3(LC_BT), 0, stream, ix, cur, ws.kflags);
+        hipLaunchKernelGGL(lc_dirs_kernel, dim3((max_M + LC_BG - 1) / LC_BG, H, B), dim3(LC_BT), 0, stream, ix, cur, ws.kflags, rounds.unposted);
         LC_HIP_CHECK(hipGetLastError());
     }
     for (int l = 0; l + 1 < L; ++l) {
@@ -1944,13 +2544,9 @@ int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const i
             const bool even = (l & 1) == 0;                          // level 0's points give way to level 2's
             next = LcPointRows{even ? ws.next_pts : ws.dirs, even ? ws.next_pts16 : ws.dirs16, even ? ix.cap[1] : ix.cap[0],
                                ws.cent[even ? 1 : 0], ws.cent16[even ? 1 : 0], ix.cap[1]};
+            if (rounds_level == l + 1) { next.cent = rounds.rows; next.cent_cap = rounds.k; }
         }
-        // per-level maxima over the batch (host mirror)
-        int maxN = 0, maxK = 0;
-        for (int b = 0; b < B; ++b) {
-            maxN = idx->N[b * LC_MAX_LEVELS + l] > maxN ? idx->N[b * LC_MAX_LEVELS + l] : maxN;
-            maxK = idx->N[b * LC_MAX_LEVELS + l + 1] > maxK ? idx->N[b * LC_MAX_LEVELS + l + 1] : maxK;
-        }
+        const int maxN = most_nodes(idx, l), maxK = most_nodes(idx, l + 1);
         // Several clusters per workgroup where they are small, or where one each would be thousands of workgroups that all read every
         // label.  Clusterings with one and with several, us by members a cluster (clusters in all): 8 heads x 3000 points 206 and 201 at 9 (2672),
         // 252 and 260 at 11 (2184); x 6000 483 and 419 at 15 (3200), 478 and 480 at 17 (2824), 504 and 519 at 19 (2528); x 10.9K 1022 and 766 at 19 (4592), 916
@@ -1963,7 +2559,23 @@ int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const i
         const int per = (maxK + LC_BG - 1) / LC_BG * BH > 1024 ? LC_UB_MAX : LC_BG;
         const dim3 per_grid((maxK + per - 1) / per, H, B);
         const LcNodeArgs w{cur.cent, cur.cent_cap, geometry, next};
-        if (maxN > 0 && maxN <= LC_KS_MAX_N && maxK <= LC_KS_MAX_K) {  // the whole level in one kernel
+        if (l == rounds_level) {                                       // a clustering in one kernel of several workgroups
+            const int share = rounds_share(BH);
+            auto run = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3(H, B, share), dim3(LC_RK_THREADS), 0, stream, ix, l, (const float*)cur.pts,
+                                   (const uint16_t*)cur.pts16, cur.cap, w, iters, rounds);
+            };
+            if (l == 0 && maxK <= 64) run(&lc_kmeans_rounds_kernel<4, false>);
+            else if (l == 0 && maxK <= 160) run(&lc_kmeans_rounds_kernel<10, false>);
+            else if (l == 0) run(&lc_kmeans_rounds_kernel<16, false>);
+            else if (maxK <= 64) run(&lc_kmeans_rounds_kernel<4, true>);
+            else if (maxK <= 160) run(&lc_kmeans_rounds_kernel<10, true>);
+            else run(&lc_kmeans_rounds_kernel<16, true>);
+            LC_HIP_CHECK(hipGetLastError());
+            cur = next;
+            continue;
+        }
+        if (maxN > 0 && small_level(maxN, maxK)) {                     // the whole level in one workgroup per (sequence, head)
             const size_t lds = lc_kmeans_small_lds(maxN, maxK);
             const auto kernel = l == 0 ? &lc_kmeans_small_kernel<false> : &lc_kmeans_small_kernel<true>;
             LC_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));

@@ -71,8 +71,17 @@ struct LcWs {
     float* cent[2];      // [B][H][cap1][d] centroids of the level being clustered, start of the next level's
     uint16_t* cent16[2];
     int* kflags;         // [level][B][H][LC_KM_FLAGS] "iteration t of the k-means moved a point" (tiled kernels only)
+    float* rounds;       // what the workgroups of a clustering post for each other (lc_kmeans_rounds_kernel), behind `total`
+    size_t rounds_bytes; // of it in this workspace; a smaller one does without
     size_t total;
 };
+// Clusterings in one kernel: most (sequence, head)s, iterations and points; most clusters.
+#define LC_RK_MAX_PAIRS 128
+#define LC_RK_MAX_SHARE 64
+#define LC_RK_MAX_ITERS 16
+#define LC_RK_MAX_POINTS 8192
+#define LC_RK_MAX_CLUSTERS 256
+size_t lc_rounds_bytes(const lc_config* cfg, int B, int H);
 // with_build = false leaves out the build scratch (directions, centroids): what a decode step needs.
 size_t lc_layout_ws(const lc_config* cfg, int B, int H_q, int H, int d, int splits, void* base, LcWs* ws,
                     bool with_build = true);

@@ -1,0 +1,74 @@
+"""The clustering in one kernel of several workgroups per (sequence, head) against the two kernels an iteration that a workspace
+without room for its posts falls back to: the same bits, at the sizes where it can go wrong.  And two such builds at the same time,
+whose workgroups cannot all be resident."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+class Build:
+    def __init__(self, H, chunks, F, iters=10, levels=2, seed=0, same=0, **config):
+        import torch
+        from paper_2603_08453_amd import binding as lc
+        self.lc, self.H, self.B = lc, H, len(chunks)
+        r = np.random.default_rng(seed)
+        self.bounds = [np.concatenate([[0], np.cumsum(r.integers(1, 4, size=m))]).astype(np.int32) for m in chunks]
+        T = max(int(b[-1]) for b in self.bounds)
+        g = torch.Generator(device="cuda")
+        g.manual_seed(seed)
+        self.K = torch.randn((self.B, H, max(T, 1), 128), generator=g, device="cuda").to(torch.bfloat16)
+        for b, bd in enumerate(self.bounds):
+            if same:                                         # the first chunks are alike: more near centroids than are listed
+                self.K[b, :, : bd[min(same, len(bd) - 1)]] = self.K[b, :, :1].clone()
+        config = dict(levels=levels, fanout=F, max_chunks=max(chunks), max_tokens=max(T, 1), **config)
+        self.cfg = lc.lc_config_default(kmeans_iters=iters, **config)
+        many = lc.lc_config_default(kmeans_iters=17, **config)   # more iterations than are posted: the workspace without room for them
+        self.room = lc.lc_workspace_bytes(self.cfg, self.B, H, H), lc.lc_workspace_bytes(many, self.B, H, H)
+        assert self.room[0] > self.room[1]
+        self.ib = torch.zeros(lc.lc_index_bytes(self.cfg, self.B, H), dtype=torch.uint8, device="cuda")
+        self.ws = torch.full((self.room[0],), 0xA5, dtype=torch.uint8, device="cuda")
+
+    def run(self, posts=True):
+        ws = self.ws if posts else self.ws[: self.room[1]]
+        self.idx = self.lc.lc_build_index(self.cfg, self.K, [int(b[-1]) for b in self.bounds], self.bounds, self.ib, ws)
+
+    def blob(self):
+        return np.frombuffer(self.lc.lc_index_export(self.idx), dtype=np.uint8).copy()
+
+
+@pytest.mark.parametrize("H,chunks,F,config", [
+    (1, [225], 15, {}), (8, [225, 1, 16, 17], 4, {}), (2, [1024, 1023], 16, {}), (2, [1025, 3], 16, {}),          # 64 clusters and 65
+    (1, [2560], 16, {}), (1, [2561, 7], 16, {}), (4, [4096], 16, {}), (1, [255], 1, {}),                          # 160 and 161; 256
+    (3, [500, 499, 64], 8, {"iters": 1}), (3, [513, 65], 8, {"iters": 2}), (2, [700], 10, {"iters": 16}),
+    (8, [4097], 17, {}), (2, [8192, 15], 32, {}), (8, [5300, 700], 25, {}),                                       # more than one window of points
+    (128, [300], 8, {}), (1, [6000], 2000, {}), (5, [900], 9, {}), (11, [450, 0, 31], 9, {}),                # shares of 2, 64, 51 and 7
+    (2, [1500], 12, {"geometry": 1}), (2, [1500], 12, {"center_dtype": 1}), (2, [1200], 12, {"levels": 4}),
+    (2, [700], 10, {"same": 400}), (2, [9000], 2, {"levels": 3, "fanouts": [0, 2, 20]})])
+def test_same_bits_as_two_kernels_an_iteration(H, chunks, F, config):
+    b = Build(H, chunks, F, seed=sum(chunks) + F, **config)
+    b.run(posts=False)
+    want = b.blob()
+    for _ in range(2):                                       # (the second one finds the first one's posts in the workspace)
+        b.ib.zero_()
+        b.run()
+        assert np.array_equal(b.blob(), want)
+
+
+def test_two_builds_at_the_same_time():
+    """Each wants every compute unit for itself: what has no place, or is late, is worked out by those that wait for it."""
+    import torch
+    builds = [Build(8, [1500], 16, seed=1), Build(8, [1400], 14, seed=2)]
+    want = []
+    for b in builds:
+        b.run(posts=False)
+        want.append(b.blob())
+    streams = [torch.cuda.Stream() for _ in builds]
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for b, s in zip(builds, streams):
+            with torch.cuda.stream(s):
+                b.run()
+    torch.cuda.synchronize()
+    for b, w in zip(builds, want):
+        assert np.array_equal(b.blob(), w)
