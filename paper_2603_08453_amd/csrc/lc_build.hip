@@ -15,6 +15,7 @@
 #include "lc_internal.h"
 #include "lc_select.h"
 
+#include <algorithm>
 #include <type_traits>
 
 #define LC_INLINE __attribute__((always_inline))       // (lambdas that hold registers by reference)
@@ -1798,8 +1799,8 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, LcNodeArg
 // everything follows from the points and the words before -- and posts it (same bits), so every wait ends whatever else occupies the device.
 // Labels, centroids and nodes are the bits of the kernels it stands for: members are added in the same order.
 // What bounds an iteration of about 10 us is single wavefronts' instructions: 3 us a cluster (its members listed, their rows' round trip, the sum and
-// its direction), 2 us 16 points against 160 centroids, and twice a store's way and a look.  512 threads: with 1024 the registers of a sum do not fit.  The
-// heads come first in the grid, so that a head's workgroups, eight apart, share an XCD's L2 for the points' rows.
+// its direction), 2 us 16 points against 160 centroids, and twice a store's way and a look.  512 threads: with 1024 the registers of a sum do not fit.
+// Where the numbers of points allow it the workgroups of a (sequence, head) share an XCD, whose L2 then holds the points' rows (lay_out_shares).
 // Measured, us a build with two kernels an iteration and now: 8 heads of 2275 points, 143 clusters and two small levels 234 and 203; 64 pairs of up
 // to 1820 in 57 334 and 307; 8 of 820 in 52 121 and 88; 8 of 10.9 K in 5461, then of those in 249 850 and 792.
 #define LC_RK_THREADS 512
@@ -1817,6 +1818,11 @@ struct LcRounds {
     int k, words;            // most clusters; words of a (sequence, head), 8 for 16 points
     int row_bytes, label_bytes;
     LcUnposted unposted;     // planes 1 and up, and the labels
+};
+// Which part of which (sequence, head) a workgroup is: pair, part << 8, parts of the pair << 16; LC_RK_NO_PART without work.
+#define LC_RK_NO_PART 0xffffffffu
+struct LcShares {
+    uint32_t of[LC_COMPUTE_UNITS];
 };
 struct LcRkWave {
     union {
@@ -2074,8 +2080,10 @@ __device__ __forceinline__ void lc_rounds_sum(int N, unsigned short* list, Membe
 }
 template <int NBLK, bool NODES>
 __global__ void __launch_bounds__(LC_RK_THREADS)
-lc_kmeans_rounds_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16, int pts_cap, LcNodeArgs w, int iters, LcRounds rd) {
+lc_kmeans_rounds_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16, int pts_cap, LcNodeArgs w, int iters, LcRounds rd, LcShares shares) {
     lc_fetch_args<sizeof(LcDev) + 32 + sizeof(LcNodeArgs) + sizeof(LcRounds)>();
+    const unsigned share = shares.of[blockIdx.x];
+    if (share == LC_RK_NO_PART) return;
     __shared__ __attribute__((aligned(16))) unsigned char rows[16 * NBLK * LC_AS_PITCH];
     constexpr bool FULL = NBLK <= 10;             // the float32 rows find room as well, piece q of row c at q ^ (c mod 32)
     __shared__ lc_v4i full[FULL ? 16 * NBLK * 32 : 1];
@@ -2087,15 +2095,16 @@ lc_kmeans_rounds_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
     constexpr int BITS = NBLK <= 10 && NBLK > 4 ? 512 : 2048;
     __shared__ unsigned long long bits[BITS];     // [mine][blocks] members of this workgroup's clusters, a bit per point
     __shared__ signed char mine_of[LC_AS_RES];    // which of this workgroup's clusters this is, or -1
-    const int h = blockIdx.x, b = blockIdx.y;
-    const int bh = b * ix.H + h, BH = ix.B * ix.H;
+    const int bh = share & 0xff, BH = ix.B * ix.H;
+    const int b = bh / ix.H;
+    const int part = (share >> 8) & 0xff, parts = (share >> 16) & 0xff;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 15, kk = lane >> 4, sub = j;
-    const int first = blockIdx.z + gridDim.z * wave, step = gridDim.z * LC_RK_WAVES;     // this wavefront's tiles of 16 points, and its clusters
+    const int first = part + parts * wave, step = parts * LC_RK_WAVES;     // this wavefront's tiles of 16 points, and its clusters
     const int N = min(min(lc_level_count(ix, b, bh, l), LC_RK_MAX_N), 2 * rd.words);
     const int k = min(min(ix.nlev[b * LC_MAX_LEVELS + l + 1], 16 * NBLK), rd.k);
     const int tiles = (N + 15) >> 4, pieces = 2 * tiles, blocks = (N + 63) >> 6;
-    const int n_mine = ((int)blockIdx.z < k ? k - 1 - (int)blockIdx.z : -1) / (int)gridDim.z + 1;
+    const int n_mine = (part < k ? k - 1 - part : -1) / parts + 1;
     const bool keep_bits = n_mine <= 127 && n_mine * blocks <= BITS;
     LcRkWave& sh = own_sh[wave];
     const float* const P = pts + (size_t)bh * pts_cap * LC_D;
@@ -2129,7 +2138,7 @@ lc_kmeans_rounds_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
     if (tid == 0) moved = -1;
     if (keep_bits)
         for (int i = tid; i < n_mine * blocks; i += LC_RK_THREADS) bits[i] = 0ull;
-    if (tid < LC_AS_RES) mine_of[tid] = (signed char)(keep_bits && tid < k && tid % (int)gridDim.z == (int)blockIdx.z ? tid / (int)gridDim.z : -1);
+    if (tid < LC_AS_RES) mine_of[tid] = (signed char)(keep_bits && tid < k && tid % parts == part ? tid / parts : -1);
     lc_barrier_lds();
     int patience = LC_RK_LOOKS;
     for (int it = 0; N > 0; ++it) {
@@ -2475,10 +2484,74 @@ int most_nodes(const lc_index* idx, int l) {
 }
 bool small_level(int n, int k) { return n <= LC_KS_MAX_N && k <= LC_KS_MAX_K; }
 
-// Workgroups of lc_kmeans_rounds_kernel for a (sequence, head): all of them run at the same time, one to a compute unit.  Beyond 64 they
+// Workgroups of lc_kmeans_rounds_kernel for a (sequence, head) if all get as many: they run at the same time, one to a compute unit.  Beyond 64 they
 // gain nothing (2 heads x 8000 points under 250 nodes, whole builds, us by workgroups a head: 16 360, 32 259, 64 224, 128 216; x 2000 under 250:
 // 67.5, 64.6, 64.1, 64.4).
 int rounds_share(long long BH) { return (int)(BH * 64 <= LC_COMPUTE_UNITS ? 64 : LC_COMPUTE_UNITS / BH); }
+
+// The parts of lc_kmeans_rounds_kernel: returns the workgroups to launch.  A (sequence, head) gets parts in proportion to its points, as the
+// kernel lasts as long as the one with the most points to a part.  Workgroups are dealt to the XCDs in turn, so the parts of a
+// (sequence, head) are 8 apart where they are to share one; they are, unless that means over an eighth more points to a part.
+// Prefill of 16 sequences of 16K to 64K tokens x 4 heads (455 to 1820 points): 349.6 us with equal parts, 338.7 in proportion; of one
+// sequence x 8 heads the same.
+int lay_out_shares(const lc_index* idx, int l, LcShares* s) {
+    constexpr int XCDS = 8, EACH = LC_COMPUTE_UNITS / XCDS;
+    const int H = idx->H_kv, BH = idx->B * H;
+    int n[LC_RK_MAX_PAIRS], order[LC_RK_MAX_PAIRS], near[LC_RK_MAX_PAIRS], far[LC_RK_MAX_PAIRS], xcd[LC_RK_MAX_PAIRS];
+    for (int p = 0; p < BH; ++p) {
+        n[p] = idx->N[p / H * LC_MAX_LEVELS + l] + 1;
+        order[p] = p;
+    }
+    std::stable_sort(order, order + BH, [&](int x, int y) { return n[x] > n[y]; });
+    // as few points to a part of the pairs of one XCD (or of all: x < 0) as give no more than `slots` parts
+    auto deal = [&](int (&parts)[LC_RK_MAX_PAIRS], int x, int slots) {
+        int lo = 1, hi = n[order[0]];                               // (hi: a part each)
+        auto count = [&](int points) {
+            int sum = 0;
+            for (int p = 0; p < BH; ++p)
+                if (x < 0 || xcd[p] == x) sum += parts[p] = std::min((n[p] + points - 1) / points, LC_RK_MAX_SHARE);
+            return sum;
+        };
+        while (lo < hi) {
+            const int mid = (lo + hi) / 2;
+            if (count(mid) <= slots) hi = mid;
+            else lo = mid + 1;
+        }
+        count(hi);
+    };
+    auto worst = [&](const int (&parts)[LC_RK_MAX_PAIRS]) {
+        int w = 0;
+        for (int p = 0; p < BH; ++p) w = std::max(w, (n[p] + parts[p] - 1) / parts[p]);
+        return w;
+    };
+    deal(far, -1, LC_COMPUTE_UNITS);
+    bool share_xcd = BH >= XCDS;
+    if (share_xcd) {
+        long long load[XCDS] = {};
+        int pairs[XCDS] = {};
+        for (int i = 0; i < BH; ++i) {
+            int to = -1;
+            for (int x = 0; x < XCDS; ++x)
+                if (pairs[x] < EACH && (to < 0 || load[x] < load[to])) to = x;
+            xcd[order[i]] = to;
+            load[to] += n[order[i]];
+            ++pairs[to];
+        }
+        for (int x = 0; x < XCDS; ++x) deal(near, x, EACH);
+        share_xcd = worst(near) * 8 <= worst(far) * 9;
+    }
+    for (int i = 0; i < LC_COMPUTE_UNITS; ++i) s->of[i] = LC_RK_NO_PART;
+    int next[XCDS] = {}, at = 0, groups = 0;
+    for (int z = 0; z < LC_RK_MAX_SHARE; ++z)
+        for (int i = 0; i < BH; ++i) {
+            const int p = order[i], parts = share_xcd ? near[p] : far[p];
+            if (z >= parts) continue;
+            const int slot = share_xcd ? xcd[p] + XCDS * next[xcd[p]]++ : at++;
+            s->of[slot] = (uint32_t)p | (uint32_t)z << 8 | (uint32_t)parts << 16;
+            groups = std::max(groups, slot + 1);
+        }
+    return groups;
+}
 
 // Whether a level of n points and k clusters is clustered by lc_kmeans_rounds_kernel, and what that posts, in the workspace's place for it.
 // Measured as whole builds of two levels over 1 to 128 pairs, 240 to 8000 points and 4 to 128 members a cluster, the time with it in parts of that
@@ -2560,10 +2633,11 @@ int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const i
         const dim3 per_grid((maxK + per - 1) / per, H, B);
         const LcNodeArgs w{cur.cent, cur.cent_cap, geometry, next};
         if (l == rounds_level) {                                       // a clustering in one kernel of several workgroups
-            const int share = rounds_share(BH);
+            LcShares shares;
+            const int groups = lay_out_shares(idx, l, &shares);
             auto run = [&](auto kernel) {
-                hipLaunchKernelGGL(kernel, dim3(H, B, share), dim3(LC_RK_THREADS), 0, stream, ix, l, (const float*)cur.pts,
-                                   (const uint16_t*)cur.pts16, cur.cap, w, iters, rounds);
+                hipLaunchKernelGGL(kernel, dim3(groups), dim3(LC_RK_THREADS), 0, stream, ix, l, (const float*)cur.pts,
+                                   (const uint16_t*)cur.pts16, cur.cap, w, iters, rounds, shares);
             };
             if (l == 0 && maxK <= 64) run(&lc_kmeans_rounds_kernel<4, false>);
             else if (l == 0 && maxK <= 160) run(&lc_kmeans_rounds_kernel<10, false>);

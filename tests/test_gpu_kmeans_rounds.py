@@ -55,6 +55,15 @@ def test_same_bits_as_two_kernels_an_iteration(H, chunks, F, config):
         assert np.array_equal(b.blob(), want)
 
 
+# Workgroups in proportion to a sequence's points: pairs that share the XCDs evenly and ones that do not, sequences without points and
+# with more than their part of the device, more workgroups than points, a sequence alone with all 64.
+@pytest.mark.parametrize("H,chunks,F", [
+    (4, [1820, 455, 60, 1200, 0, 900], 32), (3, [2000, 90, 1], 32), (8, [3000, 30], 16), (1, [2500] + [17] * 8, 16),
+    (9, [400], 8), (2, [300, 4096, 1, 0, 40], 40), (16, [600, 20, 0, 350, 1, 599, 64], 10), (1, [230, 0], 5), (4, [240] * 31 + [4000], 64)])
+def test_unequal_sequences(H, chunks, F):
+    test_same_bits_as_two_kernels_an_iteration(H, chunks, F, {})
+
+
 def test_two_builds_at_the_same_time():
     """Each wants every compute unit for itself: what has no place, or is late, is worked out by those that wait for it."""
     import torch
