@@ -1583,9 +1583,10 @@ struct LcMembers {
 // registers as well), the iterations are separated by workgroup barriers instead of kernel boundaries.  Same steps as the
 // three kernels above: strided start, assign (ties to the lower id), normalised member sums (members
 // added in ascending order; a cluster without members or with a zero sum keeps its centroid).
-// What bounds an iteration is a chain: 32 dependent matrix instructions, four barriers, and the longest cluster's members one after
-// the other, eight rows in flight.  143 points into 9 clusters, 8 heads: 33 us, now 27.6; 9 into 1: 7.5 and 6.5 (before: points read from LDS each
-// time, offsets by one wavefront between two barriers of their own, a group per cluster whatever their number).
+// What bounds an iteration is a chain: 32 dependent matrix instructions for each tile of a SIMD (2.2 us for the three of 143 points), two barriers, and
+// the longest cluster's members one after the other, 16 rows in flight.  Up to 16 clusters (WIDE) a wavefront lists its cluster's members itself; beyond
+// that all wavefronts make one list, between two more barriers (with it for 143 points into 9 clusters too, prefill of 128K tokens on one machine: 226.8
+// us, now 222.8).
 // The nodes themselves follow in the same kernel: the members' lists are in LDS, and a launch and its first round trips are worth more than
 // the compute units that a workgroup per node would have.  143 nodes into 9 and 9 into 1: 27.6 and 6.5 us and
 // 5.7 for each's nodes in a kernel of their own, 31.8 and 8.9 together (and two launches less); prefill of 128K tokens 288 us, now 285.
@@ -1596,7 +1597,7 @@ static_assert(LC_KS_MAX_N <= 16 * (LC_KS_THREADS / 64) && LC_KS_MAX_K <= LC_KS_T
 static inline size_t lc_kmeans_small_lds(int N, int k) {
     return (size_t)((N > 0 ? N : 1) + ((k + 15) & ~15)) * LC_AS_ROW * sizeof(float);
 }
-template <bool NODES>
+template <bool NODES, bool WIDE>
 __global__ void __launch_bounds__(LC_KS_THREADS)
 lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, LcNodeArgs w, int iters, int x_rows) {
     lc_fetch_args<sizeof(LcDev) + 32 + sizeof(LcNodeArgs)>();
@@ -1608,10 +1609,10 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, LcNodeArg
     __shared__ int changed[2];                    // labels changed in this iteration (one flag per parity of `it`)
     const int h = blockIdx.x, b = blockIdx.y;
     const int bh = b * ix.H + h;
-    const int tid = threadIdx.x, sub = tid & 15, grp = tid >> 4, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, sub = tid & 15, grp = tid >> 4, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 15, kk = lane >> 4;
     const int N = min(min(lc_level_count(ix, b, bh, l), LC_KS_MAX_N), x_rows);
-    const int k = min(ix.nlev[b * LC_MAX_LEVELS + l + 1], LC_KS_MAX_K);
+    const int k = min(ix.nlev[b * LC_MAX_LEVELS + l + 1], WIDE ? LC_KS_THREADS / 64 : LC_KS_MAX_K);
     const int k16 = (k + 15) & ~15;
     const int rounds = (N + 63) >> 6;
     const float* P = pts + (size_t)bh * pts_cap * LC_D;
@@ -1639,8 +1640,27 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, LcNodeArg
     }
     __syncthreads();
     int n_c = lane == 0 ? N : 0, first = 0;                         // lane c: members of cluster c, where its list begins
+    // WIDE: a wavefront to a cluster, which lists the members itself where its sums go afterwards.
+    unsigned short* const own = reinterpret_cast<unsigned short*>(sums[wave]);
+    static_assert(LC_KS_MAX_N * 2 + 32 <= sizeof(sums[0]), "read 16 members at a time");
+    int n_own = 0;
+    auto list_own = [&]() LC_INLINE {
+        constexpr int R = (LC_KS_MAX_N + 63) / 64;
+        int c[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) c[r] = lab[min(64 * r + lane, LC_KS_MAX_N - 1)];
+        n_own = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const bool in = 64 * r + lane < N && c[r] == wave;
+            const unsigned long long m = __ballot(in);
+            if (in) own[n_own + lc_mbcnt(m)] = (unsigned short)(64 * r + lane);
+            n_own += __popcll(m);
+        }
+        lc_wave_sync();
+    };
     for (int it = 0; it < iters; ++it) {
-        if (i0 < N) {
+        if (i0 < N && k > 1) {                                      // (one cluster: the labels stand as they are)
             float best[4];
             int arg[4];
 #pragma unroll
@@ -1651,8 +1671,9 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, LcNodeArg
                                  cj + j, cj + 16 + j, k, best, arg);
             if (cj < k) lc_assign_block(xa, cs + (cj + j) * LC_AS_ROW + 4 * kk, cj + j, k, best, arg);
 #pragma unroll
+            for (int r = 0; r < 4; ++r) lc_assign_merge(best[r], arg[r]);
+#pragma unroll
             for (int r = 0; r < 4; ++r) {
-                lc_assign_merge(best[r], arg[r]);
                 const int ba = arg[r] < k ? arg[r] : 0, i = i0 + 4 * kk + r;     // (no similarity that compares: not-a-number)
                 if (j == 0 && i < N) {
                     if (lab[i] != ba) changed[it & 1] = 1;
@@ -1666,6 +1687,47 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, LcNodeArg
         // centroids from the same members and every later iteration would repeat it, so the
         // remaining iterations are skipped (the first iteration always runs its update).
         if (it > 0 && changed[it & 1] == 0) break;
+        if constexpr (WIDE) {
+            if (wave < k) {
+                list_own();
+                float2 s = make_float2(0.f, 0.f);
+                for (int q = 0; q < n_own; q += 16) {               // (past the end: the batch's first row again)
+                    unsigned id[8];
+                    float2 x[16];
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const uint4 v = *reinterpret_cast<const uint4*>(own + q + 8 * e);
+                        id[4 * e] = v.x; id[4 * e + 1] = v.y; id[4 * e + 2] = v.z; id[4 * e + 3] = v.w;
+                    }
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        const int i = q + e < n_own ? (int)((id[e / 2] >> (16 * (e & 1))) & 0xffffu) : (int)(id[0] & 0xffffu);
+                        x[e] = *reinterpret_cast<const float2*>(X + i * LC_AS_ROW + 2 * lane);
+                    }
+#pragma unroll
+                    for (int e = 0; e < 16; ++e)
+                        if (q + e < n_own) { s.x += x[e].x; s.y += x[e].y; }
+                }
+                lc_wave_sync();                                     // (the list has been read)
+                *reinterpret_cast<float2*>(sums[wave] + 2 * lane) = s;
+                lc_wave_sync();
+                float sum[8];
+                lc_load8(sums[wave] + 8 * sub, sum);                // (every group the same)
+                float n2 = 0.f;
+#pragma unroll
+                for (int t = 0; t < 8; ++t) n2 = fmaf(sum[t], sum[t], n2);
+                n2 = lc_sum16(n2);
+                if (n2 > 0.f) {
+                    const float inv = 1.0f / sqrtf(n2);
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) sum[t] *= inv;
+                    if (lane < 16) lc_store8(cs + wave * LC_AS_ROW + 8 * sub, sum);
+                }
+                lc_wave_sync();                                     // (the next list comes where the sums were)
+            }
+            __syncthreads();
+            continue;
+        }
         // members of every cluster, ascending, as one list ordered by cluster: counts, then every wavefront works out the places
         for (int c = wave; c < k; c += LC_KS_THREADS / 64) {
             int n = 0;
@@ -1691,45 +1753,25 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, LcNodeArg
         }
         __syncthreads();
         {
-            // up to 16 clusters: a wavefront each, two columns per lane; beyond that a 16-lane group each, eight columns per lane
-            const bool wide = k <= LC_KS_THREADS / 64;
-            const int c = wide ? wave : grp;                        // (clusters past the last have no members)
+            // a 16-lane group to a cluster, eight columns per lane
+            const int c = grp;                                      // (clusters past the last have no members)
             const int n = __shfl(n_c, min(c, 63)), at = __shfl(first, min(c, 63));
             float sum[8];
-            auto add_rows = [&](auto cols, int col) LC_INLINE {
-                constexpr int C = decltype(cols)::value;
 #pragma unroll
-                for (int t = 0; t < 8; ++t) sum[t] = 0.f;
-                for (int q = 0; q < n; q += 8) {
-                    const uint4 id = *reinterpret_cast<const uint4*>(mem + at + q);
-                    const uint32_t w[4] = {id.x, id.y, id.z, id.w};
-                    float x[8][C];
+            for (int t = 0; t < 8; ++t) sum[t] = 0.f;
+            for (int q = 0; q < n; q += 8) {
+                const uint4 id = *reinterpret_cast<const uint4*>(mem + at + q);
+                const uint32_t w[4] = {id.x, id.y, id.z, id.w};
+                float x[8][8];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {                   // (past the end: the batch's first row again)
-                        const int i = q + e < n ? (int)((w[e / 2] >> (16 * (e & 1))) & 0xffffu) : (int)(w[0] & 0xffffu);
-                        if constexpr (C == 8) {
-                            lc_load8(X + i * LC_AS_ROW + col, x[e]);
-                        } else {
-                            const float2 v = *reinterpret_cast<const float2*>(X + i * LC_AS_ROW + col);
-                            x[e][0] = v.x;
-                            x[e][1] = v.y;
-                        }
+                for (int e = 0; e < 8; ++e)                         // (past the end: the batch's first row again)
+                    lc_load8(X + (q + e < n ? (int)((w[e / 2] >> (16 * (e & 1))) & 0xffffu) : (int)(w[0] & 0xffffu)) * LC_AS_ROW + 8 * sub, x[e]);
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (q + e < n) {
+#pragma unroll
+                        for (int t = 0; t < 8; ++t) sum[t] += x[e][t];
                     }
-#pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        if (q + e < n) {
-#pragma unroll
-                            for (int t = 0; t < C; ++t) sum[t] += x[e][t];
-                        }
-                }
-            };
-            if (wide) {
-                add_rows(std::integral_constant<int, 2>(), 2 * lane);
-                *reinterpret_cast<float2*>(sums[wave] + 2 * lane) = make_float2(sum[0], sum[1]);
-                lc_wave_sync();
-                lc_load8(sums[wave] + 8 * sub, sum);                // (every group the same)
-            } else {
-                add_rows(std::integral_constant<int, 8>(), 8 * sub);
             }
             float n2 = 0.f;
 #pragma unroll
@@ -1739,7 +1781,7 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, LcNodeArg
                 const float inv = 1.0f / sqrtf(n2);
 #pragma unroll
                 for (int t = 0; t < 8; ++t) sum[t] *= inv;
-                if (!wide || lane < 16) lc_store8(cs + c * LC_AS_ROW + 8 * sub, sum);
+                lc_store8(cs + c * LC_AS_ROW + 8 * sub, sum);
             }
         }
         __syncthreads();
@@ -1747,9 +1789,11 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, LcNodeArg
     for (int i = tid; i < N; i += LC_KS_THREADS) ix.parent[l][(size_t)bh * ix.cap[l] + i] = lab[i];
     // ---- the nodes: the lists are those of the labels as they stand.  A wavefront per node, its groups taking the members in turn, or
     // beyond 16 nodes a group each; four rows per group in flight.
-    const bool wide = k <= LC_KS_THREADS / 64;
+    const bool wide = WIDE || k <= LC_KS_THREADS / 64;
+    if (WIDE && wave < k) list_own();
     const int c = wide ? wave : grp;
-    const int n = __shfl(n_c, min(c, 63)), at = __shfl(first, min(c, 63));     // (while every lane is there)
+    const int n = WIDE ? n_own : __shfl(n_c, min(c, 63)), at = WIDE ? 0 : __shfl(first, min(c, 63));     // (while every lane is there)
+    const unsigned short* const list = WIDE ? own : mem;
     if (c >= k) return;
     const LcMembers<NODES> m(ix, b, bh, l);
     const int step = wide ? 4 : 1;
@@ -1760,14 +1804,14 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, LcNodeArg
         float x[4][8];
         int weight[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) weight[e] = m.row((int)mem[at + min(q + step * e, n - 1)], 8 * sub, x[e]);
+        for (int e = 0; e < 4; ++e) weight[e] = m.row((int)list[at + min(q + step * e, n - 1)], 8 * sub, x[e]);
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             if (q + step * e < n) lc_add_row(sum, x[e], weight[e]);
     }
     int tok = 0, chunks = 0;
     for (int q = wide ? lane : sub; q < n; q += 16 * step) {
-        const int i = mem[at + q];
+        const int i = list[at + q];
         tok += m.ntok[i];
         chunks += m.chunks(i);
     }
@@ -2651,7 +2695,8 @@ int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const i
         }
         if (maxN > 0 && small_level(maxN, maxK)) {                     // the whole level in one workgroup per (sequence, head)
             const size_t lds = lc_kmeans_small_lds(maxN, maxK);
-            const auto kernel = l == 0 ? &lc_kmeans_small_kernel<false> : &lc_kmeans_small_kernel<true>;
+            const auto kernel = maxK <= LC_KS_THREADS / 64 ? (l == 0 ? &lc_kmeans_small_kernel<false, true> : &lc_kmeans_small_kernel<true, true>)
+                                                           : (l == 0 ? &lc_kmeans_small_kernel<false, false> : &lc_kmeans_small_kernel<true, false>);
             LC_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
             hipLaunchKernelGGL(kernel, dim3(H, B), dim3(LC_KS_THREADS), lds, stream, ix, l, (const float*)cur.pts, cur.cap, w, iters, maxN);
             LC_HIP_CHECK(hipGetLastError());

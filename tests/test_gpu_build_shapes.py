@@ -214,3 +214,23 @@ def test_capacity_that_is_not_in_use_costs_a_build_nothing():
             took.append(a.elapsed_time(b) * 200)
         us[most] = min(took)
     assert us[131072] < 1.6 * us[chunks], us
+
+
+@pytest.mark.parametrize("chunks,F", [([224, 211], 14), ([209, 17, 34], 15), ([64, 65, 48], 8), ([128], 64)])
+def test_up_to_16_clusters_of_a_small_level(chunks, F):
+    """16 clusters and fewer, each listed by a wavefront: tiles of points and batches of 16 members with remainders."""
+    for iters in (2, 3):
+        test_an_iteration_follows_from_the_one_before(2, chunks, F, 0, {}, iters)
+
+
+@pytest.mark.parametrize("chunks", [[224, 1, 0, 17], [2]])
+@pytest.mark.parametrize("iters", [1, 10])
+def test_one_cluster(chunks, iters):
+    """Its centroid is the direction of the sum of all directions: a float32 sum of n unit vectors (n 2^-24 of their lengths together at
+    most) over its length, which random keys leave at sqrt(n) at least."""
+    for s, n in zip(build(2, chunks, 224, iters, geometry=1), chunks):
+        for head in s["heads"] if n else []:
+            x = unit(head[0]["center"].astype(np.float64))
+            assert not head[0]["parent"].any() and head[1]["nchunk"].tolist() == [n]
+            total = x.sum(axis=0)
+            assert np.abs(head[1]["center"][0] - unit(total[None])[0]).max() <= (n + 8) * n * 2.0 ** -24 / np.linalg.norm(total)
