@@ -2795,6 +2795,9 @@ int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const i
 // ---------------------------------------------------------------------------------
 // One workgroup per (sequence, head): over the nodes with a finite radius at build time, the sum of
 // those radii, the sum of the radii now, the largest growth and the count (fixed reduction order).
+// What bounds it is round trips, a head's nodes being one workgroup's: LC_DR_NODES of a thread are on their way at once (8 heads of 5461 nodes, one
+// at a time 14.5 us, now 4.4).
+#define LC_DR_NODES 16
 __global__ void __launch_bounds__(LC_BT)
 lc_drift_kernel(LcDev ix, int level, float* out) {
     __shared__ float sh[4][LC_BT / 64];
@@ -2803,14 +2806,22 @@ lc_drift_kernel(LcDev ix, int level, float* out) {
     const int n_l = min(ix.nlev[b * LC_MAX_LEVELS + level], ix.cap[level]);
     const size_t base = (size_t)bh * ix.cap[level];
     float s_then = 0.f, s_now = 0.f, grow = 0.f, cnt = 0.f;
-    for (int n = threadIdx.x; n < n_l; n += LC_BT) {
-        const float r0 = ix.rbuild[level][base + n], r1 = ix.radius[level][base + n];
-        if (r0 > LC_NEG_INF) {
-            s_then += r0;
-            s_now += r1;
-            grow = fmaxf(grow, r1 - r0);
-            cnt += 1.f;
+    for (int n0 = threadIdx.x; n0 < n_l; n0 += LC_DR_NODES * LC_BT) {
+        float r0[LC_DR_NODES], r1[LC_DR_NODES];
+#pragma unroll
+        for (int e = 0; e < LC_DR_NODES; ++e) {
+            const size_t n = base + min(n0 + e * LC_BT, n_l - 1);
+            r0[e] = ix.rbuild[level][n];
+            r1[e] = ix.radius[level][n];
         }
+#pragma unroll
+        for (int e = 0; e < LC_DR_NODES; ++e)
+            if (n0 + e * LC_BT < n_l && r0[e] > LC_NEG_INF) {
+                s_then += r0[e];
+                s_now += r1[e];
+                grow = fmaxf(grow, r1[e] - r0[e]);
+                cnt += 1.f;
+            }
     }
     s_then = lc_sum64(s_then);
     s_now = lc_sum64(s_now);

@@ -54,3 +54,21 @@ def test_import_export_round_trip(H, L, F, chunks, bf16):
     if L > 1:                                 # the radii at import are the baseline of the drift figures
         drift = lc.lc_index_drift(idx, 1, torch.zeros(1 << 16, dtype=torch.uint8, device="cuda"))
         assert np.all(drift[..., 2] == 0) and np.array_equal(drift[..., 0], drift[..., 1])
+
+
+@pytest.mark.parametrize("chunks", [[1, 255, 256], [4096, 4097], [9000, 0, 4351]])
+def test_drift_counts_every_node(chunks):
+    """Rounds of 16 nodes a thread with remainders: one node to a chunk, radii positive (float32 sums of n of them: n 2^-24 of the sum at most)."""
+    import torch
+    from paper_2603_08453_amd import binding as lc
+    blob = random_blob(lc, np.random.default_rng(chunks[0]), 2, 2, 1, chunks, False)
+    cfg = lc.lc_config_default(levels=2, fanout=1, max_chunks=max(chunks), max_tokens=5 * max(chunks) + 20)
+    idx = lc.lc_index_import(cfg, blob, torch.zeros(lc.lc_index_bytes(cfg, len(chunks), 2), dtype=torch.uint8, device="cuda"))
+    drift = lc.lc_index_drift(idx, 1, torch.zeros(1 << 16, dtype=torch.uint8, device="cuda"))
+    for b, s in enumerate(lc.unpack_blob(blob)["seqs"]):
+        for h, head in enumerate(s["heads"]):
+            r = head[1]["radius"].astype(np.float64)
+            r = r[np.isfinite(r)]
+            assert drift[b, h, 3] == len(r) and drift[b, h, 2] == 0
+            for total in drift[b, h, :2]:
+                assert abs(total - r.sum()) <= max(len(r), 1) * 2.0 ** -24 * np.abs(r).sum()
