@@ -13,6 +13,7 @@
 // Every reduction runs in a fixed order, so results are reproducible run to run.
 #include "lc_device.h"
 #include "lc_internal.h"
+#include "lc_rounds_planes.h"
 #include "lc_select.h"
 
 #include <algorithm>
@@ -1841,6 +1842,7 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, LcNodeArg
 // itself whether it has been posted: there is no counter, no order between stores and nothing that a late workgroup could overwrite.
 // Nobody depends on another workgroup: a wavefront that has looked for a word LC_RK_LOOKS times works out what is missing itself --
 // everything follows from the points and the words before -- and posts it (same bits), so every wait ends whatever else occupies the device.
+// A cluster that has lost its members keeps its centroid: the one of an earlier iteration's plane, all of which the workgroup has seen (LcPlanes).
 // Labels, centroids and nodes are the bits of the kernels it stands for: members are added in the same order.
 // What bounds an iteration of about 10 us is single wavefronts' instructions: 3 us a cluster (its members listed, their rows' round trip, the sum and
 // its direction), 2 us 16 points against 160 centroids, and twice a store's way and a look.  512 threads: with 1024 the registers of a sum do not fit.
@@ -2134,7 +2136,7 @@ lc_kmeans_rounds_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
     __shared__ lc_v4i lab[LC_RK_MAX_N / 8];
     __shared__ __attribute__((aligned(16))) LcRkWave own_sh[LC_RK_WAVES];
     __shared__ int fresh[LC_AS_RES];              // iteration that starts with a new centroid of this cluster
-    __shared__ int plane[LC_AS_RES];              // plane of the centroid that is in `rows`
+    __shared__ LcPlanes<LC_AS_RES> planes;        // plane of the centroid that is in `rows`
     __shared__ int moved;                         // last iteration that moved a point
     constexpr int BITS = NBLK <= 10 && NBLK > 4 ? 512 : 2048;
     __shared__ unsigned long long bits[BITS];     // [mine][blocks] members of this workgroup's clusters, a bit per point
@@ -2171,14 +2173,14 @@ lc_kmeans_rounds_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
         }
         return word;
     };
-    auto centroid = [&](int c, int q) LC_INLINE {
+    auto centroid = [&](int it, int c, int q) LC_INLINE {
         if constexpr (FULL) return __builtin_bit_cast(float4, full[32 * c + (q ^ (c & 31))]);
-        else return lc_load_agent4(rows_r, row_at(plane[c], c) + 16 * q);
+        else return lc_load_agent4(rows_r, row_at(planes.now(it, c), c) + 16 * q);
     };
     constexpr int PIECES = LC_RK_MAX_N / 8 / LC_RK_THREADS;         // pieces of labels of a thread
 #pragma unroll
     for (int e = 0; e < PIECES; ++e) lab[tid + e * LC_RK_THREADS] = lc_v4i{-1, -1, -1, -1};
-    if (tid < LC_AS_RES) { fresh[tid] = 0; plane[tid] = 0; }
+    if (tid < LC_AS_RES) { fresh[tid] = 0; planes.start(tid); }
     if (tid == 0) moved = -1;
     if (keep_bits)
         for (int i = tid; i < n_mine * blocks; i += LC_RK_THREADS) bits[i] = 0ull;
@@ -2192,7 +2194,9 @@ lc_kmeans_rounds_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
 #pragma unroll
         for (int i = 0; i < R; ++i) {
             const int c = 2 * (wave + LC_RK_WAVES * i) + (lane >> 5);
-            open |= it < iters && c < k && fresh[min(c, LC_AS_RES - 1)] == it ? 1u << i : 0u;
+            const bool changed = c < k && fresh[min(c, LC_AS_RES - 1)] == it;
+            open |= it < iters && changed ? 1u << i : 0u;
+            if (c < k && (lane & 31) == 0) planes.enter(it, c, changed);
         }
         int looks = 0;
         lc_v4i next[4];                                             // the next tile's rows in bfloat16
@@ -2228,7 +2232,6 @@ lc_kmeans_rounds_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
                                 *reinterpret_cast<uint2*>(rows + a * LC_AS_PITCH + 8 * (lane & 31)) = *reinterpret_cast<const uint2*>(rows + row * LC_AS_PITCH + 8 * (lane & 31));
                         if constexpr (FULL) full[32 * row + ((lane & 31) ^ (row & 31))] = v[i];
                         open &= ~(1u << i);
-                        if ((lane & 31) == 0) plane[row] = it;
                     }
                 }
                 if (__ballot(open != 0u) == 0ull || looks == LC_RK_LOOKS_MOST) break;
@@ -2255,7 +2258,8 @@ lc_kmeans_rounds_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
             for (int t = 0; t < 8; ++t) sum[t] *= inv;
             float4 half = kk == 0 ? make_float4(sum[0], sum[1], sum[2], sum[3]) : make_float4(sum[4], sum[5], sum[6], sum[7]);
             const int o = 32 * sub + 16 * (kk & 1);
-            if (!(n2 > 0.f)) half = lc_load_agent4(rows_r, row_at(plane[c], c) + o);      // no members, or none in sum: the centroid stands
+            // no members, or none in sum: the centroid stands, and this iteration's plane may still be in the making
+            if (!(n2 > 0.f)) half = lc_load_agent4(rows_r, row_at(planes.before(it, c), c) + o);
             auto posted = [](float f) LC_INLINE { return __float_as_int(f) == LC_UNPOSTED ? __int_as_float(0x7fc00000) : f; };
             half = make_float4(posted(half.x), posted(half.y), posted(half.z), posted(half.w));
             if (kk < 2) lc_store_agent4(rows_r, row_at(it, c) + o, half);
@@ -2301,7 +2305,7 @@ lc_kmeans_rounds_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
             for (int s = 0; s < 8; ++s) tile.full[s] = *reinterpret_cast<const float4*>(row + 16 * s);
 #pragma unroll
             for (int s = 0; s < 4; ++s) tile.half[s] = next[s];
-            const int label = lc_rounds_label<NBLK>(sh, rows, tile, min(N - 16 * t, 16), k, centroid,
+            const int label = lc_rounds_label<NBLK>(sh, rows, tile, min(N - 16 * t, 16), k, [&](int c, int q) LC_INLINE { return centroid(it, c, q); },
                                                     [&]() LC_INLINE { load_half(next, min(own, tiles - 1)); });
             const int mine = 16 * t + j < N ? label : 0xfffe;       // (no label behind the last point)
             const int two = __shfl(mine, 2 * (lane & 7)) | (__shfl(mine, 2 * (lane & 7) + 1) << 16);
