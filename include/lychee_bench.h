@@ -28,6 +28,11 @@ int lc_bench_select_attend(const lc_index* idx, const void* q, const void* K, co
  * number of query heads that it refuses). */
 int lc_bench_step_is_one_kernel(const lc_index* idx, int H_q, int budget);
 
+/* lc_recluster on a device that has no place for all its workgroups: those that cluster a (sequence, head) together come
+ * in two launches, the first `first_parts` (>= 1) of them, which work out what the others would have posted, then the
+ * others.  The same result; where no level is clustered that way, the same launches as lc_recluster. */
+int lc_bench_recluster_in_two(lc_index* idx, int first_parts, void* ws, size_t ws_bytes, void* stream);
+
 /* Reads `bytes` bytes (a multiple of 16, from a 16-byte aligned device pointer) once with plain
  * streaming loads, so that a benchmark can quote the read bandwidth this GPU reaches.  `sink`
  * (device, at least 2048 words; `sink_words` says how many there are) receives one folded word per

@@ -124,6 +124,8 @@ def lib() -> ctypes.CDLL:
     L.lc_bench_select_attend.restype = ctypes.c_int
     L.lc_bench_step_is_one_kernel.argtypes = [vp, ctypes.c_int, ctypes.c_int]
     L.lc_bench_step_is_one_kernel.restype = ctypes.c_int
+    L.lc_bench_recluster_in_two.argtypes = [vp, ctypes.c_int, vp, ctypes.c_size_t, vp]
+    L.lc_bench_recluster_in_two.restype = ctypes.c_int
     L.lc_bench_read_sweep.argtypes = [vp, ctypes.c_size_t, vp, ctypes.c_size_t, vp]
     L.lc_bench_read_sweep.restype = ctypes.c_int
     L.lc_append.argtypes = [vp, vp, vp, i64p, vp, vp, u8p, vp, ctypes.c_size_t, vp]
@@ -365,6 +367,12 @@ def lc_bench_select_attend(idx: Index, q, K, V, budget: int, out, ws, lse=None, 
 def lc_bench_step_is_one_kernel(idx: Index, q_heads: int, budget: int) -> bool:
     """Whether lc_decode_step runs as one kernel on this index as it stands."""
     return bool(lib().lc_bench_step_is_one_kernel(idx.handle, int(q_heads), int(budget)))
+
+
+def lc_bench_recluster_in_two(idx: Index, first_parts: int, ws, stream=None) -> None:
+    """lc_recluster whose workgroups come in two launches, the first `first_parts` of each (sequence, head), then the others."""
+    _check(lib().lc_bench_recluster_in_two(idx.handle, int(first_parts), _ptr(ws), ws.numel() * ws.element_size(), _stream(stream)),
+           "lc_bench_recluster_in_two")
 
 
 def lc_bench_read_sweep(src, sink, stream=None) -> None:

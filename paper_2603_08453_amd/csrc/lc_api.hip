@@ -429,7 +429,7 @@ int lc_build_index(lc_index** out, const lc_config* cfg, const void* K, const in
     return LC_OK;
 }
 
-int lc_recluster(lc_index* idx, void* ws, size_t ws_bytes, void* stream) {
+int lc_recluster_impl(lc_index* idx, void* ws, size_t ws_bytes, void* stream, int first_parts) {
     if (!idx || !ws || (reinterpret_cast<uintptr_t>(ws) & 255u)) return LC_ERR_INVALID_ARG;
     LcWs w;
     if (ws_bytes < lc_layout_ws(&idx->cfg, idx->B, idx->H_kv, idx->H_kv, idx->d, 1, nullptr, nullptr))
@@ -443,8 +443,10 @@ int lc_recluster(lc_index* idx, void* ws, size_t ws_bytes, void* stream) {
     for (int b = 0; b < idx->B; ++b)
         if (idx->M[b] > max_M) max_M = idx->M[b];
     const int64_t no_strides[3] = {0, 0, 0};
-    return lc_launch_build(idx, w, nullptr, no_strides, max_M, s);
+    return lc_launch_build(idx, w, nullptr, no_strides, max_M, s, first_parts);
 }
+
+int lc_recluster(lc_index* idx, void* ws, size_t ws_bytes, void* stream) { return lc_recluster_impl(idx, ws, ws_bytes, stream, 0); }
 
 int lc_set_policy(lc_index* idx, int policy, const int32_t* beam, int sink_tokens) {
     if (!idx) return LC_ERR_INVALID_ARG;

@@ -1,6 +1,6 @@
 // Measurement aids (lychee_bench.h), kept apart from the decode path: a plain streaming read of a
 // device buffer, so that a benchmark can report what read bandwidth this GPU reaches next to its
-// published peak, and a launch of the select+attend kernel of lc_decode_step by itself.
+// published peak, a launch of the select+attend kernel of lc_decode_step by itself, and a re-clustering short of workgroups.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -59,4 +59,9 @@ extern "C" int lc_bench_select_attend(const lc_index* idx, const void* q, const 
 
 extern "C" int lc_bench_step_is_one_kernel(const lc_index* idx, int H_q, int budget) {
     return lc_decode_step_is_one_kernel(idx, H_q, budget);
+}
+
+extern "C" int lc_bench_recluster_in_two(lc_index* idx, int first_parts, void* ws, size_t ws_bytes, void* stream) {
+    if (first_parts < 1) return LC_ERR_INVALID_ARG;
+    return lc_recluster_impl(idx, ws, ws_bytes, stream, first_parts);
 }

@@ -1842,6 +1842,12 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, LcNodeArg
 // itself whether it has been posted: there is no counter, no order between stores and nothing that a late workgroup could overwrite.
 // Nobody depends on another workgroup: a wavefront that has looked for a word LC_RK_LOOKS times works out what is missing itself --
 // everything follows from the points and the words before -- and posts it (same bits), so every wait ends whatever else occupies the device.
+// What a wavefront works out for others it takes from the missing words by its workgroup's number, so that those that wait share
+// it.  Re-clustering with half of each head's workgroups in a second launch, us when all took the first missing word after twice as many
+// looks, and now: 8 heads of 1000 points 507 and 265, of 2275 830 and 445, of 5461 2200 and 880 (all in one launch: 83, 119 and 262).
+// On a device that is shared (8 heads of 2275 points, two small levels fewer than above, us a build with two kernels an iteration and now):
+// alone 177 and 134; with another build at the same time 228 and 222 for both, with two 300 and 576 for the three (948 when all took the first
+// missing word); beside eight decode steps 203 and 232, beside 4096^3 matrix products 963 and 508, beside copies of a gigabyte 331 and 490.
 // A cluster that has lost its members keeps its centroid: the one of an earlier iteration's plane, all of which the workgroup has seen (LcPlanes).
 // Labels, centroids and nodes are the bits of the kernels it stands for: members are added in the same order.
 // What bounds an iteration of about 10 us is single wavefronts' instructions: 3 us a cluster (its members listed, their rows' round trip, the sum and
@@ -1853,8 +1859,9 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, LcNodeArg
 #define LC_RK_WAVES (LC_RK_THREADS / 64)
 #define LC_RK_MAX_N LC_RK_MAX_POINTS
 #define LC_RK_LIST 768                       // members that a wavefront lists before it adds their rows
-#define LC_RK_LOOKS 128                      // times a wavefront looks before it works out what is missing
-#define LC_RK_LOOKS_AGAIN 4                  // and once it has
+#define LC_RK_LOOKS 64                       // times a wavefront looks (1.6 us each) before it works out what is missing
+#define LC_RK_LOOKS_AGAIN 1                  // and once it has (twice as many after each wait that ended by itself)
+#define LC_RK_LOOK_MEMBERS 16                // members that are added in the time of a look, at least: it waits so much longer for a centroid
 #define LC_RK_LOOKS_MOST 1024                // more than a wavefront has words to wait for: the wait ends whatever is in memory
 #define LC_RK_WAIT_ROWS 20                   // 64 clocks each: a wavefront without clusters of its own waits before it looks for centroids,
 #define LC_RK_WAIT_LABELS 20                 // one without points before it looks for labels
@@ -2124,6 +2131,11 @@ __device__ __forceinline__ void lc_rounds_sum(int N, unsigned short* list, Membe
 #pragma unroll
     for (int t = 0; t < 4; ++t) { sum[t + 4] = sum[t]; lc_swap32(sum[t], sum[t + 4]); }
 }
+// The number of the n-th bit that is set (from 0; there are more than n).
+__device__ __forceinline__ int lc_nth_bit(unsigned long long m, int n) {
+    for (; n > 0; --n) m &= m - 1ull;
+    return __ffsll((long long)m) - 1;
+}
 template <int NBLK, bool NODES>
 __global__ void __launch_bounds__(LC_RK_THREADS)
 lc_kmeans_rounds_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16, int pts_cap, LcNodeArgs w, int iters, LcRounds rd, LcShares shares) {
@@ -2236,9 +2248,18 @@ lc_kmeans_rounds_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
                 }
                 if (__ballot(open != 0u) == 0ull || looks == LC_RK_LOOKS_MOST) break;
                 if (++looks <= patience) { __builtin_amdgcn_s_sleep(1); continue; }
+                unsigned missing = 0u;                              // rows of this wavefront; another one to each workgroup that helps
+#pragma unroll
+                for (int i = 0; i < R; ++i) {
+                    const unsigned long long m = __ballot((open >> i) & 1u);
+                    missing |= (unsigned)((unsigned)m != 0u) << (2 * i) | (unsigned)((unsigned)(m >> 32) != 0u) << (2 * i + 1);
+                }
+                const int row = lc_nth_bit(missing, part % __popc(missing));
+                c = 2 * (wave + LC_RK_WAVES * (row >> 1)) + (row & 1);
+                int n = 0;                                          // (a large cluster takes whoever has begun with it as long)
+                for (int b0 = 0; b0 < blocks; b0 += 64) n += lc_wave_sum_i(__popcll(members(-1, c, b0)));
+                if (looks <= patience + n / LC_RK_LOOK_MEMBERS) { __builtin_amdgcn_s_sleep(1); continue; }
                 patience = LC_RK_LOOKS_AGAIN;
-                const int who = __ffsll((long long)__ballot(open != 0u)) - 1;
-                c = 2 * (wave + LC_RK_WAVES * (__ffs(lc_readlane((int)open, who)) - 1)) + (who >> 5);
             }
             float sum[8];
             lc_rounds_sum<float>(N, sh.list, [&](int b0) LC_INLINE { return members(mine, c, b0); },
@@ -2266,6 +2287,7 @@ lc_kmeans_rounds_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
             if (own >= k) __builtin_amdgcn_s_waitcnt(0);            // (my own posts are there when I look)
         }
         if (it == iters) break;
+        if (looks <= patience) patience = min(2 * patience, LC_RK_LOOKS);
         lc_barrier_lds();
         // ---- the labels of my points, then everybody's
         lc_v4i v[PIECES];
@@ -2284,18 +2306,25 @@ lc_kmeans_rounds_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
 #pragma unroll
                 for (int e = 0; e < PIECES; ++e)
                     if (wait[e]) v[e] = __builtin_amdgcn_raw_buffer_load_b128(labels_r, label_at(it, 4 * (tid + e * LC_RK_THREADS)), 0, 16);
-                bool any = false;
-                int missing = 0;
+                unsigned long long missing[PIECES];
+                int n_missing = 0;
 #pragma unroll
-                for (int e = PIECES - 1; e >= 0; --e) {
+                for (int e = 0; e < PIECES; ++e) {
                     wait[e] = wait[e] && (v[e].x == LC_UNPOSTED || v[e].y == LC_UNPOSTED || v[e].z == LC_UNPOSTED || v[e].w == LC_UNPOSTED);
-                    any = any || wait[e];
-                    missing = wait[e] ? tid + e * LC_RK_THREADS : missing;
+                    missing[e] = __ballot(wait[e]);
+                    n_missing += __popcll(missing[e]);
                 }
-                if (__ballot(any) == 0ull || looks == LC_RK_LOOKS_MOST) break;
+                if (n_missing == 0 || looks == LC_RK_LOOKS_MOST) break;
                 if (++looks <= patience) { __builtin_amdgcn_s_sleep(1); continue; }
                 patience = LC_RK_LOOKS_AGAIN;
-                t = lc_readlane(missing, __ffsll((long long)__ballot(any)) - 1) >> 1;
+                int n = 2 * part % n_missing, piece = -1;           // (two pieces to a tile; another tile to each workgroup that helps)
+#pragma unroll
+                for (int e = 0; e < PIECES; ++e) {
+                    const int here = __popcll(missing[e]);
+                    if (piece < 0 && n < here) piece = 64 * wave + e * LC_RK_THREADS + lc_nth_bit(missing[e], n);
+                    n -= here;
+                }
+                t = piece >> 1;
             }
             const bool help = looks > 0;
             if (help) load_half(next, t);
@@ -2313,6 +2342,7 @@ lc_kmeans_rounds_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
 
             if (help) __builtin_amdgcn_s_waitcnt(0);
         }
+        if (looks <= patience) patience = min(2 * patience, LC_RK_LOOKS);
         bool any = false;
 #pragma unroll
         for (int e = 0; e < PIECES; ++e) {
@@ -2628,7 +2658,7 @@ bool lay_out_rounds(const LcWs& ws, long long BH, int n, int k, int iters, LcRou
 
 // K == nullptr: keep the chunk nodes (level 0) as they are and rebuild only the levels above them.
 int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const int64_t ks[3],
-                    int max_M, hipStream_t stream) {
+                    int max_M, hipStream_t stream, int first_parts) {
     const LcDev& ix = idx->dev;
     const uint16_t* K = static_cast<const uint16_t*>(Kp);
     const int geometry = idx->cfg.geometry;
@@ -2683,9 +2713,17 @@ int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const i
         if (l == rounds_level) {                                       // a clustering in one kernel of several workgroups
             LcShares shares;
             const int groups = lay_out_shares(idx, l, &shares);
-            auto run = [&](auto kernel) {
+            auto launch = [&](auto kernel, const LcShares& of) {
                 hipLaunchKernelGGL(kernel, dim3(groups), dim3(LC_RK_THREADS), 0, stream, ix, l, (const float*)cur.pts,
-                                   (const uint16_t*)cur.pts16, cur.cap, w, iters, rounds, shares);
+                                   (const uint16_t*)cur.pts16, cur.cap, w, iters, rounds, of);
+            };
+            auto run = [&](auto kernel) {
+                if (first_parts <= 0) return launch(kernel, shares);
+                LcShares first = shares, rest = shares;
+                for (int i = 0; i < LC_COMPUTE_UNITS; ++i)
+                    ((int)(shares.of[i] >> 8 & 0xff) < first_parts ? rest : first).of[i] = LC_RK_NO_PART;
+                launch(kernel, first);
+                launch(kernel, rest);
             };
             if (l == 0 && maxK <= 64) run(&lc_kmeans_rounds_kernel<4, false>);
             else if (l == 0 && maxK <= 160) run(&lc_kmeans_rounds_kernel<10, false>);

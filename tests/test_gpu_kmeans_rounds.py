@@ -81,3 +81,38 @@ def test_two_builds_at_the_same_time():
     torch.cuda.synchronize()
     for b, w in zip(builds, want):
         assert np.array_equal(b.blob(), w)
+
+
+@pytest.mark.parametrize("H,chunks,F,config,first", [
+    (8, [1500], 16, {}, (1, 7, 16, 31)), (1, [225], 15, {}, (1, 8)), (2, [700], 10, {"same": 400}, (1, 30)), (4, [4097], 17, {"same": 900}, (32,)),
+    (2, [1025, 3], 16, {}, (1, 20)), (3, [500, 499, 64], 8, {"iters": 1}, (1, 2)), (2, [8192, 15], 32, {"iters": 3}, (16,)),
+    (2, [600], 6, {"same": 600}, (1, 9)), (2, [9000], 2, {"levels": 3, "fanouts": [0, 2, 20], "iters": 3}, (30,))])
+def test_short_of_workgroups(H, chunks, F, config, first):
+    """What the workgroups of a second launch would have posted is worked out by those of the first, every label and centroid of it: with
+    clusters that lose all their members (chunks that are alike) or whose centroids stand for other reasons."""
+    b = Build(H, chunks, F, seed=sum(chunks) + F, **config)
+    b.run(posts=False)
+    want = b.blob()
+    for parts in first:
+        b.ws.fill_(0xA5)
+        b.lc.lc_bench_recluster_in_two(b.idx, parts, b.ws)
+        assert np.array_equal(b.blob(), want), parts
+
+
+def test_missing_work_is_shared():
+    """Half of the workgroups do all of an iteration's work, each a part of what is missing: with the second launch behind it 3.3 times what
+    all of them take (each the whole of what is missing: 8.3 times)."""
+    import torch
+    b = Build(8, [5461], 22, seed=3)
+    b.run()
+    took = {}
+    for parts in (64, 16):                                   # (32 workgroups a head: all, and half)
+        for _ in range(5):
+            a, z = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda.synchronize()
+            a.record()
+            b.lc.lc_bench_recluster_in_two(b.idx, parts, b.ws)
+            z.record()
+            torch.cuda.synchronize()
+            took.setdefault(parts, []).append(a.elapsed_time(z))
+    assert min(took[16]) < 5 * min(took[64]), took

@@ -118,6 +118,7 @@ def test_argument_errors_before_any_gpu_work(L):
     assert L.lc_index_drift(None, 1, four, fake, 1 << 20, None) == lc.LC_ERR_INVALID_ARG
     assert L.lc_bench_select_attend(None, fake, fake, fake, strides, 8, 16, fake, None, fake, 1 << 20, None) == lc.LC_ERR_INVALID_ARG
     assert L.lc_bench_step_is_one_kernel(None, 32, 1024) == 0
+    assert L.lc_bench_recluster_in_two(None, 1, fake, 1 << 20, None) == lc.LC_ERR_INVALID_ARG
     assert L.lc_bench_read_sweep(None, 1 << 20, fake, 2048, None) == lc.LC_ERR_INVALID_ARG
     assert L.lc_bench_read_sweep(fake, 100, fake, 2048, None) == lc.LC_ERR_INVALID_ARG          # not a multiple of 16
     assert L.lc_bench_read_sweep(ctypes.c_void_p(0x10008), 1 << 20, fake, 2048, None) == lc.LC_ERR_INVALID_ARG
