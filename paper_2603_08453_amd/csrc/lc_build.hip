@@ -1845,7 +1845,7 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, LcNodeArg
 // What a wavefront works out for others it takes from the missing words by its workgroup's number, so that those that wait share
 // it.  Re-clustering with half of each head's workgroups in a second launch, us when all took the first missing word after twice as many
 // looks, and now: 8 heads of 1000 points 507 and 265, of 2275 830 and 445, of 5461 2200 and 880 (all in one launch: 83, 119 and 262).
-// On a device that is shared (8 heads of 2275 points, two small levels fewer than above, us a build with two kernels an iteration and now):
+// On a device that is shared (8 heads of 2275 points, an index of two levels, us a build with two kernels an iteration and now):
 // alone 177 and 134; with another build at the same time 228 and 222 for both, with two 300 and 576 for the three (948 when all took the first
 // missing word); beside eight decode steps 203 and 232, beside 4096^3 matrix products 963 and 508, beside copies of a gigabyte 331 and 490.
 // A cluster that has lost its members keeps its centroid: the one of an earlier iteration's plane, all of which the workgroup has seen (LcPlanes).
@@ -2150,7 +2150,7 @@ lc_kmeans_rounds_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
     __shared__ int fresh[LC_AS_RES];              // iteration that starts with a new centroid of this cluster
     __shared__ LcPlanes<LC_AS_RES> planes;        // plane of the centroid that is in `rows`
     __shared__ int moved;                         // last iteration that moved a point
-    constexpr int BITS = NBLK <= 10 && NBLK > 4 ? 512 : 2048;
+    constexpr int BITS = NBLK <= 10 && NBLK > 8 ? 512 : 2048;
     __shared__ unsigned long long bits[BITS];     // [mine][blocks] members of this workgroup's clusters, a bit per point
     __shared__ signed char mine_of[LC_AS_RES];    // which of this workgroup's clusters this is, or -1
     const int bh = share & 0xff, BH = ix.B * ix.H;
@@ -2725,12 +2725,19 @@ int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const i
                 launch(kernel, first);
                 launch(kernel, rest);
             };
-            if (l == 0 && maxK <= 64) run(&lc_kmeans_rounds_kernel<4, false>);
-            else if (l == 0 && maxK <= 160) run(&lc_kmeans_rounds_kernel<10, false>);
-            else if (l == 0) run(&lc_kmeans_rounds_kernel<16, false>);
-            else if (maxK <= 64) run(&lc_kmeans_rounds_kernel<4, true>);
-            else if (maxK <= 160) run(&lc_kmeans_rounds_kernel<10, true>);
-            else run(&lc_kmeans_rounds_kernel<16, true>);
+            // Absent centroids of an instance's blocks are multiplied too, which is what a point's wavefront takes longest for.  Re-clustering with
+            // two kernels an iteration, blocks for 160 clusters, and these, us: 2400 points in 67 136, 156 and 127; 2 heads of 2800 in 70
+            // 140, 170 and 137; 4 of 3200 in 67 150, 176 and 143; 8 of 3200 in 80 167, 181 and 148.
+            auto run_blocks = [&](auto blocks) {
+                if (l == 0) run(&lc_kmeans_rounds_kernel<decltype(blocks)::value, false>);
+                else run(&lc_kmeans_rounds_kernel<decltype(blocks)::value, true>);
+            };
+            if (maxK <= 64) run_blocks(std::integral_constant<int, 4>());
+            else if (maxK <= 96) run_blocks(std::integral_constant<int, 6>());
+            else if (maxK <= 128) run_blocks(std::integral_constant<int, 8>());
+            else if (maxK <= 160) run_blocks(std::integral_constant<int, 10>());
+            else if (maxK <= 208) run_blocks(std::integral_constant<int, 13>());
+            else run_blocks(std::integral_constant<int, 16>());
             LC_HIP_CHECK(hipGetLastError());
             cur = next;
             continue;
