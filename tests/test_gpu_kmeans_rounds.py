@@ -23,7 +23,7 @@ class Build:
                 self.K[b, :, : bd[min(same, len(bd) - 1)]] = self.K[b, :, :1].clone()
         config = dict(levels=levels, fanout=F, max_chunks=max(chunks), max_tokens=max(T, 1), **config)
         self.cfg = lc.lc_config_default(kmeans_iters=iters, **config)
-        many = lc.lc_config_default(kmeans_iters=17, **config)   # more iterations than are posted: the workspace without room for them
+        many = lc.lc_config_default(kmeans_iters=17, decode_splits=1, **config)   # more iterations than are posted: a build's workspace, no room behind it
         self.room = lc.lc_workspace_bytes(self.cfg, self.B, H, H), lc.lc_workspace_bytes(many, self.B, H, H)
         assert self.room[0] > self.room[1]
         self.ib = torch.zeros(lc.lc_index_bytes(self.cfg, self.B, H), dtype=torch.uint8, device="cuda")
@@ -32,6 +32,10 @@ class Build:
     def run(self, posts=True):
         ws = self.ws if posts else self.ws[: self.room[1]]
         self.idx = self.lc.lc_build_index(self.cfg, self.K, [int(b[-1]) for b in self.bounds], self.bounds, self.ib, ws)
+
+    def posted(self):
+        """Whether anything has been written where the workgroups of a clustering post, since the workspace was filled: the one kernel has run."""
+        return bool((self.ws[self.room[1]:] != 0xA5).any())
 
     def blob(self):
         return np.frombuffer(self.lc.lc_index_export(self.idx), dtype=np.uint8).copy()
@@ -51,10 +55,12 @@ def test_same_bits_as_two_kernels_an_iteration(H, chunks, F, config):
     b = Build(H, chunks, F, seed=sum(chunks) + F, **config)
     b.run(posts=False)
     want = b.blob()
+    assert not b.posted()
     for _ in range(2):                                       # (the second one finds the first one's posts in the workspace)
         b.ib.zero_()
         b.run()
         assert np.array_equal(b.blob(), want)
+        assert b.posted()
 
 
 # Workgroups in proportion to a sequence's points: pairs that share the XCDs evenly and ones that do not, sequences without points and
@@ -74,6 +80,7 @@ def test_two_builds_at_the_same_time():
     for b in builds:
         b.run(posts=False)
         want.append(b.blob())
+        assert not b.posted()
     streams = [torch.cuda.Stream() for _ in builds]
     torch.cuda.synchronize()
     for _ in range(3):
@@ -82,7 +89,7 @@ def test_two_builds_at_the_same_time():
                 b.run()
     torch.cuda.synchronize()
     for b, w in zip(builds, want):
-        assert np.array_equal(b.blob(), w)
+        assert np.array_equal(b.blob(), w) and b.posted()
 
 
 @pytest.mark.parametrize("H,chunks,F,config,first", [
@@ -98,7 +105,7 @@ def test_short_of_workgroups(H, chunks, F, config, first):
     for parts in first:
         b.ws.fill_(0xA5)
         b.lc.lc_bench_recluster_in_two(b.idx, parts, b.ws)
-        assert np.array_equal(b.blob(), want), parts
+        assert np.array_equal(b.blob(), want) and b.posted(), parts
 
 
 def test_missing_work_is_shared():
