@@ -2632,15 +2632,23 @@ int lay_out_shares(const lc_index* idx, int l, LcShares* s) {
 }
 
 // Whether a level of n points and k clusters is clustered by lc_kmeans_rounds_kernel, and what that posts, in the workspace's place for it.
-// Measured as whole builds of two levels over 1 to 128 pairs, 240 to 8000 points and 4 to 128 members a cluster, the time with it in parts of that
-// with two kernels an iteration (which have no members' bits for over 4096 points): 8 pairs 0.40 to 0.95, 0.60 to 0.98 from 4000 points on; 24
-// 0.48 to 0.99; 48 0.56 to 0.98; 72 0.58 to 0.99; 128 0.63 to 0.98.  Not so, and left to the two kernels: few pairs with more than 100
-// members a cluster, one wavefront's work (1.01 to 1.05); pairs that leave a fifth of the compute units without a workgroup and have more than 256 points
-// to each (96 pairs of 1000 to 4000 points 0.92 to 1.18; of 500 0.75 to 1.02); more than 100 clusters to a workgroup (128 pairs of 1000 in 250: 1.04).
+// Measured as whole builds of two levels with random keys, 1 to 128 pairs, 300 to 8192 points, 2 to 4000 members a cluster (2200 shapes), the time with
+// it in parts of that with two kernels an iteration, which have no members' bits for over 4096 points: up to 4096 points 0.43 to 1.04, median 0.87;
+// beyond 0.56 to 1.01, median 0.82.  Not so, and left to the two kernels:
+// - a cluster is one wavefront's work, 16 groups' or a whole workgroup's with the two.  Fewer than 24 pairs with more than 64 members a cluster 0.95 to
+//   1.06 (at 64 0.87 to 1.02); 24 and more with more than 128 members 0.90 to 1.49 (at 128 0.90 to 1.00); over 4096 points, more than
+//   256 members 0.89 to 1.94 (at 256 0.86 to 1.01);
+// - up to 4 pairs of 3400 to 4096 points, where the two kernels have workgroups enough as well: 0.93 to 1.10;
+// - pairs that leave a fifth of the compute units without a workgroup and have more than 256 points to each: 96 of 1000 to 4000 points 0.92 to
+//   1.18 (of 500 0.75 to 1.02); that leave an eighth, of over 2048 points in more than 160: 72 and 104 pairs 0.91 to 1.06;
+// - more than 100 clusters to a workgroup: 128 pairs of 1000 points in 250 1.04.
 bool lay_out_rounds(const LcWs& ws, long long BH, int n, int k, int iters, LcRounds* r) {
     if (iters < 1 || iters > LC_RK_MAX_ITERS || n > LC_RK_MAX_N || BH > LC_RK_MAX_PAIRS) return false;
-    const int share = rounds_share(BH);
-    if (n <= 4096 && ((BH < 24 && n > 100 * k) || (BH > 4 && BH * share * 5 < LC_COMPUTE_UNITS * 4 && n > 256 * share) || k > 100 * share)) return false;
+    const int share = rounds_share(BH), groups = (int)BH * share;
+    if (n > (n > 4096 ? 256 : BH < 24 ? 64 : 128) * k) return false;
+    if (n <= 4096 && ((BH <= 4 && n > 3400) || k > 100 * share ||
+                      (BH > 4 && groups * 5 < LC_COMPUTE_UNITS * 4 && n > 256 * share) ||
+                      (BH > 4 && groups * 8 < LC_COMPUTE_UNITS * 7 && n > 2048 && k > 160))) return false;
     r->k = k;
     r->words = (n + 15) / 16 * 8;
     const long long plane = BH * k * LC_D * 4, row_bytes = (iters + 1) * plane, label_bytes = iters * BH * r->words * 4;

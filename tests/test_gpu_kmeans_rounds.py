@@ -43,14 +43,14 @@ class Build:
 
 @pytest.mark.parametrize("H,chunks,F,config", [
     (1, [225], 15, {}), (8, [225, 1, 16, 17], 4, {}), (2, [1024, 1023], 16, {}), (2, [1025, 3], 16, {}),          # 64 clusters and 65
-    (1, [2560], 16, {}), (1, [2561, 7], 16, {}), (4, [4096], 16, {}), (1, [255], 1, {}),                          # 160 and 161; 256
+    (1, [2560], 16, {}), (1, [2561, 7], 16, {}), (8, [4096], 16, {}), (1, [255], 1, {}),                          # 160 and 161; 256
     (3, [500, 499, 64], 8, {"iters": 1}), (3, [513, 65], 8, {"iters": 2}), (2, [700], 10, {"iters": 16}),
     (8, [4097], 17, {}), (2, [8192, 15], 32, {}), (8, [5300, 700], 25, {}),                                       # more than one window of points
-    (128, [300], 8, {}), (1, [6000], 2000, {}), (5, [900], 9, {}), (11, [450, 0, 31], 9, {}),                # shares of 2, 64, 51 and 7
+    (128, [300], 8, {}), (1, [6000], 250, {}), (5, [900], 9, {}), (11, [450, 0, 31], 9, {}),                # shares of 2, 64, 51 and 7
     (2, [1500], 12, {"geometry": 1}), (2, [1500], 12, {"center_dtype": 1}), (2, [1200], 12, {"levels": 4}),
     (2, [700], 10, {"same": 400}), (2, [9000], 2, {"levels": 3, "fanouts": [0, 2, 20]}),
     (2, [1152, 1140], 12, {}), (3, [1164], 12, {}), (2, [1664], 13, {}), (8, [1665, 40], 13, {}), (2, [2080, 900], 10, {}), (5, [2081], 10, {}),   # 96 and 97; 128, 129; 208, 209
-    (1, [700, 90], 10, {"same": 650}), (2, [1100, 1], 10, {"same": 1000}), (2, [8000], 2, {"levels": 3, "fanouts": [0, 2, 20], "iters": 4})])   # (each a few labels only)
+    (1, [700, 90], 10, {"same": 650}), (2, [1100, 1], 10, {"same": 1000}), (2, [6600], 2, {"levels": 3, "fanouts": [0, 2, 20], "iters": 4})])   # (each a few labels only)
 def test_same_bits_as_two_kernels_an_iteration(H, chunks, F, config):
     b = Build(H, chunks, F, seed=sum(chunks) + F, **config)
     b.run(posts=False)
@@ -148,3 +148,15 @@ def test_one_kernel_is_no_slower(H, chunks, F):
     b.run()
     one, two = us(lambda: b.lc.lc_recluster(b.idx, b.ws)), us(lambda: b.lc.lc_recluster(b.idx, b.ws[: b.room[1]]))
     assert one < 1.09 * two, (one, two)
+
+
+# Members a cluster, few pairs, workgroups that do not divide the device: on the lines of the rule and just beyond them.
+@pytest.mark.parametrize("H,chunks,F,one", [
+    (8, 640, 64, True), (8, 650, 65, False), (24, 1280, 128, True), (24, 1290, 129, False), (2, 5120, 256, True), (2, 5140, 257, False),
+    (1, 6000, 2000, False), (32, 2000, 500, False), (8, 8192, 4000, False), (16, 600, 400, False),
+    (4, 3400, 40, True), (4, 3401, 40, False), (5, 4096, 40, True), (4, 4097, 40, True), (96, 512, 16, True), (96, 520, 16, False),
+    (72, 2048, 12, True), (72, 2060, 12, False), (72, 2060, 13, True), (128, 600, 3, True), (128, 603, 3, False)])
+def test_shapes_left_to_two_kernels_an_iteration(H, chunks, F, one):
+    b = Build(8 if H % 8 == 0 else H, [chunks] * max(1, H // 8), F, iters=2) if H >= 8 else Build(H, [chunks], F, iters=2)
+    b.run()
+    assert b.posted() == one
