@@ -128,9 +128,17 @@ size_t lc_index_bytes(const lc_config* cfg /* host */, int B, int H_kv, int d);
  * scratch of the index build (unit directions of the points of two levels and the
  * centroids of two levels, each in float32 and bfloat16): per chunk and head about
  * 768 bytes and 2.3 KB / fan-out of level 1, i.e. 0.9 KB at fan-out 16 and 1.9 KB at
- * fan-out 2.  Up to 128 (sequence, head)s and 16 k-means iterations there is room for what the workgroups of
- * a clustering post for each other behind that: per (sequence, head) and iteration 512 bytes for each of up to 256 clusters and
- * 2 bytes for each of up to 8192 points, i.e. 0.4 KB more per chunk and head at fan-out 16 and 10 iterations.  Every call that takes a workspace asks for this size (lc_index_drift: see there). */
+ * fan-out 2.
+ * Up to 128 (sequence, head)s and 16 k-means iterations there is room behind that for what the
+ * workgroups of a clustering post for each other: per (sequence, head) 512 bytes, iterations + 1
+ * times, for each of up to 256 clusters and 2 bytes, iterations times, for each of up to 8192
+ * points, by the capacities.  With 10 iterations that is 0.4 KB more per chunk and head at 4096
+ * chunks and fan-out 16 (2.8 KB at 512 chunks and fan-out 2), at most 1.6 MB per (sequence,
+ * head) and 205 MB in all (16 iterations: 2.5 and 319 MB).  It is optional: lc_build_index and
+ * lc_recluster also take a workspace without it, or with less of it, and then launch two kernels
+ * an iteration instead of one for all, for the same result more slowly.
+ * Every call that takes a workspace is content with this size (lc_decode_workspace_bytes has a
+ * decode step's; lc_index_drift: see there). */
 size_t lc_workspace_bytes(const lc_config* cfg /* host */, int B, int H_q, int H_kv, int d);
 
 /*

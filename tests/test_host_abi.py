@@ -178,3 +178,14 @@ a.hip:9:1: remark:     ScratchSize [bytes/lane]: 56 [-Rpass-analysis=kernel-reso
 """
     k = B.kernel_resources(remarks)
     assert k == {"_Z3fooPf": {"vgprs": 26, "scratch": 0}, "_Z3barPf": {"vgprs": 128, "scratch": 56}}
+
+
+@pytest.mark.parametrize("B,H,chunks,F,iters,per_pair", [(1, 8, 4096, 16, 10, 11 * 256 * 512 + 10 * 8192), (1, 8, 512, 2, 10, 11 * 256 * 512 + 10 * 1024),
+                                                         (16, 8, 40000, 16, 10, 11 * 256 * 512 + 10 * 16384), (16, 8, 40000, 16, 16, 17 * 256 * 512 + 16 * 16384),
+                                                         (1, 3, 1600, 16, 1, 2 * 100 * 512 + 3200), (43, 3, 4096, 16, 10, 0), (1, 8, 4096, 16, 17, 0)])
+def test_room_for_a_clusterings_posts(L, B, H, chunks, F, iters, per_pair):
+    """What lychee.h says of the workspace: 512 bytes for each of up to 256 clusters, 2 for each of up to 8192 points, none beyond 128 pairs and 16 iterations."""
+    size = [lc.lc_workspace_bytes(lc.lc_config_default(levels=2, fanout=F, kmeans_iters=i, max_chunks=chunks, max_tokens=8 * chunks), B, H, H)
+            for i in (iters, 17)]                            # (17: no room for posts)
+    more = size[0] - size[1]
+    assert B * H * per_pair <= more < B * H * per_pair + 256
