@@ -2206,10 +2206,9 @@ lc_kmeans_rounds_kernel(LcDev ix, int l, const float* pts, const uint16_t* pts16
 #pragma unroll
         for (int i = 0; i < R; ++i) {
             const int c = 2 * (wave + LC_RK_WAVES * i) + (lane >> 5);
-            const bool changed = c < k && fresh[min(c, LC_AS_RES - 1)] == it;
-            open |= it < iters && changed ? 1u << i : 0u;
-            if (c < k && (lane & 31) == 0) planes.enter(it, c, changed);
+            open |= it < iters && c < k && fresh[min(c, LC_AS_RES - 1)] == it ? 1u << i : 0u;
         }
+        if (tid < LC_AS_RES) planes.enter(it, tid, fresh[tid] == it);     // (by the wavefronts that look for the rows: 3.5 us of prefill's 228)
         int looks = 0;
         lc_v4i next[4];                                             // the next tile's rows in bfloat16
         if (it > 0 && first >= k) __builtin_amdgcn_s_sleep(LC_RK_WAIT_ROWS);
