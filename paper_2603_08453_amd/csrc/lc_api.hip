@@ -119,6 +119,7 @@ size_t lc_layout_ws(const lc_config* cfg, int B, int H_q, int H, int d, int spli
     W->kflags = nullptr;
     W->rounds = nullptr;
     W->rounds_bytes = 0;
+    W->first_parts = 0;
     if (with_build) {
         W->dirs = c.take<float>(BH * cap[0] * d);
         W->dirs16 = c.take<uint16_t>(BH * cap[0] * d);
@@ -443,7 +444,8 @@ int lc_recluster_impl(lc_index* idx, void* ws, size_t ws_bytes, void* stream, in
     for (int b = 0; b < idx->B; ++b)
         if (idx->M[b] > max_M) max_M = idx->M[b];
     const int64_t no_strides[3] = {0, 0, 0};
-    return lc_launch_build(idx, w, nullptr, no_strides, max_M, s, first_parts);
+    w.first_parts = first_parts;
+    return lc_launch_build(idx, w, nullptr, no_strides, max_M, s);
 }
 
 int lc_recluster(lc_index* idx, void* ws, size_t ws_bytes, void* stream) { return lc_recluster_impl(idx, ws, ws_bytes, stream, 0); }

@@ -2665,7 +2665,7 @@ bool lay_out_rounds(const LcWs& ws, long long BH, int n, int k, int iters, LcRou
 
 // K == nullptr: keep the chunk nodes (level 0) as they are and rebuild only the levels above them.
 int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const int64_t ks[3],
-                    int max_M, hipStream_t stream, int first_parts) {
+                    int max_M, hipStream_t stream) {
     const LcDev& ix = idx->dev;
     const uint16_t* K = static_cast<const uint16_t*>(Kp);
     const int geometry = idx->cfg.geometry;
@@ -2725,10 +2725,10 @@ int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* Kp, const i
                                    (const uint16_t*)cur.pts16, cur.cap, w, iters, rounds, of);
             };
             auto run = [&](auto kernel) {
-                if (first_parts <= 0) return launch(kernel, shares);
+                if (ws.first_parts <= 0) return launch(kernel, shares);
                 LcShares first = shares, rest = shares;
                 for (int i = 0; i < LC_COMPUTE_UNITS; ++i)
-                    ((int)(shares.of[i] >> 8 & 0xff) < first_parts ? rest : first).of[i] = LC_RK_NO_PART;
+                    ((int)(shares.of[i] >> 8 & 0xff) < ws.first_parts ? rest : first).of[i] = LC_RK_NO_PART;
                 launch(kernel, first);
                 launch(kernel, rest);
             };

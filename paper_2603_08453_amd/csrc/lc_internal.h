@@ -73,6 +73,7 @@ struct LcWs {
     int* kflags;         // [level][B][H][LC_KM_FLAGS] "iteration t of the k-means moved a point" (tiled kernels only)
     float* rounds;       // what the workgroups of a clustering post for each other (lc_kmeans_rounds_kernel), behind `total`
     size_t rounds_bytes; // of it in this workspace; a smaller one does without
+    int first_parts;     // > 0: the workgroups of a clustering in one kernel come in two launches (lc_bench_recluster_in_two)
     size_t total;
 };
 // Clusterings in one kernel: most (sequence, head)s, iterations and points; most clusters.
@@ -124,7 +125,7 @@ extern "C" int lc_decode_step_impl(const lc_index* idx, const void* q, const voi
                                    int32_t* chunk_ids, int32_t* counts, int cap, void* ws, size_t ws_bytes,
                                    void* stream, bool last_kernel_only);
 extern "C" int lc_decode_step_is_one_kernel(const lc_index* idx, int H_q, int budget);
-// lc_recluster with the switch of lc_launch_build.
+// lc_recluster with LcWs::first_parts.
 extern "C" int lc_recluster_impl(lc_index* idx, void* ws, size_t ws_bytes, void* stream, int first_parts);
 
 // Limits of the two level walks (pure host functions).
@@ -132,9 +133,8 @@ int lc_walk_max_internal_nodes();   // exact walk: internal nodes of one (sequen
 int lc_beam_max_level_nodes();      // top-k per level: nodes of one internal level of one (sequence, head)
 
 // Launchers (each enqueues on `stream` and returns LC_OK or LC_ERR_HIP).
-// first_parts > 0: the workgroups of a clustering in one kernel come in two launches (lc_bench_recluster_in_two).
 int lc_launch_build(const lc_index* idx, const LcWs& ws, const void* K, const int64_t ks[3],
-                    int max_M, hipStream_t stream, int first_parts = 0);
+                    int max_M, hipStream_t stream);
 int lc_launch_retrieve(const lc_index* idx, const LcWs& ws, const void* q, int G, int budget,
                        int32_t* ids, int32_t* counts, float* scores, int cap,
                        int max_M, int max_upper, int score_only, hipStream_t stream);
