@@ -1586,8 +1586,8 @@ struct LcMembers {
 // added in ascending order; a cluster without members or with a zero sum keeps its centroid).
 // What bounds an iteration is a chain: 32 dependent matrix instructions for each tile of a SIMD (2.2 us for the three of 143 points), two barriers, and
 // the longest cluster's members one after the other, 16 rows in flight.  Up to 16 clusters (WIDE) a wavefront lists its cluster's members itself; beyond
-// that all wavefronts make one list, between two more barriers (with it for 143 points into 9 clusters too, prefill of 128K tokens on one machine: 226.8
-// us, now 222.8).
+// that all wavefronts make one list, between two more barriers.  With it for 143 points into 9 clusters too, and the one cluster of the 9 looked up
+// for each of them, prefill of 128K tokens on one machine took 226.8 us, now 222.8 (the look-up alone 2.2 of it).
 // The nodes themselves follow in the same kernel: the members' lists are in LDS, and a launch and its first round trips are worth more than
 // the compute units that a workgroup per node would have.  143 nodes into 9 and 9 into 1: 27.6 and 6.5 us and
 // 5.7 for each's nodes in a kernel of their own, 31.8 and 8.9 together (and two launches less); prefill of 128K tokens 288 us, now 285.
