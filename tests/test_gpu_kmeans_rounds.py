@@ -111,34 +111,26 @@ def test_short_of_workgroups(H, chunks, F, config, first):
 def test_missing_work_is_shared():
     """Half of the workgroups do all of an iteration's work, each a part of what is missing: with the second launch behind it 3.3 times what
     all of them take (each the whole of what is missing: 8.3 times)."""
-    import torch
     b = Build(8, [5461], 22, seed=3)
     b.run()
-    took = {}
-    for parts in (64, 16):                                   # (32 workgroups a head: all, and half)
-        for _ in range(5):
+    whole, half = us([lambda parts=parts: b.lc.lc_bench_recluster_in_two(b.idx, parts, b.ws) for parts in (64, 16)])     # (32 workgroups a head)
+    assert half < 5 * whole, (half, whole)
+
+
+def us(runs, turns=12):
+    """The shortest time of each of them, taken in turn."""
+    import torch
+    took = [[] for _ in runs]
+    for _ in range(turns):
+        for run, t in zip(runs, took):
             a, z = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
             torch.cuda.synchronize()
             a.record()
-            b.lc.lc_bench_recluster_in_two(b.idx, parts, b.ws)
+            run()
             z.record()
             torch.cuda.synchronize()
-            took.setdefault(parts, []).append(a.elapsed_time(z))
-    assert min(took[16]) < 5 * min(took[64]), took
-
-
-def us(run, runs=12):
-    import torch
-    took = []
-    for _ in range(runs):
-        a, z = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        torch.cuda.synchronize()
-        a.record()
-        run()
-        z.record()
-        torch.cuda.synchronize()
-        took.append(a.elapsed_time(z) * 1e3)
-    return min(took)
+            t.append(a.elapsed_time(z) * 1e3)
+    return [min(t) for t in took]
 
 
 # a little more than 64 clusters: 0.92 to 1.0 of the two kernels' time (and 1.14 to 1.21 when they were multiplied as 160)
@@ -146,7 +138,7 @@ def us(run, runs=12):
 def test_one_kernel_is_no_slower(H, chunks, F):
     b = Build(H, [chunks], F, seed=1)
     b.run()
-    one, two = us(lambda: b.lc.lc_recluster(b.idx, b.ws)), us(lambda: b.lc.lc_recluster(b.idx, b.ws[: b.room[1]]))
+    one, two = us([lambda ws=ws: b.lc.lc_recluster(b.idx, ws) for ws in (b.ws, b.ws[: b.room[1]])])
     assert one < 1.09 * two, (one, two)
 
 
