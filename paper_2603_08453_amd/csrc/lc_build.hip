@@ -248,6 +248,7 @@ struct LcUnposted {
 #define LC_UNPOSTED (-1)     // the bits of no label and of no number that an update makes (its not-a-numbers are the hardware's own)
 template <int NT>
 __device__ __forceinline__ void lc_clear_posts(const LcUnposted& u) {
+    if (u.n == 0) return;
     const int blocks = gridDim.x * gridDim.y * gridDim.z;
     const int per = (u.n + blocks - 1) / blocks;                    // a run of pieces for each workgroup
     const int first = (int)(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z)) * per;
@@ -1587,7 +1588,8 @@ struct LcMembers {
 // What bounds an iteration is a chain: 32 dependent matrix instructions for each tile of a SIMD (2.2 us for the three of 143 points), two barriers, and
 // the longest cluster's members one after the other, 16 rows in flight.  Up to 16 clusters (WIDE) a wavefront lists its cluster's members itself; beyond
 // that all wavefronts make one list, between two more barriers.  With it for 143 points into 9 clusters too, and the one cluster of the 9 looked up
-// for each of them, prefill of 128K tokens on one machine took 226.8 us, now 222.8 (the look-up alone 2.2 of it).
+// for each of them, prefill of 128K tokens on one machine took 226.8 us, now 222.8 (the look-up alone 2.2 of it).  Without WIDE, sequences of up
+// to 16 clusters beside a larger one still have a wavefront to a cluster: 4 of 224 to 100 points in 18 to 8 clusters 60.9 us without, now 59.7.
 // The nodes themselves follow in the same kernel: the members' lists are in LDS, and a launch and its first round trips are worth more than
 // the compute units that a workgroup per node would have.  143 nodes into 9 and 9 into 1: 27.6 and 6.5 us and
 // 5.7 for each's nodes in a kernel of their own, 31.8 and 8.9 together (and two launches less); prefill of 128K tokens 288 us, now 285.
@@ -1692,23 +1694,27 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, LcNodeArg
             if (wave < k) {
                 list_own();
                 float2 s = make_float2(0.f, 0.f);
-                for (int q = 0; q < n_own; q += 16) {               // (past the end: the batch's first row again)
-                    unsigned id[8];
-                    float2 x[16];
+                auto add = [&](auto rows, int q) LC_INLINE {        // (past the end: the batch's first row again)
+                    constexpr int E = decltype(rows)::value;
+                    unsigned id[E / 2];
+                    float2 x[E];
 #pragma unroll
-                    for (int e = 0; e < 2; ++e) {
+                    for (int e = 0; e < E / 8; ++e) {
                         const uint4 v = *reinterpret_cast<const uint4*>(own + q + 8 * e);
                         id[4 * e] = v.x; id[4 * e + 1] = v.y; id[4 * e + 2] = v.z; id[4 * e + 3] = v.w;
                     }
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) {
+                    for (int e = 0; e < E; ++e) {
                         const int i = q + e < n_own ? (int)((id[e / 2] >> (16 * (e & 1))) & 0xffffu) : (int)(id[0] & 0xffffu);
                         x[e] = *reinterpret_cast<const float2*>(X + i * LC_AS_ROW + 2 * lane);
                     }
 #pragma unroll
-                    for (int e = 0; e < 16; ++e)
+                    for (int e = 0; e < E; ++e)
                         if (q + e < n_own) { s.x += x[e].x; s.y += x[e].y; }
-                }
+                };
+                int q = 0;
+                for (; n_own - q > 8; q += 16) add(std::integral_constant<int, 16>(), q);
+                if (q < n_own) add(std::integral_constant<int, 8>(), q);
                 lc_wave_sync();                                     // (the list has been read)
                 *reinterpret_cast<float2*>(sums[wave] + 2 * lane) = s;
                 lc_wave_sync();
@@ -1754,25 +1760,45 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, LcNodeArg
         }
         __syncthreads();
         {
-            // a 16-lane group to a cluster, eight columns per lane
-            const int c = grp;                                      // (clusters past the last have no members)
+            // up to 16 clusters: a wavefront each, two columns per lane; beyond that a 16-lane group each, eight columns per lane
+            const bool wide = k <= LC_KS_THREADS / 64;
+            const int c = wide ? wave : grp;                        // (clusters past the last have no members)
             const int n = __shfl(n_c, min(c, 63)), at = __shfl(first, min(c, 63));
             float sum[8];
+            auto add_rows = [&](auto cols, int col) LC_INLINE {
+                constexpr int C = decltype(cols)::value;
 #pragma unroll
-            for (int t = 0; t < 8; ++t) sum[t] = 0.f;
-            for (int q = 0; q < n; q += 8) {
-                const uint4 id = *reinterpret_cast<const uint4*>(mem + at + q);
-                const uint32_t w[4] = {id.x, id.y, id.z, id.w};
-                float x[8][8];
+                for (int t = 0; t < 8; ++t) sum[t] = 0.f;
+                for (int q = 0; q < n; q += 8) {
+                    const uint4 id = *reinterpret_cast<const uint4*>(mem + at + q);
+                    const uint32_t w[4] = {id.x, id.y, id.z, id.w};
+                    float x[8][C];
 #pragma unroll
-                for (int e = 0; e < 8; ++e)                         // (past the end: the batch's first row again)
-                    lc_load8(X + (q + e < n ? (int)((w[e / 2] >> (16 * (e & 1))) & 0xffffu) : (int)(w[0] & 0xffffu)) * LC_AS_ROW + 8 * sub, x[e]);
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    if (q + e < n) {
-#pragma unroll
-                        for (int t = 0; t < 8; ++t) sum[t] += x[e][t];
+                    for (int e = 0; e < 8; ++e) {                   // (past the end: the batch's first row again)
+                        const int i = q + e < n ? (int)((w[e / 2] >> (16 * (e & 1))) & 0xffffu) : (int)(w[0] & 0xffffu);
+                        if constexpr (C == 8) {
+                            lc_load8(X + i * LC_AS_ROW + col, x[e]);
+                        } else {
+                            const float2 v = *reinterpret_cast<const float2*>(X + i * LC_AS_ROW + col);
+                            x[e][0] = v.x;
+                            x[e][1] = v.y;
+                        }
                     }
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        if (q + e < n) {
+#pragma unroll
+                            for (int t = 0; t < C; ++t) sum[t] += x[e][t];
+                        }
+                }
+            };
+            if (wide) {
+                add_rows(std::integral_constant<int, 2>(), 2 * lane);
+                *reinterpret_cast<float2*>(sums[wave] + 2 * lane) = make_float2(sum[0], sum[1]);
+                lc_wave_sync();
+                lc_load8(sums[wave] + 8 * sub, sum);                // (every group the same)
+            } else {
+                add_rows(std::integral_constant<int, 8>(), 8 * sub);
             }
             float n2 = 0.f;
 #pragma unroll
@@ -1782,7 +1808,7 @@ lc_kmeans_small_kernel(LcDev ix, int l, const float* pts, int pts_cap, LcNodeArg
                 const float inv = 1.0f / sqrtf(n2);
 #pragma unroll
                 for (int t = 0; t < 8; ++t) sum[t] *= inv;
-                lc_store8(cs + c * LC_AS_ROW + 8 * sub, sum);
+                if (!wide || lane < 16) lc_store8(cs + c * LC_AS_ROW + 8 * sub, sum);
             }
         }
         __syncthreads();
